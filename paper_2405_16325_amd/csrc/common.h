@@ -62,10 +62,11 @@ hipError_t launch_xl_small(const bf16_t* X, int64_t n, int64_t d_in, const bf16_
 // T[n, r] = X[n, K] * Lt[r, K]^T (dense tile kernel) for many tokens, with the k-contiguous copy Lt of L
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
                                   bf16_t* Lt, float* partial_or_null, hipStream_t s);
-// C[n, m] = sum_k B[i sbn + k sbk] * A[j sam + k sak]: any strides and extents, plain fp32 arithmetic (the
-// skinny adapter products of layers whose extents are not multiples of 64)
-hipError_t launch_plain_gemm(const bf16_t* B, int64_t sbn, int64_t sbk, const bf16_t* A, int64_t sam, int64_t sak,
-                             int64_t n, int64_t m, int64_t K, bf16_t* C, hipStream_t s);
+// C[n, m] = sum_k B(i, k) * A(j, k) for the skinny adapter products of layers whose extents are not multiples of 64:
+// an operand is k-contiguous [rows][ld] (K % 8 == 0) or k-major [K][ld] (rows % 8 == 0); m % 8 == 0.  (B k-major with A
+// k-contiguous does not occur.)
+hipError_t launch_skinny_ragged(const bf16_t* B, int64_t ldb, bool b_kmajor, const bf16_t* A, int64_t lda, bool a_kmajor,
+                                int64_t n, int64_t m, int64_t K, bf16_t* C, hipStream_t s);
 hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out,
                                int64_t d_in, bf16_t* gvals, hipStream_t s);
 // the same result from token-contiguous copies Xt [d_in][ld], dYt [d_out][ld] (ld = the pitch behind

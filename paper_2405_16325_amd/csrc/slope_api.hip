@@ -41,12 +41,12 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
 }
 
 // T[n, r] = B[n, K] A^T for the skinny products of the adapters.  a_kmajor: A is [K][r] (the factor L as
-// stored) instead of [r][K].  Whole k-steps of 64 go to the MFMA kernels, anything else to plain arithmetic.
+// stored) instead of [r][K].  Whole k-steps of 64 go to the MFMA kernels, anything else to the kernel for
+// ragged extents.
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
                           bf16_t* At_scratch, float* partial, hipStream_t s) {
     if (K % 64 != 0)
-        return a_kmajor ? launch_plain_gemm(B, K, 1, A, 1, r, n, r, K, T, s)
-                        : launch_plain_gemm(B, K, 1, A, K, 1, n, r, K, T, s);
+        return launch_skinny_ragged(B, K, false, A, a_kmajor ? r : K, a_kmajor, n, r, K, T, s);
     if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, s);
     return launch_dense_tn_plain(B, n, A, r, K, T, partial, s);
 }

@@ -728,13 +728,13 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
 
     hipError_t e;
     if (d_in % 64 != 0 || d_out % 64 != 0) {
-        // Extents that are not whole k-steps of the MFMA kernels: the in-place kernel for dW and plain
-        // arithmetic for the four skinny products (T and T2 rounded to bf16 as on the fast path).
+        // Extents that are not whole k-steps of the tile kernels: the in-place kernel for dW and the kernel for
+        // ragged extents for the four skinny products (T and T2 rounded to bf16 as on the fast path).
         if ((e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, s)) != hipSuccess) return e;
-        if ((e = launch_plain_gemm(X, d_in, 1, L, 1, r, b, r, d_in, T, s)) != hipSuccess) return e;        // T  = X L
-        if ((e = launch_plain_gemm(dY, d_out, 1, R, d_out, 1, b, r, d_out, T2, s)) != hipSuccess) return e; // T2 = dY R^T
-        if ((e = launch_plain_gemm(X, 1, d_in, T2, 1, r, d_in, r, b, dL, s)) != hipSuccess) return e;       // dL = X^T T2
-        return launch_plain_gemm(T, 1, r, dY, 1, d_out, r, d_out, b, dR, s);                               // dR = T^T dY
+        if ((e = launch_skinny_ragged(X, d_in, false, L, r, true, b, r, d_in, T, s)) != hipSuccess) return e;       // T  = X L
+        if ((e = launch_skinny_ragged(dY, d_out, false, R, d_out, false, b, r, d_out, T2, s)) != hipSuccess) return e; // T2 = dY R^T
+        if ((e = launch_skinny_ragged(X, d_in, true, T2, r, true, d_in, r, b, dL, s)) != hipSuccess) return e;      // dL = X^T T2
+        return launch_skinny_ragged(T, r, true, dY, d_out, true, r, d_out, b, dR, s);                               // dR = T^T dY
     }
     if ((e = launch_token_copies(X, d_in, Xt, dY, d_out, dYt, b, s)) != hipSuccess) return e;
     if ((e = launch_wgrad_masked_t(dYt, Xt, b, meta, d_out, d_in, gvals, tail, s)) != hipSuccess) return e;
