@@ -306,7 +306,7 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  * pin the regimes.  plan: host int32[6]
  *   [0] product: 0 small-batch kernel (one pass over the packed weight), 1 tile kernel with the
  *       contraction split into slabs (needs the workspace), 2 tile kernel, 3 generic kernel
- *       (d_in not a multiple of 256; not a multiple of 64: its form for ragged rows), 4 small-batch
+ *       (d_in not a multiple of 64, where it has a form for ragged rows, or short), 4 small-batch
  *       kernel in its row-split form (d_in a multiple of 1024 and enough weight rows, or the
  *       workspace to cut the contraction into slices)
  *   [1], [2] weight rows and tokens per workgroup      [3] slabs or slices (1 = no split)

@@ -17,7 +17,7 @@
 //
 // Three kernels here (launch_spmm picks; the forms for very few tokens are in spmm_stream.hip):
 // spmm_kernel<BM, BN> and spmm_split_kernel (the 256 x 256 tile) are the fast ones and need
-// K % 256 == 0; spmm_generic_kernel takes any K % 64 == 0 with a plain register-staged pipeline.
+// K % 64 == 0; spmm_generic_kernel takes any K % 8 == 0 with a plain register-staged pipeline.
 //
 // spmm_kernel.  What a compute unit can pull from L2 per unit of time matters as much as the matrix
 // pipe (whose clock the power management lowers well below nominal under this load), so the data
@@ -211,7 +211,30 @@ struct SpmmSmem {
 
 constexpr int SPMM_THREADS = 512;
 
-template <int BM, int BN>
+// Where a row's loads of pair `pair` (of k-steps) and quad `quad` start: byte offsets into the packed values and, for the
+// lanes that bring 16-byte half `half`, into the metadata (on top of the 16 * half the lane's address holds).  Past the
+// last k-step the last load of the row is repeated.
+template <bool TAIL>
+__device__ __forceinline__ int64_t pair_offset(int pair, int ksteps) {
+    if (TAIL) return 2 * pair + 1 < ksteps ? (int64_t)pair * 128 : ((int64_t)ksteps - 2) * 64;
+    return (int64_t)(2 * pair < ksteps ? pair : ksteps / 2 - 1) * 128;
+}
+template <bool TAIL>
+__device__ __forceinline__ int64_t quad_offset(int quad, int ksteps, int half) {
+    if (TAIL) {
+        const int64_t last = (int64_t)ksteps * 8 - 16, o = (int64_t)quad * 32;
+        const int64_t o0 = o < last ? o : last, o1 = (o + 16 < last ? o + 16 : last) - 16;
+        return half ? o1 : o0;
+    }
+    return (int64_t)(4 * quad < ksteps ? quad : ksteps / 4 - 1) * 32;
+}
+#define LAST_STEP(S4) if (TAIL && ks0 + (S4) + 1 >= ksteps) break;
+
+// TAIL: the number of k-steps is not a multiple of 4 (at least two of them).  The packed weight is fetched two k-steps at
+// a time and its metadata four, so at the end of a row those fetches would run past it.  They are moved back to end with
+// the row instead: an odd last k-step then sits where the second step of its pair (the second 8 bytes of its 16 of
+// metadata) belongs, and that is where it is read.  A template parameter, so that whole quads pay nothing for it.
+template <int BM, int BN, bool TAIL>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __restrict__ B, int n,
                                                             const bf16_t* __restrict__ Av,
                                                             const uint8_t* __restrict__ Am, int m, int K,
@@ -274,7 +297,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     // A split over k: workgroup row blockIdx.y takes k-steps [k_first, k_first + ksteps) and leaves
     // fp32 partial sums in its slab; without a slab buffer there is one row and it takes all of K.
     const int k_first = blockIdx.y * slab_steps;              // a multiple of 4
-    const int ksteps = K / 64 - k_first < slab_steps ? K / 64 - k_first : slab_steps;   // a multiple of 4
+    const int ksteps = K / 64 - k_first < slab_steps ? K / 64 - k_first : slab_steps;   // a multiple of 4 unless TAIL
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) a_src[i] += (size_t)k_first * 64;
 #pragma unroll
@@ -287,14 +310,12 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
             dma16(b_src[i] + (size_t)kc * 128, smem + S::B_OFF + stage * S::B_STAGE + (wave * B_LD + i) * 1024);
     };
     auto issue_a = [&](int pair, int buf) {                   // weight rows of k-steps 2 pair, 2 pair + 1
-        int pc = 2 * pair < ksteps ? pair : ksteps / 2 - 1;
+        const int64_t off = pair_offset<TAIL>(pair, ksteps);
 #pragma unroll
-        for (int i = 0; i < A_LD; ++i)
-            dma16(a_src[i] + (size_t)pc * 128, smem + buf * S::A_PAIR + (wave * A_LD + i) * 1024);
+        for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + off, smem + buf * S::A_PAIR + (wave * A_LD + i) * 1024);
     };
     auto issue_m = [&](int quad, int buf) {                   // metadata of k-steps 4 quad .. 4 quad + 3
-        int qc = 4 * quad < ksteps ? quad : ksteps / 4 - 1;
-        dma16(m_src + (size_t)qc * 32, m_dst0 + buf * m_dst_step);
+        dma16(m_src + quad_offset<TAIL>(quad, ksteps, (lane >> 4) & 1), m_dst0 + buf * m_dst_step);
     };
 
     f32x4 acc[MF][NF];
@@ -320,9 +341,10 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     {                                                                                                  \
         const int ks = ks0 + S4;                                                                       \
         constexpr int QUEUED = B_LD + ((S4 & 1) == 0 ? A_LD : 0) + (S4 == 0 ? 1 : 0);                  \
-        const uint8_t* pa = smem + ((S4 >> 1) & 1) * S::A_PAIR + a_rd + ((S4 & 1) ? rd1 : rd0);        \
+        const bool second = (S4 & 1) != 0 || (TAIL && ks == ksteps - 1);                               \
+        const uint8_t* pa = smem + ((S4 >> 1) & 1) * S::A_PAIR + a_rd + (second ? rd1 : rd0);          \
         const uint8_t* pb = smem + b_rd + bst * S::B_STAGE;                                            \
-        const uint8_t* pm = smem + m_rd + ((ks0 >> 2) & 1) * S::M_QUAD + (S4 >> 1) * 256 + (S4 & 1) * 8; \
+        const uint8_t* pm = smem + m_rd + ((ks0 >> 2) & 1) * S::M_QUAD + (S4 >> 1) * 256 + (second ? 8 : 0); \
         BFrag bf[NF];                                                                                  \
         AFrag af[MF];                                                                                  \
         int ai[MF];                                                                                    \
@@ -348,11 +370,15 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     }
     int bst = 0;                                              // ring stage of the current k-step
     if (group == 0) {
-        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) { SPMM_STEP(0, 0) SPMM_STEP(0, 1) SPMM_STEP(0, 2) SPMM_STEP(0, 3) }
+        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
+            SPMM_STEP(0, 0) LAST_STEP(0) SPMM_STEP(0, 1) LAST_STEP(1) SPMM_STEP(0, 2) LAST_STEP(2) SPMM_STEP(0, 3)
+        }
         wg_barrier();
     } else {
         wg_barrier();
-        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) { SPMM_STEP(1, 0) SPMM_STEP(1, 1) SPMM_STEP(1, 2) SPMM_STEP(1, 3) }
+        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
+            SPMM_STEP(1, 0) LAST_STEP(0) SPMM_STEP(1, 1) LAST_STEP(1) SPMM_STEP(1, 2) LAST_STEP(2) SPMM_STEP(1, 3)
+        }
     }
 #undef SPMM_STEP
     WAIT_HERE(waitcnt_imm(0, 15));           // drain the clamped look-ahead loads
@@ -389,7 +415,7 @@ struct SplitSmem {
 constexpr int split_even(int k) { return 2 + ((k & 1) == 0 ? 2 : 0) + ((k & 3) == 1 ? 1 : 0); }
 constexpr int split_odd(int k) { return 2 + ((k & 1) == 0 ? 2 : 0); }
 
-template <bool PREFETCH>
+template <bool PREFETCH, bool TAIL>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* __restrict__ B, int n,
                                                                   const bf16_t* __restrict__ Av,
                                                                   const uint8_t* __restrict__ Am, int m, int K,
@@ -477,7 +503,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
     const int b_rd = S::B_OFF + group * 2 * S::B_HALF + ((wn & 1) * NF) * 2048;
     const int m_rd = S::M_OFF + wm * MF * 512 + l16 * 16 + lq * 2;
 
-    const int ksteps = K / 64;                                // a multiple of 4
+    const int ksteps = K / 64;                                // a multiple of 4 unless TAIL (see spmm_kernel)
     auto issue_b = [&](int g, int ks) {                       // token half g of k-step ks (clamped)
         int kc = ks < ksteps ? ks : ksteps - 1;
         uint8_t* st = smem + S::B_OFF + (g * 2 + (ks & 1)) * S::B_HALF + (wave * 2) * 1024;
@@ -485,14 +511,14 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
         dma16(b_src[g * 2 + 1] + (size_t)kc * 128, st + 1024);
     };
     auto issue_a = [&](int half, int pair) {                  // weight rows 128 half .. +127, k-steps 2 pair, 2 pair + 1
-        int pc = 2 * pair < ksteps ? pair : ksteps / 2 - 1;
+        const int64_t off = pair_offset<TAIL>(pair, ksteps);
         uint8_t* st = smem + (pair & 1) * S::A_PAIR + (half * 16 + wave * 2) * 1024;
-        dma16(a_src[half * 2] + (size_t)pc * 128, st);
-        dma16(a_src[half * 2 + 1] + (size_t)pc * 128, st + 1024);
+        dma16(a_src[half * 2] + off, st);
+        dma16(a_src[half * 2 + 1] + off, st + 1024);
     };
     auto issue_m = [&](int quad) {                            // metadata of k-steps 4 quad .. 4 quad + 3
-        int qc = 4 * quad < ksteps ? quad : ksteps / 4 - 1;
-        dma16(m_src + (size_t)qc * 32, smem + S::M_OFF + (quad & 1) * S::M_QUAD + wave * 1024);
+        dma16(m_src + quad_offset<TAIL>(quad, ksteps, (lane >> 4) & 1),
+              smem + S::M_OFF + (quad & 1) * S::M_QUAD + wave * 1024);
     };
 
     f32x4 acc[MF][NF];
@@ -514,9 +540,10 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
         if (((S4) & 1) == 0) issue_a(1, ((k) >> 1) + 1);                                               \
     }
 #define SPLIT_READ(S4)                                                                                 \
-        const uint8_t* pa = smem + (((S4) >> 1) & 1) * S::A_PAIR + a_rd + (((S4) & 1) ? rd1 : rd0);    \
+        const bool second = ((S4) & 1) != 0 || (TAIL && ks == ksteps - 1);                             \
+        const uint8_t* pa = smem + (((S4) >> 1) & 1) * S::A_PAIR + a_rd + (second ? rd1 : rd0);        \
         const uint8_t* pb = smem + b_rd + ((S4) & 1) * S::B_HALF;                                      \
-        const uint8_t* pm = smem + m_rd + ((ks0 >> 2) & 1) * S::M_QUAD + ((S4) >> 1) * 256 + ((S4) & 1) * 8; \
+        const uint8_t* pm = smem + m_rd + ((ks0 >> 2) & 1) * S::M_QUAD + ((S4) >> 1) * 256 + (second ? 8 : 0); \
         BFrag bf[NF];                                                                                  \
         AFrag af[MF];                                                                                  \
         int ai[MF];                                                                                    \
@@ -568,13 +595,17 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
     WAIT_HERE(waitcnt_imm(4, 15));                            // metadata, A pair 0 and B0(0) have landed
     wg_barrier();
     if (group == 0) {
-        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) { SPLIT_STEP0(0) SPLIT_STEP0(1) SPLIT_STEP0(2) SPLIT_STEP0(3) }
+        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
+            SPLIT_STEP0(0) LAST_STEP(0) SPLIT_STEP0(1) LAST_STEP(1) SPLIT_STEP0(2) LAST_STEP(2) SPLIT_STEP0(3)
+        }
         wg_barrier();                                         // group 1's last compute phase
     } else {
         EVEN_LOADS(0, 0)                                      // phase 0: nothing to multiply yet
         WAIT_HERE(waitcnt_imm(split_even(0) + split_odd(3), 15));
         wg_barrier();
-        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) { SPLIT_STEP1(0) SPLIT_STEP1(1) SPLIT_STEP1(2) SPLIT_STEP1(3) }
+        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
+            SPLIT_STEP1(0) LAST_STEP(0) SPLIT_STEP1(1) LAST_STEP(1) SPLIT_STEP1(2) LAST_STEP(2) SPLIT_STEP1(3)
+        }
     }
 #undef EVEN_LOADS
 #undef ODD_LOADS
@@ -728,20 +759,28 @@ __global__ void __launch_bounds__(256) spmm_generic_kernel(const bf16_t* __restr
                                        n0);
 }
 
-template <int BM, int BN>
-hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, int nslabs = 1,
-                       int slab_steps = 0, float* slabs = nullptr) {
+template <int BM, int BN, bool TAIL>
+hipError_t launch_tile_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, int nslabs, int slab_steps,
+                          float* slabs) {
     using S = SpmmSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
-    auto kern = spmm_kernel<BM, BN>;
-    hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN>>(S::TOTAL);
+    auto kern = spmm_kernel<BM, BN, TAIL>;
+    hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL>>(S::TOTAL);
     if (e != hipSuccess) return e;
     if (!slabs) { nslabs = 1; slab_steps = (int)(K / 64); }
     kern<<<dim3((unsigned)super_grid(tiles_m, tiles_n), (unsigned)nslabs), dim3(SPMM_THREADS), S::TOTAL, s>>>(
         B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, slab_steps, slabs);
     return hipGetLastError();
+}
+
+template <int BM, int BN>
+hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, int nslabs = 1,
+                       int slab_steps = 0, float* slabs = nullptr) {
+    return K % 256 == 0 ? launch_tile_as<BM, BN, false>(B, n, Av, Am, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs)
+                        : launch_tile_as<BM, BN, true>(B, n, Av, Am, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs);
 }
 
 // C[idx] = bf16( sum over slabs, in order, of P[s][idx] ), four elements per thread
@@ -759,23 +798,27 @@ __global__ void __launch_bounds__(256) slab_reduce_kernel(const f32x4* __restric
     C[idx] = o.u;
 }
 
+template <bool PREFETCH, bool TAIL>
+hipError_t launch_split_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                           const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, int tiles_m, int tiles_n,
+                           hipStream_t s) {
+    using S = SplitSmem;
+    static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
+    hipError_t e = allow_dynamic_lds<spmm_split_kernel<PREFETCH, TAIL>>(S::TOTAL);
+    if (e != hipSuccess) return e;
+    spmm_split_kernel<PREFETCH, TAIL><<<dim3((unsigned)super_grid(tiles_m, tiles_n)), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+
 hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
                         const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
     using S = SplitSmem;
-    static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + S::BM - 1) / S::BM), tiles_n = (int)((n + S::BN - 1) / S::BN);
     const bool prefetch = wide_grid(tiles_m, tiles_n) && (size_t)n * (size_t)K * 2 > LAST_LEVEL_CACHE_BYTES;
-    hipError_t e = prefetch ? allow_dynamic_lds<spmm_split_kernel<true>>(S::TOTAL)
-                            : allow_dynamic_lds<spmm_split_kernel<false>>(S::TOTAL);
-    if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)super_grid(tiles_m, tiles_n));
-    if (prefetch)
-        spmm_split_kernel<true><<<grid, dim3(SPMM_THREADS), S::TOTAL, s>>>(B, (int)n, Av, Am, (int)m, (int)K, B2, A2,
-                                                                           (int)K2, C, tiles_m, tiles_n);
-    else
-        spmm_split_kernel<false><<<grid, dim3(SPMM_THREADS), S::TOTAL, s>>>(B, (int)n, Av, Am, (int)m, (int)K, B2, A2,
-                                                                            (int)K2, C, tiles_m, tiles_n);
-    return hipGetLastError();
+    auto launch = K % 256 == 0 ? (prefetch ? launch_split_as<true, false> : launch_split_as<false, false>)
+                               : (prefetch ? launch_split_as<true, true> : launch_split_as<false, true>);
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, tiles_m, tiles_n, s);
 }
 
 }  // namespace
@@ -787,11 +830,16 @@ hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint
 // short reduction kernel (fixed order: bit-identical runs) that rounds to bf16.
 constexpr int64_t SLAB_MAX_TOKENS = 1024;
 
+// The tile kernels take whole k-steps of 64, at least two of them (700 tokens: 4160 x 2112 54 -> 25 us, 2112 x 4160
+// 96 -> 35 us against the generic kernel).  Contractions of up to 5 k-steps that are no multiple of 256 stay with the
+// generic kernel: a ring's prologue would be most of the work.
+static bool tile_kernel_fits(int64_t K) { return K % 64 == 0 && K >= 128 && (K % 256 == 0 || K > 320); }
+
 int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
-    if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || K % 256 != 0) return 0;
+    if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || !tile_kernel_fits(K)) return 0;
     const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128);
     if (tiles >= RESIDENT) return 0;                          // the chip is full without a split (measured: slabs lose)
-    const int64_t quads = K / 256;                            // slabs are whole quads of k-steps
+    const int64_t quads = (K + 255) / 256;                    // slabs are whole quads of k-steps (the last may be shorter)
     // Estimate per slab count: the rounds of 256 workgroups, each pulling its share of the packed
     // weight at what one compute unit sustains with this tile (about 24 B/ns of weight bytes), plus
     // writing and re-reading the partial sums at HBM speed.  One slab means: not worth it.
@@ -819,7 +867,7 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
                              int64_t K, const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, float* slabs,
                              hipStream_t s) {
     const int want = spmm_slab_count(n, m, K);
-    const int64_t quads = K / 256;
+    const int64_t quads = (K + 255) / 256;
     const int slab_steps = (int)((quads + want - 1) / want) * 4;
     const int nslabs = (int)((K / 64 + slab_steps - 1) / slab_steps);       // <= want
     hipError_t e = n <= 64 ? launch_tile<256, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs)
@@ -834,7 +882,7 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel.
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 0;
-    if (K % 256 != 0) return;
+    if (!tile_kernel_fits(K)) return;
     // Few tokens (inference): the product is a single pass over the packed weight, bound by HBM.
     // Narrow token tiles, and weight tiles small enough that every compute unit streams its share.
     if (n <= 128) {

@@ -1,11 +1,51 @@
 """Kernels and dispatch branches at the sizes where they can go wrong (needs an MI355X): edges of tiles, remainders,
-the smallest and largest of a range.  Same bars as the other parity tests: integers bit for bit, products under the
-norm and element-wise bounds of tests/parity_util.py against the fp64 oracle."""
+the smallest and largest of a range.  Integers bit for bit against the oracle; products either against the fp64 oracle
+(ragged layers) or, for shapes too large for it, every element against fp32 library products on the weight masked by
+the emitted bit masks, under the element-wise bounds of tests/parity_util.py."""
 import pytest
+import torch
 
+from paper_2405_16325_amd import binding as sl
+from paper_2405_16325_amd import inputs
 from tests import test_gpu_ragged as ragged
+from tests.test_gpu_fullsize import assert_all_close, unpack_bits
 
 pytestmark = pytest.mark.gpu
+
+
+def check_layer(b, d_out, d_in, r=0, backward=True):
+    """Forward and, if asked for, the backward calls of one layer, every element against fp32 products."""
+    print(f"layer b={b} d_out={d_out} d_in={d_in} r={r}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + b + 3 * d_out + 7 * d_in + r)
+
+    def gauss(shape, std):
+        return (torch.randn(shape, generator=gen, device="cuda", dtype=torch.float32) * std).to(torch.bfloat16)
+
+    X, W, dY = gauss((b, d_in), 1.0), gauss((d_out, d_in), 0.02), gauss((b, d_out), 1e-3)
+    L, R = (gauss((d_in, r), 0.02), gauss((r, d_out), 0.02)) if r else (None, None)
+    vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    vals_t, meta_t, mask_rc = sl.slope_double_prune(vals, meta, want_mask=True)
+    keep = unpack_bits(mask)
+    w_r = torch.where(keep, W.float(), 0.0)
+    y = X.float() @ w_r.t()
+    if r:
+        y += (X.float() @ L.float()) @ R.float()
+    assert_all_close(sl.slope_spmm_fwd(X, vals, meta, L, R), y, "Y", two_stage=bool(r))
+    if not backward:
+        return
+    dx = dY.float() @ torch.where(unpack_bits(mask_rc), W.float(), 0.0)
+    assert_all_close(sl.slope_spmm_bwd_x(dY, vals_t, meta_t), dx, "dX")
+    g = (dY.float().t() @ X.float())[keep].reshape(d_out, d_in // 2)
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta), g, "dW")
+    if r:
+        u = dY.float() @ R.float().t()
+        assert_all_close(sl.slope_spmm_bwd_x_adapter(dY, vals_t, meta_t, L, R), dx + u @ L.float().t(), "dX with adapters",
+                         two_stage=True)
+        ga, dl, dr = sl.slope_wgrad_adapter(dY, X, meta, L, R)
+        assert_all_close(ga, g, "dW of the adapter call")
+        assert_all_close(dl, X.float().t() @ u, "dL", two_stage=True)
+        assert_all_close(dr, (X.float() @ L.float()).t() @ dY.float(), "dR", two_stage=True)
 
 
 # tiles of 32 x 64, eight wavefronts that take chunks of 32 k in turn: one token, one row more than a tile, less than
@@ -13,3 +53,12 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("b,d_out,d_in,r", [(1, 8, 8, 32), (33, 72, 264, 512), (257, 1000, 136, 160), (31, 136, 1000, 32)])
 def test_ragged_adapter_products(b, d_out, d_in, r):
     ragged.test_every_call_on_a_ragged_layer(b, d_out, d_in, r)
+
+
+# contractions that are multiples of 64 but not of 256: one, two and three k-steps left over, in tiles of every shape,
+# with slabs along the contraction (the last of a single k-step) and with the token prefetch of the largest tile
+@pytest.mark.parametrize("b,d_out,d_in,r", [
+    (300, 576, 448, 0), (300, 640, 704, 32), (64, 2112, 4160, 64), (700, 4160, 2112, 0), (100, 832, 8256, 0),
+    (4000, 4032, 576, 0), (4000, 4160, 640, 160), (4000, 4032, 704, 0), (16384, 2048, 8256, 0)])
+def test_contractions_with_a_remainder_of_k_steps(b, d_out, d_in, r):
+    check_layer(b, d_out, d_in, r)
