@@ -36,6 +36,7 @@ hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const u
 // the choices behind it (pure functions of the shape): tile of the tile kernels (0 x 0 = the generic kernel),
 // weight rows per workgroup of the small-batch kernel, chunks of 64 rows of L per workgroup of the X L split
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn);
+int spmm_generic_edge(int64_t n, int64_t m);                 // edge of the generic kernel's tile
 int spmm_stream_rows(int64_t n, int64_t m, int64_t K);
 int xl_subs(int64_t n, int64_t d_in, int64_t r);
 // the same product for a few dozen to a few hundred tokens, split over K with fp32 partial sums in `slabs`

@@ -450,7 +450,7 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         int bm, bn;
         spmm_tile_choice(b, d_out, d_in, bm, bn);
         if (slabs > 0) { plan[0] = 1; plan[1] = 256; plan[2] = b <= 64 ? 64 : 128; plan[3] = slabs; }
-        else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = 128; }
+        else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = spmm_generic_edge(b, d_out); }
         else { plan[0] = 2; plan[1] = bm; plan[2] = bn; }
     }
     if (r > 0) {

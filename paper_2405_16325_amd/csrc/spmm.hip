@@ -639,28 +639,30 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 // values, 16 bytes of tokens, 1 byte of metadata), each either wholly inside the row or replaced: zeros for
 // values and tokens, the nibble pair 0x44 (positions 0, 1: a legal encoding) for metadata, so the tail contributes
 // exact zeros.
-template <int F, int G>
+enum { GEN_WHOLE = 0, GEN_PARTIAL = 1, GEN_RAGGED = 2 };      // K % 128 == 0; whole k-steps (K % 64 == 0); any K % 8 == 0
+template <int FM, int FN, int G>
 struct GenSmem {
-    static constexpr int BT = 32 * F;                         // tile edge
-    static constexpr int A_BYTES = BT * 128, B_STEP = BT * 128, M_BYTES = BT * 16;
+    static constexpr int BM = 32 * FM, BN = 32 * FN;          // the tile
+    static constexpr int A_BYTES = BM * 128, B_STEP = BN * 128, M_BYTES = BM * 16;
     static constexpr int M_OFF = A_BYTES + 2 * B_STEP;
     static constexpr int STAGE = M_OFF + M_BYTES;
-    static constexpr int SUM_PITCH = BT + 4;                  // floats per token row of a partial tile
-    static constexpr int SUMS = G > 1 ? G * BT * SUM_PITCH * 4 : 0;
+    static constexpr int SUM_PITCH = BM + 4;                  // floats per token row of a partial tile
+    static constexpr int SUM_PASSES = G * BN * SUM_PITCH * 4 > 160 * 1024 ? 2 : 1;   // token halves of partial tiles at a time
+    static constexpr int SUMS = G > 1 ? G * BN / SUM_PASSES * SUM_PITCH * 4 : 0;
     static constexpr int TOTAL = G * STAGE > SUMS ? G * STAGE : SUMS;
 };
 
-template <bool RAGGED, int F, int G>
+template <int FORM, int FM, int FN, int G>
 __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __restrict__ B, int n,
                                                            const bf16_t* __restrict__ Av,
                                                            const uint8_t* __restrict__ Am, int m, int K,
                                                            const bf16_t* __restrict__ B2,
                                                            const bf16_t* __restrict__ A2, int K2,
                                                            bf16_t* __restrict__ C, int tiles_m) {
-    using S = GenSmem<F, G>;
-    constexpr int MF = F, NF = F, A_LD = F, B_LD = 2 * F;     // 16-byte pieces per lane and pair
+    using S = GenSmem<FM, FN, G>;
+    constexpr int MF = FM, NF = FN, A_LD = FM, B_LD = 2 * FN;     // 16-byte pieces per lane and pair
     __shared__ __align__(16) uint8_t smem[S::TOTAL];
-    const int m0 = (blockIdx.x % tiles_m) * S::BT, n0 = (blockIdx.x / tiles_m) * S::BT;
+    const int m0 = (blockIdx.x % tiles_m) * S::BM, n0 = (blockIdx.x / tiles_m) * S::BN;
     const int group = (int)threadIdx.x >> 8;
     const int t = threadIdx.x & 255, lane = t & 63, wave = t >> 6;   // inside the group
     uint8_t* const stage = smem + group * S::STAGE;
@@ -670,20 +672,19 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
     // (t + 256 u) / 16, k-step (t % 16) / 8, chunk t % 8
     const uint8_t* a_src[A_LD];
     const bf16_t* b_src[B_LD];
-    int a_dst[A_LD], b_dst[B_LD];
+    const int a_dst = (t >> 3) * 128 + (((t & 7) ^ ((t >> 4) & 7)) * 16);   // piece i: 32 rows further on
+    const int b_dst = S::A_BYTES + ((t >> 3) & 1) * S::B_STEP + (t >> 4) * 128 + (((t & 7) ^ ((t >> 5) & 7)) * 16);   // 16 rows
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
         const int rl = (t + 256 * i) >> 3;
         a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (t & 7) * 16;
-        a_dst[i] = rl * 128 + (((t & 7) ^ ((rl >> 1) & 7)) * 16);
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
         const int rl = (t + 256 * i) >> 4;
         b_src[i] = B + (size_t)wrap_row(n0 + rl, n) * K + (t & 15) * 8;
-        b_dst[i] = S::A_BYTES + ((t >> 3) & 1) * S::B_STEP + rl * 128 + (((t & 7) ^ ((rl >> 1) & 7)) * 16);
     }
-    const int mrow = t % S::BT;
+    const int mrow = t % S::BM;
     const uint8_t* const m_src = Am + (size_t)wrap_row(m0 + mrow, m) * (K / 8);
     f32x4 acc[MF][NF];
 #pragma unroll
@@ -694,15 +695,15 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
     u32x4 a_reg[A_LD], b_reg[B_LD], m_reg;
     auto load = [&](int p) {                                  // pair p (uniform, inside the contraction at least in part)
         const int k0 = p * 128;
-        if (k0 + 128 <= K) {
+        if (FORM == GEN_WHOLE || k0 + 128 <= K) {
 #pragma unroll
             for (int i = 0; i < A_LD; ++i) {
-                if (RAGGED) a_reg[i] = *(const u32x4_a8*)(a_src[i] + k0);
+                if (FORM == GEN_RAGGED) a_reg[i] = *(const u32x4_a8*)(a_src[i] + k0);
                 else a_reg[i] = *(const u32x4*)(a_src[i] + k0);
             }
 #pragma unroll
             for (int i = 0; i < B_LD; ++i) b_reg[i] = *(const u32x4*)(b_src[i] + k0);
-            if (t < S::BT) __builtin_memcpy(&m_reg, m_src + p * 16, 16);
+            if (t < S::BM) __builtin_memcpy(&m_reg, m_src + p * 16, 16);
             return;
         }
         const int ak = k0 + (t & 7) * 16, bk = k0 + (t & 15) * 8;
@@ -735,10 +736,10 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
         const int p = tr * G + group;
         if (tr > 0) __syncthreads();                          // everybody has read the last pair
 #pragma unroll
-        for (int i = 0; i < A_LD; ++i) *(u32x4*)(stage + a_dst[i]) = a_reg[i];
+        for (int i = 0; i < A_LD; ++i) *(u32x4*)(stage + a_dst + i * 4096) = a_reg[i];
 #pragma unroll
-        for (int i = 0; i < B_LD; ++i) *(u32x4*)(stage + b_dst[i]) = b_reg[i];
-        if (t < S::BT) *(u32x4*)(stage + S::M_OFF + t * 16) = m_reg;
+        for (int i = 0; i < B_LD; ++i) *(u32x4*)(stage + b_dst + i * 2048) = b_reg[i];
+        if (t < S::BM) *(u32x4*)(stage + S::M_OFF + t * 16) = m_reg;
         if (p + G < pairs) load(p + G);
         __syncthreads();
         if (p >= pairs) continue;                             // uniform per wavefront (the barriers are above)
@@ -766,8 +767,8 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
     }
     __syncthreads();                                          // the stages are free
     if constexpr (G == 1) {
-        static_assert(S::BT * (S::BT * 2 + 16) <= S::TOTAL, "the staged output tile fits in the stages");
-        extend_and_store<MF, NF, S::BT, S::BT, 256>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2, K2, C,
+        static_assert(S::BN * (S::BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the stages");
+        extend_and_store<MF, NF, S::BM, S::BN, 256>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2, K2, C,
                                                     smem, m0, n0);
     } else {
         // adapter extension from global memory, its steps of 32 dealt to the groups (A2 k-contiguous or k-major)
@@ -795,52 +796,63 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
                 for (int j = 0; j < NF; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[i].v, b2[j].v, acc[i][j], 0, 0, 0);
         }
-        float* const part = (float*)smem;                     // [group][token][SUM_PITCH]; the rings are idle
+        // a pass: every wavefront's fragments j0 .. j0 + NP - 1, [group][token][SUM_PITCH]; the stages are idle
+        float* const part = (float*)smem;
+        constexpr int NP = NF / S::SUM_PASSES, ROWS = S::BN / S::SUM_PASSES;
 #pragma unroll
-        for (int i = 0; i < MF; ++i)
+        for (int j0 = 0; j0 < NF; j0 += NP) {
+            if (j0 > 0) __syncthreads();
 #pragma unroll
-            for (int j = 0; j < NF; ++j)
-                *(f32x4*)(part + ((group * S::BT + (wn * NF + j) * 16 + l16) * S::SUM_PITCH + (wm * MF + i) * 16 + lq * 4)) =
-                    acc[i][j];
-        __syncthreads();
-        for (int idx = (int)threadIdx.x; idx < S::BT * S::BT / 4; idx += 256 * G) {
-            const int tok = idx / (S::BT / 4), col = (idx % (S::BT / 4)) * 4;
-            f32x4 v = *(const f32x4*)(part + tok * S::SUM_PITCH + col);
+            for (int i = 0; i < MF; ++i)
 #pragma unroll
-            for (int q = 1; q < G; ++q) {
-                const f32x4 x = *(const f32x4*)(part + (q * S::BT + tok) * S::SUM_PITCH + col);
-                v[0] += x[0]; v[1] += x[1]; v[2] += x[2]; v[3] += x[3];
-            }
-            if (n0 + tok < n && m0 + col < m) {               // m % 8 == 0
-                union { __bf16 h[4]; u32x2 u; } o;
+                for (int j = 0; j < NP; ++j)
+                    *(f32x4*)(part + ((group * ROWS + (wn * NP + j) * 16 + l16) * S::SUM_PITCH + (wm * MF + i) * 16 + lq * 4)) =
+                        acc[i][j0 + j];
+            __syncthreads();
+            for (int idx = (int)threadIdx.x; idx < S::BM * ROWS / 4; idx += 256 * G) {
+                const int row = idx / (S::BM / 4), col = (idx % (S::BM / 4)) * 4;
+                const int tok = row / (16 * NP) * (16 * NF) + 16 * j0 + row % (16 * NP);
+                f32x4 v = *(const f32x4*)(part + row * S::SUM_PITCH + col);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)v[e];
-                *(u32x2*)(C + (size_t)(n0 + tok) * m + m0 + col) = o.u;
+                for (int q = 1; q < G; ++q) {
+                    const f32x4 x = *(const f32x4*)(part + (q * ROWS + row) * S::SUM_PITCH + col);
+                    v[0] += x[0]; v[1] += x[1]; v[2] += x[2]; v[3] += x[3];
+                }
+                if (n0 + tok < n && m0 + col < m) {           // m % 8 == 0
+                    union { __bf16 h[4]; u32x2 u; } o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)v[e];
+                    *(u32x2*)(C + (size_t)(n0 + tok) * m + m0 + col) = o.u;
+                }
             }
         }
     }
 }
 
-// Four groups on 64 x 64 tiles while those tiles are at most two rounds of one workgroup per compute unit: 1000 tokens,
-// 1000 x 1000 (256 tiles) 10.5 us against 20.1 for 128 x 128, 2000 tokens (512) 18.9 against 21.1, but 2048 tokens,
-// 2056 x 2056 (1056) 79 against 43.
-static bool generic_small_tile(int64_t n, int64_t m) {
-    return ((m + 63) / 64) * ((n + 63) / 64) <= 2 * RESIDENT;
+// The form with four groups on 64 x 64 tiles, while those tiles are at most two rounds of one workgroup per compute unit
+// (1000 tokens, 1000 x 1000, 256 tiles: 10.5 us against 20.1 for 128 x 128; 2000 tokens, 512 tiles: 18.9 against 21.1; but
+// 2048 tokens, 2056 x 2056, 1056 tiles: 79 against 43).  Where whole k-steps let the tile kernels compete it is the better
+// one in a single round only (spmm_tile_choice).  Register-staged tiles of 128 x 64 to 256 x 128 with two to four groups
+// were measured too: never better than both this and the tile kernels' rings.
+inline int64_t tiles_of_64(int64_t n, int64_t m) { return ((m + 63) / 64) * ((n + 63) / 64); }
+
+template <int FM, int FN, int G>
+hipError_t launch_generic_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                             const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
+    using S = GenSmem<FM, FN, G>;
+    static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
+    const int tiles_m = (int)((m + S::BM - 1) / S::BM), tiles_n = (int)((n + S::BN - 1) / S::BN);
+    auto kern = K % 128 == 0 ? spmm_generic_kernel<GEN_WHOLE, FM, FN, G>
+                : K % 64 == 0 ? spmm_generic_kernel<GEN_PARTIAL, FM, FN, G> : spmm_generic_kernel<GEN_RAGGED, FM, FN, G>;
+    kern<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * G), 0, s>>>(B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2,
+                                                                       C, tiles_m);
+    return hipGetLastError();
 }
 
-template <bool RAGGED>
 hipError_t launch_generic(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
                           const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
-    if (generic_small_tile(n, m)) {
-        const int tiles_m = (int)((m + 63) / 64), tiles_n = (int)((n + 63) / 64);
-        spmm_generic_kernel<RAGGED, 2, 4><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(1024), 0, s>>>(
-            B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m);
-    } else {
-        const int tiles_m = (int)((m + 127) / 128), tiles_n = (int)((n + 127) / 128);
-        spmm_generic_kernel<RAGGED, 4, 1><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s>>>(
-            B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m);
-    }
-    return hipGetLastError();
+    if (spmm_generic_edge(n, m) == 64) return launch_generic_as<2, 2, 4>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
+    return launch_generic_as<4, 4, 1>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
 }
 
 template <int BM, int BN, bool TAIL>
@@ -915,9 +927,13 @@ hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint
 constexpr int64_t SLAB_MAX_TOKENS = 1024;
 
 // The tile kernels take whole k-steps of 64, at least two of them (700 tokens: 4160 x 2112 54 -> 25 us, 2112 x 4160
-// 96 -> 35 us against the generic kernel).  Contractions of up to 5 k-steps that are no multiple of 256 stay with the
-// generic kernel: a ring's prologue would be most of the work.
-static bool tile_kernel_fits(int64_t K) { return K % 64 == 0 && K >= 128 && (K % 256 == 0 || K > 320); }
+// 96 -> 35 us against the generic kernel).
+static bool tile_kernel_fits(int64_t K) { return K % 64 == 0 && K >= 128; }
+// One round of 64 x 64 tiles: the generic kernel's four groups beat the rings of the tile kernels at every contraction
+// length (input gradients without scratch: 512 tokens, 2048 x 4096: 26.5 -> 21.9 us; 128 tokens, 8192 x 9216: 67 -> 58 us;
+// 1024 tokens, 1024 x 1024: 9.9 -> 8.7 us): all of a compute unit's 16 wavefronts load, and each k-step waits for its
+// own quarter of them only.  (777 tokens, 1280 x 5120, 260 tiles in two rounds: 34 -> 50 us.)
+static bool one_round_of_64(int64_t n, int64_t m) { return tiles_of_64(n, m) <= RESIDENT; }
 
 int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
     if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || !tile_kernel_fits(K)) return 0;
@@ -940,6 +956,10 @@ int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
                           + (sl > 1 ? 2.0 * sl * (double)n * (double)m * 4.0 / hbm : 0.0);
         if (ns < best_ns) { best_ns = ns; best = sl; }
     }
+    // One round of 64 x 64 tiles with four groups takes about 3 us and 2 us per 512 of the contraction, slabs about 1.25
+    // times the estimate and 4 us for two launches (us, 64 x 64 / slabs: 128 tokens, 4096 x 2048 10.4 / 18.9; 200 tokens,
+    // 4096 x 4096 18.3 / 23.3; 100 tokens, 5120 x 5120 22.0 / 22.2; 64 tokens, 9216 x 9216 48 / 35).
+    if (one_round_of_64(n, m) && 3e3 + 2.05e3 * (double)K / 512.0 <= 4e3 + 1.25 * best_ns) return 0;
     return best < 2 ? 0 : best;
 }
 
@@ -963,10 +983,16 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
     return hipGetLastError();
 }
 
+int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RESIDENT ? 64 : 128; }
+
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel.
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 0;
     if (!tile_kernel_fits(K)) return;
+    if (one_round_of_64(n, m)) {                              // whole pairs of k-steps count as a tile shape of their own
+        if (K % 128 == 0) bm = bn = 64;
+        return;
+    }
     // Few tokens (inference): the product is a single pass over the packed weight, bound by HBM.
     // Narrow token tiles, and weight tiles small enough that every compute unit streams its share.
     if (n <= 128) {
@@ -992,8 +1018,7 @@ hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const u
     int bm, bn;
     spmm_tile_choice(n, m, K, bm, bn);
     if (bm == 0) {
-        return K % 64 == 0 ? launch_generic<false>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s)
-                           : launch_generic<true>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        return launch_generic(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     }
     switch (bm * 1000 + bn) {
         case 256256: return launch_split(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
@@ -1001,7 +1026,7 @@ hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const u
         case 256128: return launch_tile<256, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 128128: return launch_tile<128, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 128064: return launch_tile<128, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
-        case 64064: return launch_tile<64, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 64064: return launch_generic_as<2, 2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         default: return launch_tile<64, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     }
 }

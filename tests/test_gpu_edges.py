@@ -67,6 +67,8 @@ def test_contractions_with_a_remainder_of_k_steps(b, d_out, d_in, r):
 # the generic sparse kernel: whole and partial pairs of k-steps, fewer pairs than groups, more than two rounds of
 # 64 x 64 tiles (then 128 x 128 with one group), the adapter extension of both forms
 @pytest.mark.parametrize("b,d_out,d_in,r", [(65, 72, 64, 32), (700, 704, 192, 0), (1500, 1480, 320, 96), (1500, 1480, 1160, 64),
-                                            (2048, 2056, 520, 0), (64, 64, 8, 0), (40, 200, 2056, 32)])
+                                            (2048, 2056, 520, 0), (64, 64, 8, 0), (40, 200, 2056, 32),
+                                            # whole pairs on one round of 64 x 64 tiles, and just above it
+                                            (1024, 1024, 1024, 64), (1000, 1024, 128, 32), (512, 2048, 2176, 160), (1025, 1024, 1024, 0)])
 def test_generic_sparse_kernel(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
