@@ -63,12 +63,14 @@ hipError_t launch_xl_small(const bf16_t* X, int64_t n, int64_t d_in, const bf16_
                            bf16_t* T, hipStream_t s);
 // T[n, r] = X[n, K] * Lt[r, K]^T (dense tile kernel) for many tokens, with the k-contiguous copy Lt of L
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
-                                  bf16_t* Lt, float* partial_or_null, hipStream_t s);
+                                  bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s);
 // C[n, m] = sum_k B(i, k) * A(j, k) for the skinny adapter products of layers whose extents are not multiples of 64:
 // an operand is k-contiguous [rows][ld] (K % 8 == 0) or k-major [K][ld] (rows % 8 == 0); m % 8 == 0.  (B k-major with A
 // k-contiguous does not occur.)
 hipError_t launch_skinny_ragged(const bf16_t* B, int64_t ldb, bool b_kmajor, const bf16_t* A, int64_t lda, bool a_kmajor,
                                 int64_t n, int64_t m, int64_t K, bf16_t* C, hipStream_t s);
+// out[c][r] = in[r][c]: in [rows][cols], rows % 64 == 0, cols % 8 == 0
+hipError_t launch_transpose(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, hipStream_t s);
 hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out,
                                int64_t d_in, bf16_t* gvals, hipStream_t s);
 // the same result from token-contiguous copies Xt [d_in][ld], dYt [d_out][ld] (ld = the pitch behind
@@ -83,10 +85,11 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out);
 hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b, const uint8_t* meta, int64_t d_out,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s);
 
-// C[n, m] = B[n, K] * A[m, K]^T (dense bf16, fp32 accumulation), K % 64 == 0
+// C[n, m] = B[n, K] * A[m, K]^T (dense bf16, fp32 accumulation, row pitch ld of both operands), K % 64 == 0, one of n
+// and m an adapter's rank; partial_bytes of scratch allow a split over K
 size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m);
-hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
-                                 float* partial_or_null, hipStream_t s);
+hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, int64_t ld, bf16_t* C,
+                                 float* partial_or_null, size_t partial_bytes, hipStream_t s);
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s);
 // general N:M magnitude mask (M in {2, 4, 8}); axis 0: groups inside a row, axis 1: inside a column

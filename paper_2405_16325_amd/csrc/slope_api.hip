@@ -47,8 +47,9 @@ hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A
                           bf16_t* At_scratch, float* partial, hipStream_t s) {
     if (K % 64 != 0)
         return launch_skinny_ragged(B, K, false, A, a_kmajor ? r : K, a_kmajor, n, r, K, T, s);
-    if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, s);
-    return launch_dense_tn_plain(B, n, A, r, K, T, partial, s);
+    const size_t partial_bytes = partial ? dense_tn_plain_partial_bytes(n, r) : 0;
+    if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);
+    return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);
 }
 
 }  // namespace

@@ -283,13 +283,13 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(const bf16_t* __re
 #undef TN_STEP
     WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
 
-    if (EPI == EPI_PLAIN) {
+    if constexpr (EPI == EPI_PLAIN) {
         store_plain<MF, NF>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, l16, lq, out,
                             partial ? partial + (size_t)blockIdx.y * n * m : nullptr);
-        return;
+    } else {
+        static_assert(BN * (BM + 16) <= S::TOTAL, "the staged tile of pairs fits in the ring");
+        store_masked_packed<MF, NF, BM, BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out, smem);
     }
-    static_assert(BN * (BM + 16) <= S::TOTAL, "the staged tile of pairs fits in the ring");
-    store_masked_packed<MF, NF, BM, BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out, smem);
 }
 
 // out = sum over the slabs (in slab order: runs are bit-identical), rounded to bf16; four elements per lane
@@ -603,6 +603,11 @@ hipError_t launch_token_copies(const bf16_t* in0, int64_t cols0, bf16_t* out0, c
     return hipGetLastError();
 }
 
+hipError_t launch_transpose(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, hipStream_t s) {
+    launch_transpose_pad(in, rows, cols, rows, rows, out, s);
+    return hipGetLastError();
+}
+
 // The packed epilogue reads the metadata of 32 columns of W^R as one dword: rows of d_in / 8 bytes must
 // keep those dwords aligned.  Other layers take the in-place kernel.
 bool wgrad_tn_fits(int64_t d_in) { return d_in % 32 == 0; }
@@ -649,35 +654,71 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
     return launch_dense_tn<128, 64, EPI_MASKED_PACKED, 6>(Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s);
 }
 
-// C[n, m] = B[n, K] * A[m, K]^T, all bf16 row-major, K % 64 == 0 (the skinny product T = X L of the
-// adapter: m = rank).  The product is bound by streaming B once: narrow token tiles so that even
-// m = 128 gives every compute unit a tile, and a six-deep ring to keep enough reads in flight.
-//
-// A few hundred to a few thousand tokens give that product only a handful of tiles with a long
-// contraction each.  With scratch memory (`partial`, dense_tn_plain_partial_bytes(n, m) bytes) the
-// contraction is then cut into slabs that run as separate workgroups, about 256 in all, and leave
-// fp32 sums that a second kernel adds in slab order.
+// C[n, m] = B[n, K] * A[m, K]^T for the skinny products of the adapters (T = X L, dY R^T, and over the tokens dL and
+// dR): one side is the rank, the other a layer extent or the tokens.  Both operands bf16 of row pitch ld, K % 64 == 0.
+// The product is bound by streaming the long operand once, so what counts is that a single round of workgroups (one per
+// compute unit, the ring fills the LDS) covers it: with too few tiles the contraction is cut into slabs that leave fp32
+// sums for a second kernel, at most as many as fit beside each other, since a thin second round costs as much as the
+// first (5120 x 64 over 16384 tokens in tiles of 64 x 64: 1 slab 95 us, 3 slabs 44.7, 4 slabs 61.7).
+// The rule takes the least of an estimate: the long operand at 4.6 TB/s, or what a compute unit pulls for its tiles
+// at 41 B/ns; slabs cost 3 us for the second launch, 0.4 us each and their traffic (5120 x 64 / 9216 x 128 / 2560 x 64
+// over 16384 / 16384 / 4096 tokens: estimates 41 / 75 / 12 us, measured 44.7 / 76 / 11.8; before, in tiles of 128 x 64
+// without slabs, 108 / 133 / 31).
+struct SkinnyPlan { int bm, bn, slabs, slab_steps; };
+static SkinnyPlan skinny_plan(int64_t n, int64_t m, int64_t K, size_t partial_bytes) {
+    const int bms[5] = {128, 64, 64, 128, 256}, bns[5] = {64, 64, 128, 128, 64};
+    const int64_t ksteps = K / 64, longer = n > m ? n : m;
+    SkinnyPlan best = {128, 64, 1, (int)ksteps};
+    double best_us = 1e300;
+    for (int c = 0; c < 5; ++c) {
+        const int64_t tiles = ((m + bms[c] - 1) / bms[c]) * ((n + bns[c] - 1) / bns[c]);
+        int64_t slabs = RESIDENT / tiles;
+        if (slabs > ksteps / 4) slabs = ksteps / 4;          // at least four k-steps per slab
+        const int64_t room = (int64_t)(partial_bytes / ((size_t)n * (size_t)m * 4));
+        if (slabs > room) slabs = room;
+        if (slabs < 1) slabs = 1;
+        const int64_t steps = (ksteps + slabs - 1) / slabs;
+        slabs = (ksteps + steps - 1) / steps;
+        const double rounds = (double)((tiles * slabs + RESIDENT - 1) / RESIDENT);
+        const double pull = rounds * (double)steps * 128.0 * (double)(bms[c] + bns[c]) / 41e3;
+        const double stream = 2.0 * (double)longer * (double)K / 4.6e6;
+        const double us = (pull > stream ? pull : stream) +
+                          (slabs > 1 ? 3.0 + 0.4 * (double)slabs + 8.0 * (double)slabs * (double)n * (double)m / 10e6 : 0.0);
+        if (us < best_us) { best_us = us; best = {bms[c], bns[c], (int)slabs, (int)steps}; }
+    }
+    return best;
+}
+
+// scratch of the calls that compute T or dY R^T and know no contraction length: slabs for fewer than 128 tiles
 size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m) {
     const int64_t tiles = ((m + 127) / 128) * ((n + 63) / 64);
     if (tiles >= RESIDENT / 2) return 0;
     return (size_t)((RESIDENT + tiles - 1) / tiles) * (size_t)n * (size_t)m * 4;
 }
 
-hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
-                                 float* partial, hipStream_t s) {
-    const int64_t tiles = ((m + 127) / 128) * ((n + 63) / 64), ksteps = K / 64;
-    int64_t nslabs = partial && tiles < RESIDENT / 2 ? (RESIDENT + tiles - 1) / tiles : 1;
-    if (nslabs > ksteps / 8) nslabs = ksteps / 8;            // at least eight k-steps per slab
-    if (nslabs <= 1) return launch_dense_tn<128, 64, EPI_PLAIN, 6>(A, m, B, n, K, K, nullptr, C, s);
-    const int64_t slab_steps = (ksteps + nslabs - 1) / nslabs;
-    nslabs = (ksteps + slab_steps - 1) / slab_steps;
-    hipError_t e = launch_dense_tn<128, 64, EPI_PLAIN, 6>(A, m, B, n, K, K, nullptr, C, s, (int)nslabs, (int)slab_steps,
-                                                          partial);
+template <int BM, int BN, int NS>
+static hipError_t launch_skinny(const SkinnyPlan& p, const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K,
+                                int64_t ld, bf16_t* C, float* partial, hipStream_t s) {
+    if (p.slabs <= 1) return launch_dense_tn<BM, BN, EPI_PLAIN, NS>(A, m, B, n, K, ld, nullptr, C, s);
+    hipError_t e = launch_dense_tn<BM, BN, EPI_PLAIN, NS>(A, m, B, n, K, ld, nullptr, C, s, p.slabs, p.slab_steps, partial);
     if (e != hipSuccess) return e;
     const size_t count4 = (size_t)n * (size_t)m / 4;
-    partial_reduce_kernel<<<dim3((unsigned)((count4 + 255) / 256)), dim3(256), 0, s>>>((const f32x4*)partial, (int)nslabs,
-                                                                                     count4, (u32x2*)C);
+    partial_reduce_kernel<<<dim3((unsigned)((count4 + 255) / 256)), dim3(256), 0, s>>>((const f32x4*)partial, p.slabs, count4,
+                                                                                     (u32x2*)C);
     return hipGetLastError();
+}
+
+// partial_bytes of scratch at `partial` (none: no slabs)
+hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, int64_t ld, bf16_t* C,
+                                 float* partial, size_t partial_bytes, hipStream_t s) {
+    const SkinnyPlan p = skinny_plan(n, m, K, partial ? partial_bytes : 0);
+    switch (p.bm * 1000 + p.bn) {
+        case 64064: return launch_skinny<64, 64, 8>(p, B, n, A, m, K, ld, C, partial, s);
+        case 64128: return launch_skinny<64, 128, 6>(p, B, n, A, m, K, ld, C, partial, s);
+        case 128128: return launch_skinny<128, 128, 4>(p, B, n, A, m, K, ld, C, partial, s);
+        case 256064: return launch_skinny<256, 64, 4>(p, B, n, A, m, K, ld, C, partial, s);
+        default: return launch_skinny<128, 64, 6>(p, B, n, A, m, K, ld, C, partial, s);
+    }
 }
 
 // The same product for any shape (dense weights with a general N:M mask, where no sparse MFMA
@@ -704,12 +745,21 @@ hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int6
 // Weight gradient of a layer with adapters: the packed dW as above plus the adapter gradients
 // (chain rule of Eq. 11)   dL = X^T (dY R^T)  [d_in, r],   dR = (X L)^T dY  [r, d_out],
 // all three contractions over the tokens sharing the token-contiguous copies of X and dY.
-// Workspace: Xt | dYt | Lt [r][d_in] | T = X L [b][r] | T2 = dY R^T [b][r] | Tt [r][ld] | T2t [r][ld] | the
-// scratch of launch_wgrad_masked_t.
+// Workspace: Xt | dYt | Lt [r][d_in] | T = X L [b][r] | T2 = dY R^T [b][r] | Tt [r][ld] | T2t [r][ld] | scratch
+// that launch_wgrad_masked_t and the skinny products use one after the other.
+static size_t wgrad_adapter_shared_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
+    if (d_in % 64 != 0 || d_out % 64 != 0) return wgrad_tail_bytes(b, d_in, d_out);   // no tile kernel for the skinny products
+    const int64_t longest = d_in > d_out ? d_in : d_out;
+    const int64_t sl = skinny_plan(longest, r, (b + 63) / 64 * 64, ~(size_t)0).slabs;
+    const size_t tail = wgrad_tail_bytes(b, d_in, d_out);
+    const size_t sums = sl > 1 ? (size_t)sl * (size_t)longest * (size_t)r * 4 : 0;
+    return tail > sums ? tail : sums;
+}
+
 size_t wgrad_adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     size_t ld = (size_t)token_pitch((b + 63) / 64 * 64);
     return round256(token_copy_bytes(b, d_in)) + round256(token_copy_bytes(b, d_out)) + round256((size_t)r * d_in * 2) +
-           2 * round256((size_t)b * r * 2) + 2 * round256((size_t)r * ld * 2) + wgrad_tail_bytes(b, d_in, d_out);
+           2 * round256((size_t)b * r * 2) + 2 * round256((size_t)r * ld * 2) + wgrad_adapter_shared_bytes(b, d_in, d_out, r);
 }
 
 hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out,
@@ -725,6 +775,8 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     bf16_t* Tt = (bf16_t*)w;   w += round256((size_t)r * ld * 2);
     bf16_t* T2t = (bf16_t*)w;  w += round256((size_t)r * ld * 2);
     float* tail = wgrad_tail_bytes(b, d_in, d_out) ? (float*)w : nullptr;
+    const size_t shared = wgrad_adapter_shared_bytes(b, d_in, d_out, r);
+    float* sums = shared ? (float*)w : nullptr;
 
     hipError_t e;
     if (d_in % 64 != 0 || d_out % 64 != 0) {
@@ -740,11 +792,10 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     if ((e = launch_wgrad_masked_t(dYt, Xt, b, meta, d_out, d_in, gvals, tail, s)) != hipSuccess) return e;
     launch_transpose_pad(L, d_in, r, d_in, d_in, Lt, s);                          // Lt[r][d_in]
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_dense_tn_plain(X, b, Lt, r, d_in, T, nullptr, s)) != hipSuccess) return e;      // T  = X L
-    if ((e = launch_dense_tn_plain(dY, b, R, r, d_out, T2, nullptr, s)) != hipSuccess) return e;    // T2 = dY R^T
+    if ((e = launch_dense_tn_plain(X, b, Lt, r, d_in, d_in, T, sums, shared, s)) != hipSuccess) return e;        // T  = X L
+    if ((e = launch_dense_tn_plain(dY, b, R, r, d_out, d_out, T2, sums, shared, s)) != hipSuccess) return e;     // T2 = dY R^T
     launch_transpose_pad2(T, r, Tt, T2, r, T2t, b, bp, ld, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_dense_tn<128, 64, EPI_PLAIN, 6>(T2t, r, Xt, d_in, bp, ld, nullptr, dL, s);   // dL[d_in][r]
-    if (e != hipSuccess) return e;
-    return launch_dense_tn<128, 64, EPI_PLAIN, 6>(dYt, d_out, Tt, r, bp, ld, nullptr, dR, s);   // dR[r][d_out]
+    if ((e = launch_dense_tn_plain(Xt, d_in, T2t, r, bp, ld, dL, sums, shared, s)) != hipSuccess) return e;      // dL[d_in][r]
+    return launch_dense_tn_plain(Tt, r, dYt, d_out, bp, ld, dR, sums, shared, s);                                // dR[r][d_out]
 }
