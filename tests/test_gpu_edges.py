@@ -80,3 +80,10 @@ def test_generic_sparse_kernel(b, d_out, d_in, r):
                                             (6000, 2624, 1088, 96), (5000, 9216, 512, 128), (1088, 448, 9280, 512)])
 def test_skinny_adapter_products(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
+
+
+# the weight gradient in place on one or two rounds of 64 x 64 tiles, and just above: fewer slabs of 32 tokens than
+# groups, a slab that is not full, a row of tiles that is not full
+@pytest.mark.parametrize("b,d_out,d_in", [(1, 8, 8), (33, 72, 136), (1000, 1000, 1000), (130, 1032, 1992), (300, 1464, 1480)])
+def test_in_place_weight_gradient(b, d_out, d_in):
+    ragged.test_every_call_on_a_ragged_layer(b, d_out, d_in, 0)
