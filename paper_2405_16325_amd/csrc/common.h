@@ -25,7 +25,7 @@ hipError_t launch_prune_rows(const bf16_t* W, int64_t d_out, int64_t d_in, bf16_
 constexpr int64_t DP_EXTENT_MAX = (int64_t)1 << 23;
 hipError_t launch_double_prune(const bf16_t* vals, const uint8_t* meta, int64_t d_out, int64_t d_in,
                                bf16_t* valsT, uint8_t* metaT, uint8_t* maskrc, hipStream_t s);
-hipError_t launch_update_transposed(const bf16_t* vals, const uint8_t* meta, int64_t d_out, int64_t d_in,
+hipError_t launch_update_transposed(const bf16_t* vals, const uint8_t* meta, int64_t d_out, int64_t d_in, bf16_t* vals_copy,
                                     const uint8_t* metaT, bf16_t* valsT, hipStream_t s);
 hipError_t launch_sparse_add(const bf16_t* a, const bf16_t* b, size_t count, float beta, float gamma, bf16_t* out,
                              hipStream_t s);

@@ -424,14 +424,9 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
     if (misaligned(Wnew_vals, 16) || misaligned(Wr_meta, 16) || misaligned(Wr_vals, 16) ||
         misaligned(WrcT_meta, 16) || misaligned(WrcT_vals, 16))
         return SLOPE_ERR_ALIGN;
-    hipStream_t s = (hipStream_t)stream;
-    if (Wr_vals != Wnew_vals) {
-        hipError_t e = hipMemcpyAsync(Wr_vals, Wnew_vals, (size_t)d_out * (size_t)(d_in / 2) * 2,
-                                      hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return finish(e);
-    }
     return finish(launch_update_transposed((const bf16_t*)Wnew_vals, (const uint8_t*)Wr_meta, d_out, d_in,
-                                           (const uint8_t*)WrcT_meta, (bf16_t*)WrcT_vals, s));
+                                           Wr_vals != Wnew_vals ? (bf16_t*)Wr_vals : nullptr, (const uint8_t*)WrcT_meta,
+                                           (bf16_t*)WrcT_vals, (hipStream_t)stream));
 }
 
 slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t r, int with_workspace, int32_t* plan) {

@@ -7,6 +7,7 @@ import torch
 
 from paper_2405_16325_amd import binding as sl
 from paper_2405_16325_amd import inputs
+from tests import test_gpu_optimizer as optimizer
 from tests import test_gpu_ragged as ragged
 from tests.test_gpu_fullsize import assert_all_close, unpack_bits
 
@@ -87,3 +88,9 @@ def test_skinny_adapter_products(b, d_out, d_in, r):
 @pytest.mark.parametrize("b,d_out,d_in", [(1, 8, 8), (33, 72, 136), (1000, 1000, 1000), (130, 1032, 1992), (300, 1464, 1480)])
 def test_in_place_weight_gradient(b, d_out, d_in):
     ragged.test_every_call_on_a_ragged_layer(b, d_out, d_in, 0)
+
+
+# both copies rewritten in one pass: tiles of 128 that are not full, rows of any multiple of 8
+@pytest.mark.parametrize("d_out,d_in", [(8, 8), (136, 264), (1000, 1000), (128, 128), (4160, 2112)])
+def test_update_of_both_copies(d_out, d_in):
+    optimizer.test_update_sparse_bit_exact(d_out, d_in, False)
