@@ -101,6 +101,15 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
                                 int64_t d_in, const bf16_t* L, const bf16_t* R, int64_t r, bf16_t* gvals, bf16_t* dL,
                                 bf16_t* dR, void* workspace, hipStream_t s);
 
+// Per 16-bit half: 1 where kj > ki, else 0 (saturating subtract, then min with 1).  Written as instructions
+// because the compiler turns the portable form back into one compare and one select per half.
+__device__ __forceinline__ uint32_t pk_beats(uint32_t kj, uint32_t ki, uint32_t ones) {
+    uint32_t d, c;
+    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(d) : "v"(kj), "v"(ki));
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(c) : "v"(d), "v"(ones));
+    return c;
+}
+
 // Rank the four keys of a group by (key descending, index ascending) and return the 4-bit
 // set of the two winners.  Keys are small non-negative integers.
 __device__ __forceinline__ uint32_t top2_of_4(uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) {

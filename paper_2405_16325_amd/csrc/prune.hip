@@ -104,15 +104,6 @@ __device__ __forceinline__ buffer_t tile_buffer(const void* base, uint32_t bytes
 }
 constexpr uint32_t NOWHERE = 0x80000000u;   // an offset outside every descriptor (they cover less than 2^31 bytes)
 
-// Per 16-bit half: 1 where kj > ki, else 0 (saturating subtract, then min with 1).  Written as instructions
-// because the compiler turns the portable form back into one compare and one select per half.
-__device__ __forceinline__ uint32_t pk_beats(uint32_t kj, uint32_t ki, uint32_t ones) {
-    uint32_t d, c;
-    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(d) : "v"(kj), "v"(ki));
-    asm("v_pk_min_u16 %0, %1, %2" : "=v"(c) : "v"(d), "v"(ones));
-    return c;
-}
-
 // GIVEN = false: slope_double_prune, the pairs are chosen here by magnitude among the survivors
 //                 and their metadata is written.
 // GIVEN = true : slope_update_sparse, the pairs are the ones metaT_in already names (static

@@ -7,6 +7,7 @@ import torch
 
 from paper_2405_16325_amd import binding as sl
 from paper_2405_16325_amd import inputs
+from tests import test_gpu_nm_mask as nm
 from tests import test_gpu_optimizer as optimizer
 from tests import test_gpu_ragged as ragged
 from tests.test_gpu_fullsize import assert_all_close, unpack_bits
@@ -94,3 +95,11 @@ def test_in_place_weight_gradient(b, d_out, d_in):
 @pytest.mark.parametrize("d_out,d_in", [(8, 8), (136, 264), (1000, 1000), (128, 128), (4160, 2112)])
 def test_update_of_both_copies(d_out, d_in):
     optimizer.test_update_sparse_bit_exact(d_out, d_in, False)
+
+
+# column masks: tiles of 64 x 64 that end inside a row, a column or a 16-byte piece of the transposed output
+@pytest.mark.parametrize("kind", ["gauss", "ties", "special"])
+@pytest.mark.parametrize("n,m,rows,cols", [(1, 2, 66, 72), (2, 2, 130, 8), (1, 4, 68, 136), (3, 4, 60, 64), (2, 8, 200, 520),
+                                           (5, 8, 8, 1032), (8, 8, 72, 56)])
+def test_column_masks(n, m, kind, rows, cols):
+    nm.test_prune_mask_rows_then_columns(n, m, kind, rows, cols)
