@@ -313,7 +313,7 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  *   [1], [2] weight rows and tokens per workgroup      [3] slabs or slices (1 = no split)
  *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens),
  *       2 dense tile kernel, 3 dense tile kernel split over d_in, 4 MFMA kernel for ragged extents (d_in % 64 != 0)
- *   [5] chunks of 64 rows of L per workgroup for [4] == 1
+ *   [5] chunks of 64 rows of L per partial sum that the scratch is sized by, for [4] == 1
  * with_workspace: whether the call would be given its scratch.  Errors as slope_spmm_fwd.
  */
 slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t r, int with_workspace, int32_t* plan);

@@ -34,18 +34,40 @@ hipError_t launch_sparse_add(const bf16_t* a, const bf16_t* b, size_t count, flo
 hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                        int64_t K, const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s);
 // the choices behind it (pure functions of the shape): tile of the tile kernels (0 x 0 = the generic kernel),
-// weight rows per workgroup of the small-batch kernel, chunks of 64 rows of L per workgroup of the X L split
+// weight rows per workgroup of the small-batch kernel, chunks of 64 rows of L per slab that the scratch of X L is sized by
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn);
 int spmm_generic_edge(int64_t n, int64_t m);                 // edge of the generic kernel's tile
 int spmm_stream_rows(int64_t n, int64_t m, int64_t K);
 int xl_subs(int64_t n, int64_t d_in, int64_t r);
+// T = X L for few tokens (n <= XL_SMALL_MAX_TOKENS, d_in % 64 == 0) from L as stored, split over d_in: `slabs` slabs of
+// k_per rows of L, `steps` chunks of them in a row; at most max_floats sums and max_groups workgroups.  One slab writes T.
+constexpr int64_t XL_SMALL_MAX_TOKENS = 512;
+struct XlSplit { int slabs, k_per, steps; };
+XlSplit xl_split(int64_t n, int64_t d_in, int64_t r, int64_t max_floats, int64_t max_groups);
+size_t xl_small_scratch_bytes(int64_t n, int64_t d_in, int64_t r);
+hipError_t launch_xl(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, const XlSplit& x, float* Q,
+                     bf16_t* T, hipStream_t s);
+hipError_t launch_xl_reduce(const float* Q, int slabs, int64_t n, int64_t r, bf16_t* T, hipStream_t s);
+// C = bf16(sum of P[slices][n][m] + T R), T = bf16 of the sum of Q[q_slabs][n][r]
+hipError_t launch_adapter_finish(const float* P, int slices, int64_t n, int64_t m, const float* Q, int q_slabs,
+                                 const bf16_t* R, int64_t r, bf16_t* C, hipStream_t s);
 // the same product for a few dozen to a few hundred tokens, split over K with fp32 partial sums in `slabs`
-// (spmm_slab_bytes of them; 0 = this shape does not take the path)
+// (spmm_slab_bytes of them; 0 = this shape does not take the path).  The adapter (r == 0: none) comes as T = X L,
+// or, where T is null, as its sums Q; with a non-null L those are written by workgroups of the product's own first launch
+// (slab_xl_split)
+struct SlabAdapter {
+    const bf16_t* T;
+    float* Q;
+    const bf16_t* L;
+    const bf16_t* R;
+    int64_t r;
+    XlSplit x;
+};
 int spmm_slab_count(int64_t n, int64_t m, int64_t K);
 size_t spmm_slab_bytes(int64_t n, int64_t m, int64_t K);
+bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, XlSplit& x);
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
-                             int64_t K, const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, float* slabs,
-                             hipStream_t s);
+                             int64_t K, const SlabAdapter& ad, bf16_t* C, float* slabs, hipStream_t s);
 // the same product for n <= 32 tokens (any K % 64 == 0, K >= 128); adapters as T[n, K2] and R[K2, m] as stored
 constexpr int64_t STREAM_MAX_TOKENS = 32;
 inline bool spmm_stream_fits(int64_t n, int64_t K) { return n <= STREAM_MAX_TOKENS && K >= 128 && K % 64 == 0; }
@@ -56,11 +78,6 @@ size_t spmm_rows_partial_bytes(int64_t n, int64_t m, int64_t K);
 hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                               int64_t K, const bf16_t* T, const bf16_t* R, int64_t K2, bf16_t* C, float* partial_or_null,
                               hipStream_t s);
-// T = X L for few tokens (n <= XL_SMALL_MAX_TOKENS), split over d_in with fp32 partial sums in `scratch`
-constexpr int64_t XL_SMALL_MAX_TOKENS = 512;
-size_t xl_small_scratch_bytes(int64_t n, int64_t d_in, int64_t r);
-hipError_t launch_xl_small(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, float* scratch,
-                           bf16_t* T, hipStream_t s);
 // T[n, r] = X[n, K] * Lt[r, K]^T (dense tile kernel) for many tokens, with the k-contiguous copy Lt of L
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
                                   bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s);

@@ -52,6 +52,9 @@ hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A
     return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);
 }
 
+// sums of T = X L that a workgroup of the kernel after a split product adds up at most
+constexpr int64_t XL_FINISH_FLOATS = 65536;
+
 }  // namespace
 
 void note_hip_error(hipError_t e) { g_last_hip_error = (int)e; }
@@ -177,37 +180,62 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
                                  void* workspace, void* stream) {
     const bool adapter = r > 0 && (L_or_null || R_or_null);
     hipStream_t s = (hipStream_t)stream;
-    const bf16_t* x = (const bf16_t*)X;
+    const bf16_t* x_in = (const bf16_t*)X;
     const bf16_t* wv = (const bf16_t*)Wr_vals;
     const uint8_t* wm = (const uint8_t*)Wr_meta;
     uint8_t* ws = (uint8_t*)workspace;
     bf16_t* T = (bf16_t*)ws;
+    const bf16_t* l = adapter ? (const bf16_t*)L_or_null : nullptr;
+    const bf16_t* R = adapter ? (const bf16_t*)R_or_null : nullptr;
+    if (!adapter) r = 0;
+    uint8_t* after = ws + adapter_workspace_bytes(b, d_in, d_out, r);      // the slabs or slices of the product
+    bf16_t* Lt = (bf16_t*)(ws + round256((size_t)b * r * 2));
+    float* sums = (float*)((uint8_t*)Lt + round256((size_t)d_in * r * 2));
+    const int64_t sums_floats = adapter ? (int64_t)(xl_small_scratch_bytes(b, d_in, r) / 4) : 0;
+    const bool few = spmm_stream_fits(b, d_in);
+    // With scratch memory a batch of a few dozen to a few hundred tokens is split over K as well, and up to
+    // XL_SMALL_MAX_TOKENS of them the kernel that adds the slabs adds the adapter term too, straight from the sums of T = X L,
+    // which workgroups beside the product's compute where they fit (rank 128, 9216 x 9216, 128 tokens: 54.7 -> 42.8 us in
+    // all; 256 tokens: 67 -> 53).
+    const bool slabs = !few && workspace && spmm_slab_count(b, d_out, d_in) > 0;
+    SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
+    if (slabs && (!adapter || b <= XL_SMALL_MAX_TOKENS)) {
+        if (adapter) {
+            // each of that kernel's workgroups adds up 32 tokens' worth of sums: 64 K floats of them at most
+            const int64_t held = XL_FINISH_FLOATS / (32 * r) * b * r, most = held < sums_floats ? held : sums_floats;
+            if (!slab_xl_split(b, d_out, d_in, r, most, ad.x)) {           // no room beside the product
+                ad.L = nullptr;
+                ad.x = xl_split(b, d_in, r, most, RESIDENT);
+                hipError_t e = launch_xl(x_in, b, d_in, l, r, ad.x, sums, nullptr, s);
+                if (e != hipSuccess) return finish(e);
+            }
+        }
+        return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
+    }
     if (adapter) {                                            // T = X L, rounded to bf16
-        bf16_t* Lt = (bf16_t*)(ws + round256((size_t)b * r * 2));
-        float* partial = (float*)((uint8_t*)Lt + round256((size_t)d_in * r * 2));
         hipError_t e;
-        if (d_in % 64 == 0 && b <= XL_SMALL_MAX_TOKENS)       // too few tokens for the tile kernel to spread X L over the chip
-            e = launch_xl_small(x, b, d_in, (const bf16_t*)L_or_null, r, partial, T, s);
-        else
-            e = skinny_product(x, b, d_in, (const bf16_t*)L_or_null, true, r, T, Lt,
-                               b > XL_SMALL_MAX_TOKENS && dense_tn_plain_partial_bytes(b, r) ? partial : nullptr, s);
+        if (d_in % 64 == 0 && b <= XL_SMALL_MAX_TOKENS) {
+            const XlSplit x = xl_split(b, d_in, r, sums_floats, RESIDENT);
+            e = launch_xl(x_in, b, d_in, l, r, x, x.slabs > 1 ? sums : nullptr, T, s);
+            if (e == hipSuccess && x.slabs > 1) e = launch_xl_reduce(sums, x.slabs, b, r, T, s);
+        } else {
+            e = skinny_product(x_in, b, d_in, l, true, r, T, Lt,
+                               b > XL_SMALL_MAX_TOKENS && dense_tn_plain_partial_bytes(b, r) ? sums : nullptr, s);
+        }
         if (e != hipSuccess) return finish(e);
+    } else {
+        T = nullptr;
     }
-    if (spmm_stream_fits(b, d_in)) {                          // inference-size batch: one HBM-bound pass over the packed weight
-        float* slices = workspace && spmm_rows_partial_bytes(b, d_out, d_in)
-                            ? (float*)(ws + adapter_workspace_bytes(b, d_in, d_out, adapter ? r : 0)) : nullptr;
-        return finish(launch_spmm_stream(x, b, wv, wm, d_out, d_in, adapter ? T : nullptr,
-                                         adapter ? (const bf16_t*)R_or_null : nullptr, adapter ? r : 0, (bf16_t*)Y,
-                                         slices, s));
+    if (few) {                                                // inference-size batch: one HBM-bound pass over the packed weight
+        float* slices = workspace && spmm_rows_partial_bytes(b, d_out, d_in) ? (float*)after : nullptr;
+        return finish(launch_spmm_stream(x_in, b, wv, wm, d_out, d_in, T, R, r, (bf16_t*)Y, slices, s));
     }
-    // With scratch memory a batch of a few dozen to a few hundred tokens is split over K as well.
-    float* slabs = workspace && spmm_slab_count(b, d_out, d_in) > 0
-                       ? (float*)(ws + adapter_workspace_bytes(b, d_in, d_out, adapter ? r : 0)) : nullptr;
-    const bf16_t* B2 = adapter ? T : nullptr;
-    const bf16_t* A2 = adapter ? (const bf16_t*)R_or_null : nullptr;   // as stored, [r][d_out]: the kernels take it k-major
-    const int64_t K2 = adapter ? -r : 0;
-    if (slabs) return finish(launch_spmm_slabs(x, b, wv, wm, d_out, d_in, B2, A2, K2, (bf16_t*)Y, slabs, s));
-    return finish(launch_spmm(x, b, wv, wm, d_out, d_in, B2, A2, K2, (bf16_t*)Y, s));
+    if (slabs) {
+        ad.T = T;
+        return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
+    }
+    // R as stored, [r][d_out]: the kernels take it k-major
+    return finish(launch_spmm(x_in, b, wv, wm, d_out, d_in, T, R, -r, (bf16_t*)Y, s));
 }
 
 slope_status slope_spmm_fwd(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,

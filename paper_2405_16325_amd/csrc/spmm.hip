@@ -34,6 +34,7 @@
 // LDS and queues global loads, then they swap (two barriers per k-step), so every SIMD's matrix
 // pipe always has a wavefront feeding it.  Loads run two k-steps ahead of their use.
 #include "pipeline.h"
+#include "skinny.h"
 
 namespace {
 
@@ -234,22 +235,58 @@ __device__ __forceinline__ int64_t quad_offset(int quad, int ksteps, int half) {
 // a time and its metadata four, so at the end of a row those fetches would run past it.  They are moved back to end with
 // the row instead: an odd last k-step then sits where the second step of its pair (the second 8 bytes of its 16 of
 // metadata) belongs, and that is where it is read.  A template parameter, so that whole quads pay nothing for it.
-template <int BM, int BN, bool TAIL>
+//
+// SPLIT: the k range is cut into slabs of slab_steps k-steps (whole quads), which leave fp32 partial sums in slabs[slab].
+// The (tile, slab) pairs are dealt to the XCDs in eight equal runs, slab by slab (a slab's tiles share its tokens in L2),
+// the token tiles of a weight tile side by side.  A grid with the slabs in blockIdx.y gave 36 tiles per slab to seven of
+// the XCDs, five each, and one to the last (128 tokens, 9216 x 9216: 33.6 -> 27.7 us).
+// Such a launch may have workgroups of a second kind: they compute the sums of T = X L (see xl_split_kernel) that the
+// kernel after this one needs, on compute units that the product leaves idle.
+struct SplitJob {
+    int nslabs, slab_steps;
+    float* slabs;
+    const bf16_t* L;                                          // or null
+    float* Q;
+    int r, k_per, xl_slabs;
+};
+
+template <int BM, int BN, bool TAIL, bool SPLIT>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __restrict__ B, int n,
                                                             const bf16_t* __restrict__ Av,
                                                             const uint8_t* __restrict__ Am, int m, int K,
                                                             const bf16_t* __restrict__ B2,
                                                             const bf16_t* __restrict__ A2, int K2,
                                                             bf16_t* __restrict__ C, int tiles_m, int tiles_n,
-                                                            int slab_steps, float* __restrict__ slabs) {
+                                                            SplitJob job) {
     using S = SpmmSmem<BM, BN>;
     constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront
     constexpr int A_LD = BM / 64, B_LD = BN / 64;            // 1 KiB loads per wavefront: per pair, per step
     constexpr int M_WAVES = BM / 32;                         // wavefronts that load metadata (32 rows each)
     extern __shared__ __align__(16) uint8_t smem[];
 
-    int tm, tn;
-    if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+    int tm, tn, slab = 0;
+    if constexpr (SPLIT) {
+        static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
+        const int tiles = tiles_m * tiles_n, run = (tiles * job.nslabs + XCDS - 1) / XCDS;
+        const int xcd = (int)blockIdx.x % XCDS, pos = (int)blockIdx.x / XCDS;
+        if (pos >= run) {
+            const int id = (pos - run) * XCDS + xcd;
+            const int xl_tiles_r = (job.r + SK_BJ - 1) / SK_BJ, xl_tiles = xl_tiles_r * ((n + SK_BI - 1) / SK_BI);
+            const int part = id / xl_tiles, tile = id % xl_tiles;
+            if (part < job.xl_slabs)
+                skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * job.k_per, min(K, (part + 1) * job.k_per),
+                                         tile / xl_tiles_r * SK_BI, tile % xl_tiles_r * SK_BJ, nullptr,
+                                         job.Q + (size_t)part * n * job.r, smem);
+            return;
+        }
+        const int item = xcd * run + pos;
+        if (item >= tiles * job.nslabs) return;
+        slab = item / tiles;
+        tn = item % tiles % tiles_n;
+        tm = item % tiles / tiles_n;
+    } else {
+        if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+    }
     const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -294,10 +331,9 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     const int b_rd = S::B_OFF + (wn * NF) * 2048;
     const int m_rd = S::M_OFF + wm * MF * 512 + l16 * 16 + lq * 2;
 
-    // A split over k: workgroup row blockIdx.y takes k-steps [k_first, k_first + ksteps) and leaves
-    // fp32 partial sums in its slab; without a slab buffer there is one row and it takes all of K.
-    const int k_first = blockIdx.y * slab_steps;              // a multiple of 4
-    const int ksteps = K / 64 - k_first < slab_steps ? K / 64 - k_first : slab_steps;   // a multiple of 4 unless TAIL
+    const int k_first = SPLIT ? slab * job.slab_steps : 0;    // a multiple of 4
+    // a multiple of 4 unless TAIL
+    const int ksteps = SPLIT && K / 64 - k_first > job.slab_steps ? job.slab_steps : K / 64 - k_first;
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) a_src[i] += (size_t)k_first * 64;
 #pragma unroll
@@ -386,8 +422,8 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     // the dense extension is added once, by the first slab
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
     extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
-                                     blockIdx.y == 0 ? K2 : 0, C, smem, m0, n0,
-                                     slabs ? slabs + (size_t)blockIdx.y * (size_t)n * (size_t)m : nullptr);
+                                     slab == 0 ? K2 : 0, C, smem, m0, n0,
+                                     SPLIT ? job.slabs + (size_t)slab * (size_t)n * (size_t)m : nullptr);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -855,28 +891,38 @@ hipError_t launch_generic(const bf16_t* B, int64_t n, const bf16_t* Av, const ui
     return launch_generic_as<4, 4, 1>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
 }
 
-template <int BM, int BN, bool TAIL>
+template <int BM, int BN, bool TAIL, bool SPLIT>
 hipError_t launch_tile_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, int nslabs, int slab_steps,
-                          float* slabs) {
+                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job) {
     using S = SpmmSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
-    auto kern = spmm_kernel<BM, BN, TAIL>;
-    hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL>>(S::TOTAL);
+    auto kern = spmm_kernel<BM, BN, TAIL, SPLIT>;
+    hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    if (!slabs) { nslabs = 1; slab_steps = (int)(K / 64); }
-    kern<<<dim3((unsigned)super_grid(tiles_m, tiles_n), (unsigned)nslabs), dim3(SPMM_THREADS), S::TOTAL, s>>>(
-        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, slab_steps, slabs);
+    int grid = super_grid(tiles_m, tiles_n);
+    if (SPLIT) {
+        const int xl = job.L ? job.xl_slabs * ((job.r + SK_BJ - 1) / SK_BJ) * (int)((n + SK_BI - 1) / SK_BI) : 0;
+        grid = ((tiles_m * tiles_n * job.nslabs + XCDS - 1) / XCDS + (xl + XCDS - 1) / XCDS) * XCDS;
+    }
+    kern<<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C,
+                                                                    tiles_m, tiles_n, job);
     return hipGetLastError();
 }
 
 template <int BM, int BN>
 hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, int nslabs = 1,
-                       int slab_steps = 0, float* slabs = nullptr) {
-    return K % 256 == 0 ? launch_tile_as<BM, BN, false>(B, n, Av, Am, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs)
-                        : launch_tile_as<BM, BN, true>(B, n, Av, Am, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs);
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
+    auto launch = K % 256 == 0 ? launch_tile_as<BM, BN, false, false> : launch_tile_as<BM, BN, true, false>;
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, SplitJob{});
+}
+
+// a split over k
+template <int BN>
+hipError_t launch_slab_tiles(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                             const bf16_t* B2, const bf16_t* A2, int64_t K2, hipStream_t s, const SplitJob& job) {
+    auto launch = K % 256 == 0 ? launch_tile_as<256, BN, false, true> : launch_tile_as<256, BN, true, true>;
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, nullptr, s, job);
 }
 
 // C[idx] = bf16( sum over slabs, in order, of P[s][idx] ), four elements per thread
@@ -967,16 +1013,35 @@ size_t spmm_slab_bytes(int64_t n, int64_t m, int64_t K) {
     return (size_t)spmm_slab_count(n, m, K) * (size_t)n * (size_t)m * 4;
 }
 
-hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
-                             int64_t K, const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, float* slabs,
-                             hipStream_t s) {
-    const int want = spmm_slab_count(n, m, K);
+static int slab_steps_of(int64_t K, int want) {               // k-steps per slab, whole quads
     const int64_t quads = (K + 255) / 256;
-    const int slab_steps = (int)((quads + want - 1) / want) * 4;
+    return (int)((quads + want - 1) / want) * 4;
+}
+
+// Split of T = X L into workgroups beside the slabs' tiles: on the compute units that their single round leaves idle, and
+// not longer than a slab (a chunk of 32 rows of L takes a wavefront about as long as a k-step takes a tile).
+bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, XlSplit& x) {
+    const int want = spmm_slab_count(n, m, K);
+    if (want < 1) return false;
+    const int64_t groups = ((m + 255) / 256) * (n <= 64 ? 1 : (n + 127) / 128) * want;
+    const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ);
+    if (groups + tiles > RESIDENT) return false;
+    x = xl_split(n, K, r, max_floats, RESIDENT - groups);
+    return x.steps <= slab_steps_of(K, want);
+}
+
+hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
+                             int64_t K, const SlabAdapter& ad, bf16_t* C, float* slabs, hipStream_t s) {
+    const int want = spmm_slab_count(n, m, K);
+    const int slab_steps = slab_steps_of(K, want);
     const int nslabs = (int)((K / 64 + slab_steps - 1) / slab_steps);       // <= want
-    hipError_t e = n <= 64 ? launch_tile<256, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs)
-                           : launch_tile<256, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s, nslabs, slab_steps, slabs);
+    const SplitJob job = {nslabs, slab_steps, slabs, ad.T ? nullptr : ad.L, ad.Q, (int)ad.r, ad.x.k_per, ad.x.slabs};
+    const bf16_t* A2 = ad.T ? ad.R : nullptr;                 // as stored, k-major
+    const int64_t K2 = ad.T ? -ad.r : 0;
+    hipError_t e = n <= 64 ? launch_slab_tiles<64>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, s, job)
+                           : launch_slab_tiles<128>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, s, job);
     if (e != hipSuccess) return e;
+    if (ad.r && !ad.T) return launch_adapter_finish(slabs, nslabs, n, m, ad.Q, ad.x.slabs, ad.R, ad.r, C, s);
     const size_t count4 = (size_t)n * (size_t)m / 4;
     slab_reduce_kernel<<<dim3((unsigned)((count4 + 255) / 256)), dim3(256), 0, s>>>((const f32x4*)slabs, nslabs, count4,
                                                                                    (u32x2*)C);

@@ -9,15 +9,14 @@
 //     no barrier in the main loop, only the wavefront's own s_waitcnt;
 //   - the partial tiles are summed in a fixed order through LDS (bit-identical runs); before that
 //     the adapter term is added on dense MFMA from T = X L and the factor R as stored.
-// T itself comes from a split over d_in (xl_mfma_kernel, fp32 partial sums in the workspace)
-// followed by a fixed-order reduction that rounds to bf16 (xl_reduce_kernel).
+// T itself comes from a split over d_in (xl_split_kernel, fp32 partial sums in the workspace) that is added, in a
+// fixed order, and rounded to bf16 by xl_reduce_kernel or where T is used (adapter_finish_kernel).
 // (A first version kept the operands in registers and moved them into MFMA order with ds_bpermute;
 // the permutes capped a compute unit near 23 B/ns, against 44 B/ns with the LDS rings.)
 #include "pipeline.h"
+#include "skinny.h"
 
 namespace {
-
-constexpr int XL_CHUNK = 64;        // rows of L per chunk of the X L split
 
 union StB { u32x4 u[2]; bf16x16 v; };
 union StA { u32x4 u; bf16x8 v; };
@@ -483,104 +482,119 @@ __global__ void __launch_bounds__(256) rows_sum_kernel(const f32x4* __restrict__
     C[idx] = o.u;
 }
 
-// P[c][t][j] = sum over the rows i of slab c of X[t][i] * L[i][j]   (fp32 partial sums of T = X L for
-// up to XL_SMALL_MAX_TOKENS tokens, on MFMA).  L is k-major (rows = d_in), the wrong way round for an
-// MFMA operand, so a slab of it is staged in LDS as stored and read back with the transposing read
-// ds_read_b64_tr_b16: in each block of 16 lanes, lane s receives four consecutive rows (k) of
-// column s.  (A first version with fp32 multiply-adds and token values broadcast from LDS took
-// 24 us where this takes 6, at 9216 x 128 and 64 tokens, and was 2 us slower even for one token.)  D rows are the
-// columns of L, D columns the tokens: a lane ends up with four consecutive columns of one token.
-//   workgroup = slab c of 64 * subs rows x 128 columns (blockIdx.y) x 128 tokens (blockIdx.z);
-//   wavefront w takes columns 32 w .. 32 w + 31; token rows come straight from global memory
-//   (k-contiguous).
-constexpr int XLM_PITCH = 128 * 2 + 32;      // bytes per staged row of L: pitch % 128 == 32 keeps the
-                                             // four rows of a transposing read on distinct banks
-__global__ void __launch_bounds__(256) xl_mfma_kernel(const bf16_t* __restrict__ X, int n, int d_in,
-                                                      const bf16_t* __restrict__ L, int r, int subs,
-                                                      float* __restrict__ P) {
-    extern __shared__ __align__(16) uint8_t smem[];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int l16 = lane & 15, lq = lane >> 4;
-    const int c = blockIdx.x, j0 = blockIdx.y * 128;
-    const int k0 = c * XL_CHUNK * subs;
-    int rows = d_in - k0;                                    // d_in % 64 == 0: whole chunks
-    if (rows > XL_CHUNK * subs) rows = XL_CHUNK * subs;
-    if (rows <= 0) return;                                   // uniform
+// T = X L for up to XL_SMALL_MAX_TOKENS tokens: tiles of 32 tokens x 64 columns of L (as stored, see skinny.h), one per
+// blockIdx.x, rows [k_per y, k_per (y + 1)) of L for blockIdx.y = y: fp32 sums into Q[y][n][r], or T itself if Q is null
+// (one slab).  The operands are small and come from the caches, so what counts is the chain of latencies: eight
+// wavefronts share out a slab's chunks of 32 rows, which takes few slabs to be short (36864 x 128 for 16 tokens: 8.0 ->
+// 4.9 us against 128-column tiles of four wavefronts; 768 x 32 for one token needs no second kernel: 6.6 -> 3.8 us).
+__global__ void __launch_bounds__(SK_WAVES * 64) xl_split_kernel(const bf16_t* __restrict__ X, int n, int d_in,
+                                                                 const bf16_t* __restrict__ L, int r, int k_per,
+                                                                 float* __restrict__ Q, bf16_t* __restrict__ T) {
+    __shared__ __align__(16) uint8_t smem[SK_LDS];
+    const int tiles_r = (r + SK_BJ - 1) / SK_BJ, k0 = blockIdx.y * k_per;
+    skinny_tile<false, true>(X, d_in, L, r, n, r, k0, min(d_in, k0 + k_per), (int)(blockIdx.x / tiles_r) * SK_BI,
+                             (int)(blockIdx.x % tiles_r) * SK_BJ, T, Q ? Q + (size_t)blockIdx.y * n * r : nullptr, smem);
+}
 
-    // stage the slab: 16 pieces of 16 bytes per row, 16 rows per pass of the workgroup
-    {
-        const int pc = t & 15, col = j0 + pc * 8;
-        u32x4 v[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            int row = u * 16 + (t >> 4);
-            v[u] = (u32x4){0u, 0u, 0u, 0u};
-            if (row < rows && col < r) v[u] = *(const u32x4*)(L + (size_t)(k0 + row) * r + col);
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            int row = u * 16 + (t >> 4);
-            if (row < rows) *(u32x4*)(smem + row * XLM_PITCH + pc * 16) = v[u];
-        }
+// Eight columns of T = X L from its partial sums Q[slabs][n][r], added in slab order and rounded to bf16
+__device__ __forceinline__ u32x4 t_piece(const float* __restrict__ Q, int slabs, int n, int r, int tok, int col) {
+    const float* q = Q + (size_t)tok * r + col;
+    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll 4
+    for (int sl = 0; sl < slabs; ++sl) {
+        const f32x4 a = *(const f32x4*)q, b = *(const f32x4*)(q + 4);
+        q += (size_t)n * r;
+        lo[0] += a[0]; lo[1] += a[1]; lo[2] += a[2]; lo[3] += a[3];
+        hi[0] += b[0]; hi[1] += b[1]; hi[2] += b[2]; hi[3] += b[3];
     }
-    __syncthreads();
+    union { __bf16 h[8]; u32x4 u; } o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { o.h[e] = (__bf16)lo[e]; o.h[4 + e] = (__bf16)hi[e]; }
+    return o.u;
+}
 
-    const int t0 = blockIdx.z * 128;
-    const int ntf = ((n - t0 < 128 ? n - t0 : 128) + 15) / 16;   // token fragments of this workgroup, at most 8
-    const bf16_t* x_row[8];
+// C = bf16( sum over the slices, in order, of P[slice][n][m]  +  T R ), T = bf16 of the sum of Q[q_slabs][n][r] in slab
+// order: the second kernel of a product split over k, with the adapter term.  A workgroup takes 32 tokens x 64 features,
+// a wavefront 16 of the features; chunks of 128 of the rank are staged as in the kernels above.  Bound by its chain of
+// latencies (128 tokens, 9216 x 9216, rank 128, 6 slices: 10.3 us, where the sum alone takes 5.2 and the kernels it saves,
+// X L before the product and its reduction, took 12.7).  The sliced small-batch kernel gains nothing from it (72 + 8.6 us
+// against 72 + 5.3 + 5.2), nor any small-batch kernel from adding up the sums of T itself (65.8 -> 75.9 us for one token).
+constexpr int AF_TOK = 32, AF_FEAT = 64;
+__global__ void __launch_bounds__(256) adapter_finish_kernel(const float* __restrict__ P, int slices, int n, int m,
+                                                             const float* __restrict__ Q, int q_slabs,
+                                                             const bf16_t* __restrict__ R, int r, bf16_t* __restrict__ C) {
+    constexpr int TP = 128 * 2 + 16, RP = 160;                // bytes per staged row of T and of R's tile
+    __shared__ __align__(16) uint8_t smem[AF_TOK * TP + 128 * RP];
+    uint8_t* const t_lds = smem;
+    uint8_t* const r_lds = smem + AF_TOK * TP;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, lq = lane >> 4;
+    const int f0 = blockIdx.x * AF_FEAT, t0 = blockIdx.y * AF_TOK;
+    const int feat = f0 + 16 * wave + 4 * lq;                 // the lane's four features (m % 8 == 0: inside or outside together)
+    // the first slices' sums are requested before the adapter's operands
+    constexpr int AHEAD = 8;
+    f32x4 p[2][AHEAD];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int tok = t0 + 16 * j + l16;
-        x_row[j] = X + (size_t)(tok < n ? tok : t0) * d_in + k0 + lq * 8;
-    }
-    f32x4 acc[2][8];
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int sl = 0; sl < AHEAD; ++sl) {
+            const int tok = t0 + 16 * j + l16;
+            p[j][sl] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (tok < n && feat < m && sl < slices) p[j][sl] = *(const f32x4*)(P + ((size_t)sl * n + tok) * m + feat);
+        }
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int kc = 0; kc < r; kc += 128) {
+        const int kn = r - kc < 128 ? r - kc : 128;           // a multiple of 32
+        if (kc > 0) __syncthreads();                          // the last chunk is consumed
+        u32x4 rv[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    // lane (s = l16, q = lq) points at slab row 8 q + 4 h + s / 4, column 4 (s % 4) of a 16-column
-    // fragment; it receives k = 8 q + 4 h .. + 3 of column s
-    const uint8_t* tr = smem + (8 * lq + (l16 >> 2)) * XLM_PITCH + 2 * (32 * wave + 4 * (l16 & 3));
-    const int steps = rows / 32;
-    u32x4 xb[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < ntf) xb[j] = *(const u32x4*)x_row[j];
-    for (int st = 0; st < steps; ++st) {
-        StA af[2], bf[8];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            union { s16x4 h[2]; bf16x8 v; } x;
-            x.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (s16x4 __attribute__((address_space(3)))*)(tr + st * 32 * XLM_PITCH + 32 * i));
-            x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (s16x4 __attribute__((address_space(3)))*)(tr + (st * 32 + 4) * XLM_PITCH + 32 * i));
-            af[i].v = x.v;
+        for (int u = 0; u < 4; ++u) {
+            const int idx = t + 256 * u, k = idx >> 3, sg = idx & 7;
+            rv[u] = (u32x4){0u, 0u, 0u, 0u};
+            if (k < kn && f0 + 8 * sg < m) rv[u] = *(const u32x4*)(R + (size_t)(kc + k) * m + f0 + 8 * sg);
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bf[j].u = xb[j];
-        if (st + 1 < steps) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (j < ntf) xb[j] = *(const u32x4*)(x_row[j] + (st + 1) * 32);
+        for (int u = 0; u < 2; ++u) {
+            const int idx = t + 256 * u, tok = idx >> 4, pc = idx & 15;
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (t0 + tok < n && pc * 8 < kn) v = t_piece(Q, q_slabs, n, r, t0 + tok, kc + pc * 8);
+            *(u32x4*)(t_lds + tok * TP + pc * 16) = v;
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (j < ntf) {
+        for (int u = 0; u < 4; ++u) {
+            const int idx = t + 256 * u;
+            *(u32x4*)(r_lds + (idx >> 3) * RP + (idx & 7) * 16) = rv[u];
+        }
+        __syncthreads();
+        const uint8_t* ra = r_lds + (8 * lq + (l16 >> 2)) * RP + 2 * (16 * wave + 4 * (l16 & 3));
+        const uint8_t* tb = t_lds + l16 * TP + lq * 16;
+        for (int ks = 0; ks * 32 < kn; ++ks) {
+            union { s16x4 h[2]; bf16x8 v; } a;
+            a.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(ra + ks * 32 * RP));
+            a.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(ra + (ks * 32 + 4) * RP));
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i].v, bf[j].v, acc[i][j], 0, 0, 0);
+            for (int j = 0; j < 2; ++j) {
+                StA b;
+                b.u = *(const u32x4*)(tb + j * 16 * TP + ks * 64);
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc[j], 0, 0, 0);
             }
+        }
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int tok = t0 + 16 * j + l16;
-        if (tok >= n) continue;
+    for (int j = 0; j < 2; ++j) {
+        const int tok = t0 + 16 * j + l16;
+        if (tok >= n || feat >= m) continue;
+        f32x4 v = p[j][0];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            int col = j0 + 32 * wave + 16 * i + 4 * lq;
-            if (col < r) *(f32x4*)(P + ((size_t)c * n + tok) * r + col) = acc[i][j];
+        for (int sl = 1; sl < AHEAD; ++sl) { v[0] += p[j][sl][0]; v[1] += p[j][sl][1]; v[2] += p[j][sl][2]; v[3] += p[j][sl][3]; }
+#pragma unroll 4
+        for (int sl = AHEAD; sl < slices; ++sl) {
+            const f32x4 w = *(const f32x4*)(P + ((size_t)sl * n + tok) * m + feat);
+            v[0] += w[0]; v[1] += w[1]; v[2] += w[2]; v[3] += w[3];
         }
+        union { __bf16 h[4]; u32x2 u; } o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)(v[e] + acc[j][e]);
+        *(u32x2*)(C + (size_t)tok * m + feat) = o.u;
     }
 }
 
@@ -709,9 +723,9 @@ hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, 
     return launch_stream_lds<2, 4, 2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, s);
 }
 
-// T = X L for few tokens (up to XL_SMALL_MAX_TOKENS), split over d_in; scratch holds xl_small_scratch_bytes.
-// Slabs of L per workgroup: up to four chunks of 64 rows (smaller partial sums) as long as the launch
-// still has a workgroup for every compute unit.
+// Scratch for the partial sums of T = X L: slabs of up to four chunks of 64 rows of L as long as there are still
+// 256 workgroups of 128 columns x 128 tokens (launch_xl takes fewer slabs than that).
+constexpr int XL_CHUNK = 64;
 int xl_subs(int64_t n, int64_t d_in, int64_t r) {
     const int64_t per_slab = ((r + 127) / 128) * ((n + 127) / 128);   // workgroups per slab
     for (int subs = 4; subs > 1; subs /= 2)
@@ -724,17 +738,38 @@ size_t xl_small_scratch_bytes(int64_t n, int64_t d_in, int64_t r) {
     return (size_t)((d_in + rows - 1) / rows) * (size_t)n * (size_t)r * 4;
 }
 
-hipError_t launch_xl_small(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, float* scratch,
-                           bf16_t* T, hipStream_t s) {
-    const int subs = xl_subs(n, d_in, r);
-    const int slabs = (int)((d_in + XL_CHUNK * subs - 1) / (XL_CHUNK * subs));
-    const int lds = XL_CHUNK * subs * XLM_PITCH;
-    hipError_t e = allow_dynamic_lds<xl_mfma_kernel>(XL_CHUNK * 4 * XLM_PITCH);   // the largest slab (subs <= 4)
-    if (e != hipSuccess) return e;
-    dim3 grid((unsigned)slabs, (unsigned)((r + 127) / 128), (unsigned)((n + 127) / 128));
-    xl_mfma_kernel<<<grid, dim3(256), lds, s>>>(X, (int)n, (int)d_in, L, (int)r, subs, scratch);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+// Slabs of T = X L, within max_floats of sums and max_groups workgroups: one, which needs no second kernel, while that
+// leaves a wavefront no more than XL_STEPS chunks of 32 rows of L; else as many as still give every wavefront a chunk.
+constexpr int XL_STEPS = 4;
+XlSplit xl_split(int64_t n, int64_t d_in, int64_t r, int64_t max_floats, int64_t max_groups) {
+    const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ), chunks = d_in / 32;
+    int64_t slabs = (chunks + SK_WAVES - 1) / SK_WAVES;
+    if (slabs <= XL_STEPS) slabs = 1;
+    const int64_t fill = max_groups / tiles, held = max_floats / (n * r);
+    if (slabs > fill) slabs = fill;
+    if (slabs > held) slabs = held;
+    if (slabs < 1) slabs = 1;
+    const int64_t per = (chunks + slabs - 1) / slabs;
+    return {(int)((chunks + per - 1) / per), (int)(per * 32), (int)((per + SK_WAVES - 1) / SK_WAVES)};
+}
+
+hipError_t launch_xl(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, const XlSplit& x, float* Q,
+                     bf16_t* T, hipStream_t s) {
+    const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ);
+    xl_split_kernel<<<dim3((unsigned)tiles, (unsigned)x.slabs), dim3(SK_WAVES * 64), 0, s>>>(
+        X, (int)n, (int)d_in, L, (int)r, x.k_per, Q, T);
+    return hipGetLastError();
+}
+
+hipError_t launch_xl_reduce(const float* Q, int slabs, int64_t n, int64_t r, bf16_t* T, hipStream_t s) {
     const int count = (int)(n * r);
-    xl_reduce_kernel<<<dim3((unsigned)((count + 31) / 32)), dim3(256), 0, s>>>(scratch, slabs, count, T);
+    xl_reduce_kernel<<<dim3((unsigned)((count + 31) / 32)), dim3(256), 0, s>>>(Q, slabs, count, T);
+    return hipGetLastError();
+}
+
+hipError_t launch_adapter_finish(const float* P, int slices, int64_t n, int64_t m, const float* Q, int q_slabs,
+                                 const bf16_t* R, int64_t r, bf16_t* C, hipStream_t s) {
+    adapter_finish_kernel<<<dim3((unsigned)((m + 63) / 64), (unsigned)((n + 31) / 32)), dim3(256), 0, s>>>(
+        P, slices, (int)n, (int)m, Q, q_slabs, R, (int)r, C);
     return hipGetLastError();
 }

@@ -103,3 +103,20 @@ def test_update_of_both_copies(d_out, d_in):
                                            (5, 8, 8, 1032), (8, 8, 72, 56)])
 def test_column_masks(n, m, kind, rows, cols):
     nm.test_prune_mask_rows_then_columns(n, m, kind, rows, cols)
+
+
+# products split over k with an adapter: X L beside the product and in a launch of its own (no compute unit left, a
+# large rank), one slab of it and several, token and feature tiles of the second kernel that are not full, more tokens
+# than the split of X L takes
+@pytest.mark.parametrize("b,d_out,d_in,r", [(128, 9216, 9216, 128), (33, 520, 8192, 32), (64, 1000, 8256, 512),
+                                            (300, 2304, 5120, 160), (500, 5112, 8192, 512), (129, 256, 16384, 96),
+                                            (700, 512, 8256, 64)])
+def test_split_products_with_adapters(b, d_out, d_in, r):
+    assert sl.slope_spmm_fwd_plan(b, d_in, d_out, r)["product"] == 1
+    check_layer(b, d_out, d_in, r, backward=False)
+
+
+# X L of a few tokens: one slab and many, fewer chunks of 32 rows than wavefronts, ranks that fill no tile
+@pytest.mark.parametrize("b,d_out,d_in,r", [(1, 264, 128, 32), (32, 512, 1088, 96), (17, 2048, 9280, 512), (400, 1024, 2048, 160)])
+def test_adapter_product_of_few_tokens(b, d_out, d_in, r):
+    check_layer(b, d_out, d_in, r, backward=False)
