@@ -16,6 +16,8 @@
 // D rows are d_in and D columns d_out, so a lane's four accumulators (column l%16, rows
 // 4*(l/16) .. +3) are exactly one group of four of W^R's row: the epilogue picks two of them with
 // the group's metadata nibble and stores one 4-byte pair of the packed gradient.
+#include <numeric>
+
 #include "pipeline.h"
 
 namespace {
@@ -327,30 +329,49 @@ struct SplitSmem {
 };
 
 // TAIL: the tiles left over after the last full round of 256.  Run as a round of their own they would
-// keep a few compute units busy for a whole tile's time while the rest of the chip idles.  Instead each
-// of them (positions first_tile .. first_tile + tail_tiles - 1 of the tile order) is cut along k into
-// slabs of slab_steps k-steps; workgroup w takes tile w % tail_tiles, slab w / tail_tiles, and leaves its
-// fp32 accumulators in partial[w] in register order; tail_reduce_kernel adds the slabs and stores.
+// keep some compute units busy for a whole tile's time while the rest of the chip idles.  Instead they (positions
+// first_tile .. of the tile order) are taken in bundles of consecutive tiles, the bundles' k-steps are laid end to end and
+// cut into equal shares, one for each lane: as many workgroups of one XCD as a bundle has tiles, which walk the share in
+// step, one tile each, and so find each other's operand panels in the XCD's L2 (shares per workgroup instead, laid along
+// the tiles: 2.2 to 2.4 us per k-step, from HBM; a whole round 1.36).  A share lies in one bundle or in a few; a workgroup
+// leaves fp32 accumulators in register order for each tile it touches, and tail_finish_kernel adds a tile's parts and
+// stores.  Lane w's part of bundle c is number w + c, less the bundle boundaries up to c that are share boundaries too
+// (every aligned-th): no gaps, a bundle's parts one after the other.
+// 400 tiles (5120 x 5120, 16384 tokens): 617 us as two rounds, 359 + 217 + 25 with the 144 leftover ones cut; 36864 x 9216,
+// 64 leftover tiles in shares per workgroup before: 122 + 24, now 104 + 17.
+struct TailPlan { int first_tile, tiles, bundle, lanes_per_xcd, lanes, share, aligned, parts; double steps; };
+
 template <int EPI, bool TAIL>
 __global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t* __restrict__ At, int m,
                                                                     const bf16_t* __restrict__ Bt, int n, int kp,
                                                                     int ld, const uint8_t* __restrict__ meta,
                                                                     bf16_t* __restrict__ out, int tiles_m,
-                                                                    int tiles_n, int first_tile, int tail_tiles,
-                                                                    int slab_steps, f32x4* __restrict__ partial) {
+                                                                    int tiles_n, TailPlan tail,
+                                                                    f32x4* __restrict__ partial) {
     using S = SplitSmem;
     constexpr int MF = 8, NF = 4, WM = 128;                  // wavefront tile 128 x 64, 2 x 4 wavefronts
     extern __shared__ __align__(16) uint8_t smem[];
 
-    int tm, tn, k_first = 0;
+    int tm, tn, k_first = 0, ksteps = kp / 64;
+    // TAIL: this workgroup's lane and its tile in a bundle; [at, at_end) the k-steps of the lane's share that are left
+    const int slot = (int)blockIdx.x / XCDS, member = slot % tail.bundle;
+    const int lane_id = ((int)blockIdx.x % XCDS) * tail.lanes_per_xcd + slot / tail.bundle;
+    if (TAIL && (slot / tail.bundle >= tail.lanes_per_xcd || lane_id >= tail.lanes)) return;
+    int at = lane_id * tail.share, at_end = at + tail.share;
+next_part:
     if (TAIL) {
-        tile_of_position(first_tile + (int)blockIdx.x % tail_tiles, tiles_m, tiles_n, tm, tn);
-        k_first = ((int)blockIdx.x / tail_tiles) * slab_steps;
+        const int c = at / (kp / 64), tile = c * tail.bundle + member;
+        k_first = at - c * (kp / 64);
+        if (tile >= tail.tiles) return;                       // the end of the row, or a member the last bundle does not have
+        ksteps = at_end - at < kp / 64 - k_first ? at_end - at : kp / 64 - k_first;
+        tile_of_position(tail.first_tile + tile, tiles_m, tiles_n, tm, tn);
     } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
         return;
     }
     const int m0 = tm * S::BM, n0 = tn * S::BN;
-    const int t = threadIdx.x, lane = t & 63;
+    int t = threadIdx.x;
+    if (TAIL) asm volatile("" : "+v"(t));                     // the lane's coordinates are derived again per part (no spills)
+    const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int group = wave >> 2;                             // = column half of the tile
     const int wm = wave & 1, wn = wave >> 1;
@@ -369,8 +390,6 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t
         a_src[q] = (const uint8_t*)At + (size_t)ra * ld * 2 + sw16 + (size_t)k_first * 128;
         b_src[q] = (const uint8_t*)Bt + (size_t)rb * ld * 2 + sw16 + (size_t)k_first * 128;
     }
-    // k-steps of this workgroup (the host leaves no slab empty)
-    const int ksteps = TAIL ? (kp / 64 - k_first < slab_steps ? kp / 64 - k_first : slab_steps) : kp / 64;
     // the four loads a wavefront queues per phase, one at a time (ks clamped: the look-ahead of the
     // last steps re-reads the last one)
     auto issue_a = [&](int half, int ks, int i) {            // 8 rows of rows 128 half .. +127 of A(ks)
@@ -466,58 +485,74 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t
 #undef ODD_LOADS
     WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
     if (TAIL) {
-        f32x4* dst = partial + (size_t)blockIdx.x * (MF * NF * TN_THREADS) + t;
+        const int c = at / (kp / 64);
+        f32x4* dst = partial + (int64_t)((lane_id + c - c / tail.aligned) * tail.bundle + member) * (MF * NF * TN_THREADS) + t;
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int j = 0; j < NF; ++j) dst[(i * NF + j) * TN_THREADS] = acc[i][j];
-        return;
+        at += ksteps;
+        if (at >= at_end) return;
+        wg_barrier();                                         // every wavefront's reads and look-ahead loads are over
+        goto next_part;
     }
     if (EPI == EPI_PLAIN) store_plain<MF, NF>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, l16, lq, out, nullptr);
     else store_masked_packed<MF, NF, S::BM, S::BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out,
                                                    smem);
 }
 
-// Second pass of the tail, in two kernels.  tail_sum_kernel adds the slabs element by element in slab
-// order into slab 0 (slab sl of a tile lies tail_tiles tiles further on in `partial`); it has a workgroup
-// per 256 elements, because the few workgroups of tail_reduce_kernel alone would read the partial sums at
-// a small fraction of the chip's bandwidth.  tail_reduce_kernel then loads a tile's sums in the register
-// layout dense_tn_split_kernel left them in and stores the tile through that kernel's epilogue.
-__global__ void __launch_bounds__(256) tail_sum_kernel(f32x4* __restrict__ partial, int nslabs, size_t slab_stride4,
-                                                       size_t count4) {
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= count4) return;
-    f32x4 v = partial[idx];
-    for (int sl = 1; sl < nslabs; ++sl) {
-        f32x4 w = partial[(size_t)sl * slab_stride4 + idx];
-        v[0] += w[0]; v[1] += w[1]; v[2] += w[2]; v[3] += w[3];
-    }
-    partial[idx] = v;
-}
-
-constexpr int TAIL_REDUCE_LDS = SplitSmem::BN * (SplitSmem::BM + 16);
-template <int EPI>
-__global__ void __launch_bounds__(TN_THREADS) tail_reduce_kernel(const f32x4* __restrict__ partial, int m, int n,
+// Second pass of the tail: workgroup (leftover tile i, fragment column j) adds the tile's parts, in order, for one of the
+// four fragment columns of every wavefront of the kernel above, and stores the pairs that W^R keeps: 64 rows (d_out) of
+// the tile through LDS, as store_masked_packed does.  (Two kernels before, a sum and a store by one workgroup per tile:
+// 24 us for 64 tiles in four parts each, now 17.)
+__global__ void __launch_bounds__(TN_THREADS) tail_finish_kernel(const f32x4* __restrict__ partial, int m, int n, int ksteps,
                                                                  const uint8_t* __restrict__ meta,
                                                                  bf16_t* __restrict__ out, int tiles_m, int tiles_n,
-                                                                 int first_tile) {
+                                                                 TailPlan tail) {
     using S = SplitSmem;
-    constexpr int MF = 8, NF = 4, WM = 128;
-    extern __shared__ __align__(16) uint8_t smem[];
+    constexpr int MF = 8, NF = 4, WM = 128, CP = S::BM + 16, ROWS = 64;
+    __shared__ __align__(16) uint8_t smem[ROWS * CP];
+    const int tile = (int)blockIdx.x / NF, j = (int)blockIdx.x % NF;
     int tm, tn;
-    tile_of_position(first_tile + (int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+    tile_of_position(tail.first_tile + tile, tiles_m, tiles_n, tm, tn);
     const int m0 = tm * S::BM, n0 = tn * S::BN;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave & 1, wn = wave >> 1, l16 = lane & 15, lq = lane >> 4;
-    f32x4 acc[MF][NF];
-    const f32x4* src = partial + (size_t)blockIdx.x * (MF * NF * TN_THREADS) + t;
+    const int c = tile / tail.bundle, first = c * ksteps / tail.share, last = ((c + 1) * ksteps - 1) / tail.share;
+    constexpr int PART = MF * NF * TN_THREADS;
+    const f32x4* src = partial + (int64_t)((first + c - c / tail.aligned) * tail.bundle + tile % tail.bundle) * PART + j * TN_THREADS + t;
+    f32x4 acc[MF];
 #pragma unroll
-    for (int i = 0; i < MF; ++i)
+    for (int i = 0; i < MF; ++i) acc[i] = src[i * NF * TN_THREADS];
+    for (int w = first + 1; w <= last; ++w) {
+        src += (int64_t)tail.bundle * PART;
+        f32x4 x[MF];
 #pragma unroll
-        for (int j = 0; j < NF; ++j) acc[i][j] = src[(i * NF + j) * TN_THREADS];
-    if (EPI == EPI_PLAIN) store_plain<MF, NF>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, l16, lq, out, nullptr);
-    else store_masked_packed<MF, NF, S::BM, S::BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out,
-                                                   smem);
+        for (int i = 0; i < MF; ++i) x[i] = src[i * NF * TN_THREADS];
+#pragma unroll
+        for (int i = 0; i < MF; ++i) { acc[i][0] += x[i][0]; acc[i][1] += x[i][1]; acc[i][2] += x[i][2]; acc[i][3] += x[i][3]; }
+    }
+    const int o = n0 + wn * 64 + j * 16 + l16, c0 = m0 + wm * WM;
+    uint32_t mw[WM / 32];
+#pragma unroll
+    for (int q = 0; q < WM / 32; ++q)
+        mw[q] = o < n && c0 + 32 * q < m ? *(const uint32_t*)(meta + (size_t)o * (m / 8) + c0 / 8 + 4 * q) : 0u;
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+        const int gl = i * 4 + lq;
+        const uint32_t nib = (mw[i >> 1] >> (4 * (gl & 7))) & 0xFu, a = nib & 3u, c = nib >> 2;
+        union { __bf16 h[2]; uint32_t u; } pr;
+        pr.h[0] = (__bf16)(a == 0 ? acc[i][0] : (a == 1 ? acc[i][1] : acc[i][2]));
+        pr.h[1] = (__bf16)(c == 1 ? acc[i][1] : (c == 2 ? acc[i][2] : acc[i][3]));
+        *(uint32_t*)(smem + (wn * 16 + l16) * CP + (wm * (WM / 4) + gl) * 4) = pr.u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < ROWS * (S::BM / 16) / TN_THREADS; ++u) {
+        const int idx = t + u * TN_THREADS, row = idx / (S::BM / 16), pc = idx % (S::BM / 16);
+        const int orow = n0 + (row >> 4) * 64 + j * 16 + (row & 15), col = m0 + pc * 16;
+        if (orow < n && col < m) *(u32x4*)(out + (size_t)orow * (m / 2) + (col >> 1)) = *(const u32x4*)(smem + row * CP + pc * 16);
+    }
 }
 
 template <int BM, int BN, int EPI, int NS>
@@ -535,27 +570,40 @@ hipError_t launch_dense_tn(const bf16_t* At, int64_t m, const bf16_t* Bt, int64_
     return hipGetLastError();
 }
 
-// How the tiles left over after the last full round are cut: tail tiles (0 = none worth cutting), slabs
-// per tile, k-steps per slab.  Only wide grids (the tile order has positions there), only leftovers of at
-// most half a round (more would be cut into too few slabs to gain), at least eight k-steps per slab.
-struct TailPlan { int first_tile, tiles, slabs, slab_steps; };
+// How the tiles left over after the last full round are cut (tiles == 0: not worth cutting).  Only wide grids (the tile
+// order has positions there).  An XCD's 32 compute units hold 32 / bundle lanes; the bundle is the largest (its tiles share
+// panels) whose shares are within 1/16 of the shortest.  In units of a k-step (1.36 us) a share costs its k-steps, about 6
+// for every part, the parts' way through memory (256 KiB each, written and read at 6 TB/s: 0.065 per part) and a launch
+// (5); a round of whole tiles costs ksteps + 6.
 inline TailPlan tail_plan(int64_t tiles_m, int64_t tiles_n, int64_t ksteps) {
-    TailPlan p = {0, 0, 0, 0};
+    TailPlan p = {0, 0, 1, 1, 0, 1, 1, 0, 0.0};
     const int64_t tiles = tiles_m * tiles_n;
-    if (!wide_grid((int)tiles_m, (int)tiles_n) || tiles < RESIDENT || tiles > (1 << 30)) return p;
+    if (!wide_grid((int)tiles_m, (int)tiles_n) || tiles < RESIDENT || tiles > (1 << 30) || ksteps > (1 << 20)) return p;
     const int64_t rem = tiles % RESIDENT;
-    if (rem == 0 || rem > RESIDENT / 2) return p;
-    int64_t slabs = RESIDENT / rem;
-    if (slabs > ksteps / 8) slabs = ksteps / 8;
-    if (slabs < 2) return p;
-    const int64_t steps = (ksteps + slabs - 1) / slabs;
-    p.first_tile = (int)(tiles - rem);
-    p.tiles = (int)rem;
-    p.slab_steps = (int)steps;
-    p.slabs = (int)((ksteps + steps - 1) / steps);
-    return p;
+    if (rem == 0) return p;
+    constexpr int64_t PER_XCD = RESIDENT / XCDS;
+    int64_t shortest = INT64_MAX, bundle = 0, share = 0, lanes_per_xcd = 0;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int64_t e = rem < PER_XCD ? rem : PER_XCD; e >= 1; --e) {
+            const int64_t per = PER_XCD / e, row = (rem + e - 1) / e * ksteps;
+            int64_t sh = (row + XCDS * per - 1) / (XCDS * per);
+            if (sh < 8) sh = 8;
+            if (pass == 0) { if (sh < shortest) shortest = sh; }
+            else if (!bundle && sh * 16 <= shortest * 17) { bundle = e; share = sh; lanes_per_xcd = per; }
+        }
+    const int64_t bundles = (rem + bundle - 1) / bundle, lanes = (bundles * ksteps + share - 1) / share;
+    const int64_t aligned = share / std::gcd(share, ksteps), parts = lanes + bundles - 1 - (bundles - 1) / aligned;
+    double cost = (double)share + 6.0 * (1.0 + (double)((share + ksteps - 1) / ksteps)) + 0.065 * (double)(parts * bundle) + 5.0;
+    if (rem <= RESIDENT / 2 && ksteps >= 16) {                // measured: the cut never lost here; a share of the round + 1/4
+        const int64_t slabs = RESIDENT / rem < ksteps / 8 ? RESIDENT / rem : ksteps / 8;
+        cost = ((double)ksteps + 6.0) * (1.0 / (double)slabs + 0.25);
+    } else if (cost > 0.95 * ((double)ksteps + 6.0)) {
+        return p;
+    }
+    return {(int)(tiles - rem), (int)rem, (int)bundle, (int)lanes_per_xcd, (int)lanes, (int)share, (int)aligned, (int)parts, cost};
 }
 
+// tail: scratch for the parts of the leftover tiles (masked packed results only), or null
 template <int EPI>
 hipError_t launch_dense_tn_split(const bf16_t* At, int64_t m, const bf16_t* Bt, int64_t n, int64_t kp, int64_t ld,
                                  const uint8_t* meta, bf16_t* out, hipStream_t s, float* tail = nullptr) {
@@ -564,25 +612,23 @@ hipError_t launch_dense_tn_split(const bf16_t* At, int64_t m, const bf16_t* Bt, 
     int tiles_m = (int)((m + S::BM - 1) / S::BM), tiles_n = (int)((n + S::BN - 1) / S::BN);
     hipError_t e = allow_dynamic_lds<dense_tn_split_kernel<EPI, false>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    const TailPlan p = tail ? tail_plan(tiles_m, tiles_n, kp / 64) : TailPlan{0, 0, 0, 0};
+    const TailPlan p = tail ? tail_plan(tiles_m, tiles_n, kp / 64) : TailPlan{0, 0, 1, 1, 0, 1, 1, 0, 0.0};
     // with a tail the first launch is whole rounds only: workgroups 0 .. first_tile - 1 are exactly the
     // positions 0 .. first_tile - 1 of the order
     const int grid = p.tiles ? p.first_tile : super_grid(tiles_m, tiles_n);
     dense_tn_split_kernel<EPI, false><<<dim3((unsigned)grid), dim3(TN_THREADS), S::TOTAL, s>>>(
-        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, 0, 0, 0, nullptr);
+        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, TailPlan{0, 0, 1, 1, 0, 1, 1, 0, 0.0}, nullptr);
     if ((e = hipGetLastError()) != hipSuccess || !p.tiles) return e;
-    if ((e = allow_dynamic_lds<dense_tn_split_kernel<EPI, true>>(S::TOTAL)) != hipSuccess) return e;
-    if ((e = allow_dynamic_lds<tail_reduce_kernel<EPI>>(TAIL_REDUCE_LDS)) != hipSuccess) return e;
-    dense_tn_split_kernel<EPI, true><<<dim3((unsigned)(p.tiles * p.slabs)), dim3(TN_THREADS), S::TOTAL, s>>>(
-        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, p.first_tile, p.tiles, p.slab_steps,
-        (f32x4*)tail);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const size_t count4 = (size_t)p.tiles * (S::BM * S::BN / 4);
-    tail_sum_kernel<<<dim3((unsigned)((count4 + 255) / 256)), dim3(256), 0, s>>>((f32x4*)tail, p.slabs, count4, count4);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    tail_reduce_kernel<EPI><<<dim3((unsigned)p.tiles), dim3(TN_THREADS), TAIL_REDUCE_LDS, s>>>(
-        (const f32x4*)tail, (int)m, (int)n, meta, out, tiles_m, tiles_n, p.first_tile);
-    return hipGetLastError();
+    if constexpr (EPI == EPI_MASKED_PACKED) {
+        if ((e = allow_dynamic_lds<dense_tn_split_kernel<EPI, true>>(S::TOTAL)) != hipSuccess) return e;
+        dense_tn_split_kernel<EPI, true><<<dim3(RESIDENT), dim3(TN_THREADS), S::TOTAL, s>>>(
+            At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, p, (f32x4*)tail);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        tail_finish_kernel<<<dim3((unsigned)(p.tiles * 4)), dim3(TN_THREADS), 0, s>>>(
+            (const f32x4*)tail, (int)m, (int)n, (int)(kp / 64), meta, out, tiles_m, tiles_n, p);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace
@@ -616,7 +662,7 @@ bool wgrad_tn_fits(int64_t d_in) { return d_in % 32 == 0; }
 // The kernels run at the rate their compute units pull operands from L2: a launch costs about (rounds of
 // 256 resident tiles) x (rows per tile).  Take the cheapest shape, the larger on ties.  With scratch memory
 // the 256 x 256 kernel cuts the tiles left over after its last full round along the tokens
-// (launch_dense_tn_split): they then cost about 1 / slabs of a round, plus a quarter for the second pass.
+// (launch_dense_tn_split).
 static int wgrad_tile_choice(int64_t d_in, int64_t d_out, int64_t ksteps, bool with_tail) {
     const int bms[4] = {256, 256, 128, 128}, bns[4] = {256, 128, 128, 64};
     int best = 0;
@@ -626,7 +672,7 @@ static int wgrad_tile_choice(int64_t d_in, int64_t d_out, int64_t ksteps, bool w
         int64_t cost = ((tiles + RESIDENT - 1) / RESIDENT) * (bms[c] + bns[c]) * 100;
         if (c == 0 && with_tail) {
             const TailPlan p = tail_plan(tm, tn, ksteps);
-            if (p.tiles) cost = (tiles / RESIDENT) * 512 * 100 + 512 * (100 / p.slabs + 25);
+            if (p.tiles) cost = (tiles / RESIDENT) * 512 * 100 + (int64_t)(512.0 * 100.0 * p.steps / (double)(ksteps + 6));
         }
         if (cost < best_cost) { best_cost = cost; best = c; }
     }
@@ -638,7 +684,7 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     const int64_t ksteps = (b + 63) / 64;
     if (wgrad_tile_choice(d_in, d_out, ksteps, true) != 0) return 0;
     const TailPlan p = tail_plan((d_in + 255) / 256, (d_out + 255) / 256, ksteps);
-    return (size_t)p.tiles * (size_t)p.slabs * (256 * 256 * 4);
+    return (size_t)p.parts * (size_t)p.bundle * (256 * 256 * 4);
 }
 
 // dW (masked, packed) from token-contiguous copies Xt [d_in][ld], dYt [d_out][ld]; tail_or_null: scratch of

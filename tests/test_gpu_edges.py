@@ -120,3 +120,11 @@ def test_split_products_with_adapters(b, d_out, d_in, r):
 @pytest.mark.parametrize("b,d_out,d_in,r", [(1, 264, 128, 32), (32, 512, 1088, 96), (17, 2048, 9280, 512), (400, 1024, 2048, 160)])
 def test_adapter_product_of_few_tokens(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r, backward=False)
+
+
+# more than half a round of leftover 256 x 256 tiles: bundles that do not divide them, shares across bundle boundaries,
+# extents that fill no tile
+@pytest.mark.parametrize("b,d_out,d_in", [(8200, 5000, 5088), (12000, 4096, 6176)])
+def test_weight_gradient_with_a_large_last_round(b, d_out, d_in):
+    assert sl.slope_workspace_bytes(sl.SLOPE_CALL_WGRAD_MASKED_T, b, d_in, d_out) > 0
+    check_layer(b, d_out, d_in)
