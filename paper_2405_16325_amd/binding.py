@@ -92,12 +92,16 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# A call's checks and marshalling take longer than its kernels on the smallest layers (one token, 3072 x 768: 17.5 us a call, 14.1 without
+# them, 9.2 of kernels),
+# so they do without temporary objects: ctypes converts plain integers to pointers itself.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The raw handle of torch.cuda.current_stream()."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(call: str, status: int):
@@ -113,6 +117,8 @@ def _dev(*tensors):
 
 def _want(t, dtype, shape, what):
     """A raw pointer is all the library sees: dtype, shape, device and layout are checked here."""
+    if t is not None and t.dtype is dtype and t.shape == shape and t.is_cuda and t.is_contiguous():
+        return t
     if t is None:
         raise ValueError("%s is missing" % what)
     if not t.is_cuda or not t.is_contiguous():
@@ -167,10 +173,10 @@ def _packed(vals, meta, what):
     """(rows, cols) of a packed pair after checking that the two tensors belong together."""
     if vals is None or vals.dim() != 2:
         raise ValueError("%s values must be a matrix" % what)
-    rows, cols = vals.shape[0], vals.shape[1] * 2
-    _want(vals, BF16, (rows, cols // 2), what + " values")
-    _want(meta, U8, (rows, cols // 8), what + " metadata")
-    return rows, cols
+    rows, half = vals.shape
+    _want(vals, BF16, (rows, half), what + " values")
+    _want(meta, U8, (rows, half // 4), what + " metadata")
+    return rows, 2 * half
 
 
 def slope_double_prune(vals: torch.Tensor, meta: torch.Tensor, want_mask: bool = False, out=None):
