@@ -79,7 +79,8 @@ typedef enum {
     SLOPE_CALL_WGRAD_MASKED_WS = 6,
     SLOPE_CALL_SPMM_BWD_X_ADAPTER = 7,
     SLOPE_CALL_WGRAD_ADAPTER = 8,
-    SLOPE_CALL_WGRAD_MASKED_T = 9
+    SLOPE_CALL_WGRAD_MASKED_T = 9,
+    SLOPE_CALL_SPMM_BWD_X_WS = 10
 } slope_call_id;
 
 /* Bytes of scratch memory a call wants for b tokens, a d_out x d_in layer and adapter rank r (0: none);
@@ -172,6 +173,12 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
  */
 slope_status slope_spmm_bwd_x(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta,
                               int64_t d_out, int64_t d_in, void* dX, void* stream);
+/* The same with scratch memory for a split over d_out where that is faster: workspace_or_null of
+ * slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out, 0) bytes (may be 0), 256-byte aligned; a buffer that is
+ * too small: SLOPE_ERR_WORKSPACE.  NULL: slope_spmm_bwd_x. */
+slope_status slope_spmm_bwd_x_ws(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta,
+                                 int64_t d_out, int64_t d_in, void* dX, void* workspace_or_null,
+                                 size_t workspace_bytes, void* stream);
 
 /*
  * slope_wgrad_masked - dW = dY^T X (Eq. 5) evaluated with a dense contraction over the b

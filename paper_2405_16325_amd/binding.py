@@ -25,7 +25,7 @@ SLOPE_STATIC_SCRATCH_BYTES = 72 << 20      # include/slope.h
 # slope_call_id
 (SLOPE_CALL_PRUNE_ROWS, SLOPE_CALL_DOUBLE_PRUNE, SLOPE_CALL_SPMM_FWD, SLOPE_CALL_SPMM_BWD_X, SLOPE_CALL_WGRAD_MASKED,
  SLOPE_CALL_WGRAD_MASKED_WS, SLOPE_CALL_SPMM_BWD_X_ADAPTER, SLOPE_CALL_WGRAD_ADAPTER,
- SLOPE_CALL_WGRAD_MASKED_T) = range(1, 10)
+ SLOPE_CALL_WGRAD_MASKED_T, SLOPE_CALL_SPMM_BWD_X_WS) = range(1, 11)
 
 _P, _I64, _INT, _SZ = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
 
@@ -45,6 +45,7 @@ SIGNATURES = {
     "slope_spmm_fwd_ws": (_INT, [_P, _I64, _P, _P, _I64, _I64, _P, _P, _I64, _P, _P, _SZ, _P]),
     "slope_spmm_fwd_static": (_INT, [_P, _I64, _P, _P, _I64, _I64, _P, _P, _I64, _P, _P]),
     "slope_spmm_bwd_x": (_INT, [_P, _I64, _P, _P, _I64, _I64, _P, _P]),
+    "slope_spmm_bwd_x_ws": (_INT, [_P, _I64, _P, _P, _I64, _I64, _P, _P, _SZ, _P]),
     "slope_wgrad_workspace_bytes": (_SZ, [_I64, _I64, _I64]),
     "slope_wgrad_masked": (_INT, [_P, _P, _I64, _P, _I64, _I64, _P, _P]),
     "slope_wgrad_masked_ws": (_INT, [_P, _P, _I64, _P, _I64, _I64, _P, _P, _SZ, _P]),
@@ -251,8 +252,10 @@ def slope_spmm_bwd_x(dY: torch.Tensor, vals_t: torch.Tensor, meta_t: torch.Tenso
     b = dY.shape[0]
     _want(dY, BF16, (b, d_out), "dY")
     dX = _want(out, BF16, (b, d_in), "out") if out is not None else torch.empty((b, d_in), dtype=BF16, device=dY.device)
-    _check("slope_spmm_bwd_x", lib().slope_spmm_bwd_x(_ptr(dY), b, _ptr(vals_t), _ptr(meta_t), d_out, d_in, _ptr(dX),
-                                                      _stream()))
+    workspace = _scratch(None, slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out), dY.device, "workspace")
+    _check("slope_spmm_bwd_x_ws", lib().slope_spmm_bwd_x_ws(_ptr(dY), b, _ptr(vals_t), _ptr(meta_t), d_out, d_in, _ptr(dX),
+                                                            _ptr(workspace), 0 if workspace is None else workspace.numel(),
+                                                            _stream()))
     return dX
 
 

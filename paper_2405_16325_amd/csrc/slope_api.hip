@@ -128,6 +128,7 @@ size_t slope_workspace_bytes(int call_id, int64_t b, int64_t d_in, int64_t d_out
         case SLOPE_CALL_WGRAD_MASKED_WS: return slope_wgrad_workspace_bytes(b, d_in, d_out);
         case SLOPE_CALL_WGRAD_MASKED_T: return slope_wgrad_t_workspace_bytes(b, d_in, d_out);
         case SLOPE_CALL_SPMM_BWD_X_ADAPTER: return slope_spmm_bwd_x_adapter_workspace_bytes(b, r);
+        case SLOPE_CALL_SPMM_BWD_X_WS: return slope_spmm_fwd_workspace_bytes(b, d_out, d_in, 0);   // the forward's product
         case SLOPE_CALL_WGRAD_ADAPTER: return slope_wgrad_adapter_workspace_bytes(b, d_in, d_out, r);
         default: return 0;      // prune_rows, double_prune, spmm_bwd_x, wgrad_masked need no scratch; unknown ids
     }
@@ -174,10 +175,10 @@ static slope_status spmm_fwd_check(const void* X, int64_t b, const void* Wr_vals
 }
 
 // The launches of slope_spmm_fwd; arguments are checked, `workspace` (if any) has
-// slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) bytes.
+// slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) bytes, without room for slabs unless slabs_fit.
 static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,
                                  int64_t d_in, const void* L_or_null, const void* R_or_null, int64_t r, void* Y,
-                                 void* workspace, void* stream) {
+                                 void* workspace, bool slabs_fit, void* stream) {
     const bool adapter = r > 0 && (L_or_null || R_or_null);
     hipStream_t s = (hipStream_t)stream;
     const bf16_t* x_in = (const bf16_t*)X;
@@ -197,7 +198,7 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     // XL_SMALL_MAX_TOKENS of them the kernel that adds the slabs adds the adapter term too, straight from the sums of T = X L,
     // which workgroups beside the product's compute where they fit (rank 128, 9216 x 9216, 128 tokens: 54.7 -> 42.8 us in
     // all; 256 tokens: 67 -> 53).
-    const bool slabs = !few && workspace && spmm_slab_count(b, d_out, d_in) > 0;
+    const bool slabs = !few && workspace && slabs_fit && spmm_slab_count(b, d_out, d_in) > 0;
     SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
     if (slabs && (!adapter || b <= XL_SMALL_MAX_TOKENS)) {
         if (adapter) {
@@ -245,7 +246,7 @@ slope_status slope_spmm_fwd(const void* X, int64_t b, const void* Wr_vals, const
     if (st != SLOPE_OK) return st;
     if (r > 0 && (L_or_null || R_or_null) && !workspace) return SLOPE_ERR_NULL;
     if (misaligned(workspace, 256)) return SLOPE_ERR_ALIGN;
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, true, stream);
 }
 
 slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,
@@ -258,7 +259,7 @@ slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, co
     if (misaligned(workspace, 256)) return SLOPE_ERR_ALIGN;
     if (workspace && workspace_bytes < slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0))
         return SLOPE_ERR_WORKSPACE;
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, true, stream);
 }
 
 // ---- slope_spmm_fwd_static: the same call on a scratch buffer that lives in the library's image.
@@ -295,7 +296,12 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
     slope_status st = spmm_fwd_check(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y);
     if (st != SLOPE_OK) return st;
     const bool adapter = r > 0 && (L_or_null || R_or_null);
-    const size_t need = slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
+    size_t need = slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
+    bool slabs_fit = true;
+    if (need > (size_t)SLOPE_STATIC_SCRATCH_BYTES && spmm_slabs_optional(b, d_out, d_in)) {
+        slabs_fit = false;                                    // the tile kernels without a split
+        need = adapter_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
+    }
     if (need > (size_t)SLOPE_STATIC_SCRATCH_BYTES) return SLOPE_ERR_WORKSPACE;
     void* ws = nullptr;
     if (need > 0) {
@@ -304,7 +310,7 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
     }
     // Nothing in the buffer has to start at zero: every partial sum that is read was written by this
     // call's own kernels first.
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, ws, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, ws, slabs_fit, stream);
 }
 
 slope_status slope_spmm_bwd_x(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta, int64_t d_out,
@@ -319,6 +325,18 @@ slope_status slope_spmm_bwd_x(const void* dY, int64_t b, const void* WrcT_vals, 
                                          d_in, d_out, nullptr, nullptr, 0, (bf16_t*)dX, nullptr, (hipStream_t)stream));
     return finish(launch_spmm((const bf16_t*)dY, b, (const bf16_t*)WrcT_vals, (const uint8_t*)WrcT_meta, d_in, d_out,
                               nullptr, nullptr, 0, (bf16_t*)dX, (hipStream_t)stream));
+}
+
+slope_status slope_spmm_bwd_x_ws(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta,
+                                 int64_t d_out, int64_t d_in, void* dX, void* workspace_or_null, size_t workspace_bytes,
+                                 void* stream) {
+    if (!workspace_or_null) return slope_spmm_bwd_x(dY, b, WrcT_vals, WrcT_meta, d_out, d_in, dX, stream);
+    // the forward's product without an adapter: sparse rows = d_in, contraction over d_out
+    slope_status st = spmm_fwd_check(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX);
+    if (st != SLOPE_OK) return st;
+    if (misaligned(workspace_or_null, 256)) return SLOPE_ERR_ALIGN;
+    if (workspace_bytes < slope_spmm_fwd_workspace_bytes(b, d_out, d_in, 0)) return SLOPE_ERR_WORKSPACE;
+    return spmm_fwd_run(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX, workspace_or_null, true, stream);
 }
 
 slope_status slope_wgrad_masked(const void* dY, const void* X, int64_t b, const void* Wr_meta, int64_t d_out,

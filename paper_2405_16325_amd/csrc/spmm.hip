@@ -981,7 +981,7 @@ static bool tile_kernel_fits(int64_t K) { return K % 64 == 0 && K >= 128; }
 // own quarter of them only.  (777 tokens, 1280 x 5120, 260 tiles in two rounds: 34 -> 50 us.)
 static bool one_round_of_64(int64_t n, int64_t m) { return tiles_of_64(n, m) <= RESIDENT; }
 
-int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
+static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || !tile_kernel_fits(K)) return 0;
     const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128);
     if (tiles >= RESIDENT) return 0;                          // the chip is full without a split (measured: slabs lose)
@@ -1007,6 +1007,43 @@ int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
     // 4096 x 4096 18.3 / 23.3; 100 tokens, 5120 x 5120 22.0 / 22.2; 64 tokens, 9216 x 9216 48 / 35).
     if (one_round_of_64(n, m) && 3e3 + 2.05e3 * (double)K / 512.0 <= 4e3 + 1.25 * best_ns) return 0;
     return best < 2 ? 0 : best;
+}
+
+// More than 128 tokens where that rule sees no gain: the time of the tile kernels' rounds against one round of slabs.  A
+// k-step of a bm x bn tile takes about 0.35 us and 1 us per 100 KB of operands, a tile's start and end 3 us (us, estimate /
+// measured: 128 x 64 tiles, 48 and 65 k-steps 28 / 30 and 37 / 37; 256 x 128, 144 k-steps 104 / 111; 192 x 256, two rounds
+// of 80 k-steps 137 / 139), the second launch and the drained chip between the two 7 us, the slabs are written and read
+// at 6 TB/s.  Input gradients: 700 tokens, 2112 x 4160 37 -> 26.2 + 4.7 us; 512 tokens, 4096 x 4096 36 -> 22.4 + 6.2; but
+// 2048 tokens, 768 x 3072 30.3 -> 22.1 + 4.4, a microsecond slower in a step, is left alone.
+static int slabs_of_a_partial_round(int64_t n, int64_t m, int64_t K) {
+    const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128), quads = (K + 255) / 256;
+    if (n <= 128 || !tile_kernel_fits(K) || tiles > RESIDENT / 2) return 0;
+    auto step_us = [](int64_t bm, int64_t bn) { return 0.35 + (double)(72 * bm + 128 * bn) / 1e5; };
+    int bm, bn;
+    spmm_tile_choice(n, m, K, bm, bn);
+    double least;
+    if (bm == 0 || bm == 64 && bn == 64) {
+        least = 3.0 + 2.05 * (double)K / 512.0;               // the generic kernel's four groups
+    } else {
+        const int64_t t = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
+        least = (double)((t + RESIDENT - 1) / RESIDENT) * (3.0 + (double)K / 64.0 * step_us(bm, bn));
+    }
+    least *= 0.9;
+    int best = 0;
+    for (int64_t sl = 2; sl <= 16 && sl * 4 <= quads && sl * tiles <= RESIDENT; ++sl) {
+        const double us = 10.0 + (double)((quads + sl - 1) / sl * 4) * step_us(256, 128) + 8.0 * (double)sl * (double)n * (double)m / 6e6;
+        if (us < least) { least = us; best = (int)sl; }
+    }
+    return best;
+}
+
+bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K) {
+    return slabs_of_a_long_weight(n, m, K) == 0 && slabs_of_a_partial_round(n, m, K) > 0;
+}
+
+int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
+    const int slabs = slabs_of_a_long_weight(n, m, K);
+    return slabs ? slabs : slabs_of_a_partial_round(n, m, K);
 }
 
 size_t spmm_slab_bytes(int64_t n, int64_t m, int64_t K) {

@@ -128,3 +128,11 @@ def test_adapter_product_of_few_tokens(b, d_out, d_in, r):
 def test_weight_gradient_with_a_large_last_round(b, d_out, d_in):
     assert sl.slope_workspace_bytes(sl.SLOPE_CALL_WGRAD_MASKED_T, b, d_in, d_out) > 0
     check_layer(b, d_out, d_in)
+
+
+# input gradients with scratch: slabs by either rule, a last slab of one k-step, few tokens in slices, none
+@pytest.mark.parametrize("b,d_out,d_in,some", [(700, 4160, 2112, True), (512, 4096, 4096, True), (129, 8256, 520, True),
+                                               (1500, 8192, 1032, True), (16, 36864, 2048, True), (2048, 3072, 768, False)])
+def test_input_gradient_with_scratch(b, d_out, d_in, some):
+    assert (sl.slope_workspace_bytes(sl.SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out) > 0) == some
+    check_layer(b, d_out, d_in)
