@@ -1009,26 +1009,26 @@ static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     return best < 2 ? 0 : best;
 }
 
-// More than 128 tokens where that rule sees no gain: the time of the tile kernels' rounds against one round of slabs.  A
-// k-step of a bm x bn tile takes about 0.35 us and 1 us per 100 KB of operands, a tile's start and end 3 us (us, estimate /
-// measured: 128 x 64 tiles, 48 and 65 k-steps 28 / 30 and 37 / 37; 256 x 128, 144 k-steps 104 / 111; 192 x 256, two rounds
-// of 80 k-steps 137 / 139), the second launch and the drained chip between the two 7 us, the slabs are written and read
-// at 6 TB/s.  Input gradients: 700 tokens, 2112 x 4160 37 -> 26.2 + 4.7 us; 512 tokens, 4096 x 4096 36 -> 22.4 + 6.2; but
-// 2048 tokens, 768 x 3072 30.3 -> 22.1 + 4.4, a microsecond slower in a step, is left alone.
+// Time of the tile kernels' rounds for a product, in us: a k-step of a bm x bn tile takes about 0.35 us and 1 us per 100 KB
+// of operands, a tile's start and end 3 us (estimate / measured: 128 x 64 tiles, 48 and 65 k-steps 28 / 30 and 37 / 37;
+// 256 x 128, 144 k-steps 104 / 111; 192 x 256, two rounds of 80 k-steps 137 / 139).
+static double step_us(int64_t bm, int64_t bn) { return 0.35 + (double)(72 * bm + 128 * bn) / 1e5; }
+static double tiles_us(int64_t n, int64_t m, int64_t K) {
+    int bm, bn;
+    spmm_tile_choice(n, m, K, bm, bn);
+    if (bm == 0 || (bm == 64 && bn == 64)) return 3.0 + 2.05 * (double)K / 512.0;   // the generic kernel's four groups
+    const int64_t t = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
+    return (double)((t + RESIDENT - 1) / RESIDENT) * (3.0 + (double)K / 64.0 * step_us(bm, bn));
+}
+
+// More than 128 tokens where that rule sees no gain: the tile kernels' rounds against one round of slabs, the second launch
+// and the drained chip between the two 7 us, the slabs written and read at 6 TB/s.  Input gradients: 700 tokens, 2112 x
+// 4160 37 -> 26.2 + 4.7 us; 512 tokens, 4096 x 4096 36 -> 22.4 + 6.2; but 2048 tokens, 768 x 3072 30.3 -> 22.1 + 4.4, a
+// microsecond slower in a step, is left alone.
 static int slabs_of_a_partial_round(int64_t n, int64_t m, int64_t K) {
     const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128), quads = (K + 255) / 256;
     if (n <= 128 || !tile_kernel_fits(K) || tiles > RESIDENT / 2) return 0;
-    auto step_us = [](int64_t bm, int64_t bn) { return 0.35 + (double)(72 * bm + 128 * bn) / 1e5; };
-    int bm, bn;
-    spmm_tile_choice(n, m, K, bm, bn);
-    double least;
-    if (bm == 0 || bm == 64 && bn == 64) {
-        least = 3.0 + 2.05 * (double)K / 512.0;               // the generic kernel's four groups
-    } else {
-        const int64_t t = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-        least = (double)((t + RESIDENT - 1) / RESIDENT) * (3.0 + (double)K / 64.0 * step_us(bm, bn));
-    }
-    least *= 0.9;
+    double least = 0.9 * tiles_us(n, m, K);
     int best = 0;
     for (int64_t sl = 2; sl <= 16 && sl * 4 <= quads && sl * tiles <= RESIDENT; ++sl) {
         const double us = 10.0 + (double)((quads + sl - 1) / sl * 4) * step_us(256, 128) + 8.0 * (double)sl * (double)n * (double)m / 6e6;
@@ -1115,8 +1115,24 @@ void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     }
 }
 
-hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
+// Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 8 us for its launch and
+// the drained chip before it) takes for less than the round of tiles that they begin (0: none): up to 32 beyond a multiple
+// of the tile kernels' 256 or 128 (777 tokens, 20480 x 5120: 139 us in two rounds of tiles, 80 + 25 for 768 and 9 tokens).
+static int64_t rest_tokens(int64_t n, int64_t m, int64_t K) {
+    if (n <= 128 || !tile_kernel_fits(K) || one_round_of_64(n, m)) return 0;
+    double least = tiles_us(n, m, K);
+    int64_t best = 0;
+    for (int64_t edge = 256; edge >= 128; edge /= 2) {
+        const int64_t rest = n % edge;
+        if (rest == 0 || rest > STREAM_MAX_TOKENS || rest == n) continue;
+        const double us = tiles_us(n - rest, m, K) + 1.125 * (double)m * (double)K / 5e6 + 8.0;
+        if (us < 0.95 * least) { least = us / 0.95; best = rest; }
+    }
+    return best;
+}
+
+static hipError_t launch_tiles(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
+                               const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
     int bm, bn;
     spmm_tile_choice(n, m, K, bm, bn);
     if (bm == 0) {
@@ -1131,4 +1147,14 @@ hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const u
         case 64064: return launch_generic_as<2, 2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         default: return launch_tile<64, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     }
+}
+
+hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
+    const int64_t rest = K2 <= 0 ? rest_tokens(n, m, K) : 0;  // (the small-batch kernel takes A2 k-major)
+    n -= rest;
+    hipError_t e = launch_tiles(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+    if (e != hipSuccess || rest == 0) return e;
+    // second, so that it finds the packed weight in the last-level cache (777 tokens: the other way round 6 us slower)
+    return launch_spmm_stream(B + n * K, rest, A_vals, A_meta, m, K, B2 ? B2 - n * K2 : nullptr, A2, -K2, C + n * m, nullptr, s);
 }

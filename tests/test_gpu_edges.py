@@ -136,3 +136,10 @@ def test_weight_gradient_with_a_large_last_round(b, d_out, d_in):
 def test_input_gradient_with_scratch(b, d_out, d_in, some):
     assert (sl.slope_workspace_bytes(sl.SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out) > 0) == some
     check_layer(b, d_out, d_in)
+
+
+# a few tokens beyond whole tiles, which a pass of the small-batch kernel takes: one token and several, an odd number of
+# k-steps, with an adapter whose T is split at the same token
+@pytest.mark.parametrize("b,d_out,d_in,r", [(777, 20480, 5120, 64), (2049, 8192, 1024, 160), (4097, 4096, 2112, 0), (1025, 16384, 2112, 32)])
+def test_tokens_beyond_whole_tiles(b, d_out, d_in, r):
+    check_layer(b, d_out, d_in, r)
