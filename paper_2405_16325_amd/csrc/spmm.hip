@@ -46,11 +46,7 @@ namespace {
 //    workgroup stages the tile's BMT columns of 128 rows at a time in LDS (the rings are idle by
 //    then) and the wavefronts read their fragments back with the transposing LDS read; every
 //    thread of the workgroup must make the call (it contains barriers);
-//  - epilogue: a lane holds four consecutive features of one token.  Stored straight from the registers that
-//    is 8 bytes per lane in pieces of 32 contiguous bytes: sixteen rows per instruction, each a partial
-//    line.  So the workgroup's tile goes through LDS (the rings are idle by then) as [token][feature] rows
-//    and leaves in whole rows: 16 bytes per lane, up to 512 contiguous bytes per half wavefront.
-//    BNT = tokens of the workgroup's tile, tile_t0 its first token; every thread must make the call.
+//  - epilogue: store_rows. BNT = tokens of the workgroup's tile, tile_t0 its first token; every thread must make the call.
 //  - with a slab buffer (a split over k, see launch_spmm_slabs): the fp32 accumulators go to
 //    partial[token][feature] instead, 16 bytes per lane, and a reduction kernel finishes.
 template <int MF, int NF, int BMT, int BNT, int THREADS>
@@ -167,36 +163,7 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
         }
         return;
     }
-    constexpr int CP = BMT * 2 + 16;                          // bytes per staged token row: 16 rows x 4 lanes x 8 B
-                                                              // of one store fall on 64 different banks
-    constexpr int LPR = BMT / 4;                              // 8-byte pieces per row
-    __syncthreads();                                          // every wavefront is done with the rings / the staged factor
-#pragma unroll
-    for (int j = 0; j < NF; ++j)
-#pragma unroll
-        for (int i = 0; i < MF; ++i) {
-            f32x4 v = acc[i][j];
-            union { __bf16 h[4]; u32x2 u; } o;
-            o.h[0] = (__bf16)v[0]; o.h[1] = (__bf16)v[1]; o.h[2] = (__bf16)v[2]; o.h[3] = (__bf16)v[3];
-            *(u32x2*)(smem + (t0 - tile_t0 + j * 16 + l16) * CP + (f0 - tile_f0 + i * 16 + lq * 4) * 2) = o.u;
-        }
-    __syncthreads();
-    // 16-byte pieces, all read from LDS before the first is stored (a loop of read, wait, store per piece took
-    // 2.5 us of every tile); m is a multiple of 8, so a piece is inside the row or outside as a whole
-    constexpr int PPR = BMT / 8, PER_THREAD = BNT * PPR / THREADS;   // THREADS = the workgroup's size
-    static_assert(BNT * PPR % THREADS == 0 && LPR == 2 * PPR, "whole pieces per thread");
-    u32x4 piece[PER_THREAD];
-#pragma unroll
-    for (int u = 0; u < PER_THREAD; ++u) {
-        const int idx = (int)threadIdx.x + u * THREADS;
-        piece[u] = *(const u32x4*)(smem + (idx / PPR) * CP + (idx % PPR) * 16);
-    }
-#pragma unroll
-    for (int u = 0; u < PER_THREAD; ++u) {
-        const int idx = (int)threadIdx.x + u * THREADS;
-        const int tok = tile_t0 + idx / PPR, col = tile_f0 + (idx % PPR) * 8;
-        if (tok < n && col < m) *(u32x4*)(C + (size_t)tok * m + col) = piece[u];
-    }
+    store_rows<MF, NF, BMT, BNT, THREADS>(acc, f0, t0, m, n, l16, lq, C, smem, tile_f0, tile_t0);
 }
 
 template <int BM, int BN>

@@ -143,11 +143,10 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     }
 }
 
-// Plain epilogue of one wavefront: out[j][i] bf16 row-major [n][m] (row j, four consecutive i per lane), or
-// the fp32 accumulators into partial[n][m] for a later reduction.
+// The fp32 accumulators into partial[n][m] for a later reduction.
 template <int MF, int NF>
-__device__ __forceinline__ void store_plain(const f32x4 (&acc)[MF][NF], int m, int n, int c0, int o0, int l16, int lq,
-                                            bf16_t* __restrict__ out, float* __restrict__ partial) {
+__device__ __forceinline__ void store_sums(const f32x4 (&acc)[MF][NF], int m, int n, int c0, int o0, int l16, int lq,
+                                           float* __restrict__ partial) {
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
         int row = o0 + j * 16 + l16;
@@ -155,15 +154,7 @@ __device__ __forceinline__ void store_plain(const f32x4 (&acc)[MF][NF], int m, i
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
             int col = c0 + i * 16 + lq * 4;
-            if (col >= m) continue;
-            f32x4 v = acc[i][j];
-            if (partial) {
-                *(f32x4*)(partial + (size_t)row * m + col) = v;
-                continue;
-            }
-            union { __bf16 h[4]; u32x2 u; } o;
-            o.h[0] = (__bf16)v[0]; o.h[1] = (__bf16)v[1]; o.h[2] = (__bf16)v[2]; o.h[3] = (__bf16)v[3];
-            *(u32x2*)(out + (size_t)row * m + col) = o.u;
+            if (col < m) *(f32x4*)(partial + (size_t)row * m + col) = acc[i][j];
         }
     }
 }
@@ -286,8 +277,12 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(const bf16_t* __re
     WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
 
     if constexpr (EPI == EPI_PLAIN) {
-        store_plain<MF, NF>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, l16, lq, out,
-                            partial ? partial + (size_t)blockIdx.y * n * m : nullptr);
+        if (partial) {
+            store_sums<MF, NF>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, l16, lq, partial + (size_t)blockIdx.y * n * m);
+            return;
+        }
+        static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
+        store_rows<MF, NF, BM, BN, TN_THREADS>(acc, m0 + wm * WM, n0 + wn * NF * 16, m, n, l16, lq, out, smem, m0, n0);
     } else {
         static_assert(BN * (BM + 16) <= S::TOTAL, "the staged tile of pairs fits in the ring");
         store_masked_packed<MF, NF, BM, BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out, smem);
@@ -496,7 +491,9 @@ next_part:
         wg_barrier();                                         // every wavefront's reads and look-ahead loads are over
         goto next_part;
     }
-    if (EPI == EPI_PLAIN) store_plain<MF, NF>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, l16, lq, out, nullptr);
+    static_assert(S::BN * (S::BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
+    if (EPI == EPI_PLAIN)
+        store_rows<MF, NF, S::BM, S::BN, TN_THREADS>(acc, m0 + wm * WM, n0 + wn * NF * 16, m, n, l16, lq, out, smem, m0, n0);
     else store_masked_packed<MF, NF, S::BM, S::BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out,
                                                    smem);
 }
