@@ -1030,8 +1030,14 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_float
     const int64_t groups = ((m + 255) / 256) * (n <= 64 ? 1 : (n + 127) / 128) * want;
     const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ);
     if (groups + tiles > RESIDENT) return false;
-    x = xl_split(n, K, r, max_floats, RESIDENT - groups);
-    return x.steps <= slab_steps_of(K, want);
+    // the fewest slabs that take half as long as the product: the kernel after it reads them all for every 64 features
+    const int most = slab_steps_of(K, want) / 2;
+    for (int64_t held = n * r; held <= max_floats; held += n * r) {
+        x = xl_split(n, K, r, held, RESIDENT - groups);
+        if (x.steps <= most) return true;
+        if (x.slabs * tiles + tiles > RESIDENT - groups) break;
+    }
+    return x.slabs > 0 && x.steps <= 2 * most;
 }
 
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
