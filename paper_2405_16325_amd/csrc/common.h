@@ -83,10 +83,19 @@ hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, 
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
                                   bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s);
 // C[n, m] = sum_k B(i, k) * A(j, k) for the skinny adapter products of layers whose extents are not multiples of 64:
-// an operand is k-contiguous [rows][ld] (K % 8 == 0) or k-major [K][ld] (rows % 8 == 0); m % 8 == 0.  (B k-major with A
-// k-contiguous does not occur.)
-hipError_t launch_skinny_ragged(const bf16_t* B, int64_t ldb, bool b_kmajor, const bf16_t* A, int64_t lda, bool a_kmajor,
-                                int64_t n, int64_t m, int64_t K, bf16_t* C, hipStream_t s);
+// an operand is k-contiguous [rows][ld] (K % 8 == 0) or k-major [K][ld] (rows % 8 == 0); m % 8 == 0.
+struct SkinnyProduct {
+    const bf16_t* B;
+    int64_t ldb;
+    const bf16_t* A;
+    int64_t lda;
+    bool a_kmajor;
+    int64_t n, m, K;
+    bf16_t* C;
+};
+hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s);                           // B k-contiguous
+hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s);    // B's k-contiguous, A k-major; A k-contiguous
+hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s); // all operands k-major
 // out[c][r] = in[r][c]: in [rows][cols], rows % 64 == 0, cols % 8 == 0
 hipError_t launch_transpose(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, hipStream_t s);
 hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out,

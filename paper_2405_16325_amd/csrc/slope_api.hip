@@ -46,7 +46,7 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
                           bf16_t* At_scratch, float* partial, hipStream_t s) {
     if (K % 64 != 0)
-        return launch_skinny_ragged(B, K, false, A, a_kmajor ? r : K, a_kmajor, n, r, K, T, s);
+        return launch_skinny_ragged({B, K, A, a_kmajor ? r : K, a_kmajor, n, r, K, T}, s);
     const size_t partial_bytes = partial ? dense_tn_plain_partial_bytes(n, r) : 0;
     if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);
     return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);

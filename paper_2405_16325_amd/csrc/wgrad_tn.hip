@@ -826,10 +826,9 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
         // Extents that are not whole k-steps of the tile kernels: the in-place kernel for dW and the kernel for
         // ragged extents for the four skinny products (T and T2 rounded to bf16 as on the fast path).
         if ((e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, s)) != hipSuccess) return e;
-        if ((e = launch_skinny_ragged(X, d_in, false, L, r, true, b, r, d_in, T, s)) != hipSuccess) return e;       // T  = X L
-        if ((e = launch_skinny_ragged(dY, d_out, false, R, d_out, false, b, r, d_out, T2, s)) != hipSuccess) return e; // T2 = dY R^T
-        if ((e = launch_skinny_ragged(X, d_in, true, T2, r, true, d_in, r, b, dL, s)) != hipSuccess) return e;      // dL = X^T T2
-        return launch_skinny_ragged(T, r, true, dY, d_out, true, r, d_out, b, dR, s);                               // dR = T^T dY
+        e = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s);  // T = X L, T2 = dY R^T
+        if (e != hipSuccess) return e;
+        return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);   // dL = X^T T2, dR = T^T dY
     }
     if ((e = launch_token_copies(X, d_in, Xt, dY, d_out, dYt, b, s)) != hipSuccess) return e;
     if ((e = launch_wgrad_masked_t(dYt, Xt, b, meta, d_out, d_in, gvals, tail, s)) != hipSuccess) return e;
