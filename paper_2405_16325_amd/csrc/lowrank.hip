@@ -44,6 +44,16 @@ hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, bo
 
 }  // namespace
 
+// Whole k-steps have the choice: the tile kernels stream better, but want a k-contiguous copy of a k-major operand and, on
+// few tiles, a second kernel for the sums over slabs; this one takes operands as stored in one launch, at about 1.3 us per
+// chunk of 32 k that a wavefront walks and round of two workgroups per compute unit.  `most` chunks: 8 where it saves the
+// copy and the second kernel, 5 where the second kernel only, 10 for the pairs below (1024 tokens, 2048 x
+// 2048, rank 64: X L 2.7 + 5.1 + 3.8 -> 10.7 us, the gradient call's adapter part 42 us in ten launches -> 21 in two).
+bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most) {
+    const int64_t tiles = ((m + SK_BJ - 1) / SK_BJ) * ((n + SK_BI - 1) / SK_BI), steps = (K + 32 * SK_WAVES - 1) / (32 * SK_WAVES);
+    return steps * ((tiles + 511) / 512) <= most;
+}
+
 hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s) {
     return p.a_kmajor ? launch_skinny_pair<false, true, false, true>(p, p, false, s)
                       : launch_skinny_pair<false, false, false, false>(p, p, false, s);

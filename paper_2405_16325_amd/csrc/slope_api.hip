@@ -41,11 +41,11 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
 }
 
 // T[n, r] = B[n, K] A^T for the skinny products of the adapters.  a_kmajor: A is [K][r] (the factor L as
-// stored) instead of [r][K].  Whole k-steps of 64 go to the MFMA kernels, anything else to the kernel for
-// ragged extents.
+// stored) instead of [r][K].  Whole k-steps of 64 go to the tile kernels, anything else and short products to the kernel
+// for ragged extents.
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
                           bf16_t* At_scratch, float* partial, hipStream_t s) {
-    if (K % 64 != 0)
+    if (K % 64 != 0 || skinny_is_short(n, r, K, a_kmajor ? 8 : 5))
         return launch_skinny_ragged({B, K, A, a_kmajor ? r : K, a_kmajor, n, r, K, T}, s);
     const size_t partial_bytes = partial ? dense_tn_plain_partial_bytes(n, r) : 0;
     if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);

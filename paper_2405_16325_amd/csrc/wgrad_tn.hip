@@ -822,16 +822,22 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     float* sums = shared ? (float*)w : nullptr;
 
     hipError_t e;
+    auto skinny = [&]() {                                     // T = X L and T2 = dY R^T, then dL = X^T T2 and dR = T^T dY
+        hipError_t err = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s);
+        if (err != hipSuccess) return err;
+        return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);
+    };
     if (d_in % 64 != 0 || d_out % 64 != 0) {
         // Extents that are not whole k-steps of the tile kernels: the in-place kernel for dW and the kernel for
         // ragged extents for the four skinny products (T and T2 rounded to bf16 as on the fast path).
         if ((e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, s)) != hipSuccess) return e;
-        e = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s);  // T = X L, T2 = dY R^T
-        if (e != hipSuccess) return e;
-        return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);   // dL = X^T T2, dR = T^T dY
+        return skinny();
     }
     if ((e = launch_token_copies(X, d_in, Xt, dY, d_out, dYt, b, s)) != hipSuccess) return e;
     if ((e = launch_wgrad_masked_t(dYt, Xt, b, meta, d_out, d_in, gvals, tail, s)) != hipSuccess) return e;
+    if (skinny_is_short(b, r, d_in, 10) && skinny_is_short(b, r, d_out, 10) && skinny_is_short(d_in, r, b, 10) &&
+        skinny_is_short(r, d_out, b, 10))
+        return skinny();
     launch_transpose_pad(L, d_in, r, d_in, d_in, Lt, s);                          // Lt[r][d_in]
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_dense_tn_plain(X, b, Lt, r, d_in, d_in, T, sums, shared, s)) != hipSuccess) return e;        // T  = X L

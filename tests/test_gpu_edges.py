@@ -105,6 +105,13 @@ def test_column_masks(n, m, kind, rows, cols):
     nm.test_prune_mask_rows_then_columns(n, m, kind, rows, cols)
 
 
+# whole k-steps on the kernel for short products: one chunk in a row and as many as its rule lets in, ranks of one tile
+# and several, fewer tokens than a tile
+@pytest.mark.parametrize("b,d_out,d_in,r", [(20, 192, 128, 32), (600, 2560, 2560, 64), (2560, 1024, 2048, 96), (1024, 2048, 2112, 512)])
+def test_short_adapter_products(b, d_out, d_in, r):
+    check_layer(b, d_out, d_in, r)
+
+
 # products split over k with an adapter: X L beside the product and in a launch of its own (no compute unit left, a
 # large rank), one slab of it and several, token and feature tiles of the second kernel that are not full, more tokens
 # than the split of X L takes
