@@ -52,8 +52,12 @@ hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A
     return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);
 }
 
-// sums of T = X L that a workgroup of the kernel after a split product adds up at most
-constexpr int64_t XL_FINISH_FLOATS = 65536;
+// A split product's second kernel adds up the sums of T = X L itself while all its workgroups together read at most this
+// much of them, about 6 TB/s: less where X L has a launch of its own (one launch is saved, not two), and there while it
+// leaves a wavefront at most so many chunks of 32 rows of L (128 tokens, rank 128: 28 MB at 9216 x 9216, 10 us; but 600 MB at
+// 36864 x 9216 with 16 slabs, 54 us against 15 with T; 33 tokens, 36864 x 9216, rank 64, 63 MB: 107 -> 120 us in all).
+constexpr int64_t XL_BESIDE_BYTES = (int64_t)40 << 20, XL_OWN_BYTES = (int64_t)20 << 20;
+constexpr int XL_OWN_STEPS = 6;
 
 }  // namespace
 
@@ -200,18 +204,24 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     // all; 256 tokens: 67 -> 53).
     const bool slabs = !few && workspace && slabs_fit && spmm_slab_count(b, d_out, d_in) > 0;
     SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
-    if (slabs && (!adapter || b <= XL_SMALL_MAX_TOKENS)) {
-        if (adapter) {
-            // each of that kernel's workgroups adds up 32 tokens' worth of sums: 64 K floats of them at most
-            const int64_t held = XL_FINISH_FLOATS / (32 * r) * b * r, most = held < sums_floats ? held : sums_floats;
-            if (!slab_xl_split(b, d_out, d_in, r, most, ad.x)) {           // no room beside the product
-                ad.L = nullptr;
-                ad.x = xl_split(b, d_in, r, most, RESIDENT);
+    if (slabs && !adapter) return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
+    if (slabs && b <= XL_SMALL_MAX_TOKENS) {
+        // that kernel reads the sums again for every 64 features
+        const int64_t slab_read = (d_out + 63) / 64 * ((b + 31) / 32 * 32) * r * 4;
+        int64_t held = XL_BESIDE_BYTES / slab_read * b * r;
+        if (held > sums_floats) held = sums_floats;
+        bool from_sums = held > 0 && slab_xl_split(b, d_out, d_in, r, held, ad.x);
+        if (held > XL_OWN_BYTES / slab_read * b * r) held = XL_OWN_BYTES / slab_read * b * r;
+        if (!from_sums && held > 0) {                         // no room beside the product: a launch of its own, if it is short
+            ad.L = nullptr;
+            ad.x = xl_split(b, d_in, r, held, RESIDENT);
+            from_sums = ad.x.steps <= XL_OWN_STEPS;
+            if (from_sums) {
                 hipError_t e = launch_xl(x_in, b, d_in, l, r, ad.x, sums, nullptr, s);
                 if (e != hipSuccess) return finish(e);
             }
         }
-        return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
+        if (from_sums) return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
     }
     if (adapter) {                                            // T = X L, rounded to bf16
         hipError_t e;

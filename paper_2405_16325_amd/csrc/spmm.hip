@@ -204,7 +204,8 @@ __device__ __forceinline__ int64_t quad_offset(int quad, int ksteps, int half) {
 // metadata) belongs, and that is where it is read.  A template parameter, so that whole quads pay nothing for it.
 //
 // SPLIT: the k range is cut into slabs of slab_steps k-steps (whole quads), which leave fp32 partial sums in slabs[slab].
-// The (tile, slab) pairs are dealt to the XCDs in eight equal runs, slab by slab (a slab's tiles share its tokens in L2),
+// The (tile, slab) pairs are dealt to the XCDs in equal shares, slab by slab (a slab's tiles share its tokens in L2): an
+// eighth of every slab's tiles where that is a whole number, else eight equal runs of all pairs,
 // the token tiles of a weight tile side by side.  A grid with the slabs in blockIdx.y gave 36 tiles per slab to seven of
 // the XCDs, five each, and one to the last (128 tokens, 9216 x 9216: 33.6 -> 27.7 us).
 // Such a launch may have workgroups of a second kind: they compute the sums of T = X L (see xl_split_kernel) that the
@@ -231,7 +232,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     constexpr int M_WAVES = BM / 32;                         // wavefronts that load metadata (32 rows each)
     extern __shared__ __align__(16) uint8_t smem[];
 
-    int tm, tn, slab = 0;
+    int tm, tn, slab = 0, extension_slab = 0;
     if constexpr (SPLIT) {
         static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         const int tiles = tiles_m * tiles_n, run = (tiles * job.nslabs + XCDS - 1) / XCDS;
@@ -246,11 +247,19 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
                                          job.Q + (size_t)part * n * job.r, smem);
             return;
         }
-        const int item = xcd * run + pos;
-        if (item >= tiles * job.nslabs) return;
-        slab = item / tiles;
-        tn = item % tiles % tiles_n;
-        tm = item % tiles / tiles_n;
+        int tile;
+        if (tiles % XCDS == 0) {
+            slab = pos / (tiles / XCDS);
+            tile = xcd * (tiles / XCDS) + pos % (tiles / XCDS);
+        } else {
+            const int item = xcd * run + pos;
+            if (item >= tiles * job.nslabs) return;
+            slab = item / tiles;
+            tile = item % tiles;
+        }
+        extension_slab = tiles % XCDS == 0 ? 0 : tile % job.nslabs;
+        tn = tile % tiles_n;
+        tm = tile / tiles_n;
     } else {
         if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
     }
@@ -386,10 +395,11 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 #undef SPMM_STEP
     WAIT_HERE(waitcnt_imm(0, 15));           // drain the clamped look-ahead loads
 
-    // the dense extension is added once, by the first slab
+    // the dense extension is added once: by the first slab if every XCD has its share of that (its workgroups start
+    // first), else by a slab that depends on the tile
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
     extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
-                                     slab == 0 ? K2 : 0, C, smem, m0, n0,
+                                     slab == extension_slab ? K2 : 0, C, smem, m0, n0,
                                      SPLIT ? job.slabs + (size_t)slab * (size_t)n * (size_t)m : nullptr);
 }
 
