@@ -150,3 +150,13 @@ def test_input_gradient_with_scratch(b, d_out, d_in, some):
 @pytest.mark.parametrize("b,d_out,d_in,r", [(777, 20480, 5120, 64), (2049, 8192, 1024, 160), (4097, 4096, 2112, 0), (1025, 16384, 2112, 32)])
 def test_tokens_beyond_whole_tiles(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
+
+
+# dense products whose output rows are 8-byte but not 16-byte aligned, and tiles that end inside a row
+@pytest.mark.parametrize("n,m,K", [(1, 4, 64), (100, 132, 128), (300, 2052, 192), (700, 4100, 256)])
+def test_dense_product_with_rows_of_any_multiple_of_four(n, m, K):
+    print(f"gemm_tn n={n} m={m} K={K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + n + m)
+    B, A = (torch.randn((rows, K), generator=gen, device="cuda").to(torch.bfloat16) for rows in (n, m))
+    assert_all_close(sl.slope_gemm_tn(B, A), B.float() @ A.float().t(), "C")
