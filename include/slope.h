@@ -87,8 +87,8 @@ typedef enum {
  * 0 for the calls that take no workspace, for unknown ids and for invalid extents.  The per-call
  * queries below return the same numbers.
  *   slope_spmm_fwd: required when adapters are active (T = X L as bf16[b, r], a K-contiguous copy of L
- *   for many tokens, partial sums); optional otherwise: for a few dozen to about a thousand tokens the
- *   call, given this many bytes, also splits the contraction over d_in and keeps fp32 partial sums
+ *   for many tokens, partial sums); optional otherwise: for a few dozen to some thousand tokens (where
+ *   tiles alone would leave much of the chip idle) the call, given this many bytes, also splits the contraction over d_in and keeps fp32 partial sums
  *   there, which is much faster at those sizes. */
 size_t slope_workspace_bytes(int call_id, int64_t b, int64_t d_in, int64_t d_out, int64_t r);
 size_t slope_spmm_fwd_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r);
