@@ -65,7 +65,7 @@ struct SlabAdapter {
 };
 int spmm_slab_count(int64_t n, int64_t m, int64_t K);
 size_t spmm_slab_bytes(int64_t n, int64_t m, int64_t K);
-bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K);   // the second rule of spmm_slab_count
+bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K);   // any split but that of a long weight in whole quads of k-steps
 bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, XlSplit& x);
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                              int64_t K, const SlabAdapter& ad, bf16_t* C, float* slabs, hipStream_t s);

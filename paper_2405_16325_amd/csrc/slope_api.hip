@@ -40,6 +40,17 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
                                                      : dense_tn_plain_partial_bytes(b, r));
 }
 
+// The slab buffer of a forward product with adapters of rank r (0: none); 0 where the product is not split over K.
+// Shapes that the static scratch holds without an optional split keep to that: every form of the call then takes the same
+// route, and what slope_spmm_fwd_static accepts is what the workspace query says.
+size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
+    const size_t slabs = round256(spmm_slab_bytes(b, d_out, d_in));
+    if (slabs && spmm_slabs_optional(b, d_out, d_in) &&
+        adapter_workspace_bytes(b, d_in, d_out, r) + slabs > (size_t)SLOPE_STATIC_SCRATCH_BYTES)
+        return 0;
+    return slabs;
+}
+
 // T[n, r] = B[n, K] A^T for the skinny products of the adapters.  a_kmajor: A is [K][r] (the factor L as
 // stored) instead of [r][K].  Whole k-steps of 64 go to the tile kernels, anything else and short products to the kernel
 // for ragged extents.
@@ -96,9 +107,11 @@ size_t slope_mask_bytes(int64_t rows, int64_t cols) { return slope_packed_meta_b
 
 size_t slope_spmm_fwd_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     if (b <= 0 || d_in <= 0 || d_out <= 0) return 0;
-    // the slabs of mid-size batches or the slices of inference-size ones: never both
-    return adapter_workspace_bytes(b, d_in, d_out, r) + round256(spmm_slab_bytes(b, d_out, d_in)) +
-           round256(spmm_rows_partial_bytes(b, d_out, d_in));
+    // the slabs of mid-size batches or the slices of inference-size ones: never both.  Never less than without adapters,
+    // whose product may be split where this one is not.
+    const size_t with = adapter_workspace_bytes(b, d_in, d_out, r) + fwd_slab_bytes(b, d_in, d_out, r);
+    const size_t without = fwd_slab_bytes(b, d_in, d_out, 0);
+    return (with > without ? with : without) + round256(spmm_rows_partial_bytes(b, d_out, d_in));
 }
 
 size_t slope_token_copy_bytes(int64_t b, int64_t d) {
@@ -179,10 +192,10 @@ static slope_status spmm_fwd_check(const void* X, int64_t b, const void* Wr_vals
 }
 
 // The launches of slope_spmm_fwd; arguments are checked, `workspace` (if any) has
-// slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) bytes, without room for slabs unless slabs_fit.
+// slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) bytes.
 static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,
                                  int64_t d_in, const void* L_or_null, const void* R_or_null, int64_t r, void* Y,
-                                 void* workspace, bool slabs_fit, void* stream) {
+                                 void* workspace, void* stream) {
     const bool adapter = r > 0 && (L_or_null || R_or_null);
     hipStream_t s = (hipStream_t)stream;
     const bf16_t* x_in = (const bf16_t*)X;
@@ -202,7 +215,7 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     // XL_SMALL_MAX_TOKENS of them the kernel that adds the slabs adds the adapter term too, straight from the sums of T = X L,
     // which workgroups beside the product's compute where they fit (rank 128, 9216 x 9216, 128 tokens: 54.7 -> 42.8 us in
     // all; 256 tokens: 67 -> 53).
-    const bool slabs = !few && workspace && slabs_fit && spmm_slab_count(b, d_out, d_in) > 0;
+    const bool slabs = !few && workspace && fwd_slab_bytes(b, d_in, d_out, r) > 0;
     SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
     if (slabs && !adapter) return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
     if (slabs && b <= XL_SMALL_MAX_TOKENS) {
@@ -256,7 +269,7 @@ slope_status slope_spmm_fwd(const void* X, int64_t b, const void* Wr_vals, const
     if (st != SLOPE_OK) return st;
     if (r > 0 && (L_or_null || R_or_null) && !workspace) return SLOPE_ERR_NULL;
     if (misaligned(workspace, 256)) return SLOPE_ERR_ALIGN;
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, true, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, stream);
 }
 
 slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,
@@ -269,7 +282,7 @@ slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, co
     if (misaligned(workspace, 256)) return SLOPE_ERR_ALIGN;
     if (workspace && workspace_bytes < slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0))
         return SLOPE_ERR_WORKSPACE;
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, true, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, stream);
 }
 
 // ---- slope_spmm_fwd_static: the same call on a scratch buffer that lives in the library's image.
@@ -306,12 +319,7 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
     slope_status st = spmm_fwd_check(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y);
     if (st != SLOPE_OK) return st;
     const bool adapter = r > 0 && (L_or_null || R_or_null);
-    size_t need = slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
-    bool slabs_fit = true;
-    if (need > (size_t)SLOPE_STATIC_SCRATCH_BYTES && spmm_slabs_optional(b, d_out, d_in)) {
-        slabs_fit = false;                                    // the tile kernels without a split
-        need = adapter_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
-    }
+    const size_t need = slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
     if (need > (size_t)SLOPE_STATIC_SCRATCH_BYTES) return SLOPE_ERR_WORKSPACE;
     void* ws = nullptr;
     if (need > 0) {
@@ -320,7 +328,7 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
     }
     // Nothing in the buffer has to start at zero: every partial sum that is read was written by this
     // call's own kernels first.
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, ws, slabs_fit, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, ws, stream);
 }
 
 slope_status slope_spmm_bwd_x(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta, int64_t d_out,
@@ -346,7 +354,7 @@ slope_status slope_spmm_bwd_x_ws(const void* dY, int64_t b, const void* WrcT_val
     if (st != SLOPE_OK) return st;
     if (misaligned(workspace_or_null, 256)) return SLOPE_ERR_ALIGN;
     if (workspace_bytes < slope_spmm_fwd_workspace_bytes(b, d_out, d_in, 0)) return SLOPE_ERR_WORKSPACE;
-    return spmm_fwd_run(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX, workspace_or_null, true, stream);
+    return spmm_fwd_run(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX, workspace_or_null, stream);
 }
 
 slope_status slope_wgrad_masked(const void* dY, const void* X, int64_t b, const void* Wr_meta, int64_t d_out,
@@ -498,7 +506,7 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         plan[2] = b <= 16 ? 16 : 32;
         if (slices > 0) plan[3] = slices;
     } else {
-        const int slabs = with_workspace ? spmm_slab_count(b, d_out, d_in) : 0;
+        const int slabs = with_workspace && fwd_slab_bytes(b, d_in, d_out, r) ? spmm_slab_count(b, d_out, d_in) : 0;
         int bm, bn;
         spmm_tile_choice(b, d_out, d_in, bm, bn);
         if (slabs > 0) { plan[0] = 1; plan[1] = 256; plan[2] = b <= 64 ? 64 : 128; plan[3] = slabs; }

@@ -1014,9 +1014,7 @@ static int slabs_of_a_partial_round(int64_t n, int64_t m, int64_t K) {
     return best;
 }
 
-bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K) {
-    return slabs_of_a_long_weight(n, m, K) == 0 && slabs_of_a_partial_round(n, m, K) > 0;
-}
+bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K) { return K % 256 != 0 || slabs_of_a_long_weight(n, m, K) == 0; }
 
 int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
     const int slabs = slabs_of_a_long_weight(n, m, K);

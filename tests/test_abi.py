@@ -184,6 +184,15 @@ def test_static_scratch_rejects_a_shape_beyond_its_buffer():
     assert b"scratch" in lib.slope_status_string(binding.SLOPE_ERR_WORKSPACE)
 
 
+@pytest.mark.parametrize("b,d_out,d_in,r", [(170, 30080, 28480, 0), (150, 30720, 10624, 512), (258, 20352, 36800, 128),
+                                            (378, 640, 32384, 256), (510, 7936, 17088, 256), (1500, 512, 36864, 512)])
+def test_a_split_that_is_optional_stays_inside_the_static_scratch(b, d_out, d_in, r):
+    # these fit without slabs and would not with them: every form of the call leaves them whole
+    assert binding.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) <= binding.SLOPE_STATIC_SCRATCH_BYTES
+    assert binding.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) >= binding.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, 0)
+    assert binding.slope_spmm_fwd_plan(b, d_in, d_out, r)["product"] == 2      # the tile kernel
+
+
 def test_binding_refuses_host_tensors():
     import torch
     with pytest.raises(ValueError):

@@ -160,3 +160,17 @@ def test_dense_product_with_rows_of_any_multiple_of_four(n, m, K):
     gen.manual_seed(inputs.SEED_BASE + n + m)
     B, A = (torch.randn((rows, K), generator=gen, device="cuda").to(torch.bfloat16) for rows in (n, m))
     assert_all_close(sl.slope_gemm_tn(B, A), B.float() @ A.float().t(), "C")
+
+
+# products whose split over k would not leave the adapter room in the static scratch: by either rule of the split, the
+# static call accepts what the query says and takes the route of the workspace call
+@pytest.mark.parametrize("b,d_out,d_in,r", [(378, 640, 32384, 256), (1500, 512, 36864, 512)])
+def test_static_scratch_where_slabs_would_not_fit(b, d_out, d_in, r):
+    assert sl.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) <= sl.SLOPE_STATIC_SCRATCH_BYTES
+    check_layer(b, d_out, d_in, r, backward=False)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + b)
+    X, W, L, R = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+                  for shape in ((b, d_in), (d_out, d_in), (d_in, r), (r, d_out)))
+    vals, meta, _ = sl.slope_prune_rows(W)
+    assert torch.equal(sl.slope_spmm_fwd_static(X, vals, meta, L, R), sl.slope_spmm_fwd(X, vals, meta, L, R))
