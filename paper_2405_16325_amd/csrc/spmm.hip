@@ -1077,10 +1077,11 @@ void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
         return;
     }
     // Few tokens (inference): the product is a single pass over the packed weight, bound by HBM.
-    // Narrow token tiles, and weight tiles small enough that every compute unit streams its share.
+    // Narrow token tiles, and weight tiles small enough that every compute unit streams its share.  Up to 64 tokens there
+    // are more than 256 tiles of 64 x 64 here: the generic kernel's four groups take two rounds for what a round of the
+    // tile kernel's 128 x 64 does (64 tokens, us: 20480 x 1024 11.5 / 8.6, 20480 x 5120 42.2 / 33.6, 18432 x 9216 69 / 56).
     if (n <= 128) {
-        const bool many = (m + 127) / 128 >= 200;
-        bm = many ? 128 : 64;
+        bm = n <= 64 || (m + 127) / 128 >= 200 ? 128 : 64;
         bn = n <= 64 ? 64 : 128;
         return;
     }
