@@ -16,6 +16,7 @@
 // D rows are d_in and D columns d_out, so a lane's four accumulators (column l%16, rows
 // 4*(l/16) .. +3) are exactly one group of four of W^R's row: the epilogue picks two of them with
 // the group's metadata nibble and stores one 4-byte pair of the packed gradient.
+#include <cmath>
 #include <numeric>
 
 #include "pipeline.h"
@@ -704,9 +705,11 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
 // sums for a second kernel, at most as many as fit beside each other, since a thin second round costs as much as the
 // first (5120 x 64 over 16384 tokens in tiles of 64 x 64: 1 slab 95 us, 3 slabs 44.7, 4 slabs 61.7).
 // The rule takes the least of an estimate: the long operand at 4.6 TB/s, or what a compute unit pulls for its tiles
-// at 41 B/ns; slabs cost 3 us for the second launch, 0.4 us each and their traffic (5120 x 64 / 9216 x 128 / 2560 x 64
-// over 16384 / 16384 / 4096 tokens: estimates 41 / 75 / 12 us, measured 44.7 / 76 / 11.8; before, in tiles of 128 x 64
-// without slabs, 108 / 133 / 31).
+// at 41 B/ns; slabs cost 3 us for the second launch, 0.4 us each and their traffic.  With few tokens there is room for more
+// slabs than pay: the best number is where a further one adds as much to the second kernel as it takes from the first
+// (dY R^T of 127 x 17664, rank 32: 69 slabs 11.4 + 20.8 us, the call with its product 121.6; 17 slabs 103.2).
+// 5120 x 64 / 9216 x 128 / 2560 x 64 over 16384 / 16384 / 4096 tokens: estimates 41 / 75 / 12 us, measured 44.7 / 76 / 11.8;
+// before, in tiles of 128 x 64 without slabs, 108 / 133 / 31.
 struct SkinnyPlan { int bm, bn, slabs, slab_steps; };
 static SkinnyPlan skinny_plan(int64_t n, int64_t m, int64_t K, size_t partial_bytes) {
     const int bms[5] = {128, 64, 64, 128, 256}, bns[5] = {64, 64, 128, 128, 64};
@@ -715,19 +718,22 @@ static SkinnyPlan skinny_plan(int64_t n, int64_t m, int64_t K, size_t partial_by
     double best_us = 1e300;
     for (int c = 0; c < 5; ++c) {
         const int64_t tiles = ((m + bms[c] - 1) / bms[c]) * ((n + bns[c] - 1) / bns[c]);
+        const double pull = 128.0 * (double)(bms[c] + bns[c]) / 41e3;           // per k-step
+        const double per_slab = 0.4 + 8.0 * (double)n * (double)m / 10e6;
         int64_t slabs = RESIDENT / tiles;
         if (slabs > ksteps / 4) slabs = ksteps / 4;          // at least four k-steps per slab
         const int64_t room = (int64_t)(partial_bytes / ((size_t)n * (size_t)m * 4));
         if (slabs > room) slabs = room;
-        if (slabs < 1) slabs = 1;
-        const int64_t steps = (ksteps + slabs - 1) / slabs;
-        slabs = (ksteps + steps - 1) / steps;
-        const double rounds = (double)((tiles * slabs + RESIDENT - 1) / RESIDENT);
-        const double pull = rounds * (double)steps * 128.0 * (double)(bms[c] + bns[c]) / 41e3;
-        const double stream = 2.0 * (double)longer * (double)K / 4.6e6;
-        const double us = (pull > stream ? pull : stream) +
-                          (slabs > 1 ? 3.0 + 0.4 * (double)slabs + 8.0 * (double)slabs * (double)n * (double)m / 10e6 : 0.0);
-        if (us < best_us) { best_us = us; best = {bms[c], bns[c], (int)slabs, (int)steps}; }
+        const double least = sqrt((double)ksteps * pull / per_slab);             // more slabs cost more than they save
+        if ((double)slabs > least) slabs = (int64_t)(least + 0.5);
+        for (const int64_t want : {slabs, (int64_t)1}) {
+            if (want < 1) continue;
+            const int64_t steps = (ksteps + want - 1) / want, cut = (ksteps + steps - 1) / steps;
+            const double rounds = (double)((tiles * cut + RESIDENT - 1) / RESIDENT);
+            const double pulled = rounds * (double)steps * pull, stream = 2.0 * (double)longer * (double)K / 4.6e6;
+            const double us = (pulled > stream ? pulled : stream) + (cut > 1 ? 3.0 + per_slab * (double)cut : 0.0);
+            if (us < best_us) { best_us = us; best = {bms[c], bns[c], (int)cut, (int)steps}; }
+        }
     }
     return best;
 }

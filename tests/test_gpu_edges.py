@@ -79,7 +79,9 @@ def test_generic_sparse_kernel(b, d_out, d_in, r):
 # the skinny adapter products of whole k-steps: every tile shape the plan picks, with and without slabs over the
 # contraction (one short of a slab's four k-steps, a last slab that is shorter, ranks that fill no tile)
 @pytest.mark.parametrize("b,d_out,d_in,r", [(130, 640, 704, 32), (3000, 4160, 832, 320), (4096, 2560, 1280, 64),
-                                            (6000, 2624, 1088, 96), (5000, 9216, 512, 128), (1088, 448, 9280, 512)])
+                                            (6000, 2624, 1088, 96), (5000, 9216, 512, 128), (1088, 448, 9280, 512),
+                                            # few tokens: slabs up to the number that pays, on a tile or two
+                                            (127, 8256, 512, 32), (2, 2048, 1024, 160)])
 def test_skinny_adapter_products(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
 
