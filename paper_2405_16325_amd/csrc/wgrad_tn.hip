@@ -335,7 +335,10 @@ struct SplitSmem {
 // (every aligned-th): no gaps, a bundle's parts one after the other.
 // 400 tiles (5120 x 5120, 16384 tokens): 617 us as two rounds, 359 + 217 + 25 with the 144 leftover ones cut; 36864 x 9216,
 // 64 leftover tiles in shares per workgroup before: 122 + 24, now 104 + 17.
-struct TailPlan { int first_tile, tiles, bundle, lanes_per_xcd, lanes, share, aligned, parts; double steps; };
+// Short contractions have whole numbers of shares per bundle instead (row > ksteps: the last one is cut short): no share
+// then has a second part to start.
+struct TailPlan { int first_tile, tiles, bundle, lanes_per_xcd, lanes, share, row, aligned, parts; double steps; };
+constexpr TailPlan NO_TAIL = {0, 0, 1, 1, 0, 1, 1, 1, 0, 0.0};
 
 template <int EPI, bool TAIL>
 __global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t* __restrict__ At, int m,
@@ -356,9 +359,9 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t
     int at = lane_id * tail.share, at_end = at + tail.share;
 next_part:
     if (TAIL) {
-        const int c = at / (kp / 64), tile = c * tail.bundle + member;
-        k_first = at - c * (kp / 64);
-        if (tile >= tail.tiles) return;                       // the end of the row, or a member the last bundle does not have
+        const int c = at / tail.row, tile = c * tail.bundle + member;
+        k_first = at - c * tail.row;
+        if (tile >= tail.tiles || k_first >= kp / 64) return; // the end of the row, or a member the last bundle does not have
         ksteps = at_end - at < kp / 64 - k_first ? at_end - at : kp / 64 - k_first;
         tile_of_position(tail.first_tile + tile, tiles_m, tiles_n, tm, tn);
     } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
@@ -481,7 +484,7 @@ next_part:
 #undef ODD_LOADS
     WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
     if (TAIL) {
-        const int c = at / (kp / 64);
+        const int c = at / tail.row;
         f32x4* dst = partial + (int64_t)((lane_id + c - c / tail.aligned) * tail.bundle + member) * (MF * NF * TN_THREADS) + t;
 #pragma unroll
         for (int i = 0; i < MF; ++i)
@@ -516,7 +519,7 @@ __global__ void __launch_bounds__(TN_THREADS) tail_finish_kernel(const f32x4* __
     const int m0 = tm * S::BM, n0 = tn * S::BN;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave & 1, wn = wave >> 1, l16 = lane & 15, lq = lane >> 4;
-    const int c = tile / tail.bundle, first = c * ksteps / tail.share, last = ((c + 1) * ksteps - 1) / tail.share;
+    const int c = tile / tail.bundle, first = c * tail.row / tail.share, last = (c * tail.row + ksteps - 1) / tail.share;
     constexpr int PART = MF * NF * TN_THREADS;
     const f32x4* src = partial + (int64_t)((first + c - c / tail.aligned) * tail.bundle + tile % tail.bundle) * PART + j * TN_THREADS + t;
     f32x4 acc[MF];
@@ -572,9 +575,12 @@ hipError_t launch_dense_tn(const bf16_t* At, int64_t m, const bf16_t* Bt, int64_
 // order has positions there).  An XCD's 32 compute units hold 32 / bundle lanes; the bundle is the largest (its tiles share
 // panels) whose shares are within 1/16 of the shortest.  In units of a k-step (1.36 us) a share costs its k-steps, about 6
 // for every part, the parts' way through memory (256 KiB each, written and read at 6 TB/s: 0.065 per part) and a launch
-// (5); a round of whole tiles costs ksteps + 6.
+// (5); a round of whole tiles costs ksteps + 6.  Where a bundle can be cut into whole shares, its lanes have a part each and
+// its tiles fewer of them to add: then the cheaper of the two.  (19 k-steps, us: 4096 x 5120 uneven shares 77.8, whole
+// ones 72.1; 3328 x 6656 83.1 / 76.8; 128 k-steps: 3328 x 6656 282 / 266.  More than half a round left: 5120 x 5120, 128
+// k-steps, where the rule begins to cut: 316 not cut, 321 cut; 256 k-steps: 627 / 597.)
 inline TailPlan tail_plan(int64_t tiles_m, int64_t tiles_n, int64_t ksteps) {
-    TailPlan p = {0, 0, 1, 1, 0, 1, 1, 0, 0.0};
+    const TailPlan p = NO_TAIL;
     const int64_t tiles = tiles_m * tiles_n;
     if (!wide_grid((int)tiles_m, (int)tiles_n) || tiles < RESIDENT || tiles > (1 << 30) || ksteps > (1 << 20)) return p;
     const int64_t rem = tiles % RESIDENT;
@@ -589,16 +595,37 @@ inline TailPlan tail_plan(int64_t tiles_m, int64_t tiles_n, int64_t ksteps) {
             if (pass == 0) { if (sh < shortest) shortest = sh; }
             else if (!bundle && sh * 16 <= shortest * 17) { bundle = e; share = sh; lanes_per_xcd = per; }
         }
-    const int64_t bundles = (rem + bundle - 1) / bundle, lanes = (bundles * ksteps + share - 1) / share;
-    const int64_t aligned = share / std::gcd(share, ksteps), parts = lanes + bundles - 1 - (bundles - 1) / aligned;
-    double cost = (double)share + 6.0 * (1.0 + (double)((share + ksteps - 1) / ksteps)) + 0.065 * (double)(parts * bundle) + 5.0;
+    const int64_t bundles = (rem + bundle - 1) / bundle;
+    int64_t lanes = (bundles * ksteps + share - 1) / share;
+    int64_t aligned = share / std::gcd(share, ksteps), parts = lanes + bundles - 1 - (bundles - 1) / aligned, row = ksteps;
+    const double shares = (double)share + 6.0 * (1.0 + (double)((share + ksteps - 1) / ksteps)) + 0.065 * (double)(parts * bundle) + 5.0;
+    double cost = shares;
     if (rem <= RESIDENT / 2 && ksteps >= 16) {                // measured: the cut never lost here; a share of the round + 1/4
         const int64_t slabs = RESIDENT / rem < ksteps / 8 ? RESIDENT / rem : ksteps / 8;
         cost = ((double)ksteps + 6.0) * (1.0 / (double)slabs + 0.25);
     } else if (cost > 0.95 * ((double)ksteps + 6.0)) {
         return p;
     }
-    return {(int)(tiles - rem), (int)rem, (int)bundle, (int)lanes_per_xcd, (int)lanes, (int)share, (int)aligned, (int)parts, cost};
+    // whole shares: as many per bundle as an XCD's lanes and eight k-steps each allow
+    double least = shares;
+    for (int64_t e = rem < PER_XCD ? rem : PER_XCD; e >= 1; --e) {
+        const int64_t count = (rem + e - 1) / e;
+        int64_t cut = XCDS * (PER_XCD / e) / count;
+        if (cut > ksteps / 8) cut = ksteps / 8;
+        if (cut < 2) continue;
+        const int64_t sh = (ksteps + cut - 1) / cut;
+        cut = (ksteps + sh - 1) / sh;
+        const double whole = (double)sh + 6.0 + 0.065 * (double)(cut * rem) + 5.0;
+        if (whole >= least) continue;
+        least = whole;
+        bundle = e;
+        lanes_per_xcd = PER_XCD / e;
+        share = sh;
+        row = cut * sh;
+        lanes = parts = cut * count;
+        aligned = 1;
+    }
+    return {(int)(tiles - rem), (int)rem, (int)bundle, (int)lanes_per_xcd, (int)lanes, (int)share, (int)row, (int)aligned, (int)parts, cost};
 }
 
 // tail: scratch for the parts of the leftover tiles (masked packed results only), or null
@@ -610,12 +637,12 @@ hipError_t launch_dense_tn_split(const bf16_t* At, int64_t m, const bf16_t* Bt, 
     int tiles_m = (int)((m + S::BM - 1) / S::BM), tiles_n = (int)((n + S::BN - 1) / S::BN);
     hipError_t e = allow_dynamic_lds<dense_tn_split_kernel<EPI, false>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    const TailPlan p = tail ? tail_plan(tiles_m, tiles_n, kp / 64) : TailPlan{0, 0, 1, 1, 0, 1, 1, 0, 0.0};
+    const TailPlan p = tail ? tail_plan(tiles_m, tiles_n, kp / 64) : NO_TAIL;
     // with a tail the first launch is whole rounds only: workgroups 0 .. first_tile - 1 are exactly the
     // positions 0 .. first_tile - 1 of the order
     const int grid = p.tiles ? p.first_tile : super_grid(tiles_m, tiles_n);
     dense_tn_split_kernel<EPI, false><<<dim3((unsigned)grid), dim3(TN_THREADS), S::TOTAL, s>>>(
-        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, TailPlan{0, 0, 1, 1, 0, 1, 1, 0, 0.0}, nullptr);
+        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, NO_TAIL, nullptr);
     if ((e = hipGetLastError()) != hipSuccess || !p.tiles) return e;
     if constexpr (EPI == EPI_MASKED_PACKED) {
         if ((e = allow_dynamic_lds<dense_tn_split_kernel<EPI, true>>(S::TOTAL)) != hipSuccess) return e;

@@ -139,6 +139,14 @@ def test_weight_gradient_with_a_large_last_round(b, d_out, d_in):
     check_layer(b, d_out, d_in)
 
 
+# leftover tiles on short contractions, in whole shares: the last one shorter, a last bundle that is not full, tiles and
+# tokens that fill neither
+@pytest.mark.parametrize("b,d_out,d_in", [(1153, 4096, 5120), (1640, 1000, 19840), (2000, 4352, 4352), (1100, 3272, 6624)])
+def test_weight_gradient_with_leftover_tiles_and_few_tokens(b, d_out, d_in):
+    assert sl.slope_workspace_bytes(sl.SLOPE_CALL_WGRAD_MASKED_T, b, d_in, d_out) > 0
+    check_layer(b, d_out, d_in)
+
+
 # input gradients with scratch: slabs by either rule, a last slab of one k-step, few tokens in slices, none
 @pytest.mark.parametrize("b,d_out,d_in,some", [(700, 4160, 2112, True), (512, 4096, 4096, True), (129, 8256, 520, True),
                                                (1500, 8192, 1032, True), (16, 36864, 2048, True), (2048, 3072, 768, False)])
