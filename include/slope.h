@@ -312,8 +312,8 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  * would launch for a shape.  The choices are cost estimates over the shape alone, so that tests can
  * pin the regimes.  plan: host int32[6]
  *   [0] product: 0 small-batch kernel (one pass over the packed weight), 1 tile kernel with the
- *       contraction split into slabs (needs the workspace), 2 tile kernel (64 x 64: the generic
- *       kernel's form for whole pairs of k-steps), 3 generic kernel (d_in not a multiple of 128 on
+ *       contraction split into slabs (needs the workspace), 2 tile kernel (one round of 64 x 64:
+ *       the generic kernel's form for whole pairs of k-steps), 3 generic kernel (d_in not a multiple of 128 on
  *       few tiles, or of 64 on any number), 4 small-batch kernel in its row-split form
  *       (d_in a multiple of 1024 and enough weight rows, or the
  *       workspace to cut the contraction into slices)

@@ -87,14 +87,12 @@ def test_contractions_that_are_no_multiple_of_256_take_the_generic_kernel():
     assert sl.slope_spmm_fwd_plan(300, 512, 448)["product"] == TILE
 
 
-@pytest.mark.parametrize("b,d_out,d_in", [(33, 16640, 1024), (64, 20480, 1024), (64, 20480, 1088), (64, 25344, 1024), (64, 36864, 576)])
-def test_more_than_a_round_of_64_x_64_tiles_takes_wider_ones(b, d_out, d_in):
+@pytest.mark.parametrize("b,d_out,d_in", [(33, 16640, 1024), (64, 20480, 1024), (64, 20480, 1088), (64, 25344, 576)])
+def test_more_than_a_round_of_64_x_64_tiles_stays_on_the_tile_kernel(b, d_out, d_in):
     assert -(-d_out // 64) > 256
     p = sl.slope_spmm_fwd_plan(b, d_in, d_out, 0, False)
-    assert (p["product"], p["rows"], p["tokens"]) == (TILE, 128, 64)
-    # one round is the generic kernel's, whose four groups the plan names 64 x 64 tiles
-    p = sl.slope_spmm_fwd_plan(b, 1024, 16384, 0, False)
     assert (p["product"], p["rows"], p["tokens"]) == (TILE, 64, 64)
+    assert sl.slope_spmm_fwd_plan(b, d_in, 36864, 0, False)["rows"] == 128
 
 
 def test_adapter_product_regimes():

@@ -186,7 +186,7 @@ def test_static_scratch_where_slabs_would_not_fit(b, d_out, d_in, r):
     assert torch.equal(sl.slope_spmm_fwd_static(X, vals, meta, L, R), sl.slope_spmm_fwd(X, vals, meta, L, R))
 
 
-# 33 to 64 tokens on more weight rows than a round of 64 x 64 tiles: 128 x 64, whole quads of k-steps and remainders, an
+# 33 to 64 tokens on more weight rows than a round of 64 x 64 tiles: the ring kernel again, whole quads of k-steps and remainders, an
 # adapter too wide for slabs; the input gradient with adapters on the same tiles
 @pytest.mark.parametrize("b,d_out,d_in,r", [(64, 20480, 1024, 0), (33, 16648, 320, 32), (64, 512, 20480, 64), (50, 1088, 16640, 96)])
 def test_few_tokens_on_many_rows(b, d_out, d_in, r):
