@@ -979,10 +979,12 @@ static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
                           + (sl > 1 ? 2.0 * sl * (double)n * (double)m * 4.0 / hbm : 0.0);
         if (ns < best_ns) { best_ns = ns; best = sl; }
     }
-    // One round of 64 x 64 tiles with four groups takes about 3 us and 2 us per 512 of the contraction, slabs about 1.25
-    // times the estimate and 4 us for two launches (us, 64 x 64 / slabs: 128 tokens, 4096 x 2048 10.4 / 18.9; 200 tokens,
-    // 4096 x 4096 18.3 / 23.3; 100 tokens, 5120 x 5120 22.0 / 22.2; 64 tokens, 9216 x 9216 48 / 35).
-    if (one_round_of_64(n, m) && 3e3 + 2.05e3 * (double)K / 512.0 <= 4e3 + 1.25 * best_ns) return 0;
+    // One round of 64 x 64 tiles with four groups takes about 2 us and 2.6 us per 512 of the contraction on weights that come
+    // from HBM, slabs the estimate and 8 us, or the weight at 3.4 TB/s (us, 64 x 64 / slabs: 64 tokens, 4096 x 2048
+    // 12.8 / 18.8, 4096 x 4096 20.9 / 19.8, 16384 x 4096 25.1 / 28.4, 9984 x 7168 38.2 / 30.7, 12544 x 12288 67.3 / 52.8;
+    // 128 tokens, 4096 x 4096 20.5 / 23.9, 7168 x 7168 36.3 / 30.1; 39 tokens, 16384 x 9216 with rank 32 55.3 / 60.3).
+    const double slabs_ns = 8e3 + best_ns > weight / 3.4e3 ? 8e3 + best_ns : weight / 3.4e3;
+    if (one_round_of_64(n, m) && 2e3 + 2.6e3 * (double)K / 512.0 <= slabs_ns) return 0;
     return best < 2 ? 0 : best;
 }
 

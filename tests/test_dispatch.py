@@ -65,6 +65,13 @@ def test_mid_batches_split_the_contraction_only_with_scratch_and_few_tiles(b):
     assert (big["product"] == SLABS) == (b <= 128)
 
 
+@pytest.mark.parametrize("b,d_out,d_in,slabs", [(64, 9984, 7168, True), (64, 12288, 12288, True), (128, 7168, 7168, True), (64, 12544, 20480, True),
+                                                (64, 4096, 2048, False), (128, 4096, 4096, False), (48, 16384, 5120, False)])
+def test_long_contractions_split_although_64_x_64_tiles_fit_a_round(b, d_out, d_in, slabs):
+    assert -(-d_out // 64) * -(-b // 64) <= 256
+    assert (sl.slope_spmm_fwd_plan(b, d_in, d_out)["product"] == SLABS) == slabs
+
+
 def test_slabs_times_tiles_fits_one_round_for_two_token_tiles():
     p = sl.slope_spmm_fwd_plan(256, 9216, 9216, 0, True)       # 36 x 2 tiles
     assert p["slabs"] == 3                                      # 216 workgroups: one round; 4 slabs would need two
