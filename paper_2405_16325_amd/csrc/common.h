@@ -53,8 +53,7 @@ hipError_t launch_adapter_finish(const float* P, int slices, int64_t n, int64_t 
                                  const bf16_t* R, int64_t r, bf16_t* C, hipStream_t s);
 // the same product for a few dozen to a few hundred tokens, split over K with fp32 partial sums in `slabs`
 // (spmm_slab_bytes of them; 0 = this shape does not take the path).  The adapter (r == 0: none) comes as T = X L,
-// or, where T is null, as its sums Q; with a non-null L those are written by workgroups of the product's own first launch
-// (slab_xl_split)
+// or, where T is null, as its sums Q, which workgroups of the product's own first launch write (slab_xl_split)
 struct SlabAdapter {
     const bf16_t* T;
     float* Q;

@@ -63,12 +63,11 @@ hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A
     return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);
 }
 
-// A split product's second kernel adds up the sums of T = X L itself while all its workgroups together read at most this
-// much of them, about 6 TB/s: less where X L has a launch of its own (one launch is saved, not two), and there while it
-// leaves a wavefront at most so many chunks of 32 rows of L (128 tokens, rank 128: 28 MB at 9216 x 9216, 10 us; but 600 MB at
-// 36864 x 9216 with 16 slabs, 54 us against 15 with T; 33 tokens, 36864 x 9216, rank 64, 63 MB: 107 -> 120 us in all).
-constexpr int64_t XL_BESIDE_BYTES = (int64_t)40 << 20, XL_OWN_BYTES = (int64_t)20 << 20;
-constexpr int XL_OWN_STEPS = 6;
+// A split product's second kernel adds up the sums of T = X L itself where workgroups beside the product's compute them
+// (two launches fewer) and all its workgroups together read at most this much of them, about 6 TB/s (128 tokens, rank 128:
+// 28 MB at 9216 x 9216, 10 us; but 600 MB at 36864 x 9216 with 16 slabs, 54 us against 15 with T).  With X L in a launch of
+// its own it never pays: 37 tokens, 9728 x 17664, rank 32 76.5 us, 67.3 with T; 60 tokens, 20480 x 8192 73.1 / 68.5.
+constexpr int64_t XL_BESIDE_BYTES = (int64_t)40 << 20;
 
 }  // namespace
 
@@ -223,18 +222,8 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
         const int64_t slab_read = (d_out + 63) / 64 * ((b + 31) / 32 * 32) * r * 4;
         int64_t held = XL_BESIDE_BYTES / slab_read * b * r;
         if (held > sums_floats) held = sums_floats;
-        bool from_sums = held > 0 && slab_xl_split(b, d_out, d_in, r, held, ad.x);
-        if (held > XL_OWN_BYTES / slab_read * b * r) held = XL_OWN_BYTES / slab_read * b * r;
-        if (!from_sums && held > 0) {                         // no room beside the product: a launch of its own, if it is short
-            ad.L = nullptr;
-            ad.x = xl_split(b, d_in, r, held, RESIDENT);
-            from_sums = ad.x.steps <= XL_OWN_STEPS;
-            if (from_sums) {
-                hipError_t e = launch_xl(x_in, b, d_in, l, r, ad.x, sums, nullptr, s);
-                if (e != hipSuccess) return finish(e);
-            }
-        }
-        if (from_sums) return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
+        if (held > 0 && slab_xl_split(b, d_out, d_in, r, held, ad.x))
+            return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
     }
     if (adapter) {                                            // T = X L, rounded to bf16
         hipError_t e;
