@@ -244,18 +244,24 @@ def slope_spmm_fwd_static(X: torch.Tensor, vals: torch.Tensor, meta: torch.Tenso
     return Y
 
 
-def slope_spmm_bwd_x(dY: torch.Tensor, vals_t: torch.Tensor, meta_t: torch.Tensor, out=None):
-    """dX = dY W^{R,C}.  dY bf16[b, d_out]; packed (W^{R,C})^T with rows = d_in."""
+def slope_spmm_bwd_x(dY: torch.Tensor, vals_t: torch.Tensor, meta_t: torch.Tensor, out=None, workspace=None):
+    """dX = dY W^{R,C}.  dY bf16[b, d_out]; packed (W^{R,C})^T with rows = d_in.
+    workspace: a uint8 device tensor of slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out) bytes.  Without one
+    it is allocated here together with the result; a call with `out` allocates nothing and does without."""
     d_in, d_out = _packed(vals_t, meta_t, "(W^{R,C})^T")
     if dY is None or dY.dim() != 2:
         raise ValueError("dY must be a matrix")
     b = dY.shape[0]
     _want(dY, BF16, (b, d_out), "dY")
     dX = _want(out, BF16, (b, d_in), "out") if out is not None else torch.empty((b, d_in), dtype=BF16, device=dY.device)
-    workspace = _scratch(None, slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out), dY.device, "workspace")
+    if out is None or workspace is not None:
+        workspace = _scratch(workspace, slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out), dY.device, "workspace")
+    if workspace is None:
+        _check("slope_spmm_bwd_x", lib().slope_spmm_bwd_x(_ptr(dY), b, _ptr(vals_t), _ptr(meta_t), d_out, d_in, _ptr(dX),
+                                                          _stream()))
+        return dX
     _check("slope_spmm_bwd_x_ws", lib().slope_spmm_bwd_x_ws(_ptr(dY), b, _ptr(vals_t), _ptr(meta_t), d_out, d_in, _ptr(dX),
-                                                            _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                                                            _stream()))
+                                                            _ptr(workspace), workspace.numel(), _stream()))
     return dX
 
 

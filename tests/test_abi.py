@@ -171,6 +171,37 @@ def test_binding_checks_dtypes_and_shapes_before_the_call():
         binding.slope_prune_rows(Fake((8, 8), bf, cuda=False))
 
 
+def test_input_gradient_into_a_given_tensor_allocates_nothing(monkeypatch):
+    import torch
+
+    class Fake:
+        """Stands in for a device tensor (there is no GPU here): what the checks look at, and an address for the recorder."""
+        def __init__(self, shape, dtype):
+            self.shape, self.dtype, self.is_cuda, self.device = tuple(shape), dtype, True, "cuda:0"
+        def dim(self): return len(self.shape)
+        def is_contiguous(self): return True
+        def numel(self): return self.shape[0]
+        def data_ptr(self): return 0x1000
+
+    class Recorder:
+        def __init__(self): self.calls = []
+        def __getattr__(self, name):
+            return lambda *args: self.calls.append(name) or (1 << 20 if name == "slope_workspace_bytes" else 0)
+
+    def refuse(*args, **kwargs): raise AssertionError("the call allocates")
+
+    rec, bf, u8 = Recorder(), torch.bfloat16, torch.uint8
+    monkeypatch.setattr(binding, "lib", lambda: rec)
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    monkeypatch.setattr(torch, "empty", refuse)
+    dY, vals, meta, dX = Fake((700, 64), bf), Fake((128, 32), bf), Fake((128, 8), u8), Fake((700, 128), bf)
+    assert binding.slope_spmm_bwd_x(dY, vals, meta, out=dX) is dX and rec.calls[-1] == "slope_spmm_bwd_x"
+    assert binding.slope_spmm_bwd_x(dY, vals, meta, out=dX, workspace=Fake((1 << 20,), u8)) is dX
+    assert rec.calls[-1] == "slope_spmm_bwd_x_ws"
+    with pytest.raises(ValueError, match="bytes"):
+        binding.slope_spmm_bwd_x(dY, vals, meta, out=dX, workspace=Fake((256,), u8))
+
+
 def test_static_scratch_rejects_a_shape_beyond_its_buffer():
     lib = binding.lib()
     b, d_out, d_in, r = 512, 9216, 36864, 128

@@ -151,8 +151,20 @@ def test_weight_gradient_with_leftover_tiles_and_few_tokens(b, d_out, d_in):
 @pytest.mark.parametrize("b,d_out,d_in,some", [(700, 4160, 2112, True), (512, 4096, 4096, True), (129, 8256, 520, True),
                                                (1500, 8192, 1032, True), (16, 36864, 2048, True), (2048, 3072, 768, False)])
 def test_input_gradient_with_scratch(b, d_out, d_in, some):
-    assert (sl.slope_workspace_bytes(sl.SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out) > 0) == some
+    need = sl.slope_workspace_bytes(sl.SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out)
+    assert (need > 0) == some
     check_layer(b, d_out, d_in)
+    dY, W = (torch.randn(shape, device="cuda").to(torch.bfloat16) for shape in ((b, d_out), (d_out, d_in)))
+    vals_t, meta_t, _ = sl.slope_double_prune(*sl.slope_prune_rows(W)[:2])
+    ws = torch.empty(max(need, 256), dtype=torch.uint8, device="cuda")
+    given, plain = torch.empty((b, d_in), dtype=torch.bfloat16, device="cuda"), torch.empty((b, d_in), dtype=torch.bfloat16, device="cuda")
+    dx = sl.slope_spmm_bwd_x(dY, vals_t, meta_t)
+    allocations = torch.cuda.memory_stats()["allocation.all.allocated"]
+    sl.slope_spmm_bwd_x(dY, vals_t, meta_t, out=given, workspace=ws)
+    sl.slope_spmm_bwd_x(dY, vals_t, meta_t, out=plain)                # the kernels without the split
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == allocations
+    assert torch.equal(given, dx)
+    assert_all_close(plain, dx.float(), "dX without scratch", two_stage=True)
 
 
 # a few tokens beyond whole tiles, which a pass of the small-batch kernel takes: one token and several, an odd number of
