@@ -129,6 +129,15 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
                                 int64_t d_in, const bf16_t* L, const bf16_t* R, int64_t r, bf16_t* gvals, bf16_t* dL,
                                 bf16_t* dR, void* workspace, hipStream_t s);
 
+// Launches of any number of workgroups as rows of 2^20: a dimension of a grid holds fewer than 2^32 work items, and a launch
+// beyond that runs a part of them without an error.  A kernel takes flat_block() and leaves when it is past the last.
+constexpr int64_t GRID_ROW = (int64_t)1 << 20;
+inline bool grid_fits(int64_t blocks) { return blocks <= GRID_ROW * 65535; }
+inline dim3 grid_of(int64_t blocks) {
+    return blocks <= GRID_ROW ? dim3((unsigned)blocks) : dim3((unsigned)GRID_ROW, (unsigned)((blocks + GRID_ROW - 1) / GRID_ROW));
+}
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Per 16-bit half: 1 where kj > ki, else 0 (saturating subtract, then min with 1).  Written as instructions
 // because the compiler turns the portable form back into one compare and one select per half.
 __device__ __forceinline__ uint32_t pk_beats(uint32_t kj, uint32_t ki, uint32_t ones) {

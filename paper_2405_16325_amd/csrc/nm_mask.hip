@@ -34,7 +34,7 @@ template <int M>
 __global__ void __launch_bounds__(256) nm_mask_rows_kernel(const u32x4* __restrict__ W, size_t chunks, int n,
                                                            const uint8_t* __restrict__ cand,
                                                            uint8_t* __restrict__ mask, u32x4* __restrict__ masked) {
-    const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t c = (size_t)flat_block() * 256 + threadIdx.x;
     if (c >= chunks) return;
     const u32x4 v = W[c];
     const uint32_t cb = cand ? cand[c] : 0xFFu;
@@ -122,7 +122,9 @@ __global__ void __launch_bounds__(512 / M) nm_mask_cols_kernel(const bf16_t* __r
     __shared__ __align__(16) uint8_t tile[64 * TR * 2];       // [column][row]; the 16-byte pieces of column c rotated by c / 8
     const size_t cpr = (size_t)cols / 8;                      // 8-column chunks per row
     const int tx = threadIdx.x & 7, ty = threadIdx.x >> 3;
-    const size_t tile_x = blockIdx.x % tiles_x, tile_y = blockIdx.x / tiles_x;
+    const unsigned block = (unsigned)flat_block();
+    const size_t tile_x = block % tiles_x, tile_y = block / tiles_x;
+    if (tile_y * TR >= (size_t)rows) return;                  // past the last tile (uniform)
     const size_t cc = tile_x * 8 + tx;                        // chunk of 8 columns
     const size_t row0 = tile_y * TR + ty * M;                 // first row of the group
     const bool live = cc < cpr && row0 < (size_t)rows;        // rows % M == 0: a group is whole or absent
@@ -205,14 +207,14 @@ hipError_t launch_m(const bf16_t* W, int64_t rows, int64_t cols, int n, int axis
             W, (int)rows, (int)cols, n, cand, mask, masked, masked_t);
     else if (axis == 0) {
         const size_t chunks = (size_t)rows * (size_t)(cols / 8);
-        const size_t blocks = (chunks + 255) / 256;           // extents below 2^31: fewer than 2^31 workgroups unless refused here
-        if (blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
-        nm_mask_rows_kernel<M><<<dim3((unsigned)blocks), dim3(256), 0, s>>>((const u32x4*)W, chunks, n, cand, mask,
+        const int64_t blocks = (int64_t)((chunks + 255) / 256);
+        if (!grid_fits(blocks)) return hipErrorInvalidValue;
+        nm_mask_rows_kernel<M><<<grid_of(blocks), dim3(256), 0, s>>>((const u32x4*)W, chunks, n, cand, mask,
                                                                           (u32x4*)masked);
     } else {
         const int64_t tiles_x = (cols + 63) / 64, tiles = tiles_x * ((rows + 63) / 64);
         if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-        nm_mask_cols_kernel<M><<<dim3((unsigned)tiles), dim3(512 / M), 0, s>>>(W, (int)rows, (int)cols, n, cand, mask, masked,
+        nm_mask_cols_kernel<M><<<grid_of(tiles), dim3(512 / M), 0, s>>>(W, (int)rows, (int)cols, n, cand, mask, masked,
                                                                              masked_t, (unsigned)tiles_x);
     }
     return hipGetLastError();

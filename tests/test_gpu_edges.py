@@ -203,3 +203,20 @@ def test_static_scratch_where_slabs_would_not_fit(b, d_out, d_in, r):
 @pytest.mark.parametrize("b,d_out,d_in,r", [(64, 20480, 1024, 0), (33, 16648, 320, 32), (64, 512, 20480, 64), (50, 1088, 16640, 96)])
 def test_few_tokens_on_many_rows(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
+
+
+# masks of weights whose grid would exceed 2^32 work items in one dimension (2^35 elements by rows, 2^36 in column pairs):
+# one block of rows repeated, its masks against those of the block alone
+@pytest.mark.parametrize("axis,rows,cols", [(0, 1 << 18, (1 << 17) + 8), (1, 1 << 18, (1 << 18) + 64)])
+def test_masks_of_the_largest_weights(axis, rows, cols):
+    print(f"prune_mask axis={axis} {rows} x {cols}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + axis)
+    block = torch.randn((64, cols), generator=gen, device="cuda").to(torch.bfloat16)
+    want, _, _ = sl.slope_prune_mask(block, 1, 2, axis, masked=False)
+    W = torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda")
+    W.view(-1, 64, cols).copy_(block)
+    got, _, _ = sl.slope_prune_mask(W, 1, 2, axis, masked=False)
+    del W
+    for part in got.view(-1, 64, cols // 8).split(256):
+        assert torch.equal(part, want.expand_as(part))
