@@ -26,9 +26,9 @@ __device__ __forceinline__ void skinny_product_tile(const SkinnyProduct& p, int 
 template <bool PBK, bool PAK, bool QBK, bool QAK>
 __global__ void __launch_bounds__(SK_WAVES * 64) skinny_ragged_kernel(SkinnyGrid p, SkinnyGrid q) {
     __shared__ __align__(16) uint8_t smem[SK_LDS];
-    const int b = (int)blockIdx.x;
+    const int b = (int)flat_block();
     if (b < p.tiles) skinny_product_tile<PBK, PAK>(p.p, b, smem);
-    else skinny_product_tile<QBK, QAK>(q.p, b - p.tiles, smem);
+    else if (b - p.tiles < q.tiles) skinny_product_tile<QBK, QAK>(q.p, b - p.tiles, smem);
 }
 
 inline int64_t skinny_tiles(const SkinnyProduct& p) { return ((p.m + SK_BJ - 1) / SK_BJ) * ((p.n + SK_BI - 1) / SK_BI); }
@@ -36,8 +36,8 @@ inline int64_t skinny_tiles(const SkinnyProduct& p) { return ((p.m + SK_BJ - 1) 
 template <bool PBK, bool PAK, bool QBK, bool QAK>
 hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, bool two, hipStream_t s) {
     const int64_t tp = skinny_tiles(p), tq = two ? skinny_tiles(q) : 0;
-    if (tp + tq > 0x7FFFFFFF) return hipErrorInvalidValue;
-    skinny_ragged_kernel<PBK, PAK, QBK, QAK><<<dim3((unsigned)(tp + tq)), dim3(SK_WAVES * 64), 0, s>>>(SkinnyGrid{p, (int)tp},
+    if (tp + tq > 0x7FFFFFFF - GRID_ROW) return hipErrorInvalidValue;
+    skinny_ragged_kernel<PBK, PAK, QBK, QAK><<<grid_of(tp + tq), dim3(SK_WAVES * 64), 0, s>>>(SkinnyGrid{p, (int)tp},
                                                                                                    SkinnyGrid{q, (int)tq});
     return hipGetLastError();
 }

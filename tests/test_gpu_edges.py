@@ -220,3 +220,20 @@ def test_masks_of_the_largest_weights(axis, rows, cols):
     del W
     for part in got.view(-1, 64, cols // 8).split(256):
         assert torch.equal(part, want.expand_as(part))
+
+
+# as many tokens as give the kernel for ragged extents 2^23 tiles of 512 threads: a block of tokens repeated
+def test_ragged_adapter_product_of_the_most_tokens():
+    b, d, r = (1 << 28) + 64, 8, 32
+    print(f"b={b} d={d} r={r}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE)
+    x, W, L, R = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16) for shape in ((64, d), (d, d), (d, r), (r, d)))
+    vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    X = torch.empty((b, d), dtype=torch.bfloat16, device="cuda")
+    X.view(-1, 64, d).copy_(x)
+    Y = sl.slope_spmm_fwd(X, vals, meta, L, R)
+    want = x.float() @ torch.where(unpack_bits(mask), W.float(), 0.0).t() + (x.float() @ L.float()) @ R.float()
+    assert_all_close(Y[:64], want, "Y", two_stage=True)
+    for part in Y.view(-1, 64, d).split(1 << 18):
+        assert torch.equal(part, Y[:64].expand_as(part))
