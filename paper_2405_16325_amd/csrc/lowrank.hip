@@ -19,7 +19,7 @@ struct SkinnyGrid { SkinnyProduct p; int tiles; };
 template <bool BKMAJOR, bool AKMAJOR>
 __device__ __forceinline__ void skinny_product_tile(const SkinnyProduct& p, int tile, uint8_t* smem) {
     const int tiles_m = ((int)p.m + SK_BJ - 1) / SK_BJ;
-    skinny_tile<BKMAJOR, AKMAJOR>(p.B, p.ldb, p.A, p.lda, (int)p.n, (int)p.m, 0, (int)p.K, tile / tiles_m * SK_BI,
+    skinny_tile<BKMAJOR, AKMAJOR>(p.B, p.ldb, p.A, p.lda, (int)p.n, (int)p.m, 0, (uint32_t)p.K, tile / tiles_m * SK_BI,
                                   tile % tiles_m * SK_BJ, p.C, nullptr, smem);
 }
 

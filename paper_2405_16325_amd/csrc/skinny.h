@@ -26,20 +26,23 @@ constexpr int SK_LDS = SK_WAVES * (SK_STAGE > SK_BI * SK_SUM_PITCH * 4 ? SK_STAG
 
 template <bool KMAJOR, int F>                                   // F fragments of 16 rows
 struct SkinnyOperand {
-    static constexpr int PIECES = F;                            // 16-byte pieces per lane and chunk of 32 k
     static constexpr int PITCH = F * 32 + 32;
     const bf16_t* base;
     int64_t ld;
-    int rows, K, row0;
-    __device__ __forceinline__ void load(int k0, int lane, u32x4 (&v)[F]) const {
+    int rows;
+    uint32_t K;
+    int row0;
+    __device__ __forceinline__ void load(uint32_t k0, int lane, u32x4 (&v)[F]) const {
 #pragma unroll
         for (int u = 0; u < F; ++u) {
             v[u] = (u32x4){0u, 0u, 0u, 0u};
             if (KMAJOR) {
-                const int p = lane + 64 * u, k = k0 + p / (2 * F), row = row0 + 8 * (p % (2 * F));
+                const int p = lane + 64 * u, row = row0 + 8 * (p % (2 * F));
+                const uint32_t k = k0 + (uint32_t)p / (2 * F);
                 if (k < K && row < rows) v[u] = *(const u32x4*)(base + (int64_t)k * ld + row);
             } else {
-                const int row = row0 + 16 * u + (lane & 15), k = k0 + 8 * (lane >> 4);
+                const int row = row0 + 16 * u + (lane & 15);
+                const uint32_t k = k0 + 8 * (lane >> 4);
                 if (k < K && row < rows) v[u] = *(const u32x4*)(base + (int64_t)row * ld + k);
             }
         }
@@ -80,7 +83,7 @@ struct SkinnyOperand {
 // of a workgroup of SK_WAVES wavefronts must make the call (it contains barriers).
 template <bool BKMAJOR, bool AKMAJOR>
 __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_t ldb, const bf16_t* __restrict__ A, int64_t lda,
-                                            int n, int m, int k_begin, int K, int i0, int j0, bf16_t* __restrict__ C,
+                                            int n, int m, uint32_t k_begin, uint32_t K, int i0, int j0, bf16_t* __restrict__ C,
                                             float* __restrict__ sums, uint8_t* smem) {
     constexpr int FA = SK_BJ / 16, FB = SK_BI / 16;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -93,10 +96,11 @@ __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_
 #pragma unroll
         for (int j = 0; j < FB; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     u32x4 va[FA], vb[FB];
-    const int step = 32 * SK_WAVES;
+    constexpr uint32_t step = 32 * SK_WAVES;                    // K < 2^31: a look-ahead past it does not wrap in 32 bits
+    static_assert(0x7FFFFFFFu + 2 * step + 32 > 0x7FFFFFFFu, "k0 + step and the chunk after it");
     oa.load(k_begin + wave * 32, lane, va);
     ob.load(k_begin + wave * 32, lane, vb);
-    for (int k0 = k_begin + wave * 32; k0 < K; k0 += step) {    // uniform per wavefront
+    for (uint32_t k0 = k_begin + wave * 32; k0 < K; k0 += step) {    // uniform per wavefront
         u32x4 na[FA], nb[FB];
         oa.load(k0 + step, lane, na);                           // past the end: zeros, no access
         ob.load(k0 + step, lane, nb);

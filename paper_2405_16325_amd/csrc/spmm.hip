@@ -242,9 +242,9 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
             const int xl_tiles_r = (job.r + SK_BJ - 1) / SK_BJ, xl_tiles = xl_tiles_r * ((n + SK_BI - 1) / SK_BI);
             const int part = id / xl_tiles, tile = id % xl_tiles;
             if (part < job.xl_slabs)
-                skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * job.k_per, min(K, (part + 1) * job.k_per),
-                                         tile / xl_tiles_r * SK_BI, tile % xl_tiles_r * SK_BJ, nullptr,
-                                         job.Q + (size_t)part * n * job.r, smem);
+                skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * (uint32_t)job.k_per,
+                                         min((uint32_t)K, (part + 1) * (uint32_t)job.k_per), tile / xl_tiles_r * SK_BI,
+                                         tile % xl_tiles_r * SK_BJ, nullptr, job.Q + (size_t)part * n * job.r, smem);
             return;
         }
         int tile;

@@ -491,8 +491,9 @@ __global__ void __launch_bounds__(SK_WAVES * 64) xl_split_kernel(const bf16_t* _
                                                                  const bf16_t* __restrict__ L, int r, int k_per,
                                                                  float* __restrict__ Q, bf16_t* __restrict__ T) {
     __shared__ __align__(16) uint8_t smem[SK_LDS];
-    const int tiles_r = (r + SK_BJ - 1) / SK_BJ, k0 = blockIdx.y * k_per;
-    skinny_tile<false, true>(X, d_in, L, r, n, r, k0, min(d_in, k0 + k_per), (int)(blockIdx.x / tiles_r) * SK_BI,
+    const int tiles_r = (r + SK_BJ - 1) / SK_BJ;
+    const uint32_t k0 = blockIdx.y * (uint32_t)k_per;
+    skinny_tile<false, true>(X, d_in, L, r, n, r, k0, min((uint32_t)d_in, k0 + k_per), (int)(blockIdx.x / tiles_r) * SK_BI,
                              (int)(blockIdx.x % tiles_r) * SK_BJ, T, Q ? Q + (size_t)blockIdx.y * n * r : nullptr, smem);
 }
 

@@ -186,9 +186,9 @@ __global__ void __launch_bounds__(256 * WGS_GROUPS) wgrad_groups_kernel(const bf
     const bool a_in = i0 + 8 * c < d_in, b_in = o0 + 8 * c < d_out;      // extents are multiples of 8: whole pieces
     uint4 a_reg, b_reg;
     auto load_global = [&](int slab) {
-        const int tok = slab * WG_KS + row;
-        a_reg = tok < b && a_in ? *(const uint4*)(X + (size_t)tok * d_in + i0 + 8 * c) : make_uint4(0, 0, 0, 0);
-        b_reg = tok < b && b_in ? *(const uint4*)(dY + (size_t)tok * d_out + o0 + 8 * c) : make_uint4(0, 0, 0, 0);
+        const uint32_t tok = (uint32_t)slab * WG_KS + row;     // b < 2^31: past the last token, not around it
+        a_reg = tok < (uint32_t)b && a_in ? *(const uint4*)(X + (size_t)tok * d_in + i0 + 8 * c) : make_uint4(0, 0, 0, 0);
+        b_reg = tok < (uint32_t)b && b_in ? *(const uint4*)(dY + (size_t)tok * d_out + o0 + 8 * c) : make_uint4(0, 0, 0, 0);
     };
     auto store_lds = [&](int stage) {
         uint8_t* base = ring + stage * S::STAGE;
@@ -204,7 +204,7 @@ __global__ void __launch_bounds__(256 * WGS_GROUPS) wgrad_groups_kernel(const bf
     const int a_off = tr_row * S::PITCH_A + 2 * (wm * 32 + tr_col), b_off = tr_row * S::PITCH_B + 2 * (wn * 32 + tr_col);
 
     // group g takes slabs g, g + 4, ...; slabs past the last token are zeros
-    const int trips = ((b + WG_KS - 1) / WG_KS + WGS_GROUPS - 1) / WGS_GROUPS;
+    const int trips = (int)((((uint32_t)b + WG_KS - 1) / WG_KS + WGS_GROUPS - 1) / WGS_GROUPS);
     load_global(group);
     store_lds(0);
     __syncthreads();
