@@ -316,10 +316,13 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  *       the generic kernel's form for whole pairs of k-steps), 3 generic kernel (d_in not a multiple of 128 on
  *       few tiles, or of 64 on any number), 4 small-batch kernel in its row-split form
  *       (d_in a multiple of 1024 and enough weight rows, or the
- *       workspace to cut the contraction into slices)
- *   [1], [2] weight rows and tokens per workgroup      [3] slabs or slices (1 = no split)
- *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens),
+ *       workspace to cut the contraction into slices), 5 tile kernel for the tokens of whole tiles and
+ *       a small-batch kernel for the last few
+ *   [1], [2] weight rows and tokens per workgroup (of the tile kernel)
+ *   [3] slabs or slices (1 = no split); for [0] == 5 the tokens of the small-batch kernel
+ *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens; beside a split product or before it),
  *       2 dense tile kernel, 3 dense tile kernel split over d_in, 4 MFMA kernel for ragged extents (d_in % 64 != 0)
+ *       and short products
  *   [5] chunks of 64 rows of L per partial sum that the scratch is sized by, for [4] == 1
  * with_workspace: whether the call would be given its scratch.  Errors as slope_spmm_fwd.
  */

@@ -37,6 +37,7 @@ hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const u
 // weight rows per workgroup of the small-batch kernel, chunks of 64 rows of L per slab that the scratch of X L is sized by
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn);
 int spmm_generic_edge(int64_t n, int64_t m);                 // edge of the generic kernel's tile
+int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K);   // the last tokens, which the small-batch kernel takes (adapters: K2 <= 0)
 int spmm_stream_rows(int64_t n, int64_t m, int64_t K);
 int xl_subs(int64_t n, int64_t d_in, int64_t r);
 // T = X L for few tokens (n <= XL_SMALL_MAX_TOKENS, d_in % 64 == 0) from L as stored, split over d_in: `slabs` slabs of
@@ -118,6 +119,7 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
 size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m);
 hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, int64_t ld, bf16_t* C,
                                  float* partial_or_null, size_t partial_bytes, hipStream_t s);
+int dense_tn_plain_slabs(int64_t n, int64_t m, int64_t K, size_t partial_bytes);   // of the call above
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s);
 // general N:M magnitude mask (M in {2, 4, 8}); axis 0: groups inside a row, axis 1: inside a column

@@ -51,12 +51,14 @@ size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     return slabs;
 }
 
+constexpr int XL_SHORT_STEPS = 8;                             // of skinny_is_short for T = X L
+
 // T[n, r] = B[n, K] A^T for the skinny products of the adapters.  a_kmajor: A is [K][r] (the factor L as
 // stored) instead of [r][K].  Whole k-steps of 64 go to the tile kernels, anything else and short products to the kernel
 // for ragged extents.
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
                           bf16_t* At_scratch, float* partial, hipStream_t s) {
-    if (K % 64 != 0 || skinny_is_short(n, r, K, a_kmajor ? 8 : 5))
+    if (K % 64 != 0 || skinny_is_short(n, r, K, a_kmajor ? XL_SHORT_STEPS : 5))
         return launch_skinny_ragged({B, K, A, a_kmajor ? r : K, a_kmajor, n, r, K, T}, s);
     const size_t partial_bytes = partial ? dense_tn_plain_partial_bytes(n, r) : 0;
     if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);
@@ -496,11 +498,13 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         if (slices > 0) plan[3] = slices;
     } else {
         const int slabs = with_workspace && fwd_slab_bytes(b, d_in, d_out, r) ? spmm_slab_count(b, d_out, d_in) : 0;
+        const int64_t rest = slabs > 0 ? 0 : spmm_rest_tokens(b, d_out, d_in);
         int bm, bn;
-        spmm_tile_choice(b, d_out, d_in, bm, bn);
+        spmm_tile_choice(b - rest, d_out, d_in, bm, bn);
         if (slabs > 0) { plan[0] = 1; plan[1] = 256; plan[2] = b <= 64 ? 64 : 128; plan[3] = slabs; }
-        else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = spmm_generic_edge(b, d_out); }
+        else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = spmm_generic_edge(b - rest, d_out); }
         else { plan[0] = 2; plan[1] = bm; plan[2] = bn; }
+        if (rest > 0) { plan[0] = 5; plan[3] = (int32_t)rest; }
     }
     if (r > 0) {
         if (d_in % 64 != 0) {
@@ -508,8 +512,10 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         } else if (b <= XL_SMALL_MAX_TOKENS) {
             plan[4] = 1;
             plan[5] = xl_subs(b, d_in, r);
+        } else if (skinny_is_short(b, r, d_in, XL_SHORT_STEPS)) {
+            plan[4] = 4;
         } else {
-            plan[4] = dense_tn_plain_partial_bytes(b, r) ? 3 : 2;
+            plan[4] = dense_tn_plain_slabs(b, r, d_in, dense_tn_plain_partial_bytes(b, r)) > 1 ? 3 : 2;
         }
     }
     return SLOPE_OK;

@@ -1103,7 +1103,7 @@ void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
 // Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 8 us for its launch and
 // the drained chip before it) takes for less than the round of tiles that they begin (0: none): up to 32 beyond a multiple
 // of the tile kernels' 256 or 128 (777 tokens, 20480 x 5120: 139 us in two rounds of tiles, 80 + 25 for 768 and 9 tokens).
-static int64_t rest_tokens(int64_t n, int64_t m, int64_t K) {
+int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K) {
     if (n <= 128 || !tile_kernel_fits(K) || one_round_of_64(n, m)) return 0;
     double least = tiles_us(n, m, K);
     int64_t best = 0;
@@ -1138,7 +1138,7 @@ static hipError_t launch_tiles(const bf16_t* B, int64_t n, const bf16_t* A_vals,
 
 hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
                        const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
-    const int64_t rest = K2 <= 0 ? rest_tokens(n, m, K) : 0;  // (the small-batch kernel takes A2 k-major)
+    const int64_t rest = K2 <= 0 ? spmm_rest_tokens(n, m, K) : 0;  // (the small-batch kernel takes A2 k-major)
     n -= rest;
     hipError_t e = launch_tiles(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     if (e != hipSuccess || rest == 0) return e;

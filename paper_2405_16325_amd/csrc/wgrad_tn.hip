@@ -772,6 +772,8 @@ size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m) {
     return (size_t)((RESIDENT + tiles - 1) / tiles) * (size_t)n * (size_t)m * 4;
 }
 
+int dense_tn_plain_slabs(int64_t n, int64_t m, int64_t K, size_t partial_bytes) { return skinny_plan(n, m, K, partial_bytes).slabs; }
+
 template <int BM, int BN, int NS>
 static hipError_t launch_skinny(const SkinnyPlan& p, const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K,
                                 int64_t ld, bf16_t* C, float* partial, hipStream_t s) {

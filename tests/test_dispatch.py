@@ -5,7 +5,7 @@ import pytest
 
 from paper_2405_16325_amd import binding as sl
 
-STREAM, SLABS, TILE, GENERIC, STREAM_ROWS = 0, 1, 2, 3, 4
+STREAM, SLABS, TILE, GENERIC, STREAM_ROWS, TILE_AND_STREAM = range(6)
 
 
 @pytest.mark.parametrize("b", [1, 7, 16, 17, 32])
@@ -89,9 +89,14 @@ def test_a_small_layer_gets_a_tile_that_fits_one_round():
     assert p["product"] == TILE and tiles <= 256
 
 
-def test_contractions_that_are_no_multiple_of_256_take_the_generic_kernel():
+def test_contractions_by_their_multiple_of_64():
+    # on one round of 64 x 64 tiles only whole pairs of k-steps count as a tile shape
     assert sl.slope_spmm_fwd_plan(300, 320, 448)["product"] == GENERIC
     assert sl.slope_spmm_fwd_plan(300, 512, 448)["product"] == TILE
+    # on more tiles whole k-steps do, at least two of them
+    assert sl.slope_spmm_fwd_plan(3000, 320, 4480)["product"] == TILE
+    assert sl.slope_spmm_fwd_plan(3000, 328, 4480)["product"] == GENERIC
+    assert sl.slope_spmm_fwd_plan(3000, 64, 4480)["product"] == GENERIC
 
 
 @pytest.mark.parametrize("b,d_out,d_in", [(33, 16640, 1024), (64, 20480, 1024), (64, 20480, 1088), (64, 25344, 576)])
@@ -102,13 +107,41 @@ def test_more_than_a_round_of_64_x_64_tiles_stays_on_the_tile_kernel(b, d_out, d
     assert sl.slope_spmm_fwd_plan(b, d_in, 36864, 0, False)["rows"] == 128
 
 
+def test_a_few_tokens_beyond_whole_tiles_take_the_small_batch_kernel():
+    def plan(b, d_out, d_in, r=0):
+        p = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
+        return p["product"], p["rows"], p["tokens"], p["slabs"]
+    # 80 x 3 tiles of 256 x 256 are a round, the nine tokens left would begin another
+    assert plan(777, 20480, 5120, 64) == (TILE_AND_STREAM, 256, 256, 9)
+    assert plan(768, 20480, 5120)[0] == TILE
+    assert plan(800, 20480, 5120) == (TILE_AND_STREAM, 256, 256, 32) and plan(801, 20480, 5120)[0] == TILE
+    assert plan(4097, 4096, 2112) == (TILE_AND_STREAM, 256, 256, 1)
+    assert plan(16385, 36864, 9216)[0] == TILE                          # a pass over this weight costs more than the round
+
+
+def test_short_adapter_products_of_many_tokens():
+    xl = lambda b, d_in, r: sl.slope_spmm_fwd_plan(b, d_in, 2048, r)["xl"]
+    assert xl(1024, 2048, 64) == 4                                       # eight chunks of 32 rows of L per wavefront, one round
+    assert xl(1024, 2112, 64) == 3 and xl(1024, 2048, 1024 // 2) == 4    # nine; 256 tiles, still a round
+    assert xl(8192, 2048, 64) == 4 and xl(8192, 2048, 256) != 4          # one round of 512 tiles and four
+    assert xl(512, 2048, 64) == 1
+
+
+def test_split_of_a_partial_round_by_slabs():
+    slabs = lambda b, d_out, d_in: sl.slope_spmm_fwd_plan(b, d_in, d_out)["slabs"]
+    assert slabs(700, 2112, 4160) >= 2 and slabs(512, 4096, 4096) >= 2
+    assert slabs(700, 2112, 960) == 1                                    # fewer than four quads of k-steps per slab
+    assert slabs(2048, 768, 3072) == 1                                   # a microsecond slower in a step
+    assert sl.slope_spmm_fwd_plan(700, 4160, 2112, 0, False)["slabs"] == 1
+
+
 def test_adapter_product_regimes():
     xl = lambda b, r=128, d_in=9216: sl.slope_spmm_fwd_plan(b, d_in, 9216, r)["xl"]
     assert sl.slope_spmm_fwd_plan(64, 9216, 9216, 0)["xl"] == 0
     assert [xl(b) for b in (1, 16, 17, 128, 512)] == [1] * 5    # split over d_in, L as stored
     assert [xl(b) for b in (513, 4096)] == [3, 3]               # dense tile kernel, too few tiles: split over d_in
     assert xl(16384) == 2                                       # 256 tiles: no split
-    # chunks of 64 rows of L per workgroup: as many as still give every compute unit a workgroup
+    # chunks of 64 rows of L per partial sum that the scratch is sized by: as many as still give 256 workgroups
     chunks = lambda b, d_in: sl.slope_spmm_fwd_plan(b, d_in, 9216, 128)["xl_chunks"]
     assert chunks(16, 9216) == 1 and chunks(64, 9216) == 1 and chunks(16, 36864) == 2 and chunks(512, 36864) == 4
 
@@ -124,7 +157,7 @@ def test_plan_rejects_what_the_call_rejects():
 
 def test_extents_that_are_not_multiples_of_64_take_the_general_kernels():
     # any multiple of 8 is accepted; a contraction that is not a whole number of k-steps of 64 goes to the
-    # generic kernel's form for ragged rows (also for inference-size batches) and to plain arithmetic for X L
+    # generic kernel's form for ragged rows (also for inference-size batches) and to the kernel for ragged extents for X L
     for b in (1, 16, 300, 5000):
         plan = sl.slope_spmm_fwd_plan(b, 1000, 1000, 64)
         assert plan["product"] == GENERIC and plan["xl"] == 4

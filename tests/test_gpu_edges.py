@@ -111,6 +111,7 @@ def test_column_masks(n, m, kind, rows, cols):
 # and several, fewer tokens than a tile
 @pytest.mark.parametrize("b,d_out,d_in,r", [(20, 192, 128, 32), (600, 2560, 2560, 64), (2560, 1024, 2048, 96), (1024, 2048, 2112, 512)])
 def test_short_adapter_products(b, d_out, d_in, r):
+    assert sl.slope_spmm_fwd_plan(b, d_in, d_out, r)["xl"] == (1 if b <= 512 else 3 if d_in > 2048 else 4)
     check_layer(b, d_out, d_in, r)
 
 
@@ -171,6 +172,8 @@ def test_input_gradient_with_scratch(b, d_out, d_in, some):
 # k-steps, with an adapter whose T is split at the same token
 @pytest.mark.parametrize("b,d_out,d_in,r", [(777, 20480, 5120, 64), (2049, 8192, 1024, 160), (4097, 4096, 2112, 0), (1025, 16384, 2112, 32)])
 def test_tokens_beyond_whole_tiles(b, d_out, d_in, r):
+    plan = sl.slope_spmm_fwd_plan(b, d_in, d_out, r, False)
+    assert (plan["product"], plan["slabs"]) == (5, b % 256)
     check_layer(b, d_out, d_in, r)
 
 
