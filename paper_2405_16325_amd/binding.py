@@ -93,16 +93,21 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-# A call's checks and marshalling take longer than its kernels on the smallest layers (one token, 3072 x 768: 17.5 us a call, 14.1 without
-# them, 9.2 of kernels),
-# so they do without temporary objects: ctypes converts plain integers to pointers itself.
+# A call's checks and marshalling take longer than its kernels on the smallest layers (one token, 3072 x 768: 17.5 us a
+# call, 9.2 of them kernels), so they do without temporary objects: ctypes converts plain integers to pointers itself
+# (14.1 us).
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # not part of torch's public interface
+
+
 def _stream():
-    """The raw handle of torch.cuda.current_stream()."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    """The raw handle of torch.cuda.current_stream(), which builds an object per call."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(call: str, status: int):

@@ -240,3 +240,13 @@ def test_ragged_adapter_product_of_the_most_tokens():
     assert_all_close(Y[:64], want, "Y", two_stage=True)
     for part in Y.view(-1, 64, d).split(1 << 18):
         assert torch.equal(part, Y[:64].expand_as(part))
+
+
+# calls follow torch's current stream, with torch's quick way to its handle and without
+def test_calls_follow_the_current_stream(monkeypatch):
+    other = torch.cuda.Stream()
+    for raw in (sl._raw_stream, None):
+        monkeypatch.setattr(sl, "_raw_stream", raw)
+        assert sl._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(other):
+            assert sl._stream() == other.cuda_stream
