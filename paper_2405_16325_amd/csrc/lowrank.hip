@@ -11,8 +11,8 @@
 
 namespace {
 
-// The skinny products of layers whose extents are not multiples of 64, one or two of them in a launch (q.tiles == 0:
-// one): each has a few dozen workgroups, so two run beside each other (1000 tokens, 1000 x 1000, rank 64:
+// The skinny products of layers whose extents are not multiples of 64, and short ones, one or two of them in a launch (no
+// tiles: none): each has a few dozen workgroups, so two run beside each other (1000 tokens, 1000 x 1000, rank 64:
 // 5.5 + 6.3 and 6.8 + 6.9 us one after the other, 7.3 and 6.5 in pairs; the training step 67.8 -> 56.8).
 struct SkinnyGrid { SkinnyProduct p; int tiles; };
 
@@ -34,8 +34,8 @@ __global__ void __launch_bounds__(SK_WAVES * 64) skinny_ragged_kernel(SkinnyGrid
 inline int64_t skinny_tiles(const SkinnyProduct& p) { return ((p.m + SK_BJ - 1) / SK_BJ) * ((p.n + SK_BI - 1) / SK_BI); }
 
 template <bool PBK, bool PAK, bool QBK, bool QAK>
-hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, bool two, hipStream_t s) {
-    const int64_t tp = skinny_tiles(p), tq = two ? skinny_tiles(q) : 0;
+hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, hipStream_t s) {
+    const int64_t tp = skinny_tiles(p), tq = skinny_tiles(q);
     if (tp + tq > 0x7FFFFFFF - GRID_ROW) return hipErrorInvalidValue;
     skinny_ragged_kernel<PBK, PAK, QBK, QAK><<<grid_of(tp + tq), dim3(SK_WAVES * 64), 0, s>>>(SkinnyGrid{p, (int)tp},
                                                                                                    SkinnyGrid{q, (int)tq});
@@ -54,17 +54,16 @@ bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most) {
     return steps * ((tiles + 511) / 512) <= most;
 }
 
-hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s) {
-    return p.a_kmajor ? launch_skinny_pair<false, true, false, true>(p, p, false, s)
-                      : launch_skinny_pair<false, false, false, false>(p, p, false, s);
+hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s) {
+    return launch_skinny_pair<false, true, false, false>(t, t2, s);
 }
 
-hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s) {
-    return launch_skinny_pair<false, true, false, false>(t, t2, true, s);
+hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s) {
+    return p.a_kmajor ? launch_skinny_factors(p, {}, s) : launch_skinny_factors({}, p, s);
 }
 
 hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s) {
-    return launch_skinny_pair<true, true, true, true>(dl, dr, true, s);
+    return launch_skinny_pair<true, true, true, true>(dl, dr, s);
 }
 
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,

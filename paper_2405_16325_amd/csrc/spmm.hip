@@ -653,27 +653,26 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 // values and tokens, the nibble pair 0x44 (positions 0, 1: a legal encoding) for metadata, so the tail contributes
 // exact zeros.
 enum { GEN_WHOLE = 0, GEN_PARTIAL = 1, GEN_RAGGED = 2 };      // K % 128 == 0; whole k-steps (K % 64 == 0); any K % 8 == 0
-template <int FM, int FN, int G>
+template <int F, int G>
 struct GenSmem {
-    static constexpr int BM = 32 * FM, BN = 32 * FN;          // the tile
+    static constexpr int BM = 32 * F, BN = 32 * F;            // the tile
     static constexpr int A_BYTES = BM * 128, B_STEP = BN * 128, M_BYTES = BM * 16;
     static constexpr int M_OFF = A_BYTES + 2 * B_STEP;
     static constexpr int STAGE = M_OFF + M_BYTES;
     static constexpr int SUM_PITCH = BM + 4;                  // floats per token row of a partial tile
-    static constexpr int SUM_PASSES = G * BN * SUM_PITCH * 4 > 160 * 1024 ? 2 : 1;   // token halves of partial tiles at a time
-    static constexpr int SUMS = G > 1 ? G * BN / SUM_PASSES * SUM_PITCH * 4 : 0;
+    static constexpr int SUMS = G > 1 ? G * BN * SUM_PITCH * 4 : 0;
     static constexpr int TOTAL = G * STAGE > SUMS ? G * STAGE : SUMS;
 };
 
-template <int FORM, int FM, int FN, int G>
+template <int FORM, int F, int G>
 __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __restrict__ B, int n,
                                                            const bf16_t* __restrict__ Av,
                                                            const uint8_t* __restrict__ Am, int m, int K,
                                                            const bf16_t* __restrict__ B2,
                                                            const bf16_t* __restrict__ A2, int K2,
                                                            bf16_t* __restrict__ C, int tiles_m) {
-    using S = GenSmem<FM, FN, G>;
-    constexpr int MF = FM, NF = FN, A_LD = FM, B_LD = 2 * FN;     // 16-byte pieces per lane and pair
+    using S = GenSmem<F, G>;
+    constexpr int MF = F, NF = F, A_LD = F, B_LD = 2 * F;         // 16-byte pieces per lane and pair
     __shared__ __align__(16) uint8_t smem[S::TOTAL];
     const int m0 = (blockIdx.x % tiles_m) * S::BM, n0 = (blockIdx.x / tiles_m) * S::BN;
     const int group = (int)threadIdx.x >> 8;
@@ -809,34 +808,27 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
                 for (int j = 0; j < NF; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[i].v, b2[j].v, acc[i][j], 0, 0, 0);
         }
-        // a pass: every wavefront's fragments j0 .. j0 + NP - 1, [group][token][SUM_PITCH]; the stages are idle
+        // the groups' partial tiles, [group][token][SUM_PITCH]; the stages are idle
         float* const part = (float*)smem;
-        constexpr int NP = NF / S::SUM_PASSES, ROWS = S::BN / S::SUM_PASSES;
 #pragma unroll
-        for (int j0 = 0; j0 < NF; j0 += NP) {
-            if (j0 > 0) __syncthreads();
+        for (int i = 0; i < MF; ++i)
 #pragma unroll
-            for (int i = 0; i < MF; ++i)
+            for (int j = 0; j < NF; ++j)
+                *(f32x4*)(part + ((group * S::BN + (wn * NF + j) * 16 + l16) * S::SUM_PITCH + (wm * MF + i) * 16 + lq * 4)) = acc[i][j];
+        __syncthreads();
+        for (int idx = (int)threadIdx.x; idx < S::BM * S::BN / 4; idx += 256 * G) {
+            const int tok = idx / (S::BM / 4), col = (idx % (S::BM / 4)) * 4;
+            f32x4 v = *(const f32x4*)(part + tok * S::SUM_PITCH + col);
 #pragma unroll
-                for (int j = 0; j < NP; ++j)
-                    *(f32x4*)(part + ((group * ROWS + (wn * NP + j) * 16 + l16) * S::SUM_PITCH + (wm * MF + i) * 16 + lq * 4)) =
-                        acc[i][j0 + j];
-            __syncthreads();
-            for (int idx = (int)threadIdx.x; idx < S::BM * ROWS / 4; idx += 256 * G) {
-                const int row = idx / (S::BM / 4), col = (idx % (S::BM / 4)) * 4;
-                const int tok = row / (16 * NP) * (16 * NF) + 16 * j0 + row % (16 * NP);
-                f32x4 v = *(const f32x4*)(part + row * S::SUM_PITCH + col);
+            for (int q = 1; q < G; ++q) {
+                const f32x4 x = *(const f32x4*)(part + (q * S::BN + tok) * S::SUM_PITCH + col);
+                v[0] += x[0]; v[1] += x[1]; v[2] += x[2]; v[3] += x[3];
+            }
+            if (n0 + tok < n && m0 + col < m) {               // m % 8 == 0
+                union { __bf16 h[4]; u32x2 u; } o;
 #pragma unroll
-                for (int q = 1; q < G; ++q) {
-                    const f32x4 x = *(const f32x4*)(part + (q * ROWS + row) * S::SUM_PITCH + col);
-                    v[0] += x[0]; v[1] += x[1]; v[2] += x[2]; v[3] += x[3];
-                }
-                if (n0 + tok < n && m0 + col < m) {           // m % 8 == 0
-                    union { __bf16 h[4]; u32x2 u; } o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)v[e];
-                    *(u32x2*)(C + (size_t)(n0 + tok) * m + m0 + col) = o.u;
-                }
+                for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)v[e];
+                *(u32x2*)(C + (size_t)(n0 + tok) * m + m0 + col) = o.u;
             }
         }
     }
@@ -849,14 +841,14 @@ __global__ void __launch_bounds__(256 * G) spmm_generic_kernel(const bf16_t* __r
 // were measured too: never better than both this and the tile kernels' rings.
 inline int64_t tiles_of_64(int64_t n, int64_t m) { return ((m + 63) / 64) * ((n + 63) / 64); }
 
-template <int FM, int FN, int G>
+template <int F, int G>
 hipError_t launch_generic_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
                              const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
-    using S = GenSmem<FM, FN, G>;
+    using S = GenSmem<F, G>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     const int tiles_m = (int)((m + S::BM - 1) / S::BM), tiles_n = (int)((n + S::BN - 1) / S::BN);
-    auto kern = K % 128 == 0 ? spmm_generic_kernel<GEN_WHOLE, FM, FN, G>
-                : K % 64 == 0 ? spmm_generic_kernel<GEN_PARTIAL, FM, FN, G> : spmm_generic_kernel<GEN_RAGGED, FM, FN, G>;
+    auto kern = K % 128 == 0 ? spmm_generic_kernel<GEN_WHOLE, F, G>
+                : K % 64 == 0 ? spmm_generic_kernel<GEN_PARTIAL, F, G> : spmm_generic_kernel<GEN_RAGGED, F, G>;
     kern<<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256 * G), 0, s>>>(B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2,
                                                                        C, tiles_m);
     return hipGetLastError();
@@ -864,8 +856,8 @@ hipError_t launch_generic_as(const bf16_t* B, int64_t n, const bf16_t* Av, const
 
 hipError_t launch_generic(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
                           const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
-    if (spmm_generic_edge(n, m) == 64) return launch_generic_as<2, 2, 4>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
-    return launch_generic_as<4, 4, 1>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
+    if (spmm_generic_edge(n, m) == 64) return launch_generic_as<2, 4>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
+    return launch_generic_as<4, 1>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
 }
 
 template <int BM, int BN, bool TAIL, bool SPLIT>
@@ -942,11 +934,11 @@ hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint
 
 }  // namespace
 
-// A few dozen to a thousand tokens: the token tile is so narrow that small weight tiles would
-// re-read it from L2 for every few weight rows (the tile kernels run at the L2 -> LDS rate), and
-// tall weight tiles alone are too few to fill the chip.  So: 256-row weight tiles, the k range
-// cut into slabs that run as separate workgroups and leave fp32 partial sums in `slabs`, and a
-// short reduction kernel (fixed order: bit-identical runs) that rounds to bf16.
+// Products of too few tiles to fill the chip, a few dozen tokens on any weight or some thousand on a small one: narrow
+// token tiles on small weight tiles would re-read the tokens from L2 for every few weight rows (the tile kernels run at the
+// L2 -> LDS rate), and tall weight tiles alone are too few.  So: 256-row weight tiles, the k range cut into slabs that run
+// as separate workgroups and leave fp32 partial sums in `slabs`, and a short second kernel (fixed order: bit-identical
+// runs) that rounds to bf16.  SLAB_MAX_TOKENS is the reach of the first of the two rules below.
 constexpr int64_t SLAB_MAX_TOKENS = 1024;
 
 // The tile kernels take whole k-steps of 64, at least two of them (700 tokens: 4160 x 2112 54 -> 25 us, 2112 x 4160
@@ -1130,7 +1122,7 @@ static hipError_t launch_tiles(const bf16_t* B, int64_t n, const bf16_t* A_vals,
         case 128128: return launch_tile<128, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 128064: return launch_tile<128, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 64064:                                           // in two rounds the ring again (64 tokens, 20480 x 5120: 42.2 -> 34.9 us)
-            return one_round_of_64(n, m) ? launch_generic_as<2, 2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s)
+            return one_round_of_64(n, m) ? launch_generic_as<2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s)
                                          : launch_tile<64, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         default: return launch_tile<64, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     }
