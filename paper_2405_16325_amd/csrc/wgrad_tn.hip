@@ -827,10 +827,14 @@ hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int6
 // that launch_wgrad_masked_t and the skinny products use one after the other.
 static size_t wgrad_adapter_shared_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     if (d_in % 64 != 0 || d_out % 64 != 0) return wgrad_tail_bytes(b, d_in, d_out);   // no tile kernel for the skinny products
-    const int64_t longest = d_in > d_out ? d_in : d_out;
-    const int64_t sl = skinny_plan(longest, r, (b + 63) / 64 * 64, ~(size_t)0).slabs;
     const size_t tail = wgrad_tail_bytes(b, d_in, d_out);
-    const size_t sums = sl > 1 ? (size_t)sl * (size_t)longest * (size_t)r * 4 : 0;
+    auto slabs = [r](int64_t n, int64_t K) {                  // of one of the four products, n the side that is not the rank
+        const int sl = skinny_plan(n, r, K, ~(size_t)0).slabs;
+        return sl > 1 ? (size_t)sl * (size_t)n * (size_t)r * 4 : 0;
+    };
+    const int64_t bp = (b + 63) / 64 * 64;
+    size_t sums = 0;
+    for (const size_t s : {slabs(b, d_in), slabs(b, d_out), slabs(d_in, bp), slabs(d_out, bp)}) sums = s > sums ? s : sums;
     return tail > sums ? tail : sums;
 }
 
