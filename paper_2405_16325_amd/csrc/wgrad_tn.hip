@@ -252,6 +252,8 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(const bf16_t* __re
         WAIT_HERE(waitcnt_imm(G == 1 ? AHEAD : 63, 0));                                                \
         wg_barrier();                                                                                  \
         if (G == 1) issue(ks + NS);                                                                    \
+        /* before the MFMAs: among them, where the compiler may put these loads, they land 5 to 8 % later */ \
+        if (G == 1) __builtin_amdgcn_sched_barrier(0);                                                 \
         _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                  \
         _Pragma("unroll") for (int i = 0; i < MF; ++i) _Pragma("unroll") for (int jj = 0; jj < NF; ++jj) { \
             const int j = (i & 1) ? NF - 1 - jj : jj;         /* back and forth: one operand changes per MFMA */ \
