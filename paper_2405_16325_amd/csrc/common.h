@@ -83,7 +83,7 @@ hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, 
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
                                   bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s);
 // C[n, m] = sum_k B(i, k) * A(j, k) for the skinny adapter products of layers whose extents are not multiples of 64, or
-// which are short (skinny_is_short):
+// which are short (skinny_is_short, skinny_pair_is_short):
 // an operand is k-contiguous [rows][ld] (K % 8 == 0) or k-major [K][ld] (rows % 8 == 0); m % 8 == 0.
 struct SkinnyProduct {
     const bf16_t* B;
@@ -94,7 +94,8 @@ struct SkinnyProduct {
     int64_t n, m, K;
     bf16_t* C;
 };
-bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most);
+bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most, int per_round);
+bool skinny_pair_is_short(int64_t n, int64_t m, int64_t K);
 hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s);                           // B k-contiguous
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s);    // B's k-contiguous, A k-major; A k-contiguous
 hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s); // all operands k-major

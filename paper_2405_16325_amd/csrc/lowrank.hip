@@ -31,11 +31,12 @@ __global__ void __launch_bounds__(SK_WAVES * 64) skinny_ragged_kernel(SkinnyGrid
     else if (b - p.tiles < q.tiles) skinny_product_tile<QBK, QAK>(q.p, b - p.tiles, smem);
 }
 
-inline int64_t skinny_tiles(const SkinnyProduct& p) { return ((p.m + SK_BJ - 1) / SK_BJ) * ((p.n + SK_BI - 1) / SK_BI); }
+inline int64_t skinny_tiles(int64_t n, int64_t m) { return ((m + SK_BJ - 1) / SK_BJ) * ((n + SK_BI - 1) / SK_BI); }
+inline int64_t skinny_chunks(int64_t K) { return (K + 32 * SK_WAVES - 1) / (32 * SK_WAVES); }   // in a row per wavefront
 
 template <bool PBK, bool PAK, bool QBK, bool QAK>
 hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, hipStream_t s) {
-    const int64_t tp = skinny_tiles(p), tq = skinny_tiles(q);
+    const int64_t tp = skinny_tiles(p.n, p.m), tq = skinny_tiles(q.n, q.m);
     if (tp + tq > 0x7FFFFFFF - GRID_ROW) return hipErrorInvalidValue;
     skinny_ragged_kernel<PBK, PAK, QBK, QAK><<<grid_of(tp + tq), dim3(SK_WAVES * 64), 0, s>>>(SkinnyGrid{p, (int)tp},
                                                                                                    SkinnyGrid{q, (int)tq});
@@ -46,13 +47,19 @@ hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, hi
 
 // Whole k-steps have the choice: the tile kernels stream better, but want a k-contiguous copy of a k-major operand and, on
 // few tiles, a second kernel for the sums over slabs; this one takes operands as stored in one launch, at about 1.3 us per
-// chunk of 32 k that a wavefront walks and round of two workgroups per compute unit.  `most` chunks: 8 where it saves the
-// copy and the second kernel, 5 where the second kernel only, 10 for the pairs below (1024 tokens, 2048 x
-// 2048, rank 64: X L 2.7 + 5.1 + 3.8 -> 10.7 us, the gradient call's adapter part 42 us in ten launches -> 21 in two).
-bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most) {
-    const int64_t tiles = ((m + SK_BJ - 1) / SK_BJ) * ((n + SK_BI - 1) / SK_BI), steps = (K + 32 * SK_WAVES - 1) / (32 * SK_WAVES);
-    return steps * ((tiles + 511) / 512) <= most;
+// chunk of 32 k that a wavefront walks and round of two workgroups per compute unit.
+// A product by itself, `most` chunks in one round of per_round workgroups: 8 in 512 where it saves the copy and the second
+// kernel (1024 x 2048, rank 64: X L 2.7 + 5.1 + 3.8 -> 10.7 us; in two rounds, 16384 x 1024, rank 96, the forward took 33.1 us,
+// 27.0 with the tile kernel).  5 in 256 where there is no copy to save (dY R^T): with two workgroups per compute unit it
+// takes 12 us where the tile kernel, then in one launch, takes 9 (3 chunks: 3890 x 768, rank 160; 16384 x 768, rank 64; but
+// 1024 x 768, rank 64 6.5 against 7.7).
+bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most, int per_round) {
+    return skinny_tiles(n, m) <= per_round && skinny_chunks(K) <= most;
 }
+
+// One of the four products of the gradient call, which replace ten launches by two (1024 tokens, 2048 x 2048, rank 64:
+// 42 -> 21 us; 256 tokens, 2560 x 2560, rank 512, two rounds: the call 51.3 -> 40.3).
+bool skinny_pair_is_short(int64_t n, int64_t m, int64_t K) { return skinny_chunks(K) * ((skinny_tiles(n, m) + 511) / 512) <= 10; }
 
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s) {
     return launch_skinny_pair<false, true, false, false>(t, t2, s);

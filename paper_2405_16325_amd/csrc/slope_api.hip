@@ -51,14 +51,15 @@ size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     return slabs;
 }
 
-constexpr int XL_SHORT_STEPS = 8;                             // of skinny_is_short for T = X L
+// T = X L on the kernel for ragged extents although its extents are whole k-steps
+bool xl_is_short(int64_t n, int64_t r, int64_t d_in) { return skinny_is_short(n, r, d_in, 8, 2 * RESIDENT); }
 
 // T[n, r] = B[n, K] A^T for the skinny products of the adapters.  a_kmajor: A is [K][r] (the factor L as
 // stored) instead of [r][K].  Whole k-steps of 64 go to the tile kernels, anything else and short products to the kernel
 // for ragged extents.
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
                           bf16_t* At_scratch, float* partial, hipStream_t s) {
-    if (K % 64 != 0 || skinny_is_short(n, r, K, a_kmajor ? XL_SHORT_STEPS : 5))
+    if (K % 64 != 0 || (a_kmajor ? xl_is_short(n, r, K) : skinny_is_short(n, r, K, 5, RESIDENT)))
         return launch_skinny_ragged({B, K, A, a_kmajor ? r : K, a_kmajor, n, r, K, T}, s);
     const size_t partial_bytes = partial ? dense_tn_plain_partial_bytes(n, r) : 0;
     if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);
@@ -512,7 +513,7 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         } else if (b <= XL_SMALL_MAX_TOKENS) {
             plan[4] = 1;
             plan[5] = xl_subs(b, d_in, r);
-        } else if (skinny_is_short(b, r, d_in, XL_SHORT_STEPS)) {
+        } else if (xl_is_short(b, r, d_in)) {
             plan[4] = 4;
         } else {
             plan[4] = dense_tn_plain_slabs(b, r, d_in, dense_tn_plain_partial_bytes(b, r)) > 1 ? 3 : 2;

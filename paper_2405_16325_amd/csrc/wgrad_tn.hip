@@ -876,8 +876,8 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     }
     if ((e = launch_token_copies(X, d_in, Xt, dY, d_out, dYt, b, s)) != hipSuccess) return e;
     if ((e = launch_wgrad_masked_t(dYt, Xt, b, meta, d_out, d_in, gvals, tail, s)) != hipSuccess) return e;
-    if (skinny_is_short(b, r, d_in, 10) && skinny_is_short(b, r, d_out, 10) && skinny_is_short(d_in, r, b, 10) &&
-        skinny_is_short(r, d_out, b, 10))
+    if (skinny_pair_is_short(b, r, d_in) && skinny_pair_is_short(b, r, d_out) && skinny_pair_is_short(d_in, r, b) &&
+        skinny_pair_is_short(r, d_out, b))
         return skinny();
     launch_transpose_pad(L, d_in, r, d_in, d_in, Lt, s);                          // Lt[r][d_in]
     if ((e = hipGetLastError()) != hipSuccess) return e;

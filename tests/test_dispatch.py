@@ -123,7 +123,7 @@ def test_short_adapter_products_of_many_tokens():
     xl = lambda b, d_in, r: sl.slope_spmm_fwd_plan(b, d_in, 2048, r)["xl"]
     assert xl(1024, 2048, 64) == 4                                       # eight chunks of 32 rows of L per wavefront, one round
     assert xl(1024, 2112, 64) == 3 and xl(1024, 2048, 1024 // 2) == 4    # nine; 256 tiles, still a round
-    assert xl(8192, 2048, 64) == 4 and xl(8192, 2048, 256) != 4          # one round of 512 tiles and four
+    assert xl(16384, 1024, 64) == 4 and xl(16384, 1024, 96) != 4         # one round of 512 tiles and two
     assert xl(512, 2048, 64) == 1
 
 

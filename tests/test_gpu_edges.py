@@ -109,9 +109,10 @@ def test_column_masks(n, m, kind, rows, cols):
 
 # whole k-steps on the kernel for short products: one chunk in a row and as many as its rule lets in, ranks of one tile
 # and several, fewer tokens than a tile
-@pytest.mark.parametrize("b,d_out,d_in,r", [(20, 192, 128, 32), (600, 2560, 2560, 64), (2560, 1024, 2048, 96), (1024, 2048, 2112, 512)])
+@pytest.mark.parametrize("b,d_out,d_in,r", [(20, 192, 128, 32), (600, 2560, 2560, 64), (2560, 1024, 2048, 96), (1024, 2048, 2112, 512),
+                                            (5000, 256, 1024, 160), (8224, 768, 512, 64), (256, 2560, 2560, 512)])
 def test_short_adapter_products(b, d_out, d_in, r):
-    assert sl.slope_spmm_fwd_plan(b, d_in, d_out, r)["xl"] == (1 if b <= 512 else 3 if d_in > 2048 else 4)
+    assert sl.slope_spmm_fwd_plan(b, d_in, d_out, r)["xl"] == (1 if b <= 512 else 4 if d_in <= 2048 else 3)
     check_layer(b, d_out, d_in, r)
 
 
