@@ -482,11 +482,13 @@ def sweep(args, torch, sl, inputs, dev):
         Wg = torch.empty((d_out, d_in), dtype=torch.bfloat16, device=dev)
         nws = sl.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, 0)
         ws = torch.empty(nws, dtype=torch.uint8, device=dev) if nws else None
+        nbs = sl.slope_workspace_bytes(sl.SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out)
+        bws = torch.empty(nbs, dtype=torch.uint8, device=dev) if nbs else None
         wws = torch.empty(sl.slope_wgrad_workspace_bytes(b, d_in, d_out), dtype=torch.uint8, device=dev)
         flops = 2.0 * b * d_in * d_out
         iters = int(min(200, max(5, 2e12 / flops)))
         ours = [timed_ms(torch, lambda: sl.slope_spmm_fwd(X, vals, meta, out=Y, workspace=ws), iters),
-                timed_ms(torch, lambda: sl.slope_spmm_bwd_x(dY, vals_t, meta_t, out=dX), iters),
+                timed_ms(torch, lambda: sl.slope_spmm_bwd_x(dY, vals_t, meta_t, out=dX, workspace=bws), iters),
                 timed_ms(torch, lambda: sl.slope_wgrad_masked(dY, X, meta, out=G, workspace=wws), iters)]
         lib = [timed_ms(torch, lambda: torch.matmul(X, W.t(), out=Y), iters),
                timed_ms(torch, lambda: torch.matmul(dY, W, out=dX), iters),
@@ -496,7 +498,7 @@ def sweep(args, torch, sl, inputs, dev):
                       "tflops": {"fwd": flops / ours[0] / 1e9, "dX": flops / ours[1] / 1e9, "dW": flops / ours[2] / 1e9},
                       "speedup": {"fwd": lib[0] / ours[0], "dX": lib[1] / ours[1], "dW": lib[2] / ours[2],
                                   "all": sum(lib) / sum(ours)}})
-        del X, W, dY, vals, meta, vals_t, meta_t, Y, dX, G, Wg, ws, wws
+        del X, W, dY, vals, meta, vals_t, meta_t, Y, dX, G, Wg, ws, bws, wws
     big = [c for c in cases if c["kind"] != "tokens"]
     value = sum(c["speedup"]["all"] for c in big) / len(big)
     return {"metric": "speedup of the 2:4 sparse linear fwd + dX + dW over dense bf16 GEMM, mean over the aspect-ratio sweep",

@@ -87,9 +87,9 @@ typedef enum {
  * 0 for the calls that take no workspace, for unknown ids and for invalid extents.  The per-call
  * queries below return the same numbers.
  *   slope_spmm_fwd: required when adapters are active (T = X L as bf16[b, r], a K-contiguous copy of L
- *   for many tokens, partial sums); optional otherwise: for a few dozen to some thousand tokens (where
- *   tiles alone would leave much of the chip idle) the call, given this many bytes, also splits the contraction over d_in and keeps fp32 partial sums
- *   there, which is much faster at those sizes. */
+ *   for many tokens, partial sums); optional otherwise: for a few dozen to some thousand tokens, where
+ *   tiles alone would leave much of the chip idle, the call, given this many bytes, also splits the
+ *   contraction over d_in and keeps fp32 partial sums there, which is much faster at those sizes. */
 size_t slope_workspace_bytes(int call_id, int64_t b, int64_t d_in, int64_t d_out, int64_t r);
 size_t slope_spmm_fwd_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r);
 
@@ -174,8 +174,8 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
 slope_status slope_spmm_bwd_x(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta,
                               int64_t d_out, int64_t d_in, void* dX, void* stream);
 /* The same with scratch memory for a split over d_out where that is faster: workspace_or_null of
- * slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out, 0) bytes (may be 0), 256-byte aligned; a buffer that is
- * too small: SLOPE_ERR_WORKSPACE.  NULL: slope_spmm_bwd_x. */
+ * slope_workspace_bytes(SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out, 0) bytes (may be 0), 256-byte aligned;
+ * a buffer that is too small: SLOPE_ERR_WORKSPACE.  NULL: slope_spmm_bwd_x. */
 slope_status slope_spmm_bwd_x_ws(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta,
                                  int64_t d_out, int64_t d_in, void* dX, void* workspace_or_null,
                                  size_t workspace_bytes, void* stream);
