@@ -45,7 +45,7 @@ constexpr int PR_UNROLL = 2;        // 8 KiB of W per workgroup: 0.118 -> 0.087 
 __global__ void __launch_bounds__(256) prune_rows_kernel(const u32x4* __restrict__ W, size_t nchunks,
                                                          u32x2* __restrict__ vals, uint8_t* __restrict__ meta,
                                                          uint8_t* __restrict__ mask) {
-    const size_t first = (size_t)blockIdx.x * (256 * PR_UNROLL) + threadIdx.x;
+    const size_t first = (size_t)flat_block() * (256 * PR_UNROLL) + threadIdx.x;
     const int sub = threadIdx.x & 3;
     u32x4 w[PR_UNROLL];
 #pragma unroll
@@ -83,9 +83,10 @@ hipError_t launch_prune_rows(const bf16_t* W, int64_t d_out, int64_t d_in, bf16_
                              uint8_t* mask, hipStream_t s) {
     size_t nchunks = (size_t)d_out * (size_t)d_in / 8;
     size_t per_block = 256 * PR_UNROLL;
-    size_t blocks = (nchunks + per_block - 1) / per_block;    // extents below 2^31: fewer than 2^31 workgroups
+    int64_t blocks = (int64_t)((nchunks + per_block - 1) / per_block);
+    if (!grid_fits(blocks)) return hipErrorInvalidValue;
     if (blocks == 0) blocks = 1;
-    prune_rows_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>((const u32x4*)W, nchunks, (u32x2*)vals, meta, mask);
+    prune_rows_kernel<<<grid_of(blocks), dim3(256), 0, s>>>((const u32x4*)W, nchunks, (u32x2*)vals, meta, mask);
     return hipGetLastError();
 }
 
@@ -409,11 +410,11 @@ __device__ __forceinline__ uint32_t sparse_add_pair(uint32_t wa, uint32_t wb, fl
 __global__ void __launch_bounds__(256) sparse_add_kernel(const u32x4* __restrict__ a, const u32x4* __restrict__ b,
                                                          size_t nvec, bool tail4, float beta, float gamma,
                                                          u32x4* __restrict__ out) {
-    if (tail4 && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (tail4 && flat_block() == 0 && threadIdx.x == 0) {
         const u32x2 ta = *(const u32x2*)(a + nvec), tb = *(const u32x2*)(b + nvec);
         *(u32x2*)(out + nvec) = (u32x2){sparse_add_pair(ta[0], tb[0], beta, gamma), sparse_add_pair(ta[1], tb[1], beta, gamma)};
     }
-    const size_t first = (size_t)blockIdx.x * (256 * SA_UNROLL) + threadIdx.x;
+    const size_t first = (size_t)flat_block() * (256 * SA_UNROLL) + threadIdx.x;
     u32x4 va[SA_UNROLL], vb[SA_UNROLL];
 #pragma unroll
     for (int u = 0; u < SA_UNROLL; ++u) {
@@ -437,10 +438,10 @@ __global__ void __launch_bounds__(256) sparse_add_kernel(const u32x4* __restrict
 hipError_t launch_sparse_add(const bf16_t* a, const bf16_t* b, size_t count, float beta, float gamma, bf16_t* out,
                              hipStream_t s) {
     size_t nvec = count / 8;                                  // count is a multiple of 4
-    size_t blocks = (nvec + 256 * SA_UNROLL - 1) / (256 * SA_UNROLL);
-    if (blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;   // cannot happen for extents below 2^31
+    int64_t blocks = (int64_t)((nvec + 256 * SA_UNROLL - 1) / (256 * SA_UNROLL));
+    if (!grid_fits(blocks)) return hipErrorInvalidValue;
     if (blocks == 0) blocks = 1;
-    sparse_add_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>((const u32x4*)a, (const u32x4*)b, nvec, count % 8 != 0,
+    sparse_add_kernel<<<grid_of(blocks), dim3(256), 0, s>>>((const u32x4*)a, (const u32x4*)b, nvec, count % 8 != 0,
                                                                    beta, gamma, (u32x4*)out);
     return hipGetLastError();
 }

@@ -226,6 +226,32 @@ def test_masks_of_the_largest_weights(axis, rows, cols):
         assert torch.equal(part, want.expand_as(part))
 
 
+# the two streams over a weight of 2^36 elements and more, likewise
+def test_prune_and_sparse_add_of_the_largest_weights():
+    rows, cols = 1 << 18, (1 << 18) + 64
+    print(f"prune_rows, sparse_add {rows} x {cols}", flush=True)
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 230 << 30:
+        pytest.skip("not enough free device memory")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + 2)
+    block = torch.randn((64, cols), generator=gen, device="cuda").to(torch.bfloat16)
+    want = sl.slope_prune_rows(block)
+    summed = sl.slope_sparse_add(block, block, 0.5, 0.25)
+    W = torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda")
+    W.view(-1, 64, cols).copy_(block)
+    vals, meta, _ = sl.slope_prune_rows(W)
+    for got, one in ((vals, want[0]), (meta, want[1])):
+        for part in got.view(-1, 64, one.shape[1]).split(256):
+            assert torch.equal(part, one.expand_as(part))
+    del vals, meta, got, part
+    sl.slope_sparse_add(W, W, 0.5, 0.25, out=W)
+    for part in W.view(-1, 64, cols).split(256):
+        assert torch.equal(part, summed.expand_as(part))
+    del W, part
+    torch.cuda.empty_cache()
+
+
 # as many tokens as give the kernel for ragged extents 2^23 tiles of 512 threads: a block of tokens repeated
 def test_ragged_adapter_product_of_the_most_tokens():
     b, d, r = (1 << 28) + 64, 8, 32
