@@ -580,7 +580,8 @@ hipError_t launch_dense_tn(const bf16_t* At, int64_t m, const bf16_t* Bt, int64_
 // (5); a round of whole tiles costs ksteps + 6.  Where a bundle can be cut into whole shares, its lanes have a part each and
 // its tiles fewer of them to add: then the cheaper of the two.  (19 k-steps, us: 4096 x 5120 uneven shares 77.8, whole
 // ones 72.1; 3328 x 6656 83.1 / 76.8; 128 k-steps: 3328 x 6656 282 / 266.  More than half a round left: 5120 x 5120, 128
-// k-steps, where the rule begins to cut: 316 not cut, 321 cut; 256 k-steps: 627 / 597.)
+// k-steps, where the rule begins to cut: 316 not cut, 321 cut; 256 k-steps: 627 / 597; 11 x 37 tiles, 128 k-steps: 311 / 333, 192:
+// 471 / 471, 256: 632 / 611.)
 inline TailPlan tail_plan(int64_t tiles_m, int64_t tiles_n, int64_t ksteps) {
     const TailPlan p = NO_TAIL;
     const int64_t tiles = tiles_m * tiles_n;
@@ -601,7 +602,9 @@ inline TailPlan tail_plan(int64_t tiles_m, int64_t tiles_n, int64_t ksteps) {
     int64_t lanes = (bundles * ksteps + share - 1) / share;
     int64_t aligned = share / std::gcd(share, ksteps), parts = lanes + bundles - 1 - (bundles - 1) / aligned, row = ksteps;
     const double shares = (double)share + 6.0 * (1.0 + (double)((share + ksteps - 1) / ksteps)) + 0.065 * (double)(parts * bundle) + 5.0;
-    double cost = shares;
+    // (in the strips beside whole chunks of a narrow grid a bundle's tiles share few panels)
+    const bool narrow = (tiles_m < tiles_n ? tiles_m : tiles_n) < 13;
+    double cost = shares + (narrow ? 0.2 * (double)share : 0.0);
     if (rem <= RESIDENT / 2 && ksteps >= 16) {                // measured: the cut never lost here; a share of the round + 1/4
         const int64_t slabs = RESIDENT / rem < ksteps / 8 ? RESIDENT / rem : ksteps / 8;
         cost = ((double)ksteps + 6.0) * (1.0 / (double)slabs + 0.25);
