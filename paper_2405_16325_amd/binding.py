@@ -100,14 +100,16 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # not part of torch's public interface
+# not part of torch's public interface
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
 def _stream():
     """The raw handle of torch.cuda.current_stream(), which builds an object per call."""
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_device())
 
 
 def _check(call: str, status: int):
