@@ -52,9 +52,9 @@ hipError_t launch_xl_reduce(const float* Q, int slabs, int64_t n, int64_t r, bf1
 // C = bf16(sum of P[slices][n][m] + T R), T = bf16 of the sum of Q[q_slabs][n][r]
 hipError_t launch_adapter_finish(const float* P, int slices, int64_t n, int64_t m, const float* Q, int q_slabs,
                                  const bf16_t* R, int64_t r, bf16_t* C, hipStream_t s);
-// the same product for a few dozen to a few hundred tokens, split over K with fp32 partial sums in `slabs`
-// (spmm_slab_bytes of them; 0 = this shape does not take the path).  The adapter (r == 0: none) comes as T = X L,
-// or, where T is null, as its sums Q, which workgroups of the product's own first launch write (slab_xl_split)
+// the same product for more than STREAM_MAX_TOKENS tokens, split over K with fp32 partial sums, slabs x n x m of them: tile
+// and slabs from spmm_split (slabs == 0: not split).  The adapter (r == 0: none) comes as T = X L, or, where T is null, as
+// its sums Q, which workgroups of the product's own first launch write (slab_xl_split)
 struct SlabAdapter {
     const bf16_t* T;
     float* Q;
@@ -63,12 +63,13 @@ struct SlabAdapter {
     int64_t r;
     XlSplit x;
 };
-int spmm_slab_count(int64_t n, int64_t m, int64_t K);
-size_t spmm_slab_bytes(int64_t n, int64_t m, int64_t K);
-bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K);   // any split but that of a long weight in whole quads of k-steps
-bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, XlSplit& x);
+struct SpmmSplit { int bm, bn, slabs; };
+inline size_t spmm_split_bytes(const SpmmSplit& split, int64_t n, int64_t m) { return (size_t)split.slabs * (size_t)n * (size_t)m * 4; }
+SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r);
+SpmmSplit spmm_long_split(int64_t n, int64_t m, int64_t K);
+bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& split, XlSplit& x);
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
-                             int64_t K, const SlabAdapter& ad, bf16_t* C, float* slabs, hipStream_t s);
+                             int64_t K, const SlabAdapter& ad, const SpmmSplit& split, bf16_t* C, float* slabs, hipStream_t s);
 // the same product for n <= 32 tokens (any K % 64 == 0, K >= 128); adapters as T[n, K2] and R[K2, m] as stored
 constexpr int64_t STREAM_MAX_TOKENS = 32;
 inline bool spmm_stream_fits(int64_t n, int64_t K) { return n <= STREAM_MAX_TOKENS && K >= 128 && K % 64 == 0; }

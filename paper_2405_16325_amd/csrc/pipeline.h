@@ -185,20 +185,20 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[MF][NF], int f0, i
     __syncthreads();
     // 16-byte pieces, all read from LDS before the first is stored (a loop of read, wait, store per piece took
     // 2.5 us of every tile); where m is a multiple of 8 a piece is inside the row or outside as a whole
-    constexpr int PPR = BMT / 8, PER_THREAD = BNT * PPR / THREADS;
-    static_assert(BNT * PPR % THREADS == 0, "whole pieces per thread");
+    constexpr int PPR = BMT / 8, PIECES = BNT * PPR, PER_THREAD = (PIECES + THREADS - 1) / THREADS;
+    constexpr bool EVEN = PIECES % THREADS == 0;              // else the last round of pieces is for the first threads only
     u32x4 piece[PER_THREAD];
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
         const int idx = (int)threadIdx.x + u * THREADS;
-        piece[u] = *(const u32x4*)(smem + (idx / PPR) * CP + (idx % PPR) * 16);
+        if (EVEN || idx < PIECES) piece[u] = *(const u32x4*)(smem + (idx / PPR) * CP + (idx % PPR) * 16);
     }
     if (m % 8 == 0) {                                         // uniform
 #pragma unroll
         for (int u = 0; u < PER_THREAD; ++u) {
             const int idx = (int)threadIdx.x + u * THREADS;
             const int tok = tile_t0 + idx / PPR, col = tile_f0 + (idx % PPR) * 8;
-            if (tok < n && col < m) *(u32x4*)(C + (size_t)tok * m + col) = piece[u];
+            if ((EVEN || idx < PIECES) && tok < n && col < m) *(u32x4*)(C + (size_t)tok * m + col) = piece[u];
         }
         return;
     }
@@ -206,6 +206,7 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[MF][NF], int f0, i
     for (int u = 0; u < PER_THREAD; ++u) {
         const int idx = (int)threadIdx.x + u * THREADS;
         const int tok = tile_t0 + idx / PPR, col = tile_f0 + (idx % PPR) * 8;
+        if (!EVEN && idx >= PIECES) break;
         if (tok < n && col < m) *(u32x2*)(C + (size_t)tok * m + col) = (u32x2){piece[u][0], piece[u][1]};
         if (tok < n && col + 4 < m) *(u32x2*)(C + (size_t)tok * m + col + 4) = (u32x2){piece[u][2], piece[u][3]};
     }

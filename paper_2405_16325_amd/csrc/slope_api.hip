@@ -40,15 +40,27 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
                                                      : dense_tn_plain_partial_bytes(b, r));
 }
 
-// The slab buffer of a forward product with adapters of rank r (0: none); 0 where the product is not split over K.
-// Shapes that the static scratch holds without an optional split keep to that: every form of the call then takes the same
-// route, and what slope_spmm_fwd_static accepts is what the workspace query says.
-size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
-    const size_t slabs = round256(spmm_slab_bytes(b, d_out, d_in));
-    if (slabs && spmm_slabs_optional(b, d_out, d_in) &&
-        adapter_workspace_bytes(b, d_in, d_out, r) + slabs > (size_t)SLOPE_STATIC_SCRATCH_BYTES)
-        return 0;
-    return slabs;
+// The split over d_in of a forward product with adapters of rank r (0: none), {0, 0, 0} where it is not split.  Every form of
+// the call takes the same route, and what slope_spmm_fwd_static accepts is what the workspace query says: a split never
+// takes a shape past the static scratch.  A long weight in whole quads of k-steps is always split where that pays, at worst
+// into as many slabs of 256 rows as its estimate names, which its scratch is never counted below; any other product only
+// where that many, or else as many slabs of 256 x 128 tiles as one round holds, would fit the static scratch as well.
+SpmmSplit fwd_split(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
+    const SpmmSplit split = spmm_split(b, d_out, d_in, r), named = spmm_long_split(b, d_out, d_in);
+    if (split.slabs == 0) return split;
+    const size_t fixed = adapter_workspace_bytes(b, d_in, d_out, r);
+    auto fits = [&](int64_t slabs) {
+        return fixed + round256((size_t)slabs * (size_t)b * (size_t)d_out * 4) <= (size_t)SLOPE_STATIC_SCRATCH_BYTES;
+    };
+    if (named.slabs && d_in % 256 == 0) return fits(split.slabs) || !fits(named.slabs) ? split : named;
+    const int64_t tiles = ((d_out + 255) / 256) * ((b + 127) / 128), held = RESIDENT / tiles < 16 ? RESIDENT / tiles : 16;
+    return fits(split.slabs) && fits(named.slabs ? named.slabs : held > 2 ? held : 2) ? split : SpmmSplit{0, 0, 0};
+}
+
+size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {     // the slab buffer of that product
+    const size_t split = spmm_split_bytes(fwd_split(b, d_in, d_out, r), b, d_out);
+    const size_t named = d_in % 256 == 0 ? spmm_split_bytes(spmm_long_split(b, d_out, d_in), b, d_out) : 0;
+    return round256(split > named ? split : named);
 }
 
 // T = X L on the kernel for ragged extents although its extents are whole k-steps
@@ -65,12 +77,6 @@ hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A
     if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);
     return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);
 }
-
-// A split product's second kernel adds up the sums of T = X L itself where workgroups beside the product's compute them
-// (two launches fewer) and all its workgroups together read at most this much of them, about 6 TB/s (128 tokens, rank 128:
-// 28 MB at 9216 x 9216, 10 us; but 600 MB at 36864 x 9216 with 16 slabs, 54 us against 15 with T).  With X L in a launch of
-// its own it never pays: 37 tokens, 9728 x 17664, rank 32 76.5 us, 67.3 with T; 60 tokens, 20480 x 8192 73.1 / 68.5.
-constexpr int64_t XL_BESIDE_BYTES = (int64_t)40 << 20;
 
 }  // namespace
 
@@ -211,27 +217,19 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     uint8_t* after = ws + adapter_workspace_bytes(b, d_in, d_out, r);      // the slabs or slices of the product
     bf16_t* Lt = (bf16_t*)(ws + round256((size_t)b * r * 2));
     float* sums = (float*)((uint8_t*)Lt + round256((size_t)d_in * r * 2));
-    const int64_t sums_floats = adapter ? (int64_t)(xl_small_scratch_bytes(b, d_in, r) / 4) : 0;
     const bool few = spmm_stream_fits(b, d_in);
     // With scratch memory a batch of a few dozen to a few hundred tokens is split over K as well, and up to
     // XL_SMALL_MAX_TOKENS of them the kernel that adds the slabs adds the adapter term too, straight from the sums of T = X L,
     // which workgroups beside the product's compute where they fit (rank 128, 9216 x 9216, 128 tokens: 54.7 -> 42.8 us in
     // all; 256 tokens: 67 -> 53).
-    const bool slabs = !few && workspace && fwd_slab_bytes(b, d_in, d_out, r) > 0;
+    const SpmmSplit split = !few && workspace ? fwd_split(b, d_in, d_out, r) : SpmmSplit{0, 0, 0};
     SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
-    if (slabs && !adapter) return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
-    if (slabs && b <= XL_SMALL_MAX_TOKENS) {
-        // that kernel reads the sums again for every 64 features
-        const int64_t slab_read = (d_out + 63) / 64 * ((b + 31) / 32 * 32) * r * 4;
-        int64_t held = XL_BESIDE_BYTES / slab_read * b * r;
-        if (held > sums_floats) held = sums_floats;
-        if (held > 0 && slab_xl_split(b, d_out, d_in, r, held, ad.x))
-            return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
-    }
+    if (split.slabs && (!adapter || (b <= XL_SMALL_MAX_TOKENS && slab_xl_split(b, d_out, d_in, r, split, ad.x))))
+        return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, split, (bf16_t*)Y, (float*)after, s));
     if (adapter) {                                            // T = X L, rounded to bf16
         hipError_t e;
         if (d_in % 64 == 0 && b <= XL_SMALL_MAX_TOKENS) {
-            const XlSplit x = xl_split(b, d_in, r, sums_floats, RESIDENT);
+            const XlSplit x = xl_split(b, d_in, r, (int64_t)(xl_small_scratch_bytes(b, d_in, r) / 4), RESIDENT);
             e = launch_xl(x_in, b, d_in, l, r, x, x.slabs > 1 ? sums : nullptr, T, s);
             if (e == hipSuccess && x.slabs > 1) e = launch_xl_reduce(sums, x.slabs, b, r, T, s);
         } else {
@@ -246,9 +244,9 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
         float* slices = workspace && spmm_rows_partial_bytes(b, d_out, d_in) ? (float*)after : nullptr;
         return finish(launch_spmm_stream(x_in, b, wv, wm, d_out, d_in, T, R, r, (bf16_t*)Y, slices, s));
     }
-    if (slabs) {
+    if (split.slabs) {
         ad.T = T;
-        return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, (bf16_t*)Y, (float*)after, s));
+        return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, split, (bf16_t*)Y, (float*)after, s));
     }
     // R as stored, [r][d_out]: the kernels take it k-major
     return finish(launch_spmm(x_in, b, wv, wm, d_out, d_in, T, R, -r, (bf16_t*)Y, s));
@@ -498,11 +496,12 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         plan[2] = b <= 16 ? 16 : 32;
         if (slices > 0) plan[3] = slices;
     } else {
-        const int slabs = with_workspace && fwd_slab_bytes(b, d_in, d_out, r) ? spmm_slab_count(b, d_out, d_in) : 0;
-        const int64_t rest = slabs > 0 ? 0 : spmm_rest_tokens(b, d_out, d_in);
+        const SpmmSplit split = with_workspace ? fwd_split(b, d_in, d_out, r) : SpmmSplit{0, 0, 0};
+        const int64_t rest = split.slabs > 0 ? 0 : spmm_rest_tokens(b, d_out, d_in);
         int bm, bn;
         spmm_tile_choice(b - rest, d_out, d_in, bm, bn);
-        if (slabs > 0) { plan[0] = 1; plan[1] = 256; plan[2] = b <= 64 ? 64 : 128; plan[3] = slabs; }
+        const int64_t tiles_of_64 = ((b + 63) / 64) * ((d_out + 63) / 64);
+        if (split.slabs > 0) { plan[0] = b <= 128 && split.bm < 256 && tiles_of_64 <= RESIDENT ? 6 : 1; plan[1] = split.bm; plan[2] = split.bn; plan[3] = split.slabs; }
         else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = spmm_generic_edge(b - rest, d_out); }
         else { plan[0] = 2; plan[1] = bm; plan[2] = bn; }
         if (rest > 0) { plan[0] = 5; plan[3] = (int32_t)rest; }

@@ -15,9 +15,10 @@
 // so the sparse operand is the weight, rows of D are output features, and a lane's four
 // accumulators are four consecutive features of one token: an 8-byte store into row-major C.
 //
-// Three kernels here (launch_spmm picks; the forms for very few tokens are in spmm_stream.hip):
-// spmm_kernel<BM, BN> and spmm_split_kernel (the 256 x 256 tile) are the fast ones and need
-// K % 64 == 0; spmm_generic_kernel takes any K % 8 == 0 with a plain register-staged pipeline.
+// Four kernels here (launch_spmm picks; the forms for very few tokens are in spmm_stream.hip):
+// spmm_split_kernel (the 256 x 256 tile), spmm_kernel<BM, BN> (the other large tiles) and spmm_ring_kernel<BM, BN>
+// (the smaller ones) are the fast ones and need K % 64 == 0; spmm_generic_kernel takes any K % 8 == 0 with a plain
+// register-staged pipeline.
 //
 // spmm_kernel.  What a compute unit can pull from L2 per unit of time matters as much as the matrix
 // pipe (whose clock the power management lowers well below nominal under this load), so the data
@@ -33,6 +34,8 @@
 // run half a k-step apart: while one group issues its MFMAs the other reads its fragments from
 // LDS and queues global loads, then they swap (two barriers per k-step), so every SIMD's matrix
 // pipe always has a wavefront feeding it.  Loads run two k-steps ahead of their use.
+#include <type_traits>
+
 #include "pipeline.h"
 #include "skinny.h"
 
@@ -218,6 +221,40 @@ struct SplitJob {
     int r, k_per, xl_slabs;
 };
 
+// What a workgroup of a split launch does: its tile and slab, the slab that adds the dense extension, true; or a part of X L
+// (done here) or nothing, false.
+__device__ __forceinline__ bool split_item(const SplitJob& job, const bf16_t* __restrict__ B, int n, int K, int tiles_m, int tiles_n,
+                                           uint8_t* smem, int& tm, int& tn, int& slab, int& extension_slab) {
+    const int tiles = tiles_m * tiles_n, run = (tiles * job.nslabs + XCDS - 1) / XCDS;
+    const int xcd = (int)blockIdx.x % XCDS, pos = (int)blockIdx.x / XCDS;
+    if (pos >= run) {
+        const int id = (pos - run) * XCDS + xcd;
+        const int xl_tiles_r = (job.r + SK_BJ - 1) / SK_BJ, xl_tiles = xl_tiles_r * ((n + SK_BI - 1) / SK_BI);
+        const int part = id / xl_tiles, tile = id % xl_tiles;
+        if (part < job.xl_slabs)
+            skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * (uint32_t)job.k_per,
+                                     min((uint32_t)K, (part + 1) * (uint32_t)job.k_per), tile / xl_tiles_r * SK_BI,
+                                     tile % xl_tiles_r * SK_BJ, nullptr, job.Q + (size_t)part * n * job.r, smem);
+        return false;
+    }
+    int tile;
+    if (tiles % XCDS == 0) {
+        slab = pos / (tiles / XCDS);
+        tile = xcd * (tiles / XCDS) + pos % (tiles / XCDS);
+    } else {
+        const int item = xcd * run + pos;
+        if (item >= tiles * job.nslabs) return false;
+        slab = item / tiles;
+        tile = item % tiles;
+    }
+    // the extension is added once: by the first slab if every XCD has its share of that (its workgroups start first), else
+    // by a slab that depends on the tile
+    extension_slab = tiles % XCDS == 0 ? 0 : tile % job.nslabs;
+    tn = tile % tiles_n;
+    tm = tile / tiles_n;
+    return true;
+}
+
 template <int BM, int BN, bool TAIL, bool SPLIT>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __restrict__ B, int n,
                                                             const bf16_t* __restrict__ Av,
@@ -235,31 +272,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     int tm, tn, slab = 0, extension_slab = 0;
     if constexpr (SPLIT) {
         static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
-        const int tiles = tiles_m * tiles_n, run = (tiles * job.nslabs + XCDS - 1) / XCDS;
-        const int xcd = (int)blockIdx.x % XCDS, pos = (int)blockIdx.x / XCDS;
-        if (pos >= run) {
-            const int id = (pos - run) * XCDS + xcd;
-            const int xl_tiles_r = (job.r + SK_BJ - 1) / SK_BJ, xl_tiles = xl_tiles_r * ((n + SK_BI - 1) / SK_BI);
-            const int part = id / xl_tiles, tile = id % xl_tiles;
-            if (part < job.xl_slabs)
-                skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * (uint32_t)job.k_per,
-                                         min((uint32_t)K, (part + 1) * (uint32_t)job.k_per), tile / xl_tiles_r * SK_BI,
-                                         tile % xl_tiles_r * SK_BJ, nullptr, job.Q + (size_t)part * n * job.r, smem);
-            return;
-        }
-        int tile;
-        if (tiles % XCDS == 0) {
-            slab = pos / (tiles / XCDS);
-            tile = xcd * (tiles / XCDS) + pos % (tiles / XCDS);
-        } else {
-            const int item = xcd * run + pos;
-            if (item >= tiles * job.nslabs) return;
-            slab = item / tiles;
-            tile = item % tiles;
-        }
-        extension_slab = tiles % XCDS == 0 ? 0 : tile % job.nslabs;
-        tn = tile % tiles_n;
-        tm = tile / tiles_n;
+        if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
         if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
     }
@@ -395,8 +408,6 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 #undef SPMM_STEP
     WAIT_HERE(waitcnt_imm(0, 15));           // drain the clamped look-ahead loads
 
-    // the dense extension is added once: by the first slab if every XCD has its share of that (its workgroups start
-    // first), else by a slab that depends on the tile
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
     extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
                                      slab == extension_slab ? K2 : 0, C, smem, m0, n0,
@@ -637,6 +648,187 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 }
 
 // ------------------------------------------------------------------------------------------
+// spmm_ring_kernel: the smaller tiles, one barrier per pair of k-steps.  A tile of 128 x 64 gives a wavefront four MFMAs
+// per k-step, so two phases and two barriers per k-step, as above, cost more than the k-step's loads: it took 0.35 us per
+// k-step beside what its loads take.  Here a ring stage holds a pair of k-steps of both operands (the packed values come in
+// pairs anyway, 128 bytes per row), and a wavefront, per pair: waits for its own loads of the pair, passes the barrier,
+// queues the loads that refill the stage everybody has left, then reads its fragments and multiplies.  Three to four
+// stages keep at least a pair of k-steps (34 to 50 KB) on the way, more than the 16 KB a compute unit holds in flight, so
+// the operand feed is what bounds the kernel: 62 bytes per ns and compute unit on 128 x 64, 50 to 55 on the larger tiles.
+// Metadata: META_PAIRS pairs (16 bytes each) per row at a time, as many neighbouring lanes per row, the pieces of a row
+// rotated so that the sixteen rows of a 2-byte read fall on different banks.
+// Weights from HBM, us, the two-phase kernel / here: 2048 tokens, 768 x 3072 on 128 x 64 20.4 / 15.8; 512 tokens, 4096 x 4096
+// 26.7 / 20.8; 300 tokens, 9216 x 4096 on 128 x 128 39.6 / 33.0, on 192 x 64 39.9 / 29.5; on 192 x 128 and larger tiles, where
+// a stage of this ring would leave room for two only, a barrier per k-step with as many stages took 42 against 45 on
+// 192 x 128 and 53 against 49 on 256 x 128 (1000 tokens, 4352 x 4352): those stay with the kernel above.
+template <int BM, int BN>
+struct RingSmem {
+    static constexpr int A_STAGE = BM * 128, B_STEP = BN * 128;   // packed values of BM rows x 2 k-steps; BN tokens x 1
+    static constexpr int STAGE = A_STAGE + 2 * B_STEP;
+    static constexpr int META_PAIRS = 3 * STAGE + 2 * BM * 64 <= 160 * 1024 ? 4 : 2;
+    static constexpr int M_ROW = META_PAIRS * 16, M_BLOCK = BM * M_ROW;   // two blocks of metadata
+    static constexpr int FIT = (160 * 1024 - 2 * M_BLOCK) / STAGE;
+    static constexpr int STAGES = FIT < META_PAIRS + 1 ? FIT : META_PAIRS + 1;   // a block is rewritten when the pair
+                                                                                  // before its successor's first has been read
+    static constexpr int M_OFF = STAGES * STAGE, TOTAL = M_OFF + 2 * M_BLOCK;
+    static_assert(STAGES >= 3 && M_BLOCK % 1024 == 0, "a ring");
+};
+
+// Loads of the STAGES - 2 pairs after the pair with index u in its block of metadata: what may be in flight while that pair is read
+template <class S>
+constexpr int ring_leave(int u, int each, int meta) {
+    int c = 0;
+    for (int q = 1; q <= S::STAGES - 2; ++q) c += each + ((u + q) % S::META_PAIRS == 0 ? meta : 0);
+    return c;
+}
+
+// TAIL: an odd number of k-steps; the values and metadata of the last one are then fetched as the second half of a pair that
+// ends with the row (see spmm_kernel).
+template <int BM, int BN, bool TAIL, bool SPLIT>
+__global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* __restrict__ B, int n,
+                                                                 const bf16_t* __restrict__ Av,
+                                                                 const uint8_t* __restrict__ Am, int m, int K,
+                                                                 const bf16_t* __restrict__ B2,
+                                                                 const bf16_t* __restrict__ A2, int K2,
+                                                                 bf16_t* __restrict__ C, int tiles_m, int tiles_n,
+                                                                 SplitJob job) {
+    using S = RingSmem<BM, BN>;
+    constexpr int META_PAIRS = S::META_PAIRS;
+    constexpr int WM = BM == 128 && BN == 128 ? 2 : 4, WN = 8 / WM;    // wavefronts over the tile: the squarest fragments
+    constexpr int MF = BM / (16 * WM), NF = BN / (16 * WN);
+    constexpr int A_LD = BM / 64, B_LD = BN / 32;             // 1 KiB loads per wavefront and pair
+    constexpr int M_LOADS = S::M_BLOCK / 1024, M_LD = (M_LOADS + 7) / 8;   // per block; some twice where 8 does not divide them
+    static_assert(BM % 64 == 0 && BN % 32 == 0 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "whole loads and fragments");
+    extern __shared__ __align__(16) uint8_t smem[];
+
+    int tm, tn, slab = 0, extension_slab = 0;
+    if constexpr (SPLIT) {
+        static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
+        if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
+    } else {
+        if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+    }
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int k_first = SPLIT ? slab * job.slab_steps : 0;    // a multiple of 4
+    const int ksteps = SPLIT && K / 64 - k_first > job.slab_steps ? job.slab_steps : K / 64 - k_first;
+    const int pairs = (ksteps + 1) / 2;
+
+    // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8
+    const uint8_t* a_src[A_LD];
+#pragma unroll
+    for (int i = 0; i < A_LD; ++i) {
+        const int rl = (wave * A_LD + i) * 8 + (lane >> 3);
+        a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
+    }
+    const uint8_t* b_src[B_LD];
+    int b_step[B_LD];                                         // which k-step of the pair (wave-uniform)
+#pragma unroll
+    for (int i = 0; i < B_LD; ++i) {
+        const int j = wave * B_LD + i, rl = j % (BN / 8) * 8 + (lane >> 3);
+        b_step[i] = j / (BN / 8);
+        b_src[i] = (const uint8_t*)B + (size_t)wrap_row(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
+    }
+    const uint8_t* m_src[M_LD];
+    int m_pair[M_LD], m_dst[M_LD];                            // pair inside the block; LDS offset inside it
+#pragma unroll
+    for (int i = 0; i < M_LD; ++i) {
+        const int idx = (wave * M_LD + i) % M_LOADS, rl = (idx * 64 + lane) / META_PAIRS;
+        m_src[i] = Am + (size_t)wrap_row(m0 + rl, m) * (K / 8) + (size_t)k_first * 8;
+        m_pair[i] = (lane % META_PAIRS) ^ (rl * META_PAIRS / 16 % META_PAIRS);
+        m_dst[i] = S::M_OFF + idx * 1024;
+    }
+    auto issue = [&](int p, int stage, bool new_block) {      // loads of pair p (inside the contraction, at least in part)
+        uint8_t* const st = smem + stage * S::STAGE;
+        if (new_block) {
+#pragma unroll
+            for (int i = 0; i < M_LD; ++i) {
+                const int64_t off = (int64_t)(p + m_pair[i]) * 16, last = (int64_t)ksteps * 8 - 16;
+                dma16(m_src[i] + (off < last ? off : last), smem + m_dst[i] + (p / META_PAIRS & 1) * S::M_BLOCK);
+            }
+        }
+        const int64_t a_off = pair_offset<TAIL>(p, ksteps);
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + a_off, st + (wave * A_LD + i) * 1024);
+#pragma unroll
+        for (int i = 0; i < B_LD; ++i) {
+            const int k = 2 * p + b_step[i], kc = !TAIL || k < ksteps ? k : ksteps - 1;
+            dma16(b_src[i] + (size_t)kc * 128, st + S::A_STAGE + (wave * B_LD + i) * 1024);
+        }
+    };
+
+    f32x4 acc[MF][NF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    // ---- reader lanes: fragment f = rows 16f .. 16f+15 = 2 KiB; lane (l16, lq) wants chunk 4h + lq
+    const int sw = (l16 >> 1) & 7;
+    const int rd0 = l16 * 128 + ((lq ^ sw) * 16), rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);
+    const int a_rd = wm * MF * 2048, b_rd = S::A_STAGE + wn * NF * 2048;
+    const int m_rd = S::M_OFF + (wm * MF * 16 + l16) * S::M_ROW + lq * 2, m_sw = l16 * META_PAIRS / 16 % META_PAIRS;
+    auto multiply = [&](const uint8_t* st, const uint8_t* pm, int e, bool second) {
+        BFrag bf[NF];
+        AFrag af[MF];
+        int ai[MF];
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            bf[j].u[0] = *(const u32x4*)(st + b_rd + e * S::B_STEP + j * 2048 + rd0);
+            bf[j].u[1] = *(const u32x4*)(st + b_rd + e * S::B_STEP + j * 2048 + rd1);
+        }
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            af[i].u = *(const u32x4*)(st + a_rd + i * 2048 + (second ? rd1 : rd0));
+            ai[i] = *(const uint16_t*)(pm + i * 16 * S::M_ROW + (second ? 8 : 0));
+        }
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+                acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(af[i].v, bf[j].v, acc[i][j], ai[i], 0, 0);
+    };
+
+#pragma unroll
+    for (int p = 0; p < S::STAGES - 1; ++p)
+        if (p < pairs) issue(p, p, p % META_PAIRS == 0);
+    int stage = 0;
+    auto pair = [&](int p, auto index) {                      // index = p % META_PAIRS
+        constexpr int u = decltype(index)::value, leave = ring_leave<S>(u, A_LD + B_LD, M_LD);
+        // in the last STAGES - 2 pairs there are fewer loads behind this pair's: then for all of them
+        if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 0));
+        else WAIT_HERE(waitcnt_imm(0, 0));
+        wg_barrier();
+        if (p + S::STAGES - 1 < pairs)
+            issue(p + S::STAGES - 1, stage == 0 ? S::STAGES - 1 : stage - 1, (u + S::STAGES - 1) % META_PAIRS == 0);
+        const uint8_t* st = smem + stage * S::STAGE;
+        const uint8_t* pm = smem + m_rd + (p / META_PAIRS & 1) * S::M_BLOCK + (u ^ m_sw) * 16;
+        const bool odd_end = TAIL && 2 * p + 1 >= ksteps;
+        multiply(st, pm, 0, odd_end);
+        if (!odd_end) multiply(st, pm, 1, true);
+        stage = stage == S::STAGES - 1 ? 0 : stage + 1;
+    };
+    for (int p = 0; p < pairs; p += META_PAIRS) {
+        pair(p, std::integral_constant<int, 0>{});
+        if (p + 1 >= pairs) break;
+        pair(p + 1, std::integral_constant<int, 1>{});
+        if constexpr (META_PAIRS == 4) {
+            if (p + 2 >= pairs) break;
+            pair(p + 2, std::integral_constant<int, 2>{});
+            if (p + 3 >= pairs) break;
+            pair(p + 3, std::integral_constant<int, 3>{});
+        }
+    }
+    static_assert(BN * (BM * 2 + 16) <= S::TOTAL && 128 * (BM * 2 + 32) <= S::TOTAL, "the staged output tile and factor fit in the ring");
+    extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
+                                                   slab == extension_slab ? K2 : 0, C, smem, m0, n0,
+                                                   SPLIT ? job.slabs + (size_t)slab * (size_t)n * (size_t)m : nullptr);
+}
+
+// ------------------------------------------------------------------------------------------
 // Generic kernel (any K % 8 == 0): a tile of 32 F x 32 F, G groups of 4 wavefronts (2 x 2), operands staged
 // through registers, two k-steps (a pair) per trip.  What a compute unit can keep in flight is a number of requests, not
 // of bytes, so all loads are of whole 128-byte lines: 8 lanes per row of packed values, 16 per row of tokens (half as
@@ -860,38 +1052,53 @@ hipError_t launch_generic(const bf16_t* B, int64_t n, const bf16_t* Av, const ui
     return launch_generic_as<4, 1>(B, n, Av, Am, m, K, B2, A2, K2, C, s);
 }
 
+// workgroups of a launch over the tiles, or over the tiles of every slab and the parts of X L beside them
+template <bool SPLIT>
+int tile_grid(int tiles_m, int tiles_n, int64_t n, const SplitJob& job) {
+    if (!SPLIT) return super_grid(tiles_m, tiles_n);
+    const int xl = job.L ? job.xl_slabs * ((job.r + SK_BJ - 1) / SK_BJ) * (int)((n + SK_BI - 1) / SK_BI) : 0;
+    return ((tiles_m * tiles_n * job.nslabs + XCDS - 1) / XCDS + (xl + XCDS - 1) / XCDS) * XCDS;
+}
+
 template <int BM, int BN, bool TAIL, bool SPLIT>
 hipError_t launch_tile_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
                           const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job) {
     using S = SpmmSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
-    auto kern = spmm_kernel<BM, BN, TAIL, SPLIT>;
     hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    int grid = super_grid(tiles_m, tiles_n);
-    if (SPLIT) {
-        const int xl = job.L ? job.xl_slabs * ((job.r + SK_BJ - 1) / SK_BJ) * (int)((n + SK_BI - 1) / SK_BI) : 0;
-        grid = ((tiles_m * tiles_n * job.nslabs + XCDS - 1) / XCDS + (xl + XCDS - 1) / XCDS) * XCDS;
-    }
-    kern<<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C,
-                                                                    tiles_m, tiles_n, job);
+    spmm_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)tile_grid<SPLIT>(tiles_m, tiles_n, n, job)), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
     return hipGetLastError();
 }
 
-template <int BM, int BN>
-hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
-    auto launch = K % 256 == 0 ? launch_tile_as<BM, BN, false, false> : launch_tile_as<BM, BN, true, false>;
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, SplitJob{});
+template <int BM, int BN, bool TAIL, bool SPLIT>
+hipError_t launch_ring_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job) {
+    using S = RingSmem<BM, BN>;
+    static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
+    int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
+    hipError_t e = allow_dynamic_lds<spmm_ring_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
+    if (e != hipSuccess) return e;
+    spmm_ring_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)tile_grid<SPLIT>(tiles_m, tiles_n, n, job)), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
+    return hipGetLastError();
 }
 
-// a split over k
-template <int BN>
-hipError_t launch_slab_tiles(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                             const bf16_t* B2, const bf16_t* A2, int64_t K2, hipStream_t s, const SplitJob& job) {
-    auto launch = K % 256 == 0 ? launch_tile_as<256, BN, false, true> : launch_tile_as<256, BN, true, true>;
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, nullptr, s, job);
+// a whole product, or one split over k
+template <int BM, int BN, bool SPLIT = false>
+hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}) {
+    auto launch = K % 256 == 0 ? launch_tile_as<BM, BN, false, SPLIT> : launch_tile_as<BM, BN, true, SPLIT>;
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job);
+}
+
+template <int BM, int BN, bool SPLIT = false>
+hipError_t launch_ring(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}) {
+    auto launch = K % 128 == 0 ? launch_ring_as<BM, BN, false, SPLIT> : launch_ring_as<BM, BN, true, SPLIT>;
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job);
 }
 
 // C[idx] = bf16( sum over slabs, in order, of P[s][idx] ), four elements per thread
@@ -936,19 +1143,24 @@ hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint
 
 // Products of too few tiles to fill the chip, a few dozen tokens on any weight or some thousand on a small one: narrow
 // token tiles on small weight tiles would re-read the tokens from L2 for every few weight rows (the tile kernels run at the
-// L2 -> LDS rate), and tall weight tiles alone are too few.  So: 256-row weight tiles, the k range cut into slabs that run
+// L2 -> LDS rate), and tall weight tiles alone are too few.  So the k range is cut into slabs that run
 // as separate workgroups and leave fp32 partial sums in `slabs`, and a short second kernel (fixed order: bit-identical
-// runs) that rounds to bf16.  SLAB_MAX_TOKENS is the reach of the first of the two rules below.
+// runs) rounds to bf16.  SLAB_MAX_TOKENS is the reach of the estimate for long weights on tiles of 256 rows below.
 constexpr int64_t SLAB_MAX_TOKENS = 1024;
 
 // The tile kernels take whole k-steps of 64, at least two of them (700 tokens: 4160 x 2112 54 -> 25 us, 2112 x 4160
 // 96 -> 35 us against the generic kernel).
 static bool tile_kernel_fits(int64_t K) { return K % 64 == 0 && K >= 128; }
-// One round of 64 x 64 tiles: the generic kernel's four groups beat the rings of the tile kernels at every contraction
-// length (input gradients without scratch: 512 tokens, 2048 x 4096: 26.5 -> 21.9 us; 128 tokens, 8192 x 9216: 67 -> 58 us;
-// 1024 tokens, 1024 x 1024: 9.9 -> 8.7 us): all of a compute unit's 16 wavefronts load, and each k-step waits for its
-// own quarter of them only.  (777 tokens, 1280 x 5120, 260 tiles in two rounds: 34 -> 50 us.)
+// One round of 64 x 64 tiles: the generic kernel's four groups are the best form without a split where twice as large
+// tiles would leave half of the compute units idle (300 tokens, 1536 x 1536 8.6 us, on 128 x 64 9.5; 1024 tokens, 1024 x
+// 1024 8.7): all of a compute unit's 16 wavefronts load, and each k-step waits for its own quarter of them only.  (777
+// tokens, 1280 x 5120, 260 tiles in two rounds: 34 -> 50 us.)
 static bool one_round_of_64(int64_t n, int64_t m) { return tiles_of_64(n, m) <= RESIDENT; }
+
+static int slab_steps_of(int64_t K, int want) {               // k-steps per slab, whole quads
+    const int64_t quads = (K + 255) / 256;
+    return (int)((quads + want - 1) / want) * 4;
+}
 
 static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || !tile_kernel_fits(K)) return 0;
@@ -980,60 +1192,54 @@ static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     return best < 2 ? 0 : best;
 }
 
-// Time of the tile kernels' rounds for a product, in us: a k-step of a bm x bn tile takes about 0.35 us and 1 us per 100 KB
-// of operands, a tile's start and end 3 us (estimate / measured: 128 x 64 tiles, 48 and 65 k-steps 28 / 30 and 37 / 37;
-// 256 x 128, 144 k-steps 104 / 111; 192 x 256, two rounds of 80 k-steps 137 / 139).
-static double step_us(int64_t bm, int64_t bn) { return 0.35 + (double)(72 * bm + 128 * bn) / 1e5; }
+// Tiles of the product without a split; of two that take as long the first.  64 x 64 stands for the generic kernel's four groups.
+struct SpmmTile { int bm, bn; };
+constexpr SpmmTile SPMM_TILES[] = {{256, 256}, {256, 192}, {192, 256}, {192, 192}, {256, 128}, {192, 128},
+                                   {128, 128}, {192, 96}, {192, 64}, {128, 96}, {128, 64}};
+static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 128); }
+
+// Time of a product on bm x bn tiles, in us: rounds of 256 resident tiles, each of 3.3 us and its k-steps.  A k-step is the
+// operand feed of a compute unit, 53 bytes per ns (a little more on the smaller tiles of the ring kernel; up to a fifth more
+// with few compute units at work), and takes longer for weight bytes that come from HBM: those that few token tiles share.
+// With slabs: the k-steps of one, and the second launch, which reads what the first has written.
+// The constants are a fit to 195 shapes of 40 to 6000 tokens on weights from HBM (768 to 36864 on either side), each on
+// all tiles and up to 14 slabs: the form chosen takes 0.5 % longer than the best one over all of them, more than 10 % in 4.
+static double product_us(int64_t n, int64_t m, int64_t K, int bm, int bn, int64_t slabs) {
+    const int64_t tiles_n = (n + bn - 1) / bn, tiles = ((m + bm - 1) / bm) * tiles_n * slabs, rounds = (tiles + RESIDENT - 1) / RESIDENT;
+    const double busy = (double)tiles / (double)(rounds * RESIDENT), idle = 1.0 - 0.2 * (1.0 - busy);
+    const double ksteps = slabs > 1 ? (double)slab_steps_of(K, (int)slabs) : (double)K / 64.0;
+    if (bm == 64)                                             // (half of the last pair's loads go by where K % 128 is not 0)
+        return (double)rounds * (3.0 + ksteps * 0.248 * (1.0 + 0.25 / (double)tiles_n) * idle * (K % 128 ? 1.12 : 1.0));
+    const double weight = 72.0 * bm, step = (weight * (1.0 + 0.54 / (double)tiles_n) + 128.0 * bn) / 53e3 * idle;
+    double us = (double)rounds * (3.3 + ksteps * (step - (ring_tile(bm, bn) && bm * bn != 192 * 96 ? 0.057 : 0.0)));
+    const double stream = 3.3 + 1.125 * (double)m * (double)K / 6.2e6;      // one pass over the weight
+    if (us < stream) us = stream;
+    return slabs > 1 ? us + 1.7 + 0.12 * (double)slabs + 8.0 * (double)slabs * (double)n * (double)m / 4.84e6 : us;
+}
+
 static double tiles_us(int64_t n, int64_t m, int64_t K) {
     int bm, bn;
     spmm_tile_choice(n, m, K, bm, bn);
-    if (bm == 0 || (bm == 64 && bn == 64)) return 3.0 + 2.05 * (double)K / 512.0;   // the generic kernel's four groups
-    const int64_t t = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
-    return (double)((t + RESIDENT - 1) / RESIDENT) * (3.0 + (double)K / 64.0 * step_us(bm, bn));
-}
-
-// More than 128 tokens where that rule sees no gain: the tile kernels' rounds against one round of slabs, the second launch
-// and the drained chip between the two 7 us, the slabs written and read at 6 TB/s.  Input gradients: 700 tokens, 2112 x
-// 4160 37 -> 26.2 + 4.7 us; 512 tokens, 4096 x 4096 36 -> 22.4 + 6.2; but 2048 tokens, 768 x 3072 30.3 -> 22.1 + 4.4, a
-// microsecond slower in a step, is left alone.
-static int slabs_of_a_partial_round(int64_t n, int64_t m, int64_t K) {
-    const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128), quads = (K + 255) / 256;
-    if (n <= 128 || !tile_kernel_fits(K) || tiles > RESIDENT / 2) return 0;
-    double least = 0.9 * tiles_us(n, m, K);
-    int best = 0;
-    for (int64_t sl = 2; sl <= 16 && sl * 4 <= quads && sl * tiles <= RESIDENT; ++sl) {
-        const double us = 10.0 + (double)((quads + sl - 1) / sl * 4) * step_us(256, 128) + 8.0 * (double)sl * (double)n * (double)m / 6e6;
-        if (us < least) { least = us; best = (int)sl; }
-    }
-    return best;
-}
-
-bool spmm_slabs_optional(int64_t n, int64_t m, int64_t K) { return K % 256 != 0 || slabs_of_a_long_weight(n, m, K) == 0; }
-
-int spmm_slab_count(int64_t n, int64_t m, int64_t K) {
-    const int slabs = slabs_of_a_long_weight(n, m, K);
-    return slabs ? slabs : slabs_of_a_partial_round(n, m, K);
-}
-
-size_t spmm_slab_bytes(int64_t n, int64_t m, int64_t K) {
-    return (size_t)spmm_slab_count(n, m, K) * (size_t)n * (size_t)m * 4;
-}
-
-static int slab_steps_of(int64_t K, int want) {               // k-steps per slab, whole quads
-    const int64_t quads = (K + 255) / 256;
-    return (int)((quads + want - 1) / want) * 4;
+    return product_us(n, m, K, bm ? bm : 64, bn ? bn : 64, 1);
 }
 
 // Split of T = X L into workgroups beside the slabs' tiles: on the compute units that their single round leaves idle, and
-// not longer than a slab (a chunk of 32 rows of L takes a wavefront about as long as a k-step takes a tile).
-bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, XlSplit& x) {
-    const int want = spmm_slab_count(n, m, K);
-    if (want < 1) return false;
-    const int64_t groups = ((m + 255) / 256) * (n <= 64 ? 1 : (n + 127) / 128) * want;
+// not longer than a slab (a chunk of 32 rows of L takes a wavefront about as long as a k-step takes a tile).  The second
+// kernel then adds up the sums of T = X L itself, for every 64 features: two launches fewer, as long as its workgroups
+// together read at most XL_BESIDE_BYTES of them, about 6 TB/s (128 tokens, rank 128: 28 MB at 9216 x 9216, 10 us; but
+// 600 MB at 36864 x 9216 with 16 slabs, 54 us against 15 with T).  With X L in a launch of its own that never pays: 37
+// tokens, 9728 x 17664, rank 32 76.5 us, 67.3 with T; 60 tokens, 20480 x 8192 73.1 / 68.5.
+constexpr int64_t XL_BESIDE_BYTES = (int64_t)40 << 20;
+bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& split, XlSplit& x) {
+    const int64_t groups = ((m + split.bm - 1) / split.bm) * ((n + split.bn - 1) / split.bn) * split.slabs;
     const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ);
     if (groups + tiles > RESIDENT) return false;
+    const int64_t slab_read = (m + 63) / 64 * ((n + 31) / 32 * 32) * r * 4;
+    int64_t max_floats = XL_BESIDE_BYTES / slab_read * n * r;
+    if (max_floats > (int64_t)(xl_small_scratch_bytes(n, K, r) / 4)) max_floats = (int64_t)(xl_small_scratch_bytes(n, K, r) / 4);
+    if (max_floats <= 0) return false;
     // the fewest slabs that take half as long as the product: the kernel after it reads them all for every 64 features
-    const int most = slab_steps_of(K, want) / 2;
+    const int most = slab_steps_of(K, split.slabs) / 2;
     for (int64_t held = n * r; held <= max_floats; held += n * r) {
         x = xl_split(n, K, r, held, RESIDENT - groups);
         if (x.steps <= most) return true;
@@ -1042,16 +1248,67 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_float
     return x.slabs > 0 && x.steps <= 2 * most;
 }
 
+// Split of the product over k, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split whose launch
+// has room for X L beside its tiles saves the launches of X L (about 8 us against 3 for the larger second kernel).
+SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r) {
+    SpmmSplit best = {0, 0, 0};
+    if (n <= STREAM_MAX_TOKENS || !tile_kernel_fits(K)) return best;
+    const bool xl = r > 0 && n <= XL_SMALL_MAX_TOKENS;
+    double least = 1e300;
+    auto consider = [&](int bm, int bn, int64_t slabs) {
+        const SpmmSplit c = {bm, bn, (int)slabs};
+        if ((K / 64 + slab_steps_of(K, c.slabs) - 1) / slab_steps_of(K, c.slabs) != slabs) return;   // the last would be empty
+        double us = product_us(n, m, K, bm, bn, slabs);
+        XlSplit x;
+        if (xl) us += slab_xl_split(n, m, K, r, c, x) ? 3.0 : 8.0;
+        if (us < least) { least = us; best = c; }
+    };
+    const int64_t quads = (K + 255) / 256, most = quads / 2 < 16 ? quads / 2 : 16;     // two quads of k-steps per slab at least
+    // A long weight: 256 rows, which ask least often for the tokens, in any number of rounds
+    const bool long_weight = slabs_of_a_long_weight(n, m, K) > 0;
+    if (long_weight && K >= 7168) {
+        for (int64_t sl = 2; sl <= most; ++sl) {
+            consider(256, n <= 64 ? 64 : 128, sl);
+        }
+        return best;
+    }
+    for (int64_t sl = 2; sl <= most; ++sl) {
+        auto one_round = [&](int bm, int bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn) * sl <= RESIDENT; };
+        if (one_round(128, 64)) consider(128, 64, sl);
+        if (one_round(192, 64)) consider(192, 64, sl);
+        if (one_round(128, 128)) consider(128, 128, sl);
+        if (n > 128 && (long_weight || one_round(256, 128))) consider(256, 128, sl);
+    }
+    int bm, bn;
+    spmm_tile_choice(n, m, K, bm, bn);
+    // Whole 128 x 64 tiles of 64 k-steps and more are estimated too well, slabs of 129 to 1024 tokens too badly by as much:
+    // 700 tokens, 2112 x 4160 22.3 us whole, 22.7 in two slabs; 300, 4096 x 4096 19.6 / 19.7; 512, 2112 x 4160 21.9 / 20.8;
+    // 512, 4096 x 4096, which fills every compute unit, 21.1 / 24.3
+    const bool close = bm == 128 && bn == 64 && K >= 4096 && n > 128 && n <= 1024;
+    return least < (close ? 1.25 : 1.0) * (tiles_us(n, m, K) + (xl ? 8.0 : 0.0)) ? best : SpmmSplit{0, 0, 0};
+}
+
+// The split of a long weight on tiles of 256 rows by the estimate of slabs_of_a_long_weight alone
+SpmmSplit spmm_long_split(int64_t n, int64_t m, int64_t K) {
+    const int slabs = slabs_of_a_long_weight(n, m, K);
+    return slabs > 0 ? SpmmSplit{256, n <= 64 ? 64 : 128, slabs} : SpmmSplit{0, 0, 0};
+}
+
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
-                             int64_t K, const SlabAdapter& ad, bf16_t* C, float* slabs, hipStream_t s) {
-    const int want = spmm_slab_count(n, m, K);
-    const int slab_steps = slab_steps_of(K, want);
-    const int nslabs = (int)((K / 64 + slab_steps - 1) / slab_steps);       // <= want
+                             int64_t K, const SlabAdapter& ad, const SpmmSplit& split, bf16_t* C, float* slabs, hipStream_t s) {
+    const int slab_steps = slab_steps_of(K, split.slabs);
+    const int nslabs = (int)((K / 64 + slab_steps - 1) / slab_steps);       // <= split.slabs
     const SplitJob job = {nslabs, slab_steps, slabs, ad.T ? nullptr : ad.L, ad.Q, (int)ad.r, ad.x.k_per, ad.x.slabs};
     const bf16_t* A2 = ad.T ? ad.R : nullptr;                 // as stored, k-major
     const int64_t K2 = ad.T ? -ad.r : 0;
-    hipError_t e = n <= 64 ? launch_slab_tiles<64>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, s, job)
-                           : launch_slab_tiles<128>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, s, job);
+    hipError_t e;
+    switch (split.bm * 1000 + split.bn) {
+        case 128064: e = launch_ring<128, 64, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 192064: e = launch_ring<192, 64, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 256064: e = launch_ring<256, 64, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 128128: e = launch_ring<128, 128, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        default: e = launch_tile<256, 128, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+    }
     if (e != hipSuccess) return e;
     if (ad.r && !ad.T) return launch_adapter_finish(slabs, nslabs, n, m, ad.Q, ad.x.slabs, ad.R, ad.r, C, s);
     const size_t count4 = (size_t)n * (size_t)m / 4;
@@ -1066,29 +1323,21 @@ int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RE
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 0;
     if (!tile_kernel_fits(K)) return;
-    if (one_round_of_64(n, m)) {                              // whole pairs of k-steps count as a tile shape of their own
+    const bool one_round = one_round_of_64(n, m);
+    // Up to 64 tokens on more weight rows than a round of 64 x 64 tiles, short contractions: those tiles, several to a compute unit
+    if (n <= 64 && !one_round && K <= 1088) {
+        bm = (m + 127) / 128 >= 200 ? 128 : 64;
+        bn = 64;
+        return;
+    }
+    double least = 1e300;
+    if (one_round) {                                          // whole pairs of k-steps count as a tile shape of their own
+        least = product_us(n, m, K, 64, 64, 1);
         if (K % 128 == 0) bm = bn = 64;
-        return;
     }
-    // Few tokens (inference): the product is a single pass over the packed weight, bound by HBM.
-    // Narrow token tiles, and weight tiles small enough that every compute unit streams its share (weights from HBM, us,
-    // 64 x 64 / 128 x 64 tiles: 33 tokens, 20480 x 1024 12.0 / 12.9, 20480 x 13056 105 / 115; 64 tokens, 20480 x 5120
-    // 52.7 / 50.6, 18432 x 9216 83.4 / 84.0).
-    if (n <= 128) {
-        const bool many = (m + 127) / 128 >= 200;
-        bm = many ? 128 : 64;
-        bn = n <= 64 ? 64 : 128;
-        return;
-    }
-    // The tile kernels run at the rate their compute units pull operands from L2, so a launch costs
-    // about (rounds of 256 resident tiles) x (operand bytes per tile and k-step: 72 per weight row,
-    // 128 per token row).  Take the tile shape for which that is least; ties go to the larger tile.
-    const int bms[6] = {256, 192, 256, 128, 128, 64}, bns[6] = {256, 256, 128, 128, 64, 128};
-    int64_t best_cost = INT64_MAX;
-    for (int c = 0; c < 6; ++c) {
-        int64_t tiles = ((m + bms[c] - 1) / bms[c]) * ((n + bns[c] - 1) / bns[c]);
-        int64_t cost = ((tiles + RESIDENT - 1) / RESIDENT) * (72 * bms[c] + 128 * bns[c]);
-        if (cost < best_cost) { best_cost = cost; bm = bms[c]; bn = bns[c]; }
+    for (const SpmmTile& t : SPMM_TILES) {
+        const double us = product_us(n, m, K, t.bm, t.bn, 1);
+        if (us < least) { least = us; bm = t.bm; bn = t.bn; }
     }
 }
 
@@ -1102,7 +1351,7 @@ int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K) {
     for (int64_t edge = 256; edge >= 128; edge /= 2) {
         const int64_t rest = n % edge;
         if (rest == 0 || rest > STREAM_MAX_TOKENS || rest == n) continue;
-        const double us = tiles_us(n - rest, m, K) + 1.125 * (double)m * (double)K / 5e6 + 8.0;
+        const double us = tiles_us(n - rest, m, K) + 1.125 * (double)m * (double)K / 5e6 + 6.0;
         if (us < 0.95 * least) { least = us / 0.95; best = rest; }
     }
     return best;
@@ -1117,14 +1366,19 @@ static hipError_t launch_tiles(const bf16_t* B, int64_t n, const bf16_t* A_vals,
     }
     switch (bm * 1000 + bn) {
         case 256256: return launch_split(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 256192: return launch_tile<256, 192>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 192256: return launch_tile<192, 256>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 192192: return launch_tile<192, 192>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 256128: return launch_tile<256, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
-        case 128128: return launch_tile<128, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
-        case 128064: return launch_tile<128, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
-        case 64064:                                           // in two rounds the ring again (64 tokens, 20480 x 5120: 42.2 -> 34.9 us)
+        case 192128: return launch_tile<192, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 128128: return launch_ring<128, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 192096: return launch_ring<192, 96>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 192064: return launch_ring<192, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 128096: return launch_ring<128, 96>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        case 128064: return launch_ring<128, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        default:                                              // 64 x 64
             return one_round_of_64(n, m) ? launch_generic_as<2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s)
                                          : launch_tile<64, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
-        default: return launch_tile<64, 128>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     }
 }
 
