@@ -100,7 +100,6 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     constexpr int WM = MF * 16;
     constexpr int CP = BMT + 16;                              // bytes per staged row of pairs: 16 rows x 4 lanes x 4 B
                                                               // of one store fall on 64 different banks
-    constexpr int LPR = BMT / 8;                              // 8-byte pieces per row
     const size_t mpitch = (size_t)m / 8, gpitch = (size_t)m / 2;
     __syncthreads();                                          // every wavefront is done with the rings
 #pragma unroll
@@ -128,19 +127,19 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     __syncthreads();
     // 16-byte pieces (four pairs = sixteen columns of W), all read from LDS before the first is stored; the layers
     // that come here have d_in % 32 == 0, so a piece is inside the row or outside as a whole
-    constexpr int PPR = BMT / 16, PER_THREAD = BNT * PPR / TN_THREADS;
-    static_assert(BNT * PPR % TN_THREADS == 0 && LPR == 2 * PPR, "whole pieces per thread");
+    constexpr int PPR = BMT / 16, PIECES = BNT * PPR, PER_THREAD = (PIECES + TN_THREADS - 1) / TN_THREADS;
+    constexpr bool EVEN = PIECES % TN_THREADS == 0;           // else the last round of pieces is for the first threads only
     u32x4 piece[PER_THREAD];
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
         const int idx = (int)threadIdx.x + u * TN_THREADS;
-        piece[u] = *(const u32x4*)(smem + (idx / PPR) * CP + (idx % PPR) * 16);
+        if (EVEN || idx < PIECES) piece[u] = *(const u32x4*)(smem + (idx / PPR) * CP + (idx % PPR) * 16);
     }
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
         const int idx = (int)threadIdx.x + u * TN_THREADS;
         const int o = tile_o0 + idx / PPR, col = tile_c0 + (idx % PPR) * 16;
-        if (o < n && col < m) *(u32x4*)(out + (size_t)o * gpitch + (col >> 1)) = piece[u];
+        if ((EVEN || idx < PIECES) && o < n && col < m) *(u32x4*)(out + (size_t)o * gpitch + (col >> 1)) = piece[u];
     }
 }
 
@@ -688,32 +687,64 @@ hipError_t launch_transpose(const bf16_t* in, int64_t rows, int64_t cols, bf16_t
 // keep those dwords aligned.  Other layers take the in-place kernel.
 bool wgrad_tn_fits(int64_t d_in) { return d_in % 32 == 0; }
 
-// Tile shape of the weight gradient: 0 = 256 x 256 (split rings), 1 = 256 x 128, 2 = 128 x 128, 3 = 128 x 64.
-// The kernels run at the rate their compute units pull operands from L2: a launch costs about (rounds of
-// 256 resident tiles) x (rows per tile).  Take the cheapest shape, the larger on ties.  With scratch memory
-// the 256 x 256 kernel cuts the tiles left over after its last full round along the tokens
-// (launch_dense_tn_split).
-static int wgrad_tile_choice(int64_t d_in, int64_t d_out, int64_t ksteps, bool with_tail) {
-    const int bms[4] = {256, 256, 128, 128}, bns[4] = {256, 128, 128, 64};
+// Tiles (m x n) of the dense products, the weight gradient's and those of masked dense weights; of two that take as long the
+// first.  [0] is the kernel with split rings, which with scratch memory cuts the tiles left over after its last full
+// round along the tokens (launch_dense_tn_split).
+struct DenseTile { int bm, bn; };
+constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 128}, {192, 128}, {128, 128}, {64, 128}, {64, 64}};
+
+// The kernels run at the rate their compute units pull operands from L2, 53 bytes per ns (up to a fifth more with few of them
+// at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
+// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  Take the shape with the least
+// estimate: over 290 shapes (512 to 22000 on either side, 256 to 16000 along the contraction, operands from HBM and
+// from the caches), each on eleven tiles, it takes 0.3 % longer than the best one in the mean, 7 % at most; the rule before,
+// of 256 x 256, 256 x 128, 128 x 128 and 128 x 64 the one with the fewest rounds x rows, 5.8 to 7.7 % (gradients, us: 700
+// tokens, 4160 x 2112 20.4 -> 16.6 on 192 x 192; 752 tokens, 5120 x 6464 66.5 -> 63.9 on 256 x 192; 4096 tokens, 1024 x
+// 1024 25 -> 20 on 64 x 64).
+static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tail) {
     int best = 0;
-    int64_t best_cost = INT64_MAX;
-    for (int c = 0; c < 4; ++c) {
-        const int64_t tm = (d_in + bms[c] - 1) / bms[c], tn = (d_out + bns[c] - 1) / bns[c], tiles = tm * tn;
-        int64_t cost = ((tiles + RESIDENT - 1) / RESIDENT) * (bms[c] + bns[c]) * 100;
+    double least = 1e300;
+    for (int c = 0; c < (int)(sizeof(DENSE_TILES) / sizeof(DENSE_TILES[0])); ++c) {
+        const int bm = DENSE_TILES[c].bm, bn = DENSE_TILES[c].bn;
+        const int64_t tm = (m + bm - 1) / bm, tn = (n + bn - 1) / bn, tiles = tm * tn, rounds = (tiles + RESIDENT - 1) / RESIDENT;
+        const double step = 128.0 * (double)(bm + bn) / 53e3 * (bn != 192 ? 1.0 : bm == 256 ? 1.15 : 1.04), start = 3.0 + 6.0 * (double)(bm * bn) / 65536.0;
+        const double busy = (double)tiles / (double)(rounds * RESIDENT);
+        double us = (double)rounds * (start + (double)ksteps * step * (1.0 - 0.22 * (1.0 - busy)));
         if (c == 0 && with_tail) {
             const TailPlan p = tail_plan(tm, tn, ksteps);
-            if (p.tiles) cost = (tiles / RESIDENT) * 512 * 100 + (int64_t)(512.0 * 100.0 * p.steps / (double)(ksteps + 6));
+            if (p.tiles) us = (double)(tiles / RESIDENT) * (start + (double)ksteps * step) + 1.3 * p.steps + 16.0;
         }
-        if (cost < best_cost) { best_cost = cost; best = c; }
+        if (us < least) { least = us; best = c; }
     }
     return best;
 }
 
-// scratch bytes of launch_wgrad_masked_t's tail pass (0: the shape has none)
+template <int EPI>
+static hipError_t launch_dense_tile(int tile, const bf16_t* A, int64_t m, const bf16_t* B, int64_t n, int64_t kp, int64_t ld,
+                                    const uint8_t* meta, bf16_t* out, hipStream_t s, float* tail = nullptr) {
+    switch (tile) {
+        case 0: return launch_dense_tn_split<EPI>(A, m, B, n, kp, ld, meta, out, s, tail);
+        case 1: return launch_dense_tn<256, 192, EPI, 2>(A, m, B, n, kp, ld, meta, out, s);
+        case 2: return launch_dense_tn<192, 192, EPI, 3>(A, m, B, n, kp, ld, meta, out, s);
+        case 3: return launch_dense_tn<256, 128, EPI, 3>(A, m, B, n, kp, ld, meta, out, s);
+        case 4: return launch_dense_tn<192, 128, EPI, 4>(A, m, B, n, kp, ld, meta, out, s);
+        case 5: return launch_dense_tn<128, 128, EPI, 4>(A, m, B, n, kp, ld, meta, out, s);
+        case 6: return launch_dense_tn<64, 128, EPI, 6>(A, m, B, n, kp, ld, meta, out, s);
+        default: return launch_dense_tn<64, 64, EPI, 8>(A, m, B, n, kp, ld, meta, out, s);
+    }
+}
+
+// Scratch bytes of launch_wgrad_masked_t's tail pass (0: none).  They are counted wherever a rule of fewest rounds x rows among
+// four of the tiles would cut, also where the estimate above now takes whole tiles of another shape (5120 x 4096, 1153
+// tokens: 73.9 us cut, 56.5 on 192 x 256): buffers of the size this has always named stay large enough.
 size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     const int64_t ksteps = (b + 63) / 64;
-    if (wgrad_tile_choice(d_in, d_out, ksteps, true) != 0) return 0;
     const TailPlan p = tail_plan((d_in + 255) / 256, (d_out + 255) / 256, ksteps);
+    if (!p.tiles) return 0;
+    auto rows = [&](int64_t bm, int64_t bn) { return (((d_in + bm - 1) / bm) * ((d_out + bn - 1) / bn) + RESIDENT - 1) / RESIDENT * (bm + bn) * 100; };
+    const int64_t whole = ((d_in + 255) / 256) * ((d_out + 255) / 256) / RESIDENT * 512 * 100;
+    const int64_t cut = whole + (int64_t)(512.0 * 100.0 * p.steps / (double)(ksteps + 6));
+    if (cut > rows(256, 128) || cut > rows(128, 128) || cut > rows(128, 64)) return 0;
     return (size_t)p.parts * (size_t)p.bundle * (256 * 256 * 4);
 }
 
@@ -722,12 +753,8 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
 hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b, const uint8_t* meta, int64_t d_out,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s) {
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
-    const int best = wgrad_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
-    if (best == 0)
-        return launch_dense_tn_split<EPI_MASKED_PACKED>(Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s, tail_or_null);
-    if (best == 1) return launch_dense_tn<256, 128, EPI_MASKED_PACKED, 3>(Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s);
-    if (best == 2) return launch_dense_tn<128, 128, EPI_MASKED_PACKED, 4>(Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s);
-    return launch_dense_tn<128, 64, EPI_MASKED_PACKED, 6>(Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s);
+    const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
+    return launch_dense_tile<EPI_MASKED_PACKED>(tile, Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s, tail_or_null);
 }
 
 // C[n, m] = B[n, K] * A[m, K]^T for the skinny products of the adapters (T = X L, dY R^T, and over the tokens dL and
@@ -804,24 +831,10 @@ hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, in
     }
 }
 
-// The same product for any shape (dense weights with a general N:M mask, where no sparse MFMA
-// applies): tile by the rounds x operand-rows estimate of the other tile kernels.
+// The same product for any shape (dense weights with a general N:M mask, where no sparse MFMA applies)
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s) {
-    const int bms[4] = {256, 256, 128, 128}, bns[4] = {256, 128, 128, 64};
-    int best = 0;
-    int64_t best_cost = INT64_MAX;
-    for (int c = 0; c < 4; ++c) {
-        int64_t tiles = ((m + bms[c] - 1) / bms[c]) * ((n + bns[c] - 1) / bns[c]);
-        int64_t cost = ((tiles + RESIDENT - 1) / RESIDENT) * (bms[c] + bns[c]);
-        if (cost < best_cost) { best_cost = cost; best = c; }
-    }
-    switch (best) {
-        case 0: return launch_dense_tn_split<EPI_PLAIN>(A, m, B, n, K, K, nullptr, C, s);
-        case 1: return launch_dense_tn<256, 128, EPI_PLAIN, 3>(A, m, B, n, K, K, nullptr, C, s);
-        case 2: return launch_dense_tn<128, 128, EPI_PLAIN, 4>(A, m, B, n, K, K, nullptr, C, s);
-        default: return launch_dense_tn<128, 64, EPI_PLAIN, 6>(A, m, B, n, K, K, nullptr, C, s);
-    }
+    return launch_dense_tile<EPI_PLAIN>(dense_tile_choice(m, n, K / 64, false), A, m, B, n, K, K, nullptr, C, s);
 }
 
 // ------------------------------------------------------------------------------------------

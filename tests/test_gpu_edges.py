@@ -294,3 +294,24 @@ def test_tiles_and_slabs_of_the_sparse_product(b, d_out, d_in, r, form):
     plan = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
     assert (plan["product"], plan["rows"], plan["tokens"]) == form
     check_layer(b, d_out, d_in, r, backward=False)
+
+
+# the weight gradient and the dense products on each of their tiles, rows that fill none of them: two k-steps, and more than
+# a ring holds
+@pytest.mark.parametrize("b,d_out,d_in", [(70, 888, 96), (69, 232, 4128), (67, 2680, 800), (72, 4920, 800), (68, 1416, 2848), (65, 5480, 1440),
+                                          (67, 2696, 4000), (68, 1800, 3424), (75, 2680, 3488), (70, 5160, 2336), (700, 4160, 2112),
+                                          (1100, 4360, 4320), (2900, 1032, 1056)])
+def test_weight_gradient_on_every_tile(b, d_out, d_in):
+    print(f"wgrad b={b} d_out={d_out} d_in={d_in}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + b + d_out)
+    X, W, dY = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16) for shape in ((b, d_in), (d_out, d_in), (b, d_out)))
+    _, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    want = (dY.float().t() @ X.float())[unpack_bits(mask)].reshape(d_out, d_in // 2)
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
+
+
+@pytest.mark.parametrize("n,m,K", [(77, 796, 128), (4100, 204, 128), (534, 3268, 192), (4646, 792, 128), (1177, 3216, 448), (3686, 2056, 128),
+                                   (1943, 4476, 192), (4826, 1156, 128), (4463, 1928, 320), (2322, 4932, 128)])
+def test_dense_product_on_every_tile(n, m, K):
+    test_dense_product_with_rows_of_any_multiple_of_four(n, m, K)
