@@ -321,7 +321,7 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  *       one round, on tiles of less than 256 rows
  *   [1], [2] weight rows and tokens per workgroup (of the tile kernel)
  *   [3] slabs or slices (1 = no split); for [0] == 5 the tokens of the small-batch kernel
- *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens; beside a split product or before it),
+ *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens; before the product, beside it or in it),
  *       2 dense tile kernel, 3 dense tile kernel split over d_in, 4 MFMA kernel for ragged extents (d_in % 64 != 0)
  *       and short products
  *   [5] chunks of 64 rows of L per partial sum that the scratch is sized by, for [4] == 1

@@ -80,6 +80,9 @@ size_t spmm_rows_partial_bytes(int64_t n, int64_t m, int64_t K);
 hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                               int64_t K, const bf16_t* T, const bf16_t* R, int64_t K2, bf16_t* C, float* partial_or_null,
                               hipStream_t s);
+bool launch_spmm_stream_adapter(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
+                                const bf16_t* L, const bf16_t* R, int64_t r, bf16_t* C, float* Q, float* P, size_t p_bytes,
+                                bool sliced, hipStream_t s, hipError_t& e);
 // T[n, r] = X[n, K] * Lt[r, K]^T (dense tile kernel) for many tokens, with the k-contiguous copy Lt of L
 hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
                                   bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s);

@@ -22,7 +22,9 @@ constexpr int SK_PA = SK_BJ * 2 + 32, SK_PB = SK_BI * 2 + 32;   // bytes per sta
                                                                 // read fall on distinct banks
 constexpr int SK_STAGE = 32 * (SK_PA + SK_PB);
 constexpr int SK_SUM_PITCH = SK_BJ + 4;                         // floats per token row of a partial tile
-constexpr int SK_LDS = SK_WAVES * (SK_STAGE > SK_BI * SK_SUM_PITCH * 4 ? SK_STAGE : SK_BI * SK_SUM_PITCH * 4);   // bytes of smem
+// bytes of LDS that a tile of WAVES wavefronts takes
+constexpr int skinny_lds(int waves) { return waves * (SK_STAGE > SK_BI * SK_SUM_PITCH * 4 ? SK_STAGE : SK_BI * SK_SUM_PITCH * 4); }
+constexpr int SK_LDS = skinny_lds(SK_WAVES);
 
 template <bool KMAJOR, int F>                                   // F fragments of 16 rows
 struct SkinnyOperand {
@@ -79,12 +81,11 @@ struct SkinnyOperand {
 };
 
 // The tile at rows i0 of B and j0 of A, contraction [k_begin, K) (k_begin a multiple of 32; K bounds the operands too):
-// bf16 into C[n][m], or the fp32 sums into sums[n][m] if that is given.  smem: SK_LDS bytes, 16-byte aligned.  Every thread
-// of a workgroup of SK_WAVES wavefronts must make the call (it contains barriers).
-template <bool BKMAJOR, bool AKMAJOR>
-__device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_t ldb, const bf16_t* __restrict__ A, int64_t lda,
-                                            int n, int m, uint32_t k_begin, uint32_t K, int i0, int j0, bf16_t* __restrict__ C,
-                                            float* __restrict__ sums, uint8_t* smem) {
+// store(i, j, four sums of columns j .. j + 3 of the tile's row i).  smem: skinny_lds(WAVES) bytes, 16-byte aligned.  Every
+// thread of a workgroup of WAVES wavefronts must make the call (it contains barriers).
+template <bool BKMAJOR, bool AKMAJOR, int WAVES, class Store>
+__device__ __forceinline__ void skinny_sums(const bf16_t* __restrict__ B, int64_t ldb, const bf16_t* __restrict__ A, int64_t lda,
+                                            int n, int m, uint32_t k_begin, uint32_t K, int i0, int j0, uint8_t* smem, const Store& store) {
     constexpr int FA = SK_BJ / 16, FB = SK_BI / 16;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const SkinnyOperand<BKMAJOR, FB> ob = {B, ldb, n, K, i0};
@@ -96,7 +97,7 @@ __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_
 #pragma unroll
         for (int j = 0; j < FB; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     u32x4 va[FA], vb[FB];
-    constexpr uint32_t step = 32 * SK_WAVES;                    // K < 2^31: a look-ahead past it does not wrap in 32 bits
+    constexpr uint32_t step = 32 * WAVES;                       // K < 2^31: a look-ahead past it does not wrap in 32 bits
     static_assert(0x7FFFFFFFu + 2 * step + 32 > 0x7FFFFFFFu, "k0 + step and the chunk after it");
     oa.load(k_begin + wave * 32, lane, va);
     ob.load(k_begin + wave * 32, lane, vb);
@@ -126,14 +127,26 @@ __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_
         for (int j = 0; j < FB; ++j)
             *(f32x4*)(part + (wave * SK_BI + 16 * j + l16) * SK_SUM_PITCH + 16 * i + 4 * lq) = acc[i][j];
     __syncthreads();
-    const int row = t / (SK_BJ / 4), col = (t % (SK_BJ / 4)) * 4;   // 512 threads: 32 rows x 16 groups of four
-    f32x4 v = *(const f32x4*)(part + row * SK_SUM_PITCH + col);
 #pragma unroll
-    for (int w = 1; w < SK_WAVES; ++w) {
-        const f32x4 x = *(const f32x4*)(part + (w * SK_BI + row) * SK_SUM_PITCH + col);
-        v[0] += x[0]; v[1] += x[1]; v[2] += x[2]; v[3] += x[3];
+    for (int idx = t; idx < SK_BI * SK_BJ / 4; idx += WAVES * 64) {  // 32 rows x 16 groups of four
+        const int row = idx / (SK_BJ / 4), col = (idx % (SK_BJ / 4)) * 4;
+        f32x4 v = *(const f32x4*)(part + row * SK_SUM_PITCH + col);
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const f32x4 x = *(const f32x4*)(part + (w * SK_BI + row) * SK_SUM_PITCH + col);
+            v[0] += x[0]; v[1] += x[1]; v[2] += x[2]; v[3] += x[3];
+        }
+        store(row, col, v);
     }
-    if (i0 + row < n && j0 + col < m) {                         // m % 8 == 0
+}
+
+// The same with the results in memory: bf16 in C[n][m], or the fp32 sums in sums[n][m] if that is given (m % 8 == 0).
+template <bool BKMAJOR, bool AKMAJOR, int WAVES = SK_WAVES>
+__device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_t ldb, const bf16_t* __restrict__ A, int64_t lda,
+                                            int n, int m, uint32_t k_begin, uint32_t K, int i0, int j0, bf16_t* __restrict__ C,
+                                            float* __restrict__ sums, uint8_t* smem) {
+    skinny_sums<BKMAJOR, AKMAJOR, WAVES>(B, ldb, A, lda, n, m, k_begin, K, i0, j0, smem, [&](int row, int col, const f32x4& v) {
+        if (i0 + row >= n || j0 + col >= m) return;
         if (sums) {
             *(f32x4*)(sums + (int64_t)(i0 + row) * m + j0 + col) = v;
             return;
@@ -142,7 +155,7 @@ __device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ B, int64_
 #pragma unroll
         for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)v[e];
         *(u32x2*)(C + (int64_t)(i0 + row) * m + j0 + col) = o.u;
-    }
+    });
 }
 
 }  // namespace

@@ -226,6 +226,14 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
     if (split.slabs && (!adapter || (b <= XL_SMALL_MAX_TOKENS && slab_xl_split(b, d_out, d_in, r, split, ad.x))))
         return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, split, (bf16_t*)Y, (float*)after, s));
+    float* const slices = few && workspace && spmm_rows_partial_bytes(b, d_out, d_in) ? (float*)after : nullptr;
+    if (few && adapter) {
+        // X L beside the one pass over the weight, or inside it (T and Lt are not needed then: their room holds the sums)
+        hipError_t e;
+        if (launch_spmm_stream_adapter(x_in, b, wv, wm, d_out, d_in, l, R, r, (bf16_t*)Y, sums, (float*)ws,
+                                       (size_t)((uint8_t*)sums - ws), slices != nullptr, s, e))
+            return finish(e);
+    }
     if (adapter) {                                            // T = X L, rounded to bf16
         hipError_t e;
         if (d_in % 64 == 0 && b <= XL_SMALL_MAX_TOKENS) {
@@ -240,10 +248,8 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     } else {
         T = nullptr;
     }
-    if (few) {                                                // inference-size batch: one HBM-bound pass over the packed weight
-        float* slices = workspace && spmm_rows_partial_bytes(b, d_out, d_in) ? (float*)after : nullptr;
+    if (few)                                                  // inference-size batch: one HBM-bound pass over the packed weight
         return finish(launch_spmm_stream(x_in, b, wv, wm, d_out, d_in, T, R, r, (bf16_t*)Y, slices, s));
-    }
     if (split.slabs) {
         ad.T = T;
         return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, split, (bf16_t*)Y, (float*)after, s));

@@ -18,6 +18,26 @@
 
 namespace {
 
+// How a launch of spmm_stream_lds_kernel comes by the adapter term, where T = X L is not given:
+//   groups > 0: its first workgroups compute sums of X L into Q (`slabs` slabs of k_per rows of L), the others leave fp32 sums
+//               of the product in P, and adapter_finish_kernel adds both (xl_beside);
+//   L, groups == 0: every workgroup computes T for itself, at the end (xl_by_itself).
+struct StreamXl {
+    const bf16_t* L;
+    float *Q, *P;
+    int r, groups, slabs, k_per;
+};
+
+// workgroup w of the first kind
+template <int WAVES>
+__device__ __forceinline__ void stream_xl_part(const StreamXl& xl, int w, const bf16_t* __restrict__ X, int n, int d_in, uint8_t* smem) {
+    const int tiles = (xl.r + SK_BJ - 1) / SK_BJ, part = w / tiles;       // n <= 32: one tile of tokens
+    if (part >= xl.slabs) return;
+    const uint32_t k0 = part * (uint32_t)xl.k_per;
+    skinny_tile<false, true, WAVES>(X, d_in, xl.L, xl.r, n, xl.r, k0, min((uint32_t)d_in, k0 + xl.k_per), 0, w % tiles * SK_BJ, nullptr,
+                                    xl.Q + (size_t)part * n * xl.r, smem);
+}
+
 union StB { u32x4 u[2]; bf16x16 v; };
 union StA { u32x4 u; bf16x8 v; };
 
@@ -37,21 +57,31 @@ struct StreamLds {
     static constexpr int TOTAL = RING + WAVES * BM * PART_PITCH * 4;
 };
 
-template <int MF, int WAVES, int NF>
+// XL: X L in the same launch (StreamXl); else T is given and xl is not looked at
+template <int MF, int WAVES, int NF, bool XL>
 __global__ void __launch_bounds__(WAVES * 64) spmm_stream_lds_kernel(const bf16_t* __restrict__ B, int n,
                                                                    const bf16_t* __restrict__ Av,
                                                                    const uint8_t* __restrict__ Am, int m, int K,
                                                                    const bf16_t* __restrict__ T,
                                                                    const bf16_t* __restrict__ R, int K2,
-                                                                   bf16_t* __restrict__ C) {
+                                                                   bf16_t* __restrict__ C, StreamXl xl) {
     using S = StreamLds<MF, WAVES, NF>;
     extern __shared__ __align__(16) uint8_t smem[];
+    static_assert(skinny_lds(WAVES) <= S::RING, "a part of X L fits");
+    int block = (int)blockIdx.x;
+    if constexpr (XL) {
+        if (block < xl.groups) {
+            stream_xl_part<WAVES>(xl, block, B, n, K, smem);
+            return;
+        }
+        block -= xl.groups;
+    }
     float* part = (float*)(smem + S::RING);                   // [wave][row][PART_PITCH]
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
-    const int m0 = blockIdx.x * S::BM;
+    const int m0 = block * S::BM;
     const int ksteps = K / 64, kpairs = (ksteps + 1) / 2;
     const bool odd_tail = (ksteps & 1) != 0;                 // the last pair has one step only
     uint8_t* const ring = smem + wave * 2 * S::STAGE;
@@ -130,7 +160,7 @@ __global__ void __launch_bounds__(WAVES * 64) spmm_stream_lds_kernel(const bf16_
     };
 
     // workgroups start at different places of the k range and wrap around
-    const int rot = (int)((blockIdx.x * 37u) % (unsigned)kpairs);
+    const int rot = (int)((block * 37u) % (unsigned)kpairs);
     auto pair_of = [&](int q) {                               // q-th pair of this workgroup; late ones clamped
         if (q >= kpairs) return kpairs - 1;
         int p = q + rot;
@@ -175,19 +205,33 @@ __global__ void __launch_bounds__(WAVES * 64) spmm_stream_lds_kernel(const bf16_
         constexpr int TP = 128 * 2 + 16, RP = 160;            // bytes per staged row of T and of R's tile
         constexpr int FR = (MF * NF + WAVES - 1) / WAVES;     // fragments per wavefront
         constexpr int SEG = S::BM / 8;                        // 16-byte segments per row of R's tile
-        static_assert(16 * NF * TP + 128 * RP <= S::RING, "adapter operands fit in the ring");
+        static_assert(16 * NF * TP + 128 * RP + skinny_lds(WAVES) <= S::RING, "adapter operands and a part of X L fit in the ring");
         uint8_t* const t_lds = smem;                          // [16 NF tokens][TP]
         uint8_t* const r_lds = smem + 16 * NF * TP;           // [128 k][RP]
+        uint8_t* const x_lds = r_lds + 128 * RP;
         f32x4 low[FR];
 #pragma unroll
         for (int q = 0; q < FR; ++q) low[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
         for (int kc = 0; kc < K2; kc += 128) {
             const int kn = K2 - kc < 128 ? K2 - kc : 128;     // a multiple of 32
-            for (int idx = t; idx < 16 * NF * 16; idx += WAVES * 64) {
-                int tok = idx >> 4, pc = idx & 15;
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (tok < n && pc * 8 < kn) v = *(const u32x4*)(T + (size_t)tok * K2 + kc + pc * 8);
-                *(u32x4*)(t_lds + tok * TP + pc * 16) = v;
+            if constexpr (XL) {                               // T from X and L as stored, into the same place
+                for (int c = 0; c < kn; c += SK_BJ) {         // tokens from n on are zeros: X is not read there
+                    skinny_sums<false, true, WAVES>(B, K, xl.L, K2, n, K2, 0, (uint32_t)K, 0, kc + c, x_lds, [&](int tok, int col, const f32x4& v) {
+                        if (tok >= 16 * NF) return;
+                        union { __bf16 h[4]; u32x2 u; } o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o.h[e] = (__bf16)v[e];
+                        *(u32x2*)(t_lds + tok * TP + (c + col) * 2) = o.u;
+                    });
+                    __syncthreads();                          // the sums have been read
+                }
+            } else {
+                for (int idx = t; idx < 16 * NF * 16; idx += WAVES * 64) {
+                    int tok = idx >> 4, pc = idx & 15;
+                    u32x4 v = {0u, 0u, 0u, 0u};
+                    if (tok < n && pc * 8 < kn) v = *(const u32x4*)(T + (size_t)tok * K2 + kc + pc * 8);
+                    *(u32x4*)(t_lds + tok * TP + pc * 16) = v;
+                }
             }
             for (int idx = t; idx < 128 * SEG; idx += WAVES * 64) {
                 int k = idx / SEG, sg = idx % SEG;
@@ -238,6 +282,10 @@ __global__ void __launch_bounds__(WAVES * 64) spmm_stream_lds_kernel(const bf16_
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) v += part[(w * S::BM + o) * S::PART_PITCH + tok];
         if (m0 + o < m) {
+            if (XL && xl.P) {
+                xl.P[(size_t)tok * m + m0 + o] = v;
+                continue;
+            }
             union { __bf16 h; bf16_t u; } r;
             r.h = (__bf16)v;
             C[(size_t)tok * m + m0 + o] = r.u;
@@ -247,14 +295,15 @@ __global__ void __launch_bounds__(WAVES * 64) spmm_stream_lds_kernel(const bf16_
 
 template <int MF, int WAVES, int NF>
 hipError_t launch_stream_lds(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                             const bf16_t* T, const bf16_t* R, int64_t K2, bf16_t* C, hipStream_t s) {
+                             const bf16_t* T, const bf16_t* R, int64_t K2, bf16_t* C, const StreamXl& xl, hipStream_t s) {
     using S = StreamLds<MF, WAVES, NF>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
-    auto kern = spmm_stream_lds_kernel<MF, WAVES, NF>;
-    hipError_t e = allow_dynamic_lds<spmm_stream_lds_kernel<MF, WAVES, NF>>(S::TOTAL);
+    auto kern = xl.L ? spmm_stream_lds_kernel<MF, WAVES, NF, true> : spmm_stream_lds_kernel<MF, WAVES, NF, false>;
+    hipError_t e = xl.L ? allow_dynamic_lds<spmm_stream_lds_kernel<MF, WAVES, NF, true>>(S::TOTAL)
+                        : allow_dynamic_lds<spmm_stream_lds_kernel<MF, WAVES, NF, false>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    kern<<<dim3((unsigned)((m + S::BM - 1) / S::BM)), dim3(WAVES * 64), S::TOTAL, s>>>(B, (int)n, Av, Am, (int)m, (int)K,
-                                                                                     T, R, (int)K2, C);
+    kern<<<dim3((unsigned)((m + S::BM - 1) / S::BM + xl.groups)), dim3(WAVES * 64), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, T, R, (int)K2, C, xl);
     return hipGetLastError();
 }
 
@@ -519,7 +568,8 @@ __device__ __forceinline__ u32x4 t_piece(const float* __restrict__ Q, int slabs,
 // a wavefront 16 of the features; chunks of 128 of the rank are staged as in the kernels above.  Bound by its chain of
 // latencies (128 tokens, 9216 x 9216, rank 128, 6 slices: 10.3 us, where the sum alone takes 5.2 and the kernels it saves,
 // X L before the product and its reduction, took 12.7).  The sliced small-batch kernel gains nothing from it (72 + 8.6 us
-// against 72 + 5.3 + 5.2), nor any small-batch kernel from adding up the sums of T itself (65.8 -> 75.9 us for one token).
+// against 72 + 5.3 + 5.2), nor any small-batch kernel from adding up the sums of T itself (65.8 -> 75.9 us for one token).  It is the second
+// kernel of a small-batch product too where X L runs beside that (xl_beside).
 constexpr int AF_TOK = 32, AF_FEAT = 64;
 __global__ void __launch_bounds__(256) adapter_finish_kernel(const float* __restrict__ P, int slices, int n, int m,
                                                              const float* __restrict__ Q, int q_slabs,
@@ -705,23 +755,84 @@ static hipError_t launch_rows(const bf16_t* B, int64_t n, const bf16_t* Av, cons
     return hipGetLastError();
 }
 
+static hipError_t launch_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
+                                const bf16_t* T, const bf16_t* R, int64_t K2, bf16_t* C, float* partial, int slices,
+                                const StreamXl& xl, hipStream_t s) {
+    if (slices > 0)
+        return n <= 16 ? launch_rows<1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, partial, slices, s)
+                       : launch_rows<2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, partial, slices, s);
+    const int rows = spmm_stream_rows(n, m, K);
+    if (n <= 16) {
+        if (rows == 32) return launch_stream_lds<2, 8, 1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, xl, s);
+        if (rows == 48) return launch_stream_lds<3, 6, 1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, xl, s);
+        return launch_stream_lds<4, 4, 1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, xl, s);
+    }
+    if (rows == 48) return launch_stream_lds<3, 4, 2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, xl, s);
+    return launch_stream_lds<2, 4, 2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, xl, s);
+}
+
 // n <= 32, K % 64 == 0, K >= 128; T (bf16[n][K2]) and R (bf16[K2][m]) only when K2 > 0; partial_or_null: scratch of
 // spmm_rows_partial_bytes(n, m, K) bytes
 hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                               int64_t K, const bf16_t* T, const bf16_t* R, int64_t K2, bf16_t* C, float* partial_or_null,
                               hipStream_t s) {
-    const int slices = spmm_rows_slices(n, m, K, partial_or_null != nullptr);
-    if (slices > 0)
-        return n <= 16 ? launch_rows<1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, partial_or_null, slices, s)
-                       : launch_rows<2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, partial_or_null, slices, s);
+    return launch_stream(B, n, A_vals, A_meta, m, K, T, R, K2, C, partial_or_null, spmm_rows_slices(n, m, K, partial_or_null != nullptr),
+                         {}, s);
+}
+
+constexpr int XL_STEPS = 4;                                   // see xl_split
+
+// wavefronts of launch_stream's kernels that split the contraction
+static int stream_waves(int64_t n, int64_t m, int64_t K) {
+    if (n > 16) return 4;
     const int rows = spmm_stream_rows(n, m, K);
-    if (n <= 16) {
-        if (rows == 32) return launch_stream_lds<2, 8, 1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, s);
-        if (rows == 48) return launch_stream_lds<3, 6, 1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, s);
-        return launch_stream_lds<4, 4, 1>(B, n, A_vals, A_meta, m, K, T, R, K2, C, s);
+    return rows == 32 ? 8 : rows == 48 ? 6 : 4;
+}
+
+// Every workgroup computes T by itself while that is one tile of columns and at most six chunks of 32 rows of L for each of
+// its wavefronts, about 1 us each at the end of its own weight rows: one launch instead of two (us, one token: 3072 x 768, rank
+// 32 8.9 -> 7.4; 3328 x 512, rank 32 7.9 -> 6.4; 1216 x 1344, rank 32 10.1 -> 8.7; but with several tiles 12 tokens, 5632 x
+// 512, rank 96 8.4 -> 9.0).
+static bool xl_by_itself(int64_t n, int64_t m, int64_t K, int64_t r) {
+    const int64_t waves = stream_waves(n, m, K);
+    return r <= SK_BJ && (K / 32 + waves - 1) / waves <= 6;
+}
+
+// Beside the product, where X L would otherwise take two launches before it: as few slabs as take half the time of the pass over
+// the weight (1.3 us per chunk of 32 rows and wavefront), if the second kernel gets by with 2 us for them, 0.17 us each and 1 us
+// per 32 KB (us: 1 token, 9216 x 9216, rank 128 29.1 -> 27.2; 8, 4096 x 4096, rank 64 12.8 -> 11.6; 16, 8000 x 8640, rank 64 28.5 ->
+// 25.6; 2, 17152 x 3328, rank 32 25.3 -> 22.3; without that limit 1, 512 x 26624, rank 96 26.8 -> 50.7, 32, 9216 x 9216, rank
+// 64 37.8 -> 39.3).  Not beside the row-split kernel, whose three wavefronts take 3 us and more per chunk while it saturates
+// the memory: 1, 36864 x 9216, rank 128 72.5 -> 85.3.
+static bool xl_beside(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, StreamXl& xl) {
+    const int64_t chunks = K / 32, waves = stream_waves(n, m, K);
+    if ((chunks + SK_WAVES - 1) / SK_WAVES <= XL_STEPS || r > 128) return false;   // one slab, one launch (xl_split)
+    const int64_t half = (int64_t)((1.0 + 1.125 * (double)m * (double)K / 11e6) / 1.3), steps = half > 1 ? half : 1;
+    const int64_t want = (chunks + waves * steps - 1) / (waves * steps), per = (chunks + want - 1) / want;
+    const int64_t slabs = (chunks + per - 1) / per;
+    if (slabs * n * r > max_floats || 0.17 * (double)slabs + (double)(slabs * n * r * 4) / 32e3 > 2.0) return false;
+    xl.slabs = (int)slabs;
+    xl.k_per = (int)(per * 32);
+    xl.groups = (int)(((r + SK_BJ - 1) / SK_BJ) * slabs);
+    return true;
+}
+
+// The product with its adapter, T = X L included: false where this has no form for the shape, nothing launched.  Q:
+// xl_small_scratch_bytes of sums; P: p_bytes of scratch for the sums of the product; sliced: the caller has scratch for slices
+bool launch_spmm_stream_adapter(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
+                                const bf16_t* L, const bf16_t* R, int64_t r, bf16_t* C, float* Q, float* P, size_t p_bytes,
+                                bool sliced, hipStream_t s, hipError_t& e) {
+    if (spmm_rows_slices(n, m, K, sliced) > 0) return false;  // the row-split kernel
+    StreamXl xl = {L, Q, nullptr, (int)r, 0, 0, 0};
+    if (xl_by_itself(n, m, K, r)) {
+        e = launch_stream(B, n, A_vals, A_meta, m, K, nullptr, R, r, C, nullptr, 0, xl, s);
+        return true;
     }
-    if (rows == 48) return launch_stream_lds<3, 4, 2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, s);
-    return launch_stream_lds<2, 4, 2>(B, n, A_vals, A_meta, m, K, T, R, K2, C, s);
+    xl.P = P;
+    if ((size_t)n * (size_t)m * 4 > p_bytes || !xl_beside(n, m, K, r, (int64_t)(xl_small_scratch_bytes(n, K, r) / 4), xl)) return false;
+    e = launch_stream(B, n, A_vals, A_meta, m, K, nullptr, nullptr, 0, nullptr, nullptr, 0, xl, s);
+    if (e == hipSuccess) e = launch_adapter_finish(P, 1, n, m, Q, xl.slabs, R, r, C, s);
+    return true;
 }
 
 // Scratch for the partial sums of T = X L: slabs of up to four chunks of 64 rows of L as long as there are still
@@ -741,7 +852,6 @@ size_t xl_small_scratch_bytes(int64_t n, int64_t d_in, int64_t r) {
 
 // Slabs of T = X L, within max_floats of sums and max_groups workgroups: one, which needs no second kernel, while that
 // leaves a wavefront no more than XL_STEPS chunks of 32 rows of L; else as many as still give every wavefront a chunk.
-constexpr int XL_STEPS = 4;
 XlSplit xl_split(int64_t n, int64_t d_in, int64_t r, int64_t max_floats, int64_t max_groups) {
     const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ), chunks = d_in / 32;
     int64_t slabs = (chunks + SK_WAVES - 1) / SK_WAVES;

@@ -133,6 +133,21 @@ def test_adapter_product_of_few_tokens(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r, backward=False)
 
 
+# X L inside the small-batch kernel (up to six chunks of 32 rows of L per wavefront, eight, six and four of them; one token tile
+# and two) and beside it, an odd number of k-steps, a rank that fills no tile of columns, rows that fill no workgroup
+@pytest.mark.parametrize("b,d_out,d_in,r", [(1, 3072, 768, 32), (16, 1000, 1472, 64), (5, 9224, 1088, 32), (20, 520, 384, 64), (31, 12296, 704, 32),
+                                            (3, 4096, 4096, 64), (1, 9224, 2880, 96), (12, 16392, 2112, 128), (25, 36872, 2176, 32), (2, 17160, 3264, 32)])
+def test_adapter_product_in_and_beside_a_small_batch(b, d_out, d_in, r):
+    check_layer(b, d_out, d_in, r, backward=False)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + d_out)
+    X, W, L, R = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16) for shape in ((b, d_in), (d_out, d_in), (d_in, r), (r, d_out)))
+    vals, meta, _ = sl.slope_prune_rows(W)
+    y = sl.slope_spmm_fwd(X, vals, meta, L, R)
+    assert torch.equal(sl.slope_spmm_fwd(X, vals, meta, L, R), y)          # bit-identical runs
+    assert torch.equal(sl.slope_spmm_fwd_static(X, vals, meta, L, R), y)   # and forms of the call
+
+
 # more than half a round of leftover 256 x 256 tiles: bundles that do not divide them, shares across bundle boundaries,
 # extents that fill no tile
 @pytest.mark.parametrize("b,d_out,d_in", [(8200, 5000, 5088), (12000, 4096, 6176)])
