@@ -8,6 +8,8 @@
 //                (packed, whole lines per 16 lanes), decompresses them in registers, ranks each column's
 //                group of four along d_out among the surviving positions, and the tile is written out
 //                transposed through an LDS stage so that the write is coalesced as well.
+#include <algorithm>
+
 #include "common.h"
 
 // ------------------------------------------------------------------------------------------
@@ -129,7 +131,7 @@ __global__ void __launch_bounds__(DP_THREADS) double_prune_kernel(const bf16_t* 
                                                            bf16_t* __restrict__ valsT, uint8_t* __restrict__ metaT,
                                                            uint8_t* __restrict__ maskrc,
                                                            const uint8_t* __restrict__ metaT_in,
-                                                           bf16_t* __restrict__ vals_copy, int tiles_x, int tiles_y) {
+                                                           bf16_t* __restrict__ vals_copy, int tiles_x, int tiles_y, int high) {
     // the output tile: kept value pairs [i][og] and metadata nibbles [i][og]; given metadata (GIVEN) has its own
     __shared__ __align__(16) uint8_t sbuf[DP_TILE * DP_OPITCH * 4 + DP_TILE * DP_NPITCH];
     __shared__ __align__(4) uint8_t sG[GIVEN ? DP_TILE * DP_NPITCH : 4];
@@ -154,10 +156,10 @@ __global__ void __launch_bounds__(DP_THREADS) double_prune_kernel(const bf16_t* 
     // rows are 1 KB runs of values in both arrays (measured: 171 -> 157 us at 36864 x 9216; 8 x 4 163, 16 x 8 166,
     // 8 x 16 161, 8 x 1 180; chunk after chunk along d_out instead of d_in: 161).
     const uint32_t xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
-    const uint32_t chunk = (slot / (DP_CHUNK * DP_CHUNK)) * 8 + xcd, within = slot % (DP_CHUNK * DP_CHUNK);
+    const uint32_t chunk = (slot >> (3 + high)) * 8 + xcd, within = slot & ((DP_CHUNK << high) - 1);
     const uint32_t chunks_x = ((uint32_t)tiles_x + DP_CHUNK - 1) / DP_CHUNK;
     const int tile_x = (int)((chunk % chunks_x) * DP_CHUNK + within % DP_CHUNK);
-    const int tile_y = (int)((chunk / chunks_x) * DP_CHUNK + within / DP_CHUNK);
+    const int tile_y = (int)(((chunk / chunks_x) << high) + within / DP_CHUNK);
     if (tile_x >= tiles_x || tile_y >= tiles_y) return;         // the whole workgroup: padding of the chunked order
     const int o0 = tile_y * DP_TILE;
     // Bytes per row: packed W^R values d_in, its metadata (and the mask) d_in / 8; transposed values d_out,
@@ -346,31 +348,57 @@ __global__ void __launch_bounds__(DP_THREADS) double_prune_kernel(const bf16_t* 
     }
 }
 
-// Grid of the chunked tile order: whole chunks of 8 x 8 tiles, a multiple of 8 chunks (one per XCD); workgroups
-// whose tile lies outside the matrix leave at once.
-static dim3 double_prune_grid(int64_t tiles_x, int64_t tiles_y) {
-    const int64_t chunks = ((tiles_x + DP_CHUNK - 1) / DP_CHUNK) * ((tiles_y + DP_CHUNK - 1) / DP_CHUNK);
-    return dim3((unsigned)(((chunks + 7) / 8) * 8 * DP_CHUNK * DP_CHUNK));
+// Chunks of 8 x 2^high tiles, 8 x 8 unless lower ones leave the busiest XCD fewer tiles by more than an eighth of that per
+// halving, which is what they cost: lines of the transposed metadata that more XCDs share.  Chunks of 8 x 8 alone kept
+// layers of a few million weights on a few of the XCDs (us, double prune and update: 1000 x 1000 7.0 -> 4.4 and 7.0 -> 4.4,
+// 3072 x 768 5.2 -> 3.9 and 5.5 -> 3.9, 4160 x 2112 7.9 -> 7.3 and 8.9 -> 7.4, 5120 x 5120 13.3 -> 12.5 and 16.7 -> 16.1;
+// without the charge 1536 x 6144, 96 -> 80 tiles in 8 x 2, took 16.0 with the row prune before it, 15.3 in 8 x 8).
+static int double_prune_height(uint32_t tiles_x, uint32_t tiles_y) {
+    const uint32_t chunks_x = (tiles_x + DP_CHUNK - 1) / DP_CHUNK;
+    int best = 3;
+    uint32_t least = ~0u;
+    for (int high = 3; high >= 0; --high) {
+        const uint32_t chunks_y = (tiles_y + (1u << high) - 1) >> high;
+        if ((uint64_t)chunks_x * chunks_y > 64) break;           // an XCD has eight chunks or more: equal enough
+        uint32_t of_xcd[8] = {0, 0, 0, 0, 0, 0, 0, 0}, most = 0, c = 0;
+        for (uint32_t y = 0; y < chunks_y; ++y)
+            for (uint32_t x = 0; x < chunks_x; ++x, ++c) {
+                uint32_t& n = of_xcd[c % 8];
+                n += std::min((uint32_t)DP_CHUNK, tiles_x - x * DP_CHUNK) * std::min(1u << high, tiles_y - (y << high));
+                most = std::max(most, n);
+            }
+        const uint32_t cost = most * (uint32_t)(11 - high);      // 8, 9, 10, 11 eighths
+        if (cost < least) { least = cost; best = high; }
+    }
+    return best;
+}
+
+// Grid of that order: whole chunks, a multiple of 8 of them (one per XCD); workgroups whose tile lies outside the matrix
+// leave at once.
+static dim3 double_prune_grid(int64_t tiles_x, int64_t tiles_y, int high) {
+    const int64_t chunks = ((tiles_x + DP_CHUNK - 1) / DP_CHUNK) * ((tiles_y + (1 << high) - 1) >> high);
+    return dim3((unsigned)((((chunks + 7) / 8) * 8 * DP_CHUNK) << high));
 }
 
 hipError_t launch_double_prune(const bf16_t* vals, const uint8_t* meta, int64_t d_out, int64_t d_in, bf16_t* valsT,
                                uint8_t* metaT, uint8_t* maskrc, hipStream_t s) {
     const int64_t tiles_x = (d_in + DP_TILE - 1) / DP_TILE, tiles_y = (d_out + DP_TILE - 1) / DP_TILE;
-    const dim3 grid = double_prune_grid(tiles_x, tiles_y);
     if (d_in > DP_EXTENT_MAX || d_out > DP_EXTENT_MAX) return hipErrorInvalidValue;
+    const int high = double_prune_height((uint32_t)tiles_x, (uint32_t)tiles_y);
+    const dim3 grid = double_prune_grid(tiles_x, tiles_y, high);
     const bool ragged = d_out % 32 != 0;
     if (ragged && maskrc)
         double_prune_kernel<false, true, true><<<grid, dim3(DP_THREADS), 0, s>>>(vals, meta, (int)d_out, (int)d_in, valsT,
-                                                                          metaT, maskrc, nullptr, nullptr, (int)tiles_x, (int)tiles_y);
+                                                                          metaT, maskrc, nullptr, nullptr, (int)tiles_x, (int)tiles_y, high);
     else if (ragged)
         double_prune_kernel<false, false, true><<<grid, dim3(DP_THREADS), 0, s>>>(vals, meta, (int)d_out, (int)d_in, valsT,
-                                                                           metaT, nullptr, nullptr, nullptr, (int)tiles_x, (int)tiles_y);
+                                                                           metaT, nullptr, nullptr, nullptr, (int)tiles_x, (int)tiles_y, high);
     else if (maskrc)
         double_prune_kernel<false, true, false><<<grid, dim3(DP_THREADS), 0, s>>>(vals, meta, (int)d_out, (int)d_in, valsT,
-                                                                           metaT, maskrc, nullptr, nullptr, (int)tiles_x, (int)tiles_y);
+                                                                           metaT, maskrc, nullptr, nullptr, (int)tiles_x, (int)tiles_y, high);
     else
         double_prune_kernel<false, false, false><<<grid, dim3(DP_THREADS), 0, s>>>(vals, meta, (int)d_out, (int)d_in, valsT,
-                                                                            metaT, nullptr, nullptr, nullptr, (int)tiles_x, (int)tiles_y);
+                                                                            metaT, nullptr, nullptr, nullptr, (int)tiles_x, (int)tiles_y, high);
     return hipGetLastError();
 }
 
@@ -380,14 +408,15 @@ hipError_t launch_double_prune(const bf16_t* vals, const uint8_t* meta, int64_t 
 hipError_t launch_update_transposed(const bf16_t* vals, const uint8_t* meta, int64_t d_out, int64_t d_in, bf16_t* vals_copy,
                                     const uint8_t* metaT, bf16_t* valsT, hipStream_t s) {
     const int64_t tiles_x = (d_in + DP_TILE - 1) / DP_TILE, tiles_y = (d_out + DP_TILE - 1) / DP_TILE;
-    const dim3 grid = double_prune_grid(tiles_x, tiles_y);
     if (d_in > DP_EXTENT_MAX || d_out > DP_EXTENT_MAX) return hipErrorInvalidValue;
+    const int high = double_prune_height((uint32_t)tiles_x, (uint32_t)tiles_y);
+    const dim3 grid = double_prune_grid(tiles_x, tiles_y, high);
     if (d_in % 16 != 0 || d_out % 64 != 0)
         double_prune_kernel<true, false, true><<<grid, dim3(DP_THREADS), 0, s>>>(vals, meta, (int)d_out, (int)d_in, valsT, nullptr,
-                                                                          nullptr, metaT, vals_copy, (int)tiles_x, (int)tiles_y);
+                                                                          nullptr, metaT, vals_copy, (int)tiles_x, (int)tiles_y, high);
     else
         double_prune_kernel<true, false, false><<<grid, dim3(DP_THREADS), 0, s>>>(vals, meta, (int)d_out, (int)d_in, valsT, nullptr,
-                                                                           nullptr, metaT, vals_copy, (int)tiles_x, (int)tiles_y);
+                                                                           nullptr, metaT, vals_copy, (int)tiles_x, (int)tiles_y, high);
     return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@ from paper_2405_16325_amd import binding as sl
 from paper_2405_16325_amd import inputs
 from tests import test_gpu_nm_mask as nm
 from tests import test_gpu_optimizer as optimizer
+from tests import test_gpu_parity as parity
 from tests import test_gpu_ragged as ragged
 from tests.test_gpu_fullsize import assert_all_close, unpack_bits
 
@@ -96,6 +97,13 @@ def test_in_place_weight_gradient(b, d_out, d_in):
 # both copies rewritten in one pass: tiles of 128 that are not full, rows of any multiple of 8
 @pytest.mark.parametrize("d_out,d_in", [(8, 8), (136, 264), (1000, 1000), (128, 128), (4160, 2112)])
 def test_update_of_both_copies(d_out, d_in):
+    optimizer.test_update_sparse_bit_exact(d_out, d_in, False)
+
+
+# both prunings and the update with an XCD's chunks of 8, 4, 2 and 1 rows of tiles, in whole chunks and ragged ones
+@pytest.mark.parametrize("d_out,d_in", [(520, 7688), (1992, 1992), (2048, 2048), (1800, 904), (2056, 2056), (1032, 3080), (2496, 1304)])
+def test_chunks_of_the_double_prune(d_out, d_in):
+    parity.test_double_prune_bit_exact(f"chunks {d_out} x {d_in}", lambda: inputs.gaussian_bf16((d_out, d_in), 0.02, d_out + d_in, 2))
     optimizer.test_update_sparse_bit_exact(d_out, d_in, False)
 
 
