@@ -195,9 +195,9 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
         int rb = wrap_row(n0 + rl, n);
         b_src[i] = (const uint8_t*)Bt + (size_t)rb * ldb * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16);
     }
-    auto issue = [&](int ks) {                               // k-step ks (clamped) into stage ks % NS
+    auto issue = [&](int ks, int at) {                       // k-step ks (clamped) into the stage at byte `at`
         int kc = ks < ksteps ? ks : ksteps - 1;
-        uint8_t* st = smem + (ks % NS) * S::STAGE;
+        uint8_t* st = smem + at;
 #pragma unroll
         for (int i = 0; i < LD_A; ++i) dma16(a_src[i] + (size_t)kc * 128, st + (wave * LD_A + i) * 1024);
 #pragma unroll
@@ -224,7 +224,7 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
     // step s + 1.
 #define TN_STEP(G)                                                                                     \
     {                                                                                                  \
-        const uint8_t* st = smem + (ks % NS) * S::STAGE;                                               \
+        const uint8_t* st = smem + at;                                                                 \
         BFrag af[MF], bf[NF];                                                                          \
         _Pragma("unroll") for (int i = 0; i < MF; ++i) {                                               \
             af[i].u[0] = *(const u32x4*)(st + a_rd + i * 2048 + rd0);                                  \
@@ -234,11 +234,11 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
             bf[j].u[0] = *(const u32x4*)(st + b_rd + j * 2048 + rd0);                                  \
             bf[j].u[1] = *(const u32x4*)(st + b_rd + j * 2048 + rd1);                                  \
         }                                                                                              \
-        if (G == 0) issue(ks + NS - 1);                                                                \
+        if (G == 0) issue(ks + NS - 1, at == 0 ? LAST : at - S::STAGE);                                \
         /* all LDS reads of this stage have returned before anybody may overwrite it */                \
         WAIT_HERE(waitcnt_imm(G == 1 ? AHEAD : 63, 0));                                                \
         wg_barrier();                                                                                  \
-        if (G == 1) issue(ks + NS);                                                                    \
+        if (G == 1) issue(ks + NS, at);                                                                \
         /* before the MFMAs: among them, where the compiler may put these loads, they land 5 to 8 % later */ \
         if (G == 1) __builtin_amdgcn_sched_barrier(0);                                                 \
         _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                  \
@@ -250,16 +250,22 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
         }                                                                                              \
         if (G == 0) WAIT_HERE(waitcnt_imm(AHEAD, 15));                                                 \
         wg_barrier();                                                                                  \
+        at = at == LAST ? 0 : at + S::STAGE;                                                           \
     }
+    // The stage that is read, as a byte offset that wraps.  As (ks % NS) * STAGE it became a multiply-high and subtractions per
+    // lane before every step's LDS reads (us, from HBM: 2048 x 1024 over 4096 on 64 x 128 30.5 -> 26.0, 704 x 2112 over 4160
+    // 27.0 -> 22.2, 2048 x 1024 over 8192 51.8 -> 41.8); the 256 x 256 kernel, where registers are short, is 1 % slower this way.
+    constexpr int LAST = (NS - 1) * S::STAGE;
+    int at = 0;
 #pragma unroll
-    for (int p = 0; p < NS - 1; ++p) issue(k_begin + p);
+    for (int p = 0; p < NS - 1; ++p) issue(k_begin + p, p * S::STAGE);
     WAIT_HERE(waitcnt_imm(AHEAD, 15));                        // the first step has landed (this wave's share)
     wg_barrier();
     if (group == 0) {
         for (int ks = k_begin; ks < k_end; ++ks) TN_STEP(0)
         wg_barrier();
     } else {
-        issue(k_begin + NS - 1);
+        issue(k_begin + NS - 1, LAST);
         wg_barrier();
         for (int ks = k_begin; ks < k_end; ++ks) TN_STEP(1)
     }
@@ -744,7 +750,8 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
 // of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  Take the shape with the least
 // estimate: over 290 shapes (512 to 22000 on either side, 256 to 16000 along the contraction, operands from HBM and
-// from the caches), each on eleven tiles, it takes 0.3 % longer than the best one in the mean, 7 % at most; the rule before,
+// from the caches), each on eleven tiles, it takes 0.3 % longer than the best one in the mean, 7 % at most (tiles below 192 x 192 have
+// gained another fifth since, all alike: over 90 more shapes 0.2 %, 13 % at most, and a new fit chooses no better); the rule before,
 // of 256 x 256, 256 x 128, 128 x 128 and 128 x 64 the one with the fewest rounds x rows, 5.8 to 7.7 % (gradients, us: 700
 // tokens, 4160 x 2112 20.4 -> 16.6 on 192 x 192; 752 tokens, 5120 x 6464 66.5 -> 63.9 on 256 x 192; 4096 tokens, 1024 x
 // 1024 25 -> 20 on 64 x 64).
