@@ -1248,6 +1248,11 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
     return x.slabs > 0 && x.steps <= 2 * most;
 }
 
+// Without T's launches to save, a product that one launch is estimated to take less than this for is left whole: a call of
+// two launches takes the host 13.3 us, one of one launch 8.5, and the card gains 2 at most (us a call and on the card, split
+// and whole: 64 tokens, 1024 x 2048 13.4 and 8.0, 8.5 and 8.7; 81, 1344 x 2816 13.3 and 9.4, 10.7 and 11.1; 200, 512 x 3072
+// 13.5 and 9.3, 11.2 and 11.5; 48, 3072 x 3072 13.3 and 9.4, 11.1 and 11.3).  The estimate is up to 4 too high there.
+constexpr double SPLIT_MIN_US = 16.0;
 // Split of the product over k, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split whose launch
 // has room for X L beside its tiles saves the launches of X L (about 8 us against 3 for the larger second kernel).
 SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r) {
@@ -1279,6 +1284,7 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r) {
         if (one_round(128, 128)) consider(128, 128, sl);
         if (n > 128 && (long_weight || one_round(256, 128))) consider(256, 128, sl);
     }
+    if (!xl && tiles_us(n, m, K) < SPLIT_MIN_US) return SpmmSplit{0, 0, 0};
     int bm, bn;
     spmm_tile_choice(n, m, K, bm, bn);
     // Whole 128 x 64 tiles of 64 k-steps and more are estimated too well, slabs of 129 to 1024 tokens too badly by as much:

@@ -310,7 +310,7 @@ def test_calls_follow_the_current_stream(monkeypatch):
     (357, 5504, 128, 0, (2, 128, 96)), (467, 4232, 192, 32, (2, 128, 96)), (581, 5000, 704, 0, (2, 128, 128)), (580, 5168, 192, 32, (2, 128, 128)),
     (510, 5408, 128, 96, (2, 192, 64)), (698, 4304, 192, 0, (2, 192, 64)), (659, 5472, 128, 32, (2, 192, 96)), (520, 6536, 192, 0, (2, 192, 96)),
     (1193, 3928, 320, 0, (2, 192, 128)), (2828, 3128, 192, 96, (2, 192, 192)), (2008, 4640, 192, 32, (2, 256, 192)),
-    (257, 8, 1408, 0, (1, 128, 64)), (43, 48, 3136, 0, (6, 128, 64)), (35, 48, 832, 32, (6, 128, 64)), (300, 776, 4160, 160, (1, 128, 64)),
+    (257, 8, 1408, 0, (2, 64, 64)), (257, 8, 4160, 0, (1, 128, 64)), (43, 48, 3136, 0, (6, 128, 64)), (35, 48, 832, 32, (6, 128, 64)), (300, 776, 4160, 160, (1, 128, 64)),
     (2154, 8, 6592, 0, (1, 128, 128)), (2712, 8, 6912, 32, (1, 128, 128)), (69, 2696, 5312, 0, (6, 192, 64)), (344, 2448, 832, 96, (1, 192, 64)),
     (39, 24, 8384, 0, (1, 256, 64)), (54, 8, 8704, 32, (1, 256, 64)), (127, 72, 9280, 96, (1, 256, 128)), (194, 56, 7616, 0, (1, 256, 128))])
 def test_tiles_and_slabs_of_the_sparse_product(b, d_out, d_in, r, form):
