@@ -1285,13 +1285,13 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r) {
         if (n > 128 && (long_weight || one_round(256, 128))) consider(256, 128, sl);
     }
     if (!xl && tiles_us(n, m, K) < SPLIT_MIN_US) return SpmmSplit{0, 0, 0};
-    int bm, bn;
-    spmm_tile_choice(n, m, K, bm, bn);
-    // Whole 128 x 64 tiles of 64 k-steps and more are estimated too well, slabs of 129 to 1024 tokens too badly by as much:
-    // 700 tokens, 2112 x 4160 22.3 us whole, 22.7 in two slabs; 300, 4096 x 4096 19.6 / 19.7; 512, 2112 x 4160 21.9 / 20.8;
-    // 512, 4096 x 4096, which fills every compute unit, 21.1 / 24.3
-    const bool close = bm == 128 && bn == 64 && K >= 4096 && n > 128 && n <= 1024;
-    return least < (close ? 1.25 : 1.0) * (tiles_us(n, m, K) + (xl ? 8.0 : 0.0)) ? best : SpmmSplit{0, 0, 0};
+    // Whole products of 64 k-steps and more take an eighth longer than estimated beside split ones, on weights from HBM: of 44
+    // shapes of 129 to 1024 tokens, k of 4096 to 10000, the form chosen takes 0.1 % longer than the better one in the mean, 8 %
+    // at most, on weights from the last-level cache 2 % (taken as they are 1.8 % and 0.1 %).  us, whole / two or three slabs from
+    // HBM and from the cache: 512 tokens, 4096 x 4096 23.0 / 25.8 and 20.0 / 24.5; 700, 2112 x 4160 27.6 / 27.7 and 22.5 / 23.8;
+    // 518, 2240 x 4928 30.8 / 27.8 and 24.7 / 24.1; 530, 1792 x 4864 26.9 / 20.4 and 22.3 / 18.4.
+    const double whole = (K >= 4096 ? 1.125 : 1.0) * tiles_us(n, m, K) + (xl ? 8.0 : 0.0);
+    return least < whole ? best : SpmmSplit{0, 0, 0};
 }
 
 // The split of a long weight on tiles of 256 rows by the estimate of slabs_of_a_long_weight alone

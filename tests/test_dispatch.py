@@ -129,7 +129,9 @@ def test_short_adapter_products_of_many_tokens():
 
 def test_split_of_a_partial_round_by_slabs():
     slabs = lambda b, d_out, d_in: sl.slope_spmm_fwd_plan(b, d_in, d_out)["slabs"]
-    assert slabs(700, 2112, 4160) >= 2 and slabs(512, 4096, 4096) >= 2
+    assert slabs(530, 1792, 4864) >= 2 and slabs(512, 2048, 8192) >= 2
+    # measured as fast or faster whole: one launch, no scratch (26.6 us against 27.3; 21 us against 24)
+    assert slabs(700, 2112, 4160) == 1 and slabs(512, 4096, 4096) == 1 and slabs(1024, 2048, 4096) == 1
     assert slabs(700, 2112, 960) == 1                                    # fewer than four quads of k-steps per slab
     assert slabs(2048, 768, 3072) == 1                                   # a microsecond slower in a step
     assert sl.slope_spmm_fwd_plan(700, 4160, 2112, 0, False)["slabs"] == 1

@@ -172,8 +172,9 @@ def test_weight_gradient_with_leftover_tiles_and_few_tokens(b, d_out, d_in):
     check_layer(b, d_out, d_in)
 
 
-# input gradients with scratch: slabs by either rule, a last slab of one k-step, few tokens in slices, none
-@pytest.mark.parametrize("b,d_out,d_in,some", [(700, 4160, 2112, True), (512, 4096, 4096, True), (129, 8256, 520, True),
+# input gradients with scratch: slabs, a last slab of one k-step, few tokens in slices, none
+@pytest.mark.parametrize("b,d_out,d_in,some", [(700, 4160, 2112, False), (512, 4096, 4096, False), (129, 8256, 520, True),
+                                               (530, 4864, 1792, True), (803, 4800, 576, True),
                                                (1500, 8192, 1032, True), (16, 36864, 2048, True), (2048, 3072, 768, False)])
 def test_input_gradient_with_scratch(b, d_out, d_in, some):
     need = sl.slope_workspace_bytes(sl.SLOPE_CALL_SPMM_BWD_X_WS, b, d_in, d_out)
