@@ -317,8 +317,7 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  *       few tiles, or of 64 on any number), 4 small-batch kernel in its row-split form
  *       (d_in a multiple of 1024 and enough weight rows, or the
  *       workspace to cut the contraction into slices), 5 tile kernel for the tokens of whole tiles and
- *       a small-batch kernel for the last few, 6 as 1 for up to 128 tokens where 64 x 64 tiles would be
- *       one round, on tiles of less than 256 rows
+ *       a small-batch kernel for the last few
  *   [1], [2] weight rows and tokens per workgroup (of the tile kernel)
  *   [3] slabs or slices (1 = no split); for [0] == 5 the tokens of the small-batch kernel
  *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens; before the product, beside it or in it),

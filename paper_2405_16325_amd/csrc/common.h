@@ -65,8 +65,9 @@ struct SlabAdapter {
 };
 struct SpmmSplit { int bm, bn, slabs; };
 inline size_t spmm_split_bytes(const SpmmSplit& split, int64_t n, int64_t m) { return (size_t)split.slabs * (size_t)n * (size_t)m * 4; }
-SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r);
-SpmmSplit spmm_long_split(int64_t n, int64_t m, int64_t K);
+struct SlabRoom { int slabs; bool optional, long_weight; };
+SlabRoom spmm_slab_room(int64_t n, int64_t m, int64_t K);
+SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom& room);
 bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& split, XlSplit& x);
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                              int64_t K, const SlabAdapter& ad, const SpmmSplit& split, bf16_t* C, float* slabs, hipStream_t s);

@@ -41,26 +41,17 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
 }
 
 // The split over d_in of a forward product with adapters of rank r (0: none), {0, 0, 0} where it is not split.  Every form of
-// the call takes the same route, and what slope_spmm_fwd_static accepts is what the workspace query says: a split never
-// takes a shape past the static scratch.  A long weight in whole quads of k-steps is always split where that pays, at worst
-// into as many slabs of 256 rows as its estimate names, which its scratch is never counted below; any other product only
-// where that many, or else as many slabs of 256 x 128 tiles as one round holds, would fit the static scratch as well.
+// the call takes the same route, and what slope_spmm_fwd_static accepts is what the workspace query says: room for slabs that
+// is optional is only there where all of it fits the static scratch beside the adapter's.
 SpmmSplit fwd_split(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
-    const SpmmSplit split = spmm_split(b, d_out, d_in, r), named = spmm_long_split(b, d_out, d_in);
-    if (split.slabs == 0) return split;
-    const size_t fixed = adapter_workspace_bytes(b, d_in, d_out, r);
-    auto fits = [&](int64_t slabs) {
-        return fixed + round256((size_t)slabs * (size_t)b * (size_t)d_out * 4) <= (size_t)SLOPE_STATIC_SCRATCH_BYTES;
-    };
-    if (named.slabs && d_in % 256 == 0) return fits(split.slabs) || !fits(named.slabs) ? split : named;
-    const int64_t tiles = ((d_out + 255) / 256) * ((b + 127) / 128), held = RESIDENT / tiles < 16 ? RESIDENT / tiles : 16;
-    return fits(split.slabs) && fits(named.slabs ? named.slabs : held > 2 ? held : 2) ? split : SpmmSplit{0, 0, 0};
+    const SlabRoom room = spmm_slab_room(b, d_out, d_in);
+    const size_t bytes = round256((size_t)room.slabs * (size_t)b * (size_t)d_out * 4);
+    if (room.optional && adapter_workspace_bytes(b, d_in, d_out, r) + bytes > (size_t)SLOPE_STATIC_SCRATCH_BYTES) return {0, 0, 0};
+    return spmm_split(b, d_out, d_in, r, room);
 }
 
 size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {     // the slab buffer of that product
-    const size_t split = spmm_split_bytes(fwd_split(b, d_in, d_out, r), b, d_out);
-    const size_t named = d_in % 256 == 0 ? spmm_split_bytes(spmm_long_split(b, d_out, d_in), b, d_out) : 0;
-    return round256(split > named ? split : named);
+    return round256(spmm_split_bytes(fwd_split(b, d_in, d_out, r), b, d_out));
 }
 
 // T = X L on the kernel for ragged extents although its extents are whole k-steps
@@ -506,8 +497,7 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         const int64_t rest = split.slabs > 0 ? 0 : spmm_rest_tokens(b, d_out, d_in);
         int bm, bn;
         spmm_tile_choice(b - rest, d_out, d_in, bm, bn);
-        const int64_t tiles_of_64 = ((b + 63) / 64) * ((d_out + 63) / 64);
-        if (split.slabs > 0) { plan[0] = b <= 128 && split.bm < 256 && tiles_of_64 <= RESIDENT ? 6 : 1; plan[1] = split.bm; plan[2] = split.bn; plan[3] = split.slabs; }
+        if (split.slabs > 0) { plan[0] = 1; plan[1] = split.bm; plan[2] = split.bn; plan[3] = split.slabs; }
         else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = spmm_generic_edge(b - rest, d_out); }
         else { plan[0] = 2; plan[1] = bm; plan[2] = bn; }
         if (rest > 0) { plan[0] = 5; plan[3] = (int32_t)rest; }

@@ -1162,6 +1162,10 @@ static int slab_steps_of(int64_t K, int want) {               // k-steps per sla
     return (int)((quads + want - 1) / want) * 4;
 }
 
+// ---- The room for slabs: how many of them a call's scratch holds.  Sizes of scratch are part of the interface (programs keep
+// buffers, and slope_spmm_fwd takes its buffer on trust), so a split may never want more than the two rules below name,
+// whatever the estimate that chooses it (product_us, further down) prefers: they stay as they are, with the times of earlier
+// kernels in them, while that one follows the kernels.
 static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || !tile_kernel_fits(K)) return 0;
     const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128);
@@ -1173,9 +1177,8 @@ static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     const double weight = 1.125 * (double)m * (double)K, cu = 24.0, hbm = 5.0e3;   // bytes, bytes per ns
     int best = 1;
     double best_ns = 1e300;
-    // (a round is counted full at 7/8 of the compute units: on a 9216 x 36864 layer at 128 tokens 7 slabs, 252
-    // workgroups, took 180 us where 6 slabs, 216 workgroups, take 138 us, and 8, 9 and 12 slabs 172, 170 and 149 us;
-    // the cut tail of the weight gradient shows no such step between 224 and 256 workgroups)
+    // (a round is counted full at 7/8 of the compute units, which leaves room for X L beside the tiles.  9216 x 36864 at 128
+    // tokens, us: 6 slabs, 216 workgroups, 112, with an adapter of rank 128 117; 7 slabs, 252 workgroups, 107 and 123)
     const int64_t fit = RESIDENT - RESIDENT / 8;
     for (int sl = 1; sl <= 16 && sl * 4 <= quads; ++sl) {
         const double rounds = (double)((tiles * sl + fit - 1) / fit);
@@ -1190,6 +1193,40 @@ static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     const double slabs_ns = 8e3 + best_ns > weight / 3.4e3 ? 8e3 + best_ns : weight / 3.4e3;
     if (one_round_of_64(n, m) && 2e3 + 2.6e3 * (double)K / 512.0 <= slabs_ns) return 0;
     return best < 2 ? 0 : best;
+}
+
+// More than 128 tokens on up to half a round of 256 x 128 tiles: slabs on those where they were once estimated a tenth faster
+// than whole tiles of the shape with the fewest rounds x operand bytes.
+static int slabs_of_a_partial_round(int64_t n, int64_t m, int64_t K) {
+    const int64_t tiles = ((m + 255) / 256) * ((n + 127) / 128), quads = (K + 255) / 256;
+    if (n <= 128 || !tile_kernel_fits(K) || tiles > RESIDENT / 2) return 0;
+    auto step_us = [](int64_t bm, int64_t bn) { return 0.35 + (double)(72 * bm + 128 * bn) / 1e5; };
+    double whole = 3.0 + 2.05 * (double)K / 512.0;
+    if (!one_round_of_64(n, m)) {
+        constexpr int bms[6] = {256, 192, 256, 128, 128, 64}, bns[6] = {256, 256, 128, 128, 64, 128};
+        int64_t least = INT64_MAX;
+        for (int c = 0; c < 6; ++c) {
+            const int64_t rounds = (((m + bms[c] - 1) / bms[c]) * ((n + bns[c] - 1) / bns[c]) + RESIDENT - 1) / RESIDENT;
+            if (rounds * (72 * bms[c] + 128 * bns[c]) >= least) continue;
+            least = rounds * (72 * bms[c] + 128 * bns[c]);
+            whole = (double)rounds * (3.0 + (double)K / 64.0 * step_us(bms[c], bns[c]));
+        }
+    }
+    double least = 0.9 * whole;
+    int best = 0;
+    for (int64_t sl = 2; sl <= 16 && sl * 4 <= quads && sl * tiles <= RESIDENT; ++sl) {
+        const double us = 10.0 + (double)((quads + sl - 1) / sl * 4) * step_us(256, 128) + 8.0 * (double)sl * (double)n * (double)m / 6e6;
+        if (us < least) { least = us; best = (int)sl; }
+    }
+    return best;
+}
+
+// Slabs there is room for, 0: none.  The room of a long weight in whole quads of k-steps is always there, any other only where
+// the call's scratch with it fits that of slope_spmm_fwd_static (`optional`).
+SlabRoom spmm_slab_room(int64_t n, int64_t m, int64_t K) {
+    const int slabs = slabs_of_a_long_weight(n, m, K);
+    if (slabs) return {slabs, K % 256 != 0, true};
+    return {slabs_of_a_partial_round(n, m, K), true, false};
 }
 
 // Tiles of the product without a split; of two that take as long the first.  64 x 64 stands for the generic kernel's four groups.
@@ -1253,36 +1290,35 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
 // and whole: 64 tokens, 1024 x 2048 13.4 and 8.0, 8.5 and 8.7; 81, 1344 x 2816 13.3 and 9.4, 10.7 and 11.1; 200, 512 x 3072
 // 13.5 and 9.3, 11.2 and 11.5; 48, 3072 x 3072 13.3 and 9.4, 11.1 and 11.3).  The estimate is up to 4 too high there.
 constexpr double SPLIT_MIN_US = 16.0;
-// Split of the product over k, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split whose launch
-// has room for X L beside its tiles saves the launches of X L (about 8 us against 3 for the larger second kernel).
-SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r) {
+// Split of the product over k within that room, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split
+// whose launch has room for X L beside its tiles saves the launches of X L (about 8 us against 3 for the larger second kernel).
+SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom& room) {
     SpmmSplit best = {0, 0, 0};
-    if (n <= STREAM_MAX_TOKENS || !tile_kernel_fits(K)) return best;
+    if (room.slabs < 2) return best;
     const bool xl = r > 0 && n <= XL_SMALL_MAX_TOKENS;
     double least = 1e300;
-    auto consider = [&](int bm, int bn, int64_t slabs) {
-        const SpmmSplit c = {bm, bn, (int)slabs};
-        if ((K / 64 + slab_steps_of(K, c.slabs) - 1) / slab_steps_of(K, c.slabs) != slabs) return;   // the last would be empty
+    auto consider = [&](int bm, int bn, int slabs) {
+        const SpmmSplit c = {bm, bn, slabs};
+        if ((K / 64 + slab_steps_of(K, slabs) - 1) / slab_steps_of(K, slabs) != slabs) return;   // the last would be empty
         double us = product_us(n, m, K, bm, bn, slabs);
         XlSplit x;
         if (xl) us += slab_xl_split(n, m, K, r, c, x) ? 3.0 : 8.0;
         if (us < least) { least = us; best = c; }
     };
-    const int64_t quads = (K + 255) / 256, most = quads / 2 < 16 ? quads / 2 : 16;     // two quads of k-steps per slab at least
-    // A long weight: 256 rows, which ask least often for the tokens, in any number of rounds
-    const bool long_weight = slabs_of_a_long_weight(n, m, K) > 0;
-    if (long_weight && K >= 7168) {
-        for (int64_t sl = 2; sl <= most; ++sl) {
-            consider(256, n <= 64 ? 64 : 128, sl);
-        }
+    // A long weight on enough rows: tiles of 256, which ask least often for the tokens, in any number of rounds.  Where all the
+    // slabs there is room for fill less than three quarters of a round of them, smaller tiles (us, cold: 127 tokens, 1024 x 7424
+    // 256 x 128 in 7 slabs 22.4, 128 x 64 in 6 13.3; 217, 512 x 19456 16 slabs 30.9, 13 slabs 19.4; but 256, 9216 x 9216 as on 256).
+    const int64_t tall = ((m + 255) / 256) * ((n + 127) / 128);
+    if (room.long_weight && K >= 7168 && 4 * tall * room.slabs >= 3 * RESIDENT) {
+        for (int sl = 2; sl <= room.slabs; ++sl) consider(256, n <= 64 ? 64 : 128, sl);
         return best;
     }
-    for (int64_t sl = 2; sl <= most; ++sl) {
+    for (int sl = 2; sl <= room.slabs; ++sl) {
         auto one_round = [&](int bm, int bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn) * sl <= RESIDENT; };
         if (one_round(128, 64)) consider(128, 64, sl);
         if (one_round(192, 64)) consider(192, 64, sl);
         if (one_round(128, 128)) consider(128, 128, sl);
-        if (n > 128 && (long_weight || one_round(256, 128))) consider(256, 128, sl);
+        if (n > 64 || K >= 7168) consider(256, n <= 64 ? 64 : 128, sl);
     }
     if (!xl && tiles_us(n, m, K) < SPLIT_MIN_US) return SpmmSplit{0, 0, 0};
     // Whole products of 64 k-steps and more take an eighth longer than estimated beside split ones, on weights from HBM: of 44
@@ -1292,12 +1328,6 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r) {
     // 518, 2240 x 4928 30.8 / 27.8 and 24.7 / 24.1; 530, 1792 x 4864 26.9 / 20.4 and 22.3 / 18.4.
     const double whole = (K >= 4096 ? 1.125 : 1.0) * tiles_us(n, m, K) + (xl ? 8.0 : 0.0);
     return least < whole ? best : SpmmSplit{0, 0, 0};
-}
-
-// The split of a long weight on tiles of 256 rows by the estimate of slabs_of_a_long_weight alone
-SpmmSplit spmm_long_split(int64_t n, int64_t m, int64_t K) {
-    const int slabs = slabs_of_a_long_weight(n, m, K);
-    return slabs > 0 ? SpmmSplit{256, n <= 64 ? 64 : 128, slabs} : SpmmSplit{0, 0, 0};
 }
 
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,

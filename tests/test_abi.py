@@ -224,6 +224,20 @@ def test_a_split_that_is_optional_stays_inside_the_static_scratch(b, d_out, d_in
     assert binding.slope_spmm_fwd_plan(b, d_in, d_out, r)["product"] == 2      # the tile kernel
 
 
+# What a call may ask for, whatever split the estimate prefers: programs keep buffers of these sizes, and slope_spmm_fwd takes its
+# buffer on trust.  Nothing beyond the slabs that run is asked for either.
+@pytest.mark.parametrize("b,d_in,d_out,r,most", [
+    (510, 26368, 6400, 0, 26112000), (1452, 4416, 512, 0, 0), (560, 7360, 1408, 32, 15201280), (128, 36864, 9216, 0, 28311552),
+    (85, 16448, 24064, 128, 31780608), (67, 1280, 960, 32, 257792), (934, 9600, 1792, 32, 16216064), (34, 4160, 3328, 0, 1810432),
+    (78, 35776, 3776, 0, 16493568), (40, 832, 48, 96, 367104), (316, 35072, 19072, 0, 96428032), (64, 9216, 9216, 128, 21250048)])
+def test_scratch_of_the_forward_is_bounded_and_used(b, d_in, d_out, r, most):
+    need = binding.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r)
+    assert need <= most
+    if r == 0:
+        plan = binding.slope_spmm_fwd_plan(b, d_in, d_out)
+        assert need == (-(-plan["slabs"] * b * d_out * 4 // 256) * 256 if plan["slabs"] > 1 else 0)
+
+
 def test_binding_refuses_host_tensors():
     import torch
     with pytest.raises(ValueError):

@@ -137,6 +137,14 @@ def test_split_of_a_partial_round_by_slabs():
     assert sl.slope_spmm_fwd_plan(700, 4160, 2112, 0, False)["slabs"] == 1
 
 
+# whatever the tile: a caller that looks for code 1 finds every product that wants the workspace for slabs
+@pytest.mark.parametrize("b,d_out,d_in,r,rows", [(33, 520, 8192, 32, 128), (34, 3328, 4160, 0, 128), (38, 3072, 6400, 256, 128), (67, 4176, 4096, 0, 192),
+                                                 (64, 9216, 9216, 128, 256), (300, 2304, 5120, 160, 128)])
+def test_every_split_product_has_one_code(b, d_out, d_in, r, rows):
+    p = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
+    assert (p["product"], p["rows"]) == (SLABS, rows) and p["slabs"] > 1
+
+
 def test_adapter_product_regimes():
     xl = lambda b, r=128, d_in=9216: sl.slope_spmm_fwd_plan(b, d_in, 9216, r)["xl"]
     assert sl.slope_spmm_fwd_plan(64, 9216, 9216, 0)["xl"] == 0

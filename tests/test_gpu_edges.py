@@ -305,15 +305,18 @@ def test_calls_follow_the_current_stream(monkeypatch):
 
 # tiles of the ring kernel and the larger ones at the sizes where they can go wrong: fewer pairs of k-steps than ring stages, an odd
 # last k-step, a block of metadata that ends inside a row, ragged tiles on both sides; slabs, whose last one is of a single k-step
-# or of a few, X L beside them and before them.  Products of slope_spmm_fwd_plan: 1 and 6 split, 2 whole
+# or of a few, X L beside them and before them.  Products of slope_spmm_fwd_plan: 1 split, 2 and 3 whole
 @pytest.mark.parametrize("b,d_out,d_in,r,form", [
     (700, 1480, 128, 0, (2, 128, 64)), (193, 4520, 192, 160, (2, 128, 64)), (700, 1480, 1344, 32, (2, 128, 64)),
     (357, 5504, 128, 0, (2, 128, 96)), (467, 4232, 192, 32, (2, 128, 96)), (581, 5000, 704, 0, (2, 128, 128)), (580, 5168, 192, 32, (2, 128, 128)),
     (510, 5408, 128, 96, (2, 192, 64)), (698, 4304, 192, 0, (2, 192, 64)), (659, 5472, 128, 32, (2, 192, 96)), (520, 6536, 192, 0, (2, 192, 96)),
     (1193, 3928, 320, 0, (2, 192, 128)), (2828, 3128, 192, 96, (2, 192, 192)), (2008, 4640, 192, 32, (2, 256, 192)),
-    (257, 8, 1408, 0, (2, 64, 64)), (257, 8, 4160, 0, (1, 128, 64)), (43, 48, 3136, 0, (6, 128, 64)), (35, 48, 832, 32, (6, 128, 64)), (300, 776, 4160, 160, (1, 128, 64)),
-    (2154, 8, 6592, 0, (1, 128, 128)), (2712, 8, 6912, 32, (1, 128, 128)), (69, 2696, 5312, 0, (6, 192, 64)), (344, 2448, 832, 96, (1, 192, 64)),
-    (39, 24, 8384, 0, (1, 256, 64)), (54, 8, 8704, 32, (1, 256, 64)), (127, 72, 9280, 96, (1, 256, 128)), (194, 56, 7616, 0, (1, 256, 128))])
+    (257, 8, 1408, 0, (2, 64, 64)), (257, 8, 4160, 0, (1, 128, 64)), (43, 48, 3136, 0, (1, 128, 64)), (35, 48, 832, 32, (3, 64, 64)), (300, 776, 4160, 160, (1, 128, 64)),
+    (33, 8, 1856, 96, (1, 128, 64)), (34, 8, 5184, 160, (1, 128, 64)), (39, 24, 8384, 0, (1, 128, 64)), (54, 8, 8704, 32, (1, 128, 64)),
+    (127, 72, 9280, 96, (1, 128, 64)), (194, 56, 7616, 0, (1, 128, 64)), (2154, 8, 6592, 0, (1, 128, 64)), (2712, 8, 6912, 32, (1, 128, 64)),
+    (2747, 8, 8128, 0, (1, 128, 128)), (2719, 8, 8064, 160, (1, 128, 128)), (69, 2696, 5312, 0, (1, 128, 64)), (344, 2448, 832, 96, (2, 128, 64)),
+    (33, 9656, 3904, 0, (1, 192, 64)), (1700, 136, 7744, 96, (1, 192, 64)), (34, 5832, 10304, 0, (1, 256, 64)), (47, 7464, 9280, 96, (1, 256, 64)),
+    (134, 2584, 9664, 160, (1, 256, 128)), (135, 2696, 10304, 0, (1, 256, 128))])
 def test_tiles_and_slabs_of_the_sparse_product(b, d_out, d_in, r, form):
     plan = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
     assert (plan["product"], plan["rows"], plan["tokens"]) == form
