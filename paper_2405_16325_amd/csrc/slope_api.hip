@@ -43,15 +43,29 @@ size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r
 // The split over d_in of a forward product with adapters of rank r (0: none), {0, 0, 0} where it is not split.  Every form of
 // the call takes the same route, and what slope_spmm_fwd_static accepts is what the workspace query says: room for slabs that
 // is optional is only there where all of it fits the static scratch beside the adapter's.
-SpmmSplit fwd_split(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
-    const SlabRoom room = spmm_slab_room(b, d_out, d_in);
+SpmmSplit split_within(const SlabRoom& room, size_t fixed, int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     const size_t bytes = round256((size_t)room.slabs * (size_t)b * (size_t)d_out * 4);
-    if (room.optional && adapter_workspace_bytes(b, d_in, d_out, r) + bytes > (size_t)SLOPE_STATIC_SCRATCH_BYTES) return {0, 0, 0};
+    if (room.optional && fixed + bytes > (size_t)SLOPE_STATIC_SCRATCH_BYTES) return {0, 0, 0};
     return spmm_split(b, d_out, d_in, r, room);
 }
 
-size_t fwd_slab_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {     // the slab buffer of that product
-    return round256(spmm_split_bytes(fwd_split(b, d_in, d_out, r), b, d_out));
+SpmmSplit fwd_split(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
+    return split_within(spmm_slab_room(b, d_out, d_in), adapter_workspace_bytes(b, d_in, d_out, r), b, d_in, d_out, r);
+}
+
+// Bytes of the call's scratch, and its split: [ adapter | slabs ] for mid-size batches, [ adapter | slices ] for inference-size
+// ones.  Never less than without adapters, whose product may be split where this one is not (never into more slabs than there
+// is room for, so that this is seldom looked at).
+size_t fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t r, SpmmSplit& split) {
+    const SlabRoom room = spmm_slab_room(b, d_out, d_in);
+    const size_t fixed = adapter_workspace_bytes(b, d_in, d_out, r);
+    split = split_within(room, fixed, b, d_in, d_out, r);
+    size_t need = fixed + round256(spmm_split_bytes(split, b, d_out));
+    if (r > 0 && need < (size_t)room.slabs * (size_t)b * (size_t)d_out * 4) {
+        const size_t without = round256(spmm_split_bytes(split_within(room, 0, b, d_in, d_out, 0), b, d_out));
+        if (without > need) need = without;
+    }
+    return need + round256(spmm_rows_partial_bytes(b, d_out, d_in));
 }
 
 // T = X L on the kernel for ragged extents although its extents are whole k-steps
@@ -106,11 +120,8 @@ size_t slope_mask_bytes(int64_t rows, int64_t cols) { return slope_packed_meta_b
 
 size_t slope_spmm_fwd_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     if (b <= 0 || d_in <= 0 || d_out <= 0) return 0;
-    // the slabs of mid-size batches or the slices of inference-size ones: never both.  Never less than without adapters,
-    // whose product may be split where this one is not.
-    const size_t with = adapter_workspace_bytes(b, d_in, d_out, r) + fwd_slab_bytes(b, d_in, d_out, r);
-    const size_t without = fwd_slab_bytes(b, d_in, d_out, 0);
-    return (with > without ? with : without) + round256(spmm_rows_partial_bytes(b, d_out, d_in));
+    SpmmSplit split;
+    return fwd_plan(b, d_in, d_out, r, split);
 }
 
 size_t slope_token_copy_bytes(int64_t b, int64_t d) {
@@ -191,10 +202,10 @@ static slope_status spmm_fwd_check(const void* X, int64_t b, const void* Wr_vals
 }
 
 // The launches of slope_spmm_fwd; arguments are checked, `workspace` (if any) has
-// slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) bytes.
+// slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) bytes.  split: fwd_split of the call, none without a workspace.
 static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,
                                  int64_t d_in, const void* L_or_null, const void* R_or_null, int64_t r, void* Y,
-                                 void* workspace, void* stream) {
+                                 void* workspace, const SpmmSplit& split, void* stream) {
     const bool adapter = r > 0 && (L_or_null || R_or_null);
     hipStream_t s = (hipStream_t)stream;
     const bf16_t* x_in = (const bf16_t*)X;
@@ -213,7 +224,6 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     // XL_SMALL_MAX_TOKENS of them the kernel that adds the slabs adds the adapter term too, straight from the sums of T = X L,
     // which workgroups beside the product's compute where they fit (rank 128, 9216 x 9216, 128 tokens: 54.7 -> 42.8 us in
     // all; 256 tokens: 67 -> 53).
-    const SpmmSplit split = !few && workspace ? fwd_split(b, d_in, d_out, r) : SpmmSplit{0, 0, 0};
     SlabAdapter ad = {nullptr, sums, l, R, r, {0, 0, 0}};
     if (split.slabs && (!adapter || (b <= XL_SMALL_MAX_TOKENS && slab_xl_split(b, d_out, d_in, r, split, ad.x))))
         return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, split, (bf16_t*)Y, (float*)after, s));
@@ -256,7 +266,9 @@ slope_status slope_spmm_fwd(const void* X, int64_t b, const void* Wr_vals, const
     if (st != SLOPE_OK) return st;
     if (r > 0 && (L_or_null || R_or_null) && !workspace) return SLOPE_ERR_NULL;
     if (misaligned(workspace, 256)) return SLOPE_ERR_ALIGN;
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, stream);
+    const bool adapter = r > 0 && (L_or_null || R_or_null);
+    const SpmmSplit split = workspace ? fwd_split(b, d_in, d_out, adapter ? r : 0) : SpmmSplit{0, 0, 0};
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, split, stream);
 }
 
 slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, const void* Wr_meta, int64_t d_out,
@@ -267,9 +279,9 @@ slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, co
     const bool adapter = r > 0 && (L_or_null || R_or_null);
     if (adapter && !workspace) return SLOPE_ERR_NULL;
     if (misaligned(workspace, 256)) return SLOPE_ERR_ALIGN;
-    if (workspace && workspace_bytes < slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0))
-        return SLOPE_ERR_WORKSPACE;
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, stream);
+    SpmmSplit split = {0, 0, 0};
+    if (workspace && workspace_bytes < fwd_plan(b, d_in, d_out, adapter ? r : 0, split)) return SLOPE_ERR_WORKSPACE;
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, workspace, split, stream);
 }
 
 // ---- slope_spmm_fwd_static: the same call on a scratch buffer that lives in the library's image.
@@ -306,7 +318,8 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
     slope_status st = spmm_fwd_check(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y);
     if (st != SLOPE_OK) return st;
     const bool adapter = r > 0 && (L_or_null || R_or_null);
-    const size_t need = slope_spmm_fwd_workspace_bytes(b, d_in, d_out, adapter ? r : 0);
+    SpmmSplit split;
+    const size_t need = fwd_plan(b, d_in, d_out, adapter ? r : 0, split);
     if (need > (size_t)SLOPE_STATIC_SCRATCH_BYTES) return SLOPE_ERR_WORKSPACE;
     void* ws = nullptr;
     if (need > 0) {
@@ -315,7 +328,7 @@ slope_status slope_spmm_fwd_static(const void* X, int64_t b, const void* Wr_vals
     }
     // Nothing in the buffer has to start at zero: every partial sum that is read was written by this
     // call's own kernels first.
-    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, ws, stream);
+    return spmm_fwd_run(X, b, Wr_vals, Wr_meta, d_out, d_in, L_or_null, R_or_null, r, Y, ws, split, stream);
 }
 
 slope_status slope_spmm_bwd_x(const void* dY, int64_t b, const void* WrcT_vals, const void* WrcT_meta, int64_t d_out,
@@ -340,8 +353,9 @@ slope_status slope_spmm_bwd_x_ws(const void* dY, int64_t b, const void* WrcT_val
     slope_status st = spmm_fwd_check(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX);
     if (st != SLOPE_OK) return st;
     if (misaligned(workspace_or_null, 256)) return SLOPE_ERR_ALIGN;
-    if (workspace_bytes < slope_spmm_fwd_workspace_bytes(b, d_out, d_in, 0)) return SLOPE_ERR_WORKSPACE;
-    return spmm_fwd_run(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX, workspace_or_null, stream);
+    SpmmSplit split;
+    if (workspace_bytes < fwd_plan(b, d_out, d_in, 0, split)) return SLOPE_ERR_WORKSPACE;
+    return spmm_fwd_run(dY, b, WrcT_vals, WrcT_meta, d_in, d_out, nullptr, nullptr, 0, dX, workspace_or_null, split, stream);
 }
 
 slope_status slope_wgrad_masked(const void* dY, const void* X, int64_t b, const void* Wr_meta, int64_t d_out,

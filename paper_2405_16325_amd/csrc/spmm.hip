@@ -1164,7 +1164,7 @@ static int slab_steps_of(int64_t K, int want) {               // k-steps per sla
 
 // ---- The room for slabs: how many of them a call's scratch holds.  Sizes of scratch are part of the interface (programs keep
 // buffers, and slope_spmm_fwd takes its buffer on trust), so a split may never want more than the two rules below name,
-// whatever the estimate that chooses it (product_us, further down) prefers: they stay as they are, with the times of earlier
+// whatever the estimate that chooses it (launch_us, further down) prefers: they stay as they are, with the times of earlier
 // kernels in them, while that one follows the kernels.
 static int slabs_of_a_long_weight(int64_t n, int64_t m, int64_t K) {
     if (n <= STREAM_MAX_TOKENS || n > SLAB_MAX_TOKENS || !tile_kernel_fits(K)) return 0;
@@ -1241,23 +1241,38 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
 // The constants are a fit to 195 shapes of 40 to 6000 tokens on weights from HBM (768 to 36864 on either side), each on
 // all tiles and up to 14 slabs: the form chosen takes 0.5 % longer than the best one over all of them, more than 10 % in 4.
-static double product_us(int64_t n, int64_t m, int64_t K, int bm, int bn, int64_t slabs) {
-    const int64_t tiles_n = (n + bn - 1) / bn, tiles = ((m + bm - 1) / bm) * tiles_n * slabs, rounds = (tiles + RESIDENT - 1) / RESIDENT;
-    const double busy = (double)tiles / (double)(rounds * RESIDENT), idle = 1.0 - 0.2 * (1.0 - busy);
-    const double ksteps = slabs > 1 ? (double)slab_steps_of(K, (int)slabs) : (double)K / 64.0;
+struct TileCost { int64_t tiles; double start, step, less, stream; };   // what does not depend on the slabs
+static TileCost tile_cost(int64_t n, int64_t m, int64_t K, int bm, int bn) {
+    const int64_t tiles_n = (n + bn - 1) / bn, tiles = ((m + bm - 1) / bm) * tiles_n;
     if (bm == 64)                                             // (half of the last pair's loads go by where K % 128 is not 0)
-        return (double)rounds * (3.0 + ksteps * 0.248 * (1.0 + 0.25 / (double)tiles_n) * idle * (K % 128 ? 1.12 : 1.0));
-    const double weight = 72.0 * bm, step = (weight * (1.0 + 0.54 / (double)tiles_n) + 128.0 * bn) / 53e3 * idle;
-    double us = (double)rounds * (3.3 + ksteps * (step - (ring_tile(bm, bn) && bm * bn != 192 * 96 ? 0.057 : 0.0)));
-    const double stream = 3.3 + 1.125 * (double)m * (double)K / 6.2e6;      // one pass over the weight
-    if (us < stream) us = stream;
-    return slabs > 1 ? us + 1.7 + 0.12 * (double)slabs + 8.0 * (double)slabs * (double)n * (double)m / 4.84e6 : us;
+        return {tiles, 3.0, 0.248 * (1.0 + 0.25 / (double)tiles_n) * (K % 128 ? 1.12 : 1.0), 0.0, 0.0};
+    return {tiles, 3.3, (72.0 * bm * (1.0 + 0.54 / (double)tiles_n) + 128.0 * bn) / 53e3,
+            ring_tile(bm, bn) && bm * bn != 192 * 96 ? 0.057 : 0.0,
+            3.3 + 1.125 * (double)m * (double)K / 6.2e6};                   // one pass over the weight
+}
+static double launch_us(const TileCost& c, double ksteps, int slabs) {
+    const int64_t groups = c.tiles * slabs, rounds = (groups + RESIDENT - 1) / RESIDENT;
+    const double idle = 1.0 - 0.2 * (1.0 - (double)groups / (double)(rounds * RESIDENT));
+    const double us = (double)rounds * (c.start + ksteps * (c.step * idle - c.less));
+    return us < c.stream ? c.stream : us;
 }
 
-static double tiles_us(int64_t n, int64_t m, int64_t K) {
-    int bm, bn;
-    spmm_tile_choice(n, m, K, bm, bn);
-    return product_us(n, m, K, bm ? bm : 64, bn ? bn : 64, 1);
+// the tile of least time and that time
+static double best_tile_us(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
+    bm = bn = 64;
+    const double ksteps = (double)K / 64.0;
+    const bool one_round = one_round_of_64(n, m);
+    // Up to 64 tokens on more weight rows than a round of 64 x 64 tiles, short contractions: those tiles, several to a compute unit
+    if (n <= 64 && !one_round && K <= 1088) {
+        bm = (m + 127) / 128 >= 200 ? 128 : 64;
+        return launch_us(tile_cost(n, m, K, bm, bn), ksteps, 1);
+    }
+    double least = one_round ? launch_us(tile_cost(n, m, K, 64, 64), ksteps, 1) : 1e300;
+    for (const SpmmTile& t : SPMM_TILES) {
+        const double us = launch_us(tile_cost(n, m, K, t.bm, t.bn), ksteps, 1);
+        if (us < least) { least = us; bm = t.bm; bn = t.bn; }
+    }
+    return least;
 }
 
 // Split of T = X L into workgroups beside the slabs' tiles: on the compute units that their single round leaves idle, and
@@ -1296,38 +1311,44 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
     SpmmSplit best = {0, 0, 0};
     if (room.slabs < 2) return best;
     const bool xl = r > 0 && n <= XL_SMALL_MAX_TOKENS;
-    double least = 1e300;
-    auto consider = [&](int bm, int bn, int slabs) {
-        const SpmmSplit c = {bm, bn, slabs};
-        if ((K / 64 + slab_steps_of(K, slabs) - 1) / slab_steps_of(K, slabs) != slabs) return;   // the last would be empty
-        double us = product_us(n, m, K, bm, bn, slabs);
-        XlSplit x;
-        if (xl) us += slab_xl_split(n, m, K, r, c, x) ? 3.0 : 8.0;
-        if (us < least) { least = us; best = c; }
-    };
-    // A long weight on enough rows: tiles of 256, which ask least often for the tokens, in any number of rounds.  Where all the
-    // slabs there is room for fill less than three quarters of a round of them, smaller tiles (us, cold: 127 tokens, 1024 x 7424
-    // 256 x 128 in 7 slabs 22.4, 128 x 64 in 6 13.3; 217, 512 x 19456 16 slabs 30.9, 13 slabs 19.4; but 256, 9216 x 9216 as on 256).
-    const int64_t tall = ((m + 255) / 256) * ((n + 127) / 128);
-    if (room.long_weight && K >= 7168 && 4 * tall * room.slabs >= 3 * RESIDENT) {
-        for (int sl = 2; sl <= room.slabs; ++sl) consider(256, n <= 64 ? 64 : 128, sl);
-        return best;
-    }
-    for (int sl = 2; sl <= room.slabs; ++sl) {
-        auto one_round = [&](int bm, int bn) { return ((m + bm - 1) / bm) * ((n + bn - 1) / bn) * sl <= RESIDENT; };
-        if (one_round(128, 64)) consider(128, 64, sl);
-        if (one_round(192, 64)) consider(192, 64, sl);
-        if (one_round(128, 128)) consider(128, 128, sl);
-        if (n > 64 || K >= 7168) consider(256, n <= 64 ? 64 : 128, sl);
-    }
-    if (!xl && tiles_us(n, m, K) < SPLIT_MIN_US) return SpmmSplit{0, 0, 0};
+    int bm, bn;
+    double least = best_tile_us(n, m, K, bm, bn);
+    if (!xl && least < SPLIT_MIN_US) return best;
     // Whole products of 64 k-steps and more take an eighth longer than estimated beside split ones, on weights from HBM: of 44
     // shapes of 129 to 1024 tokens, k of 4096 to 10000, the form chosen takes 0.1 % longer than the better one in the mean, 8 %
     // at most, on weights from the last-level cache 2 % (taken as they are 1.8 % and 0.1 %).  us, whole / two or three slabs from
     // HBM and from the cache: 512 tokens, 4096 x 4096 23.0 / 25.8 and 20.0 / 24.5; 700, 2112 x 4160 27.6 / 27.7 and 22.5 / 23.8;
     // 518, 2240 x 4928 30.8 / 27.8 and 24.7 / 24.1; 530, 1792 x 4864 26.9 / 20.4 and 22.3 / 18.4.
-    const double whole = (K >= 4096 ? 1.125 : 1.0) * tiles_us(n, m, K) + (xl ? 8.0 : 0.0);
-    return least < whole ? best : SpmmSplit{0, 0, 0};
+    least = (K >= 4096 ? 1.125 : 1.0) * least + (xl ? 8.0 : 0.0);
+    // On tiles of bm rows, into all numbers of slabs that leave none empty.  (X L is looked at only where it decides.)
+    auto consider = [&](const SpmmTile& t, bool one_round) {
+        const TileCost cost = tile_cost(n, m, K, t.bm, t.bn);
+        const double finish = 0.12 + 8.0 * (double)n * (double)m / 4.84e6;  // the second launch, per slab
+        const int most = one_round && cost.tiles * room.slabs > RESIDENT ? (int)(RESIDENT / cost.tiles) : room.slabs;
+        for (int sl = 2; sl <= most; ++sl) {
+            const int steps = slab_steps_of(K, sl);
+            double us = launch_us(cost, steps, sl) + 1.7 + finish * sl + (xl ? 3.0 : 0.0);
+            if (us >= least || (K / 64 + steps - 1) / steps != sl) continue;
+            const SpmmSplit c = {t.bm, t.bn, sl};
+            XlSplit x;
+            if (xl && !slab_xl_split(n, m, K, r, c, x)) us += 5.0;
+            if (us < least) { least = us; best = c; }
+        }
+    };
+    const SpmmTile tall = {256, n <= 64 ? 64 : 128};
+    // A long weight on enough rows: tiles of 256, which ask least often for the tokens, in any number of rounds.  Where all the
+    // slabs there is room for fill less than three quarters of a round of them, smaller tiles (us, cold: 127 tokens, 1024 x 7424
+    // 256 x 128 in 7 slabs 22.4, 128 x 64 in 6 13.3; 217, 512 x 19456 16 slabs 30.9, 13 slabs 19.4; but 256, 9216 x 9216 as on 256).
+    if (room.long_weight && K >= 7168 && 4 * ((m + 255) / 256) * ((n + 127) / 128) * room.slabs >= 3 * RESIDENT) {
+        least = 1e300;
+        consider(tall, false);
+        return best;
+    }
+    consider({128, 64}, true);
+    consider({192, 64}, true);
+    consider({128, 128}, true);
+    if (n > 64 || K >= 7168) consider(tall, false);
+    return best;
 }
 
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
@@ -1355,26 +1376,13 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
 
 int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RESIDENT ? 64 : 128; }
 
-// Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel.
+// Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel, whose whole pairs of
+// k-steps on a round of 64 x 64 tiles count as a tile shape of their own.
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 0;
     if (!tile_kernel_fits(K)) return;
-    const bool one_round = one_round_of_64(n, m);
-    // Up to 64 tokens on more weight rows than a round of 64 x 64 tiles, short contractions: those tiles, several to a compute unit
-    if (n <= 64 && !one_round && K <= 1088) {
-        bm = (m + 127) / 128 >= 200 ? 128 : 64;
-        bn = 64;
-        return;
-    }
-    double least = 1e300;
-    if (one_round) {                                          // whole pairs of k-steps count as a tile shape of their own
-        least = product_us(n, m, K, 64, 64, 1);
-        if (K % 128 == 0) bm = bn = 64;
-    }
-    for (const SpmmTile& t : SPMM_TILES) {
-        const double us = product_us(n, m, K, t.bm, t.bn, 1);
-        if (us < least) { least = us; bm = t.bm; bn = t.bn; }
-    }
+    best_tile_us(n, m, K, bm, bn);
+    if (bm == 64 && K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
 }
 
 // Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 8 us for its launch and
@@ -1382,12 +1390,13 @@ void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
 // of the tile kernels' 256 or 128 (777 tokens, 20480 x 5120: 139 us in two rounds of tiles, 80 + 25 for 768 and 9 tokens).
 int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K) {
     if (n <= 128 || !tile_kernel_fits(K) || one_round_of_64(n, m)) return 0;
-    double least = tiles_us(n, m, K);
+    int bm, bn;
+    double least = best_tile_us(n, m, K, bm, bn);
     int64_t best = 0;
     for (int64_t edge = 256; edge >= 128; edge /= 2) {
         const int64_t rest = n % edge;
         if (rest == 0 || rest > STREAM_MAX_TOKENS || rest == n) continue;
-        const double us = tiles_us(n - rest, m, K) + 1.125 * (double)m * (double)K / 5e6 + 6.0;
+        const double us = best_tile_us(n - rest, m, K, bm, bn) + 1.125 * (double)m * (double)K / 5e6 + 6.0;
         if (us < 0.95 * least) { least = us / 0.95; best = rest; }
     }
     return best;

@@ -1,6 +1,8 @@
 """Host logic: which kernels slope_spmm_fwd picks for a shape (slope_spmm_fwd_plan, no GPU needed).
 The regimes pinned here are the ones the design notes describe; the boundaries are properties of the
 cost estimates, not of measured times."""
+import time
+
 import pytest
 
 from paper_2405_16325_amd import binding as sl
@@ -154,6 +156,23 @@ def test_adapter_product_regimes():
     # chunks of 64 rows of L per partial sum that the scratch is sized by: as many as still give 256 workgroups
     chunks = lambda b, d_in: sl.slope_spmm_fwd_plan(b, d_in, 9216, 128)["xl_chunks"]
     assert chunks(16, 9216) == 1 and chunks(64, 9216) == 1 and chunks(16, 36864) == 2 and chunks(512, 36864) == 4
+
+
+@pytest.mark.parametrize("b,d_out,d_in,r", [(128, 4096, 4096, 128), (300, 4096, 4096, 0), (700, 2112, 4160, 0), (64, 1024, 2048, 0), (128, 9216, 9216, 128)])
+def test_planning_costs_less_than_the_call_into_the_library(b, d_out, d_in, r):
+    """Every call plans, and the small ones are bound by the host: the query of a shape against one that plans nothing
+    (0.6 us both through ctypes, up to 0.4 more here; 1.0 to 1.9 more while every form was priced)."""
+    query = sl.lib().slope_spmm_fwd_workspace_bytes
+
+    def least_s(*shape):
+        best = float("inf")
+        for _ in range(200):
+            t = time.perf_counter()
+            for _ in range(100):
+                query(*shape)
+            best = min(best, time.perf_counter() - t)
+        return best
+    assert least_s(b, d_in, d_out, r) < 2.2 * least_s(0, d_in, d_out, r)
 
 
 def test_plan_rejects_what_the_call_rejects():
