@@ -1241,6 +1241,8 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
 // The constants are a fit to 195 shapes of 40 to 6000 tokens on weights from HBM (768 to 36864 on either side), each on
 // all tiles and up to 14 slabs: the form chosen takes 0.5 % longer than the best one over all of them, more than 10 % in 4.
+// Few tokens on many rows are no exception (us, from HBM: 64 tokens, 20480 x 1024 10.4 on 128 x 64, 13.3 on 64 x 64 tiles, several
+// to a compute unit; 36864 x 1024 13.6 on 192 x 64, 18.5 and 19.3).
 struct TileCost { int64_t tiles; double start, step, less, stream; };   // what does not depend on the slabs
 static TileCost tile_cost(int64_t n, int64_t m, int64_t K, int bm, int bn) {
     const int64_t tiles_n = (n + bn - 1) / bn, tiles = ((m + bm - 1) / bm) * tiles_n;
@@ -1261,13 +1263,7 @@ static double launch_us(const TileCost& c, double ksteps, int slabs) {
 static double best_tile_us(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 64;
     const double ksteps = (double)K / 64.0;
-    const bool one_round = one_round_of_64(n, m);
-    // Up to 64 tokens on more weight rows than a round of 64 x 64 tiles, short contractions: those tiles, several to a compute unit
-    if (n <= 64 && !one_round && K <= 1088) {
-        bm = (m + 127) / 128 >= 200 ? 128 : 64;
-        return launch_us(tile_cost(n, m, K, bm, bn), ksteps, 1);
-    }
-    double least = one_round ? launch_us(tile_cost(n, m, K, 64, 64), ksteps, 1) : 1e300;
+    double least = one_round_of_64(n, m) ? launch_us(tile_cost(n, m, K, 64, 64), ksteps, 1) : 1e300;
     for (const SpmmTile& t : SPMM_TILES) {
         const double us = launch_us(tile_cost(n, m, K, t.bm, t.bn), ksteps, 1);
         if (us < least) { least = us; bm = t.bm; bn = t.bn; }
@@ -1421,9 +1417,7 @@ static hipError_t launch_tiles(const bf16_t* B, int64_t n, const bf16_t* A_vals,
         case 192064: return launch_ring<192, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 128096: return launch_ring<128, 96>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
         case 128064: return launch_ring<128, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
-        default:                                              // 64 x 64
-            return one_round_of_64(n, m) ? launch_generic_as<2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s)
-                                         : launch_tile<64, 64>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
+        default: return launch_generic_as<2, 4>(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);     // 64 x 64
     }
 }
 

@@ -105,8 +105,8 @@ def test_contractions_by_their_multiple_of_64():
 def test_more_than_a_round_of_64_x_64_tiles_stays_on_the_tile_kernel(b, d_out, d_in):
     assert -(-d_out // 64) > 256
     p = sl.slope_spmm_fwd_plan(b, d_in, d_out, 0, False)
-    assert (p["product"], p["rows"], p["tokens"]) == (TILE, 64, 64)
-    assert sl.slope_spmm_fwd_plan(b, d_in, 36864, 0, False)["rows"] == 128
+    assert (p["product"], p["rows"], p["tokens"]) == (TILE, 128, 64)
+    assert sl.slope_spmm_fwd_plan(b, d_in, 36864, 0, False)["rows"] == 192
 
 
 def test_a_few_tokens_beyond_whole_tiles_take_the_small_batch_kernel():
