@@ -788,9 +788,9 @@ static hipError_t launch_dense_tile(int tile, const bf16_t* A, int64_t m, const 
     }
 }
 
-// Scratch bytes of launch_wgrad_masked_t's tail pass (0: none).  They are counted wherever a rule of fewest rounds x rows among
-// four of the tiles would cut, also where the estimate above now takes whole tiles of another shape (5120 x 4096, 1153
-// tokens: 73.9 us cut, 56.5 on 192 x 256): buffers of the size this has always named stay large enough.
+// Scratch bytes of launch_wgrad_masked_t's tail pass, 0 where it does not cut: where the estimate above takes whole tiles, of
+// this or another shape (1153 tokens, 5120 x 4096: 78 us cut, 58 on 256 x 192; 1640, 19840 x 1000: 89 cut, 80 whole), and where a rule of fewest rounds x
+// rows among four of the tiles would not cut, which is as much scratch as this call ever asks for: programs keep buffers.
 size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     const int64_t ksteps = (b + 63) / 64;
     const TailPlan p = tail_plan((d_in + 255) / 256, (d_out + 255) / 256, ksteps);
@@ -799,6 +799,7 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     const int64_t whole = ((d_in + 255) / 256) * ((d_out + 255) / 256) / RESIDENT * 512 * 100;
     const int64_t cut = whole + (int64_t)(512.0 * 100.0 * p.steps / (double)(ksteps + 6));
     if (cut > rows(256, 128) || cut > rows(128, 128) || cut > rows(128, 64)) return 0;
+    if (dense_tile_choice(d_in, d_out, ksteps, true) != 0) return 0;
     return (size_t)p.parts * (size_t)p.bundle * (256 * 256 * 4);
 }
 

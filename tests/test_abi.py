@@ -98,6 +98,9 @@ def test_argument_errors_are_reported_before_launch():
     assert lib.slope_workspace_bytes(E.SLOPE_CALL_WGRAD_MASKED_T, 16384, 4096, 4096, 0) == 0
     assert lib.slope_workspace_bytes(E.SLOPE_CALL_WGRAD_MASKED_T, 16384, 2560, 2560, 0) == 0
     assert lib.slope_workspace_bytes(E.SLOPE_CALL_WGRAD_MASKED_T, 512, 9216, 9216, 0) == 0
+    # leftover tiles, but whole tiles of another shape take less: nothing is asked for that no kernel touches
+    assert lib.slope_workspace_bytes(E.SLOPE_CALL_WGRAD_MASKED_T, 1153, 5120, 4096, 0) == 0
+    assert lib.slope_workspace_bytes(E.SLOPE_CALL_WGRAD_MASKED_T, 1100, 6624, 3272, 0) == 0
     assert lib.slope_spmm_bwd_x_adapter(p, 8, p, p, 64, 64, p, None, 32, p, p, big, None) == E.SLOPE_ERR_NULL
     assert lib.slope_spmm_bwd_x_adapter(p, 8, p, p, 64, 64, p, p, 48, p, p, big, None) == E.SLOPE_ERR_UNSUPPORTED
     assert lib.slope_spmm_bwd_x_adapter(p, 8, p, p, 64, 64, p, p, 32, p, odd, big, None) == E.SLOPE_ERR_ALIGN

@@ -165,10 +165,11 @@ def test_weight_gradient_with_a_large_last_round(b, d_out, d_in):
 
 
 # leftover tiles on short contractions, in whole shares: the last one shorter, a last bundle that is not full, tiles and
-# tokens that fill neither
-@pytest.mark.parametrize("b,d_out,d_in", [(1153, 4096, 5120), (1640, 1000, 19840), (2000, 4352, 4352), (1100, 3272, 6624)])
-def test_weight_gradient_with_leftover_tiles_and_few_tokens(b, d_out, d_in):
-    assert sl.slope_workspace_bytes(sl.SLOPE_CALL_WGRAD_MASKED_T, b, d_in, d_out) > 0
+# tokens that fill neither; and grids that were cut once and are better off on whole tiles of another shape, without scratch
+@pytest.mark.parametrize("b,d_out,d_in,cut", [(2000, 4352, 4352, True), (1423, 3520, 6720, True), (1466, 1176, 19232, True), (1986, 1184, 14048, True),
+                                              (1153, 4096, 5120, False), (1640, 1000, 19840, False), (1100, 3272, 6624, False)])
+def test_weight_gradient_with_leftover_tiles_and_few_tokens(b, d_out, d_in, cut):
+    assert (sl.slope_workspace_bytes(sl.SLOPE_CALL_WGRAD_MASKED_T, b, d_in, d_out) > 0) == cut
     check_layer(b, d_out, d_in)
 
 
