@@ -2,6 +2,8 @@
 the smallest and largest of a range.  Integers bit for bit against the oracle; products either against the fp64 oracle
 (ragged layers) or, for shapes too large for it, every element against fp32 library products on the weight masked by
 the emitted bit masks, under the element-wise bounds of tests/parity_util.py."""
+import ctypes
+
 import pytest
 import torch
 
@@ -77,13 +79,25 @@ def test_generic_sparse_kernel(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
 
 
-# the skinny adapter products of whole k-steps: every tile shape the plan picks, with and without slabs over the
-# contraction (one short of a slab's four k-steps, a last slab that is shorter, ranks that fill no tile)
+# the skinny adapter products of whole k-steps, with and without slabs over the contraction (one short of a slab's four k-steps, a
+# last slab that is shorter, ranks that fill no tile)
 @pytest.mark.parametrize("b,d_out,d_in,r", [(130, 640, 704, 32), (3000, 4160, 832, 320), (4096, 2560, 1280, 64),
                                             (6000, 2624, 1088, 96), (5000, 9216, 512, 128), (1088, 448, 9280, 512),
                                             # few tokens: slabs up to the number that pays, on a tile or two
                                             (127, 8256, 512, 32), (2, 2048, 1024, 160)])
 def test_skinny_adapter_products(b, d_out, d_in, r):
+    check_layer(b, d_out, d_in, r)
+
+
+# both launches of the adapter gradients on every tile (long side x rank) that their plan picks, token counts that fill none: X L
+# and dY R^T on 64 x 64, 64 x 128, 128 x 64, 128 x 128 and 64 x 256, with different numbers of slabs and with the same, on tiles the
+# rank does not fill; dL and dR on each of them, whole and in slabs
+@pytest.mark.parametrize("b,d_out,d_in,r", [
+    (65, 2624, 128, 320), (647, 128, 2688, 512), (773, 128, 3328, 320), (1374, 1984, 3456, 320), (1037, 2624, 128, 512), (1572, 4544, 128, 512),
+    (3207, 6976, 3648, 160), (6534, 5440, 7360, 160),
+    (2561, 128, 128, 160), (65, 128, 3008, 512), (3080, 128, 448, 512), (68, 5824, 128, 320), (3103, 128, 704, 320), (65, 128, 5440, 512),
+    (2729, 960, 128, 512), (2819, 192, 2496, 512)])
+def test_adapter_gradients_on_every_tile(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
 
 
@@ -141,11 +155,27 @@ def test_adapter_product_of_few_tokens(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r, backward=False)
 
 
+def launches(call):
+    """Kernels that a call launches: the nodes of its graph."""
+    call()
+    torch.cuda.synchronize()
+    graph, count = torch.cuda.CUDAGraph(keep_graph=True), ctypes.c_size_t()
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
 # X L inside the small-batch kernel (up to six chunks of 32 rows of L per wavefront, eight, six and four of them; one token tile
-# and two) and beside it, an odd number of k-steps, a rank that fills no tile of columns, rows that fill no workgroup
-@pytest.mark.parametrize("b,d_out,d_in,r", [(1, 3072, 768, 32), (16, 1000, 1472, 64), (5, 9224, 1088, 32), (20, 520, 384, 64), (31, 12296, 704, 32),
-                                            (3, 4096, 4096, 64), (1, 9224, 2880, 96), (12, 16392, 2112, 128), (25, 36872, 2176, 32), (2, 17160, 3264, 32)])
-def test_adapter_product_in_and_beside_a_small_batch(b, d_out, d_in, r):
+# and two), beside it (one token tile and two, one tile of columns and two) and before it, an odd number of k-steps, a rank that
+# fills no tile of columns, rows that fill no workgroup.  One, two and three launches tell which it was
+@pytest.mark.parametrize("b,d_out,d_in,r,kernels", [
+    (1, 3072, 768, 32, 1), (16, 1000, 1472, 64, 1), (5, 9224, 1088, 32, 1), (20, 520, 384, 64, 1), (31, 12296, 704, 32, 1),
+    (3, 4096, 4096, 64, 2), (1, 9224, 2880, 96, 2), (2, 17160, 3264, 32, 2), (8, 16392, 2112, 128, 2), (17, 17000, 9152, 64, 2),
+    (12, 16392, 2112, 128, 3), (25, 36872, 2176, 32, 3)])
+def test_adapter_product_in_and_beside_a_small_batch(b, d_out, d_in, r, kernels):
     check_layer(b, d_out, d_in, r, backward=False)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(inputs.SEED_BASE + d_out)
@@ -154,6 +184,7 @@ def test_adapter_product_in_and_beside_a_small_batch(b, d_out, d_in, r):
     y = sl.slope_spmm_fwd(X, vals, meta, L, R)
     assert torch.equal(sl.slope_spmm_fwd(X, vals, meta, L, R), y)          # bit-identical runs
     assert torch.equal(sl.slope_spmm_fwd_static(X, vals, meta, L, R), y)   # and forms of the call
+    assert launches(lambda: sl.slope_spmm_fwd_static(X, vals, meta, L, R, out=y)) == kernels
 
 
 # more than half a round of leftover 256 x 256 tiles: bundles that do not divide them, shares across bundle boundaries,
