@@ -1297,10 +1297,10 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
 }
 
 // Without T's launches to save, a product that one launch is estimated to take less than this for is left whole: a call of
-// two launches takes the host 13.3 us, one of one launch 8.5, and the card gains 2 at most (us a call and on the card, split
-// and whole: 64 tokens, 1024 x 2048 13.4 and 8.0, 8.5 and 8.7; 81, 1344 x 2816 13.3 and 9.4, 10.7 and 11.1; 200, 512 x 3072
-// 13.5 and 9.3, 11.2 and 11.5; 48, 3072 x 3072 13.3 and 9.4, 11.1 and 11.3).  The estimate is up to 4 too high there.
-constexpr double SPLIT_MIN_US = 16.0;
+// two launches takes the host 13.4 to 13.8 us whatever the card does in them, one of one launch 8.5 (us a call, whole and
+// split: estimate 14.0, 358 tokens, 256 x 3328 14.6, 13.6; 14.3, 767, 896 x 3008 16.0, 14.7; 15.7, 399, 256 x 3840 16.5, 13.5; but
+// 10.7, 742, 512 x 2112 12.2, 13.8; 11.0, 487, 1216 x 2176 12.3, 13.5; 12.1, 239, 5760 x 2048 13.1, 18.1).
+constexpr double SPLIT_MIN_US = 13.5;
 // Split of the product over k within that room, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split
 // whose launch has room for X L beside its tiles saves the launches of X L (about 8 us against 3 for the larger second kernel).
 SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom& room) {
@@ -1381,7 +1381,7 @@ void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     if (bm == 64 && K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
 }
 
-// Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 8 us for its launch and
+// Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 6 us for its launch and
 // the drained chip before it) takes for less than the round of tiles that they begin (0: none): up to 32 beyond a multiple
 // of the tile kernels' 256 or 128 (777 tokens, 20480 x 5120: 139 us in two rounds of tiles, 80 + 25 for 768 and 9 tokens).
 int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K) {
