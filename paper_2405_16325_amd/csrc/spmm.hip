@@ -1333,9 +1333,11 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
     };
     const SpmmTile tall = {256, n <= 64 ? 64 : 128};
     // A long weight on enough rows: tiles of 256, which ask least often for the tokens, in any number of rounds.  Where all the
-    // slabs there is room for fill less than three quarters of a round of them, smaller tiles (us, cold: 127 tokens, 1024 x 7424
-    // 256 x 128 in 7 slabs 22.4, 128 x 64 in 6 13.3; 217, 512 x 19456 16 slabs 30.9, 13 slabs 19.4; but 256, 9216 x 9216 as on 256).
-    if (room.long_weight && K >= 7168 && 4 * ((m + 255) / 256) * ((n + 127) / 128) * room.slabs >= 3 * RESIDENT) {
+    // slabs there is room for fill less than 13/16 of a round of them, the smaller tiles fill it up (us from HBM, 256 x 128 /
+    // the smaller tile, workgroups of the former: 134 tokens, 8064 x 7808 47.2 / 38.6, 192; 482, 4096 x 8192 46.4 / 39.7, 192;
+    // 327, 3328 x 8960 35.4 / 33.4, 195; 217, 512 x 19456 30.9 / 19.4, 32; from there on the two are within 3 %: 128, 9216 x 9216
+    // 41.5 / 40.4, 216; 100, 5632 x 13056 38.1 / 37.1, 220; 256, 9216 x 9216 the same form).
+    if (room.long_weight && K >= 7168 && 16 * ((m + 255) / 256) * ((n + 127) / 128) * room.slabs >= 13 * RESIDENT) {
         least = 1e300;
         consider(tall, false);
         return best;

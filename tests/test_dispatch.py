@@ -147,6 +147,14 @@ def test_every_split_product_has_one_code(b, d_out, d_in, r, rows):
     assert (p["product"], p["rows"]) == (SLABS, rows) and p["slabs"] > 1
 
 
+def test_long_weights_on_too_few_rows_of_256_are_filled_up_with_smaller_tiles():
+    # 16 x 4 and 32 x 2 tiles of 256 x 128 in the three slabs there is room for are 192 workgroups
+    for b, d_out, d_in in ((482, 4096, 8192), (134, 8064, 7808), (217, 512, 19456)):
+        p = sl.slope_spmm_fwd_plan(b, d_in, d_out)
+        assert p["product"] == SLABS and p["rows"] < 256
+    assert sl.slope_spmm_fwd_plan(128, 9216, 9216)["rows"] == 256
+
+
 def test_adapter_product_regimes():
     xl = lambda b, r=128, d_in=9216: sl.slope_spmm_fwd_plan(b, d_in, 9216, r)["xl"]
     assert sl.slope_spmm_fwd_plan(64, 9216, 9216, 0)["xl"] == 0

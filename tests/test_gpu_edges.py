@@ -347,8 +347,8 @@ def test_calls_follow_the_current_stream(monkeypatch):
     (33, 8, 1856, 96, (1, 128, 64)), (34, 8, 5184, 160, (1, 128, 64)), (39, 24, 8384, 0, (1, 128, 64)), (54, 8, 8704, 32, (1, 128, 64)),
     (127, 72, 9280, 96, (1, 128, 64)), (194, 56, 7616, 0, (1, 128, 64)), (2154, 8, 6592, 0, (1, 128, 64)), (2712, 8, 6912, 32, (1, 128, 64)),
     (2747, 8, 8128, 0, (1, 128, 128)), (2719, 8, 8064, 160, (1, 128, 128)), (69, 2696, 5312, 0, (1, 128, 64)), (344, 2448, 832, 96, (2, 128, 64)),
-    (33, 9656, 3904, 0, (1, 192, 64)), (1700, 136, 7744, 96, (1, 192, 64)), (34, 5832, 10304, 0, (1, 256, 64)), (47, 7464, 9280, 96, (1, 256, 64)),
-    (134, 2584, 9664, 160, (1, 256, 128)), (135, 2696, 10304, 0, (1, 256, 128))])
+    (33, 9656, 3904, 0, (1, 192, 64)), (1700, 136, 7744, 96, (1, 192, 64)), (34, 5832, 10304, 0, (1, 192, 64)), (33, 4760, 11072, 0, (1, 256, 64)), (47, 7464, 9280, 96, (1, 256, 64)),
+    (134, 2584, 9664, 160, (1, 192, 64)), (135, 3336, 8000, 32, (1, 256, 128)), (135, 2696, 10304, 0, (1, 256, 128))])
 def test_tiles_and_slabs_of_the_sparse_product(b, d_out, d_in, r, form):
     plan = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
     assert (plan["product"], plan["rows"], plan["tokens"]) == form
