@@ -1281,7 +1281,9 @@ constexpr int64_t XL_BESIDE_BYTES = (int64_t)40 << 20;
 bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& split, XlSplit& x) {
     const int64_t groups = ((m + split.bm - 1) / split.bm) * ((n + split.bn - 1) / split.bn) * split.slabs;
     const int64_t tiles = ((n + SK_BI - 1) / SK_BI) * ((r + SK_BJ - 1) / SK_BJ);
-    if (groups + tiles > RESIDENT) return false;
+    // (each XCD gets its share of both, rounded up: one workgroup too many on one would only start after the round)
+    const int64_t idle = (RESIDENT / XCDS - (groups + XCDS - 1) / XCDS) * XCDS;
+    if (tiles > idle) return false;
     const int64_t slab_read = (m + 63) / 64 * ((n + 31) / 32 * 32) * r * 4;
     int64_t max_floats = XL_BESIDE_BYTES / slab_read * n * r;
     if (max_floats > (int64_t)(xl_small_scratch_bytes(n, K, r) / 4)) max_floats = (int64_t)(xl_small_scratch_bytes(n, K, r) / 4);
@@ -1289,9 +1291,9 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
     // the fewest slabs that take half as long as the product: the kernel after it reads them all for every 64 features
     const int most = slab_steps_of(K, split.slabs) / 2;
     for (int64_t held = n * r; held <= max_floats; held += n * r) {
-        x = xl_split(n, K, r, held, RESIDENT - groups);
+        x = xl_split(n, K, r, held, idle);
         if (x.steps <= most) return true;
-        if (x.slabs * tiles + tiles > RESIDENT - groups) break;
+        if (x.slabs * tiles + tiles > idle) break;
     }
     return x.slabs > 0 && x.steps <= 2 * most;
 }
@@ -1302,7 +1304,11 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
 // 10.7, 742, 512 x 2112 12.2, 13.8; 11.0, 487, 1216 x 2176 12.3, 13.5; 12.1, 239, 5760 x 2048 13.1, 18.1).
 constexpr double SPLIT_MIN_US = 13.5;
 // Split of the product over k within that room, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split
-// whose launch has room for X L beside its tiles saves the launches of X L (about 8 us against 3 for the larger second kernel).
+// whose launch has room for X L beside its tiles saves the launches of X L: about 8 us and their operands at 4.4 TB/s,
+// against 3 for the larger second kernel, or the time of X L, 0.8 us per chunk of 32 rows of L and wavefront, where that is the
+// longer.  (70 shapes of 33 to 512 tokens with adapters on up to 12 forms: the one chosen takes 1.0 % longer than the best from HBM;
+// priced at 8 and 3 alone 7.0 %.  us: 166 tokens, 1280 x 27008, rank 32 58 in 8 slabs of 128 x 64, X L 53 chunks; 35 in 9 of 192 x
+// 64; 264 tokens, 2048 x 14272, rank 64 61 and 39; 330 tokens, 3328 x 13568, rank 64 67 and 51.)
 SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom& room) {
     SpmmSplit best = {0, 0, 0};
     if (room.slabs < 2) return best;
@@ -1315,7 +1321,8 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
     // at most, on weights from the last-level cache 2 % (taken as they are 1.8 % and 0.1 %).  us, whole / two or three slabs from
     // HBM and from the cache: 512 tokens, 4096 x 4096 23.0 / 25.8 and 20.0 / 24.5; 700, 2112 x 4160 27.6 / 27.7 and 22.5 / 23.8;
     // 518, 2240 x 4928 30.8 / 27.8 and 24.7 / 24.1; 530, 1792 x 4864 26.9 / 20.4 and 22.3 / 18.4.
-    least = (K >= 4096 ? 1.125 : 1.0) * least + (xl ? 8.0 : 0.0);
+    const double xl_first = xl ? 8.0 + 2.0 * (double)(n + r) * (double)K / 4.4e6 : 0.0;
+    least = (K >= 4096 ? 1.125 : 1.0) * least + xl_first;
     // On tiles of bm rows, into all numbers of slabs that leave none empty.  (X L is looked at only where it decides.)
     auto consider = [&](const SpmmTile& t, bool one_round) {
         const TileCost cost = tile_cost(n, m, K, t.bm, t.bn);
@@ -1323,11 +1330,12 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
         const int most = one_round && cost.tiles * room.slabs > RESIDENT ? (int)(RESIDENT / cost.tiles) : room.slabs;
         for (int sl = 2; sl <= most; ++sl) {
             const int steps = slab_steps_of(K, sl);
-            double us = launch_us(cost, steps, sl) + 1.7 + finish * sl + (xl ? 3.0 : 0.0);
-            if (us >= least || (K / 64 + steps - 1) / steps != sl) continue;
+            double us = launch_us(cost, steps, sl) + 1.7 + finish * sl;
+            if (us + (xl ? 3.0 : 0.0) >= least || (K / 64 + steps - 1) / steps != sl) continue;
             const SpmmSplit c = {t.bm, t.bn, sl};
             XlSplit x;
-            if (xl && !slab_xl_split(n, m, K, r, c, x)) us += 5.0;
+            if (xl && slab_xl_split(n, m, K, r, c, x)) us = (us > 5.0 + 0.8 * x.steps ? us : 5.0 + 0.8 * x.steps) + 3.0;
+            else us += xl_first;
             if (us < least) { least = us; best = c; }
         }
     };

@@ -141,7 +141,7 @@ def test_split_of_a_partial_round_by_slabs():
 
 # whatever the tile: a caller that looks for code 1 finds every product that wants the workspace for slabs
 @pytest.mark.parametrize("b,d_out,d_in,r,rows", [(33, 520, 8192, 32, 128), (34, 3328, 4160, 0, 128), (38, 3072, 6400, 256, 128), (67, 4176, 4096, 0, 192),
-                                                 (64, 9216, 9216, 128, 256), (300, 2304, 5120, 160, 128)])
+                                                 (64, 9216, 9216, 128, 256), (300, 2304, 5120, 160, 192)])
 def test_every_split_product_has_one_code(b, d_out, d_in, r, rows):
     p = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
     assert (p["product"], p["rows"]) == (SLABS, rows) and p["slabs"] > 1
@@ -153,6 +153,16 @@ def test_long_weights_on_too_few_rows_of_256_are_filled_up_with_smaller_tiles():
         p = sl.slope_spmm_fwd_plan(b, d_in, d_out)
         assert p["product"] == SLABS and p["rows"] < 256
     assert sl.slope_spmm_fwd_plan(128, 9216, 9216)["rows"] == 256
+
+
+def test_adapter_beside_a_split_product_does_not_outlast_it():
+    def plan(b, d_out, d_in, r):
+        p = sl.slope_spmm_fwd_plan(b, d_in, d_out, r)
+        return p["rows"], p["tokens"], p["slabs"]
+    # in eight slabs of 128 x 64 the 16 compute units left over would take 53 chunks of X L for 56 k-steps of the product
+    assert plan(166, 1280, 27008, 0) != plan(166, 1280, 27008, 32)
+    # 234 workgroups are 30 on most XCDs: the last of 22 for X L would be a 33rd there and wait for the round to end
+    assert plan(330, 3328, 13568, 64) == (256, 128, 5)
 
 
 def test_adapter_product_regimes():
