@@ -1239,8 +1239,9 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // operand feed of a compute unit, 53 bytes per ns (a little more on the smaller tiles of the ring kernel; up to a fifth more
 // with few compute units at work), and takes longer for weight bytes that come from HBM: those that few token tiles share.
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
-// The constants are a fit to 195 shapes of 40 to 6000 tokens on weights from HBM (768 to 36864 on either side), each on
-// all tiles and up to 14 slabs: the form chosen takes 0.5 % longer than the best one over all of them, more than 10 % in 4.
+// The constants were fitted on weights from HBM; over 110 shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128
+// to 20000), each on the five tiles and four splits of least estimate, the form chosen takes 0.8 % longer than the best one in
+// the mean, more than 10 % in two.  (192 x 96 has no gain from its small tile: 77 shapes at 1.10 of the estimate, 128 x 96 at 1.09.)
 // Few tokens on many rows are no exception (us, from HBM: 64 tokens, 20480 x 1024 10.4 on 128 x 64, 13.3 on 64 x 64 tiles, several
 // to a compute unit; 36864 x 1024 13.6 on 192 x 64, 18.5 and 19.3).
 struct TileCost { int64_t tiles; double start, step, less, stream; };   // what does not depend on the slabs
@@ -1316,9 +1317,9 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
     int bm, bn;
     double least = best_tile_us(n, m, K, bm, bn);
     if (!xl && least < SPLIT_MIN_US) return best;
-    // Whole products of 64 k-steps and more take an eighth longer than estimated beside split ones, on weights from HBM: of 44
-    // shapes of 129 to 1024 tokens, k of 4096 to 10000, the form chosen takes 0.1 % longer than the better one in the mean, 8 %
-    // at most, on weights from the last-level cache 2 % (taken as they are 1.8 % and 0.1 %).  us, whole / two or three slabs from
+    // Whole products of 64 k-steps and more take an eighth longer than estimated beside split ones, on weights from HBM: over 44
+    // shapes of 129 to 1024 tokens, k of 4096 to 10000, the form chosen takes 0.2 % longer than the best measured one in the
+    // mean, 6 % at most, on weights from the last-level cache 2.4 % and 11 %.  us, whole / two or three slabs from
     // HBM and from the cache: 512 tokens, 4096 x 4096 23.0 / 25.8 and 20.0 / 24.5; 700, 2112 x 4160 27.6 / 27.7 and 22.5 / 23.8;
     // 518, 2240 x 4928 30.8 / 27.8 and 24.7 / 24.1; 530, 1792 x 4864 26.9 / 20.4 and 22.3 / 18.4.
     const double xl_first = xl ? 8.0 + 2.0 * (double)(n + r) * (double)K / 4.4e6 : 0.0;

@@ -749,12 +749,10 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 // The kernels run at the rate their compute units pull operands from L2, 53 bytes per ns (up to a fifth more with few of them
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
 // of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  Take the shape with the least
-// estimate: over 290 shapes (512 to 22000 on either side, 256 to 16000 along the contraction, operands from HBM and
-// from the caches), each on eleven tiles, it takes 0.3 % longer than the best one in the mean, 7 % at most (tiles below 192 x 192 have
-// gained another fifth since, all alike: over 90 more shapes 0.2 %, 13 % at most, and a new fit chooses no better); the rule before,
-// of 256 x 256, 256 x 128, 128 x 128 and 128 x 64 the one with the fewest rounds x rows, 5.8 to 7.7 % (gradients, us: 700
-// tokens, 4160 x 2112 20.4 -> 16.6 on 192 x 192; 752 tokens, 5120 x 6464 66.5 -> 63.9 on 256 x 192; 4096 tokens, 1024 x
-// 1024 25 -> 20 on 64 x 64).
+// estimate: over 80 shapes (400 to 16000 rows on one side, 256 to 9000 on the other, contractions of 256 to 12000), each on all
+// eight tiles, it takes 0.5 % longer than the best one in the mean, 14 % at most; a rule of fewest rounds x rows among 256 x 256,
+// 256 x 128, 128 x 128 and 128 x 64 took 5.8 to 7.7 % (gradients, us: 700 tokens, 4160 x 2112 20.4 -> 16.6 on 192 x 192; 752
+// tokens, 5120 x 6464 66.5 -> 63.9 on 256 x 192; 4096 tokens, 1024 x 1024 25 -> 20 on 64 x 64).
 static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tail) {
     int best = 0;
     double least = 1e300;
