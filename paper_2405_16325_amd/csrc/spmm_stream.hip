@@ -789,13 +789,21 @@ static int stream_waves(int64_t n, int64_t m, int64_t K) {
     return rows == 32 ? 8 : rows == 48 ? 6 : 4;
 }
 
+// rounds of one workgroup per compute unit that launch_stream's kernels take
+static int64_t stream_rounds(int64_t n, int64_t m, int64_t K) {
+    const int64_t rows = spmm_stream_rows(n, m, K);
+    return ((m + rows - 1) / rows + RESIDENT - 1) / RESIDENT;
+}
+
 // Every workgroup computes T by itself while that is one tile of columns and at most six chunks of 32 rows of L for each of
 // its wavefronts, about 1 us each at the end of its own weight rows: one launch instead of two (us, one token: 3072 x 768, rank
 // 32 8.9 -> 7.4; 3328 x 512, rank 32 7.9 -> 6.4; 1216 x 1344, rank 32 10.1 -> 8.7; but with several tiles 12 tokens, 5632 x
-// 512, rank 96 8.4 -> 9.0).
+// 512, rank 96 8.4 -> 9.0).  In one round of workgroups, that is: every further round does it again (1 token, 38336 x 1536, rank 32
+// 35.5 -> 54.2; 4, 22528 x 1536 24.8 -> 33.9; 2, 17408 x 512 13.7 -> 15.0); in two of them with one chunk at most, where the card
+// takes as long and the call a launch less (4, 13056 x 256, rank 64 11.0 -> 11.2, a call 14.2 -> 11.7; 14, 14336 x 192 11.4 -> 11.2).
 static bool xl_by_itself(int64_t n, int64_t m, int64_t K, int64_t r) {
-    const int64_t waves = stream_waves(n, m, K);
-    return r <= SK_BJ && (K / 32 + waves - 1) / waves <= 6;
+    const int64_t waves = stream_waves(n, m, K), chunks = (K / 32 + waves - 1) / waves, rounds = stream_rounds(n, m, K);
+    return r <= SK_BJ && (rounds == 1 ? chunks <= 6 : rounds == 2 && chunks <= 1);
 }
 
 // Beside the product, where X L would otherwise take two launches before it: as few slabs as take half the time of the pass over
