@@ -789,10 +789,10 @@ static int stream_waves(int64_t n, int64_t m, int64_t K) {
     return rows == 32 ? 8 : rows == 48 ? 6 : 4;
 }
 
-// rounds of one workgroup per compute unit that launch_stream's kernels take
-static int64_t stream_rounds(int64_t n, int64_t m, int64_t K) {
+// rounds of one workgroup per compute unit that launch_stream's kernels take, with `more` beside the product's
+static int64_t stream_rounds(int64_t n, int64_t m, int64_t K, int64_t more) {
     const int64_t rows = spmm_stream_rows(n, m, K);
-    return ((m + rows - 1) / rows + RESIDENT - 1) / RESIDENT;
+    return ((m + rows - 1) / rows + more + RESIDENT - 1) / RESIDENT;
 }
 
 // Every workgroup computes T by itself while that is one tile of columns and at most six chunks of 32 rows of L for each of
@@ -802,7 +802,7 @@ static int64_t stream_rounds(int64_t n, int64_t m, int64_t K) {
 // 35.5 -> 54.2; 4, 22528 x 1536 24.8 -> 33.9; 2, 17408 x 512 13.7 -> 15.0); in two of them with one chunk at most, where the card
 // takes as long and the call a launch less (4, 13056 x 256, rank 64 11.0 -> 11.2, a call 14.2 -> 11.7; 14, 14336 x 192 11.4 -> 11.2).
 static bool xl_by_itself(int64_t n, int64_t m, int64_t K, int64_t r) {
-    const int64_t waves = stream_waves(n, m, K), chunks = (K / 32 + waves - 1) / waves, rounds = stream_rounds(n, m, K);
+    const int64_t waves = stream_waves(n, m, K), chunks = (K / 32 + waves - 1) / waves, rounds = stream_rounds(n, m, K, 0);
     return r <= SK_BJ && (rounds == 1 ? chunks <= 6 : rounds == 2 && chunks <= 1);
 }
 
@@ -811,7 +811,8 @@ static bool xl_by_itself(int64_t n, int64_t m, int64_t K, int64_t r) {
 // per 32 KB (us: 1 token, 9216 x 9216, rank 128 29.1 -> 27.2; 8, 4096 x 4096, rank 64 12.8 -> 11.6; 16, 8000 x 8640, rank 64 28.5 ->
 // 25.6; 2, 17152 x 3328, rank 32 25.3 -> 22.3; without that limit 1, 512 x 26624, rank 96 26.8 -> 50.7, 32, 9216 x 9216, rank
 // 64 37.8 -> 39.3).  Not beside the row-split kernel, whose three wavefronts take 3 us and more per chunk while it saturates
-// the memory: 1, 36864 x 9216, rank 128 72.5 -> 85.3.
+// the memory: 1, 36864 x 9216, rank 128 72.5 -> 85.3.  And not where its workgroups would begin another round of the product's:
+// 8, 16384 x 16256, rank 32, 512 and 4 workgroups 72.9 -> 80.9; 1, 11776 x 18624, rank 96, 246 and 12 65.9 -> 73.0.
 static bool xl_beside(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_floats, StreamXl& xl) {
     const int64_t chunks = K / 32, waves = stream_waves(n, m, K);
     if ((chunks + SK_WAVES - 1) / SK_WAVES <= XL_STEPS || r > 128) return false;   // one slab, one launch (xl_split)
@@ -819,9 +820,11 @@ static bool xl_beside(int64_t n, int64_t m, int64_t K, int64_t r, int64_t max_fl
     const int64_t want = (chunks + waves * steps - 1) / (waves * steps), per = (chunks + want - 1) / want;
     const int64_t slabs = (chunks + per - 1) / per;
     if (slabs * n * r > max_floats || 0.17 * (double)slabs + (double)(slabs * n * r * 4) / 32e3 > 2.0) return false;
+    const int64_t groups = (r + SK_BJ - 1) / SK_BJ * slabs;
+    if (stream_rounds(n, m, K, groups) != stream_rounds(n, m, K, 0)) return false;
     xl.slabs = (int)slabs;
     xl.k_per = (int)(per * 32);
-    xl.groups = (int)(((r + SK_BJ - 1) / SK_BJ) * slabs);
+    xl.groups = (int)groups;
     return true;
 }
 

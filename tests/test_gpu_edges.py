@@ -175,8 +175,9 @@ def launches(call):
     (1, 3072, 768, 32, 1), (16, 1000, 1472, 64, 1), (5, 9224, 1088, 32, 1), (20, 520, 384, 64, 1), (31, 12296, 704, 32, 2), (31, 8184, 704, 32, 1),
     (3, 4096, 4096, 64, 2), (1, 9224, 2880, 96, 2), (2, 17160, 3264, 32, 2), (8, 16392, 2112, 128, 2), (17, 17000, 9152, 64, 2),
     (12, 16392, 2112, 128, 3), (25, 36872, 2176, 32, 3),
-    # more than one round of workgroups: not inside the product, but for a single chunk in two rounds
-    (1, 38336, 1536, 32, 3), (2, 17408, 512, 32, 2), (22, 26632, 256, 32, 2), (4, 13064, 256, 64, 1), (31, 22280, 128, 32, 1)])
+    # 252 workgroups and 12 beside them are two rounds; more than one round of workgroups: not inside the product, but for a
+    # single chunk in two rounds
+    (3, 8064, 1472, 128, 3), (1, 38336, 1536, 32, 3), (2, 17408, 512, 32, 2), (22, 26632, 256, 32, 2), (4, 13064, 256, 64, 1), (31, 22280, 128, 32, 1)])
 def test_adapter_product_in_and_beside_a_small_batch(b, d_out, d_in, r, kernels):
     check_layer(b, d_out, d_in, r, backward=False)
     gen = torch.Generator(device="cuda")
