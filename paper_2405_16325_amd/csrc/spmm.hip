@@ -1157,9 +1157,9 @@ static bool tile_kernel_fits(int64_t K) { return K % 64 == 0 && K >= 128; }
 // tokens, 1280 x 5120, 260 tiles in two rounds: 34 -> 50 us.)
 static bool one_round_of_64(int64_t n, int64_t m) { return tiles_of_64(n, m) <= RESIDENT; }
 
-static int slab_steps_of(int64_t K, int want) {               // k-steps per slab, whole quads
+static int64_t slab_steps_of(int64_t K, int want) {           // k-steps per slab, whole quads
     const int64_t quads = (K + 255) / 256;
-    return (int)((quads + want - 1) / want) * 4;
+    return (quads + want - 1) / want * 4;
 }
 
 // ---- The room for slabs: how many of them a call's scratch holds.  Sizes of scratch are part of the interface (programs keep
@@ -1290,7 +1290,7 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
     if (max_floats > (int64_t)(xl_small_scratch_bytes(n, K, r) / 4)) max_floats = (int64_t)(xl_small_scratch_bytes(n, K, r) / 4);
     if (max_floats <= 0) return false;
     // the fewest slabs that take half as long as the product: the kernel after it reads them all for every 64 features
-    const int most = slab_steps_of(K, split.slabs) / 2;
+    const int64_t most = slab_steps_of(K, split.slabs) / 2;
     for (int64_t held = n * r; held <= max_floats; held += n * r) {
         x = xl_split(n, K, r, held, idle);
         if (x.steps <= most) return true;
@@ -1330,8 +1330,8 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
         const double finish = 0.12 + 8.0 * (double)n * (double)m / 4.84e6;  // the second launch, per slab
         const int most = one_round && cost.tiles * room.slabs > RESIDENT ? (int)(RESIDENT / cost.tiles) : room.slabs;
         for (int sl = 2; sl <= most; ++sl) {
-            const int steps = slab_steps_of(K, sl);
-            double us = launch_us(cost, steps, sl) + 1.7 + finish * sl;
+            const int64_t steps = slab_steps_of(K, sl);
+            double us = launch_us(cost, (double)steps, sl) + 1.7 + finish * sl;
             if (us + (xl ? 3.0 : 0.0) >= least || (K / 64 + steps - 1) / steps != sl) continue;
             const SpmmSplit c = {t.bm, t.bn, sl};
             XlSplit x;
@@ -1360,7 +1360,7 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
 
 hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m,
                              int64_t K, const SlabAdapter& ad, const SpmmSplit& split, bf16_t* C, float* slabs, hipStream_t s) {
-    const int slab_steps = slab_steps_of(K, split.slabs);
+    const int slab_steps = (int)slab_steps_of(K, split.slabs);
     const int nslabs = (int)((K / 64 + slab_steps - 1) / slab_steps);       // <= split.slabs
     const SplitJob job = {nslabs, slab_steps, slabs, ad.T ? nullptr : ad.L, ad.Q, (int)ad.r, ad.x.k_per, ad.x.slabs};
     const bf16_t* A2 = ad.T ? ad.R : nullptr;                 // as stored, k-major

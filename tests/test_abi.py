@@ -42,6 +42,14 @@ def test_size_queries():
     assert ws >= 2 * 64 * (2048 + 768 + 3072) and ws % 256 == 0
 
 
+def test_size_queries_take_any_extents():
+    # beyond 2^31 no call accepts them, and a query still answers (one divided by a truncated number of k-steps)
+    lib = binding.lib()
+    for b, d_in, d_out, r in [(500, 1 << 40, 512, 0), (500, 1 << 40, 512, 64), (1000, 1 << 40, 4096, 64), (500, 512, 1 << 40, 64), (1 << 31, 1 << 31, 1 << 31, 0)]:
+        assert lib.slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) >= 0
+        assert lib.slope_workspace_bytes(binding.SLOPE_CALL_SPMM_BWD_X_WS, b, d_out, d_in, 0) >= 0
+
+
 def test_argument_errors_are_reported_before_launch():
     lib = binding.lib()
     p = ctypes.c_void_p(0x1000)       # aligned, never dereferenced: every call below must fail first
