@@ -189,9 +189,9 @@ slope_status slope_spmm_bwd_x_ws(const void* dY, int64_t b, const void* WrcT_val
  *   dW_vals out bf16[d_out, d_in/2]; fp32 accumulation.
  * No scratch memory: the operands are read as stored, tokens being their slow index.
  *
- * slope_wgrad_masked_ws - the same result (up to fp32 summation order) through token-contiguous copies
- * of X and dY in the caller's workspace, which is what large layers should use: the product then runs at
- * the rate of the other tile kernels.
+ * slope_wgrad_masked_ws - the same result (up to fp32 summation order) with scratch memory, which is what
+ * large layers should use: the tiles that a last, partly filled round of the chip would hold are cut (see
+ * below), and an operand of a wide layer is copied token-contiguous where the product then runs faster.
  *   workspace  slope_workspace_bytes(SLOPE_CALL_WGRAD_MASKED_WS, b, d_in, d_out, 0) bytes
  *
  * Layers that share an operand (q, k and v share X) need its copy only once:

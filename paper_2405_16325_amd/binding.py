@@ -291,8 +291,8 @@ def _wgrad_args(dY, X, meta, out):
 
 def slope_wgrad_masked(dY: torch.Tensor, X: torch.Tensor, meta: torch.Tensor, out=None, workspace="auto"):
     """dW = dY^T X at W^R's kept positions, packed bf16[d_out, d_in/2].
-    workspace: None = slope_wgrad_masked (no scratch, in-place kernel); a uint8 device tensor or "auto"
-    (allocated here) = slope_wgrad_masked_ws (token-contiguous copies in the workspace)."""
+    workspace: None = slope_wgrad_masked (no scratch); a uint8 device tensor or "auto" (allocated here) =
+    slope_wgrad_masked_ws (the tiles of a last partial round cut, an operand of wide layers copied)."""
     b, d_in, d_out, G = _wgrad_args(dY, X, meta, out)
     if workspace is None:
         _check("slope_wgrad_masked", lib().slope_wgrad_masked(_ptr(dY), _ptr(X), b, _ptr(meta), d_out, d_in, _ptr(G),

@@ -84,9 +84,10 @@ hipError_t launch_spmm_stream(const bf16_t* B, int64_t n, const bf16_t* A_vals, 
 bool launch_spmm_stream_adapter(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
                                 const bf16_t* L, const bf16_t* R, int64_t r, bf16_t* C, float* Q, float* P, size_t p_bytes,
                                 bool sliced, hipStream_t s, hipError_t& e);
-// T[n, r] = X[n, K] * Lt[r, K]^T (dense tile kernel) for many tokens, with the k-contiguous copy Lt of L
-hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
-                                  bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s);
+// T[n, r] = B[n, K] A (A k-major [K][r], the factor L) or B A^T (A [r][K], the factor R) on the dense tile kernels, K % 64 == 0;
+// partial_bytes of scratch allow a split over K
+hipError_t launch_skinny_factor(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
+                                float* partial_or_null, size_t partial_bytes, hipStream_t s);
 // C[n, m] = sum_k B(i, k) * A(j, k) for the skinny adapter products of layers whose extents are not multiples of 64, or
 // which are short (skinny_is_short, skinny_pair_is_short):
 // an operand is k-contiguous [rows][ld] (K % 8 == 0) or k-major [K][ld] (rows % 8 == 0); m % 8 == 0.
@@ -104,10 +105,12 @@ bool skinny_pair_is_short(int64_t n, int64_t m, int64_t K);
 hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s);                           // B k-contiguous
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s);    // B's k-contiguous, A k-major; A k-contiguous
 hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s); // all operands k-major
-// out[c][r] = in[r][c]: in [rows][cols], rows % 64 == 0, cols % 8 == 0
-hipError_t launch_transpose(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, hipStream_t s);
-hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out,
-                               int64_t d_in, bf16_t* gvals, hipStream_t s);
+// dW from operands as stored; Xt, dYt: scratch of token_copy_bytes each for copies that it may make, or null; tail: see
+// launch_wgrad_masked_t.  launch_wgrad_wide: extents from 2^24 on
+hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in,
+                               bf16_t* gvals, bf16_t* Xt, bf16_t* dYt, float* tail_or_null, hipStream_t s);
+hipError_t launch_wgrad_wide(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in,
+                             bf16_t* gvals, hipStream_t s);
 // the same result from token-contiguous copies Xt [d_in][ld], dYt [d_out][ld] (ld = the pitch behind
 // token_copy_bytes); launch_token_copies writes one or two such copies (in1 == nullptr: one)
 size_t token_copy_bytes(int64_t b, int64_t d);
@@ -120,12 +123,9 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out);
 hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b, const uint8_t* meta, int64_t d_out,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s);
 
-// C[n, m] = B[n, K] * A[m, K]^T (dense bf16, fp32 accumulation, row pitch ld of both operands), K % 64 == 0, one of n
-// and m an adapter's rank; partial_bytes of scratch allow a split over K
 size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m);
-hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, int64_t ld, bf16_t* C,
-                                 float* partial_or_null, size_t partial_bytes, hipStream_t s);
 int dense_tn_plain_slabs(int64_t n, int64_t m, int64_t K, size_t partial_bytes);   // of the call above
+// C[n, m] = B[n, K] * A[m, K]^T (dense bf16, fp32 accumulation), K % 64 == 0
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s);
 // general N:M magnitude mask (M in {2, 4, 8}); axis 0: groups inside a row, axis 1: inside a column

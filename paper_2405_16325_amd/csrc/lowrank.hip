@@ -72,12 +72,3 @@ hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s) {
 hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s) {
     return launch_skinny_pair<true, true, true, true>(dl, dr, s);
 }
-
-hipError_t launch_lowrank_prepare(const bf16_t* X, int64_t n, int64_t d_in, const bf16_t* L, int64_t r, bf16_t* T,
-                                  bf16_t* Lt, float* partial_or_null, size_t partial_bytes, hipStream_t s) {
-    // L[d_in, r] -> Lt[r, d_in] (16-byte accesses on both sides: 5120 x 64 7.8 -> 4.6 us against 2-byte ones)
-    hipError_t e = launch_transpose(L, d_in, r, Lt, s);
-    if (e != hipSuccess) return e;
-    // T[n, r] = X[n, d_in] * Lt[r, d_in]^T
-    return launch_dense_tn_plain(X, n, Lt, r, d_in, d_in, T, partial_or_null, partial_bytes, s);
-}

@@ -30,7 +30,7 @@ inline bool bad_rank(int64_t r) { return r % 32 != 0 || r > 512; }
 
 inline size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// [ T | Lt | partial sums of X L ] when adapters are active, then the slab buffer of the split over K
+// [ T | as many bytes as L | partial sums of X L ] when adapters are active, then the slab buffer of the split over K
 size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     (void)d_out;
     if (r <= 0) return 0;
@@ -75,12 +75,10 @@ bool xl_is_short(int64_t n, int64_t r, int64_t d_in) { return skinny_is_short(n,
 // stored) instead of [r][K].  Whole k-steps of 64 go to the tile kernels, anything else and short products to the kernel
 // for ragged extents.
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
-                          bf16_t* At_scratch, float* partial, hipStream_t s) {
+                          float* partial, hipStream_t s) {
     if (K % 64 != 0 || (a_kmajor ? xl_is_short(n, r, K) : skinny_is_short(n, r, K, 5, RESIDENT)))
         return launch_skinny_ragged({B, K, A, a_kmajor ? r : K, a_kmajor, n, r, K, T}, s);
-    const size_t partial_bytes = partial ? dense_tn_plain_partial_bytes(n, r) : 0;
-    if (a_kmajor) return launch_lowrank_prepare(B, n, K, A, r, T, At_scratch, partial, partial_bytes, s);
-    return launch_dense_tn_plain(B, n, A, r, K, K, T, partial, partial_bytes, s);
+    return launch_skinny_factor(B, n, K, A, a_kmajor, r, T, partial, partial ? dense_tn_plain_partial_bytes(n, r) : 0, s);
 }
 
 }  // namespace
@@ -217,8 +215,7 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
     const bf16_t* R = adapter ? (const bf16_t*)R_or_null : nullptr;
     if (!adapter) r = 0;
     uint8_t* after = ws + adapter_workspace_bytes(b, d_in, d_out, r);      // the slabs or slices of the product
-    bf16_t* Lt = (bf16_t*)(ws + round256((size_t)b * r * 2));
-    float* sums = (float*)((uint8_t*)Lt + round256((size_t)d_in * r * 2));
+    float* sums = (float*)(ws + round256((size_t)b * r * 2) + round256((size_t)d_in * r * 2));
     const bool few = spmm_stream_fits(b, d_in);
     // With scratch memory a batch of a few dozen to a few hundred tokens is split over K as well, and up to
     // XL_SMALL_MAX_TOKENS of them the kernel that adds the slabs adds the adapter term too, straight from the sums of T = X L,
@@ -229,7 +226,7 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
         return finish(launch_spmm_slabs(x_in, b, wv, wm, d_out, d_in, ad, split, (bf16_t*)Y, (float*)after, s));
     float* const slices = few && workspace && spmm_rows_partial_bytes(b, d_out, d_in) ? (float*)after : nullptr;
     if (few && adapter) {
-        // X L beside the one pass over the weight, or inside it (T and Lt are not needed then: their room holds the sums)
+        // X L beside the one pass over the weight, or inside it (T is not needed then: the room before the sums is free)
         hipError_t e;
         if (launch_spmm_stream_adapter(x_in, b, wv, wm, d_out, d_in, l, R, r, (bf16_t*)Y, sums, (float*)ws,
                                        (size_t)((uint8_t*)sums - ws), slices != nullptr, s, e))
@@ -242,7 +239,7 @@ static slope_status spmm_fwd_run(const void* X, int64_t b, const void* Wr_vals, 
             e = launch_xl(x_in, b, d_in, l, r, x, x.slabs > 1 ? sums : nullptr, T, s);
             if (e == hipSuccess && x.slabs > 1) e = launch_xl_reduce(sums, x.slabs, b, r, T, s);
         } else {
-            e = skinny_product(x_in, b, d_in, l, true, r, T, Lt,
+            e = skinny_product(x_in, b, d_in, l, true, r, T,
                                b > XL_SMALL_MAX_TOKENS && dense_tn_plain_partial_bytes(b, r) ? sums : nullptr, s);
         }
         if (e != hipSuccess) return finish(e);
@@ -365,7 +362,7 @@ slope_status slope_wgrad_masked(const void* dY, const void* X, int64_t b, const 
     if (misaligned(dY, 16) || misaligned(X, 16) || misaligned(Wr_meta, 16) || misaligned(dW_vals, 16))
         return SLOPE_ERR_ALIGN;
     return finish(launch_wgrad_masked((const bf16_t*)dY, (const bf16_t*)X, b, (const uint8_t*)Wr_meta, d_out, d_in,
-                                      (bf16_t*)dW_vals, (hipStream_t)stream));
+                                      (bf16_t*)dW_vals, nullptr, nullptr, nullptr, (hipStream_t)stream));
 }
 
 slope_status slope_wgrad_masked_ws(const void* dY, const void* X, int64_t b, const void* Wr_meta, int64_t d_out,
@@ -377,18 +374,13 @@ slope_status slope_wgrad_masked_ws(const void* dY, const void* X, int64_t b, con
         misaligned(workspace, 256))
         return SLOPE_ERR_ALIGN;
     if (workspace_bytes < slope_wgrad_workspace_bytes(b, d_in, d_out)) return SLOPE_ERR_WORKSPACE;
-    hipStream_t s = (hipStream_t)stream;
-    if (!wgrad_tn_fits(d_in))                                 // the packed epilogue of the tile kernels reads metadata by dwords
-        return finish(launch_wgrad_masked((const bf16_t*)dY, (const bf16_t*)X, b, (const uint8_t*)Wr_meta, d_out, d_in,
-                                          (bf16_t*)dW_vals, s));
     bf16_t* Xt = (bf16_t*)workspace;
     bf16_t* dYt = (bf16_t*)((uint8_t*)workspace + slope_token_copy_bytes(b, d_in));
     float* tail = slope_wgrad_t_workspace_bytes(b, d_in, d_out)
                       ? (float*)((uint8_t*)workspace + slope_token_copy_bytes(b, d_in) + slope_token_copy_bytes(b, d_out))
                       : nullptr;
-    hipError_t e = launch_token_copies((const bf16_t*)X, d_in, Xt, (const bf16_t*)dY, d_out, dYt, b, s);
-    if (e != hipSuccess) return finish(e);
-    return finish(launch_wgrad_masked_t(dYt, Xt, b, (const uint8_t*)Wr_meta, d_out, d_in, (bf16_t*)dW_vals, tail, s));
+    return finish(launch_wgrad_masked((const bf16_t*)dY, (const bf16_t*)X, b, (const uint8_t*)Wr_meta, d_out, d_in, (bf16_t*)dW_vals,
+                                      Xt, dYt, tail, (hipStream_t)stream));
 }
 
 slope_status slope_transpose_tokens(const void* A, int64_t b, int64_t d, void* At, size_t At_bytes, void* stream) {
@@ -428,7 +420,7 @@ slope_status slope_spmm_bwd_x_adapter(const void* dY, int64_t b, const void* Wrc
     bf16_t* T2 = (bf16_t*)workspace;                          // dY R^T, bf16[b, r]
     float* partial = dense_tn_plain_partial_bytes(b, r)
                          ? (float*)((uint8_t*)workspace + round256((size_t)b * r * 2)) : nullptr;
-    hipError_t e = skinny_product((const bf16_t*)dY, b, d_out, (const bf16_t*)R, false, r, T2, nullptr, partial, s);
+    hipError_t e = skinny_product((const bf16_t*)dY, b, d_out, (const bf16_t*)R, false, r, T2, partial, s);
     if (e != hipSuccess) return finish(e);
     // sparse rows = d_in, contraction over d_out, then r more k-steps on T2 and L (K-contiguous as stored)
     return finish(launch_spmm((const bf16_t*)dY, b, (const bf16_t*)WrcT_vals, (const uint8_t*)WrcT_meta, d_in, d_out,

@@ -1,25 +1,24 @@
-// slope_wgrad_masked with a workspace: dW = dY^T X (Eq. 5) as a token-contiguous dense MFMA
-// product, with the prune-and-compress step of Algorithm 1 line 13 folded into the epilogue.
+// Dense products on MFMA tiles: the weight gradient dW = dY^T X (Eq. 5) with the prune-and-compress step of Algorithm 1
+// line 13 folded into the epilogue, the skinny products of the adapters, products of masked dense weights.
 //
-// The contraction runs over the b tokens, the slow index of both operands in memory.  Feeding the
-// MFMA straight from [token][feature] slabs needs the transposing LDS read, which delivers only a
-// quarter of the LDS bandwidth of ds_read_b128 and caps the kernel near half the MFMA peak.  So
-// the operands are first copied once into token-contiguous form in the caller's workspace
+// The contraction of the gradients runs over the b tokens, the slow index of both operands in memory, and the tiles read
+// them as they are stored: [token][feature] panels in LDS, fragments through the transposing LDS read (dense.h).  Only
+// where the matrix pipes would wait for those reads are operands copied into token-contiguous form first (wgrad_copies),
+// and callers that share an operand between layers may make such copies themselves:
 //     Xt [d_in ][ld],  dYt[d_out][ld],   bp = b rounded up to 64, the tail zero-filled,
 //     ld = row pitch: bp, plus one 128-byte line where bp * 2 is a multiple of 4 KiB (rows that
 //     far apart crowd the same L2 channels: the padded pitch is 2-3 % faster at b = 16384)
-// (two HBM streams, a few percent of the product's time at LLM layer sizes), and the product
-//     D[i, j] = sum_t Xt[i, t] * dYt[j, t]
-// runs with the same machinery as the sparse kernels: 8 wavefronts in two groups half a k-step
-// apart, global -> LDS loads of full 128-byte lines (8 rows x 128 B per instruction, 16-byte chunks
-// rotated by (row / 2) % 8), conflict-free ds_read_b128 in MFMA order, v_mfma_f32_16x16x32_bf16.
+// The product
+//     D[i, j] = sum_t X[t, i] * dY[t, j]
+// runs with the same machinery as the sparse kernels: 8 wavefronts in two groups half a k-step apart, global -> LDS loads of
+// full 128-byte lines, conflict-free LDS reads in MFMA order, v_mfma_f32_16x16x32_bf16.
 // D rows are d_in and D columns d_out, so a lane's four accumulators (column l%16, rows
 // 4*(l/16) .. +3) are exactly one group of four of W^R's row: the epilogue picks two of them with
 // the group's metadata nibble and stores one 4-byte pair of the packed gradient.
 #include <cmath>
 #include <numeric>
 
-#include "pipeline.h"
+#include "dense.h"
 
 namespace {
 
@@ -88,6 +87,19 @@ struct TnSmem {
 constexpr int TN_THREADS = 512;
 enum { EPI_MASKED_PACKED = 0, EPI_PLAIN = 1 };
 
+// Metadata of the 32 columns of W^R from c (a multiple of 32) of row o; columns outside the matrix: any.  Rows of a multiple of 32
+// columns are read by dwords, others by bytes.
+__device__ __forceinline__ uint32_t meta_dword(const uint8_t* __restrict__ meta, int o, int c, int m, int n) {
+    const uint8_t* p = meta + (size_t)o * (m / 8) + c / 8;
+    if (o >= n) return 0u;
+    if (m % 32 == 0) return c < m ? *(const uint32_t*)p : 0u;  // uniform
+    uint32_t w = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (c + 8 * e < m) w |= (uint32_t)p[e] << (8 * e);
+    return w;
+}
+
 // Masked, packed epilogue: acc[i][j] of a wavefront is the 16 x 16 fragment at D rows c0 + 16 i (d_in) and D
 // columns o0 + 16 j (d_out).  A lane's four accumulators are one group of four along d_in of row o: the
 // group's metadata nibble picks the two that W^R keeps.  Stored straight from the registers a pair is a
@@ -102,7 +114,7 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     constexpr int WM = MF * 16;
     constexpr int CP = BMT + 16;                              // bytes per staged row of pairs: 16 rows x 4 lanes x 4 B
                                                               // of one store fall on 64 different banks
-    const size_t mpitch = (size_t)m / 8, gpitch = (size_t)m / 2;
+    const size_t gpitch = (size_t)m / 2;
     __syncthreads();                                          // every wavefront is done with the rings
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
@@ -111,7 +123,7 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
         uint32_t mw[WM / 32];
 #pragma unroll
         for (int q = 0; q < WM / 32; ++q)
-            mw[q] = o < n && c0 + 32 * q < m ? *(const uint32_t*)(meta + (size_t)o * mpitch + c0 / 8 + 4 * q) : 0u;
+            mw[q] = meta_dword(meta, o, c0 + 32 * q, m, n);
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
             int gl = i * 4 + lq;                              // group index inside the WM columns
@@ -127,8 +139,8 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
         }
     }
     __syncthreads();
-    // 16-byte pieces (four pairs = sixteen columns of W), all read from LDS before the first is stored; the layers
-    // that come here have d_in % 32 == 0, so a piece is inside the row or outside as a whole
+    // 16-byte pieces (four pairs = sixteen columns of W), all read from LDS before the first is stored; where rows are not a
+    // multiple of 16 columns they leave in halves, each inside the row or outside as a whole
     constexpr int PPR = BMT / 16, PIECES = BNT * PPR, PER_THREAD = (PIECES + TN_THREADS - 1) / TN_THREADS;
     constexpr bool EVEN = PIECES % TN_THREADS == 0;           // else the last round of pieces is for the first threads only
     u32x4 piece[PER_THREAD];
@@ -141,7 +153,14 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     for (int u = 0; u < PER_THREAD; ++u) {
         const int idx = (int)threadIdx.x + u * TN_THREADS;
         const int o = tile_o0 + idx / PPR, col = tile_c0 + (idx % PPR) * 16;
-        if ((EVEN || idx < PIECES) && o < n && col < m) *(u32x4*)(out + (size_t)o * gpitch + (col >> 1)) = piece[u];
+        if ((!EVEN && idx >= PIECES) || o >= n || col >= m) continue;
+        bf16_t* const dst = out + (size_t)o * gpitch + (col >> 1);
+        if (m % 16 == 0) {                                    // uniform
+            *(u32x4*)dst = piece[u];
+        } else {
+            *(u32x2*)dst = (u32x2){piece[u][0], piece[u][1]};
+            if (col + 8 < m) *(u32x2*)(dst + 4) = (u32x2){piece[u][2], piece[u][3]};
+        }
     }
 }
 
@@ -166,10 +185,9 @@ __device__ __forceinline__ void store_sums(const f32x4 (&acc)[MF][NF], int m, in
 // NS = ring depth: loads run NS - 1 k-steps ahead.  Two stages are all that fits beside a 256 x 256
 // tile; small tiles (memory-bound skinny products) take a deeper ring to cover the HBM latency.
 // Every thread of the workgroup must make the call; wavefront w holds the fragments at rows w % 2 * BM / 2, columns w / 2 * BN / 4.
-template <int BM, int BN, int NS>
-__device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int m, int lda, const bf16_t* __restrict__ Bt, int n,
-                                              int ldb, int ksteps, int k_begin, int k_end, int m0, int n0, uint8_t* smem,
-                                              f32x4 (&acc)[BM / 32][BN / 64]) {
+template <int BM, int BN, int NS, bool AKM, bool BKM>
+__device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const DenseOperand& Bt, int ksteps, int k_begin, int k_end, int m0,
+                                              int n0, uint8_t* smem, f32x4 (&acc)[BM / 32][BN / 64]) {
     using S = TnSmem<BM, BN, NS>;
     constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront (2 x 4 waves)
     constexpr int LD_A = BM / 64, LD_B = BN / 64;            // 1 KiB loads per wavefront per step
@@ -177,40 +195,16 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int group = wave >> 2;
-    const int wm = wave & 1, wn = wave >> 1;
-    const int l16 = lane & 15, lq = lane >> 4;
-
-    // loader lanes: 8 lanes per row, chunk rotated by (row / 2) % 8 (rows past the end wrapped, never stored)
-    const uint8_t* a_src[LD_A];
-    const uint8_t* b_src[LD_B];
-#pragma unroll
-    for (int i = 0; i < LD_A; ++i) {
-        int rl = (wave * LD_A + i) * 8 + (lane >> 3);
-        int ra = wrap_row(m0 + rl, m);
-        a_src[i] = (const uint8_t*)At + (size_t)ra * lda * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16);
-    }
-#pragma unroll
-    for (int i = 0; i < LD_B; ++i) {
-        int rl = (wave * LD_B + i) * 8 + (lane >> 3);
-        int rb = wrap_row(n0 + rl, n);
-        b_src[i] = (const uint8_t*)Bt + (size_t)rb * ldb * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16);
-    }
+    DenseLoader<AKM, BKM, BM, BM / 2> opa;
+    DenseLoader<BKM, AKM, BN, BN / 4> opb;
+    opa.init(At, m0, (wave & 1) * (BM / 2), wave, lane, 0, ksteps, smem);
+    opb.init(Bt, n0, (wave >> 1) * (BN / 4), wave, lane, 0, ksteps, smem);
     auto issue = [&](int ks, int at) {                       // k-step ks (clamped) into the stage at byte `at`
-        int kc = ks < ksteps ? ks : ksteps - 1;
-        uint8_t* st = smem + at;
 #pragma unroll
-        for (int i = 0; i < LD_A; ++i) dma16(a_src[i] + (size_t)kc * 128, st + (wave * LD_A + i) * 1024);
+        for (int i = 0; i < LD_A; ++i) opa.load(ks, i, smem, at, wave);
 #pragma unroll
-        for (int i = 0; i < LD_B; ++i)
-            dma16(b_src[i] + (size_t)kc * 128, st + S::A_BYTES + (wave * LD_B + i) * 1024);
+        for (int i = 0; i < LD_B; ++i) opb.load(ks, i, smem, at + S::A_BYTES, wave);
     };
-
-    // reader lanes: fragment f = rows 16f .. 16f+15 = 2 KiB; lane (l16, lq) wants chunk 4h + lq
-    const int sw = (l16 >> 1) & 7;
-    const int rd0 = l16 * 128 + ((lq ^ sw) * 16);
-    const int rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);
-    const int a_rd = (wm * MF) * 2048;
-    const int b_rd = S::A_BYTES + (wn * NF) * 2048;
 
 #pragma unroll
     for (int i = 0; i < MF; ++i)
@@ -224,16 +218,11 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
     // step s + 1.
 #define TN_STEP(G)                                                                                     \
     {                                                                                                  \
-        const uint8_t* st = smem + at;                                                                 \
+        const auto sa = opa.stage(smem, at);                                                           \
+        const auto sb = opb.stage(smem, at + S::A_BYTES);                                              \
         BFrag af[MF], bf[NF];                                                                          \
-        _Pragma("unroll") for (int i = 0; i < MF; ++i) {                                               \
-            af[i].u[0] = *(const u32x4*)(st + a_rd + i * 2048 + rd0);                                  \
-            af[i].u[1] = *(const u32x4*)(st + a_rd + i * 2048 + rd1);                                  \
-        }                                                                                              \
-        _Pragma("unroll") for (int j = 0; j < NF; ++j) {                                               \
-            bf[j].u[0] = *(const u32x4*)(st + b_rd + j * 2048 + rd0);                                  \
-            bf[j].u[1] = *(const u32x4*)(st + b_rd + j * 2048 + rd1);                                  \
-        }                                                                                              \
+        _Pragma("unroll") for (int i = 0; i < MF; ++i) af[i] = opa.frag(sa, i);                        \
+        _Pragma("unroll") for (int j = 0; j < NF; ++j) bf[j] = opb.frag(sb, j);                        \
         if (G == 0) issue(ks + NS - 1, at == 0 ? LAST : at - S::STAGE);                                \
         /* all LDS reads of this stage have returned before anybody may overwrite it */                \
         WAIT_HERE(waitcnt_imm(G == 1 ? AHEAD : 63, 0));                                                \
@@ -276,10 +265,8 @@ __device__ __forceinline__ void dense_tn_sums(const bf16_t* __restrict__ At, int
 // D[i, j] = sum_k At[i, k] * Bt[j, k];  At: m rows, Bt: n rows, both of pitch ld elements; kp % 64 == 0.
 //   EPI_MASKED_PACKED: out = packed gradient [n][m/2] selected by meta (u8[n][m/8])
 //   EPI_PLAIN        : out = bf16 [n][m]  (row j, four consecutive i per lane)
-template <int BM, int BN, int EPI, int NS>
-__global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(const bf16_t* __restrict__ At, int m,
-                                                              const bf16_t* __restrict__ Bt, int n, int kp,
-                                                              int ld, const uint8_t* __restrict__ meta,
+template <int BM, int BN, int EPI, int NS, bool AKM, bool BKM>
+__global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(DenseOperand At, DenseOperand Bt, int ksteps, const uint8_t* __restrict__ meta,
                                                               bf16_t* __restrict__ out, int tiles_m, int tiles_n) {
     using S = TnSmem<BM, BN, NS>;
     constexpr int MF = BM / 32, NF = BN / 64;
@@ -288,8 +275,9 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(const bf16_t* __re
     if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
     const int m0 = tm * BM, n0 = tn * BN, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / 4);
+    const int m = At.rows, n = Bt.rows;
     f32x4 acc[MF][NF];
-    dense_tn_sums<BM, BN, NS>(At, m, ld, Bt, n, ld, kp / 64, 0, kp / 64, m0, n0, smem, acc);
+    dense_tn_sums<BM, BN, NS, AKM, BKM>(At, Bt, ksteps, 0, ksteps, m0, n0, smem, acc);
     if constexpr (EPI == EPI_PLAIN) {
         static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
         store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, m, n, l16, lq, out, smem, m0, n0);
@@ -299,49 +287,43 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(const bf16_t* __re
     }
 }
 
-// The skinny products of the adapters, one or two in a launch (no workgroups: none): D as above, bf16 [n][m], or, of an A of
-// `valid` rows only, with zeros in the columns from there on, or fp32 sums of slabs of the contraction for skinny_sum_kernel.  One of the sides is the rank, in tiles of RANK
-// rows, the other in tiles of LONG; FLIP: the rank is the side m.  grid: workgroups per slab, a multiple of 8.
+// The skinny products of the adapters, one or two in a launch (no workgroups: none): D as above, bf16 [n][m], or fp32 sums of
+// slabs of the contraction for skinny_sum_kernel.  One of the sides is the rank, in tiles of RANK rows, the other in tiles of
+// LONG; FLIP: the rank is the side m.  grid: workgroups per slab, a multiple of 8.  Operands are read as they are stored:
+//   the factors   (GRADIENTS false): T = X L with L k-major, T2 = dY R^T, both operands k-contiguous; the rank is m in both;
+//   the gradients (GRADIENTS true):  dL = X^T T2 (rank m) and dR = T^T dY (rank n), contractions over the tokens, all k-major.
 struct SkinnyJob {
-    const bf16_t *A, *B;
-    int m, n, lda, ldb, ksteps, valid;
+    DenseOperand A, B;
+    int ksteps;
     bf16_t* out;
     float* sums;
     int tiles_m, tiles_n, grid, slabs, slab_steps;
 };
 
-template <int BM, int BN, int NS>
+template <int BM, int BN, int NS, bool AKM, bool BKM>
 __device__ __forceinline__ void skinny_tn_tile(const SkinnyJob& j, int w, uint8_t* smem) {
     using S = TnSmem<BM, BN, NS>;
     constexpr int MF = BM / 32, NF = BN / 64;
-    const int slab = w / j.grid;
+    const int slab = w / j.grid, m = j.A.rows, n = j.B.rows;
     int tm, tn;
     if (!tile_of_index(w % j.grid, j.tiles_m, j.tiles_n, tm, tn)) return;
     const int m0 = tm * BM, n0 = tn * BN, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / 4);
     const int k_begin = slab * j.slab_steps, k_end = min(k_begin + j.slab_steps, j.ksteps);
     f32x4 acc[MF][NF];
-    dense_tn_sums<BM, BN, NS>(j.A, j.valid, j.lda, j.B, j.n, j.ldb, j.ksteps, k_begin, k_end, m0, n0, smem, acc);
-    if (j.valid < j.m) {                                      // uniform
-#pragma unroll
-        for (int i = 0; i < MF; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (mw + i * 16 + lq * 4 + e >= j.valid)
-#pragma unroll
-                    for (int q = 0; q < NF; ++q) acc[i][q][e] = 0.f;
-    }
+    dense_tn_sums<BM, BN, NS, AKM, BKM>(j.A, j.B, j.ksteps, k_begin, k_end, m0, n0, smem, acc);
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
-    if (j.slabs > 1) store_sums<MF, NF>(acc, j.m, j.n, mw, nw, l16, lq, j.sums + (size_t)slab * j.n * j.m);
-    else store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, j.m, j.n, l16, lq, j.out, smem, m0, n0);
+    if (j.slabs > 1) store_sums<MF, NF>(acc, m, n, mw, nw, l16, lq, j.sums + (size_t)slab * n * m);
+    else store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, m, n, l16, lq, j.out, smem, m0, n0);
 }
 
-template <int LONG, int RANK, int NS, bool FLIP0, bool FLIP1>
+template <int LONG, int RANK, int NS, bool GRADIENTS>
 __global__ void __launch_bounds__(TN_THREADS) skinny_tn_kernel(SkinnyJob j0, SkinnyJob j1) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int w = (int)blockIdx.x, first = j0.grid * j0.slabs;
-    if (w < first) skinny_tn_tile<FLIP0 ? RANK : LONG, FLIP0 ? LONG : RANK, NS>(j0, w, smem);
-    else skinny_tn_tile<FLIP1 ? RANK : LONG, FLIP1 ? LONG : RANK, NS>(j1, w - first, smem);
+    if (w < first) skinny_tn_tile<RANK, LONG, NS, true, GRADIENTS>(j0, w, smem);
+    else if (GRADIENTS) skinny_tn_tile<LONG, RANK, NS, true, true>(j1, w - first, smem);
+    else skinny_tn_tile<RANK, LONG, NS, false, false>(j1, w - first, smem);
 }
 
 // out = sum over the slabs (in slab order: runs are bit-identical), rounded to bf16; four elements per lane, one or two outputs
@@ -398,10 +380,9 @@ struct SplitSmem {
 struct TailPlan { int first_tile, tiles, bundle, lanes_per_xcd, lanes, share, row, aligned, parts; double steps; };
 constexpr TailPlan NO_TAIL = {0, 0, 1, 1, 0, 1, 1, 1, 0, 0.0};
 
-template <int EPI, bool TAIL>
-__global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t* __restrict__ At, int m,
-                                                                    const bf16_t* __restrict__ Bt, int n, int kp,
-                                                                    int ld, const uint8_t* __restrict__ meta,
+template <int EPI, bool TAIL, bool AKM, bool BKM>
+__global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(DenseOperand At, DenseOperand Bt, int all_steps,
+                                                                    const uint8_t* __restrict__ meta,
                                                                     bf16_t* __restrict__ out, int tiles_m,
                                                                     int tiles_n, TailPlan tail,
                                                                     f32x4* __restrict__ partial) {
@@ -409,7 +390,8 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_split_kernel(const bf16_t
     constexpr int MF = 8, NF = 4, WM = 128;                  // wavefront tile 128 x 64, 2 x 4 wavefronts
     extern __shared__ __align__(16) uint8_t smem[];
 
-    int tm, tn, k_first = 0, ksteps = kp / 64;
+    const int m = At.rows, n = Bt.rows;
+    int tm, tn, k_first = 0, ksteps = all_steps;
     // TAIL: this workgroup's lane and its tile in a bundle; [at, at_end) the k-steps of the lane's share that are left
     const int slot = (int)blockIdx.x / XCDS, member = slot % tail.bundle;
     const int lane_id = ((int)blockIdx.x % XCDS) * tail.lanes_per_xcd + slot / tail.bundle;
@@ -419,8 +401,8 @@ next_part:
     if (TAIL) {
         const int c = at / tail.row, tile = c * tail.bundle + member;
         k_first = at - c * tail.row;
-        if (tile >= tail.tiles || k_first >= kp / 64) return; // the end of the row, or a member the last bundle does not have
-        ksteps = at_end - at < kp / 64 - k_first ? at_end - at : kp / 64 - k_first;
+        if (tile >= tail.tiles || k_first >= all_steps) return; // the end of the row, or a member the last bundle does not have
+        ksteps = at_end - at < all_steps - k_first ? at_end - at : all_steps - k_first;
         tile_of_position(tail.first_tile + tile, tiles_m, tiles_n, tm, tn);
     } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
         return;
@@ -434,38 +416,16 @@ next_part:
     const int wm = wave & 1, wn = wave >> 1;
     const int l16 = lane & 15, lq = lane >> 4;
 
-    // loader lanes: 8 lanes per row, chunk rotated by (row / 2) % 8 (rows past the end wrapped, never stored).
-    // Each load set (half of A, half of B) is 16 loads of 8 rows: two per wavefront.
-    const uint8_t* a_src[4];                                 // [half * 2 + i]
-    const uint8_t* b_src[4];                                 // [group * 2 + i]
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        int rl = ((q >> 1) * 16 + wave * 2 + (q & 1)) * 8 + (lane >> 3);     // row inside the tile
-        int sw16 = ((lane & 7) ^ ((rl >> 1) & 7)) * 16;
-        int ra = wrap_row(m0 + rl, m);
-        int rb = wrap_row(n0 + rl, n);
-        a_src[q] = (const uint8_t*)At + (size_t)ra * ld * 2 + sw16 + (size_t)k_first * 128;
-        b_src[q] = (const uint8_t*)Bt + (size_t)rb * ld * 2 + sw16 + (size_t)k_first * 128;
-    }
-    // the four loads a wavefront queues per phase, one at a time (ks clamped: the look-ahead of the
-    // last steps re-reads the last one)
-    auto issue_a = [&](int half, int ks, int i) {            // 8 rows of rows 128 half .. +127 of A(ks)
-        int kc = ks < ksteps ? ks : ksteps - 1;
-        dma16(a_src[half * 2 + i] + (size_t)kc * 128, smem + (ks % 3) * S::A_STAGE + (half * 16 + wave * 2 + i) * 1024);
-    };
-    auto issue_b = [&](int g, int ks, int i) {               // 8 rows of the B half of group g, step ks
-        int kc = ks < ksteps ? ks : ksteps - 1;
-        dma16(b_src[g * 2 + i] + (size_t)kc * 128, smem + S::B_OFF + (g * 2 + (ks & 1)) * S::B_HALF + (wave * 2 + i) * 1024);
-    };
+    // Each load set (half of A, half of B) is 16 loads: two per wavefront, one at a time (look-ahead past the last step: unused)
+    DenseLoader<AKM, BKM, S::BM, WM> opa;
+    DenseLoader<BKM, AKM, S::BN, NF * 16> opb;
+    opa.init(At, m0, wm * WM, wave, lane, k_first, ksteps, smem);
+    opb.init(Bt, n0, wn * (NF * 16), wave, lane, k_first, ksteps, smem);
+    auto issue_a = [&](int half, int ks, int i) { opa.load(ks, half * 2 + i, smem, (ks % 3) * S::A_STAGE, wave); };
+    // (B half g of step ks lies at (g * 2 + ks % 2) * B_HALF; its pieces are numbered from the tile's first column)
+    auto issue_b = [&](int g, int ks, int i) { opb.load(ks, g * 2 + i, smem, S::B_OFF + (g + (ks & 1)) * S::B_HALF, wave); };
     auto even_load = [&](int k, int idx) { if (idx < 2) issue_b(1, k + 1, idx); else issue_a(0, k + 2, idx - 2); };
     auto odd_load = [&](int k, int idx) { if (idx < 2) issue_a(1, k + 2, idx); else issue_b(0, k + 2, idx - 2); };
-
-    // reader lanes: fragment f = rows 16f .. 16f+15 = 2 KiB; lane (l16, lq) wants chunk 4h + lq
-    const int sw = (l16 >> 1) & 7;
-    const int rd0 = l16 * 128 + ((lq ^ sw) * 16);
-    const int rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);
-    const int a_rd = (wm * MF) * 2048;
-    const int b_rd = S::B_OFF + group * 2 * S::B_HALF + ((wn & 1) * NF) * 2048;
 
     f32x4 acc[MF][NF];
 #pragma unroll
@@ -475,17 +435,11 @@ next_part:
 
     constexpr int KEEP = 8;                                  // loads of the last two phases
 #define SPLIT_READ(ks)                                                                                 \
-        const uint8_t* sa = smem + ((ks) % 3) * S::A_STAGE + a_rd;                                     \
-        const uint8_t* sb = smem + b_rd + ((ks) & 1) * S::B_HALF;                                      \
+        const auto sa = opa.stage(smem, ((ks) % 3) * S::A_STAGE);                                      \
+        const auto sb = opb.stage(smem, S::B_OFF + (group + ((ks) & 1)) * S::B_HALF);                  \
         BFrag af[MF], bf[NF];                                                                          \
-        _Pragma("unroll") for (int i = 0; i < MF; ++i) {                                               \
-            af[i].u[0] = *(const u32x4*)(sa + i * 2048 + rd0);                                         \
-            af[i].u[1] = *(const u32x4*)(sa + i * 2048 + rd1);                                         \
-        }                                                                                              \
-        _Pragma("unroll") for (int j = 0; j < NF; ++j) {                                               \
-            bf[j].u[0] = *(const u32x4*)(sb + j * 2048 + rd0);                                         \
-            bf[j].u[1] = *(const u32x4*)(sb + j * 2048 + rd1);                                         \
-        }
+        _Pragma("unroll") for (int i = 0; i < MF; ++i) af[i] = opa.frag(sa, i);                        \
+        _Pragma("unroll") for (int j = 0; j < NF; ++j) bf[j] = opb.frag(sb, j);
 // the compute phase: 64 MFMAs with the phase's four loads spread between them (queued in one burst
 // at the start of the phase they cost 2 % more).  The B fragments are taken back and forth, so that only
 // one operand changes from one MFMA to the next: the kernel runs at the clock the chip's power limit
@@ -614,17 +568,15 @@ __global__ void __launch_bounds__(TN_THREADS) tail_finish_kernel(const f32x4* __
     }
 }
 
-template <int BM, int BN, int EPI, int NS>
-hipError_t launch_dense_tn(const bf16_t* At, int64_t m, const bf16_t* Bt, int64_t n, int64_t kp, int64_t ld,
-                           const uint8_t* meta, bf16_t* out, hipStream_t s) {
+template <int BM, int BN, int EPI, int NS, bool AKM, bool BKM>
+hipError_t launch_dense_tn(const DenseOperand& A, const DenseOperand& B, int64_t ksteps, const uint8_t* meta, bf16_t* out, hipStream_t s) {
     using S = TnSmem<BM, BN, NS>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
-    int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
-    auto kern = dense_tn_kernel<BM, BN, EPI, NS>;
-    hipError_t e = allow_dynamic_lds<dense_tn_kernel<BM, BN, EPI, NS>>(S::TOTAL);
+    const int tiles_m = (A.rows + BM - 1) / BM, tiles_n = (B.rows + BN - 1) / BN;
+    hipError_t e = allow_dynamic_lds<dense_tn_kernel<BM, BN, EPI, NS, AKM, BKM>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    kern<<<dim3((unsigned)super_grid(tiles_m, tiles_n)), dim3(TN_THREADS), S::TOTAL, s>>>(
-        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n);
+    dense_tn_kernel<BM, BN, EPI, NS, AKM, BKM><<<dim3((unsigned)super_grid(tiles_m, tiles_n)), dim3(TN_THREADS), S::TOTAL, s>>>(
+        A, B, (int)ksteps, meta, out, tiles_m, tiles_n);
     return hipGetLastError();
 }
 
@@ -689,28 +641,28 @@ inline TailPlan tail_plan(int64_t tiles_m, int64_t tiles_n, int64_t ksteps) {
 }
 
 // tail: scratch for the parts of the leftover tiles (masked packed results only), or null
-template <int EPI>
-hipError_t launch_dense_tn_split(const bf16_t* At, int64_t m, const bf16_t* Bt, int64_t n, int64_t kp, int64_t ld,
-                                 const uint8_t* meta, bf16_t* out, hipStream_t s, float* tail = nullptr) {
+template <int EPI, bool AKM, bool BKM>
+hipError_t launch_dense_tn_split(const DenseOperand& A, const DenseOperand& B, int64_t ksteps, const uint8_t* meta, bf16_t* out,
+                                 hipStream_t s, float* tail) {
     using S = SplitSmem;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
-    int tiles_m = (int)((m + S::BM - 1) / S::BM), tiles_n = (int)((n + S::BN - 1) / S::BN);
-    hipError_t e = allow_dynamic_lds<dense_tn_split_kernel<EPI, false>>(S::TOTAL);
+    const int tiles_m = (A.rows + S::BM - 1) / S::BM, tiles_n = (B.rows + S::BN - 1) / S::BN;
+    hipError_t e = allow_dynamic_lds<dense_tn_split_kernel<EPI, false, AKM, BKM>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    const TailPlan p = tail ? tail_plan(tiles_m, tiles_n, kp / 64) : NO_TAIL;
+    const TailPlan p = tail ? tail_plan(tiles_m, tiles_n, ksteps) : NO_TAIL;
     // with a tail the first launch is whole rounds only: workgroups 0 .. first_tile - 1 are exactly the
     // positions 0 .. first_tile - 1 of the order
     const int grid = p.tiles ? p.first_tile : super_grid(tiles_m, tiles_n);
-    dense_tn_split_kernel<EPI, false><<<dim3((unsigned)grid), dim3(TN_THREADS), S::TOTAL, s>>>(
-        At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, NO_TAIL, nullptr);
+    dense_tn_split_kernel<EPI, false, AKM, BKM><<<dim3((unsigned)grid), dim3(TN_THREADS), S::TOTAL, s>>>(
+        A, B, (int)ksteps, meta, out, tiles_m, tiles_n, NO_TAIL, nullptr);
     if ((e = hipGetLastError()) != hipSuccess || !p.tiles) return e;
     if constexpr (EPI == EPI_MASKED_PACKED) {
-        if ((e = allow_dynamic_lds<dense_tn_split_kernel<EPI, true>>(S::TOTAL)) != hipSuccess) return e;
-        dense_tn_split_kernel<EPI, true><<<dim3(RESIDENT), dim3(TN_THREADS), S::TOTAL, s>>>(
-            At, (int)m, Bt, (int)n, (int)kp, (int)ld, meta, out, tiles_m, tiles_n, p, (f32x4*)tail);
+        if ((e = allow_dynamic_lds<dense_tn_split_kernel<EPI, true, AKM, BKM>>(S::TOTAL)) != hipSuccess) return e;
+        dense_tn_split_kernel<EPI, true, AKM, BKM><<<dim3(RESIDENT), dim3(TN_THREADS), S::TOTAL, s>>>(
+            A, B, (int)ksteps, meta, out, tiles_m, tiles_n, p, (f32x4*)tail);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         tail_finish_kernel<<<dim3((unsigned)(p.tiles * 4)), dim3(TN_THREADS), 0, s>>>(
-            (const f32x4*)tail, (int)m, (int)n, (int)(kp / 64), meta, out, tiles_m, tiles_n, p);
+            (const f32x4*)tail, A.rows, B.rows, (int)ksteps, meta, out, tiles_m, tiles_n, p);
         e = hipGetLastError();
     }
     return e;
@@ -732,12 +684,7 @@ hipError_t launch_token_copies(const bf16_t* in0, int64_t cols0, bf16_t* out0, c
     return launch_transposes(transpose_job(in0, b, cols0, bp, ld, out0), in1 ? transpose_job(in1, b, cols1, bp, ld, out1) : TransposeJob{}, {}, s);
 }
 
-hipError_t launch_transpose(const bf16_t* in, int64_t rows, int64_t cols, bf16_t* out, hipStream_t s) {
-    return launch_transposes(transpose_job(in, rows, cols, rows, rows, out), {}, {}, s);
-}
-
-// The packed epilogue reads the metadata of 32 columns of W^R as one dword: rows of d_in / 8 bytes must
-// keep those dwords aligned.  Other layers take the in-place kernel.
+// Layers that the forms with token-contiguous copies in their interface take.
 bool wgrad_tn_fits(int64_t d_in) { return d_in % 32 == 0; }
 
 // Tiles (m x n) of the dense products, the weight gradient's and those of masked dense weights; of two that take as long the
@@ -771,18 +718,18 @@ static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tai
     return best;
 }
 
-template <int EPI>
-static hipError_t launch_dense_tile(int tile, const bf16_t* A, int64_t m, const bf16_t* B, int64_t n, int64_t kp, int64_t ld,
-                                    const uint8_t* meta, bf16_t* out, hipStream_t s, float* tail = nullptr) {
+template <int EPI, bool AKM, bool BKM>
+static hipError_t launch_dense_tile(int tile, const DenseOperand& A, const DenseOperand& B, int64_t ksteps, const uint8_t* meta,
+                                    bf16_t* out, hipStream_t s, float* tail = nullptr) {
     switch (tile) {
-        case 0: return launch_dense_tn_split<EPI>(A, m, B, n, kp, ld, meta, out, s, tail);
-        case 1: return launch_dense_tn<256, 192, EPI, 2>(A, m, B, n, kp, ld, meta, out, s);
-        case 2: return launch_dense_tn<192, 192, EPI, 3>(A, m, B, n, kp, ld, meta, out, s);
-        case 3: return launch_dense_tn<256, 128, EPI, 3>(A, m, B, n, kp, ld, meta, out, s);
-        case 4: return launch_dense_tn<192, 128, EPI, 4>(A, m, B, n, kp, ld, meta, out, s);
-        case 5: return launch_dense_tn<128, 128, EPI, 4>(A, m, B, n, kp, ld, meta, out, s);
-        case 6: return launch_dense_tn<64, 128, EPI, 6>(A, m, B, n, kp, ld, meta, out, s);
-        default: return launch_dense_tn<64, 64, EPI, 8>(A, m, B, n, kp, ld, meta, out, s);
+        case 0: return launch_dense_tn_split<EPI, AKM, BKM>(A, B, ksteps, meta, out, s, tail);
+        case 1: return launch_dense_tn<256, 192, EPI, 2, AKM, BKM>(A, B, ksteps, meta, out, s);
+        case 2: return launch_dense_tn<192, 192, EPI, 3, AKM, BKM>(A, B, ksteps, meta, out, s);
+        case 3: return launch_dense_tn<256, 128, EPI, 3, AKM, BKM>(A, B, ksteps, meta, out, s);
+        case 4: return launch_dense_tn<192, 128, EPI, 4, AKM, BKM>(A, B, ksteps, meta, out, s);
+        case 5: return launch_dense_tn<128, 128, EPI, 4, AKM, BKM>(A, B, ksteps, meta, out, s);
+        case 6: return launch_dense_tn<64, 128, EPI, 6, AKM, BKM>(A, B, ksteps, meta, out, s);
+        default: return launch_dense_tn<64, 64, EPI, 8, AKM, BKM>(A, B, ksteps, meta, out, s);
     }
 }
 
@@ -807,7 +754,48 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s) {
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
     const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
-    return launch_dense_tile<EPI_MASKED_PACKED>(tile, Xt, d_in, dYt, d_out, bp, ld, meta, gvals, s, tail_or_null);
+    return launch_dense_tile<EPI_MASKED_PACKED, false, false>(tile, {Xt, (int)d_in, (int)ld, (int)bp}, {dYt, (int)d_out, (int)ld, (int)bp}, bp / 64, meta, gvals, s, tail_or_null);
+}
+
+// The same product from the operands as stored, token after token.  The tiles that pull their operands from L2 as fast as they can
+// lose nothing by it, and the copies are saved (us, copies and product before: 2048 tokens, 3072 x 768 33.3 -> 22.4; 700, 4160 x
+// 2112 25.7 -> 18.1; 4096, 4096 x 4096 122.7 -> 99.8; 16384, 2560 x 10240 752 -> 633).  The 256 x 256 kernel on many rounds
+// keeps its matrix pipes busy, and there the transposing LDS reads, half as many bytes per cycle as plain ones, make it 4 % slower
+// with X as stored, 3 % with dY, 9 % with both (16384 tokens, 8192 x 8192: 1400 us from copies, 1459, 1441, 1520), while a
+// copy is a stream of its operand at 5.9 TB/s.  So an operand is copied, where there is room, when the other one is wide: X from
+// about 9000 rows, dY from about 11000 columns on (16384 tokens, 36864 x 9216: both copied 7462, X 7389, none 7649).
+enum { COPY_X = 1, COPY_DY = 2 };
+int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
+    if (d_in % 32 != 0 || dense_tile_choice(d_in, d_out, (b + 63) / 64, with_tail) != 0) return 0;
+    const double product = 2.0 * (double)d_out * (double)d_in / 1.5e9, x = 4.0 * (double)d_in / 5.9e6, dy = 4.0 * (double)d_out / 5.9e6;   // us per token
+    const double cost[4] = {0.088 * product, x + 0.032 * product, dy + 0.042 * product, x + dy};
+    int best = 0;
+    for (int c = 1; c < 4; ++c)
+        if (cost[c] < cost[best]) best = c;
+    return best;
+}
+
+// dW (masked, packed) from dY [b][d_out] and X [b][d_in].  Xt, dYt: room for their copies (launch_token_copies), or null; tail as above.
+hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in, bf16_t* gvals,
+                               bf16_t* Xt, bf16_t* dYt, float* tail_or_null, hipStream_t s) {
+    if (d_in >= KMAJOR_EXTENT_MAX || d_out >= KMAJOR_EXTENT_MAX) return launch_wgrad_wide(dY, X, b, meta, d_out, d_in, gvals, s);
+    const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
+    const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
+    const int copies = Xt && dYt ? wgrad_copies(b, d_in, d_out, tail_or_null != nullptr) : 0;
+    const DenseOperand x = copies & COPY_X ? DenseOperand{Xt, (int)d_in, (int)ld, (int)bp} : DenseOperand{X, (int)d_in, (int)d_in, (int)b};
+    const DenseOperand dy = copies & COPY_DY ? DenseOperand{dYt, (int)d_out, (int)ld, (int)bp} : DenseOperand{dY, (int)d_out, (int)d_out, (int)b};
+    if (copies) {
+        const hipError_t e = launch_transposes(copies & COPY_X ? transpose_job(X, b, d_in, bp, ld, Xt) : TransposeJob{},
+                                               copies & COPY_DY ? transpose_job(dY, b, d_out, bp, ld, dYt) : TransposeJob{}, {}, s);
+        if (e != hipSuccess) return e;
+    }
+    constexpr int EPI = EPI_MASKED_PACKED;
+    switch (copies) {                                         // (tile 0 only where there are any)
+        case COPY_X: return launch_dense_tn_split<EPI, false, true>(x, dy, bp / 64, meta, gvals, s, tail_or_null);
+        case COPY_DY: return launch_dense_tn_split<EPI, true, false>(x, dy, bp / 64, meta, gvals, s, tail_or_null);
+        case COPY_X | COPY_DY: return launch_dense_tn_split<EPI, false, false>(x, dy, bp / 64, meta, gvals, s, tail_or_null);
+        default: return launch_dense_tile<EPI, true, true>(tile, x, dy, bp / 64, meta, gvals, s, tail_or_null);
+    }
 }
 
 // C[n, m] = B[n, K] * A[m, K]^T for the skinny products of the adapters (T = X L, dY R^T, and over the tokens dL and
@@ -888,32 +876,31 @@ size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m) {
 
 int dense_tn_plain_slabs(int64_t n, int64_t m, int64_t K, size_t partial_bytes) { return skinny_plan(n, m, K, partial_bytes).slabs; }
 
-// One skinny product for launch_skinny_tn: the rank is the side m (FLIP) or n, slab_steps k-steps per slab
-static SkinnyJob skinny_job(const bf16_t* A, int64_t m, int64_t lda, const bf16_t* B, int64_t n, int64_t ldb, int64_t K, int64_t valid,
-                            bf16_t* out, int64_t slab_steps) {
-    SkinnyJob j = {A, B, (int)m, (int)n, (int)lda, (int)ldb, (int)(K / 64), (int)valid, out, nullptr, 0, 0, 0, 1, (int)slab_steps};
+static SkinnyJob skinny_job(const DenseOperand& A, const DenseOperand& B, int64_t K, bf16_t* out, int64_t slab_steps) {
+    SkinnyJob j = {A, B, (int)((K + 63) / 64), out, nullptr, 0, 0, 0, 1, (int)slab_steps};
     j.slabs = (j.ksteps + j.slab_steps - 1) / j.slab_steps;
     return j;
 }
+constexpr SkinnyJob NO_JOB = {{}, {}, 0, nullptr, nullptr, 0, 0, 0, 1, 1};
 
-template <int LONG, int RANK, int NS, bool FLIP0, bool FLIP1>
+template <int LONG, int RANK, int NS, bool GRADIENTS>
 static hipError_t launch_skinny_as(SkinnyJob j0, SkinnyJob j1, hipStream_t s) {
     using S = TnSmem<LONG, RANK, NS>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     auto place = [](SkinnyJob& j, bool flip) {
         const int bm = flip ? RANK : LONG, bn = flip ? LONG : RANK;
-        j.tiles_m = (j.m + bm - 1) / bm;
-        j.tiles_n = (j.n + bn - 1) / bn;
-        j.grid = j.A ? super_grid(j.tiles_m, j.tiles_n) : 0;
+        j.tiles_m = (j.A.rows + bm - 1) / bm;
+        j.tiles_n = (j.B.rows + bn - 1) / bn;
+        j.grid = j.A.p ? super_grid(j.tiles_m, j.tiles_n) : 0;
     };
-    place(j0, FLIP0);
-    place(j1, FLIP1);
-    hipError_t e = allow_dynamic_lds<skinny_tn_kernel<LONG, RANK, NS, FLIP0, FLIP1>>(S::TOTAL);
+    place(j0, true);
+    place(j1, !GRADIENTS);
+    hipError_t e = allow_dynamic_lds<skinny_tn_kernel<LONG, RANK, NS, GRADIENTS>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    skinny_tn_kernel<LONG, RANK, NS, FLIP0, FLIP1><<<dim3((unsigned)(j0.grid * j0.slabs + j1.grid * j1.slabs)), dim3(TN_THREADS), S::TOTAL, s>>>(j0, j1);
+    skinny_tn_kernel<LONG, RANK, NS, GRADIENTS><<<dim3((unsigned)(j0.grid * j0.slabs + j1.grid * j1.slabs)), dim3(TN_THREADS), S::TOTAL, s>>>(j0, j1);
     if ((e = hipGetLastError()) != hipSuccess || (j0.slabs <= 1 && j1.slabs <= 1)) return e;
     auto sum = [](const SkinnyJob& j) {
-        return j.slabs > 1 ? SkinnySum{(const f32x4*)j.sums, j.slabs, (int64_t)j.n * j.m / 4, (u32x2*)j.out} : SkinnySum{};
+        return j.slabs > 1 ? SkinnySum{(const f32x4*)j.sums, j.slabs, (int64_t)j.A.rows * j.B.rows / 4, (u32x2*)j.out} : SkinnySum{};
     };
     const SkinnySum a = sum(j0), b = sum(j1);
     skinny_sum_kernel<<<dim3((unsigned)((a.count4 + b.count4 + 255) / 256)), dim3(256), 0, s>>>(a, b);
@@ -921,42 +908,40 @@ static hipError_t launch_skinny_as(SkinnyJob j0, SkinnyJob j1, hipStream_t s) {
 }
 
 // sums: scratch for the slabs of both
-template <bool FLIP0, bool FLIP1>
+template <bool GRADIENTS>
 static hipError_t launch_skinny_tn(int tile, SkinnyJob j0, SkinnyJob j1, float* sums, hipStream_t s) {
     j0.sums = sums;
-    j1.sums = sums + (j0.slabs > 1 ? (size_t)j0.slabs * j0.n * j0.m : 0);
+    j1.sums = sums + (j0.slabs > 1 ? (size_t)j0.slabs * j0.A.rows * j0.B.rows : 0);
     switch (tile) {
-        case 0: return launch_skinny_as<64, 128, 6, FLIP0, FLIP1>(j0, j1, s);
-        case 1: return launch_skinny_as<64, 64, 8, FLIP0, FLIP1>(j0, j1, s);
-        case 2: return launch_skinny_as<128, 64, 6, FLIP0, FLIP1>(j0, j1, s);
-        case 3: return launch_skinny_as<128, 128, 4, FLIP0, FLIP1>(j0, j1, s);
-        default: return launch_skinny_as<64, 256, 4, FLIP0, FLIP1>(j0, j1, s);
+        case 0: return launch_skinny_as<64, 128, 6, GRADIENTS>(j0, j1, s);
+        case 1: return launch_skinny_as<64, 64, 8, GRADIENTS>(j0, j1, s);
+        case 2: return launch_skinny_as<128, 64, 6, GRADIENTS>(j0, j1, s);
+        case 3: return launch_skinny_as<128, 128, 4, GRADIENTS>(j0, j1, s);
+        default: return launch_skinny_as<64, 256, 4, GRADIENTS>(j0, j1, s);
     }
 }
 
-// m: the rank; partial_bytes of scratch at `partial` (none: no slabs)
-hipError_t launch_dense_tn_plain(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, int64_t ld, bf16_t* C,
-                                 float* partial, size_t partial_bytes, hipStream_t s) {
-    const SkinnyPlan p = skinny_plan(n, m, K, partial ? partial_bytes : 0);
-    SkinnyJob none = {};
-    none.slabs = 1;
-    return launch_skinny_tn<true, true>(p.tile, skinny_job(A, m, ld, B, n, ld, K, m, C, p.slab_steps), none, partial, s);
+// T[n, r] = X[n, K] L[K, r] (k-major) or dY R^T with R [r][K]; partial_bytes of scratch at `partial` (none: no slabs)
+hipError_t launch_skinny_factor(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
+                                float* partial, size_t partial_bytes, hipStream_t s) {
+    const SkinnyPlan p = skinny_plan(n, r, K, partial ? partial_bytes : 0);
+    const SkinnyJob j = skinny_job({A, (int)r, (int)(a_kmajor ? r : K), (int)K}, {B, (int)n, (int)K, (int)K}, K, T, p.slab_steps);
+    return launch_skinny_tn<false>(p.tile, a_kmajor ? j : NO_JOB, a_kmajor ? NO_JOB : j, partial, s);
 }
 
 // The same product for any shape (dense weights with a general N:M mask, where no sparse MFMA applies)
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s) {
-    return launch_dense_tile<EPI_PLAIN>(dense_tile_choice(m, n, K / 64, false), A, m, B, n, K, K, nullptr, C, s);
+    return launch_dense_tile<EPI_PLAIN, false, false>(dense_tile_choice(m, n, K / 64, false), {A, (int)m, (int)K, (int)K}, {B, (int)n, (int)K, (int)K}, K / 64, nullptr, C, s);
 }
 
 // ------------------------------------------------------------------------------------------
 // Weight gradient of a layer with adapters: the packed dW as above plus the adapter gradients
 // (chain rule of Eq. 11)   dL = X^T (dY R^T)  [d_in, r],   dR = (X L)^T dY  [r, d_out],
-// all three contractions over the tokens sharing the token-contiguous copies of X and dY.
-// Workspace: Xt | dYt | Lt [r][d_in] | Tt [r][..] | T2t [r][..] | T = X L [b][r] | T2 = dY R^T [b][r] | scratch that
-// launch_wgrad_masked_t and the skinny products use one after the other.  T and T2 are laid out as stored for the short products only;
-// else the skinny products write them token-contiguous, zero beyond the tokens, which is what the gradients want, and the
-// room of T and T2 is scratch too.
+// all three contractions over the tokens.
+// Workspace: Xt | dYt | room of r x d_in values | T = X L [b][r] | T2 = dY R^T [b][r] (r rows of a token-contiguous copy's pitch
+// each) | scratch that launch_wgrad_masked and the skinny products use one after the other, for these with room for T and T2 once more.
+// Xt and dYt are written where launch_wgrad_masked wants copies.
 static size_t wgrad_adapter_shared_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     if (d_in % 64 != 0 || d_out % 64 != 0) return wgrad_tail_bytes(b, d_in, d_out);   // no tile kernel for the skinny products
     const size_t tail = wgrad_tail_bytes(b, d_in, d_out);
@@ -983,42 +968,30 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     uint8_t* w = (uint8_t*)workspace;
     bf16_t* Xt = (bf16_t*)w;   w += round256(token_copy_bytes(b, d_in));
     bf16_t* dYt = (bf16_t*)w;  w += round256(token_copy_bytes(b, d_out));
-    bf16_t* Lt = (bf16_t*)w;   w += round256((size_t)r * d_in * 2);
-    bf16_t* Tt = (bf16_t*)w;   w += round256((size_t)r * ld * 2);
-    bf16_t* T2t = (bf16_t*)w;  w += round256((size_t)r * ld * 2);
-    bf16_t* T = (bf16_t*)w;    w += round256((size_t)b * r * 2);
-    bf16_t* T2 = (bf16_t*)w;   w += round256((size_t)b * r * 2);
+    w += round256((size_t)r * d_in * 2);
+    bf16_t* T = (bf16_t*)w;    w += round256((size_t)r * ld * 2);
+    bf16_t* T2 = (bf16_t*)w;   w += round256((size_t)r * ld * 2);
+    float* const sums = (float*)w;
+    w += 2 * round256((size_t)b * r * 2);
     float* tail = wgrad_tail_bytes(b, d_in, d_out) ? (float*)w : nullptr;
-    float* const sums = (float*)T;
     const size_t room = 2 * round256((size_t)b * r * 2) + wgrad_adapter_shared_bytes(b, d_in, d_out, r);
 
-    hipError_t e;
-    auto skinny = [&]() {                                     // T = X L and T2 = dY R^T, then dL = X^T T2 and dR = T^T dY
-        hipError_t err = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s);
-        if (err != hipSuccess) return err;
+    hipError_t e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, Xt, dYt, d_in % 32 == 0 ? tail : nullptr, s);
+    if (e != hipSuccess) return e;
+    // Extents that are not whole k-steps of the tile kernels or too wide for them, and short products: the kernel for ragged extents
+    if (d_in % 64 != 0 || d_out % 64 != 0 || d_in >= KMAJOR_EXTENT_MAX || d_out >= KMAJOR_EXTENT_MAX ||
+        (skinny_pair_is_short(b, r, d_in) && skinny_pair_is_short(b, r, d_out) && skinny_pair_is_short(d_in, r, b) && skinny_pair_is_short(r, d_out, b))) {
+        if ((e = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s)) != hipSuccess) return e;
         return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);
-    };
-    if (d_in % 64 != 0 || d_out % 64 != 0) {
-        // Extents that are not whole k-steps of the tile kernels: the in-place kernel for dW and the kernel for
-        // ragged extents for the four skinny products (T and T2 rounded to bf16 as on the fast path).
-        if ((e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, s)) != hipSuccess) return e;
-        return skinny();
     }
-    const bool is_short = skinny_pair_is_short(b, r, d_in) && skinny_pair_is_short(b, r, d_out) && skinny_pair_is_short(d_in, r, b) &&
-                          skinny_pair_is_short(r, d_out, b);
-    // the copies of X and dY, and Lt
-    if ((e = launch_transposes(transpose_job(X, b, d_in, bp, ld, Xt), transpose_job(dY, b, d_out, bp, ld, dYt),
-                               is_short ? TransposeJob{} : transpose_job(L, d_in, r, d_in, d_in, Lt), s)) != hipSuccess)
-        return e;
-    if ((e = launch_wgrad_masked_t(dYt, Xt, b, meta, d_out, d_in, gvals, tail, s)) != hipSuccess) return e;
-    if (is_short) return skinny();
-    // Tt = (X L)^T and T2t = (dY R^T)^T in one launch, then dL = X^T T2 and dR = T^T dY in another, each with one kernel for the
-    // sums of its slabs (2048 tokens, 4352 x 4352, rank 128: ten launches, 71 us, before)
-    const SkinnyPair f = skinny_pair_plan(bp, d_in, bp, d_out, r, room);
-    if ((e = launch_skinny_tn<false, false>(f.tile, skinny_job(X, bp, d_in, Lt, r, d_in, d_in, b, Tt, f.slab_steps),
-                                            skinny_job(dY, bp, d_out, R, r, d_out, d_out, b, T2t, f.slab_steps), sums, s)) != hipSuccess)
+    // T and T2 in one launch, then dL and dR in another, each with one kernel for the sums of its slabs (2048 tokens, 4352 x
+    // 4352, rank 128: ten launches, 71 us, before)
+    const int ir = (int)r, ib = (int)b, in = (int)d_in, out = (int)d_out;
+    const SkinnyPair f = skinny_pair_plan(b, d_in, b, d_out, r, room);
+    if ((e = launch_skinny_tn<false>(f.tile, skinny_job({L, ir, ir, in}, {X, ib, in, in}, d_in, T, f.slab_steps),
+                                     skinny_job({R, ir, out, out}, {dY, ib, out, out}, d_out, T2, f.slab_steps), sums, s)) != hipSuccess)
         return e;
     const SkinnyPair g = skinny_pair_plan(d_in, bp, d_out, bp, r, room);
-    return launch_skinny_tn<true, false>(g.tile, skinny_job(T2t, r, bp, Xt, d_in, ld, bp, r, dL, g.slab_steps),
-                                         skinny_job(dYt, d_out, ld, Tt, r, bp, bp, d_out, dR, g.slab_steps), sums, s);
+    return launch_skinny_tn<true>(g.tile, skinny_job({T2, ir, ir, ib}, {X, in, in, ib}, b, dL, g.slab_steps),
+                                  skinny_job({dY, out, out, ib}, {T, ir, ir, ib}, b, dR, g.slab_steps), sums, s);
 }

@@ -1,0 +1,62 @@
+"""The weight gradient from operands as they are stored, token after token (needs an MI355X): tokens and widths that end
+inside a k-step, a panel or a piece; the rule that copies an operand all the same; values that are not finite; the kernel
+for layers wider than the tiles' offsets reach.  Against fp32 products under the element bounds of tests/parity_util.py."""
+import pytest
+import torch
+
+from paper_2405_16325_amd import binding as sl
+from paper_2405_16325_amd import inputs
+from tests.test_gpu_fullsize import assert_all_close, unpack_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(b, d_out, d_in):
+    print(f"wgrad b={b} d_out={d_out} d_in={d_in}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + b + d_out + 5 * d_in)
+    X, W, dY = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16) for shape in ((b, d_in), (d_out, d_in), (b, d_out)))
+    _, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    return X, dY, meta, unpack_bits(mask)
+
+
+# one token, one less and one more than a k-step, two k-steps; rows of 8 features, of pieces that end in half, of panels that end
+# inside one
+@pytest.mark.parametrize("b,d_out,d_in", [(1, 8, 8), (63, 72, 24), (64, 8, 1000), (65, 1000, 40), (129, 264, 72), (127, 136, 904),
+                                          (1000, 1000, 1000), (2048, 3080, 776), (300, 2184, 4392), (191, 5128, 2056)])
+def test_widths_and_tokens_that_end_inside_a_tile(b, d_out, d_in):
+    X, dY, meta, keep = layer(b, d_out, d_in)
+    want = (dY.float().t() @ X.float())[keep].reshape(d_out, d_in // 2)
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta, workspace=None), want, "dW without scratch")
+
+
+# (where both are wide, dY, X, and neither is copied): the same sums in the same order from every layout
+@pytest.mark.parametrize("b,d_out,d_in", [(130, 18432, 16384), (100, 9216, 36864), (70, 36864, 9216), (200, 8192, 8192)])
+def test_copies_change_nothing(b, d_out, d_in):
+    X, dY, meta, _ = layer(b, d_out, d_in)
+    g = sl.slope_wgrad_masked(dY, X, meta)
+    want = sl.slope_wgrad_masked_t(sl.slope_transpose_tokens(dY), sl.slope_transpose_tokens(X), b, meta)
+    assert torch.equal(g.view(torch.int16), want.view(torch.int16))
+
+
+# a feature whose values are not finite spoils its own row or column and nothing else, also where loads past the end of a row
+# find it in the next token, and where the last k-step is short
+@pytest.mark.parametrize("b,d_out,d_in", [(70, 72, 264), (1000, 200, 96), (100, 4168, 2120)])
+def test_values_that_are_not_finite_stay_in_their_feature(b, d_out, d_in):
+    X, dY, meta, keep = layer(b, d_out, d_in)
+    g = sl.slope_wgrad_masked(dY, X, meta)
+    X[b - 1, 0], dY[b - 1, 0], X[0, 8] = float("inf"), float("nan"), float("nan")
+    bad = sl.slope_wgrad_masked(dY, X, meta)
+    touched = torch.zeros((d_out, d_in), dtype=torch.bool, device="cuda")
+    touched[0, :] = touched[:, 0] = touched[:, 8] = True
+    rest = ~touched[keep].reshape(d_out, d_in // 2)
+    assert torch.equal(g[rest], bad[rest]) and not torch.isfinite(bad[~rest].float()).any()
+
+
+def test_layer_wider_than_the_offsets_of_the_tiles():
+    b, d_out, d_in = 9, 8, (1 << 24) + 8
+    X, dY, meta, keep = layer(b, d_out, d_in)
+    g = sl.slope_wgrad_masked(dY, X, meta)
+    want = (dY.float().t() @ X.float())[keep].reshape(d_out, d_in // 2)
+    assert_all_close(g, want, "dW")
