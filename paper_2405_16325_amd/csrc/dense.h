@@ -115,19 +115,22 @@ struct DenseLoader {
             }
         return st;
     }
-    __device__ __forceinline__ BFrag frag(const Stage& st, int i) const {
-        BFrag f;
+    // fragment i, half h of the k-step: 16 rows x 32 k
+    __device__ __forceinline__ u32x4 half(const Stage& st, int i, int h) const {
         if (KM) {
             typedef s16x4 __attribute__((address_space(3)))* lds_t;
-            const uint32_t at = st.at[i % UNITS] + i / UNITS * 8192;
-            union { s16x4 h[4]; BFrag f; } x;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x.h[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(at + (u >> 1) * 4096 + (u & 1) * 512));
-            f = x.f;
-        } else {
-            f.u[0] = *(const u32x4*)(st.p + frag_off[0] + i * 2048);
-            f.u[1] = *(const u32x4*)(st.p + frag_off[1] + i * 2048);
+            const uint32_t at = st.at[i % UNITS] + i / UNITS * 8192 + h * 4096;
+            union { s16x4 q[2]; u32x4 u; } x;
+            x.q[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)at);
+            x.q[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(at + 512));
+            return x.u;
         }
+        return *(const u32x4*)(st.p + frag_off[h] + i * 2048);
+    }
+    __device__ __forceinline__ BFrag frag(const Stage& st, int i) const {
+        BFrag f;
+        f.u[0] = half(st, i, 0);
+        f.u[1] = half(st, i, 1);
         return f;
     }
 };

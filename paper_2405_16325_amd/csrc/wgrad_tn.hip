@@ -17,6 +17,7 @@
 // the group's metadata nibble and stores one 4-byte pair of the packed gradient.
 #include <cmath>
 #include <numeric>
+#include <type_traits>
 
 #include "dense.h"
 
@@ -194,7 +195,6 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
     constexpr int AHEAD = (NS - 2) * (LD_A + LD_B);          // loads that may stay in flight at a wait
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int group = wave >> 2;
     DenseLoader<AKM, BKM, BM, BM / 2> opa;
     DenseLoader<BKM, AKM, BN, BN / 4> opb;
     opa.init(At, m0, (wave & 1) * (BM / 2), wave, lane, 0, ksteps, smem);
@@ -211,36 +211,6 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
 #pragma unroll
         for (int j = 0; j < NF; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    // One k-step.  Loads of step s + NS - 1 are queued in the even phase in which their stage, last
-    // read for step s - 1, has just been released: group 0 is then in its memory phase of step s,
-    // group 1 in its compute phase of step s - 1.  One phase later every wavefront waits until only
-    // the loads of steps beyond s + 1 are outstanding, before the barrier after which group 0 reads
-    // step s + 1.
-#define TN_STEP(G)                                                                                     \
-    {                                                                                                  \
-        const auto sa = opa.stage(smem, at);                                                           \
-        const auto sb = opb.stage(smem, at + S::A_BYTES);                                              \
-        BFrag af[MF], bf[NF];                                                                          \
-        _Pragma("unroll") for (int i = 0; i < MF; ++i) af[i] = opa.frag(sa, i);                        \
-        _Pragma("unroll") for (int j = 0; j < NF; ++j) bf[j] = opb.frag(sb, j);                        \
-        if (G == 0) issue(ks + NS - 1, at == 0 ? LAST : at - S::STAGE);                                \
-        /* all LDS reads of this stage have returned before anybody may overwrite it */                \
-        WAIT_HERE(waitcnt_imm(G == 1 ? AHEAD : 63, 0));                                                \
-        wg_barrier();                                                                                  \
-        if (G == 1) issue(ks + NS, at);                                                                \
-        /* before the MFMAs: among them, where the compiler may put these loads, they land 5 to 8 % later */ \
-        if (G == 1) __builtin_amdgcn_sched_barrier(0);                                                 \
-        _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                  \
-        _Pragma("unroll") for (int i = 0; i < MF; ++i) _Pragma("unroll") for (int jj = 0; jj < NF; ++jj) { \
-            const int j = (i & 1) ? NF - 1 - jj : jj;         /* back and forth: one operand changes per MFMA */ \
-            AFrag a, b;                                                                                \
-            a.u = af[i].u[h]; b.u = bf[j].u[h];                                                        \
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc[i][j], 0, 0, 0);         \
-        }                                                                                              \
-        if (G == 0) WAIT_HERE(waitcnt_imm(AHEAD, 15));                                                 \
-        wg_barrier();                                                                                  \
-        at = at == LAST ? 0 : at + S::STAGE;                                                           \
-    }
     // The stage that is read, as a byte offset that wraps.  As (ks % NS) * STAGE it became a multiply-high and subtractions per
     // lane before every step's LDS reads (us, from HBM: 2048 x 1024 over 4096 on 64 x 128 30.5 -> 26.0, 704 x 2112 over 4160
     // 27.0 -> 22.2, 2048 x 1024 over 8192 51.8 -> 41.8); the 256 x 256 kernel, where registers are short, is 1 % slower this way.
@@ -250,15 +220,120 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
     for (int p = 0; p < NS - 1; ++p) issue(k_begin + p, p * S::STAGE);
     WAIT_HERE(waitcnt_imm(AHEAD, 15));                        // the first step has landed (this wave's share)
     wg_barrier();
-    if (group == 0) {
-        for (int ks = k_begin; ks < k_end; ++ks) TN_STEP(0)
-        wg_barrier();
-    } else {
-        issue(k_begin + NS - 1, LAST);
-        wg_barrier();
-        for (int ks = k_begin; ks < k_end; ++ks) TN_STEP(1)
-    }
+    // Two schedules of a k-step.  Where each wavefront's products cover its own reads: one barrier, the fragments of a half of the
+    // k-step read while the other half is multiplied.  (us, operands in the last-level cache, in two phases / so: 64 x 64, 1024
+    // x 1024 over 4096 tokens 23.9 / 21.0; 128 x 128, 3072 x 768 over 2048 tokens 22.4 / 20.6; 192 x 192, 1024 x 2048 over 4096 47.9
+    // / 42.7; 256 x 128, 4096 x 4096 over 4096 tokens 129 / 120.)  Else two phases, as in the 256 x 256 kernel: where the ring has
+    // two stages, so that loads are queued later (256 x 192, 5120 x 6464 over 752 tokens: 62.7 against 65.3), and on k-contiguous
+    // operands with 8 or 12 products per half (128 x 128, 1920 x 1973 over 3840: 31.4 against 33.2; 192 x 128 34.8 / 35.7).
+    if constexpr (NS == 2 || (!AKM && !BKM && MF * NF >= 8 && MF * NF <= 12)) {
+        const int group = wave >> 2;
+        // One k-step.  Loads of step s + NS - 1 are queued in the even phase in which their stage, last
+        // read for step s - 1, has just been released: group 0 is then in its memory phase of step s,
+        // group 1 in its compute phase of step s - 1.  One phase later every wavefront waits until only
+        // the loads of steps beyond s + 1 are outstanding, before the barrier after which group 0 reads
+        // step s + 1.
+#define TN_STEP(G)                                                                                         \
+        {                                                                                                  \
+            const auto sa = opa.stage(smem, at);                                                           \
+            const auto sb = opb.stage(smem, at + S::A_BYTES);                                              \
+            BFrag af[MF], bf[NF];                                                                          \
+            _Pragma("unroll") for (int i = 0; i < MF; ++i) af[i] = opa.frag(sa, i);                        \
+            _Pragma("unroll") for (int j = 0; j < NF; ++j) bf[j] = opb.frag(sb, j);                        \
+            if (G == 0) issue(ks + NS - 1, at == 0 ? LAST : at - S::STAGE);                                \
+            /* all LDS reads of this stage have returned before anybody may overwrite it */                \
+            WAIT_HERE(waitcnt_imm(G == 1 ? AHEAD : 63, 0));                                                \
+            wg_barrier();                                                                                  \
+            if (G == 1) issue(ks + NS, at);                                                                \
+            /* before the MFMAs: among them, where the compiler may put these loads, they land 5 to 8 % later */\
+            if (G == 1) __builtin_amdgcn_sched_barrier(0);                                                 \
+            _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                  \
+            _Pragma("unroll") for (int i = 0; i < MF; ++i) _Pragma("unroll") for (int jj = 0; jj < NF; ++jj) {\
+                const int j = (i & 1) ? NF - 1 - jj : jj;         /* back and forth: one operand changes per MFMA */\
+                AFrag a, b;                                                                                \
+                a.u = af[i].u[h]; b.u = bf[j].u[h];                                                        \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc[i][j], 0, 0, 0);         \
+            }                                                                                              \
+            if (G == 0) WAIT_HERE(waitcnt_imm(AHEAD, 15));                                                 \
+            wg_barrier();                                                                                  \
+            at = at == LAST ? 0 : at + S::STAGE;                                                           \
+        }
+        if (group == 0) {
+            for (int ks = k_begin; ks < k_end; ++ks) TN_STEP(0)
+            wg_barrier();
+        } else {
+            issue(k_begin + NS - 1, LAST);
+            wg_barrier();
+            for (int ks = k_begin; ks < k_end; ++ks) TN_STEP(1)
+        }
 #undef TN_STEP
+    } else {
+        struct Half { u32x4 a[MF], b[NF]; };                  // fragments of half a k-step
+        constexpr int READS = MF + NF, LOADS = LD_A + LD_B, MFMAS = MF * NF;
+        auto read_one = [&](Half& f, const auto& sa, const auto& sb, int h, int x) {
+            if (x < NF) f.b[x] = opb.half(sb, x, h);
+            else f.a[x - NF] = opa.half(sa, x - NF, h);
+        };
+        auto load_one = [&](int ks, int x) {                  // into the stage at `at`
+            if (x < LD_A) opa.load(ks, x, smem, at, wave);
+            else opb.load(ks, x - LD_A, smem, at + S::A_BYTES, wave);
+        };
+        // The products of f and P pieces of other work: spread among them, or before them where they are few (64 x 64 tiles, spread:
+        // 22.7 us for 21.0; 256 x 128, not spread: 60.5 for 48.7)
+        constexpr bool SPREAD = MFMAS > 8;
+        auto multiply = [&](const Half& f, auto pieces, auto piece) {
+            constexpr int P = decltype(pieces)::value, PER = (P + MFMAS - 1) / MFMAS;
+            if (!SPREAD) {
+#pragma unroll
+                for (int x = 0; x < P; ++x) {
+                    if (x == READS) __builtin_amdgcn_sched_barrier(0);
+                    piece(x);
+                }
+                if (P <= READS) __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int q = 0; q < MFMAS; ++q) {
+                const int i = q / NF, j = (i & 1) ? NF - 1 - q % NF : q % NF;   // back and forth: one operand changes per MFMA
+                AFrag a, b;
+                a.u = f.a[i]; b.u = f.b[j];
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc[i][j], 0, 0, 0);
+                if (!SPREAD) continue;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int x = q * PER; x < (q + 1) * PER; ++x)
+                    if (x < P) piece(x);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        Half f0, f1;
+        {
+            const auto sa = opa.stage(smem, 0);
+            const auto sb = opb.stage(smem, S::A_BYTES);
+#pragma unroll
+            for (int x = 0; x < READS; ++x) read_one(f0, sa, sb, 0, x);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        issue(k_begin + NS - 1, LAST);
+        WAIT_HERE(waitcnt_imm(63, 0));                        // (else the compiler waits for all reads at the head of the loop)
+        for (int ks = k_begin; ks < k_end; ++ks) {
+            {
+                const auto sa = opa.stage(smem, at);
+                const auto sb = opb.stage(smem, at + S::A_BYTES);
+                multiply(f0, std::integral_constant<int, READS>{}, [&](int x) { read_one(f1, sa, sb, 1, x); });
+            }
+            // this wavefront has read the stage, and its loads of the next one have landed
+            WAIT_HERE(waitcnt_imm(AHEAD, 0));
+            wg_barrier();
+            const int next = at == LAST ? 0 : at + S::STAGE;
+            const auto sa = opa.stage(smem, next);            // (after the last k-step read and not used)
+            const auto sb = opb.stage(smem, next + S::A_BYTES);
+            multiply(f1, std::integral_constant<int, READS + LOADS>{}, [&](int x) {
+                if (x < READS) read_one(f0, sa, sb, 0, x);
+                else load_one(ks + NS, x - READS);            // into the stage that everybody has read
+            });
+            at = next;
+        }
+    }
     WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
 }
 

@@ -1,0 +1,39 @@
+"""Contractions shorter and longer than the load rings of the tile kernels, on each of their tile shapes (needs an MI355X).
+Against fp32 products under the element bounds of tests/parity_util.py."""
+import pytest
+import torch
+
+from paper_2405_16325_amd import binding as sl
+from paper_2405_16325_amd import inputs
+from tests.test_gpu_fullsize import assert_all_close, unpack_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def gauss(*shape):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE + 3 * shape[0] + shape[1])
+    return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+
+
+# extents whose least estimate is, for these contractions, on 64 x 64, 64 x 128, 128 x 128, 192 x 128, 256 x 128, 192 x 192 and 256 x 192
+# tiles, each ragged at both edges
+TILES = [(1000, 1016), (1010, 1928), (2000, 1928), (2290, 2552), (2040, 4088), (3000, 3064), (3000, 4000)]
+
+
+@pytest.mark.parametrize("ksteps", [1, 2, 3, 4, 5, 7, 8, 9])
+@pytest.mark.parametrize("n,m", TILES)
+def test_dense_product(n, m, ksteps):
+    print(f"gemm n={n} m={m} k-steps={ksteps}", flush=True)
+    B, A = gauss(n, 64 * ksteps), gauss(m, 64 * ksteps)
+    assert_all_close(sl.slope_gemm_tn(B, A), B.float() @ A.float().t(), "C")
+
+
+@pytest.mark.parametrize("b", [5, 64, 100, 192, 250, 320, 450, 512, 577])
+@pytest.mark.parametrize("d_out,d_in", [(n - n % 8, m) for n, m in TILES])
+def test_weight_gradient(b, d_out, d_in):
+    print(f"wgrad b={b} d_out={d_out} d_in={d_in}", flush=True)
+    X, dY = gauss(b, d_in), gauss(b, d_out)
+    _, meta, mask = sl.slope_prune_rows(gauss(d_out, d_in), want_mask=True)
+    want = (dY.float().t() @ X.float())[unpack_bits(mask)].reshape(d_out, d_in // 2)
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
