@@ -30,10 +30,13 @@
 //     a time into two alternating pair buffers, and its metadata for four k-steps at a time;
 //   - inside a row the eight 16-byte chunks are rotated by (row / 2) % 8, which makes the
 //     ds_read_b128 of the MFMA layout (16 lanes = 16 rows, same chunk) hit 16 different bank groups.
-// A workgroup owns a BM x BN tile of C with 8 wavefronts (2 x 4, two per SIMD) in two groups that
-// run half a k-step apart: while one group issues its MFMAs the other reads its fragments from
-// LDS and queues global loads, then they swap (two barriers per k-step), so every SIMD's matrix
-// pipe always has a wavefront feeding it.  Loads run two k-steps ahead of their use.
+// A workgroup owns a BM x BN tile of C with 8 wavefronts (2 x 4, two per SIMD), one barrier per k-step: while a wavefront
+// multiplies a k-step it reads the fragments of the next one and queues the loads of the third after it.  (Before, two groups of
+// wavefronts took turns at reading and multiplying, two barriers per k-step, which made a k-step at least twice a group's
+// LDS reads: the matrix pipes were busy a third of it.  us, operands in the last-level cache, before / now: 1000 tokens, 4352 x 4352 on
+// 192 x 128 40.1 / 35.0, on 256 x 128 43.6 / 39.2; 2048 tokens, 4352 x 4352 on 256 x 192 57.3 / 52.7, on 192 x 192 51.3 / 50.3; 330
+// tokens, 3328 x 13568, rank 64, in slabs 44.6 / 41.0.  From HBM, whose latency bounds them, 48.2 / 45.5, 52.1 / 52.2, 65.3 / 64.2,
+// 59.0 / 59.0, 52.1 / 50.4.)
 #include <type_traits>
 
 #include "pipeline.h"
@@ -279,7 +282,6 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int group = wave >> 2;                             // the two wavefronts of a SIMD differ here
     const int wm = wave & 1, wn = wave >> 1;
     const int l16 = lane & 15, lq = lane >> 4;
 
@@ -349,63 +351,87 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 #pragma unroll
         for (int j = 0; j < NF; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    // ---- prologue: k-steps 0 and 1 in flight; the second group starts half a step late
+    struct Frags {                                            // of a k-step
+        BFrag bf[NF];
+        AFrag af[MF];
+        int ai[MF];
+    };
+    // fragment x (the tokens' first) of k-step ks, with S4 = ks % 4 and its tokens in stage `bst`
+    auto read_one = [&](Frags& f, int ks, int S4, int bst, int x) {
+        if (x < NF) {
+            const uint8_t* const pb = smem + b_rd + bst * S::B_STAGE + x * 2048;
+            f.bf[x].u[0] = *(const u32x4*)(pb + rd0);
+            f.bf[x].u[1] = *(const u32x4*)(pb + rd1);
+        } else {
+            const bool second = (S4 & 1) != 0 || (TAIL && ks == ksteps - 1);
+            const int i = x - NF;
+            f.af[i].u = *(const u32x4*)(smem + ((S4 >> 1) & 1) * S::A_PAIR + a_rd + i * 2048 + (second ? rd1 : rd0));
+            f.ai[i] = *(const uint16_t*)(smem + m_rd + ((ks >> 2) & 1) * S::M_QUAD + (S4 >> 1) * 256 + i * 512 + (second ? 8 : 0));
+        }
+    };
+
+    // ---- prologue: what the k-steps before the first would have queued
     issue_m(0, 0);
     issue_a(0, 0);
     issue_b(0, 0);
+    issue_m(1, 1);
     issue_b(1, 1);
-    WAIT_HERE(waitcnt_imm(B_LD, 15));        // everything but B of step 1 has landed
+    issue_a(1, 1);
+    issue_b(2, 2);
+    WAIT_HERE(waitcnt_imm(A_LD + 2 * B_LD + 1, 15));
+    wg_barrier();
+    Frags f;
+#pragma unroll
+    for (int x = 0; x < MF + NF; ++x) read_one(f, 0, 0, 0, x);
+    WAIT_HERE(waitcnt_imm(A_LD + B_LD, 0));
     wg_barrier();
 
-    // One k-step of one wavefront; S4 = ks % 4 is a literal so that the number of loads queued in
-    // this step, which the wait below has to leave outstanding, is a constant.  The wait for the
-    // wavefront's own share of step ks + 1 sits at the end of the compute phase for group 0 and at
-    // the end of the memory phase for group 1: either way it precedes the barrier after which
-    // group 0 starts reading that step.
-#define SPMM_STEP(G, S4)                                                                               \
-    {                                                                                                  \
-        const int ks = ks0 + S4;                                                                       \
-        constexpr int QUEUED = B_LD + ((S4 & 1) == 0 ? A_LD : 0) + (S4 == 0 ? 1 : 0);                  \
-        const bool second = (S4 & 1) != 0 || (TAIL && ks == ksteps - 1);                               \
-        const uint8_t* pa = smem + ((S4 >> 1) & 1) * S::A_PAIR + a_rd + (second ? rd1 : rd0);          \
-        const uint8_t* pb = smem + b_rd + bst * S::B_STAGE;                                            \
-        const uint8_t* pm = smem + m_rd + ((ks0 >> 2) & 1) * S::M_QUAD + (S4 >> 1) * 256 + (second ? 8 : 0); \
-        BFrag bf[NF];                                                                                  \
-        AFrag af[MF];                                                                                  \
-        int ai[MF];                                                                                    \
-        issue_b(ks + 2, bst >= 1 ? bst - 1 : 2);                                                       \
-        if ((S4 & 1) == 0) issue_a((ks >> 1) + 1, ((S4 >> 1) + 1) & 1);                                \
-        if (S4 == 0) issue_m((ks >> 2) + 1, ((ks0 >> 2) + 1) & 1);                                     \
-        _Pragma("unroll") for (int j = 0; j < NF; ++j) {                                               \
-            bf[j].u[0] = *(const u32x4*)(pb + j * 2048 + rd0);                                         \
-            bf[j].u[1] = *(const u32x4*)(pb + j * 2048 + rd1);                                         \
-        }                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < MF; ++i) {                                               \
-            af[i].u = *(const u32x4*)(pa + i * 2048);                                                  \
-            ai[i] = *(const uint16_t*)(pm + i * 512);                                                  \
-        }                                                                                              \
-        bst = bst == 2 ? 0 : bst + 1;                                                                  \
-        /* all LDS reads of this stage have returned before anybody may overwrite it */                \
-        WAIT_HERE(waitcnt_imm(G == 1 ? QUEUED : 63, 0));                              \
-        wg_barrier();                                                                                  \
-        _Pragma("unroll") for (int i = 0; i < MF; ++i) _Pragma("unroll") for (int j = 0; j < NF; ++j)  \
-            acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(af[i].v, bf[j].v, acc[i][j], ai[i], 0, 0); \
-        if (G == 0) WAIT_HERE(waitcnt_imm(QUEUED, 15));                               \
-        wg_barrier();                                                                                  \
-    }
+    // One k-step, its fragments in registers: everybody has read it from LDS, the next one has landed.  Spread among its products
+    // are the loads that refill the buffers it has left, first, since the k-step after the next one waits for them (last: up to 5 %
+    // slower), and the reads of the next k-step's fragments: tokens, and a row of weights after the products of the same row, in
+    // whose registers it can be.  S4 = ks % 4 is a literal so that the number of loads queued, which the wait at the end has to leave
+    // outstanding, is a constant.
     int bst = 0;                                              // ring stage of the current k-step
-    if (group == 0) {
-        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
-            SPMM_STEP(0, 0) LAST_STEP(0) SPMM_STEP(0, 1) LAST_STEP(1) SPMM_STEP(0, 2) LAST_STEP(2) SPMM_STEP(0, 3)
+    auto step = [&](int ks, auto s4) {
+        constexpr int S4 = decltype(s4)::value, N4 = (S4 + 1) & 3;
+        constexpr int LOADS = B_LD + (S4 & 1) * A_LD + (S4 == 3), EARLY = NF + LOADS, SLOTS = MF * NF, PER = (EARLY + SLOTS - 1) / SLOTS;
+        const int next = bst == 2 ? 0 : bst + 1;
+        const int kb = ks + 3 < ksteps ? ks + 3 : ksteps - 1;
+        const int64_t a_off = (S4 & 1) ? pair_offset<TAIL>((ks >> 1) + 2, ksteps) : 0;
+        Frags g;
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(f.af[i].v, f.bf[j].v, acc[i][j], f.ai[i], 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int x = (i * NF + j) * PER; x < (i * NF + j + 1) * PER; ++x) {
+                    if (x < B_LD) dma16(b_src[x] + (size_t)kb * 128, smem + S::B_OFF + bst * S::B_STAGE + (wave * B_LD + x) * 1024);
+                    else if (x < B_LD + (S4 & 1) * A_LD)
+                        dma16(a_src[x - B_LD] + a_off, smem + (S4 >> 1) * S::A_PAIR + (wave * A_LD + x - B_LD) * 1024);
+                    else if (x < LOADS) issue_m((ks >> 2) + 2, (ks >> 2) & 1);
+                    else if (x < EARLY) read_one(g, ks + 1, N4, next, x - LOADS);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            read_one(g, ks + 1, N4, next, NF + i);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        WAIT_HERE(waitcnt_imm(LOADS, 0));
         wg_barrier();
-    } else {
-        wg_barrier();
-        for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
-            SPMM_STEP(1, 0) LAST_STEP(0) SPMM_STEP(1, 1) LAST_STEP(1) SPMM_STEP(1, 2) LAST_STEP(2) SPMM_STEP(1, 3)
-        }
+        f = g;
+        bst = next;
+    };
+    for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
+        step(ks0, std::integral_constant<int, 0>{});
+        LAST_STEP(0)
+        step(ks0 + 1, std::integral_constant<int, 1>{});
+        LAST_STEP(1)
+        step(ks0 + 2, std::integral_constant<int, 2>{});
+        LAST_STEP(2)
+        step(ks0 + 3, std::integral_constant<int, 3>{});
     }
-#undef SPMM_STEP
     WAIT_HERE(waitcnt_imm(0, 15));           // drain the clamped look-ahead loads
 
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
@@ -649,12 +675,15 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 
 // ------------------------------------------------------------------------------------------
 // spmm_ring_kernel: the smaller tiles, one barrier per pair of k-steps.  A tile of 128 x 64 gives a wavefront four MFMAs
-// per k-step, so two phases and two barriers per k-step, as above, cost more than the k-step's loads: it took 0.35 us per
-// k-step beside what its loads take.  Here a ring stage holds a pair of k-steps of both operands (the packed values come in
-// pairs anyway, 128 bytes per row), and a wavefront, per pair: waits for its own loads of the pair, passes the barrier,
-// queues the loads that refill the stage everybody has left, then reads its fragments and multiplies.  Three to four
-// stages keep at least a pair of k-steps (34 to 50 KB) on the way, more than the 16 KB a compute unit holds in flight, so
-// the operand feed is what bounds the kernel: 62 bytes per ns and compute unit on 128 x 64, 50 to 55 on the larger tiles.
+// per k-step, so a barrier per k-step, as above, would cost more than the k-step's loads (two of them took 0.35 us per
+// k-step beside what its loads take).  Here a ring stage holds a pair of k-steps of both operands (the packed values come in
+// pairs anyway, 128 bytes per row), and a wavefront, per pair: reads the second k-step's fragments and multiplies the first, waits
+// for its own loads of the next pair, passes the barrier, reads that pair's first k-step, queues the loads that refill the stage
+// everybody has left and multiplies the second.  So no product waits for the reads of its own k-step, three to four stages keep
+// two or three pairs (34 to 50 KB each) on the way, and the operand feed bounds the kernel.  (Before, a pair's reads followed
+// the barrier and the loads, and its products them: us, operands in the last-level cache, 2048 tokens, 768 x 3072 on 128 x 64 16.9
+// -> 15.7, on 128 x 128 23.3 -> 20.8; 512 tokens, 4096 x 4096 20.9 -> 19.8; 300, 9216 x 4096 on 192 x 64 26.7 -> 23.8; from HBM
+// 18.3 -> 18.1, 24.8 -> 24.5, 23.8 -> 23.6, 29.9 -> 29.3.  Loads after the second products: 8 % slower.)
 // Metadata: META_PAIRS pairs (16 bytes each) per row at a time, as many neighbouring lanes per row, the pieces of a row
 // rotated so that the sixteen rows of a 2-byte read fall on different banks.
 // Weights from HBM, us, the two-phase kernel / here: 2048 tokens, 768 x 3072 on 128 x 64 20.4 / 15.8; 512 tokens, 4096 x 4096
@@ -771,45 +800,66 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
     const int rd0 = l16 * 128 + ((lq ^ sw) * 16), rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);
     const int a_rd = wm * MF * 2048, b_rd = S::A_STAGE + wn * NF * 2048;
     const int m_rd = S::M_OFF + (wm * MF * 16 + l16) * S::M_ROW + lq * 2, m_sw = l16 * META_PAIRS / 16 % META_PAIRS;
-    auto multiply = [&](const uint8_t* st, const uint8_t* pm, int e, bool second) {
+    struct Frags {                                            // of a k-step
         BFrag bf[NF];
         AFrag af[MF];
         int ai[MF];
+    };
+    // second: the second half of the pair's rows of values and metadata
+    auto read = [&](Frags& f, int stage, int p, int u, int e, bool second) {
+        const uint8_t* const st = smem + stage * S::STAGE;
+        const uint8_t* const pm = smem + m_rd + (p / META_PAIRS & 1) * S::M_BLOCK + (u ^ m_sw) * 16 + (second ? 8 : 0);
 #pragma unroll
         for (int j = 0; j < NF; ++j) {
-            bf[j].u[0] = *(const u32x4*)(st + b_rd + e * S::B_STEP + j * 2048 + rd0);
-            bf[j].u[1] = *(const u32x4*)(st + b_rd + e * S::B_STEP + j * 2048 + rd1);
+            f.bf[j].u[0] = *(const u32x4*)(st + b_rd + e * S::B_STEP + j * 2048 + rd0);
+            f.bf[j].u[1] = *(const u32x4*)(st + b_rd + e * S::B_STEP + j * 2048 + rd1);
         }
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
-            af[i].u = *(const u32x4*)(st + a_rd + i * 2048 + (second ? rd1 : rd0));
-            ai[i] = *(const uint16_t*)(pm + i * 16 * S::M_ROW + (second ? 8 : 0));
+            f.af[i].u = *(const u32x4*)(st + a_rd + i * 2048 + (second ? rd1 : rd0));
+            f.ai[i] = *(const uint16_t*)(pm + i * 16 * S::M_ROW);
         }
+    };
+    auto multiply = [&](const Frags& f) {
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int j = 0; j < NF; ++j)
-                acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(af[i].v, bf[j].v, acc[i][j], ai[i], 0, 0);
+                acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(f.af[i].v, f.bf[j].v, acc[i][j], f.ai[i], 0, 0);
+    };
+    // pair p, with index u in its block of metadata, has landed and everybody has read what came before it (in the last
+    // STAGES - 2 pairs there are fewer loads behind it: then all are waited for)
+    auto landed = [&](int p, auto index) {
+        constexpr int leave = ring_leave<S>(decltype(index)::value, A_LD + B_LD, M_LD);
+        if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 0));
+        else WAIT_HERE(waitcnt_imm(0, 0));
+        wg_barrier();
     };
 
 #pragma unroll
     for (int p = 0; p < S::STAGES - 1; ++p)
         if (p < pairs) issue(p, p, p % META_PAIRS == 0);
+    landed(0, std::integral_constant<int, 0>{});
+    Frags f0, f1;
+    read(f0, 0, 0, 0, 0, TAIL && ksteps == 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (S::STAGES - 1 < pairs) issue(S::STAGES - 1, S::STAGES - 1, (S::STAGES - 1) % META_PAIRS == 0);
     int stage = 0;
-    auto pair = [&](int p, auto index) {                      // index = p % META_PAIRS
-        constexpr int u = decltype(index)::value, leave = ring_leave<S>(u, A_LD + B_LD, M_LD);
-        // in the last STAGES - 2 pairs there are fewer loads behind this pair's: then for all of them
-        if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 0));
-        else WAIT_HERE(waitcnt_imm(0, 0));
-        wg_barrier();
-        if (p + S::STAGES - 1 < pairs)
-            issue(p + S::STAGES - 1, stage == 0 ? S::STAGES - 1 : stage - 1, (u + S::STAGES - 1) % META_PAIRS == 0);
-        const uint8_t* st = smem + stage * S::STAGE;
-        const uint8_t* pm = smem + m_rd + (p / META_PAIRS & 1) * S::M_BLOCK + (u ^ m_sw) * 16;
+    auto pair = [&](int p, auto index) {                      // index = p % META_PAIRS; f0 holds the pair's first k-step
+        constexpr int u = decltype(index)::value, next = (u + 1) % META_PAIRS;
         const bool odd_end = TAIL && 2 * p + 1 >= ksteps;
-        multiply(st, pm, 0, odd_end);
-        if (!odd_end) multiply(st, pm, 1, true);
-        stage = stage == S::STAGES - 1 ? 0 : stage + 1;
+        if (!odd_end) read(f1, stage, p, u, 1, true);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f0);
+        if (p + 1 < pairs) {
+            landed(p + 1, std::integral_constant<int, next>{});
+            const int after = stage == S::STAGES - 1 ? 0 : stage + 1;
+            read(f0, after, p + 1, next, 0, TAIL && 2 * p + 3 >= ksteps);
+            __builtin_amdgcn_sched_barrier(0);
+            if (p + S::STAGES < pairs) issue(p + S::STAGES, stage, (u + S::STAGES) % META_PAIRS == 0);
+            stage = after;
+        }
+        if (!odd_end) multiply(f1);
     };
     for (int p = 0; p < pairs; p += META_PAIRS) {
         pair(p, std::integral_constant<int, 0>{});

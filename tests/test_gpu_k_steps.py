@@ -37,3 +37,19 @@ def test_weight_gradient(b, d_out, d_in):
     _, meta, mask = sl.slope_prune_rows(gauss(d_out, d_in), want_mask=True)
     want = (dY.float().t() @ X.float())[unpack_bits(mask)].reshape(d_out, d_in // 2)
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
+
+
+# sparse products on 64 x 64, 128 x 64, 192 x 64, 128 x 128, 192 x 128, 256 x 128, 192 x 192 and 256 x 192 tiles (without an adapter or scratch for
+# slabs; the ring kernel's pairs, odd ends of them, blocks of metadata; the other kernel's quads and what is left of them)
+SPARSE = [(500, 1032), (1000, 2040), (700, 4160), (2000, 1920), (2040, 3000), (2048, 3900), (2040, 4352), (3000, 4000)]
+
+
+@pytest.mark.parametrize("ksteps", [2, 3, 4, 5, 6, 7, 8, 9, 11, 16, 21])
+@pytest.mark.parametrize("b,d_out", SPARSE)
+def test_sparse_product(b, d_out, ksteps):
+    d_out -= d_out % 8
+    print(f"spmm b={b} d_out={d_out} k-steps={ksteps} plan={sl.slope_spmm_fwd_plan(b, 64 * ksteps, d_out)}", flush=True)
+    X, W = gauss(b, 64 * ksteps), gauss(d_out, 64 * ksteps)
+    vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    want = X.float() @ torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float().t()
+    assert_all_close(sl.slope_spmm_fwd(X, vals, meta), want, "Y")
