@@ -258,6 +258,23 @@ __device__ __forceinline__ bool split_item(const SplitJob& job, const bf16_t* __
     return true;
 }
 
+// The 256 x 256 tiles left over after the whole rounds of a wide grid, positions first .. first + count - 1 of its order, as
+// tiles of BM x BN that divide them.  An XCD gets an equal run of them, the parts of one side by side.
+struct Leftover { int first, count, tiles_m, tiles_n; };
+template <int BM, int BN>
+__host__ __device__ inline bool leftover_tile(int block, const Leftover& left, int& tm, int& tn) {
+    constexpr int PM = 256 / BM, PN = 256 / BN;
+    const int run = (left.count + XCDS - 1) / XCDS, slot = block / XCDS, part = slot % (PM * PN);
+    const int mine = slot / (PM * PN), tile = block % XCDS * run + mine;
+    if (mine >= run || tile >= left.count) return false;
+    tile_of_position(left.first + tile, left.tiles_m, left.tiles_n, tm, tn);
+    tm = tm * PM + part % PM;
+    tn = tn * PN + part / PM;
+    return true;
+}
+template <int BM, int BN>
+inline int leftover_grid(const Leftover& left) { return (left.count + XCDS - 1) / XCDS * XCDS * (256 / BM) * (256 / BN); }
+
 template <int BM, int BN, bool TAIL, bool SPLIT>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __restrict__ B, int n,
                                                             const bf16_t* __restrict__ Av,
@@ -265,7 +282,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
                                                             const bf16_t* __restrict__ B2,
                                                             const bf16_t* __restrict__ A2, int K2,
                                                             bf16_t* __restrict__ C, int tiles_m, int tiles_n,
-                                                            SplitJob job) {
+                                                            SplitJob job, Leftover left) {
     using S = SpmmSmem<BM, BN>;
     constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront
     constexpr int A_LD = BM / 64, B_LD = BN / 64;            // 1 KiB loads per wavefront: per pair, per step
@@ -277,7 +294,14 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
         static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
-        if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+        if (left.count) {                                     // uniform
+            if constexpr (256 % BM == 0 && 256 % BN == 0) {
+                if (!leftover_tile<BM, BN>((int)blockIdx.x, left, tm, tn)) return;
+                if (tm * BM >= m || tn * BN >= n) return;     // a part past the edge of a ragged tile
+            }
+        } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
+            return;
+        }
     }
     const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63;
@@ -720,7 +744,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
                                                                  const bf16_t* __restrict__ B2,
                                                                  const bf16_t* __restrict__ A2, int K2,
                                                                  bf16_t* __restrict__ C, int tiles_m, int tiles_n,
-                                                                 SplitJob job) {
+                                                                 SplitJob job, Leftover left) {
     using S = RingSmem<BM, BN>;
     constexpr int META_PAIRS = S::META_PAIRS;
     constexpr int WM = BM == 128 && BN == 128 ? 2 : 4, WN = 8 / WM;    // wavefronts over the tile: the squarest fragments
@@ -735,7 +759,14 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
         static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
-        if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+        if (left.count) {                                     // uniform
+            if constexpr (256 % BM == 0 && 256 % BN == 0) {
+                if (!leftover_tile<BM, BN>((int)blockIdx.x, left, tm, tn)) return;
+                if (tm * BM >= m || tn * BN >= n) return;     // a part past the edge of a ragged tile
+            }
+        } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
+            return;
+        }
     }
     const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63;
@@ -1112,43 +1143,45 @@ int tile_grid(int tiles_m, int tiles_n, int64_t n, const SplitJob& job) {
 
 template <int BM, int BN, bool TAIL, bool SPLIT>
 hipError_t launch_tile_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job) {
+                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job, const Leftover& left) {
     using S = SpmmSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
     hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    spmm_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)tile_grid<SPLIT>(tiles_m, tiles_n, n, job)), dim3(SPMM_THREADS), S::TOTAL, s>>>(
-        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
+    const int grid = left.count ? leftover_grid<BM, BN>(left) : tile_grid<SPLIT>(tiles_m, tiles_n, n, job);
+    spmm_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job, left);
     return hipGetLastError();
 }
 
 template <int BM, int BN, bool TAIL, bool SPLIT>
 hipError_t launch_ring_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job) {
+                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job, const Leftover& left) {
     using S = RingSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
     hipError_t e = allow_dynamic_lds<spmm_ring_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    spmm_ring_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)tile_grid<SPLIT>(tiles_m, tiles_n, n, job)), dim3(SPMM_THREADS), S::TOTAL, s>>>(
-        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
+    const int grid = left.count ? leftover_grid<BM, BN>(left) : tile_grid<SPLIT>(tiles_m, tiles_n, n, job);
+    spmm_ring_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job, left);
     return hipGetLastError();
 }
 
 // a whole product, or one split over k
 template <int BM, int BN, bool SPLIT = false>
 hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}) {
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}, const Leftover& left = {}) {
     auto launch = K % 256 == 0 ? launch_tile_as<BM, BN, false, SPLIT> : launch_tile_as<BM, BN, true, SPLIT>;
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job);
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job, left);
 }
 
 template <int BM, int BN, bool SPLIT = false>
 hipError_t launch_ring(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}) {
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}, const Leftover& left = {}) {
     auto launch = K % 128 == 0 ? launch_ring_as<BM, BN, false, SPLIT> : launch_ring_as<BM, BN, true, SPLIT>;
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job);
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job, left);
 }
 
 // C[idx] = bf16( sum over slabs, in order, of P[s][idx] ), four elements per thread
@@ -1168,15 +1201,30 @@ __global__ void __launch_bounds__(256) slab_reduce_kernel(const f32x4* __restric
 
 template <bool PREFETCH, bool TAIL>
 hipError_t launch_split_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                           const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, int tiles_m, int tiles_n,
+                           const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, int tiles_m, int tiles_n, int grid,
                            hipStream_t s) {
     using S = SplitSmem;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     hipError_t e = allow_dynamic_lds<spmm_split_kernel<PREFETCH, TAIL>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    spmm_split_kernel<PREFETCH, TAIL><<<dim3((unsigned)super_grid(tiles_m, tiles_n)), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+    spmm_split_kernel<PREFETCH, TAIL><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
         B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n);
     return hipGetLastError();
+}
+
+// A last round of 256 x 256 tiles that at most half of the compute units would have a tile of: its tiles as one round of
+// tiles of a half, 256 x 128, or up to a quarter of a round of 128 x 128, in a launch of their own.  The first launch is whole rounds
+// then: its workgroups 0 .. first - 1 are exactly the positions 0 .. first - 1 of the order.  Half a round's own compute units
+// pull their operands faster than a full round's, so that halving the tiles pays on long contractions only (us, from the last-level
+// cache and from HBM, one launch / two: 64 tiles left, 16384 tokens, 4352 x 4352 309 / 289 and 379 / 345; 48, 4096, 4864 x 2048 58.6 /
+// 54.8 and 58.5 / 53.4; 16, 4096, 4352 x 2048 58.7 / 52.8 and 59.8 / 53.7; 64, 16384, 4352 x 1024 97.3 / 96.4 and 109.7 / 108.3, x 512 64.7
+// / 64.6 and 80.1 / 83.4; 128 left, 16384, 2560 x 10240 469 / 451 and 542 / 521, x 6144 267 / 266 and 315 / 297, x 4096 171 / 175 and 208
+// / 197, x 2048 94.6 / 97.8 and 110.8 / 114.0; 12288, 6144 x 4160 303 / 311 and 356 / 367).
+inline Leftover leftover_tiles(int tiles_m, int tiles_n, int64_t K) {
+    const int64_t tiles = (int64_t)tiles_m * tiles_n, rem = tiles % RESIDENT;
+    const int64_t shortest = rem <= RESIDENT / 4 ? 2048 : 6144;
+    if (!wide_grid(tiles_m, tiles_n) || tiles > (1 << 30) || rem == 0 || rem > RESIDENT / 2 || K < shortest) return {0, 0, 0, 0};
+    return {(int)(tiles - rem), (int)rem, tiles_m, tiles_n};
 }
 
 hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
@@ -1186,7 +1234,11 @@ hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint
     const bool prefetch = wide_grid(tiles_m, tiles_n) && (size_t)n * (size_t)K * 2 > LAST_LEVEL_CACHE_BYTES;
     auto launch = K % 256 == 0 ? (prefetch ? launch_split_as<true, false> : launch_split_as<false, false>)
                                : (prefetch ? launch_split_as<true, true> : launch_split_as<false, true>);
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, tiles_m, tiles_n, s);
+    const Leftover left = leftover_tiles(tiles_m, tiles_n, K);
+    const hipError_t e = launch(B, n, Av, Am, m, K, B2, A2, K2, C, tiles_m, tiles_n, left.count ? left.first : super_grid(tiles_m, tiles_n), s);
+    if (e != hipSuccess || !left.count) return e;
+    if (left.count > RESIDENT / 4) return launch_tile<256, 128>(B, n, Av, Am, m, K, B2, A2, K2, C, s, {}, left);
+    return launch_ring<128, 128>(B, n, Av, Am, m, K, B2, A2, K2, C, s, {}, left);
 }
 
 }  // namespace
@@ -1316,7 +1368,16 @@ static double best_tile_us(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     const double ksteps = (double)K / 64.0;
     double least = one_round_of_64(n, m) ? launch_us(tile_cost(n, m, K, 64, 64), ksteps, 1) : 1e300;
     for (const SpmmTile& t : SPMM_TILES) {
-        const double us = launch_us(tile_cost(n, m, K, t.bm, t.bn), ksteps, 1);
+        const TileCost cost = tile_cost(n, m, K, t.bm, t.bn);
+        double us = launch_us(cost, ksteps, 1);
+        if (t.bm == 256 && t.bn == 256) {                     // whole rounds, and a round of 128 x 128 or 256 x 128 tiles with its launch
+            const Leftover left = leftover_tiles((int)((m + 255) / 256), (int)((n + 255) / 256), K);
+            const bool halves = left.count > RESIDENT / 4;
+            TileCost part = tile_cost(n, m, K, halves ? 256 : 128, 128);
+            part.tiles = left.count * (halves ? 2 : 4);
+            part.stream = 0.0;
+            if (left.count) us = launch_us({left.first, cost.start, cost.step, 0.0, cost.stream}, ksteps, 1) + launch_us(part, ksteps, 1) + 3.0;
+        }
         if (us < least) { least = us; bm = t.bm; bn = t.bn; }
     }
     return least;

@@ -53,3 +53,21 @@ def test_sparse_product(b, d_out, ksteps):
     vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
     want = X.float() @ torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float().t()
     assert_all_close(sl.slope_spmm_fwd(X, vals, meta), want, "Y")
+
+
+# whole rounds of 256 x 256 tiles and 33 or 64 left over, in quarters, or 128, in halves; parts that lie past the edge of a ragged tile;
+# an odd number of k-steps; with and without an adapter
+@pytest.mark.parametrize("r", [0, 32])
+@pytest.mark.parametrize("b,d_out,d_in", [(4350, 4344, 2048), (4140, 4352, 2048), (4350, 4352, 2112), (4000, 5120, 3072),
+                                          (16300, 2552, 6144), (16200, 2440, 6208)])
+def test_leftover_tiles_of_a_sparse_product(b, d_out, d_in, r):
+    print(f"spmm b={b} d_out={d_out} d_in={d_in} r={r} plan={sl.slope_spmm_fwd_plan(b, d_in, d_out, r)}", flush=True)
+    X, W = gauss(b, d_in), gauss(d_out, d_in)
+    vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    kept = torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float()
+    if not r:
+        assert_all_close(sl.slope_spmm_fwd(X, vals, meta), X.float() @ kept.t(), "Y")
+        return
+    L, R = gauss(d_in, r) * 0.02, gauss(r, d_out)
+    T = (X.float() @ L.float()).to(torch.bfloat16).float()
+    assert_all_close(sl.slope_spmm_fwd(X, vals, meta, L, R), X.float() @ kept.t() + T @ R.float(), "Y", two_stage=True)
