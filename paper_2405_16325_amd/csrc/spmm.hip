@@ -209,7 +209,7 @@ __device__ __forceinline__ int64_t quad_offset(int quad, int ksteps, int half) {
 // the row instead: an odd last k-step then sits where the second step of its pair (the second 8 bytes of its 16 of
 // metadata) belongs, and that is where it is read.  A template parameter, so that whole quads pay nothing for it.
 //
-// SPLIT: the k range is cut into slabs of slab_steps k-steps (whole quads), which leave fp32 partial sums in slabs[slab].
+// SplitJob: the k range is cut into slabs of slab_steps k-steps (whole quads), which leave fp32 partial sums in slabs[slab].
 // The (tile, slab) pairs are dealt to the XCDs in equal shares, slab by slab (a slab's tiles share its tokens in L2): an
 // eighth of every slab's tiles where that is a whole number, else eight equal runs of all pairs,
 // the token tiles of a weight tile side by side.  A grid with the slabs in blockIdx.y gave 36 tiles per slab to seven of
@@ -275,14 +275,31 @@ __host__ __device__ inline bool leftover_tile(int block, const Leftover& left, i
 template <int BM, int BN>
 inline int leftover_grid(const Leftover& left) { return (left.count + XCDS - 1) / XCDS * XCDS * (256 / BM) * (256 / BN); }
 
-template <int BM, int BN, bool TAIL, bool SPLIT>
+// What a launch of a tile kernel is: a whole product, one split over k (SplitJob), or a wide grid's leftover tiles (Leftover).  Each
+// has only its own arguments: with all of them in one kernel whole products of a few us took 0.2 us longer, for a further
+// read of arguments before the first load (2 to 4 %: 447 tokens, 2168 x 128 4.46 us, 559, 3960 x 128 5.78 -> 6.04).
+struct WholeJob {};
+template <class Job> constexpr bool is_split = std::is_same<Job, SplitJob>::value;
+template <class Job> constexpr bool is_leftover = std::is_same<Job, Leftover>::value;
+
+// The workgroup's tile of a launch that is not split; false: none
+template <int BM, int BN>
+__device__ __forceinline__ bool tile_of(const WholeJob&, int m, int n, int tiles_m, int tiles_n, int& tm, int& tn) {
+    return tile_of_block(tiles_m, tiles_n, tm, tn);
+}
+template <int BM, int BN>
+__device__ __forceinline__ bool tile_of(const Leftover& left, int m, int n, int tiles_m, int tiles_n, int& tm, int& tn) {
+    return leftover_tile<BM, BN>((int)blockIdx.x, left, tm, tn) && tm * BM < m && tn * BN < n;   // (parts past the edge of a ragged tile)
+}
+
+template <int BM, int BN, bool TAIL, class Job>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __restrict__ B, int n,
                                                             const bf16_t* __restrict__ Av,
                                                             const uint8_t* __restrict__ Am, int m, int K,
                                                             const bf16_t* __restrict__ B2,
                                                             const bf16_t* __restrict__ A2, int K2,
                                                             bf16_t* __restrict__ C, int tiles_m, int tiles_n,
-                                                            SplitJob job, Leftover left) {
+                                                            Job job) {
     using S = SpmmSmem<BM, BN>;
     constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront
     constexpr int A_LD = BM / 64, B_LD = BN / 64;            // 1 KiB loads per wavefront: per pair, per step
@@ -290,18 +307,11 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     extern __shared__ __align__(16) uint8_t smem[];
 
     int tm, tn, slab = 0, extension_slab = 0;
-    if constexpr (SPLIT) {
+    if constexpr (is_split<Job>) {
         static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
-        if (left.count) {                                     // uniform
-            if constexpr (256 % BM == 0 && 256 % BN == 0) {
-                if (!leftover_tile<BM, BN>((int)blockIdx.x, left, tm, tn)) return;
-                if (tm * BM >= m || tn * BN >= n) return;     // a part past the edge of a ragged tile
-            }
-        } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
-            return;
-        }
+        if (!tile_of<BM, BN>(job, m, n, tiles_m, tiles_n, tm, tn)) return;
     }
     const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63;
@@ -346,9 +356,15 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     const int b_rd = S::B_OFF + (wn * NF) * 2048;
     const int m_rd = S::M_OFF + wm * MF * 512 + l16 * 16 + lq * 2;
 
-    const int k_first = SPLIT ? slab * job.slab_steps : 0;    // a multiple of 4
+    int k_first = 0, slab_steps = K / 64;
+    float* sums = nullptr;
+    if constexpr (is_split<Job>) {
+        slab_steps = job.slab_steps;
+        k_first = slab * slab_steps;                          // a multiple of 4
+        sums = job.slabs + (size_t)slab * (size_t)n * (size_t)m;
+    }
     // a multiple of 4 unless TAIL
-    const int ksteps = SPLIT && K / 64 - k_first > job.slab_steps ? job.slab_steps : K / 64 - k_first;
+    const int ksteps = K / 64 - k_first > slab_steps ? slab_steps : K / 64 - k_first;
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) a_src[i] += (size_t)k_first * 64;
 #pragma unroll
@@ -460,8 +476,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
     extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
-                                     slab == extension_slab ? K2 : 0, C, smem, m0, n0,
-                                     SPLIT ? job.slabs + (size_t)slab * (size_t)n * (size_t)m : nullptr);
+                                     slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -737,14 +752,14 @@ constexpr int ring_leave(int u, int each, int meta) {
 
 // TAIL: an odd number of k-steps; the values and metadata of the last one are then fetched as the second half of a pair that
 // ends with the row (see spmm_kernel).
-template <int BM, int BN, bool TAIL, bool SPLIT>
+template <int BM, int BN, bool TAIL, class Job>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* __restrict__ B, int n,
                                                                  const bf16_t* __restrict__ Av,
                                                                  const uint8_t* __restrict__ Am, int m, int K,
                                                                  const bf16_t* __restrict__ B2,
                                                                  const bf16_t* __restrict__ A2, int K2,
                                                                  bf16_t* __restrict__ C, int tiles_m, int tiles_n,
-                                                                 SplitJob job, Leftover left) {
+                                                                 Job job) {
     using S = RingSmem<BM, BN>;
     constexpr int META_PAIRS = S::META_PAIRS;
     constexpr int WM = BM == 128 && BN == 128 ? 2 : 4, WN = 8 / WM;    // wavefronts over the tile: the squarest fragments
@@ -755,26 +770,25 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
     extern __shared__ __align__(16) uint8_t smem[];
 
     int tm, tn, slab = 0, extension_slab = 0;
-    if constexpr (SPLIT) {
+    if constexpr (is_split<Job>) {
         static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
-        if (left.count) {                                     // uniform
-            if constexpr (256 % BM == 0 && 256 % BN == 0) {
-                if (!leftover_tile<BM, BN>((int)blockIdx.x, left, tm, tn)) return;
-                if (tm * BM >= m || tn * BN >= n) return;     // a part past the edge of a ragged tile
-            }
-        } else if (!tile_of_block(tiles_m, tiles_n, tm, tn)) {
-            return;
-        }
+        if (!tile_of<BM, BN>(job, m, n, tiles_m, tiles_n, tm, tn)) return;
     }
     const int m0 = tm * BM, n0 = tn * BN;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave % WM, wn = wave / WM;
     const int l16 = lane & 15, lq = lane >> 4;
-    const int k_first = SPLIT ? slab * job.slab_steps : 0;    // a multiple of 4
-    const int ksteps = SPLIT && K / 64 - k_first > job.slab_steps ? job.slab_steps : K / 64 - k_first;
+    int k_first = 0, slab_steps = K / 64;
+    float* sums = nullptr;
+    if constexpr (is_split<Job>) {
+        slab_steps = job.slab_steps;
+        k_first = slab * slab_steps;                          // a multiple of 4
+        sums = job.slabs + (size_t)slab * (size_t)n * (size_t)m;
+    }
+    const int ksteps = K / 64 - k_first > slab_steps ? slab_steps : K / 64 - k_first;
     const int pairs = (ksteps + 1) / 2;
 
     // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8
@@ -905,8 +919,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
     }
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL && 128 * (BM * 2 + 32) <= S::TOTAL, "the staged output tile and factor fit in the ring");
     extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
-                                                   slab == extension_slab ? K2 : 0, C, smem, m0, n0,
-                                                   SPLIT ? job.slabs + (size_t)slab * (size_t)n * (size_t)m : nullptr);
+                                                   slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1134,54 +1147,57 @@ hipError_t launch_generic(const bf16_t* B, int64_t n, const bf16_t* Av, const ui
 }
 
 // workgroups of a launch over the tiles, or over the tiles of every slab and the parts of X L beside them
-template <bool SPLIT>
+template <int BM, int BN>
+int tile_grid(int tiles_m, int tiles_n, int64_t, const WholeJob&) { return super_grid(tiles_m, tiles_n); }
+template <int BM, int BN>
+int tile_grid(int, int, int64_t, const Leftover& left) { return leftover_grid<BM, BN>(left); }
+template <int BM, int BN>
 int tile_grid(int tiles_m, int tiles_n, int64_t n, const SplitJob& job) {
-    if (!SPLIT) return super_grid(tiles_m, tiles_n);
     const int xl = job.L ? job.xl_slabs * ((job.r + SK_BJ - 1) / SK_BJ) * (int)((n + SK_BI - 1) / SK_BI) : 0;
     return ((tiles_m * tiles_n * job.nslabs + XCDS - 1) / XCDS + (xl + XCDS - 1) / XCDS) * XCDS;
 }
 
-template <int BM, int BN, bool TAIL, bool SPLIT>
+template <int BM, int BN, bool TAIL, class Job>
 hipError_t launch_tile_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job, const Leftover& left) {
+                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const Job& job) {
     using S = SpmmSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
-    hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
+    hipError_t e = allow_dynamic_lds<spmm_kernel<BM, BN, TAIL, Job>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    const int grid = left.count ? leftover_grid<BM, BN>(left) : tile_grid<SPLIT>(tiles_m, tiles_n, n, job);
-    spmm_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
-        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job, left);
+    const int grid = tile_grid<BM, BN>(tiles_m, tiles_n, n, job);
+    spmm_kernel<BM, BN, TAIL, Job><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
     return hipGetLastError();
 }
 
-template <int BM, int BN, bool TAIL, bool SPLIT>
+template <int BM, int BN, bool TAIL, class Job>
 hipError_t launch_ring_as(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job, const Leftover& left) {
+                          const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const Job& job) {
     using S = RingSmem<BM, BN>;
     static_assert(S::TOTAL <= 160 * 1024, "LDS budget");
     int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
-    hipError_t e = allow_dynamic_lds<spmm_ring_kernel<BM, BN, TAIL, SPLIT>>(S::TOTAL);
+    hipError_t e = allow_dynamic_lds<spmm_ring_kernel<BM, BN, TAIL, Job>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    const int grid = left.count ? leftover_grid<BM, BN>(left) : tile_grid<SPLIT>(tiles_m, tiles_n, n, job);
-    spmm_ring_kernel<BM, BN, TAIL, SPLIT><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
-        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job, left);
+    const int grid = tile_grid<BM, BN>(tiles_m, tiles_n, n, job);
+    spmm_ring_kernel<BM, BN, TAIL, Job><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+        B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
     return hipGetLastError();
 }
 
 // a whole product, or one split over k
-template <int BM, int BN, bool SPLIT = false>
+template <int BM, int BN, class Job = WholeJob>
 hipError_t launch_tile(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}, const Leftover& left = {}) {
-    auto launch = K % 256 == 0 ? launch_tile_as<BM, BN, false, SPLIT> : launch_tile_as<BM, BN, true, SPLIT>;
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job, left);
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const Job& job = {}) {
+    auto launch = K % 256 == 0 ? launch_tile_as<BM, BN, false, Job> : launch_tile_as<BM, BN, true, Job>;
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job);
 }
 
-template <int BM, int BN, bool SPLIT = false>
+template <int BM, int BN, class Job = WholeJob>
 hipError_t launch_ring(const bf16_t* B, int64_t n, const bf16_t* Av, const uint8_t* Am, int64_t m, int64_t K,
-                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const SplitJob& job = {}, const Leftover& left = {}) {
-    auto launch = K % 128 == 0 ? launch_ring_as<BM, BN, false, SPLIT> : launch_ring_as<BM, BN, true, SPLIT>;
-    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job, left);
+                       const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s, const Job& job = {}) {
+    auto launch = K % 128 == 0 ? launch_ring_as<BM, BN, false, Job> : launch_ring_as<BM, BN, true, Job>;
+    return launch(B, n, Av, Am, m, K, B2, A2, K2, C, s, job);
 }
 
 // C[idx] = bf16( sum over slabs, in order, of P[s][idx] ), four elements per thread
@@ -1237,8 +1253,8 @@ hipError_t launch_split(const bf16_t* B, int64_t n, const bf16_t* Av, const uint
     const Leftover left = leftover_tiles(tiles_m, tiles_n, K);
     const hipError_t e = launch(B, n, Av, Am, m, K, B2, A2, K2, C, tiles_m, tiles_n, left.count ? left.first : super_grid(tiles_m, tiles_n), s);
     if (e != hipSuccess || !left.count) return e;
-    if (left.count > RESIDENT / 4) return launch_tile<256, 128>(B, n, Av, Am, m, K, B2, A2, K2, C, s, {}, left);
-    return launch_ring<128, 128>(B, n, Av, Am, m, K, B2, A2, K2, C, s, {}, left);
+    if (left.count > RESIDENT / 4) return launch_tile<256, 128>(B, n, Av, Am, m, K, B2, A2, K2, C, s, left);
+    return launch_ring<128, 128>(B, n, Av, Am, m, K, B2, A2, K2, C, s, left);
 }
 
 }  // namespace
@@ -1478,11 +1494,11 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
     const int64_t K2 = ad.T ? -ad.r : 0;
     hipError_t e;
     switch (split.bm * 1000 + split.bn) {
-        case 128064: e = launch_ring<128, 64, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
-        case 192064: e = launch_ring<192, 64, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
-        case 256064: e = launch_ring<256, 64, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
-        case 128128: e = launch_ring<128, 128, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
-        default: e = launch_tile<256, 128, true>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 128064: e = launch_ring<128, 64>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 192064: e = launch_ring<192, 64>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 256064: e = launch_ring<256, 64>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        case 128128: e = launch_ring<128, 128>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
+        default: e = launch_tile<256, 128>(B, n, A_vals, A_meta, m, K, ad.T, A2, K2, nullptr, s, job); break;
     }
     if (e != hipSuccess) return e;
     if (ad.r && !ad.T) return launch_adapter_finish(slabs, nslabs, n, m, ad.Q, ad.x.slabs, ad.R, ad.r, C, s);
