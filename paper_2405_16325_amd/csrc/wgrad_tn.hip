@@ -88,17 +88,21 @@ struct TnSmem {
 constexpr int TN_THREADS = 512;
 enum { EPI_MASKED_PACKED = 0, EPI_PLAIN = 1 };
 
-// Metadata of the 32 columns of W^R from c (a multiple of 32) of row o; columns outside the matrix: any.  Rows of a multiple of 32
-// columns are read by dwords, others by bytes.
-__device__ __forceinline__ uint32_t meta_dword(const uint8_t* __restrict__ meta, int o, int c, int m, int n) {
-    const uint8_t* p = meta + (size_t)o * (m / 8) + c / 8;
-    if (o >= n) return 0u;
-    if (m % 32 == 0) return c < m ? *(const uint32_t*)p : 0u;  // uniform
-    uint32_t w = 0;
+// Metadata of the 32 Q columns of W^R from c (a multiple of 32) of row o, by dwords; columns outside the matrix: any.  The dwords of
+// rows that are not a multiple of 32 columns may lie at any byte, and the last of such a row, which ends inside it, is read by bytes.
+template <int Q>
+__device__ __forceinline__ void load_meta(const uint8_t* __restrict__ meta, int o, int c, int m, int n, uint32_t (&w)[Q]) {
+    typedef uint32_t __attribute__((aligned(1))) u32_a1;
+    const uint8_t* const p = meta + (size_t)o * (m / 8) + c / 8;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (c + 8 * e < m) w |= (uint32_t)p[e] << (8 * e);
-    return w;
+    for (int q = 0; q < Q; ++q) w[q] = o < n && c + 32 * q + 32 <= m ? *(const u32_a1*)(p + 4 * q) : 0u;
+    if (m % 32 != 0 && c < m && c + 32 * Q > m) {             // uniform
+        uint32_t v = 0;
+        if (o < n)
+            for (int e = 0; e < m / 8 % 4; ++e) v |= (uint32_t)p[(m - c) / 32 * 4 + e] << (8 * e);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) w[q] = q == (m - c) / 32 ? v : w[q];
+    }
 }
 
 // Masked, packed epilogue: acc[i][j] of a wavefront is the 16 x 16 fragment at D rows c0 + 16 i (d_in) and D
@@ -122,9 +126,7 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
         int o = o0 + j * 16 + l16;
         // metadata of the wavefront's WM d_in columns of row o: WM / 4 groups = WM / 8 bytes
         uint32_t mw[WM / 32];
-#pragma unroll
-        for (int q = 0; q < WM / 32; ++q)
-            mw[q] = meta_dword(meta, o, c0 + 32 * q, m, n);
+        load_meta(meta, o, c0, m, n, mw);
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
             int gl = i * 4 + lq;                              // group index inside the WM columns
@@ -140,8 +142,8 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
         }
     }
     __syncthreads();
-    // 16-byte pieces (four pairs = sixteen columns of W), all read from LDS before the first is stored; where rows are not a
-    // multiple of 16 columns they leave in halves, each inside the row or outside as a whole
+    // 16-byte pieces (four pairs = sixteen columns of W), all read from LDS before the first is stored; the last of a row that is not
+    // a multiple of 16 columns is a half one
     constexpr int PPR = BMT / 16, PIECES = BNT * PPR, PER_THREAD = (PIECES + TN_THREADS - 1) / TN_THREADS;
     constexpr bool EVEN = PIECES % TN_THREADS == 0;           // else the last round of pieces is for the first threads only
     u32x4 piece[PER_THREAD];
@@ -154,14 +156,14 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     for (int u = 0; u < PER_THREAD; ++u) {
         const int idx = (int)threadIdx.x + u * TN_THREADS;
         const int o = tile_o0 + idx / PPR, col = tile_c0 + (idx % PPR) * 16;
-        if ((!EVEN && idx >= PIECES) || o >= n || col >= m) continue;
-        bf16_t* const dst = out + (size_t)o * gpitch + (col >> 1);
-        if (m % 16 == 0) {                                    // uniform
-            *(u32x4*)dst = piece[u];
-        } else {
-            *(u32x2*)dst = (u32x2){piece[u][0], piece[u][1]};
-            if (col + 8 < m) *(u32x2*)(dst + 4) = (u32x2){piece[u][2], piece[u][3]};
-        }
+        if ((EVEN || idx < PIECES) && o < n && col + 16 <= m) *(u32x4_a8*)(out + (size_t)o * gpitch + (col >> 1)) = piece[u];
+    }
+    if (m % 16 == 0) return;                                  // uniform
+#pragma unroll
+    for (int u = 0; u < PER_THREAD; ++u) {
+        const int idx = (int)threadIdx.x + u * TN_THREADS;
+        const int o = tile_o0 + idx / PPR, col = tile_c0 + (idx % PPR) * 16;
+        if ((EVEN || idx < PIECES) && o < n && col + 8 == m) *(u32x2*)(out + (size_t)o * gpitch + (col >> 1)) = (u32x2){piece[u][0], piece[u][1]};
     }
 }
 
