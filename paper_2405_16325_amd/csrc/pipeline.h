@@ -28,7 +28,7 @@ constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 1
 // Kernel arguments, all in registers from here on: a kernel's head then waits once for them, where the compiler, which fetches an
 // argument shortly before its first use, makes up to four such waits follow one another before the first load of an operand
 // (0.1 to 0.3 us of a launch; us, without / with: sparse, 1278 tokens, 1608 x 192 on 128 x 128 6.89 / 6.69; 851, 3064 x 192 on
-// 128 x 96 6.26 / 6.13; 3178, 1280 x 384 on 192 x 128 9.15 / 9.00).
+// 128 x 96 6.26 / 6.13; 3178, 1280 x 384 on 192 x 128 9.15 / 9.00; dense, 9357 x 256 over 384 7.76 / 7.55).
 template <class... T>
 __device__ __forceinline__ void fetch_arguments(T... args) {
     auto fetch = [](auto v) { asm volatile("" ::"s"(v)); };

@@ -348,6 +348,7 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(DenseOperand At, D
     using S = TnSmem<BM, BN, NS>;
     constexpr int MF = BM / 32, NF = BN / 64;
     extern __shared__ __align__(16) uint8_t smem[];
+    fetch_arguments(At.p, At.rows, At.ld, At.k, Bt.p, Bt.rows, Bt.ld, Bt.k, ksteps, meta, out, tiles_m, tiles_n);
     int tm, tn;
     if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
     const int m0 = tm * BM, n0 = tn * BN, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
