@@ -106,11 +106,14 @@ hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s);         
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s);    // B's k-contiguous, A k-major; A k-contiguous
 hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s); // all operands k-major
 // dW from operands as stored; Xt, dYt: scratch of token_copy_bytes each for copies that it may make, or null; tail: see
-// launch_wgrad_masked_t.  launch_wgrad_wide: extents from 2^24 on
+// launch_wgrad_masked_t.  launch_wgrad_wide: extents from 2^24 on; launch_wgrad_groups: where wgrad_in_groups
 hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in,
                                bf16_t* gvals, bf16_t* Xt, bf16_t* dYt, float* tail_or_null, hipStream_t s);
 hipError_t launch_wgrad_wide(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in,
                              bf16_t* gvals, hipStream_t s);
+bool wgrad_in_groups(int64_t b, int64_t d_in, int64_t d_out);
+hipError_t launch_wgrad_groups(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in,
+                               bf16_t* gvals, hipStream_t s);
 // the same result from token-contiguous copies Xt [d_in][ld], dYt [d_out][ld] (ld = the pitch behind
 // token_copy_bytes); launch_token_copies writes one or two such copies (in1 == nullptr: one)
 size_t token_copy_bytes(int64_t b, int64_t d);

@@ -892,6 +892,7 @@ int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
 hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in, bf16_t* gvals,
                                bf16_t* Xt, bf16_t* dYt, float* tail_or_null, hipStream_t s) {
     if (d_in >= KMAJOR_EXTENT_MAX || d_out >= KMAJOR_EXTENT_MAX) return launch_wgrad_wide(dY, X, b, meta, d_out, d_in, gvals, s);
+    if (wgrad_in_groups(b, d_in, d_out)) return launch_wgrad_groups(dY, X, b, meta, d_out, d_in, gvals, s);
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
     const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
     const int copies = Xt && dYt ? wgrad_copies(b, d_in, d_out, tail_or_null != nullptr) : 0;

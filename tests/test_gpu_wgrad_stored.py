@@ -31,6 +31,18 @@ def test_widths_and_tokens_that_end_inside_a_tile(b, d_out, d_in):
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta, workspace=None), want, "dW without scratch")
 
 
+# the kernel for few tokens: groups without a slab, a slab of one token, one to four trips of the groups, a tile's edges; its last
+# tokens and tiles and the first beyond them (512 tokens on a round of 64 x 64 tiles, 65 to 128 tokens on two)
+@pytest.mark.parametrize("b,d_out,d_in", [(1, 8, 64), (31, 72, 56), (33, 64, 136), (96, 200, 328), (128, 1024, 1024), (129, 520, 8), (257, 8, 1000),
+                                          (384, 456, 1016), (512, 1024, 1016), (513, 1024, 1016), (128, 1032, 1024), (65, 2048, 1024),
+                                          (64, 2048, 1024), (129, 2048, 1024), (100, 2056, 1024)])
+def test_few_tokens_on_few_tiles(b, d_out, d_in):
+    X, dY, meta, keep = layer(b, d_out, d_in)
+    want = (dY.float().t() @ X.float())[keep].reshape(d_out, d_in // 2)
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta, workspace=None), want, "dW without scratch")
+
+
 # (where both are wide, dY, X, and neither is copied): the same sums in the same order from every layout
 @pytest.mark.parametrize("b,d_out,d_in", [(130, 18432, 16384), (100, 9216, 36864), (70, 36864, 9216), (200, 8192, 8192)])
 def test_copies_change_nothing(b, d_out, d_in):
