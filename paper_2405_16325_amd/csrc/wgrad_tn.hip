@@ -878,7 +878,7 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
 // copy is a stream of its operand at 5.9 TB/s.  So an operand is copied, where there is room, when the other one is wide: X from
 // about 9000 rows, dY from about 11000 columns on (16384 tokens, 36864 x 9216: both copied 7462, X 7389, none 7649).
 enum { COPY_X = 1, COPY_DY = 2 };
-int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
+static int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
     if (d_in % 32 != 0 || dense_tile_choice(d_in, d_out, (b + 63) / 64, with_tail) != 0) return 0;
     const double product = 2.0 * (double)d_out * (double)d_in / 1.5e9, x = 4.0 * (double)d_in / 5.9e6, dy = 4.0 * (double)d_out / 5.9e6;   // us per token
     const double cost[4] = {0.088 * product, x + 0.032 * product, dy + 0.042 * product, x + dy};
@@ -888,10 +888,14 @@ int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
     return best;
 }
 
+// Layers that the tiles cannot read as stored.  (Not from copies: us, 500 tokens, 64 x (2^24 + 64), copies and tiles 10580, the kernel
+// with 64-bit addresses 4910.)
+static bool too_wide(int64_t d_in, int64_t d_out) { return d_in >= KMAJOR_EXTENT_MAX || d_out >= KMAJOR_EXTENT_MAX; }
+
 // dW (masked, packed) from dY [b][d_out] and X [b][d_in].  Xt, dYt: room for their copies (launch_token_copies), or null; tail as above.
 hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out, int64_t d_in, bf16_t* gvals,
                                bf16_t* Xt, bf16_t* dYt, float* tail_or_null, hipStream_t s) {
-    if (d_in >= KMAJOR_EXTENT_MAX || d_out >= KMAJOR_EXTENT_MAX) return launch_wgrad_wide(dY, X, b, meta, d_out, d_in, gvals, s);
+    if (too_wide(d_in, d_out)) return launch_wgrad_wide(dY, X, b, meta, d_out, d_in, gvals, s);
     if (wgrad_in_groups(b, d_in, d_out)) return launch_wgrad_groups(dY, X, b, meta, d_out, d_in, gvals, s);
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
     const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
@@ -1092,8 +1096,8 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
 
     hipError_t e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, Xt, dYt, d_in % 32 == 0 ? tail : nullptr, s);
     if (e != hipSuccess) return e;
-    // Extents that are not whole k-steps of the tile kernels or too wide for them, and short products: the kernel for ragged extents
-    if (d_in % 64 != 0 || d_out % 64 != 0 || d_in >= KMAJOR_EXTENT_MAX || d_out >= KMAJOR_EXTENT_MAX ||
+    // Extents that are not whole k-steps of the tile kernels, and short products: the kernel for ragged extents
+    if (d_in % 64 != 0 || d_out % 64 != 0 ||
         (skinny_pair_is_short(b, r, d_in) && skinny_pair_is_short(b, r, d_out) && skinny_pair_is_short(d_in, r, b) && skinny_pair_is_short(r, d_out, b))) {
         if ((e = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s)) != hipSuccess) return e;
         return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);
@@ -1105,6 +1109,9 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     if ((e = launch_skinny_tn<false>(f.tile, skinny_job({L, ir, ir, in}, {X, ib, in, in}, d_in, T, f.slab_steps),
                                      skinny_job({R, ir, out, out}, {dY, ib, out, out}, d_out, T2, f.slab_steps), sums, s)) != hipSuccess)
         return e;
+    // Wide layers: T and T2, whose long contraction wants slabs, are the tiles' in any case (us, the call, 64 tokens, 64 x (2^24 + 64),
+    // rank 64: 71880 with all four products on the kernel for ragged extents, 7800 so)
+    if (too_wide(d_in, d_out)) return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);
     const SkinnyPair g = skinny_pair_plan(d_in, bp, d_out, bp, r, room);
     return launch_skinny_tn<true>(g.tile, skinny_job({T2, ir, ir, ib}, {X, in, in, ib}, b, dL, g.slab_steps),
                                   skinny_job({dY, out, out, ib}, {T, ir, ir, ib}, b, dR, g.slab_steps), sums, s);

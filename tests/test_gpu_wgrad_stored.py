@@ -66,9 +66,31 @@ def test_values_that_are_not_finite_stay_in_their_feature(b, d_out, d_in):
     assert torch.equal(g[rest], bad[rest]) and not torch.isfinite(bad[~rest].float()).any()
 
 
-def test_layer_wider_than_the_offsets_of_the_tiles():
-    b, d_out, d_in = 9, 8, (1 << 24) + 8
+WIDE = (1 << 24) + 8
+
+
+# one slab of tokens and less; several slabs with a remainder, more than one tile along the narrow side, either side wide
+@pytest.mark.parametrize("b,d_out,d_in", [(9, 8, WIDE), (70, 136, WIDE), (70, WIDE, 136)])
+def test_layer_wider_than_the_offsets_of_the_tiles(b, d_out, d_in):
     X, dY, meta, keep = layer(b, d_out, d_in)
     g = sl.slope_wgrad_masked(dY, X, meta)
-    want = (dY.float().t() @ X.float())[keep].reshape(d_out, d_in // 2)
-    assert_all_close(g, want, "dW")
+    for o in range(0, d_out, d_out // 8):                                # in pieces: rows of W
+        rows = slice(o, o + d_out // 8)
+        want = (dY[:, rows].float().t() @ X.float())[keep[rows]].reshape(-1, d_in // 2)
+        assert_all_close(g[rows], want, "dW", chunk=1 << 20)
+
+
+# ... with an adapter: the products over the wide side are long contractions, the gradients of its factor as wide as it is
+@pytest.mark.parametrize("b,d_out,d_in", [(70, 64, (1 << 24) + 64), (33, (1 << 24) + 64, 64)])
+def test_adapter_of_a_layer_wider_than_the_offsets_of_the_tiles(b, d_out, d_in):
+    r = 32
+    X, dY, meta, keep = layer(b, d_out, d_in)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(inputs.SEED_BASE)
+    L, R = (torch.randn(shape, generator=gen, device="cuda").mul_(max(shape) ** -0.5).to(torch.bfloat16) for shape in ((d_in, r), (r, d_out)))
+    dW, dL, dR = sl.slope_wgrad_adapter(dY, X, meta, L, R)
+    assert torch.equal(dW, sl.slope_wgrad_masked(dY, X, meta))
+    T, T2 = ((A.float() @ B.float()).to(torch.bfloat16).float() for A, B in ((X, L), (dY, R.t())))
+    # (in pieces: a library product of more than 2^24 columns has left its last ones zero)
+    assert_all_close(dL, torch.cat([x.float().t() @ T2 for x in X.split(1 << 20, 1)]), "dL", two_stage=True, chunk=1 << 20)
+    assert_all_close(dR, torch.cat([T.t() @ y.float() for y in dY.split(1 << 20, 1)], 1), "dR", two_stage=True)
