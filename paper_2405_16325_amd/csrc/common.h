@@ -100,8 +100,8 @@ struct SkinnyProduct {
     int64_t n, m, K;
     bf16_t* C;
 };
-bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most, int per_round);
-bool skinny_pair_is_short(int64_t n, int64_t m, int64_t K);
+bool skinny_is_short(int64_t n, int64_t m, int64_t K, bool a_kmajor);
+bool skinny_pair_is_short(int64_t b, int64_t d_in, int64_t d_out, int64_t r);
 hipError_t launch_skinny_ragged(const SkinnyProduct& p, hipStream_t s);                           // B k-contiguous
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s);    // B's k-contiguous, A k-major; A k-contiguous
 hipError_t launch_skinny_gradients(const SkinnyProduct& dl, const SkinnyProduct& dr, hipStream_t s); // all operands k-major

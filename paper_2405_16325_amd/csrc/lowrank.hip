@@ -3,10 +3,11 @@
 // The paper concatenates L to the sparse weight so that one vendor SpMM call yields [Y1 | Y2] and
 // a second fused GEMM adds Y2 R.  Here the sparse kernel is simply extended by r more k-steps on
 // dense MFMA (operands T and R as stored), so only the skinny product T = X L is a kernel of its
-// own: the dense tile kernel with a plain epilogue on a k-contiguous copy of L, split over d_in
-// while its tiles are too few to fill the chip; it is bound by reading X once.  With up to
+// own: the dense tile kernel with a plain epilogue, L as stored, split over d_in while its tiles
+// are too few to fill the chip; it is bound by reading X once.  With up to
 // XL_SMALL_MAX_TOKENS tokens the split over d_in in spmm_stream.hip computes T instead, from L as
 // stored.
+#include "pipeline.h"
 #include "skinny.h"
 
 namespace {
@@ -45,21 +46,29 @@ hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, hi
 
 }  // namespace
 
-// Whole k-steps have the choice: the tile kernels stream better, but want a k-contiguous copy of a k-major operand and, on
-// few tiles, a second kernel for the sums over slabs; this one takes operands as stored in one launch, at about 1.3 us per
-// chunk of 32 k that a wavefront walks and round of two workgroups per compute unit.
-// A product by itself, `most` chunks in one round of per_round workgroups: 8 in 512 where it saves the copy and the second
-// kernel (1024 x 2048, rank 64: X L 2.7 + 5.1 + 3.8 -> 10.7 us; in two rounds, 16384 x 1024, rank 96, the forward took 33.1 us,
-// 27.0 with the tile kernel).  5 in 256 where there is no copy to save (dY R^T): with two workgroups per compute unit it
-// takes 12 us where the tile kernel, then in one launch, takes 9 (3 chunks: 3890 x 768, rank 160; 16384 x 768, rank 64; but
-// 1024 x 768, rank 64 6.5 against 7.7).
-bool skinny_is_short(int64_t n, int64_t m, int64_t K, int most, int per_round) {
-    return skinny_tiles(n, m) <= per_round && skinny_chunks(K) <= most;
+// Whole k-steps have the choice: the tile kernels stream better, but on few tiles of a long contraction need a second kernel for the
+// sums over slabs; this one is one launch always, at about 1.3 us per chunk of 32 k that a wavefront walks and round of
+// workgroups.
+// A product by itself, on at most one round of workgroups.  us, the call, tile kernel / here:
+//   X L, up to four chunks, up to six with 64 tiles and more: 1024 x 512, rank 64 11.35 / 10.8; 2048 x 1024, rank 128 16.1 / 16.0;
+//     1024 x 1536, rank 64 (32 tiles) 17.3 / 18.3, rank 160 (96) 19.7 / 19.4; 4096 x 1536, rank 64 (128) 20.1 / 19.0; 1024 x 2048, rank 64
+//     19.4 / 21.5; two rounds, 16384 x 512, rank 64 14.9 / 16.0;
+//   dY R^T, one chunk, four of rank 32, whose A is half a tile: 1024 x 256, rank 64 9.1 / 8.9; 1024 x 512, rank 64 11.15 / 11.5; 520 x 1024,
+//     rank 32 14.4 / 13.9; 520 x 1536, rank 32 16.1 / 17.6.
+bool skinny_is_short(int64_t n, int64_t m, int64_t K, bool a_kmajor) {
+    const int64_t tiles = skinny_tiles(n, m);
+    const int64_t most = a_kmajor ? (tiles < 64 ? 4 : 6) : (m <= 32 ? 4 : 1);
+    return tiles <= RESIDENT && skinny_chunks(K) <= most;
 }
 
-// One of the four products of the gradient call, which replace ten launches by two (1024 tokens, 2048 x 2048, rank 64:
-// 42 -> 21 us; 256 tokens, 2560 x 2560, rank 512, two rounds: the call 51.3 -> 40.3).
-bool skinny_pair_is_short(int64_t n, int64_t m, int64_t K) { return skinny_chunks(K) * ((skinny_tiles(n, m) + 511) / 512) <= 10; }
+// One of the four products of the gradient call, in pairs, which the tile kernels take in two launches or up to four: up to two
+// chunks x rounds of two workgroups per compute unit for the factors T and T2, five for the gradients (us, the call, tile kernels
+// / here: 256 x 256, rank 32, 512 tokens 16.1 / 14.2, 1536 21.8 / 21.7, 2048 24.2 / 25.4; 512 x 512, rank 64, 1024 tokens 21.8 / 21.0,
+// 1536 24.3 / 24.8; 1024 x 1024, rank 64, 64 tokens 14.6 / 15.4; 2048 x 2048, rank 64, 1024 tokens 30.9 / 35.2).
+bool skinny_pair_is_short(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
+    auto cost = [](int64_t n, int64_t m, int64_t K) { return skinny_chunks(K) * ((skinny_tiles(n, m) + 2 * RESIDENT - 1) / (2 * RESIDENT)); };
+    return cost(b, r, d_in) <= 2 && cost(b, r, d_out) <= 2 && cost(d_in, r, b) <= 5 && cost(r, d_out, b) <= 5;
+}
 
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s) {
     return launch_skinny_pair<false, true, false, false>(t, t2, s);

@@ -69,14 +69,14 @@ size_t fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t r, SpmmSplit& sp
 }
 
 // T = X L on the kernel for ragged extents although its extents are whole k-steps
-bool xl_is_short(int64_t n, int64_t r, int64_t d_in) { return skinny_is_short(n, r, d_in, 8, 2 * RESIDENT); }
+bool xl_is_short(int64_t n, int64_t r, int64_t d_in) { return skinny_is_short(n, r, d_in, true); }
 
 // T[n, r] = B[n, K] A^T for the skinny products of the adapters.  a_kmajor: A is [K][r] (the factor L as
 // stored) instead of [r][K].  Whole k-steps of 64 go to the tile kernels, anything else and short products to the kernel
 // for ragged extents.
 hipError_t skinny_product(const bf16_t* B, int64_t n, int64_t K, const bf16_t* A, bool a_kmajor, int64_t r, bf16_t* T,
                           float* partial, hipStream_t s) {
-    if (K % 64 != 0 || (a_kmajor ? xl_is_short(n, r, K) : skinny_is_short(n, r, K, 5, RESIDENT)))
+    if (K % 64 != 0 || skinny_is_short(n, r, K, a_kmajor))
         return launch_skinny_ragged({B, K, A, a_kmajor ? r : K, a_kmajor, n, r, K, T}, s);
     return launch_skinny_factor(B, n, K, A, a_kmajor, r, T, partial, partial ? dense_tn_plain_partial_bytes(n, r) : 0, s);
 }

@@ -1097,8 +1097,7 @@ hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, co
     hipError_t e = launch_wgrad_masked(dY, X, b, meta, d_out, d_in, gvals, Xt, dYt, d_in % 32 == 0 ? tail : nullptr, s);
     if (e != hipSuccess) return e;
     // Extents that are not whole k-steps of the tile kernels, and short products: the kernel for ragged extents
-    if (d_in % 64 != 0 || d_out % 64 != 0 ||
-        (skinny_pair_is_short(b, r, d_in) && skinny_pair_is_short(b, r, d_out) && skinny_pair_is_short(d_in, r, b) && skinny_pair_is_short(r, d_out, b))) {
+    if (d_in % 64 != 0 || d_out % 64 != 0 || skinny_pair_is_short(b, d_in, d_out, r)) {
         if ((e = launch_skinny_factors({X, d_in, L, r, true, b, r, d_in, T}, {dY, d_out, R, d_out, false, b, r, d_out, T2}, s)) != hipSuccess) return e;
         return launch_skinny_gradients({X, d_in, T2, r, true, d_in, r, b, dL}, {T, r, dY, d_out, true, r, d_out, b, dR}, s);
     }

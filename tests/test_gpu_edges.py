@@ -129,12 +129,15 @@ def test_column_masks(n, m, kind, rows, cols):
     nm.test_prune_mask_rows_then_columns(n, m, kind, rows, cols)
 
 
-# whole k-steps on the kernel for short products: one chunk in a row and as many as its rule lets in, ranks of one tile
-# and several, fewer tokens than a tile
-@pytest.mark.parametrize("b,d_out,d_in,r", [(20, 192, 128, 32), (600, 2560, 2560, 64), (2560, 1024, 2048, 96), (1024, 2048, 2112, 512),
-                                            (5000, 256, 1024, 160), (8224, 768, 512, 64), (256, 2560, 2560, 512)])
-def test_short_adapter_products(b, d_out, d_in, r):
-    assert sl.slope_spmm_fwd_plan(b, d_in, d_out, r)["xl"] == (1 if b <= 512 else 4 if d_in <= 2048 else 3)
+# whole k-steps on the kernel for short products: one chunk in a row and as many as its rules let in, on few tiles and many, ranks of
+# one tile and several, fewer tokens than a tile; a chunk and a tile more, which are the tile kernels'
+@pytest.mark.parametrize("b,d_out,d_in,r,short", [(20, 192, 128, 32, False), (600, 2560, 2560, 64, False), (600, 256, 1024, 64, True),
+                                                  (2560, 1024, 1536, 96, True), (2560, 1024, 2048, 96, False), (1024, 2048, 2112, 512, False),
+                                                  (2700, 256, 1024, 160, True), (5000, 256, 1024, 160, False), (8192, 768, 512, 64, True),
+                                                  (8224, 768, 512, 64, False), (256, 512, 512, 512, False), (1280, 512, 512, 64, True),
+                                                  (1300, 512, 576, 64, True), (256, 2560, 2560, 512, False)])
+def test_short_adapter_products(b, d_out, d_in, r, short):
+    assert (sl.slope_spmm_fwd_plan(b, d_in, d_out, r)["xl"] == 4) == short
     check_layer(b, d_out, d_in, r)
 
 
