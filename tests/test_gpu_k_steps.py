@@ -1,5 +1,8 @@
 """Contractions shorter and longer than the load rings of the tile kernels, on each of their tile shapes (needs an MI355X).
 Against fp32 products under the element bounds of tests/parity_util.py."""
+import ctypes
+import re
+
 import pytest
 import torch
 
@@ -16,39 +19,80 @@ def gauss(*shape):
     return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
 
 
-# extents whose least estimate is, for these contractions, on 64 x 64, 64 x 128, 128 x 128, 192 x 128, 256 x 128, 192 x 192 and 256 x 192
-# tiles, each ragged at both edges
-TILES = [(1000, 1016), (1010, 1928), (2000, 1928), (2290, 2552), (2040, 4088), (3000, 3064), (3000, 4000)]
+class KernelNode(ctypes.Structure):                                      # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def kernels(call):
+    """The kernels of this library that a call launches, as (name, its first numbers): the nodes of its graph."""
+    call()
+    torch.cuda.synchronize()
+    graph, count = torch.cuda.CUDAGraph(keep_graph=True), ctypes.c_size_t()
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    handle = ctypes.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
+    found = []
+    for node in nodes:
+        kind, params = ctypes.c_int(-1), KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        if kind.value != 0:                                              # hipGraphNodeTypeKernel
+            continue
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(params)) == 0
+        name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(params.func), None).decode()
+        own = re.search(r"\d+([a-z_]+_kernel)(I\w*)?", name)
+        if "_GLOBAL__N_1" in name and own:
+            found.append((own.group(1), tuple(int(x) for x in re.findall(r"Li(\d+)E", own.group(2) or "")[:2])))
+    return found
+
+
+# extents whose least estimate is, for these contractions, on this tile (rows of A x rows of B), each ragged at both edges
+TILES = [(1000, 1016, (64, 64)), (1010, 1928, (64, 128)), (2000, 1928, (128, 128)), (2290, 2552, (192, 128)), (2040, 4088, (256, 128)),
+         (3000, 3064, (192, 192)), (3000, 4000, (256, 192))]
 
 
 @pytest.mark.parametrize("ksteps", [1, 2, 3, 4, 5, 7, 8, 9])
-@pytest.mark.parametrize("n,m", TILES)
-def test_dense_product(n, m, ksteps):
+@pytest.mark.parametrize("n,m,tile", TILES)
+def test_dense_product(n, m, tile, ksteps):
     print(f"gemm n={n} m={m} k-steps={ksteps}", flush=True)
     B, A = gauss(n, 64 * ksteps), gauss(m, 64 * ksteps)
+    assert kernels(lambda: sl.slope_gemm_tn(B, A)) == [("dense_tn_kernel", tile)]
     assert_all_close(sl.slope_gemm_tn(B, A), B.float() @ A.float().t(), "C")
 
 
 @pytest.mark.parametrize("b", [5, 64, 100, 192, 250, 320, 450, 512, 577])
-@pytest.mark.parametrize("d_out,d_in", [(n - n % 8, m) for n, m in TILES])
-def test_weight_gradient(b, d_out, d_in):
+@pytest.mark.parametrize("d_out,d_in,tile", [(n - n % 8, m, tile) for n, m, tile in TILES])
+def test_weight_gradient(b, d_out, d_in, tile):
     print(f"wgrad b={b} d_out={d_out} d_in={d_in}", flush=True)
     X, dY = gauss(b, d_in), gauss(b, d_out)
     _, meta, mask = sl.slope_prune_rows(gauss(d_out, d_in), want_mask=True)
     want = (dY.float().t() @ X.float())[unpack_bits(mask)].reshape(d_out, d_in // 2)
+    tiles = -(-d_out // 64) * -(-d_in // 64)
+    few = b <= 512 if tiles <= 256 else tiles <= 512 and 64 < b <= 128  # the kernel for few tokens
+    assert kernels(lambda: sl.slope_wgrad_masked(dY, X, meta)) == [("wgrad_groups_kernel", ()) if few else ("dense_tn_kernel", tile)]
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
 
 
-# sparse products on 64 x 64, 128 x 64, 192 x 64, 128 x 128, 192 x 128, 256 x 128, 192 x 192 and 256 x 192 tiles (without an adapter or scratch for
-# slabs; the ring kernel's pairs, odd ends of them, blocks of metadata; the other kernel's quads and what is left of them)
-SPARSE = [(500, 1032), (1000, 2040), (700, 4160), (2000, 1920), (2040, 3000), (2048, 3900), (2040, 4352), (3000, 4000)]
+# sparse products without an adapter or scratch for slabs, by tile (weight rows x tokens): the ring kernel's pairs, odd ends of them, blocks of
+# metadata; the other kernel's quads and what is left of them.  (64 x 64, the generic kernel's form for whole pairs of k-steps, is
+# the 128 x 64 tile's neighbour: 21 k-steps are on that one.)
+SPARSE = [(500, 1032, (64, 64)), (1000, 2040, (128, 64)), (700, 4160, (192, 64)), (1500, 2040, (128, 96)), (1500, 3064, (192, 96)),
+          (2000, 1920, (128, 128)), (2040, 3000, (192, 128)), (2048, 3896, (256, 128)), (2040, 4352, (192, 192)), (3830, 3256, (192, 256)),
+          (3000, 4000, (256, 192))]
 
 
 @pytest.mark.parametrize("ksteps", [2, 3, 4, 5, 6, 7, 8, 9, 11, 16, 21])
-@pytest.mark.parametrize("b,d_out", SPARSE)
-def test_sparse_product(b, d_out, ksteps):
-    d_out -= d_out % 8
-    print(f"spmm b={b} d_out={d_out} k-steps={ksteps} plan={sl.slope_spmm_fwd_plan(b, 64 * ksteps, d_out)}", flush=True)
+@pytest.mark.parametrize("b,d_out,tile", SPARSE)
+def test_sparse_product(b, d_out, tile, ksteps):
+    print(f"spmm b={b} d_out={d_out} k-steps={ksteps}", flush=True)
+    plan = sl.slope_spmm_fwd_plan(b, 64 * ksteps, d_out)
+    assert plan["slabs"] == 1 and (plan["rows"], plan["tokens"]) == ((128, 64) if tile == (64, 64) and ksteps == 21 else tile)
     X, W = gauss(b, 64 * ksteps), gauss(d_out, 64 * ksteps)
     vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
     want = X.float() @ torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float().t()
@@ -64,6 +108,8 @@ def test_leftover_tiles_of_a_sparse_product(b, d_out, d_in, r):
     print(f"spmm b={b} d_out={d_out} d_in={d_in} r={r} plan={sl.slope_spmm_fwd_plan(b, d_in, d_out, r)}", flush=True)
     X, W = gauss(b, d_in), gauss(d_out, d_in)
     vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    part = ("spmm_ring_kernel", (128, 128)) if b < 5000 else ("spmm_kernel", (256, 128))
+    assert kernels(lambda: sl.slope_spmm_fwd(X, vals, meta))[-2:] == [("spmm_split_kernel", ()), part]
     kept = torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float()
     if not r:
         assert_all_close(sl.slope_spmm_fwd(X, vals, meta), X.float() @ kept.t(), "Y")
