@@ -101,7 +101,7 @@ def test_adapter_gradients_on_every_tile(b, d_out, d_in, r):
     check_layer(b, d_out, d_in, r)
 
 
-# the weight gradient in place on one or two rounds of 64 x 64 tiles, and just above: fewer slabs of 32 tokens than
+# the weight gradient without scratch on one or two rounds of 64 x 64 tiles, and just above: fewer slabs of 32 tokens than
 # groups, a slab that is not full, a row of tiles that is not full
 @pytest.mark.parametrize("b,d_out,d_in", [(1, 8, 8), (33, 72, 136), (1000, 1000, 1000), (130, 1032, 1992), (300, 1464, 1480)])
 def test_in_place_weight_gradient(b, d_out, d_in):

@@ -1,13 +1,11 @@
 """Contractions shorter and longer than the load rings of the tile kernels, on each of their tile shapes (needs an MI355X).
 Against fp32 products under the element bounds of tests/parity_util.py."""
-import ctypes
-import re
-
 import pytest
 import torch
 
 from paper_2405_16325_amd import binding as sl
 from paper_2405_16325_amd import inputs
+from tests.graph_util import kernels
 from tests.test_gpu_fullsize import assert_all_close, unpack_bits
 
 pytestmark = pytest.mark.gpu
@@ -19,37 +17,9 @@ def gauss(*shape):
     return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
 
 
-class KernelNode(ctypes.Structure):                                      # hipKernelNodeParams
-    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
-                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
-
-
-def kernels(call):
-    """The kernels of this library that a call launches, as (name, its first numbers): the nodes of its graph."""
-    call()
-    torch.cuda.synchronize()
-    graph, count = torch.cuda.CUDAGraph(keep_graph=True), ctypes.c_size_t()
-    with torch.cuda.graph(graph):
-        call()
-    with open("/proc/self/maps") as maps:
-        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
-    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
-    handle = ctypes.c_void_p(graph.raw_cuda_graph())
-    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
-    nodes = (ctypes.c_void_p * count.value)()
-    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
-    found = []
-    for node in nodes:
-        kind, params = ctypes.c_int(-1), KernelNode()
-        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
-        if kind.value != 0:                                              # hipGraphNodeTypeKernel
-            continue
-        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(params)) == 0
-        name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(params.func), None).decode()
-        own = re.search(r"\d+([a-z_]+_kernel)(I\w*)?", name)
-        if "_GLOBAL__N_1" in name and own:
-            found.append((own.group(1), tuple(int(x) for x in re.findall(r"Li(\d+)E", own.group(2) or "")[:2])))
-    return found
+def tiles(call):
+    """(name, tile) of each kernel that a call launches."""
+    return [(name, args[:2] if name != "spmm_split_kernel" else ()) for name, args in kernels(call)]
 
 
 # extents whose least estimate is, for these contractions, on this tile (rows of A x rows of B), each ragged at both edges
@@ -62,7 +32,7 @@ TILES = [(1000, 1016, (64, 64)), (1010, 1928, (64, 128)), (2000, 1928, (128, 128
 def test_dense_product(n, m, tile, ksteps):
     print(f"gemm n={n} m={m} k-steps={ksteps}", flush=True)
     B, A = gauss(n, 64 * ksteps), gauss(m, 64 * ksteps)
-    assert kernels(lambda: sl.slope_gemm_tn(B, A)) == [("dense_tn_kernel", tile)]
+    assert tiles(lambda: sl.slope_gemm_tn(B, A)) == [("dense_tn_kernel", tile)]
     assert_all_close(sl.slope_gemm_tn(B, A), B.float() @ A.float().t(), "C")
 
 
@@ -73,9 +43,9 @@ def test_weight_gradient(b, d_out, d_in, tile):
     X, dY = gauss(b, d_in), gauss(b, d_out)
     _, meta, mask = sl.slope_prune_rows(gauss(d_out, d_in), want_mask=True)
     want = (dY.float().t() @ X.float())[unpack_bits(mask)].reshape(d_out, d_in // 2)
-    tiles = -(-d_out // 64) * -(-d_in // 64)
-    few = b <= 512 if tiles <= 256 else tiles <= 512 and 64 < b <= 128  # the kernel for few tokens
-    assert kernels(lambda: sl.slope_wgrad_masked(dY, X, meta)) == [("wgrad_groups_kernel", ()) if few else ("dense_tn_kernel", tile)]
+    small = -(-d_out // 64) * -(-d_in // 64)
+    few = b <= 512 if small <= 256 else small <= 512 and 64 < b <= 128  # the kernel for few tokens
+    assert tiles(lambda: sl.slope_wgrad_masked(dY, X, meta)) == [("wgrad_groups_kernel", ()) if few else ("dense_tn_kernel", tile)]
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
 
 
@@ -109,7 +79,7 @@ def test_leftover_tiles_of_a_sparse_product(b, d_out, d_in, r):
     X, W = gauss(b, d_in), gauss(d_out, d_in)
     vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
     part = ("spmm_ring_kernel", (128, 128)) if b < 5000 else ("spmm_kernel", (256, 128))
-    assert kernels(lambda: sl.slope_spmm_fwd(X, vals, meta))[-2:] == [("spmm_split_kernel", ()), part]
+    assert tiles(lambda: sl.slope_spmm_fwd(X, vals, meta))[-2:] == [("spmm_split_kernel", ()), part]
     kept = torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float()
     if not r:
         assert_all_close(sl.slope_spmm_fwd(X, vals, meta), X.float() @ kept.t(), "Y")

@@ -156,8 +156,8 @@ def test_spmm_bwd_x(b, d_out, d_in):
     say(f"  rel_fro {err:.3e}")
 
 
-# the last three are large enough for the workspace path (256 x 256 tiles of token-contiguous
-# copies): full tiles, ragged tiles in both dimensions, a token count that is not a multiple of 64
+# the last four: tiles that are full and tiles that are ragged in both dimensions, token counts that are no multiples of 64.  (Scratch
+# changes the route on larger layers only: tests/test_gpu_wgrad_stored.py, tests/test_gpu_edges.py.)
 WGRAD_SHAPES = PRODUCT_SHAPES + [(1000, 320, 448), (200, 4096, 2048), (1000, 4160, 2112), (77, 2048, 4096)]
 
 

@@ -2,8 +2,8 @@
 the library against the CPU oracle, through the C ABI.  These shapes leave the fast kernels' quanta
 (contraction lengths that are multiples of 256 or 64, 16-byte rows) and are routed to the general
 kernels inside the same calls: the generic sparse kernel's form for ragged rows, the byte-granular form
-of the double-prune tile kernel, the in-place weight-gradient kernel, the MFMA kernel for ragged extents for
-the skinny adapter products.  Integer outputs bit for bit, products under the norm and element-wise bounds."""
+of the double-prune tile kernel, the dense tiles' packed epilogue for rows that end inside a dword of metadata, the MFMA
+kernel for ragged extents for the skinny adapter products.  Integer outputs bit for bit, products under the norm and element-wise bounds."""
 import numpy as np
 import pytest
 import torch

@@ -6,6 +6,7 @@ import torch
 
 from paper_2405_16325_amd import binding as sl
 from paper_2405_16325_amd import inputs
+from tests.graph_util import kernels
 from tests.test_gpu_fullsize import assert_all_close, unpack_bits
 
 pytestmark = pytest.mark.gpu
@@ -43,10 +44,18 @@ def test_few_tokens_on_few_tiles(b, d_out, d_in):
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta, workspace=None), want, "dW without scratch")
 
 
-# (where both are wide, dY, X, and neither is copied): the same sums in the same order from every layout
-@pytest.mark.parametrize("b,d_out,d_in", [(130, 18432, 16384), (100, 9216, 36864), (70, 36864, 9216), (200, 8192, 8192)])
-def test_copies_change_nothing(b, d_out, d_in):
+# (both copied, X, dY, and neither: which operand is wide; a few k-steps, and 17 of them with tokens left over and the tiles of a last
+# partial round cut): the same sums in the same order from every layout
+X_COPY, DY_COPY, BOTH, NONE = (0, 1), (1, 0), (0, 0), (1, 1)           # flags: X, dY as stored
+
+
+@pytest.mark.parametrize("b,d_out,d_in,stored", [(130, 18432, 16384, BOTH), (100, 36864, 9216, X_COPY), (70, 9216, 36864, DY_COPY), (200, 8192, 8192, NONE),
+                                                 (1030, 12288, 16640, BOTH), (1030, 12544, 4096, X_COPY), (1030, 4352, 9216, NONE),
+                                                 (1030, 4096, 12544, DY_COPY), (1030, 9216, 4352, X_COPY)])
+def test_copies_change_nothing(b, d_out, d_in, stored):
     X, dY, meta, _ = layer(b, d_out, d_in)
+    launched = [(name, args[2:]) for name, args in kernels(lambda: sl.slope_wgrad_masked(dY, X, meta)) if name != "tail_finish_kernel"]
+    assert launched in ([("transpose_pad_kernel", ())] * (stored != NONE) + [("dense_tn_split_kernel", stored)] * n for n in (1, 2))
     g = sl.slope_wgrad_masked(dY, X, meta)
     want = sl.slope_wgrad_masked_t(sl.slope_transpose_tokens(dY), sl.slope_transpose_tokens(X), b, meta)
     assert torch.equal(g.view(torch.int16), want.view(torch.int16))
