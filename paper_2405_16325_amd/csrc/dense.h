@@ -56,7 +56,7 @@ struct DenseLoader {
         const int l16 = lane & 15, lq = lane >> 4;
         ksteps = steps;
         lds = (uint32_t)(uintptr_t)(uint8_t __attribute__((address_space(3)))*)smem;
-        if (KM) {
+        if constexpr (KM) {
             row_bytes = (uint32_t)o.ld * 2;
             from = (uint64_t)o.p + (uint64_t)(uint32_t)k_first * ((uint64_t)row_bytes * 64);
             from = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)from) |
@@ -89,7 +89,7 @@ struct DenseLoader {
     }
     __device__ __forceinline__ void load(int ks, int i, uint8_t* smem, int stage, int wave) const {   // stage: its offset in smem
         const int dst = stage + slot(i, wave) * 1024;
-        if (KM) {
+        if constexpr (KM) {
             const uint32_t bytes = (ks < whole ? 64u : ks == whole ? (uint32_t)rest : 0u) * row_bytes;
             const uint64_t at = from + (uint64_t)(uint32_t)ks * ((uint64_t)row_bytes * 64);
             if (i == 0) dma16_bounded<0>(at, bytes, lane_off, lds + dst);
@@ -107,7 +107,7 @@ struct DenseLoader {
     __device__ __forceinline__ Stage stage(uint8_t* smem, int offset) const {
         Stage st;
         st.p = smem + offset;
-        if (KM)
+        if constexpr (KM)
 #pragma unroll
             for (int u = 0; u < UNITS; ++u) {
                 st.at[u] = lds + (uint32_t)(offset + frag_off[u]);
@@ -117,12 +117,12 @@ struct DenseLoader {
     }
     // fragment i, half h of the k-step: 16 rows x 32 k
     __device__ __forceinline__ u32x4 half(const Stage& st, int i, int h) const {
-        if (KM) {
+        if constexpr (KM) {
             typedef s16x4 __attribute__((address_space(3)))* lds_t;
             const uint32_t at = st.at[i % UNITS] + i / UNITS * 8192 + h * 4096;
             union { s16x4 q[2]; u32x4 u; } x;
-            x.q[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)at);
-            x.q[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(at + 512));
+            x.q[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(uintptr_t)at);
+            x.q[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(uintptr_t)(at + 512));
             return x.u;
         }
         return *(const u32x4*)(st.p + frag_off[h] + i * 2048);

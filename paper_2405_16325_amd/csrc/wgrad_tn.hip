@@ -27,8 +27,7 @@ namespace {
 // cols % 8 == 0, out is [cols] rows of pitch ld >= rows_pad, rows_pad % 64 == 0, ld % 8 == 0.
 // Tiles of TP_ROWS rows x 64 columns through LDS, 16-byte global accesses on both sides, non-temporal (116.9 -> 99.4 us
 // for 16384 x 9216 alone, 8 % inside a training step); consecutive workgroups go down the rows, so that every output
-// row is written front to back.  One launch takes up to three matrices one after the other (the operands of a product, and
-// the small factor that the product after it wants).
+// row is written front to back.  One launch takes one or two matrices one after the other (the operands of a product).
 constexpr int TP_ROWS = 64;                                   // 128 and 256 measured the same
 struct TransposeJob {
     const bf16_t* in;
@@ -39,12 +38,12 @@ inline TransposeJob transpose_job(const bf16_t* in, int64_t rows, int64_t cols, 
     return {in, out, (int)cols, (int)rows, (int)rows_pad, (int)ld, (int)(((rows_pad + TP_ROWS - 1) / TP_ROWS) * ((cols + 63) / 64))};
 }
 
-__global__ void __launch_bounds__(256) transpose_pad_kernel(TransposeJob j0, TransposeJob j1, TransposeJob j2) {
+__global__ void __launch_bounds__(256) transpose_pad_kernel(TransposeJob j0, TransposeJob j1) {
     __shared__ bf16_t tile[64][TP_ROWS + 2];
     int64_t w = flat_block();
-    const bool first = w < j0.tiles, second = w < (int64_t)j0.tiles + j1.tiles;
-    const TransposeJob j = first ? j0 : second ? j1 : j2;
-    w -= first ? 0 : second ? j0.tiles : (int64_t)j0.tiles + j1.tiles;
+    const bool first = w < j0.tiles;
+    const TransposeJob j = first ? j0 : j1;
+    w -= first ? 0 : j0.tiles;
     if (w >= j.tiles) return;
     const bf16_t* __restrict__ in = j.in;
     bf16_t* __restrict__ out = j.out;
@@ -69,9 +68,9 @@ __global__ void __launch_bounds__(256) transpose_pad_kernel(TransposeJob j0, Tra
     }
 }
 
-inline hipError_t launch_transposes(const TransposeJob& j0, const TransposeJob& j1, const TransposeJob& j2, hipStream_t s) {
-    const int64_t tiles = (int64_t)j0.tiles + j1.tiles + j2.tiles;
-    transpose_pad_kernel<<<grid_of(tiles), dim3(256), 0, s>>>(j0, j1, j2);
+inline hipError_t launch_transposes(const TransposeJob& j0, const TransposeJob& j1, hipStream_t s) {
+    const int64_t tiles = (int64_t)j0.tiles + j1.tiles;
+    transpose_pad_kernel<<<grid_of(tiles), dim3(256), 0, s>>>(j0, j1);
     return hipGetLastError();
 }
 
@@ -794,7 +793,7 @@ size_t token_copy_bytes(int64_t b, int64_t d) { return (size_t)d * (size_t)token
 hipError_t launch_token_copies(const bf16_t* in0, int64_t cols0, bf16_t* out0, const bf16_t* in1, int64_t cols1,
                                bf16_t* out1, int64_t b, hipStream_t s) {
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
-    return launch_transposes(transpose_job(in0, b, cols0, bp, ld, out0), in1 ? transpose_job(in1, b, cols1, bp, ld, out1) : TransposeJob{}, {}, s);
+    return launch_transposes(transpose_job(in0, b, cols0, bp, ld, out0), in1 ? transpose_job(in1, b, cols1, bp, ld, out1) : TransposeJob{}, s);
 }
 
 // Layers that the forms with token-contiguous copies in their interface take.
@@ -904,7 +903,7 @@ hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, con
     const DenseOperand dy = copies & COPY_DY ? DenseOperand{dYt, (int)d_out, (int)ld, (int)bp} : DenseOperand{dY, (int)d_out, (int)d_out, (int)b};
     if (copies) {
         const hipError_t e = launch_transposes(copies & COPY_X ? transpose_job(X, b, d_in, bp, ld, Xt) : TransposeJob{},
-                                               copies & COPY_DY ? transpose_job(dY, b, d_out, bp, ld, dYt) : TransposeJob{}, {}, s);
+                                               copies & COPY_DY ? transpose_job(dY, b, d_out, bp, ld, dYt) : TransposeJob{}, s);
         if (e != hipSuccess) return e;
     }
     constexpr int EPI = EPI_MASKED_PACKED;
