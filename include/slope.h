@@ -86,8 +86,8 @@ typedef enum {
 /* Bytes of scratch memory a call wants for b tokens, a d_out x d_in layer and adapter rank r (0: none);
  * 0 for the calls that take no workspace, for unknown ids and for invalid extents.  The per-call
  * queries below return the same numbers.
- *   slope_spmm_fwd: required when adapters are active (T = X L as bf16[b, r], a K-contiguous copy of L
- *   for many tokens, partial sums); optional otherwise: for a few dozen to some thousand tokens, where
+ *   slope_spmm_fwd: required when adapters are active (T = X L as bf16[b, r], partial sums, and as many
+ *   bytes as L, which a few tokens use for more of these); optional otherwise: for a few dozen to some thousand tokens, where
  *   tiles alone would leave much of the chip idle, the call, given this many bytes, also splits the
  *   contraction over d_in and keeps fp32 partial sums there, which is much faster at those sizes. */
 size_t slope_workspace_bytes(int call_id, int64_t b, int64_t d_in, int64_t d_out, int64_t r);
@@ -153,7 +153,7 @@ slope_status slope_spmm_fwd_ws(const void* X, int64_t b, const void* Wr_vals, co
  *   - A shape whose slope_spmm_fwd_workspace_bytes(b, d_in, d_out, r) exceeds SLOPE_STATIC_SCRATCH_BYTES
  *     is rejected with SLOPE_ERR_WORKSPACE before anything is launched; that query is the test.  (Every
  *     token count up to 128 fits for the OPT-66B layers with rank-128 adapters, and so does every
- *     training-size batch of them, whose need is T = X L plus a copy of L, about 10-18 MiB.)
+ *     training-size batch of them, whose need is T = X L and as many bytes as L, about 10-18 MiB.)
  *   - The buffer is found once per device, on the first call made while that device is current
  *     (make that call outside stream capture); the stream must belong to the current device.
  *   - All calls on one GPU share the buffer: calls that overlap in time on one GPU (different
@@ -238,7 +238,8 @@ slope_status slope_spmm_bwd_x_adapter(const void* dY, int64_t b, const void* Wrc
  * masked dW of slope_wgrad_masked (Eq. 5, Algorithm 1 lines 12-13) and the gradients of the
  * low-rank term of Eq. 11 by the chain rule,
  *     dL = X^T (dY R^T)   bf16[d_in, r]          dR = (X L)^T dY   bf16[r, d_out].
- * The three contractions over the tokens share one pair of token-contiguous copies of X and dY.
+ * X and dY are read as stored by all three contractions over the tokens, but for the copies that
+ * slope_wgrad_masked_ws makes of operands of wide layers for dW.
  * X L and dY R^T are rounded to bf16 before the second product.
  *   dY, X, Wr_meta, dW_vals   as for slope_wgrad_masked
  *   L, R, r                    as for slope_spmm_fwd (r % 32 == 0, 32 <= r <= 512)
@@ -318,7 +319,8 @@ slope_status slope_update_sparse(const void* Wnew_vals, const void* Wr_meta, int
  *       (d_in a multiple of 1024 and enough weight rows, or the
  *       workspace to cut the contraction into slices), 5 tile kernel for the tokens of whole tiles and
  *       a small-batch kernel for the last few
- *   [1], [2] weight rows and tokens per workgroup (of the tile kernel)
+ *   [1], [2] weight rows and tokens per workgroup (of the tile kernel; 256 x 256 on a long contraction: of its
+ *       whole rounds, the tiles left over after them may run as smaller ones in a second launch)
  *   [3] slabs or slices (1 = no split); for [0] == 5 the tokens of the small-batch kernel
  *   [4] T = X L: 0 no adapter, 1 split over d_in from L as stored (few tokens; before the product, beside it or in it),
  *       2 dense tile kernel, 3 dense tile kernel split over d_in, 4 MFMA kernel for ragged extents (d_in % 64 != 0)

@@ -364,7 +364,7 @@ def slope_wgrad_adapter_workspace_bytes(b: int, d_in: int, d_out: int, r: int) -
 
 
 def slope_wgrad_adapter(dY, X, meta, L, R, out=None, workspace=None):
-    """(dW packed, dL, dR) of a layer with adapters; one call, shared token-contiguous copies."""
+    """(dW packed, dL, dR) of a layer with adapters in one call."""
     b, d_in, d_out, _ = _wgrad_args(dY, X, meta, None if out is None else out[0])
     if L is None or L.dim() != 2:
         raise ValueError("L must be a matrix")

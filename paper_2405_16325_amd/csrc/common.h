@@ -127,14 +127,14 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s);
 
 size_t dense_tn_plain_partial_bytes(int64_t n, int64_t m);
-int dense_tn_plain_slabs(int64_t n, int64_t m, int64_t K, size_t partial_bytes);   // of the call above
+int dense_tn_plain_slabs(int64_t n, int64_t m, int64_t K, size_t partial_bytes);   // of launch_skinny_factor
 // C[n, m] = B[n, K] * A[m, K]^T (dense bf16, fp32 accumulation), K % 64 == 0
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s);
 // general N:M magnitude mask (M in {2, 4, 8}); axis 0: groups inside a row, axis 1: inside a column
 hipError_t launch_nm_mask(const bf16_t* W, int64_t rows, int64_t cols, int n, int m, int axis, const uint8_t* cand,
                           uint8_t* mask, bf16_t* masked, bf16_t* masked_t, hipStream_t s);
-// dW (packed) + dL + dR of a layer with adapters, sharing the token-contiguous copies
+// dW (packed) + dL + dR of a layer with adapters
 size_t wgrad_adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r);
 hipError_t launch_wgrad_adapter(const bf16_t* dY, const bf16_t* X, int64_t b, const uint8_t* meta, int64_t d_out,
                                 int64_t d_in, const bf16_t* L, const bf16_t* R, int64_t r, bf16_t* gvals, bf16_t* dL,

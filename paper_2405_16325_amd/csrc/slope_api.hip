@@ -30,7 +30,8 @@ inline bool bad_rank(int64_t r) { return r % 32 != 0 || r > 512; }
 
 inline size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// [ T | as many bytes as L | partial sums of X L ] when adapters are active, then the slab buffer of the split over K
+// [ T | as many bytes as L | partial sums of X L ] when adapters are active, then the slab buffer of the split over K.  (Sizes of
+// scratch are part of the interface.  The second part, once a copy of L, is room for sums of a few tokens together with the first.)
 size_t adapter_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     (void)d_out;
     if (r <= 0) return 0;
@@ -132,6 +133,7 @@ size_t slope_wgrad_t_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     return wgrad_tail_bytes(b, d_in, d_out);
 }
 
+// Room for both copies whether the call makes them or not: sizes of scratch are part of the interface.
 size_t slope_wgrad_workspace_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     if (b <= 0 || d_in <= 0 || d_out <= 0) return 0;
     return slope_token_copy_bytes(b, d_in) + slope_token_copy_bytes(b, d_out) + slope_wgrad_t_workspace_bytes(b, d_in, d_out);

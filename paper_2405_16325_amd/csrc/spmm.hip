@@ -1359,11 +1359,13 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // operand feed of a compute unit, 53 bytes per ns (a little more on the smaller tiles of the ring kernel; up to a fifth more
 // with few compute units at work), and takes longer for weight bytes that come from HBM: those that few token tiles share.
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
-// The constants were fitted on weights from HBM; over 110 shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128
-// to 20000), each on the five tiles and four splits of least estimate, the form chosen takes 0.8 % longer than the best one in
-// the mean, more than 10 % in two.  (192 x 96 has no gain from its small tile: 77 shapes at 1.10 of the estimate, 128 x 96 at 1.09.)
-// Few tokens on many rows are no exception (us, from HBM: 64 tokens, 20480 x 1024 10.4 on 128 x 64, 13.3 on 64 x 64 tiles, several
-// to a compute unit; 36864 x 1024 13.6 on 192 x 64, 18.5 and 19.3).
+// The constants were fitted on weights from HBM and on tiles that read a k-step before they multiplied it.  Against them the kernels
+// now take 1.02 (128 x 128) to 1.18 (256 x 192) of the estimate on such weights, 0.91 to 1.12 on those from the cache: over 110
+// shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128 to 20000), each on five whole tiles and four splits of low
+// estimate, the form chosen takes 1.2 % longer than the best one in the mean, more than 10 % in one (65 tokens, 21888 x 7232),
+// 1.5 % on weights from the cache.
+// Few tokens on many rows are no exception (us, from HBM: 64 tokens, 20480 x 1024 11.2 on 128 x 64, 15.8 on 64 x 64 tiles, several
+// to a compute unit; 36864 x 1024 14.6 on 192 x 64, 18.3 and 23.6).
 struct TileCost { int64_t tiles; double start, step, less, stream; };   // what does not depend on the slabs
 static TileCost tile_cost(int64_t n, int64_t m, int64_t K, int bm, int bn) {
     const int64_t tiles_n = (n + bn - 1) / bn, tiles = ((m + bm - 1) / bm) * tiles_n;
@@ -1429,16 +1431,17 @@ bool slab_xl_split(int64_t n, int64_t m, int64_t K, int64_t r, const SpmmSplit& 
 }
 
 // Without T's launches to save, a product that one launch is estimated to take less than this for is left whole: a call of
-// two launches takes the host 13.4 to 13.8 us whatever the card does in them, one of one launch 8.5 (us a call, whole and
-// split: estimate 14.0, 358 tokens, 256 x 3328 14.6, 13.6; 14.3, 767, 896 x 3008 16.0, 14.7; 15.7, 399, 256 x 3840 16.5, 13.5; but
-// 10.7, 742, 512 x 2112 12.2, 13.8; 11.0, 487, 1216 x 2176 12.3, 13.5; 12.1, 239, 5760 x 2048 13.1, 18.1).
+// two launches takes the host 12.2 us and more whatever the card does in them, one of one launch 8.5 (us a call, whole and
+// split: estimate 14.0, 358 tokens, 256 x 3328 14.0, 12.2; 14.3, 767, 896 x 3008 15.8, 14.4; 15.7, 399, 256 x 3840 15.7, 12.9; but
+// 10.7, 742, 512 x 2112 12.0, 13.0; 11.0, 487, 1216 x 2176 12.1, 12.9; 12.1, 239, 5760 x 2048 12.8, 17.9).
 constexpr double SPLIT_MIN_US = 13.5;
 // Split of the product over k within that room, {0, 0, 0}: none.  With an adapter and up to XL_SMALL_MAX_TOKENS tokens a split
 // whose launch has room for X L beside its tiles saves the launches of X L: about 8 us and their operands at 4.4 TB/s,
 // against 3 for the larger second kernel, or the time of X L, 0.8 us per chunk of 32 rows of L and wavefront, where that is the
-// longer.  (70 shapes of 33 to 512 tokens with adapters on up to 12 forms: the one chosen takes 1.0 % longer than the best from HBM;
-// priced at 8 and 3 alone 7.0 %.  us: 166 tokens, 1280 x 27008, rank 32 58 in 8 slabs of 128 x 64, X L 53 chunks; 35 in 9 of 192 x
-// 64; 264 tokens, 2048 x 14272, rank 64 61 and 39; 330 tokens, 3328 x 13568, rank 64 67 and 51.)
+// longer.  (70 shapes of 33 to 512 tokens with adapters on up to 14 forms: the one chosen takes 2.2 % longer than the best from HBM,
+// 18 % at most.  us: 166 tokens, 1280 x 27008, rank 32 52 in 8 slabs of 128 x 64, X L 53 chunks; 34 in 9 of 192 x 64, 37 in the 11
+// that are taken; 264 tokens, 2048 x 14272, rank 64 53 in three of 128 x 64 and 38; 330 tokens, 3328 x 13568, rank 64 64 in three of
+// 256 x 128 and 49.)
 SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom& room) {
     SpmmSplit best = {0, 0, 0};
     if (room.slabs < 2) return best;
@@ -1447,10 +1450,10 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
     double least = best_tile_us(n, m, K, bm, bn);
     if (!xl && least < SPLIT_MIN_US) return best;
     // Whole products of 64 k-steps and more take an eighth longer than estimated beside split ones, on weights from HBM: over 44
-    // shapes of 129 to 1024 tokens, k of 4096 to 10000, the form chosen takes 0.2 % longer than the best measured one in the
-    // mean, 6 % at most, on weights from the last-level cache 2.4 % and 11 %.  us, whole / two or three slabs from
-    // HBM and from the cache: 512 tokens, 4096 x 4096 23.0 / 25.8 and 20.0 / 24.5; 700, 2112 x 4160 27.6 / 27.7 and 22.5 / 23.8;
-    // 518, 2240 x 4928 30.8 / 27.8 and 24.7 / 24.1; 530, 1792 x 4864 26.9 / 20.4 and 22.3 / 18.4.
+    // shapes of 129 to 1024 tokens, k of 4096 to 10000, the form chosen takes 0.4 % longer than the best measured one in the
+    // mean, 8.5 % at most, on weights from the last-level cache 2.4 % and 13 %.  us, whole / two or three slabs from
+    // HBM and from the cache: 512 tokens, 4096 x 4096 22.3 / 25.0 and 19.5 / 24.0; 700, 2112 x 4160 25.4 / 27.2 and 22.0 / 24.5;
+    // 518, 2240 x 4928 29.2 / 27.2 and 24.5 / 23.9; 530, 1792 x 4864 25.2 / 19.7 and 20.5 / 17.9.
     const double xl_first = xl ? 8.0 + 2.0 * (double)(n + r) * (double)K / 4.4e6 : 0.0;
     least = (K >= 4096 ? 1.125 : 1.0) * least + xl_first;
     // On tiles of bm rows, into all numbers of slabs that leave none empty.  (X L is looked at only where it decides.)
@@ -1472,9 +1475,10 @@ SpmmSplit spmm_split(int64_t n, int64_t m, int64_t K, int64_t r, const SlabRoom&
     const SpmmTile tall = {256, n <= 64 ? 64 : 128};
     // A long weight on enough rows: tiles of 256, which ask least often for the tokens, in any number of rounds.  Where all the
     // slabs there is room for fill less than 13/16 of a round of them, the smaller tiles fill it up (us from HBM, 256 x 128 /
-    // the smaller tile, workgroups of the former: 134 tokens, 8064 x 7808 47.2 / 38.6, 192; 482, 4096 x 8192 46.4 / 39.7, 192;
-    // 327, 3328 x 8960 35.4 / 33.4, 195; 217, 512 x 19456 30.9 / 19.4, 32; from there on the two are within 3 %: 128, 9216 x 9216
-    // 41.5 / 40.4, 216; 100, 5632 x 13056 38.1 / 37.1, 220; 256, 9216 x 9216 the same form).
+    // the smaller tile, workgroups of the former: 134 tokens, 8064 x 7808 48.5 / 38.4, 192; 482, 4096 x 8192 47.0 / 40.2, 192;
+    // 327, 3328 x 8960 36.0 / 33.4, 195; 217, 512 x 19456 30.2 / 18.0, 32; from there on the former are as fast on the widest, 256,
+    // 9216 x 9216 56.9 / 68, and behind by less: 128, 9216 x 9216 41.6 / 39.9, 216; 100, 5632 x 13056 37.8 / 34.9, 220; 114, 5376 x 16384
+    // 46.0 / 40.5, 210).
     if (room.long_weight && K >= 7168 && 16 * ((m + 255) / 256) * ((n + 127) / 128) * room.slabs >= 13 * RESIDENT) {
         least = 1e300;
         consider(tall, false);

@@ -10,8 +10,8 @@
 //     far apart crowd the same L2 channels: the padded pitch is 2-3 % faster at b = 16384)
 // The product
 //     D[i, j] = sum_t X[t, i] * dY[t, j]
-// runs with the same machinery as the sparse kernels: 8 wavefronts in two groups half a k-step apart, global -> LDS loads of
-// full 128-byte lines, conflict-free LDS reads in MFMA order, v_mfma_f32_16x16x32_bf16.
+// runs with the same machinery as the sparse kernels: 8 wavefronts, with one barrier per k-step or in two groups half a k-step
+// apart (dense_tn_sums), global -> LDS loads of full 128-byte lines, conflict-free LDS reads in MFMA order, v_mfma_f32_16x16x32_bf16.
 // D rows are d_in and D columns d_out, so a lane's four accumulators (column l%16, rows
 // 4*(l/16) .. +3) are exactly one group of four of W^R's row: the epilogue picks two of them with
 // the group's metadata nibble and stores one 4-byte pair of the packed gradient.
@@ -182,8 +182,8 @@ __device__ __forceinline__ void store_sums(const f32x4 (&acc)[MF][NF], int m, in
     }
 }
 
-// acc = the tile at (m0, n0) of D[i, j] = sum_k At[i, k] * Bt[j, k] over the k-steps [k_begin, k_end): At m rows of pitch lda,
-// Bt n rows of pitch ldb elements, ksteps k-steps of 64 in all (the look-ahead past a slab's end reads real, unused data).
+// acc = the tile at (m0, n0) of D[i, j] = sum_k At[i, k] * Bt[j, k] over the k-steps [k_begin, k_end), of ksteps k-steps of 64 in
+// all (the look-ahead past a slab's end reads real, unused data).  AKM, BKM: the operand is k-major.
 // NS = ring depth: loads run NS - 1 k-steps ahead.  Two stages are all that fits beside a 256 x 256
 // tile; small tiles (memory-bound skinny products) take a deeper ring to cover the HBM latency.
 // Every thread of the workgroup must make the call; wavefront w holds the fragments at rows w % 2 * BM / 2, columns w / 2 * BN / 4.
@@ -227,6 +227,9 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
     // / 42.7; 256 x 128, 4096 x 4096 over 4096 tokens 129 / 120.)  Else two phases, as in the 256 x 256 kernel: where the ring has
     // two stages, so that loads are queued later (256 x 192, 5120 x 6464 over 752 tokens: 62.7 against 65.3), and on k-contiguous
     // operands with 8 or 12 products per half (128 x 128, 1920 x 1973 over 3840: 31.4 against 33.2; 192 x 128 34.8 / 35.7).
+    // (Each tile both ways on seven shapes per layout, contractions of 192 to 12000, from HBM and from the cache; one barrier against two
+    // phases in the mean: k-major 256 x 192 4 % slower, the others 0 to 8 % faster; k-contiguous 256 x 128, 192 x 192, 64 x 128 and
+    // 64 x 64 1 to 11 % faster, 256 x 192, 192 x 128 and 128 x 128 1 to 3 % slower.)
     if constexpr (NS == 2 || (!AKM && !BKM && MF * NF >= 8 && MF * NF <= 12)) {
         const int group = wave >> 2;
         // One k-step.  Loads of step s + NS - 1 are queued in the even phase in which their stage, last
@@ -338,7 +341,7 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
     WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
 }
 
-// D[i, j] = sum_k At[i, k] * Bt[j, k];  At: m rows, Bt: n rows, both of pitch ld elements; kp % 64 == 0.
+// D[i, j] = sum_k At[i, k] * Bt[j, k] over ksteps k-steps of 64;  At: m rows, Bt: n rows.
 //   EPI_MASKED_PACKED: out = packed gradient [n][m/2] selected by meta (u8[n][m/8])
 //   EPI_PLAIN        : out = bf16 [n][m]  (row j, four consecutive i per lane)
 template <int BM, int BN, int EPI, int NS, bool AKM, bool BKM>
@@ -366,7 +369,7 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(DenseOperand At, D
 
 // The skinny products of the adapters, one or two in a launch (no workgroups: none): D as above, bf16 [n][m], or fp32 sums of
 // slabs of the contraction for skinny_sum_kernel.  One of the sides is the rank, in tiles of RANK rows, the other in tiles of
-// LONG; FLIP: the rank is the side m.  grid: workgroups per slab, a multiple of 8.  Operands are read as they are stored:
+// LONG.  grid: workgroups per slab, a multiple of 8.  Operands are read as they are stored:
 //   the factors   (GRADIENTS false): T = X L with L k-major, T2 = dY R^T, both operands k-contiguous; the rank is m in both;
 //   the gradients (GRADIENTS true):  dL = X^T T2 (rank m) and dR = T^T dY (rank n), contractions over the tokens, all k-major.
 struct SkinnyJob {
@@ -808,10 +811,11 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 // The kernels run at the rate their compute units pull operands from L2, 53 bytes per ns (up to a fifth more with few of them
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
 // of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  Take the shape with the least
-// estimate: over 80 shapes (400 to 16000 rows on one side, 256 to 9000 on the other, contractions of 256 to 12000), each on all
-// eight tiles, it takes 0.5 % longer than the best one in the mean, 14 % at most; a rule of fewest rounds x rows among 256 x 256,
-// 256 x 128, 128 x 128 and 128 x 64 took 5.8 to 7.7 % (gradients, us: 700 tokens, 4160 x 2112 20.4 -> 16.6 on 192 x 192; 752
-// tokens, 5120 x 6464 66.5 -> 63.9 on 256 x 192; 4096 tokens, 1024 x 1024 25 -> 20 on 64 x 64).
+// estimate, whatever the operands' layout: over 80 shapes (400 to 16000 rows on one side, 256 to 9000 on the other, contractions of
+// 256 to 12000), each on all eight tiles, it takes 0.6 % longer than the best one in the mean and 14 % at most from k-contiguous
+// operands, 0.7 % and 20 % (2816 tokens, 3520 x 2664, where 256 x 192 would be better) from operands as stored (gradients as
+// stored, us: 700 tokens, 4160 x 2112 18.5 on 192 x 192, 256 x 128 27.5; 752 tokens, 5120 x 6464 63.2 on 256 x 192, 256 x 256
+// 73.1; 4096 tokens, 1024 x 1024 21.2 on 64 x 64, 128 x 128 32.8).
 static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tail) {
     int best = 0;
     double least = 1e300;
@@ -870,12 +874,13 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
 }
 
 // The same product from the operands as stored, token after token.  The tiles that pull their operands from L2 as fast as they can
-// lose nothing by it, and the copies are saved (us, copies and product before: 2048 tokens, 3072 x 768 33.3 -> 22.4; 700, 4160 x
-// 2112 25.7 -> 18.1; 4096, 4096 x 4096 122.7 -> 99.8; 16384, 2560 x 10240 752 -> 633).  The 256 x 256 kernel on many rounds
+// lose nothing by it, and the copies are saved (us, copies and product / as stored: 2048 tokens, 3072 x 768 33.0 / 20.2; 700, 4160 x
+// 2112 26.6 / 18.7; 4096, 4096 x 4096 134 / 117; 16384, 2560 x 10240 793 / 682).  The 256 x 256 kernel on many rounds
 // keeps its matrix pipes busy, and there the transposing LDS reads, half as many bytes per cycle as plain ones, make it 4 % slower
-// with X as stored, 3 % with dY, 9 % with both (16384 tokens, 8192 x 8192: 1400 us from copies, 1459, 1441, 1520), while a
-// copy is a stream of its operand at 5.9 TB/s.  So an operand is copied, where there is room, when the other one is wide: X from
-// about 9000 rows, dY from about 11000 columns on (16384 tokens, 36864 x 9216: both copied 7462, X 7389, none 7649).
+// with X as stored, 3 % with dY, 9 % with both, while a copy is a stream of its operand at 5.9 TB/s.  So an operand is copied, where
+// there is room, when the other one is wide: X from about 9000 rows, dY from about 11000 columns on (16384 tokens, us, the call with
+// neither copied, X, dY, both: 8192 x 8192 1486, 1513, 1537, 1605; 36864 x 9216 7700, 7287, 7691, 7522; 9216 x 36864 7802, 7713, 7539,
+// 7610; 16384 x 16384 6022, 5926, 6014, 6057: the rule loses 2 % there, elsewhere nothing).
 enum { COPY_X = 1, COPY_DY = 2 };
 static int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
     if (d_in % 32 != 0 || dense_tile_choice(d_in, d_out, (b + 63) / 64, with_tail) != 0) return 0;
@@ -1056,7 +1061,7 @@ hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int6
 // Weight gradient of a layer with adapters: the packed dW as above plus the adapter gradients
 // (chain rule of Eq. 11)   dL = X^T (dY R^T)  [d_in, r],   dR = (X L)^T dY  [r, d_out],
 // all three contractions over the tokens.
-// Workspace: Xt | dYt | room of r x d_in values | T = X L [b][r] | T2 = dY R^T [b][r] (r rows of a token-contiguous copy's pitch
+// Workspace: Xt | dYt | r x d_in values (a size that is part of the interface, not used) | T = X L [b][r] | T2 = dY R^T [b][r] (r rows of a token-contiguous copy's pitch
 // each) | scratch that launch_wgrad_masked and the skinny products use one after the other, for these with room for T and T2 once more.
 // Xt and dYt are written where launch_wgrad_masked wants copies.
 static size_t wgrad_adapter_shared_bytes(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {

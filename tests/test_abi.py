@@ -73,7 +73,7 @@ def test_argument_errors_are_reported_before_launch():
     assert lib.slope_spmm_fwd(p, 8, p, p, 64, 1 << 31, None, None, 0, p, None, None) == E.SLOPE_ERR_SHAPE
     assert lib.slope_spmm_fwd(p, 8, p, p, 64, 68, None, None, 0, p, None, None) == E.SLOPE_ERR_SHAPE
     assert lib.slope_spmm_fwd(p, 8, p, p, 64, 64, None, None, 0, p, odd, None) == E.SLOPE_ERR_ALIGN
-    # the sized form refuses a workspace that is too small (here: adapters need T, a copy of L, partial sums)
+    # the sized form refuses a workspace that is too small (here: adapters need T, partial sums)
     need = lib.slope_workspace_bytes(E.SLOPE_CALL_SPMM_FWD, 8, 64, 64, 32)
     assert need > 0 and need == lib.slope_spmm_fwd_workspace_bytes(8, 64, 64, 32)
     assert lib.slope_spmm_fwd_ws(p, 8, p, p, 64, 64, p, p, 32, p, p, need - 1, None) == E.SLOPE_ERR_WORKSPACE

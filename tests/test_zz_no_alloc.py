@@ -16,7 +16,7 @@ from tests.parity_util import check_product
 pytestmark = pytest.mark.gpu
 
 # (b, d_out, d_in, r) in call order: split over K with partial sums + adapters; the same layer with fewer
-# tokens (small-batch kernel, T = X L from partial sums); many tokens (copy of L in the buffer); a smaller
+# tokens (small-batch kernel, T = X L from partial sums); many tokens (T in the buffer); a smaller
 # layer without adapters that still takes the split over K; few tokens on a short matrix with a long contraction
 # (row-split small-batch kernel, slices' partial sums in the buffer); a single token
 SEQUENCE = [(100, 768, 4096, 128), (16, 768, 4096, 128), (700, 512, 768, 64), (48, 512, 8192, 0),
