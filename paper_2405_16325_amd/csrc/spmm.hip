@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     constexpr int A_LD = BM / 64, B_LD = BN / 64;            // 1 KiB loads per wavefront: per pair, per step
     constexpr int M_WAVES = BM / 32;                         // wavefronts that load metadata (32 rows each)
     extern __shared__ __align__(16) uint8_t smem[];
-    fetch_arguments(B, n, Av, Am, m, K, B2, A2, K2, C, tiles_m, tiles_n);
+    fetch_arguments(B, n, Av, Am, m, K, tiles_m, tiles_n);
 
     int tm, tn, slab = 0, extension_slab = 0;
     if constexpr (is_split<Job>) {
@@ -769,7 +769,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
     constexpr int M_LOADS = S::M_BLOCK / 1024, M_LD = (M_LOADS + 7) / 8;   // per block; some twice where 8 does not divide them
     static_assert(BM % 64 == 0 && BN % 32 == 0 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "whole loads and fragments");
     extern __shared__ __align__(16) uint8_t smem[];
-    fetch_arguments(B, n, Av, Am, m, K, B2, A2, K2, C, tiles_m, tiles_n);
+    fetch_arguments(B, n, Av, Am, m, K, tiles_m, tiles_n);
 
     int tm, tn, slab = 0, extension_slab = 0;
     if constexpr (is_split<Job>) {
