@@ -50,24 +50,27 @@ hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, hi
 // sums over slabs; this one is one launch always, at about 1.3 us per chunk of 32 k that a wavefront walks and round of
 // workgroups.
 // A product by itself, on at most one round of workgroups.  us, the call, tile kernel / here:
-//   X L, up to four chunks, up to six with 64 tiles and more: 1024 x 512, rank 64 11.35 / 10.8; 2048 x 1024, rank 128 16.1 / 16.0;
-//     1024 x 1536, rank 64 (32 tiles) 17.3 / 18.3, rank 160 (96) 19.7 / 19.4; 4096 x 1536, rank 64 (128) 20.1 / 19.0; 1024 x 2048, rank 64
+//   X L, up to five chunks, six on 64 tiles and more: 1024 x 512, rank 64 11.35 / 10.8; 600 x 1088, rank 64 18.4 / 17.9; 4096 x 1280,
+//     rank 64 (128 tiles) 19.6 / 17.6; 1024 x 1536, rank 64 (32 tiles) 17.3 / 18.3, rank 160 (96) 19.7 / 19.4; 1024 x 2048, rank 64
 //     19.4 / 21.5; two rounds, 16384 x 512, rank 64 14.9 / 16.0;
-//   dY R^T, one chunk, four of rank 32, whose A is half a tile: 1024 x 256, rank 64 9.1 / 8.9; 1024 x 512, rank 64 11.15 / 11.5; 520 x 1024,
-//     rank 32 14.4 / 13.9; 520 x 1536, rank 32 16.1 / 17.6.
+//   dY R^T, one chunk, four of rank 32, whose A is half a tile: 1024 x 256, rank 64 9.1 / 8.9; 1024 x 512, rank 64 11.15 / 11.5; 1 x 768,
+//     rank 32 10.5 / 9.6, 64 tokens 10.6 / 11.2, 520 12.6 / 12.4; 520 x 1536, rank 32 16.1 / 17.6.
 bool skinny_is_short(int64_t n, int64_t m, int64_t K, bool a_kmajor) {
     const int64_t tiles = skinny_tiles(n, m);
-    const int64_t most = a_kmajor ? (tiles < 64 ? 4 : 6) : (m <= 32 ? 4 : 1);
+    const int64_t most = a_kmajor ? (tiles < 64 ? 5 : 6) : (m <= 32 ? 4 : 1);
     return tiles <= RESIDENT && skinny_chunks(K) <= most;
 }
 
-// One of the four products of the gradient call, in pairs, which the tile kernels take in two launches or up to four: up to two
-// chunks x rounds of two workgroups per compute unit for the factors T and T2, five for the gradients (us, the call, tile kernels
-// / here: 256 x 256, rank 32, 512 tokens 16.1 / 14.2, 1536 21.8 / 21.7, 2048 24.2 / 25.4; 512 x 512, rank 64, 1024 tokens 21.8 / 21.0,
-// 1536 24.3 / 24.8; 1024 x 1024, rank 64, 64 tokens 14.6 / 15.4; 2048 x 2048, rank 64, 1024 tokens 30.9 / 35.2).
+// One of the four products of the gradient call, in pairs, which the tile kernels take in two launches or up to four.  In chunks x
+// rounds of two workgroups per compute unit: up to five for the gradients dL and dR; for the factors T and T2 five of rank 32,
+// four of up to 16 tokens, else two.  us, the call, tile kernels / here: 256 x 256, rank 32, 512 tokens 16.1 / 14.2, 1536 21.8 / 21.7,
+// 2048 24.2 / 25.4; 1280 x 1280, rank 32, 200 tokens 19.0 / 17.7; 1536 x 512, rank 32, 64 tokens 14.8 / 15.2; 1024 x 1024, rank 128, 4
+// tokens 14.6 / 13.4, 16 14.7 / 14.2, 32 14.8 / 15.3; 1280 x 1280, rank 64, 4 tokens 15.7 / 15.8; 512 x 512, rank 64, 1024 tokens 21.8 /
+// 21.0; 2048 x 2048, rank 64, 1024 tokens 30.9 / 35.2.
 bool skinny_pair_is_short(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     auto cost = [](int64_t n, int64_t m, int64_t K) { return skinny_chunks(K) * ((skinny_tiles(n, m) + 2 * RESIDENT - 1) / (2 * RESIDENT)); };
-    return cost(b, r, d_in) <= 2 && cost(b, r, d_out) <= 2 && cost(d_in, r, b) <= 5 && cost(r, d_out, b) <= 5;
+    const int64_t most = r <= 32 ? 5 : b <= 16 ? 4 : 2;
+    return cost(b, r, d_in) <= most && cost(b, r, d_out) <= most && cost(d_in, r, b) <= 5 && cost(r, d_out, b) <= 5;
 }
 
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s) {

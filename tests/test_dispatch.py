@@ -123,7 +123,7 @@ def test_a_few_tokens_beyond_whole_tiles_take_the_small_batch_kernel():
 
 def test_short_adapter_products_of_many_tokens():
     xl = lambda b, d_in, r: sl.slope_spmm_fwd_plan(b, d_in, 2048, r)["xl"]
-    assert xl(1024, 1024, 64) == 4 and xl(1024, 1088, 64) != 4           # four chunks of 32 rows of L per wavefront and five, 32 tiles
+    assert xl(1024, 1280, 64) == 4 and xl(1024, 1344, 64) != 4           # five chunks of 32 rows of L per wavefront and six, 32 tiles
     assert xl(2048, 1536, 64) == 4 and xl(2048, 1600, 64) != 4           # six and seven, 64 tiles
     assert xl(8192, 1024, 64) == 4 and xl(8224, 1024, 64) != 4           # one round of tiles and a tile more
     assert xl(512, 2048, 64) == 1
