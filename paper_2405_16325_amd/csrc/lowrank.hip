@@ -49,7 +49,8 @@ hipError_t launch_skinny_pair(const SkinnyProduct& p, const SkinnyProduct& q, hi
 // Whole k-steps have the choice: the tile kernels stream better, but on few tiles of a long contraction need a second kernel for the
 // sums over slabs; this one is one launch always, at about 1.3 us per chunk of 32 k that a wavefront walks and round of
 // workgroups.
-// A product by itself, on at most one round of workgroups.  us, the call, tile kernel / here:
+// A product by itself, on at most one round of workgroups.  Over 260 calls each of X L and of dY R^T the form taken is 0.1 % and 0.2 %
+// slower than the better one in the mean.  us, the call, tile kernel / here:
 //   X L, up to five chunks, six on 64 tiles and more: 1024 x 512, rank 64 11.35 / 10.8; 600 x 1088, rank 64 18.4 / 17.9; 4096 x 1280,
 //     rank 64 (128 tiles) 19.6 / 17.6; 1024 x 1536, rank 64 (32 tiles) 17.3 / 18.3, rank 160 (96) 19.7 / 19.4; 1024 x 2048, rank 64
 //     19.4 / 21.5; two rounds, 16384 x 512, rank 64 14.9 / 16.0;
@@ -62,15 +63,14 @@ bool skinny_is_short(int64_t n, int64_t m, int64_t K, bool a_kmajor) {
 }
 
 // One of the four products of the gradient call, in pairs, which the tile kernels take in two launches or up to four.  In chunks x
-// rounds of two workgroups per compute unit: up to five for the gradients dL and dR; for the factors T and T2 five of rank 32,
-// four of up to 16 tokens, else two.  us, the call, tile kernels / here: 256 x 256, rank 32, 512 tokens 16.1 / 14.2, 1536 21.8 / 21.7,
-// 2048 24.2 / 25.4; 1280 x 1280, rank 32, 200 tokens 19.0 / 17.7; 1536 x 512, rank 32, 64 tokens 14.8 / 15.2; 1024 x 1024, rank 128, 4
-// tokens 14.6 / 13.4, 16 14.7 / 14.2, 32 14.8 / 15.3; 1280 x 1280, rank 64, 4 tokens 15.7 / 15.8; 512 x 512, rank 64, 1024 tokens 21.8 /
-// 21.0; 2048 x 2048, rank 64, 1024 tokens 30.9 / 35.2.
+// rounds of two workgroups per compute unit: up to six for the factors T and T2, five for the gradients dL and dR.  Over 420 calls of
+// 1 to 2000 tokens, 256 to 2048 a side, the form taken is 1.3 % slower than the better one in the mean (with ten for all 3.7 %; fewer
+// chunks pay at some ranks and token counts and not at others).  us, the call, tile kernels / here: 1280 x 1280, rank 32, 200 tokens
+// 19.0 / 17.7; 1024 x 1024, rank 128, 4 tokens 14.6 / 13.4, 32 14.8 / 15.3; 512 x 512, rank 64, 1024 tokens 21.8 / 21.0; 2048 x 2048, rank
+// 64, 1024 tokens 30.9 / 35.2; 256 x 256, rank 32, 1536 tokens 21.8 / 21.7, 2048 24.2 / 25.4.
 bool skinny_pair_is_short(int64_t b, int64_t d_in, int64_t d_out, int64_t r) {
     auto cost = [](int64_t n, int64_t m, int64_t K) { return skinny_chunks(K) * ((skinny_tiles(n, m) + 2 * RESIDENT - 1) / (2 * RESIDENT)); };
-    const int64_t most = r <= 32 ? 5 : b <= 16 ? 4 : 2;
-    return cost(b, r, d_in) <= most && cost(b, r, d_out) <= most && cost(d_in, r, b) <= 5 && cost(r, d_out, b) <= 5;
+    return cost(b, r, d_in) <= 6 && cost(b, r, d_out) <= 6 && cost(d_in, r, b) <= 5 && cost(r, d_out, b) <= 5;
 }
 
 hipError_t launch_skinny_factors(const SkinnyProduct& t, const SkinnyProduct& t2, hipStream_t s) {
