@@ -5,8 +5,8 @@ One step = one pass of the whole hot path over the linear layers of one OPT-66B-
 transformer block (q, k, v, o: 9216 x 9216; fc1: 36864 x 9216; fc2: 9216 x 36864; 16384 tokens,
 rank-128 adapters in the forward): for every layer slope_prune_rows, slope_double_prune (weights
 are re-pruned from dense each step), slope_spmm_fwd with the adapter, slope_spmm_bwd_x and the
-masked weight gradient (token-contiguous copies + slope_wgrad_masked_t; q, k and v share the copy of
-their common input).  All inputs are synthetic (seeded Gaussians, generated on the device) and
+masked weight gradient (q, k and v from token-contiguous copies by slope_wgrad_masked_t, since they share
+the copy of their common input; the others by slope_wgrad_masked with scratch).  All inputs are synthetic (seeded Gaussians, generated on the device) and
 resident in HBM before the clock starts.
 
 Prints ONE JSON line.  value = effective TFLOP/s = 3 * 2 * b * d_in * d_out summed over the
@@ -144,7 +144,8 @@ def train(args, torch, sl, inputs, dev, workload, steps, warmup, full):
     """The timed step on one layer set.  full: also the side measurements of the headline run."""
     spec, layers = build_layers(torch, sl, inputs, dev, workload)
     b, rank = spec["b"], spec["rank"]
-    # token-contiguous copies for the weight gradient: one buffer per input group, one for the output gradients
+    # token-contiguous copies for the weight gradient of layers that share their input: one buffer per input group, one for
+    # the output gradients
     xt = {}
     for lay in layers:
         if lay["x_group"] not in xt:
@@ -160,7 +161,7 @@ def train(args, torch, sl, inputs, dev, workload, steps, warmup, full):
     shared = {g for g in xt if sum(1 for l in layers if l["x_group"] == g) > 1}
 
     def wgrad(lay, fresh):
-        if not use_t or lay["x_group"] not in shared:         # nothing to share: both copies and the product in one call
+        if not use_t or lay["x_group"] not in shared:         # nothing to share: one call, which copies what pays
             sl.slope_wgrad_masked(lay["dY"], lay["X"], lay["meta"], out=lay["G"], workspace=wg_ws)
             return
         if fresh:
@@ -240,7 +241,7 @@ def train(args, torch, sl, inputs, dev, workload, steps, warmup, full):
         # dense contraction: 2 b d_in d_out flops per launch against the dense bf16 MFMA peak
         "wgrad_masked": {"bound": "mfma", "achieved": sum_f / (per_call["wgrad_masked"] * 1e-3) / 1e12,
                          "peak": PEAK_DENSE_BF16, "unit": "TFLOP/s",
-                         "note": "token-contiguous copies included (one per distinct input, one per output gradient)"},
+                         "note": "token-contiguous copies included (where layers share their input, and those that the call makes)"},
         # sparse contraction: credited dense-equivalent 2 b d_in d_out against the sparse bf16 peak
         "spmm_bwd_x": {"bound": "mfma", "achieved": sum_f / (per_call["spmm_bwd_x"] * 1e-3) / 1e12,
                        "peak": PEAK_SPARSE_BF16, "unit": "TFLOP/s"},
