@@ -27,7 +27,7 @@
 //     fetches 8 rows x 128 contiguous bytes, 8 consecutive lanes per row;
 //   - a row of the token operand has 128 bytes per k-step of 64, so B sits in a ring of three
 //     k-step stages; a row of the packed weight has only 64, so A is fetched for two k-steps at
-//     a time into two alternating pair buffers, and its metadata for four k-steps at a time;
+//     a time into two alternating pair buffers, and its metadata for eight k-steps at a time (four where LDS is short);
 //   - inside a row the eight 16-byte chunks are rotated by (row / 2) % 8, which makes the
 //     ds_read_b128 of the MFMA layout (16 lanes = 16 rows, same chunk) hit 16 different bank groups.
 // A workgroup owns a BM x BN tile of C with 8 wavefronts (2 x 4, two per SIMD), one barrier per k-step: while a wavefront
@@ -176,36 +176,41 @@ template <int BM, int BN>
 struct SpmmSmem {
     static constexpr int A_PAIR = BM * 128;     // packed values of BM rows x 2 k-steps
     static constexpr int B_STAGE = BN * 128;    // BN token rows x 1 k-step
-    static constexpr int M_QUAD = BM * 32;      // metadata of BM rows x 4 k-steps
     static constexpr int B_OFF = 2 * A_PAIR;
     static constexpr int M_OFF = B_OFF + 3 * B_STAGE;
-    static constexpr int DUMMY = M_OFF + 2 * M_QUAD;   // landing zone for the metadata load of idle wavefronts
+    // k-steps of a block of metadata, BM rows of 8 bytes per k-step; two blocks
+    static constexpr int META_STEPS = M_OFF + 2 * BM * 64 + 1024 <= 160 * 1024 ? 8 : 4, M_BLOCK = BM * 8 * META_STEPS;
+    static constexpr int DUMMY = M_OFF + 2 * M_BLOCK;  // landing zone for the metadata load of idle wavefronts
     static constexpr int TOTAL = DUMMY + 1024;
 };
 
 constexpr int SPMM_THREADS = 512;
 
-// Where a row's loads of pair `pair` (of k-steps) and quad `quad` start: byte offsets into the packed values and, for the
-// lanes that bring 16-byte half `half`, into the metadata (on top of the 16 * half the lane's address holds).  Past the
-// last k-step the last load of the row is repeated.
+// Where a row's loads of pair `pair` (of k-steps) start, in bytes of packed values.  Past the last k-step the last load of the row
+// is repeated.
 template <bool TAIL>
 __device__ __forceinline__ int64_t pair_offset(int pair, int ksteps) {
     if (TAIL) return 2 * pair + 1 < ksteps ? (int64_t)pair * 128 : ((int64_t)ksteps - 2) * 64;
     return (int64_t)(2 * pair < ksteps ? pair : ksteps / 2 - 1) * 128;
 }
-template <bool TAIL>
-__device__ __forceinline__ int64_t quad_offset(int quad, int ksteps, int half) {
-    if (TAIL) {
-        const int64_t last = (int64_t)ksteps * 8 - 16, o = (int64_t)quad * 32;
-        const int64_t o0 = o < last ? o : last, o1 = (o + 16 < last ? o + 16 : last) - 16;
-        return half ? o1 : o0;
-    }
-    return (int64_t)(4 * quad < ksteps ? quad : ksteps / 4 - 1) * 32;
-}
+// Metadata comes in blocks of STEPS k-steps, a row's 8 * STEPS bytes by as many neighbouring lanes as they have 16-byte pieces: a
+// load is 64 contiguous bytes of 16 rows, or 32 of 32 rows.  One load of a wavefront (per part) is a block of 256 rows by 4 k-steps.
+// The pieces of a row are exchanged by the row's upper bits, so that the sixteen rows of a 2-byte read of LDS fall on different banks.
+// What loads cost is requests more than bytes, and these are a tenth of them: leaving the metadata out made the products 2 to 11 %
+// faster.  us, blocks of four k-steps with a row's halves sixteen lanes apart / neighbouring lanes / blocks of eight: 2048 tokens, 4096 x
+// 4096 on 256 x 128 44.0 / 43.8 / 42.7, weights from HBM 50.9 / 49.8 / 46.5; 16384, 5120 x 5120 on 256 x 256 405.5 / 404.0 / 399.1; 128
+// tokens, 9216 x 9216, rank 128, in slabs 42.2 / - / 40.8.
+template <int STEPS>
+struct MetaLanes {
+    static constexpr int PIECES = STEPS / 2, ROW = PIECES * 16, ROWS = 64 / PIECES, PARTS = STEPS / 4;
+    // which piece of a row is in which place, both ways
+    __device__ __forceinline__ static int swap(int row) { return row * PIECES / 16 % PIECES; }
+    __device__ __forceinline__ static int piece(int lane) { return (lane % PIECES) ^ swap(lane / PIECES); }
+};
 #define LAST_STEP(S4) if (TAIL && ks0 + (S4) + 1 >= ksteps) break;
 
 // TAIL: the number of k-steps is not a multiple of 4 (at least two of them).  The packed weight is fetched two k-steps at
-// a time and its metadata four, so at the end of a row those fetches would run past it.  They are moved back to end with
+// a time and its metadata eight or four, so at the end of a row those fetches would run past it.  They are moved back to end with
 // the row instead: an odd last k-step then sits where the second step of its pair (the second 8 bytes of its 16 of
 // metadata) belongs, and that is where it is read.  A template parameter, so that whole quads pay nothing for it.
 //
@@ -303,7 +308,6 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     using S = SpmmSmem<BM, BN>;
     constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront
     constexpr int A_LD = BM / 64, B_LD = BN / 64;            // 1 KiB loads per wavefront: per pair, per step
-    constexpr int M_WAVES = BM / 32;                         // wavefronts that load metadata (32 rows each)
     extern __shared__ __align__(16) uint8_t smem[];
     fetch_arguments(B, n, Av, Am, m, K, tiles_m, tiles_n);
 
@@ -335,19 +339,19 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
         int row = wrap_row(n0 + rl, n);
         b_src[i] = (const uint8_t*)B + (size_t)row * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16);
     }
-    const bool meta_wave = wave < M_WAVES;                    // wave-uniform
-    const uint8_t* m_src;
-    {
-        // 32 rows = two fragments per instruction; lane l brings the 16-byte half (l >> 4) & 1 of row
-        // 16 (l >> 5) + (l & 15), so that LDS holds each fragment as [half][row]: the sixteen rows of a
-        // 2-byte metadata read then fall on sixteen different bank groups ([row][half] made rows r and r + 8
-        // collide: over a third of the LDS-active cycles of the 256 x 256 kernel were bank conflicts)
-        int rl = (meta_wave ? wave : 0) * 32 + (lane >> 5) * 16 + (lane & 15);
-        int row = wrap_row(m0 + rl, m);
-        m_src = Am + (size_t)row * (K / 8) + ((lane >> 4) & 1) * 16;
+    using ML = MetaLanes<S::META_STEPS>;
+    const uint8_t* m_src[ML::PARTS];
+    int m_dst[ML::PARTS], m_dst_step[ML::PARTS];              // (rows the tile does not have land in the dummy, all from one place)
+#pragma unroll
+    for (int p = 0; p < ML::PARTS; ++p) {
+        const int rl = (p * 8 + wave) * ML::ROWS;
+        const bool has = rl < BM;                             // wave-uniform
+        const int row = has ? wrap_row(m0 + rl + lane / ML::PIECES, m) : 0;
+        m_src[p] = Am + (size_t)row * (K / 8);
+        m_dst[p] = has ? S::M_OFF + (p * 8 + wave) * 1024 : S::DUMMY;
+        m_dst_step[p] = has ? S::M_BLOCK : 0;
     }
-    uint8_t* const m_dst0 = smem + (meta_wave ? S::M_OFF + wave * 1024 : S::DUMMY);
-    const int m_dst_step = meta_wave ? S::M_QUAD : 0;
+    const int m_piece = ML::piece(lane) * 16;
 
     // ---- reader lanes: fragment f = rows 16f .. 16f+15 = 2 KiB; lane (l16, lq) wants chunk 4h + lq
     const int sw = (l16 >> 1) & 7;
@@ -355,7 +359,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     const int rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);       // h = 1
     const int a_rd = (wm * MF) * 2048;
     const int b_rd = S::B_OFF + (wn * NF) * 2048;
-    const int m_rd = S::M_OFF + wm * MF * 512 + l16 * 16 + lq * 2;
+    const int m_rd = S::M_OFF + (wm * MF * 16 + l16) * ML::ROW + lq * 2, m_sw = ML::swap(l16) * 16;
 
     int k_first = 0, slab_steps = K / 64;
     float* sums = nullptr;
@@ -370,7 +374,8 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     for (int i = 0; i < A_LD; ++i) a_src[i] += (size_t)k_first * 64;
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) b_src[i] += (size_t)k_first * 128;
-    m_src += (size_t)k_first * 8;
+#pragma unroll
+    for (int p = 0; p < ML::PARTS; ++p) m_src[p] += (size_t)k_first * 8;
     auto issue_b = [&](int ks, int stage) {                   // token rows of k-step ks (clamped)
         int kc = ks < ksteps ? ks : ksteps - 1;
 #pragma unroll
@@ -382,8 +387,9 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + off, smem + buf * S::A_PAIR + (wave * A_LD + i) * 1024);
     };
-    auto issue_m = [&](int quad, int buf) {                   // metadata of k-steps 4 quad .. 4 quad + 3
-        dma16(m_src + quad_offset<TAIL>(quad, ksteps, (lane >> 4) & 1), m_dst0 + buf * m_dst_step);
+    auto issue_m = [&](int block, int part) {                 // metadata of k-steps META_STEPS * block ..
+        const int off = block * ML::ROW + m_piece, last = ksteps * 8 - 16;
+        dma16(m_src[part] + (off < last ? off : last), smem + m_dst[part] + (block & 1) * m_dst_step[part]);
     };
 
     f32x4 acc[MF][NF];
@@ -407,19 +413,20 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
             const bool second = (S4 & 1) != 0 || (TAIL && ks == ksteps - 1);
             const int i = x - NF;
             f.af[i].u = *(const u32x4*)(smem + ((S4 >> 1) & 1) * S::A_PAIR + a_rd + i * 2048 + (second ? rd1 : rd0));
-            f.ai[i] = *(const uint16_t*)(smem + m_rd + ((ks >> 2) & 1) * S::M_QUAD + (S4 >> 1) * 256 + i * 512 + (second ? 8 : 0));
+            const int piece = ((S4 >> 1) + (ML::PARTS == 2 ? (ks >> 2 & 1) * 2 : 0)) * 16;
+            f.ai[i] = *(const uint16_t*)(smem + m_rd + (ks / S::META_STEPS & 1) * S::M_BLOCK + (piece ^ m_sw) + i * 16 * ML::ROW + (second ? 8 : 0));
         }
     };
 
     // ---- prologue: what the k-steps before the first would have queued
-    issue_m(0, 0);
+#pragma unroll
+    for (int p = 0; p < ML::PARTS; ++p) issue_m(0, p);
     issue_a(0, 0);
     issue_b(0, 0);
-    issue_m(1, 1);
     issue_b(1, 1);
     issue_a(1, 1);
     issue_b(2, 2);
-    WAIT_HERE(waitcnt_imm(A_LD + 2 * B_LD + 1, 15));
+    WAIT_HERE(waitcnt_imm(A_LD + 2 * B_LD, 15));
     wg_barrier();
     Frags f;
 #pragma unroll
@@ -435,7 +442,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     int bst = 0;                                              // ring stage of the current k-step
     auto step = [&](int ks, auto s4) {
         constexpr int S4 = decltype(s4)::value, N4 = (S4 + 1) & 3;
-        constexpr int LOADS = B_LD + (S4 & 1) * A_LD + (S4 == 3), EARLY = NF + LOADS, SLOTS = MF * NF, PER = (EARLY + SLOTS - 1) / SLOTS;
+        constexpr int LOADS = B_LD + (S4 & 1) * A_LD + (S4 == 0), EARLY = NF + LOADS, SLOTS = MF * NF, PER = (EARLY + SLOTS - 1) / SLOTS;
         const int next = bst == 2 ? 0 : bst + 1;
         const int kb = ks + 3 < ksteps ? ks + 3 : ksteps - 1;
         const int64_t a_off = (S4 & 1) ? pair_offset<TAIL>((ks >> 1) + 2, ksteps) : 0;
@@ -451,7 +458,11 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
                     if (x < B_LD) dma16(b_src[x] + (size_t)kb * 128, smem + S::B_OFF + bst * S::B_STAGE + (wave * B_LD + x) * 1024);
                     else if (x < B_LD + (S4 & 1) * A_LD)
                         dma16(a_src[x - B_LD] + a_off, smem + (S4 >> 1) * S::A_PAIR + (wave * A_LD + x - B_LD) * 1024);
-                    else if (x < LOADS) issue_m((ks >> 2) + 2, (ks >> 2) & 1);
+                    else if (x < LOADS) {                     // a part of the next block
+                        const int quad = ks >> 2;
+                        if (ML::PARTS == 1 || (quad & 1) == 0) issue_m(quad / ML::PARTS + 1, 0);
+                        else issue_m(quad / ML::PARTS + 1, ML::PARTS - 1);
+                    }
                     else if (x < EARLY) read_one(g, ks + 1, N4, next, x - LOADS);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -486,19 +497,19 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 // own the two token halves of the tile, so each half of a B stage is private to one group and free
 // again as soon as that group has read it; two stages per half then give every load the same two
 // to three phases (half k-steps) of flight that the shared ring of three gave:
-//     A pair buffers 2 x 32 KiB | B half of group 0  2 x 16 KiB | of group 1  2 x 16 KiB | metadata 2 x 8 KiB
+//     A pair buffers 2 x 32 KiB | B half of group 0  2 x 16 KiB | of group 1  2 x 16 KiB | metadata 2 x 16 KiB
 // Queued by every wavefront, k = k-step, phases 2k (group 0 reads step k) and 2k + 1 (group 1 does):
-//     phase 2k     : B1(k+1);  lower half of A pair k/2 + 1 if k is even;  metadata quad (k+3)/4 if k % 4 == 1
+//     phase 2k     : B1(k+1);  lower half of A pair k/2 + 1 if k is even;  half of the metadata block of k/8 + 1 if k % 4 == 1
 //     phase 2k + 1 : B0(k+2);  upper half of A pair k/2 + 1 if k is even
 // and at the end of each phase a wavefront waits for everything it queued two or more phases ago,
 // which covers all that the next phase reads.  Every buffer is rewritten in the first phase after
 // the barrier that ends its last reader's phase.
 struct SplitSmem {
     static constexpr int BM = 256, BN = 256;
-    static constexpr int A_PAIR = BM * 128, B_HALF = BN / 2 * 128, M_QUAD = BM * 32;
+    static constexpr int A_PAIR = BM * 128, B_HALF = BN / 2 * 128, M_BLOCK = BM * 64;   // metadata: 8 k-steps
     static constexpr int B_OFF = 2 * A_PAIR;                  // then [group][stage] halves of B
     static constexpr int M_OFF = B_OFF + 4 * B_HALF;
-    static constexpr int TOTAL = M_OFF + 2 * M_QUAD;
+    static constexpr int TOTAL = M_OFF + 2 * M_BLOCK;
 };
 
 // loads one wavefront queues in the even / odd phase of k-step k (k taken mod 4)
@@ -538,12 +549,12 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
         a_src[q] = (const uint8_t*)Av + (size_t)ra * K + sw16;
         b_src[q] = (const uint8_t*)B + (size_t)rb * K * 2 + sw16;
     }
-    const uint8_t* m_src;                                    // 32 rows per wavefront
-    {
-        int rl = wave * 32 + (lane >> 5) * 16 + (lane & 15);  // fragments land as [half][row], see spmm_kernel
-        int row = wrap_row(m0 + rl, m);
-        m_src = Am + (size_t)row * (K / 8) + ((lane >> 4) & 1) * 16;
-    }
+    using ML = MetaLanes<8>;
+    const uint8_t* m_src[2];                                 // 16 rows per wavefront and part
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+        m_src[p] = Am + (size_t)wrap_row(m0 + (p * 8 + wave) * 16 + lane / ML::PIECES, m) * (K / 8);
+    const int m_piece = ML::piece(lane) * 16;
 
     // ---- L2 prefetch of the token panel through the scalar cache.  A compute unit holds about 128 vector-memory
     //      requests of 128 bytes in flight, so its operand feed is that many lines per mean latency, and the
@@ -591,7 +602,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
     const int rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);       // h = 1
     const int a_rd = (wm * MF) * 2048;
     const int b_rd = S::B_OFF + group * 2 * S::B_HALF + ((wn & 1) * NF) * 2048;
-    const int m_rd = S::M_OFF + wm * MF * 512 + l16 * 16 + lq * 2;
+    const int m_rd = S::M_OFF + (wm * MF * 16 + l16) * ML::ROW + lq * 2, m_sw = ML::swap(l16) * 16;
 
     const int ksteps = K / 64;                                // a multiple of 4 unless TAIL (see spmm_kernel)
     auto issue_b = [&](int g, int ks) {                       // token half g of k-step ks (clamped)
@@ -606,9 +617,9 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
         dma16(a_src[half * 2] + off, st);
         dma16(a_src[half * 2 + 1] + off, st + 1024);
     };
-    auto issue_m = [&](int quad) {                            // metadata of k-steps 4 quad .. 4 quad + 3
-        dma16(m_src + quad_offset<TAIL>(quad, ksteps, (lane >> 4) & 1),
-              smem + S::M_OFF + (quad & 1) * S::M_QUAD + wave * 1024);
+    auto issue_m = [&](int block, int part) {                 // metadata of k-steps 8 block .. 8 block + 7, half of the rows
+        const int off = block * 64 + m_piece, last = ksteps * 8 - 16;
+        dma16((part ? m_src[1] : m_src[0]) + (off < last ? off : last), smem + S::M_OFF + (block & 1) * S::M_BLOCK + (part * 8 + wave) * 1024);
     };
 
     f32x4 acc[MF][NF];
@@ -622,7 +633,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
     {                                                                                                  \
         issue_b(1, (k) + 1);                                                                           \
         if (((S4) & 1) == 0) issue_a(0, ((k) >> 1) + 1);                                               \
-        if (((S4) & 3) == 1) issue_m(((k) + 3) >> 2);                                                  \
+        if (((S4) & 3) == 1) issue_m(((k) >> 3) + 1, ((k) >> 2) & 1);                                  \
     }
 #define ODD_LOADS(k, S4)                                                                               \
     {                                                                                                  \
@@ -633,7 +644,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
         const bool second = ((S4) & 1) != 0 || (TAIL && ks == ksteps - 1);                             \
         const uint8_t* pa = smem + (((S4) >> 1) & 1) * S::A_PAIR + a_rd + (second ? rd1 : rd0);        \
         const uint8_t* pb = smem + b_rd + ((S4) & 1) * S::B_HALF;                                      \
-        const uint8_t* pm = smem + m_rd + ((ks0 >> 2) & 1) * S::M_QUAD + ((S4) >> 1) * 256 + (second ? 8 : 0); \
+        const uint8_t* pm = smem + m_rd + ((ks0 >> 3) & 1) * S::M_BLOCK + (((((S4) >> 1) + (ks0 >> 1 & 2)) * 16) ^ m_sw) + (second ? 8 : 0); \
         BFrag bf[NF];                                                                                  \
         AFrag af[MF];                                                                                  \
         int ai[MF];                                                                                    \
@@ -643,7 +654,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
         }                                                                                              \
         _Pragma("unroll") for (int i = 0; i < MF; ++i) {                                               \
             af[i].u = *(const u32x4*)(pa + i * 2048);                                                  \
-            ai[i] = *(const uint16_t*)(pm + i * 512);                                                  \
+            ai[i] = *(const uint16_t*)(pm + i * 16 * ML::ROW);                                         \
         }
 #define SPLIT_MFMA                                                                                     \
         _Pragma("unroll") for (int i = 0; i < MF; ++i) _Pragma("unroll") for (int j = 0; j < NF; ++j)  \
@@ -678,7 +689,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
     }
 
     // ---- prologue: what the schedule would have queued in the phases before phase 0
-    issue_m(0);
+    issue_m(0, 0); issue_m(0, 1);
     issue_a(0, 0); issue_a(1, 0); issue_b(0, 0);
     issue_b(1, 0);
     issue_b(0, 1);                                            // = the odd phase of step -1

@@ -69,6 +69,18 @@ def test_sparse_product(b, d_out, tile, ksteps):
     assert_all_close(sl.slope_spmm_fwd(X, vals, meta), want, "Y")
 
 
+# blocks of metadata (8 k-steps) that end inside the contraction: 256 x 256 tiles, slabs of 20 k-steps
+@pytest.mark.parametrize("b,d_out,ksteps", [(4090, 4088, k) for k in (2, 3, 4, 5, 7, 8, 9, 11, 12, 13, 16, 17)] + [(128, 9216, 120)])
+def test_metadata_blocks_of_a_sparse_product(b, d_out, ksteps):
+    print(f"spmm b={b} d_out={d_out} k-steps={ksteps}", flush=True)
+    plan = sl.slope_spmm_fwd_plan(b, 64 * ksteps, d_out, 0, True)
+    assert (plan["rows"], plan["tokens"], plan["slabs"]) == ((256, 256, 1) if b > 128 else (256, 128, 6))
+    X, W = gauss(b, 64 * ksteps), gauss(d_out, 64 * ksteps)
+    vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    want = X.float() @ torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float().t()
+    assert_all_close(sl.slope_spmm_fwd(X, vals, meta), want, "Y")
+
+
 # whole rounds of 256 x 256 tiles and 33 or 64 left over, in quarters, or 128, in halves; parts that lie past the edge of a ragged tile;
 # an odd number of k-steps; with and without an adapter
 @pytest.mark.parametrize("r", [0, 32])
