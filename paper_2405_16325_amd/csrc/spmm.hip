@@ -239,7 +239,7 @@ __device__ __forceinline__ bool split_item(const SplitJob& job, const bf16_t* __
         const int id = (pos - run) * XCDS + xcd;
         const int xl_tiles_r = (job.r + SK_BJ - 1) / SK_BJ, xl_tiles = xl_tiles_r * ((n + SK_BI - 1) / SK_BI);
         const int part = id / xl_tiles, tile = id % xl_tiles;
-        if (part < job.xl_slabs)
+        if (part < job.xl_slabs && (int)threadIdx.x < SK_WAVES * 64)     // (the ring kernel's workgroups have more wavefronts)
             skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * (uint32_t)job.k_per,
                                      min((uint32_t)K, (part + 1) * (uint32_t)job.k_per), tile / xl_tiles_r * SK_BI,
                                      tile % xl_tiles_r * SK_BJ, nullptr, job.Q + (size_t)part * n * job.r, smem);
@@ -728,13 +728,20 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 // spmm_ring_kernel: the smaller tiles, one barrier per pair of k-steps.  A tile of 128 x 64 gives a wavefront four MFMAs
 // per k-step, so a barrier per k-step, as above, would cost more than the k-step's loads (two of them took 0.35 us per
 // k-step beside what its loads take).  Here a ring stage holds a pair of k-steps of both operands (the packed values come in
-// pairs anyway, 128 bytes per row), and a wavefront, per pair: reads the second k-step's fragments and multiplies the first, waits
-// for its own loads of the next pair, passes the barrier, reads that pair's first k-step, queues the loads that refill the stage
-// everybody has left and multiplies the second.  So no product waits for the reads of its own k-step, three to four stages keep
-// two or three pairs (34 to 50 KB each) on the way, and the operand feed bounds the kernel.  (Before, a pair's reads followed
-// the barrier and the loads, and its products them: us, operands in the last-level cache, 2048 tokens, 768 x 3072 on 128 x 64 16.9
-// -> 15.7, on 128 x 128 23.3 -> 20.8; 512 tokens, 4096 x 4096 20.9 -> 19.8; 300, 9216 x 4096 on 192 x 64 26.7 -> 23.8; from HBM
-// 18.3 -> 18.1, 24.8 -> 24.5, 23.8 -> 23.6, 29.9 -> 29.3.  Loads after the second products: 8 % slower.)
+// pairs anyway, 128 bytes per row).  Eight wavefronts, per pair, read the second k-step's fragments, multiply the first, pass the barrier,
+// read the next pair's first k-step and multiply the second, so that no product waits for the reads of its own k-step.
+// LOADERS more, one per SIMD, only load: wait for their loads of the next pair, pass the barrier and queue the loads that refill the
+// stage everybody has left.  Three to four stages keep two or three pairs (34 to 50 KB each) on the way, and the operand feed
+// bounds the kernel.
+// A wavefront that queues loads stands still until the address unit, 64 bytes per cycle for the whole compute unit, has taken them: where
+// the multiplying ones did it, after the barrier, the last of them began their products some hundred cycles late (1000 tokens, 4352 x
+// 4352: of 940 cycles per k-step four of the wavefronts spent 390 at the barrier, waiting for the other four; 50 for loads).  us, operands
+// in the last-level cache and from HBM, loads by the eight / by four of their own: 700 tokens, 4160 x 2112 on 192 x 64 17.0 / 15.1 and 17.1
+// / 15.3; 1000, 4352 x 4352 on 192 x 96 32.4 / 29.1 and 37.5 / 35.4; 1500, 2040 x 4096 on 128 x 96 22.2 / 20.1 and 22.3 / 20.3; 2048, 768 x
+// 3072 on 128 x 64 13.2 / 12.5.  Two loaders: 2 to 7 % slower than four; four of higher priority: 0 to 4 %.  The kernel above, whose loads
+// are spread among its products, gains nothing by it.
+// (Reads a k-step ahead of their products, against products that follow their reads: 2048 tokens, 768 x 3072 on 128 x 64 16.9
+// -> 15.7 us, on 128 x 128 23.3 -> 20.8; 300, 9216 x 4096 on 192 x 64 26.7 -> 23.8.)
 // Metadata: META_PAIRS pairs (16 bytes each) per row at a time, as many neighbouring lanes per row, the pieces of a row
 // rotated so that the sixteen rows of a 2-byte read fall on different banks.
 // Weights from HBM, us, the two-phase kernel / here: 2048 tokens, 768 x 3072 on 128 x 64 20.4 / 15.8; 512 tokens, 4096 x 4096
@@ -764,8 +771,9 @@ constexpr int ring_leave(int u, int each, int meta) {
 
 // TAIL: an odd number of k-steps; the values and metadata of the last one are then fetched as the second half of a pair that
 // ends with the row (see spmm_kernel).
+constexpr int LOADERS = 4, RING_THREADS = SPMM_THREADS + 64 * LOADERS;
 template <int BM, int BN, bool TAIL, class Job>
-__global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* __restrict__ B, int n,
+__global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* __restrict__ B, int n,
                                                                  const bf16_t* __restrict__ Av,
                                                                  const uint8_t* __restrict__ Am, int m, int K,
                                                                  const bf16_t* __restrict__ B2,
@@ -776,8 +784,8 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
     constexpr int META_PAIRS = S::META_PAIRS;
     constexpr int WM = BM == 128 && BN == 128 ? 2 : 4, WN = 8 / WM;    // wavefronts over the tile: the squarest fragments
     constexpr int MF = BM / (16 * WM), NF = BN / (16 * WN);
-    constexpr int A_LD = BM / 64, B_LD = BN / 32;             // 1 KiB loads per wavefront and pair
-    constexpr int M_LOADS = S::M_BLOCK / 1024, M_LD = (M_LOADS + 7) / 8;   // per block; some twice where 8 does not divide them
+    constexpr int A_LD = BM / (8 * LOADERS), B_LD = BN / (4 * LOADERS);   // 1 KiB loads per loading wavefront and pair
+    constexpr int M_LOADS = S::M_BLOCK / 1024, M_LD = (M_LOADS + LOADERS - 1) / LOADERS;   // per block; some twice where need be
     static_assert(BM % 64 == 0 && BN % 32 == 0 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "whole loads and fragments");
     extern __shared__ __align__(16) uint8_t smem[];
     fetch_arguments(B, n, Av, Am, m, K, tiles_m, tiles_n);
@@ -804,48 +812,77 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
     const int ksteps = K / 64 - k_first > slab_steps ? slab_steps : K / 64 - k_first;
     const int pairs = (ksteps + 1) / 2;
 
-    // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8
-    const uint8_t* a_src[A_LD];
+    if (wave >= 8) {                                          // (a wavefront that has ended does not count at barriers)
+        const int loader = wave - 8;
+        // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8
+        const uint8_t* a_src[A_LD];
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-        const int rl = (wave * A_LD + i) * 8 + (lane >> 3);
-        a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
-    }
-    const uint8_t* b_src[B_LD];
-    int b_step[B_LD];                                         // which k-step of the pair (wave-uniform)
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) {
-        const int j = wave * B_LD + i, rl = j % (BN / 8) * 8 + (lane >> 3);
-        b_step[i] = j / (BN / 8);
-        b_src[i] = (const uint8_t*)B + (size_t)wrap_row(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
-    }
-    const uint8_t* m_src[M_LD];
-    int m_pair[M_LD], m_dst[M_LD];                            // pair inside the block; LDS offset inside it
-#pragma unroll
-    for (int i = 0; i < M_LD; ++i) {
-        const int idx = (wave * M_LD + i) % M_LOADS, rl = (idx * 64 + lane) / META_PAIRS;
-        m_src[i] = Am + (size_t)wrap_row(m0 + rl, m) * (K / 8) + (size_t)k_first * 8;
-        m_pair[i] = (lane % META_PAIRS) ^ (rl * META_PAIRS / 16 % META_PAIRS);
-        m_dst[i] = S::M_OFF + idx * 1024;
-    }
-    auto issue = [&](int p, int stage, bool new_block) {      // loads of pair p (inside the contraction, at least in part)
-        uint8_t* const st = smem + stage * S::STAGE;
-        if (new_block) {
-#pragma unroll
-            for (int i = 0; i < M_LD; ++i) {
-                const int64_t off = (int64_t)(p + m_pair[i]) * 16, last = (int64_t)ksteps * 8 - 16;
-                dma16(m_src[i] + (off < last ? off : last), smem + m_dst[i] + (p / META_PAIRS & 1) * S::M_BLOCK);
-            }
+        for (int i = 0; i < A_LD; ++i) {
+            const int rl = (loader * A_LD + i) * 8 + (lane >> 3);
+            a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
         }
-        const int64_t a_off = pair_offset<TAIL>(p, ksteps);
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + a_off, st + (wave * A_LD + i) * 1024);
+        const uint8_t* b_src[B_LD];
+        int b_step[B_LD];                                         // which k-step of the pair (wave-uniform)
 #pragma unroll
         for (int i = 0; i < B_LD; ++i) {
-            const int k = 2 * p + b_step[i], kc = !TAIL || k < ksteps ? k : ksteps - 1;
-            dma16(b_src[i] + (size_t)kc * 128, st + S::A_STAGE + (wave * B_LD + i) * 1024);
+            const int j = loader * B_LD + i, rl = j % (BN / 8) * 8 + (lane >> 3);
+            b_step[i] = j / (BN / 8);
+            b_src[i] = (const uint8_t*)B + (size_t)wrap_row(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
         }
-    };
+        const uint8_t* m_src[M_LD];
+        int m_pair[M_LD], m_dst[M_LD];                            // pair inside the block; LDS offset inside it
+#pragma unroll
+        for (int i = 0; i < M_LD; ++i) {
+            const int idx = (loader * M_LD + i) % M_LOADS, rl = (idx * 64 + lane) / META_PAIRS;
+            m_src[i] = Am + (size_t)wrap_row(m0 + rl, m) * (K / 8) + (size_t)k_first * 8;
+            m_pair[i] = (lane % META_PAIRS) ^ (rl * META_PAIRS / 16 % META_PAIRS);
+            m_dst[i] = S::M_OFF + idx * 1024;
+        }
+        auto issue = [&](int p, int stage, bool new_block) {      // loads of pair p (inside the contraction, at least in part)
+            uint8_t* const st = smem + stage * S::STAGE;
+            if (new_block) {
+#pragma unroll
+                for (int i = 0; i < M_LD; ++i) {
+                    const int64_t off = (int64_t)(p + m_pair[i]) * 16, last = (int64_t)ksteps * 8 - 16;
+                    dma16(m_src[i] + (off < last ? off : last), smem + m_dst[i] + (p / META_PAIRS & 1) * S::M_BLOCK);
+                }
+            }
+            const int64_t a_off = pair_offset<TAIL>(p, ksteps);
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + a_off, st + (loader * A_LD + i) * 1024);
+#pragma unroll
+            for (int i = 0; i < B_LD; ++i) {
+                const int k = 2 * p + b_step[i], kc = !TAIL || k < ksteps ? k : ksteps - 1;
+                dma16(b_src[i] + (size_t)kc * 128, st + S::A_STAGE + (loader * B_LD + i) * 1024);
+            }
+        };
+#pragma unroll
+        for (int p = 0; p < S::STAGES - 1; ++p)
+            if (p < pairs) issue(p, p, p % META_PAIRS == 0);
+        int stage = S::STAGES - 1;
+        // pair p, with index u in its block of metadata, has landed (in the last STAGES - 2 pairs there are fewer loads behind it: then
+        // all are waited for) and everybody has read the one before it, whose stage is filled again
+        auto pair = [&](int p, auto index) {
+            constexpr int u = decltype(index)::value, leave = ring_leave<S>(u, A_LD + B_LD, M_LD);
+            if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 15));
+            else WAIT_HERE(waitcnt_imm(0, 15));
+            wg_barrier();
+            if (p + S::STAGES - 1 < pairs) issue(p + S::STAGES - 1, stage, (u + S::STAGES - 1) % META_PAIRS == 0);
+            stage = stage == S::STAGES - 1 ? 0 : stage + 1;
+        };
+        for (int p = 0; p < pairs; p += META_PAIRS) {
+            pair(p, std::integral_constant<int, 0>{});
+            if (p + 1 >= pairs) break;
+            pair(p + 1, std::integral_constant<int, 1>{});
+            if constexpr (META_PAIRS == 4) {
+                if (p + 2 >= pairs) break;
+                pair(p + 2, std::integral_constant<int, 2>{});
+                if (p + 3 >= pairs) break;
+                pair(p + 3, std::integral_constant<int, 3>{});
+            }
+        }
+        return;
+    }
 
     f32x4 acc[MF][NF];
 #pragma unroll
@@ -885,23 +922,14 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
             for (int j = 0; j < NF; ++j)
                 acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(f.af[i].v, f.bf[j].v, acc[i][j], f.ai[i], 0, 0);
     };
-    // pair p, with index u in its block of metadata, has landed and everybody has read what came before it (in the last
-    // STAGES - 2 pairs there are fewer loads behind it: then all are waited for)
-    auto landed = [&](int p, auto index) {
-        constexpr int leave = ring_leave<S>(decltype(index)::value, A_LD + B_LD, M_LD);
-        if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 0));
-        else WAIT_HERE(waitcnt_imm(0, 0));
+    // the loaders pass this when pair p has landed, the others when they have read what came before it
+    auto landed = [&]() {
+        WAIT_HERE(waitcnt_imm(63, 0));
         wg_barrier();
     };
-
-#pragma unroll
-    for (int p = 0; p < S::STAGES - 1; ++p)
-        if (p < pairs) issue(p, p, p % META_PAIRS == 0);
-    landed(0, std::integral_constant<int, 0>{});
+    landed();
     Frags f0, f1;
     read(f0, 0, 0, 0, 0, TAIL && ksteps == 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (S::STAGES - 1 < pairs) issue(S::STAGES - 1, S::STAGES - 1, (S::STAGES - 1) % META_PAIRS == 0);
     int stage = 0;
     auto pair = [&](int p, auto index) {                      // index = p % META_PAIRS; f0 holds the pair's first k-step
         constexpr int u = decltype(index)::value, next = (u + 1) % META_PAIRS;
@@ -910,11 +938,10 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_ring_kernel(const bf16_t* _
         __builtin_amdgcn_sched_barrier(0);
         multiply(f0);
         if (p + 1 < pairs) {
-            landed(p + 1, std::integral_constant<int, next>{});
+            landed();
             const int after = stage == S::STAGES - 1 ? 0 : stage + 1;
             read(f0, after, p + 1, next, 0, TAIL && 2 * p + 3 >= ksteps);
             __builtin_amdgcn_sched_barrier(0);
-            if (p + S::STAGES < pairs) issue(p + S::STAGES, stage, (u + S::STAGES) % META_PAIRS == 0);
             stage = after;
         }
         if (!odd_end) multiply(f1);
@@ -1193,7 +1220,7 @@ hipError_t launch_ring_as(const bf16_t* B, int64_t n, const bf16_t* Av, const ui
     hipError_t e = allow_dynamic_lds<spmm_ring_kernel<BM, BN, TAIL, Job>>(S::TOTAL);
     if (e != hipSuccess) return e;
     const int grid = tile_grid<BM, BN>(tiles_m, tiles_n, n, job);
-    spmm_ring_kernel<BM, BN, TAIL, Job><<<dim3((unsigned)grid), dim3(SPMM_THREADS), S::TOTAL, s>>>(
+    spmm_ring_kernel<BM, BN, TAIL, Job><<<dim3((unsigned)grid), dim3(RING_THREADS), S::TOTAL, s>>>(
         B, (int)n, Av, Am, (int)m, (int)K, B2, A2, (int)K2, C, tiles_m, tiles_n, job);
     return hipGetLastError();
 }
