@@ -84,7 +84,13 @@ struct TnSmem {
     static constexpr int TOTAL = NS * STAGE;                       // ring of NS stages
 };
 
-constexpr int TN_THREADS = 512;
+constexpr int TN_THREADS = 512;                              // the wavefronts that multiply
+// Tiles up to 128 x 128 have four more that only load (why: spmm_ring_kernel), and load nothing past the end.  us, loads by the
+// eight / by four of their own: dW of 1024 x 1024 over 4096 tokens on 64 x 64 18.7 / 17.4, 3072 x 768 over 2048 on 128 x 128 19.8 / 19.1;
+// masked dense 2000 x 1928 over 2048 on 128 x 128 18.9 / 18.3; the gradients of 3136 x 896, rank 64 over 14376 tokens 163.9 / 157.3.
+// 192 x 128, whose loads are spread among its products: 65.3 / 66.4 (dW of 4096 x 3000 over 3064 tokens).
+constexpr int TN_LOADERS = 4;
+constexpr int tn_threads(int bm, int bn) { return TN_THREADS + (bm * bn <= 128 * 128 ? TN_LOADERS * 64 : 0); }
 enum { EPI_MASKED_PACKED = 0, EPI_PLAIN = 1 };
 
 // Metadata of the 32 Q columns of W^R from c (a multiple of 32) of row o, by dwords; columns outside the matrix: any.  The dwords of
@@ -187,8 +193,9 @@ __device__ __forceinline__ void store_sums(const f32x4 (&acc)[MF][NF], int m, in
 // NS = ring depth: loads run NS - 1 k-steps ahead.  Two stages are all that fits beside a 256 x 256
 // tile; small tiles (memory-bound skinny products) take a deeper ring to cover the HBM latency.
 // Every thread of the workgroup must make the call; wavefront w holds the fragments at rows w % 2 * BM / 2, columns w / 2 * BN / 4.
+// False: a wavefront that has only loaded, and is done.
 template <int BM, int BN, int NS, bool AKM, bool BKM>
-__device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const DenseOperand& Bt, int ksteps, int k_begin, int k_end, int m0,
+__device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const DenseOperand& Bt, int ksteps, int k_begin, int k_end, int m0,
                                               int n0, uint8_t* smem, f32x4 (&acc)[BM / 32][BN / 64]) {
     using S = TnSmem<BM, BN, NS>;
     constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront (2 x 4 waves)
@@ -196,6 +203,41 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
     constexpr int AHEAD = (NS - 2) * (LD_A + LD_B);          // loads that may stay in flight at a wait
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    constexpr bool LOADERS = tn_threads(BM, BN) != TN_THREADS;
+    constexpr int LAST = (NS - 1) * S::STAGE;
+    if (LOADERS && wave >= 8) {
+        constexpr int EACH = 8 / TN_LOADERS;                  // a loader has the loads of so many of the wavefronts
+        DenseLoader<AKM, BKM, BM, BM / 2> la[EACH];
+        DenseLoader<BKM, AKM, BN, BN / 4> lb[EACH];
+#pragma unroll
+        for (int v = 0; v < EACH; ++v) {
+            la[v].init(At, m0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
+            lb[v].init(Bt, n0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
+        }
+        auto issue = [&](int ks, int at) {
+#pragma unroll
+            for (int v = 0; v < EACH; ++v) {
+#pragma unroll
+                for (int i = 0; i < LD_A; ++i) la[v].load(ks, i, smem, at, wave - 8 + v * TN_LOADERS);
+#pragma unroll
+                for (int i = 0; i < LD_B; ++i) lb[v].load(ks, i, smem, at + S::A_BYTES, wave - 8 + v * TN_LOADERS);
+            }
+        };
+#pragma unroll
+        for (int p = 0; p < NS - 1; ++p)
+            if (k_begin + p < k_end) issue(k_begin + p, p * S::STAGE);
+        int at = LAST;
+        for (int ks = k_begin; ks < k_end; ++ks) {
+            // step ks has landed (in the last NS - 2 steps there are fewer loads behind it: then all are waited for) and everybody has
+            // read the one before it, whose stage is filled again
+            if (ks + NS - 2 < k_end) WAIT_HERE(waitcnt_imm(AHEAD * EACH, 15));
+            else WAIT_HERE(waitcnt_imm(0, 15));
+            wg_barrier();
+            if (ks + NS - 1 < k_end) issue(ks + NS - 1, at);
+            at = at == LAST ? 0 : at + S::STAGE;
+        }
+        return false;
+    }
     DenseLoader<AKM, BKM, BM, BM / 2> opa;
     DenseLoader<BKM, AKM, BN, BN / 4> opb;
     opa.init(At, m0, (wave & 1) * (BM / 2), wave, lane, 0, ksteps, smem);
@@ -215,22 +257,23 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
     // The stage that is read, as a byte offset that wraps.  As (ks % NS) * STAGE it became a multiply-high and subtractions per
     // lane before every step's LDS reads (us, from HBM: 2048 x 1024 over 4096 on 64 x 128 30.5 -> 26.0, 704 x 2112 over 4160
     // 27.0 -> 22.2, 2048 x 1024 over 8192 51.8 -> 41.8); the 256 x 256 kernel, where registers are short, is 1 % slower this way.
-    constexpr int LAST = (NS - 1) * S::STAGE;
     int at = 0;
+    if (!LOADERS) {
 #pragma unroll
-    for (int p = 0; p < NS - 1; ++p) issue(k_begin + p, p * S::STAGE);
-    WAIT_HERE(waitcnt_imm(AHEAD, 15));                        // the first step has landed (this wave's share)
+        for (int p = 0; p < NS - 1; ++p) issue(k_begin + p, p * S::STAGE);
+        WAIT_HERE(waitcnt_imm(AHEAD, 15));                    // the first step has landed (this wave's share)
+    }
     wg_barrier();
     // Two schedules of a k-step.  Where each wavefront's products cover its own reads: one barrier, the fragments of a half of the
     // k-step read while the other half is multiplied.  (us, operands in the last-level cache, in two phases / so: 64 x 64, 1024
     // x 1024 over 4096 tokens 23.9 / 21.0; 128 x 128, 3072 x 768 over 2048 tokens 22.4 / 20.6; 192 x 192, 1024 x 2048 over 4096 47.9
     // / 42.7; 256 x 128, 4096 x 4096 over 4096 tokens 129 / 120.)  Else two phases, as in the 256 x 256 kernel: where the ring has
     // two stages, so that loads are queued later (256 x 192, 5120 x 6464 over 752 tokens: 62.7 against 65.3), and on k-contiguous
-    // operands with 8 or 12 products per half (128 x 128, 1920 x 1973 over 3840: 31.4 against 33.2; 192 x 128 34.8 / 35.7).
+    // operands on 192 x 128 (1920 x 1973 over 3840: 34.8 against 35.7).
     // (Each tile both ways on seven shapes per layout, contractions of 192 to 12000, from HBM and from the cache; one barrier against two
     // phases in the mean: k-major 256 x 192 4 % slower, the others 0 to 8 % faster; k-contiguous 256 x 128, 192 x 192, 64 x 128 and
     // 64 x 64 1 to 11 % faster, 256 x 192, 192 x 128 and 128 x 128 1 to 3 % slower.)
-    if constexpr (NS == 2 || (!AKM && !BKM && MF * NF >= 8 && MF * NF <= 12)) {
+    if constexpr (!LOADERS && (NS == 2 || (!AKM && !BKM && MF * NF == 12))) {
         const int group = wave >> 2;
         // One k-step.  Loads of step s + NS - 1 are queued in the even phase in which their stage, last
         // read for step s - 1, has just been released: group 0 is then in its memory phase of step s,
@@ -273,7 +316,7 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
 #undef TN_STEP
     } else {
         struct Half { u32x4 a[MF], b[NF]; };                  // fragments of half a k-step
-        constexpr int READS = MF + NF, LOADS = LD_A + LD_B, MFMAS = MF * NF;
+        constexpr int READS = MF + NF, LOADS = LOADERS ? 0 : LD_A + LD_B, MFMAS = MF * NF;
         auto read_one = [&](Half& f, const auto& sa, const auto& sb, int h, int x) {
             if (x < NF) f.b[x] = opb.half(sb, x, h);
             else f.a[x - NF] = opa.half(sa, x - NF, h);
@@ -317,7 +360,7 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
             for (int x = 0; x < READS; ++x) read_one(f0, sa, sb, 0, x);
         }
         __builtin_amdgcn_sched_barrier(0);
-        issue(k_begin + NS - 1, LAST);
+        if (!LOADERS) issue(k_begin + NS - 1, LAST);
         WAIT_HERE(waitcnt_imm(63, 0));                        // (else the compiler waits for all reads at the head of the loop)
         for (int ks = k_begin; ks < k_end; ++ks) {
             {
@@ -325,8 +368,12 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
                 const auto sb = opb.stage(smem, at + S::A_BYTES);
                 multiply(f0, std::integral_constant<int, READS>{}, [&](int x) { read_one(f1, sa, sb, 1, x); });
             }
+            if (LOADERS && ks + 1 == k_end) {
+                multiply(f1, std::integral_constant<int, 0>{}, [](int) {});
+                break;
+            }
             // this wavefront has read the stage, and its loads of the next one have landed
-            WAIT_HERE(waitcnt_imm(AHEAD, 0));
+            WAIT_HERE(waitcnt_imm(LOADERS ? 63 : AHEAD, 0));
             wg_barrier();
             const int next = at == LAST ? 0 : at + S::STAGE;
             const auto sa = opa.stage(smem, next);            // (after the last k-step read and not used)
@@ -338,14 +385,15 @@ __device__ __forceinline__ void dense_tn_sums(const DenseOperand& At, const Dens
             at = next;
         }
     }
-    WAIT_HERE(waitcnt_imm(0, 15));                            // drain the clamped look-ahead loads
+    if (!LOADERS) WAIT_HERE(waitcnt_imm(0, 15));              // drain the clamped look-ahead loads
+    return true;
 }
 
 // D[i, j] = sum_k At[i, k] * Bt[j, k] over ksteps k-steps of 64;  At: m rows, Bt: n rows.
 //   EPI_MASKED_PACKED: out = packed gradient [n][m/2] selected by meta (u8[n][m/8])
 //   EPI_PLAIN        : out = bf16 [n][m]  (row j, four consecutive i per lane)
 template <int BM, int BN, int EPI, int NS, bool AKM, bool BKM>
-__global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(DenseOperand At, DenseOperand Bt, int ksteps, const uint8_t* __restrict__ meta,
+__global__ void __launch_bounds__(tn_threads(BM, BN)) dense_tn_kernel(DenseOperand At, DenseOperand Bt, int ksteps, const uint8_t* __restrict__ meta,
                                                               bf16_t* __restrict__ out, int tiles_m, int tiles_n) {
     using S = TnSmem<BM, BN, NS>;
     constexpr int MF = BM / 32, NF = BN / 64;
@@ -357,7 +405,7 @@ __global__ void __launch_bounds__(TN_THREADS) dense_tn_kernel(DenseOperand At, D
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / 4);
     const int m = At.rows, n = Bt.rows;
     f32x4 acc[MF][NF];
-    dense_tn_sums<BM, BN, NS, AKM, BKM>(At, Bt, ksteps, 0, ksteps, m0, n0, smem, acc);
+    if (!dense_tn_sums<BM, BN, NS, AKM, BKM>(At, Bt, ksteps, 0, ksteps, m0, n0, smem, acc)) return;
     if constexpr (EPI == EPI_PLAIN) {
         static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
         store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, m, n, l16, lq, out, smem, m0, n0);
@@ -391,14 +439,14 @@ __device__ __forceinline__ void skinny_tn_tile(const SkinnyJob& j, int w, uint8_
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / 4);
     const int k_begin = slab * j.slab_steps, k_end = min(k_begin + j.slab_steps, j.ksteps);
     f32x4 acc[MF][NF];
-    dense_tn_sums<BM, BN, NS, AKM, BKM>(j.A, j.B, j.ksteps, k_begin, k_end, m0, n0, smem, acc);
+    if (!dense_tn_sums<BM, BN, NS, AKM, BKM>(j.A, j.B, j.ksteps, k_begin, k_end, m0, n0, smem, acc)) return;
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
     if (j.slabs > 1) store_sums<MF, NF>(acc, m, n, mw, nw, l16, lq, j.sums + (size_t)slab * n * m);
     else store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, m, n, l16, lq, j.out, smem, m0, n0);
 }
 
 template <int LONG, int RANK, int NS, bool GRADIENTS>
-__global__ void __launch_bounds__(TN_THREADS) skinny_tn_kernel(SkinnyJob j0, SkinnyJob j1) {
+__global__ void __launch_bounds__(tn_threads(LONG, RANK)) skinny_tn_kernel(SkinnyJob j0, SkinnyJob j1) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int w = (int)blockIdx.x, first = j0.grid * j0.slabs;
     if (w < first) skinny_tn_tile<RANK, LONG, NS, true, GRADIENTS>(j0, w, smem);
@@ -690,7 +738,7 @@ hipError_t launch_dense_tn(const DenseOperand& A, const DenseOperand& B, int64_t
     const int tiles_m = (A.rows + BM - 1) / BM, tiles_n = (B.rows + BN - 1) / BN;
     hipError_t e = allow_dynamic_lds<dense_tn_kernel<BM, BN, EPI, NS, AKM, BKM>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    dense_tn_kernel<BM, BN, EPI, NS, AKM, BKM><<<dim3((unsigned)super_grid(tiles_m, tiles_n)), dim3(TN_THREADS), S::TOTAL, s>>>(
+    dense_tn_kernel<BM, BN, EPI, NS, AKM, BKM><<<dim3((unsigned)super_grid(tiles_m, tiles_n)), dim3(tn_threads(BM, BN)), S::TOTAL, s>>>(
         A, B, (int)ksteps, meta, out, tiles_m, tiles_n);
     return hipGetLastError();
 }
@@ -1019,7 +1067,7 @@ static hipError_t launch_skinny_as(SkinnyJob j0, SkinnyJob j1, hipStream_t s) {
     place(j1, !GRADIENTS);
     hipError_t e = allow_dynamic_lds<skinny_tn_kernel<LONG, RANK, NS, GRADIENTS>>(S::TOTAL);
     if (e != hipSuccess) return e;
-    skinny_tn_kernel<LONG, RANK, NS, GRADIENTS><<<dim3((unsigned)(j0.grid * j0.slabs + j1.grid * j1.slabs)), dim3(TN_THREADS), S::TOTAL, s>>>(j0, j1);
+    skinny_tn_kernel<LONG, RANK, NS, GRADIENTS><<<dim3((unsigned)(j0.grid * j0.slabs + j1.grid * j1.slabs)), dim3(tn_threads(LONG, RANK)), S::TOTAL, s>>>(j0, j1);
     if ((e = hipGetLastError()) != hipSuccess || (j0.slabs <= 1 && j1.slabs <= 1)) return e;
     auto sum = [](const SkinnyJob& j) {
         return j.slabs > 1 ? SkinnySum{(const f32x4*)j.sums, j.slabs, (int64_t)j.A.rows * j.B.rows / 4, (u32x2*)j.out} : SkinnySum{};
