@@ -43,13 +43,18 @@ __device__ __forceinline__ void fetch_arguments(T... args) {
 //    (a chunk's tiles share 8 + 4 operand panels in the XCD's L2), chunk after chunk, numbered so
 //    that eight consecutive chunks form a 16 x 16 patch (2 x 4 chunks; the chip then shares 16 + 16
 //    panels in the last-level cache), patch after patch along n, then along m; then the rows that
-//    are left below it, column by column (32 positions: their few rows of 8 or more columns); then
-//    the columns left beside it, row by row.  What is left of the order after the last whole round of 256 is dealt
+//    are left below it, column by column (32 positions: their few rows of some columns); then
+//    the columns left beside it, row by row.  A strip of up to three rows or columns takes the last of several rows or columns of chunks along:
+//    by itself its 32 positions would share few panels, and the long operand would come from memory for it once more.  (us, sparse
+//    products, strips by themselves / with the chunks, operands from memory: 16640 tokens, 5120 x 5120, 65 tiles wide, 465 / 456; 16640,
+//    4352 x 2048, 17 x 65, 189 / 182; 16800, 2048 x 5120 209 / 202; 9000, 4864 x 4096, 19 x 36, 197 / 189; 12500, 4608 x 4608, 18 x 49, 288 / 284;
+//    16384, 4352 x 4352 331 / 336; weight gradients within 1 %.  Not a single row of chunks, whose columns of 9 to 11 are high: 16384,
+//    2560 x 2048 100 / 107, x 4096 202 / 197, x 10240 426 / 438.)  What is left of the order after the last whole round of 256 is dealt
 //    out in eight equal runs.
 //  * A narrow grid (skinny products, inference-size batches): tiles are numbered short axis first
 //    and each XCD takes runs of consecutive tiles: at most 32, sized so that all 8 XCDs get equal
 //    shares in every round, also when there are fewer than 256 tiles.
-constexpr int CHUNK_M = 8, CHUNK_N = 4;
+constexpr int CHUNK_M = 8, CHUNK_N = 4, THIN = 3;
 
 __host__ __device__ inline int narrow_run(int tiles) {
     int rounds = (tiles + RESIDENT - 1) / RESIDENT;        // even shares in every round, the last included
@@ -60,14 +65,11 @@ __host__ __device__ inline int narrow_run(int tiles) {
 __host__ __device__ inline bool wide_grid(int tiles_m, int tiles_n) {
     return tiles_m >= CHUNK_M && tiles_n >= CHUNK_N && (int64_t)tiles_m * tiles_n >= RESIDENT;
 }
-// the tile belongs to a whole 8 x 4 chunk of a wide grid: then the 32 tiles its XCD holds with it are that chunk
-__host__ __device__ inline bool in_whole_chunk(int tm, int tn, int tiles_m, int tiles_n) {
-    return wide_grid(tiles_m, tiles_n) && tm < tiles_m / CHUNK_M * CHUNK_M && tn < tiles_n / CHUNK_N * CHUNK_N;
-}
-
 // position q (0 <= q < tiles_m * tiles_n) in the order of a wide grid -> tile
 __host__ __device__ inline void tile_of_position(int q, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int m8 = tiles_m / CHUNK_M * CHUNK_M, n4 = tiles_n / CHUNK_N * CHUNK_N;
+    int m8 = tiles_m / CHUNK_M * CHUNK_M, n4 = tiles_n / CHUNK_N * CHUNK_N;
+    if (m8 < tiles_m && tiles_m - m8 <= THIN && m8 >= 2 * CHUNK_M) m8 -= CHUNK_M;
+    if (n4 < tiles_n && tiles_n - n4 <= THIN && n4 >= 2 * CHUNK_N) n4 -= CHUNK_N;
     if (q < m8 * n4) {
         const int c = q / 32, w = q % 32;
         const int chunks_m = m8 / CHUNK_M, chunks_n = n4 / CHUNK_N;

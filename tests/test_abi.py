@@ -309,3 +309,16 @@ def test_tile_order_of_wide_grids_has_no_gaps(tiles_m, tiles_n):
     assert last.size == -(-(tiles - whole) // 8) * 8
     per_xcd = np.array([(last[x::8] >= 0).sum() for x in range(8)])
     assert per_xcd.sum() == tiles - whole and per_xcd.max() - per_xcd.min() <= per_xcd.max() and per_xcd.max() <= -(-(tiles - whole) // 8)
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n", [(17, 16), (17, 65), (18, 17), (19, 19), (40, 9), (16, 65), (36, 66), (8, 67), (8, 33)])
+def test_tile_order_thin_strips_share_panels(tiles_m, tiles_n):
+    """The 32 consecutive positions that an XCD holds touch about as few panels where a strip of up to three rows or columns is left."""
+    tm, tn = sl.slope_tile_order(tiles_m, tiles_n)
+    whole = tiles_m * tiles_n // 256 * 256
+    assert whole
+    for block in range(0, whole, 256):
+        for xcd in range(8):
+            mine = range(block + xcd, block + 256, 8)
+            panels = len({tm[b] for b in mine}) + len({tn[b] for b in mine})
+            assert panels <= 20, (block, xcd, panels)      # a strip one tile high by itself: 33
