@@ -139,7 +139,10 @@ inline int super_grid(int tiles_m, int tiles_n) {
 // end only feed accumulators that are never stored, so any valid row will do; they are spread over
 // the operand (row % rows) rather than clamped to the last row, which would make that one row's
 // lines a hot spot of the L2 channel they live in (a ragged token tile ran 25 % slower that way).
-__device__ __forceinline__ int wrap_row(int row, int rows) { return row < rows ? row : row % rows; }
+__device__ __forceinline__ int wrap_row(int row, int rows) {
+    if (row >= rows) row = row - rows < rows ? row - rows : row % rows;   // (no division where the operand has half a tile's rows)
+    return row;
+}
 
 // 64 lanes x 16 bytes: lane l's bytes land at lds_dst + 16 * l; lds_dst is wave-uniform
 __device__ __forceinline__ void dma16(const void* gsrc, uint8_t* lds_dst) {

@@ -784,7 +784,7 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
     constexpr int META_PAIRS = S::META_PAIRS;
     constexpr int WM = BM == 128 && BN == 128 ? 2 : 4, WN = 8 / WM;    // wavefronts over the tile: the squarest fragments
     constexpr int MF = BM / (16 * WM), NF = BN / (16 * WN);
-    constexpr int A_LD = BM / (8 * LOADERS), B_LD = BN / (4 * LOADERS);   // 1 KiB loads per loading wavefront and pair
+    constexpr int A_LD = BM / (8 * LOADERS), B_LD = BN / (8 * LOADERS);   // 1 KiB loads per loading wavefront: of a pair, of a k-step
     constexpr int M_LOADS = S::M_BLOCK / 1024, M_LD = (M_LOADS + LOADERS - 1) / LOADERS;   // per block; some twice where need be
     static_assert(BM % 64 == 0 && BN % 32 == 0 && BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "whole loads and fragments");
     extern __shared__ __align__(16) uint8_t smem[];
@@ -814,56 +814,63 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
 
     if (wave >= 8) {                                          // (a wavefront that has ended does not count at barriers)
         const int loader = wave - 8;
-        // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8
+        // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8; the tokens' two k-steps are the same rows
         const uint8_t* a_src[A_LD];
+        const uint8_t* b_src[B_LD];
+        const uint8_t* m_src[M_LD];
+        int m_pair[M_LD], m_dst[M_LD];                        // pair inside the block; LDS offset inside it
+        auto load_a = [&](int i, int p, uint8_t* st) { dma16(a_src[i] + pair_offset<TAIL>(p, ksteps), st + (loader * A_LD + i) * 1024); };
+        auto load_b = [&](int i, int p, uint8_t* st) {
+            uint8_t* const dst = st + S::A_STAGE + (loader * B_LD + i) * 1024;
+            dma16(b_src[i] + (size_t)p * 256, dst);
+            dma16(b_src[i] + (size_t)p * 256 + (!TAIL || 2 * p + 1 < ksteps ? 128 : 0), dst + S::B_STEP);
+        };
+        auto load_m = [&](int i, int p) {
+            const int64_t off = (int64_t)(p + m_pair[i]) * 16, last = (int64_t)ksteps * 8 - 16;
+            dma16(m_src[i] + (off < last ? off : last), smem + m_dst[i] + (p / META_PAIRS & 1) * S::M_BLOCK);
+        };
+        // Each address is followed by its load of the first pair, so that those are on their way while the next ones are made (us, from
+        // memory, all addresses first / so: 46 tokens, 8256 x 8448 in five slabs of 192 x 64 21.4 / 20.2; 700, 4160 x 2112 16.0 / 15.3; 1114, 1600
+        // x 704 7.5 / 7.2)
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
             const int rl = (loader * A_LD + i) * 8 + (lane >> 3);
             a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
+            load_a(i, 0, smem);
         }
-        const uint8_t* b_src[B_LD];
-        int b_step[B_LD];                                         // which k-step of the pair (wave-uniform)
 #pragma unroll
         for (int i = 0; i < B_LD; ++i) {
-            const int j = loader * B_LD + i, rl = j % (BN / 8) * 8 + (lane >> 3);
-            b_step[i] = j / (BN / 8);
+            const int rl = (loader * B_LD + i) * 8 + (lane >> 3);
             b_src[i] = (const uint8_t*)B + (size_t)wrap_row(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
+            load_b(i, 0, smem);
         }
-        const uint8_t* m_src[M_LD];
-        int m_pair[M_LD], m_dst[M_LD];                            // pair inside the block; LDS offset inside it
 #pragma unroll
         for (int i = 0; i < M_LD; ++i) {
             const int idx = (loader * M_LD + i) % M_LOADS, rl = (idx * 64 + lane) / META_PAIRS;
             m_src[i] = Am + (size_t)wrap_row(m0 + rl, m) * (K / 8) + (size_t)k_first * 8;
             m_pair[i] = (lane % META_PAIRS) ^ (rl * META_PAIRS / 16 % META_PAIRS);
             m_dst[i] = S::M_OFF + idx * 1024;
+            load_m(i, 0);
         }
-        auto issue = [&](int p, int stage, bool new_block) {      // loads of pair p (inside the contraction, at least in part)
+        auto issue = [&](int p, int stage, bool new_block) {  // loads of pair p (inside the contraction, at least in part)
             uint8_t* const st = smem + stage * S::STAGE;
             if (new_block) {
 #pragma unroll
-                for (int i = 0; i < M_LD; ++i) {
-                    const int64_t off = (int64_t)(p + m_pair[i]) * 16, last = (int64_t)ksteps * 8 - 16;
-                    dma16(m_src[i] + (off < last ? off : last), smem + m_dst[i] + (p / META_PAIRS & 1) * S::M_BLOCK);
-                }
+                for (int i = 0; i < M_LD; ++i) load_m(i, p);
             }
-            const int64_t a_off = pair_offset<TAIL>(p, ksteps);
 #pragma unroll
-            for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + a_off, st + (loader * A_LD + i) * 1024);
+            for (int i = 0; i < A_LD; ++i) load_a(i, p, st);
 #pragma unroll
-            for (int i = 0; i < B_LD; ++i) {
-                const int k = 2 * p + b_step[i], kc = !TAIL || k < ksteps ? k : ksteps - 1;
-                dma16(b_src[i] + (size_t)kc * 128, st + S::A_STAGE + (loader * B_LD + i) * 1024);
-            }
+            for (int i = 0; i < B_LD; ++i) load_b(i, p, st);
         };
 #pragma unroll
-        for (int p = 0; p < S::STAGES - 1; ++p)
+        for (int p = 1; p < S::STAGES - 1; ++p)
             if (p < pairs) issue(p, p, p % META_PAIRS == 0);
         int stage = S::STAGES - 1;
         // pair p, with index u in its block of metadata, has landed (in the last STAGES - 2 pairs there are fewer loads behind it: then
         // all are waited for) and everybody has read the one before it, whose stage is filled again
         auto pair = [&](int p, auto index) {
-            constexpr int u = decltype(index)::value, leave = ring_leave<S>(u, A_LD + B_LD, M_LD);
+            constexpr int u = decltype(index)::value, leave = ring_leave<S>(u, A_LD + 2 * B_LD, M_LD);
             if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 15));
             else WAIT_HERE(waitcnt_imm(0, 15));
             wg_barrier();

@@ -209,22 +209,31 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
         constexpr int EACH = 8 / TN_LOADERS;                  // a loader has the loads of so many of the wavefronts
         DenseLoader<AKM, BKM, BM, BM / 2> la[EACH];
         DenseLoader<BKM, AKM, BN, BN / 4> lb[EACH];
+        auto load_a = [&](int v, int ks, int at) {
 #pragma unroll
-        for (int v = 0; v < EACH; ++v) {
-            la[v].init(At, m0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
-            lb[v].init(Bt, n0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
-        }
+            for (int i = 0; i < LD_A; ++i) la[v].load(ks, i, smem, at, wave - 8 + v * TN_LOADERS);
+        };
+        auto load_b = [&](int v, int ks, int at) {
+#pragma unroll
+            for (int i = 0; i < LD_B; ++i) lb[v].load(ks, i, smem, at + S::A_BYTES, wave - 8 + v * TN_LOADERS);
+        };
         auto issue = [&](int ks, int at) {
 #pragma unroll
             for (int v = 0; v < EACH; ++v) {
-#pragma unroll
-                for (int i = 0; i < LD_A; ++i) la[v].load(ks, i, smem, at, wave - 8 + v * TN_LOADERS);
-#pragma unroll
-                for (int i = 0; i < LD_B; ++i) lb[v].load(ks, i, smem, at + S::A_BYTES, wave - 8 + v * TN_LOADERS);
+                load_a(v, ks, at);
+                load_b(v, ks, at);
             }
         };
+        // the loads of the first k-step are on their way while the next addresses are made
 #pragma unroll
-        for (int p = 0; p < NS - 1; ++p)
+        for (int v = 0; v < EACH; ++v) {
+            la[v].init(At, m0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
+            load_a(v, k_begin, 0);
+            lb[v].init(Bt, n0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
+            load_b(v, k_begin, 0);
+        }
+#pragma unroll
+        for (int p = 1; p < NS - 1; ++p)
             if (k_begin + p < k_end) issue(k_begin + p, p * S::STAGE);
         int at = LAST;
         for (int ks = k_begin; ks < k_end; ++ks) {
