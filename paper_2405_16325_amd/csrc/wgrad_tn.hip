@@ -84,13 +84,18 @@ struct TnSmem {
     static constexpr int TOTAL = NS * STAGE;                       // ring of NS stages
 };
 
-constexpr int TN_THREADS = 512;                              // the wavefronts that multiply
-// Tiles up to 128 x 128 have four more that only load (why: spmm_ring_kernel), and load nothing past the end.  us, loads by the
-// eight / by four of their own: dW of 1024 x 1024 over 4096 tokens on 64 x 64 18.7 / 17.4, 3072 x 768 over 2048 on 128 x 128 19.8 / 19.1;
-// masked dense 2000 x 1928 over 2048 on 128 x 128 18.9 / 18.3; the gradients of 3136 x 896, rank 64 over 14376 tokens 163.9 / 157.3.
-// 192 x 128, whose loads are spread among its products: 65.3 / 66.4 (dW of 4096 x 3000 over 3064 tokens).
+constexpr int TN_THREADS = 512;
+// Wavefronts of a tile.  Up to 128 x 128 four of them only load (why: spmm_ring_kernel), and load nothing past the end: us, loads by
+// the eight that multiply / by four of their own: dW of 1024 x 1024 over 4096 tokens on 64 x 64 18.7 / 17.4, 3072 x 768 over 2048 on
+// 128 x 128 19.8 / 19.1; masked dense 2000 x 1928 over 2048 on 128 x 128 18.9 / 18.3; the gradients of 3136 x 896, rank 64 over 14376 tokens
+// 163.9 / 157.3.  192 x 128, whose loads are spread among its products: 65.3 / 66.4 (dW of 4096 x 3000 over 3064 tokens).
+// Up to 64 x 128 four multiply, with twice as many products for their reads, a third fewer bytes from LDS in all, and workgroups as large
+// as before: eight / four, from memory: dW of 1024 x 1024 over 4096 tokens 18.0 / 17.2, masked dense 704 x 768 over 518 5.3 / 5.0, the
+// gradients of 4096 x 1024, rank 128 over 2000 tokens 41.5 / 40.8; on 128 x 128 k-contiguous 3 % faster, k-major 3 % slower.
 constexpr int TN_LOADERS = 4;
-constexpr int tn_threads(int bm, int bn) { return TN_THREADS + (bm * bn <= 128 * 128 ? TN_LOADERS * 64 : 0); }
+constexpr int tn_loaders(int bm, int bn) { return bm * bn <= 128 * 128 ? TN_LOADERS : 0; }
+constexpr int tn_mult(int bm, int bn) { return bm * bn <= 64 * 128 ? 4 : 8; }
+constexpr int tn_threads(int bm, int bn) { return 64 * (tn_mult(bm, bn) + tn_loaders(bm, bn)); }
 enum { EPI_MASKED_PACKED = 0, EPI_PLAIN = 1 };
 
 // Metadata of the 32 Q columns of W^R from c (a multiple of 32) of row o, by dwords; columns outside the matrix: any.  The dwords of
@@ -116,7 +121,7 @@ __device__ __forceinline__ void load_meta(const uint8_t* __restrict__ meta, int 
 // 4-byte piece and an instruction touches sixteen rows; so the workgroup's tile of pairs goes through LDS
 // (the rings are idle) as [d_out row][pair] and leaves in whole rows, 16 bytes per lane.
 // BMT x BNT = the workgroup's tile (d_in x d_out) at (tile_c0, tile_o0); every thread must make the call.
-template <int MF, int NF, int BMT, int BNT>
+template <int MF, int NF, int BMT, int BNT, int THREADS>
 __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], int m, int n, int c0, int o0,
                                                     int tile_c0, int tile_o0, int l16, int lq,
                                                     const uint8_t* __restrict__ meta, bf16_t* __restrict__ out,
@@ -149,24 +154,24 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
     __syncthreads();
     // 16-byte pieces (four pairs = sixteen columns of W), all read from LDS before the first is stored; the last of a row that is not
     // a multiple of 16 columns is a half one
-    constexpr int PPR = BMT / 16, PIECES = BNT * PPR, PER_THREAD = (PIECES + TN_THREADS - 1) / TN_THREADS;
-    constexpr bool EVEN = PIECES % TN_THREADS == 0;           // else the last round of pieces is for the first threads only
+    constexpr int PPR = BMT / 16, PIECES = BNT * PPR, PER_THREAD = (PIECES + THREADS - 1) / THREADS;
+    constexpr bool EVEN = PIECES % THREADS == 0;           // else the last round of pieces is for the first threads only
     u32x4 piece[PER_THREAD];
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
-        const int idx = (int)threadIdx.x + u * TN_THREADS;
+        const int idx = (int)threadIdx.x + u * THREADS;
         if (EVEN || idx < PIECES) piece[u] = *(const u32x4*)(smem + (idx / PPR) * CP + (idx % PPR) * 16);
     }
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
-        const int idx = (int)threadIdx.x + u * TN_THREADS;
+        const int idx = (int)threadIdx.x + u * THREADS;
         const int o = tile_o0 + idx / PPR, col = tile_c0 + (idx % PPR) * 16;
         if ((EVEN || idx < PIECES) && o < n && col + 16 <= m) *(u32x4_a8*)(out + (size_t)o * gpitch + (col >> 1)) = piece[u];
     }
     if (m % 16 == 0) return;                                  // uniform
 #pragma unroll
     for (int u = 0; u < PER_THREAD; ++u) {
-        const int idx = (int)threadIdx.x + u * TN_THREADS;
+        const int idx = (int)threadIdx.x + u * THREADS;
         const int o = tile_o0 + idx / PPR, col = tile_c0 + (idx % PPR) * 16;
         if ((EVEN || idx < PIECES) && o < n && col + 8 == m) *(u32x2*)(out + (size_t)o * gpitch + (col >> 1)) = (u32x2){piece[u][0], piece[u][1]};
     }
@@ -192,30 +197,31 @@ __device__ __forceinline__ void store_sums(const f32x4 (&acc)[MF][NF], int m, in
 // all (the look-ahead past a slab's end reads real, unused data).  AKM, BKM: the operand is k-major.
 // NS = ring depth: loads run NS - 1 k-steps ahead.  Two stages are all that fits beside a 256 x 256
 // tile; small tiles (memory-bound skinny products) take a deeper ring to cover the HBM latency.
-// Every thread of the workgroup must make the call; wavefront w holds the fragments at rows w % 2 * BM / 2, columns w / 2 * BN / 4.
+// Every thread of the workgroup must make the call; wavefront w holds the fragments at rows w % 2 * BM / 2, columns w / 2 * WROWS.
 // False: a wavefront that has only loaded, and is done.
 template <int BM, int BN, int NS, bool AKM, bool BKM>
 __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const DenseOperand& Bt, int ksteps, int k_begin, int k_end, int m0,
-                                              int n0, uint8_t* smem, f32x4 (&acc)[BM / 32][BN / 64]) {
+                                              int n0, uint8_t* smem, f32x4 (&acc)[BM / 32][BN / (8 * tn_mult(BM, BN))]) {
     using S = TnSmem<BM, BN, NS>;
-    constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront (2 x 4 waves)
+    constexpr int MULT = tn_mult(BM, BN), WROWS = BN / (MULT / 2);
+    constexpr int MF = BM / 32, NF = WROWS / 16;             // 16 x 16 fragments per wavefront (2 x 4 or 2 x 2 waves)
     constexpr int LD_A = BM / 64, LD_B = BN / 64;            // 1 KiB loads per wavefront per step
     constexpr int AHEAD = (NS - 2) * (LD_A + LD_B);          // loads that may stay in flight at a wait
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    constexpr bool LOADERS = tn_threads(BM, BN) != TN_THREADS;
+    constexpr bool LOADERS = tn_loaders(BM, BN) != 0;
     constexpr int LAST = (NS - 1) * S::STAGE;
-    if (LOADERS && wave >= 8) {
+    if (LOADERS && wave >= MULT) {
         constexpr int EACH = 8 / TN_LOADERS;                  // a loader has the loads of so many of the wavefronts
         DenseLoader<AKM, BKM, BM, BM / 2> la[EACH];
-        DenseLoader<BKM, AKM, BN, BN / 4> lb[EACH];
+        DenseLoader<BKM, AKM, BN, WROWS> lb[EACH];
         auto load_a = [&](int v, int ks, int at) {
 #pragma unroll
-            for (int i = 0; i < LD_A; ++i) la[v].load(ks, i, smem, at, wave - 8 + v * TN_LOADERS);
+            for (int i = 0; i < LD_A; ++i) la[v].load(ks, i, smem, at, wave - MULT + v * TN_LOADERS);
         };
         auto load_b = [&](int v, int ks, int at) {
 #pragma unroll
-            for (int i = 0; i < LD_B; ++i) lb[v].load(ks, i, smem, at + S::A_BYTES, wave - 8 + v * TN_LOADERS);
+            for (int i = 0; i < LD_B; ++i) lb[v].load(ks, i, smem, at + S::A_BYTES, wave - MULT + v * TN_LOADERS);
         };
         auto issue = [&](int ks, int at) {
 #pragma unroll
@@ -227,9 +233,9 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
         // the loads of the first k-step are on their way while the next addresses are made
 #pragma unroll
         for (int v = 0; v < EACH; ++v) {
-            la[v].init(At, m0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
+            la[v].init(At, m0, 0, wave - MULT + v * TN_LOADERS, lane, 0, ksteps, smem);
             load_a(v, k_begin, 0);
-            lb[v].init(Bt, n0, 0, wave - 8 + v * TN_LOADERS, lane, 0, ksteps, smem);
+            lb[v].init(Bt, n0, 0, wave - MULT + v * TN_LOADERS, lane, 0, ksteps, smem);
             load_b(v, k_begin, 0);
         }
 #pragma unroll
@@ -248,9 +254,9 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
         return false;
     }
     DenseLoader<AKM, BKM, BM, BM / 2> opa;
-    DenseLoader<BKM, AKM, BN, BN / 4> opb;
+    DenseLoader<BKM, AKM, BN, WROWS> opb;
     opa.init(At, m0, (wave & 1) * (BM / 2), wave, lane, 0, ksteps, smem);
-    opb.init(Bt, n0, (wave >> 1) * (BN / 4), wave, lane, 0, ksteps, smem);
+    opb.init(Bt, n0, (wave >> 1) * WROWS, wave, lane, 0, ksteps, smem);
     auto issue = [&](int ks, int at) {                       // k-step ks (clamped) into the stage at byte `at`
 #pragma unroll
         for (int i = 0; i < LD_A; ++i) opa.load(ks, i, smem, at, wave);
@@ -405,22 +411,22 @@ template <int BM, int BN, int EPI, int NS, bool AKM, bool BKM>
 __global__ void __launch_bounds__(tn_threads(BM, BN)) dense_tn_kernel(DenseOperand At, DenseOperand Bt, int ksteps, const uint8_t* __restrict__ meta,
                                                               bf16_t* __restrict__ out, int tiles_m, int tiles_n) {
     using S = TnSmem<BM, BN, NS>;
-    constexpr int MF = BM / 32, NF = BN / 64;
+    constexpr int MULT = tn_mult(BM, BN), MF = BM / 32, NF = BN / (8 * MULT);
     extern __shared__ __align__(16) uint8_t smem[];
     fetch_arguments(At.p, At.rows, At.ld, At.k, Bt.p, Bt.rows, Bt.ld, Bt.k, ksteps, meta, out, tiles_m, tiles_n);
     int tm, tn;
     if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
     const int m0 = tm * BM, n0 = tn * BN, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / 4);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / (MULT / 2));
     const int m = At.rows, n = Bt.rows;
     f32x4 acc[MF][NF];
     if (!dense_tn_sums<BM, BN, NS, AKM, BKM>(At, Bt, ksteps, 0, ksteps, m0, n0, smem, acc)) return;
     if constexpr (EPI == EPI_PLAIN) {
         static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
-        store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, m, n, l16, lq, out, smem, m0, n0);
+        store_rows<MF, NF, BM, BN, 64 * MULT>(acc, mw, nw, m, n, l16, lq, out, smem, m0, n0);
     } else {
         static_assert(BN * (BM + 16) <= S::TOTAL, "the staged tile of pairs fits in the ring");
-        store_masked_packed<MF, NF, BM, BN>(acc, m, n, mw, nw, m0, n0, l16, lq, meta, out, smem);
+        store_masked_packed<MF, NF, BM, BN, 64 * MULT>(acc, m, n, mw, nw, m0, n0, l16, lq, meta, out, smem);
     }
 }
 
@@ -440,18 +446,18 @@ struct SkinnyJob {
 template <int BM, int BN, int NS, bool AKM, bool BKM>
 __device__ __forceinline__ void skinny_tn_tile(const SkinnyJob& j, int w, uint8_t* smem) {
     using S = TnSmem<BM, BN, NS>;
-    constexpr int MF = BM / 32, NF = BN / 64;
+    constexpr int MULT = tn_mult(BM, BN), MF = BM / 32, NF = BN / (8 * MULT);
     const int slab = w / j.grid, m = j.A.rows, n = j.B.rows;
     int tm, tn;
     if (!tile_of_index(w % j.grid, j.tiles_m, j.tiles_n, tm, tn)) return;
     const int m0 = tm * BM, n0 = tn * BN, lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / 4);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), mw = m0 + (wave & 1) * (BM / 2), nw = n0 + (wave >> 1) * (BN / (MULT / 2));
     const int k_begin = slab * j.slab_steps, k_end = min(k_begin + j.slab_steps, j.ksteps);
     f32x4 acc[MF][NF];
     if (!dense_tn_sums<BM, BN, NS, AKM, BKM>(j.A, j.B, j.ksteps, k_begin, k_end, m0, n0, smem, acc)) return;
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the ring");
     if (j.slabs > 1) store_sums<MF, NF>(acc, m, n, mw, nw, l16, lq, j.sums + (size_t)slab * n * m);
-    else store_rows<MF, NF, BM, BN, TN_THREADS>(acc, mw, nw, m, n, l16, lq, j.out, smem, m0, n0);
+    else store_rows<MF, NF, BM, BN, 64 * MULT>(acc, mw, nw, m, n, l16, lq, j.out, smem, m0, n0);
 }
 
 template <int LONG, int RANK, int NS, bool GRADIENTS>
@@ -682,7 +688,7 @@ next_part:
     static_assert(S::BN * (S::BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
     if (EPI == EPI_PLAIN)
         store_rows<MF, NF, S::BM, S::BN, TN_THREADS>(acc, m0 + wm * WM, n0 + wn * NF * 16, m, n, l16, lq, out, smem, m0, n0);
-    else store_masked_packed<MF, NF, S::BM, S::BN>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out,
+    else store_masked_packed<MF, NF, S::BM, S::BN, TN_THREADS>(acc, m, n, m0 + wm * WM, n0 + wn * NF * 16, m0, n0, l16, lq, meta, out,
                                                    smem);
 }
 
