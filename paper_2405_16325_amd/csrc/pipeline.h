@@ -139,8 +139,10 @@ inline int super_grid(int tiles_m, int tiles_n) {
 // end only feed accumulators that are never stored, so any valid row will do; they are spread over
 // the operand (row % rows) rather than clamped to the last row, which would make that one row's
 // lines a hot spot of the L2 channel they live in (a ragged token tile ran 25 % slower that way).
-__device__ __forceinline__ int wrap_row(int row, int rows) {
-    if (row >= rows) row = row - rows < rows ? row - rows : row % rows;   // (no division where the operand has half a tile's rows)
+__device__ __forceinline__ int wrap_row(int row, int rows) { return row < rows ? row : row % rows; }
+// the same without a division where the operand has half a tile's rows, for wavefronts that make many addresses
+__device__ __forceinline__ int wrap_row_near(int row, int rows) {
+    if (row >= rows) row = row - rows < rows ? row - rows : row % rows;
     return row;
 }
 

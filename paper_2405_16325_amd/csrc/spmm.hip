@@ -728,18 +728,21 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 // spmm_ring_kernel: the smaller tiles, one barrier per pair of k-steps.  A tile of 128 x 64 gives a wavefront four MFMAs
 // per k-step, so a barrier per k-step, as above, would cost more than the k-step's loads (two of them took 0.35 us per
 // k-step beside what its loads take).  Here a ring stage holds a pair of k-steps of both operands (the packed values come in
-// pairs anyway, 128 bytes per row).  Eight wavefronts, per pair, read the second k-step's fragments, multiply the first, pass the barrier,
+// pairs anyway, 128 bytes per row).  Four wavefronts, per pair, read the second k-step's fragments, multiply the first, pass the barrier,
 // read the next pair's first k-step and multiply the second, so that no product waits for the reads of its own k-step.
-// LOADERS more, one per SIMD, only load: wait for their loads of the next pair, pass the barrier and queue the loads that refill the
+// Four more, one per SIMD as well, only load: wait for their loads of the next pair, pass the barrier and queue the loads that refill the
 // stage everybody has left.  Three to four stages keep two or three pairs (34 to 50 KB each) on the way, and the operand feed
 // bounds the kernel.
 // A wavefront that queues loads stands still until the address unit, 64 bytes per cycle for the whole compute unit, has taken them: where
 // the multiplying ones did it, after the barrier, the last of them began their products some hundred cycles late (1000 tokens, 4352 x
 // 4352: of 940 cycles per k-step four of the wavefronts spent 390 at the barrier, waiting for the other four; 50 for loads).  us, operands
-// in the last-level cache and from HBM, loads by the eight / by four of their own: 700 tokens, 4160 x 2112 on 192 x 64 17.0 / 15.1 and 17.1
-// / 15.3; 1000, 4352 x 4352 on 192 x 96 32.4 / 29.1 and 37.5 / 35.4; 1500, 2040 x 4096 on 128 x 96 22.2 / 20.1 and 22.3 / 20.3; 2048, 768 x
-// 3072 on 128 x 64 13.2 / 12.5.  Two loaders: 2 to 7 % slower than four; four of higher priority: 0 to 4 %.  The kernel above, whose loads
-// are spread among its products, gains nothing by it.
+// in the last-level cache and from HBM, eight that load and multiply / eight that multiply and four that load: 700 tokens, 4160 x 2112 on
+// 192 x 64 17.0 / 15.1 and 17.1 / 15.3; 1000, 4352 x 4352 on 192 x 96 32.4 / 29.1 and 37.5 / 35.4; 1500, 2040 x 4096 on 128 x 96 22.2 / 20.1 and
+// 22.3 / 20.3; 2048, 768 x 3072 on 128 x 64 13.2 / 12.5.  Two loaders: 2 to 7 % slower than four; four of higher priority: 0 to 4 %.  The
+// kernel above, whose loads are spread among its products, gains nothing by it.
+// Four that multiply have a quarter of the tile each, a third fewer bytes from LDS in all than eight, and the workgroup starts faster (us, from
+// memory, eight / four and four loaders: 1000 tokens, 4352 x 4352 30.4 / 29.7; 1114, 704 x 1600 9.9 / 9.5; 875, 1536 x 768 6.8 / 6.6, without
+// loaders 6.7; 2000, 1920 x 2048 15.4 / 15.1; 424, 1792 x 3584 in slabs 14.4 / 14.2; 300, 9216 x 4096 20.9 / 21.5).
 // (Reads a k-step ahead of their products, against products that follow their reads: 2048 tokens, 768 x 3072 on 128 x 64 16.9
 // -> 15.7 us, on 128 x 128 23.3 -> 20.8; 300, 9216 x 4096 on 192 x 64 26.7 -> 23.8.)
 // Metadata: META_PAIRS pairs (16 bytes each) per row at a time, as many neighbouring lanes per row, the pieces of a row
@@ -771,7 +774,7 @@ constexpr int ring_leave(int u, int each, int meta) {
 
 // TAIL: an odd number of k-steps; the values and metadata of the last one are then fetched as the second half of a pair that
 // ends with the row (see spmm_kernel).
-constexpr int LOADERS = 4, RING_THREADS = SPMM_THREADS + 64 * LOADERS;
+constexpr int LOADERS = 4, RING_MULT = 4, RING_THREADS = 64 * (RING_MULT + LOADERS);
 template <int BM, int BN, bool TAIL, class Job>
 __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* __restrict__ B, int n,
                                                                  const bf16_t* __restrict__ Av,
@@ -782,7 +785,7 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
                                                                  Job job) {
     using S = RingSmem<BM, BN>;
     constexpr int META_PAIRS = S::META_PAIRS;
-    constexpr int WM = BM == 128 && BN == 128 ? 2 : 4, WN = 8 / WM;    // wavefronts over the tile: the squarest fragments
+    constexpr int WM = 2, WN = RING_MULT / WM;                // wavefronts over the tile
     constexpr int MF = BM / (16 * WM), NF = BN / (16 * WN);
     constexpr int A_LD = BM / (8 * LOADERS), B_LD = BN / (8 * LOADERS);   // 1 KiB loads per loading wavefront: of a pair, of a k-step
     constexpr int M_LOADS = S::M_BLOCK / 1024, M_LD = (M_LOADS + LOADERS - 1) / LOADERS;   // per block; some twice where need be
@@ -812,8 +815,8 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
     const int ksteps = K / 64 - k_first > slab_steps ? slab_steps : K / 64 - k_first;
     const int pairs = (ksteps + 1) / 2;
 
-    if (wave >= 8) {                                          // (a wavefront that has ended does not count at barriers)
-        const int loader = wave - 8;
+    if (wave >= RING_MULT) {                                  // (a wavefront that has ended does not count at barriers)
+        const int loader = wave - RING_MULT;
         // ---- loader lanes: 8 lanes per row of 128 bytes, chunk rotated by (row / 2) % 8; the tokens' two k-steps are the same rows
         const uint8_t* a_src[A_LD];
         const uint8_t* b_src[B_LD];
@@ -835,19 +838,18 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
             const int rl = (loader * A_LD + i) * 8 + (lane >> 3);
-            a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
+            a_src[i] = (const uint8_t*)Av + (size_t)wrap_row_near(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
             load_a(i, 0, smem);
         }
 #pragma unroll
         for (int i = 0; i < B_LD; ++i) {
             const int rl = (loader * B_LD + i) * 8 + (lane >> 3);
-            b_src[i] = (const uint8_t*)B + (size_t)wrap_row(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
-            load_b(i, 0, smem);
+            b_src[i] = (const uint8_t*)B + (size_t)wrap_row_near(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
         }
 #pragma unroll
         for (int i = 0; i < M_LD; ++i) {
             const int idx = (loader * M_LD + i) % M_LOADS, rl = (idx * 64 + lane) / META_PAIRS;
-            m_src[i] = Am + (size_t)wrap_row(m0 + rl, m) * (K / 8) + (size_t)k_first * 8;
+            m_src[i] = Am + (size_t)wrap_row_near(m0 + rl, m) * (K / 8) + (size_t)k_first * 8;
             m_pair[i] = (lane % META_PAIRS) ^ (rl * META_PAIRS / 16 % META_PAIRS);
             m_dst[i] = S::M_OFF + idx * 1024;
             load_m(i, 0);
@@ -929,6 +931,14 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
             for (int j = 0; j < NF; ++j)
                 acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(f.af[i].v, f.bf[j].v, acc[i][j], f.ai[i], 0, 0);
     };
+    // The tokens of the first pair, which the loaders leave out: theirs are the weights (0.3 % less than all by the loaders in the mean)
+#pragma unroll
+    for (int i = 0; i < BN / (4 * RING_MULT); ++i) {
+        const int j = wave * (BN / (4 * RING_MULT)) + i, step = j / (BN / 8), rl = j % (BN / 8) * 8 + (lane >> 3);   // step: wave-uniform
+        dma16((const uint8_t*)B + (size_t)wrap_row_near(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128 +
+                  (step && (!TAIL || ksteps > 1) ? 128 : 0), smem + S::A_STAGE + j * 1024);
+    }
+    WAIT_HERE(waitcnt_imm(0, 15));
     // the loaders pass this when pair p has landed, the others when they have read what came before it
     auto landed = [&]() {
         WAIT_HERE(waitcnt_imm(63, 0));
@@ -965,7 +975,7 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
         }
     }
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL && 128 * (BM * 2 + 32) <= S::TOTAL, "the staged output tile and factor fit in the ring");
-    extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
+    extend_and_store<MF, NF, BM, BN, 64 * RING_MULT>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
                                                    slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
 }
 

@@ -210,9 +210,19 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     constexpr bool LOADERS = tn_loaders(BM, BN) != 0;
+    // The first k-steps' loads are shared out to eight as they would be without loaders, of whom the multiplying wavefronts are the first: four
+    // loaders alone took long to fill the ring (us, from memory, by themselves / so: masked dense 768 x 704 over 518 5.0 / 4.7, 576 x 1408 over
+    // 1625 7.8 / 7.5; dW of 1000 x 1000 over 1000 9.5 / 9.3, 1024 x 1024 over 4096 17.3 / 17.0; eight, no loaders: 5.0, 7.7, 9.3, 19.0)
+    constexpr int PRE = 3;                                    // (what `behind` is asked for knows)
     constexpr int LAST = (NS - 1) * S::STAGE;
     if (LOADERS && wave >= MULT) {
-        constexpr int EACH = 8 / TN_LOADERS;                  // a loader has the loads of so many of the wavefronts
+        constexpr int EACH = 8 / TN_LOADERS;                  // a loader has the loads of so many of the eight
+        // loads behind step k_begin + s, those of the NS - 2 steps after it
+        constexpr auto behind = [](int s) {
+            int c = 0;
+            for (int p = s + 1; p <= s + NS - 2; ++p) c += (LD_A + LD_B) * (p < PRE ? EACH - MULT / TN_LOADERS : EACH);
+            return c;
+        };
         DenseLoader<AKM, BKM, BM, BM / 2> la[EACH];
         DenseLoader<BKM, AKM, BN, WROWS> lb[EACH];
         auto load_a = [&](int v, int ks, int at) {
@@ -223,32 +233,32 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
 #pragma unroll
             for (int i = 0; i < LD_B; ++i) lb[v].load(ks, i, smem, at + S::A_BYTES, wave - MULT + v * TN_LOADERS);
         };
-        auto issue = [&](int ks, int at) {
+        auto issue = [&](int ks, int at, int from) {          // the loads of the eight from `from` on
 #pragma unroll
-            for (int v = 0; v < EACH; ++v) {
-                load_a(v, ks, at);
-                load_b(v, ks, at);
-            }
+            for (int v = 0; v < EACH; ++v)
+                if (v * TN_LOADERS >= from) {
+                    load_a(v, ks, at);
+                    load_b(v, ks, at);
+                }
         };
-        // the loads of the first k-step are on their way while the next addresses are made
 #pragma unroll
         for (int v = 0; v < EACH; ++v) {
             la[v].init(At, m0, 0, wave - MULT + v * TN_LOADERS, lane, 0, ksteps, smem);
-            load_a(v, k_begin, 0);
             lb[v].init(Bt, n0, 0, wave - MULT + v * TN_LOADERS, lane, 0, ksteps, smem);
-            load_b(v, k_begin, 0);
         }
 #pragma unroll
-        for (int p = 1; p < NS - 1; ++p)
-            if (k_begin + p < k_end) issue(k_begin + p, p * S::STAGE);
+        for (int p = 0; p < NS - 1; ++p)
+            if (k_begin + p < k_end) issue(k_begin + p, p * S::STAGE, p < PRE ? MULT : 0);
         int at = LAST;
         for (int ks = k_begin; ks < k_end; ++ks) {
             // step ks has landed (in the last NS - 2 steps there are fewer loads behind it: then all are waited for) and everybody has
             // read the one before it, whose stage is filled again
-            if (ks + NS - 2 < k_end) WAIT_HERE(waitcnt_imm(AHEAD * EACH, 15));
-            else WAIT_HERE(waitcnt_imm(0, 15));
+            if (ks + NS - 2 >= k_end) WAIT_HERE(waitcnt_imm(0, 15));
+            else if (ks == k_begin) WAIT_HERE(waitcnt_imm(behind(0), 15));
+            else if (ks == k_begin + 1) WAIT_HERE(waitcnt_imm(behind(1), 15));
+            else WAIT_HERE(waitcnt_imm(behind(2), 15));
             wg_barrier();
-            if (ks + NS - 1 < k_end) issue(ks + NS - 1, at);
+            if (ks + NS - 1 < k_end) issue(ks + NS - 1, at, 0);
             at = at == LAST ? 0 : at + S::STAGE;
         }
         return false;
@@ -273,7 +283,13 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
     // lane before every step's LDS reads (us, from HBM: 2048 x 1024 over 4096 on 64 x 128 30.5 -> 26.0, 704 x 2112 over 4160
     // 27.0 -> 22.2, 2048 x 1024 over 8192 51.8 -> 41.8); the 256 x 256 kernel, where registers are short, is 1 % slower this way.
     int at = 0;
-    if (!LOADERS) {
+    if (LOADERS) {
+#pragma unroll
+        for (int p = 0; p < PRE; ++p)
+            if (k_begin + p < k_end) issue(k_begin + p, p * S::STAGE);
+        if (k_begin + PRE - 1 < k_end) WAIT_HERE(waitcnt_imm((PRE - 1) * (LD_A + LD_B), 15));
+        else WAIT_HERE(waitcnt_imm(0, 15));
+    } else {
 #pragma unroll
         for (int p = 0; p < NS - 1; ++p) issue(k_begin + p, p * S::STAGE);
         WAIT_HERE(waitcnt_imm(AHEAD, 15));                    // the first step has landed (this wave's share)
@@ -387,8 +403,8 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
                 multiply(f1, std::integral_constant<int, 0>{}, [](int) {});
                 break;
             }
-            // this wavefront has read the stage, and its loads of the next one have landed
-            WAIT_HERE(waitcnt_imm(LOADERS ? 63 : AHEAD, 0));
+            // this wavefront has read the stage, and its loads of the next one (with loaders: of the first ones) have landed
+            WAIT_HERE(waitcnt_imm(LOADERS ? 0 : AHEAD, 0));
             wg_barrier();
             const int next = at == LAST ? 0 : at + S::STAGE;
             const auto sa = opa.stage(smem, next);            // (after the last k-step read and not used)
