@@ -30,8 +30,9 @@
 //     a time into two alternating pair buffers, and its metadata for eight k-steps at a time (four where LDS is short);
 //   - inside a row the eight 16-byte chunks are rotated by (row / 2) % 8, which makes the
 //     ds_read_b128 of the MFMA layout (16 lanes = 16 rows, same chunk) hit 16 different bank groups.
-// A workgroup owns a BM x BN tile of C with 8 wavefronts (2 x 4, two per SIMD), one barrier per k-step: while a wavefront
-// multiplies a k-step it reads the fragments of the next one and queues the loads of the third after it.  (Before, two groups of
+// A workgroup owns a BM x BN tile of C with 8 wavefronts, two per SIMD, all of which multiply (2 x 4) and load or four of which multiply
+// (2 x 2) while the others load (tile_mult); one barrier per k-step: while a wavefront
+// multiplies a k-step it reads the fragments of the next one, and the loads of the third after it are queued.  (Before, two groups of
 // wavefronts took turns at reading and multiplying, two barriers per k-step, which made a k-step at least twice a group's
 // LDS reads: the matrix pipes were busy a third of it.  us, operands in the last-level cache, before / now: 1000 tokens, 4352 x 4352 on
 // 192 x 128 40.1 / 35.0, on 256 x 128 43.6 / 39.2; 2048 tokens, 4352 x 4352 on 256 x 192 57.3 / 52.7, on 192 x 192 51.3 / 50.3; 330
@@ -72,32 +73,37 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
         const uint8_t* tr = smem + (8 * lq + (l16 >> 2)) * PITCH + 2 * (f0 - tile_f0 + 4 * (l16 & 3));
         // pieces of the staged chunk per thread: a compile-time count, so that all of a thread's global loads are
         // in flight together (a loop of load, wait, LDS store per piece pays the L2 latency once per piece)
-        constexpr int PER = 128 * SEG / THREADS;
-        static_assert(128 * SEG % THREADS == 0, "whole pieces per thread");
+        // (at most eight: the accumulators are most of the registers of a wavefront with a quarter of a large tile)
+        constexpr int PER = 128 * SEG / THREADS, ROUNDS = (PER + 7) / 8, EACH = PER / ROUNDS;
+        constexpr int FIRST = THREADS < 512 && MF * NF > 24 ? 0 : 2;   // steps whose token-side fragments are requested before the pieces
+        static_assert(128 * SEG % THREADS == 0 && PER % ROUNDS == 0, "whole pieces per thread and round");
         for (int kc = 0; kc < KR; kc += 128) {
             const int kn = KR - kc < 128 ? KR - kc : 128;     // a multiple of 32
             // the token-side fragments of the whole chunk come straight from global memory: requested first
             // (steps past the chunk's end re-read the first, unused)
             AFrag b2[4][NF];
 #pragma unroll
-            for (int st = 0; st < 2; ++st)
+            for (int st = 0; st < FIRST; ++st)
 #pragma unroll
                 for (int j = 0; j < NF; ++j) b2[st][j].u = *(const u32x4*)(b_row[j] + kc + (32 * st < kn ? 32 * st : 0));
-            u32x4 piece[PER];
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int idx = tid + u * THREADS, k = idx / SEG, col = tile_f0 + 8 * (idx % SEG);
-                piece[u] = (u32x4){0u, 0u, 0u, 0u};
-                if (k < kn && col < m) piece[u] = *(const u32x4*)(A2 + (size_t)(kc + k) * m + col);
+            for (int round = 0; round < ROUNDS; ++round) {
+                u32x4 piece[EACH];
+#pragma unroll
+                for (int u = 0; u < EACH; ++u) {
+                    const int idx = tid + (round * EACH + u) * THREADS, k = idx / SEG, col = tile_f0 + 8 * (idx % SEG);
+                    piece[u] = (u32x4){0u, 0u, 0u, 0u};
+                    if (k < kn && col < m) piece[u] = *(const u32x4*)(A2 + (size_t)(kc + k) * m + col);
+                }
+                if (round == 0) __syncthreads();              // the rings are drained / the last chunk is consumed
+#pragma unroll
+                for (int u = 0; u < EACH; ++u) {
+                    const int idx = tid + (round * EACH + u) * THREADS;
+                    *(u32x4*)(smem + (idx / SEG) * PITCH + (idx % SEG) * 16) = piece[u];
+                }
             }
-            __syncthreads();                                  // the rings are drained / the last chunk is consumed
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int idx = tid + u * THREADS;
-                *(u32x4*)(smem + (idx / SEG) * PITCH + (idx % SEG) * 16) = piece[u];
-            }
-#pragma unroll
-            for (int st = 2; st < 4; ++st)                    // in the registers the staged pieces have left
+            for (int st = FIRST; st < 4; ++st)                // in the registers the staged pieces have left
 #pragma unroll
                 for (int j = 0; j < NF; ++j) b2[st][j].u = *(const u32x4*)(b_row[j] + kc + (32 * st < kn ? 32 * st : 0));
             __syncthreads();
@@ -133,6 +139,7 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
             int row = t0 + j * 16 + l16;
             b_row[j] = B2 + (size_t)wrap_row(row, n) * K2 + lq * 8;
         }
+        constexpr int AHEAD = THREADS >= 512 || MF * NF <= 16 ? 1 : 0;   // as above: no room for the operands of two steps beside larger tiles' sums
         AFrag a2[2][MF], b2[2][NF];
 #pragma unroll
         for (int i = 0; i < MF; ++i) a2[0][i].u = *(const u32x4*)(a_row[i]);
@@ -143,11 +150,11 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
             for (int h = 0; h < 2; ++h) {
                 const int kk = k0 + 32 * h;                   // uniform
                 if (kk >= K2) break;
-                const int kn = kk + 32 < K2 ? kk + 32 : kk;   // the last step re-reads itself (unused)
+                const int kn = AHEAD && kk + 32 < K2 ? kk + 32 : kk;   // the last step re-reads itself (unused)
 #pragma unroll
-                for (int i = 0; i < MF; ++i) a2[h ^ 1][i].u = *(const u32x4*)(a_row[i] + kn);
+                for (int i = 0; i < MF; ++i) a2[h ^ AHEAD][i].u = *(const u32x4*)(a_row[i] + kn);
 #pragma unroll
-                for (int j = 0; j < NF; ++j) b2[h ^ 1][j].u = *(const u32x4*)(b_row[j] + kn);
+                for (int j = 0; j < NF; ++j) b2[h ^ AHEAD][j].u = *(const u32x4*)(b_row[j] + kn);
 #pragma unroll
                 for (int i = 0; i < MF; ++i)
 #pragma unroll
@@ -185,6 +192,15 @@ struct SpmmSmem {
 };
 
 constexpr int SPMM_THREADS = 512;
+// Wavefronts of a workgroup: RING_MULT that multiply and LOADERS that only load, in spmm_ring_kernel and on the tiles of spmm_kernel
+// where four wavefronts have registers for the sums; elsewhere eight that do both.  Four have a quarter of the tile each and read a third
+// fewer bytes from LDS in all, which with the loads' writes takes as long as the products (a k-step of 256 x 128: 105 KB read by eight
+// wavefronts, 69 by four, at 240 bytes per cycle, 35 written at 128, against 512 cycles of products).  us, from memory, eight / four: 2048
+// tokens, 4096 x 4096 on 256 x 128 42.0 / 38.7; 1500, 4352 x 4352 39.3 / 37.9; on 192 x 128 2040, 3000 x 6144 48.8 / 46.3, 3000 x 2048 21.1 / 20.0;
+// 2048, 3072 x 768 12.3 / 11.9; the input gradient of 2048, 4096 x 4096 with rank 64 59.0 / 53.1.  (256 x 128 with leftover k-steps, TAIL,
+// spills at the exits of its loop.)
+constexpr int LOADERS = 4, RING_MULT = 4, RING_THREADS = 64 * (RING_MULT + LOADERS);
+constexpr int tile_mult(int bm, int bn, bool tail) { return bm * bn <= (tail ? 192 : 256) * 128 ? RING_MULT : 8; }
 
 // Where a row's loads of pair `pair` (of k-steps) start, in bytes of packed values.  Past the last k-step the last load of the row
 // is repeated.
@@ -239,7 +255,7 @@ __device__ __forceinline__ bool split_item(const SplitJob& job, const bf16_t* __
         const int id = (pos - run) * XCDS + xcd;
         const int xl_tiles_r = (job.r + SK_BJ - 1) / SK_BJ, xl_tiles = xl_tiles_r * ((n + SK_BI - 1) / SK_BI);
         const int part = id / xl_tiles, tile = id % xl_tiles;
-        if (part < job.xl_slabs && (int)threadIdx.x < SK_WAVES * 64)     // (the ring kernel's workgroups have more wavefronts)
+        if (part < job.xl_slabs)
             skinny_tile<false, true>(B, K, job.L, job.r, n, job.r, part * (uint32_t)job.k_per,
                                      min((uint32_t)K, (part + 1) * (uint32_t)job.k_per), tile / xl_tiles_r * SK_BI,
                                      tile % xl_tiles_r * SK_BJ, nullptr, job.Q + (size_t)part * n * job.r, smem);
@@ -297,6 +313,89 @@ __device__ __forceinline__ bool tile_of(const Leftover& left, int m, int n, int 
     return leftover_tile<BM, BN>((int)blockIdx.x, left, tm, tn) && tm * BM < m && tn * BN < n;   // (parts past the edge of a ragged tile)
 }
 
+// The loads of spmm_kernel, by all eight wavefronts (ALL) or by LOADERS of them.
+template <int BM, int BN, bool TAIL, bool ALL>
+struct SpmmLoads {
+    using S = SpmmSmem<BM, BN>;
+    using ML = MetaLanes<S::META_STEPS>;
+    static constexpr int LW = ALL ? 8 : LOADERS, A_LD = BM / (8 * LW), B_LD = BN / (8 * LW);   // 1 KiB loads per wavefront: per pair, per step
+    static constexpr int M_LD = 8 / LW, M_ALL = ML::PARTS * M_LD;                             // per quad of k-steps, per block of metadata
+    static constexpr int step_loads(int S4) { return B_LD + (S4 & 1) * A_LD + (S4 == 0) * M_LD; }
+    const uint8_t* a_src[A_LD];
+    const uint8_t* b_src[B_LD];
+    const uint8_t* m_src[M_ALL];
+    int m_dst[M_ALL], m_dst_step[M_ALL];                      // (rows the tile does not have land in the dummy, all from one place)
+    int ksteps, loader, m_piece;
+    uint8_t* smem;
+
+    // loader lanes: 8 lanes per row, chunk rotated by (row / 2) % 8
+    __device__ __forceinline__ void init(const bf16_t* B, int n, const bf16_t* Av, const uint8_t* Am, int m, int K, int m0, int n0,
+                                         int k_first, int steps, int wave, int lane, uint8_t* lds) {
+        ksteps = steps;
+        loader = wave;
+        smem = lds;
+        m_piece = ML::piece(lane) * 16;
+#pragma unroll
+        for (int i = 0; i < A_LD; ++i) {
+            const int rl = (loader * A_LD + i) * 8 + (lane >> 3);     // row inside the tile
+            a_src[i] = (const uint8_t*)Av + (size_t)wrap_row(m0 + rl, m) * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 64;
+        }
+#pragma unroll
+        for (int i = 0; i < B_LD; ++i) {
+            const int rl = (loader * B_LD + i) * 8 + (lane >> 3);
+            b_src[i] = (const uint8_t*)B + (size_t)wrap_row(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)k_first * 128;
+        }
+#pragma unroll
+        for (int p = 0; p < M_ALL; ++p) {
+            const int rl = (p * LW + loader) * ML::ROWS;
+            const bool has = rl < BM;                         // wave-uniform
+            m_src[p] = Am + (size_t)(has ? wrap_row(m0 + rl + lane / ML::PIECES, m) : 0) * (K / 8) + (size_t)k_first * 8;
+            m_dst[p] = has ? S::M_OFF + (p * LW + loader) * 1024 : S::DUMMY;
+            m_dst_step[p] = has ? S::M_BLOCK : 0;
+        }
+    }
+    __device__ __forceinline__ void tokens(int64_t off, int stage, int i) const {
+        dma16(b_src[i] + off, smem + S::B_OFF + stage * S::B_STAGE + (loader * B_LD + i) * 1024);
+    }
+    __device__ __forceinline__ void weights(int64_t off, int buf, int i) const {
+        dma16(a_src[i] + off, smem + buf * S::A_PAIR + (loader * A_LD + i) * 1024);
+    }
+    __device__ __forceinline__ void metadata(int block, int p) const {       // of k-steps META_STEPS * block ..
+        const int off = block * ML::ROW + m_piece, last = ksteps * 8 - 16;
+        dma16(m_src[p] + (off < last ? off : last), smem + m_dst[p] + (block & 1) * m_dst_step[p]);
+    }
+    // what the k-steps before the first would have queued; not by all: the tokens of the first two are left to the other wavefronts
+    __device__ __forceinline__ void first() const {
+#pragma unroll
+        for (int p = 0; p < M_ALL; ++p) metadata(0, p);
+        auto pair = [&](int p) {
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) weights(pair_offset<TAIL>(p, ksteps), p, i);
+        };
+        auto step = [&](int ks) {
+#pragma unroll
+            for (int i = 0; i < B_LD; ++i) tokens((int64_t)(ks < ksteps ? ks : ksteps - 1) * 128, ks, i);
+        };
+        pair(0);
+        if (ALL) {
+            step(0);
+            step(1);
+        }
+        pair(1);
+        step(2);
+    }
+    // Load x of step ks, S4 = ks % 4: what refills the buffers that it has left, `stage` of them the tokens', by k-step ks + 3 and the
+    // pair after the next one, and a part of the next block of metadata.
+    __device__ __forceinline__ int64_t b_offset(int ks) const { return (int64_t)(ks + 3 < ksteps ? ks + 3 : ksteps - 1) * 128; }
+    __device__ __forceinline__ int64_t a_offset(int ks, int S4) const { return (S4 & 1) ? pair_offset<TAIL>((ks >> 1) + 2, ksteps) : 0; }
+    __device__ __forceinline__ void one(int ks, int S4, int stage, int64_t b_off, int64_t a_off, int x) const {
+        if (x < B_LD) tokens(b_off, stage, x);
+        else if (S4 & 1) weights(a_off, S4 >> 1, x - B_LD);
+        else if (ML::PARTS == 1 || (ks >> 2 & 1) == 0) metadata((ks >> 2) / ML::PARTS + 1, x - B_LD);
+        else metadata((ks >> 2) / ML::PARTS + 1, M_ALL - M_LD + x - B_LD);
+    }
+};
+
 template <int BM, int BN, bool TAIL, class Job>
 __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __restrict__ B, int n,
                                                             const bf16_t* __restrict__ Av,
@@ -306,14 +405,17 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
                                                             bf16_t* __restrict__ C, int tiles_m, int tiles_n,
                                                             Job job) {
     using S = SpmmSmem<BM, BN>;
-    constexpr int MF = BM / 32, NF = BN / 64;                // 16 x 16 fragments per wavefront
-    constexpr int A_LD = BM / 64, B_LD = BN / 64;            // 1 KiB loads per wavefront: per pair, per step
+    constexpr int MULT = tile_mult(BM, BN, TAIL);                // wavefronts that multiply
+    constexpr bool OWN = MULT == 8;                          // all load as well, or LOADERS more do
+    constexpr int MF = BM / 32, NF = BN / (8 * MULT);        // 16 x 16 fragments per wavefront
+    using Loads = SpmmLoads<BM, BN, TAIL, OWN>;
+    using ML = typename Loads::ML;
     extern __shared__ __align__(16) uint8_t smem[];
     fetch_arguments(B, n, Av, Am, m, K, tiles_m, tiles_n);
 
     int tm, tn, slab = 0, extension_slab = 0;
     if constexpr (is_split<Job>) {
-        static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
+        static_assert(SPMM_THREADS == SK_WAVES * 64 && RING_THREADS == SPMM_THREADS && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
         if (!tile_of<BM, BN>(job, m, n, tiles_m, tiles_n, tm, tn)) return;
@@ -324,43 +426,6 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     const int wm = wave & 1, wn = wave >> 1;
     const int l16 = lane & 15, lq = lane >> 4;
 
-    // ---- loader lanes: 8 lanes per row, chunk rotated by (row / 2) % 8
-    const uint8_t* a_src[A_LD];
-#pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-        int rl = (wave * A_LD + i) * 8 + (lane >> 3);         // row inside the tile
-        int row = wrap_row(m0 + rl, m);
-        a_src[i] = (const uint8_t*)Av + (size_t)row * K + (((lane & 7) ^ ((rl >> 1) & 7)) * 16);
-    }
-    const uint8_t* b_src[B_LD];
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) {
-        int rl = (wave * B_LD + i) * 8 + (lane >> 3);
-        int row = wrap_row(n0 + rl, n);
-        b_src[i] = (const uint8_t*)B + (size_t)row * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16);
-    }
-    using ML = MetaLanes<S::META_STEPS>;
-    const uint8_t* m_src[ML::PARTS];
-    int m_dst[ML::PARTS], m_dst_step[ML::PARTS];              // (rows the tile does not have land in the dummy, all from one place)
-#pragma unroll
-    for (int p = 0; p < ML::PARTS; ++p) {
-        const int rl = (p * 8 + wave) * ML::ROWS;
-        const bool has = rl < BM;                             // wave-uniform
-        const int row = has ? wrap_row(m0 + rl + lane / ML::PIECES, m) : 0;
-        m_src[p] = Am + (size_t)row * (K / 8);
-        m_dst[p] = has ? S::M_OFF + (p * 8 + wave) * 1024 : S::DUMMY;
-        m_dst_step[p] = has ? S::M_BLOCK : 0;
-    }
-    const int m_piece = ML::piece(lane) * 16;
-
-    // ---- reader lanes: fragment f = rows 16f .. 16f+15 = 2 KiB; lane (l16, lq) wants chunk 4h + lq
-    const int sw = (l16 >> 1) & 7;
-    const int rd0 = l16 * 128 + ((lq ^ sw) * 16);             // h = 0
-    const int rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);       // h = 1
-    const int a_rd = (wm * MF) * 2048;
-    const int b_rd = S::B_OFF + (wn * NF) * 2048;
-    const int m_rd = S::M_OFF + (wm * MF * 16 + l16) * ML::ROW + lq * 2, m_sw = ML::swap(l16) * 16;
-
     int k_first = 0, slab_steps = K / 64;
     float* sums = nullptr;
     if constexpr (is_split<Job>) {
@@ -370,27 +435,51 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     }
     // a multiple of 4 unless TAIL
     const int ksteps = K / 64 - k_first > slab_steps ? slab_steps : K / 64 - k_first;
+
+    // ---- reader lanes: fragment f = rows 16f .. 16f+15 = 2 KiB; lane (l16, lq) wants chunk 4h + lq
+    const int sw = (l16 >> 1) & 7;
+    const int rd0 = l16 * 128 + ((lq ^ sw) * 16);             // h = 0
+    const int rd1 = l16 * 128 + (((4 + lq) ^ sw) * 16);       // h = 1
+    const int a_rd = (wm * MF) * 2048;
+    const int b_rd = S::B_OFF + (wn * NF) * 2048;
+    const int m_rd = S::M_OFF + (wm * MF * 16 + l16) * ML::ROW + lq * 2, m_sw = ML::swap(l16) * 16;
+
+    if constexpr (!OWN) {
+        if (wave >= MULT) {                                   // (its barriers are those of the others)
+            Loads load;
+            load.init(B, n, Av, Am, m, K, m0, n0, k_first, ksteps, wave - MULT, lane, smem);
+            load.first();
+            WAIT_HERE(waitcnt_imm(Loads::A_LD + Loads::B_LD, 15));
+            wg_barrier();
+            wg_barrier();
+            int stage = 0;
+            auto step = [&](int ks, auto s4) {
+                constexpr int S4 = decltype(s4)::value, LOADS = Loads::step_loads(S4);
+                if (ks + 3 < ksteps) {
+                    const int64_t b_off = load.b_offset(ks), a_off = load.a_offset(ks, S4);
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) a_src[i] += (size_t)k_first * 64;
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) b_src[i] += (size_t)k_first * 128;
-#pragma unroll
-    for (int p = 0; p < ML::PARTS; ++p) m_src[p] += (size_t)k_first * 8;
-    auto issue_b = [&](int ks, int stage) {                   // token rows of k-step ks (clamped)
-        int kc = ks < ksteps ? ks : ksteps - 1;
-#pragma unroll
-        for (int i = 0; i < B_LD; ++i)
-            dma16(b_src[i] + (size_t)kc * 128, smem + S::B_OFF + stage * S::B_STAGE + (wave * B_LD + i) * 1024);
-    };
-    auto issue_a = [&](int pair, int buf) {                   // weight rows of k-steps 2 pair, 2 pair + 1
-        const int64_t off = pair_offset<TAIL>(pair, ksteps);
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i) dma16(a_src[i] + off, smem + buf * S::A_PAIR + (wave * A_LD + i) * 1024);
-    };
-    auto issue_m = [&](int block, int part) {                 // metadata of k-steps META_STEPS * block ..
-        const int off = block * ML::ROW + m_piece, last = ksteps * 8 - 16;
-        dma16(m_src[part] + (off < last ? off : last), smem + m_dst[part] + (block & 1) * m_dst_step[part]);
-    };
+                    for (int x = 0; x < LOADS; ++x) load.one(ks, S4, stage, b_off, a_off, x);
+                    WAIT_HERE(waitcnt_imm(LOADS, 15));
+                } else {                                      // nothing of what the last three k-steps would load is used
+                    WAIT_HERE(waitcnt_imm(0, 15));
+                }
+                wg_barrier();
+                stage = stage == 2 ? 0 : stage + 1;
+            };
+            for (int ks0 = 0; ks0 < ksteps; ks0 += 4) {
+                step(ks0, std::integral_constant<int, 0>{});
+                LAST_STEP(0)
+                step(ks0 + 1, std::integral_constant<int, 1>{});
+                LAST_STEP(1)
+                step(ks0 + 2, std::integral_constant<int, 2>{});
+                LAST_STEP(2)
+                step(ks0 + 3, std::integral_constant<int, 3>{});
+            }
+            return;
+        }
+    }
+    Loads load;
+    if constexpr (OWN) load.init(B, n, Av, Am, m, K, m0, n0, k_first, ksteps, wave, lane, smem);
 
     f32x4 acc[MF][NF];
 #pragma unroll
@@ -418,20 +507,24 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
         }
     };
 
-    // ---- prologue: what the k-steps before the first would have queued
+    if constexpr (OWN) {
+        load.first();
+        WAIT_HERE(waitcnt_imm(Loads::A_LD + 2 * Loads::B_LD, 15));
+    } else {                                                  // the tokens of the first two k-steps, which the loaders leave out
+        constexpr int T_LD = BN / (8 * MULT);
 #pragma unroll
-    for (int p = 0; p < ML::PARTS; ++p) issue_m(0, p);
-    issue_a(0, 0);
-    issue_b(0, 0);
-    issue_b(1, 1);
-    issue_a(1, 1);
-    issue_b(2, 2);
-    WAIT_HERE(waitcnt_imm(A_LD + 2 * B_LD, 15));
+        for (int i = 0; i < 2 * T_LD; ++i) {
+            const int g = wave * T_LD + i % T_LD, rl = g * 8 + (lane >> 3), step = i / T_LD;
+            dma16((const uint8_t*)B + (size_t)wrap_row_near(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)(k_first + step) * 128,
+                  smem + S::B_OFF + step * S::B_STAGE + g * 1024);
+        }
+        WAIT_HERE(waitcnt_imm(T_LD, 15));
+    }
     wg_barrier();
     Frags f;
 #pragma unroll
     for (int x = 0; x < MF + NF; ++x) read_one(f, 0, 0, 0, x);
-    WAIT_HERE(waitcnt_imm(A_LD + B_LD, 0));
+    WAIT_HERE(waitcnt_imm(OWN ? Loads::A_LD + Loads::B_LD : 0, 0));
     wg_barrier();
 
     // One k-step, its fragments in registers: everybody has read it from LDS, the next one has landed.  Spread among its products
@@ -442,10 +535,9 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     int bst = 0;                                              // ring stage of the current k-step
     auto step = [&](int ks, auto s4) {
         constexpr int S4 = decltype(s4)::value, N4 = (S4 + 1) & 3;
-        constexpr int LOADS = B_LD + (S4 & 1) * A_LD + (S4 == 0), EARLY = NF + LOADS, SLOTS = MF * NF, PER = (EARLY + SLOTS - 1) / SLOTS;
+        constexpr int LOADS = OWN ? Loads::step_loads(S4) : 0, EARLY = NF + LOADS, SLOTS = MF * NF, PER = (EARLY + SLOTS - 1) / SLOTS;
         const int next = bst == 2 ? 0 : bst + 1;
-        const int kb = ks + 3 < ksteps ? ks + 3 : ksteps - 1;
-        const int64_t a_off = (S4 & 1) ? pair_offset<TAIL>((ks >> 1) + 2, ksteps) : 0;
+        const int64_t b_off = OWN ? load.b_offset(ks) : 0, a_off = OWN ? load.a_offset(ks, S4) : 0;
         Frags g;
 #pragma unroll
         for (int i = 0; i < MF; ++i) {
@@ -455,14 +547,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int x = (i * NF + j) * PER; x < (i * NF + j + 1) * PER; ++x) {
-                    if (x < B_LD) dma16(b_src[x] + (size_t)kb * 128, smem + S::B_OFF + bst * S::B_STAGE + (wave * B_LD + x) * 1024);
-                    else if (x < B_LD + (S4 & 1) * A_LD)
-                        dma16(a_src[x - B_LD] + a_off, smem + (S4 >> 1) * S::A_PAIR + (wave * A_LD + x - B_LD) * 1024);
-                    else if (x < LOADS) {                     // a part of the next block
-                        const int quad = ks >> 2;
-                        if (ML::PARTS == 1 || (quad & 1) == 0) issue_m(quad / ML::PARTS + 1, 0);
-                        else issue_m(quad / ML::PARTS + 1, ML::PARTS - 1);
-                    }
+                    if (x < LOADS) load.one(ks, S4, bst, b_off, a_off, x);
                     else if (x < EARLY) read_one(g, ks + 1, N4, next, x - LOADS);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -470,7 +555,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
             read_one(g, ks + 1, N4, next, NF + i);
             __builtin_amdgcn_sched_barrier(0);
         }
-        WAIT_HERE(waitcnt_imm(LOADS, 0));
+        WAIT_HERE(waitcnt_imm(OWN ? LOADS : 63, 0));
         wg_barrier();
         f = g;
         bst = next;
@@ -484,11 +569,14 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
         LAST_STEP(2)
         step(ks0 + 3, std::integral_constant<int, 3>{});
     }
-    WAIT_HERE(waitcnt_imm(0, 15));           // drain the clamped look-ahead loads
+    if (OWN) WAIT_HERE(waitcnt_imm(0, 15));  // drain the clamped look-ahead loads
 
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL, "the staged output tile fits in the rings");
-    extend_and_store<MF, NF, BM, BN, SPMM_THREADS>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
-                                     slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
+    int te = threadIdx.x;                                    // (the lane's coordinates again rather than kept across the loop)
+    if (!OWN) asm volatile("" : "+v"(te));
+    const int we = __builtin_amdgcn_readfirstlane(te >> 6);
+    extend_and_store<MF, NF, BM, BN, 64 * MULT>(acc, m0 + (we & 1) * MF * 16, n0 + (we >> 1) * NF * 16, m, n, te & 15, te >> 4 & 3, B2, A2,
+                                                slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -774,7 +862,6 @@ constexpr int ring_leave(int u, int each, int meta) {
 
 // TAIL: an odd number of k-steps; the values and metadata of the last one are then fetched as the second half of a pair that
 // ends with the row (see spmm_kernel).
-constexpr int LOADERS = 4, RING_MULT = 4, RING_THREADS = 64 * (RING_MULT + LOADERS);
 template <int BM, int BN, bool TAIL, class Job>
 __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* __restrict__ B, int n,
                                                                  const bf16_t* __restrict__ Av,
@@ -795,7 +882,7 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
 
     int tm, tn, slab = 0, extension_slab = 0;
     if constexpr (is_split<Job>) {
-        static_assert(SPMM_THREADS == SK_WAVES * 64 && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
+        static_assert(SPMM_THREADS == SK_WAVES * 64 && RING_THREADS == SPMM_THREADS && SK_LDS <= S::TOTAL, "a skinny tile fits in the workgroup");
         if (!split_item(job, B, n, K, tiles_m, tiles_n, smem, tm, tn, slab, extension_slab)) return;
     } else {
         if (!tile_of<BM, BN>(job, m, n, tiles_m, tiles_n, tm, tn)) return;
