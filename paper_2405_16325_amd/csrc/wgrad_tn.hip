@@ -85,16 +85,15 @@ struct TnSmem {
 };
 
 constexpr int TN_THREADS = 512;
-// Wavefronts of a tile.  Up to 128 x 128 four of them only load (why: spmm_ring_kernel), and load nothing past the end: us, loads by
-// the eight that multiply / by four of their own: dW of 1024 x 1024 over 4096 tokens on 64 x 64 18.7 / 17.4, 3072 x 768 over 2048 on
-// 128 x 128 19.8 / 19.1; masked dense 2000 x 1928 over 2048 on 128 x 128 18.9 / 18.3; the gradients of 3136 x 896, rank 64 over 14376 tokens
-// 163.9 / 157.3.  192 x 128, whose loads are spread among its products: 65.3 / 66.4 (dW of 4096 x 3000 over 3064 tokens).
-// Up to 64 x 128 four multiply, with twice as many products for their reads, a third fewer bytes from LDS in all, and workgroups as large
-// as before: eight / four, from memory: dW of 1024 x 1024 over 4096 tokens 18.0 / 17.2, masked dense 704 x 768 over 518 5.3 / 5.0, the
-// gradients of 4096 x 1024, rank 128 over 2000 tokens 41.5 / 40.8; on 128 x 128 k-contiguous 3 % faster, k-major 3 % slower.
+// Wavefronts of a tile.  Up to 256 x 128 four of them only load (why: spmm_ring_kernel) and load nothing past the end, and four multiply,
+// with a quarter of the tile each: a third fewer bytes from LDS in all than eight, which on operands as stored, by the transposing reads, take
+// longer than the products.  us, from memory, eight that do both / four and four: dW of 1024 x 1024 over 4096 tokens on 64 x 64 19.4 / 16.9,
+// 3072 x 768 over 2048 on 128 x 128 18.7 / 17.0, 4096 x 2048 over 4096 on 256 x 128 59.5 / 56.6, 2816 x 2816 59.9 / 56.0; masked dense 704 x 768 over
+// 518 5.1 / 4.8, 3072 x 2048 over 2048 on 192 x 128 24.6 / 22.9; the gradients of 3136 x 896, rank 64 over 14376 tokens 187 / 182.  On 192 x
+// 192, where their registers just suffice: 2112 x 4160 over 700 15.9 / 17.3.
 constexpr int TN_LOADERS = 4;
-constexpr int tn_loaders(int bm, int bn) { return bm * bn <= 128 * 128 ? TN_LOADERS : 0; }
-constexpr int tn_mult(int bm, int bn) { return bm * bn <= 64 * 128 ? 4 : 8; }
+constexpr int tn_loaders(int bm, int bn) { return bm * bn <= 256 * 128 ? TN_LOADERS : 0; }
+constexpr int tn_mult(int bm, int bn) { return tn_loaders(bm, bn) ? 4 : 8; }
 constexpr int tn_threads(int bm, int bn) { return 64 * (tn_mult(bm, bn) + tn_loaders(bm, bn)); }
 enum { EPI_MASKED_PACKED = 0, EPI_PLAIN = 1 };
 
@@ -295,16 +294,11 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
         WAIT_HERE(waitcnt_imm(AHEAD, 15));                    // the first step has landed (this wave's share)
     }
     wg_barrier();
-    // Two schedules of a k-step.  Where each wavefront's products cover its own reads: one barrier, the fragments of a half of the
-    // k-step read while the other half is multiplied.  (us, operands in the last-level cache, in two phases / so: 64 x 64, 1024
-    // x 1024 over 4096 tokens 23.9 / 21.0; 128 x 128, 3072 x 768 over 2048 tokens 22.4 / 20.6; 192 x 192, 1024 x 2048 over 4096 47.9
-    // / 42.7; 256 x 128, 4096 x 4096 over 4096 tokens 129 / 120.)  Else two phases, as in the 256 x 256 kernel: where the ring has
-    // two stages, so that loads are queued later (256 x 192, 5120 x 6464 over 752 tokens: 62.7 against 65.3), and on k-contiguous
-    // operands on 192 x 128 (1920 x 1973 over 3840: 34.8 against 35.7).
-    // (Each tile both ways on seven shapes per layout, contractions of 192 to 12000, from HBM and from the cache; one barrier against two
-    // phases in the mean: k-major 256 x 192 4 % slower, the others 0 to 8 % faster; k-contiguous 256 x 128, 192 x 192, 64 x 128 and
-    // 64 x 64 1 to 11 % faster, 256 x 192, 192 x 128 and 128 x 128 1 to 3 % slower.)
-    if constexpr (!LOADERS && (NS == 2 || (!AKM && !BKM && MF * NF == 12))) {
+    // Two schedules of a k-step.  One barrier, the fragments of a half of the k-step read while the other half is multiplied (us, operands in
+    // the last-level cache, in two phases / so: 64 x 64, 1024 x 1024 over 4096 tokens 23.9 / 21.0; 128 x 128, 3072 x 768 over 2048 tokens 22.4 / 20.6;
+    // 192 x 192, 1024 x 2048 over 4096 47.9 / 42.7; 256 x 128, 4096 x 4096 over 4096 tokens 129 / 120).  Where the ring has two stages two
+    // phases, as in the 256 x 256 kernel, so that loads are queued later (256 x 192, 5120 x 6464 over 752 tokens: 62.7 against 65.3).
+    if constexpr (!LOADERS && NS == 2) {
         const int group = wave >> 2;
         // One k-step.  Loads of step s + NS - 1 are queued in the even phase in which their stage, last
         // read for step s - 1, has just been released: group 0 is then in its memory phase of step s,
@@ -393,13 +387,18 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
         __builtin_amdgcn_sched_barrier(0);
         if (!LOADERS) issue(k_begin + NS - 1, LAST);
         WAIT_HERE(waitcnt_imm(63, 0));                        // (else the compiler waits for all reads at the head of the loop)
-        for (int ks = k_begin; ks < k_end; ++ks) {
-            {
-                const auto sa = opa.stage(smem, at);
-                const auto sb = opb.stage(smem, at + S::A_BYTES);
-                multiply(f0, std::integral_constant<int, READS>{}, [&](int x) { read_one(f1, sa, sb, 1, x); });
-            }
-            if (LOADERS && ks + 1 == k_end) {
+        auto first_half = [&] {
+            const auto sa = opa.stage(smem, at);
+            const auto sb = opb.stage(smem, at + S::A_BYTES);
+            multiply(f0, std::integral_constant<int, READS>{}, [&](int x) { read_one(f1, sa, sb, 1, x); });
+        };
+        // With loaders nothing follows the last k-step, which comes after the loop.  (On up to 64 x 128 it stays inside: 1024 x 4096 over
+        // 2048 20.2 / 21.4 after it, while leaving the loop from inside costs larger tiles copies of their sums: 3072 x 768 over 2048 17.6 / 17.0)
+        constexpr bool AFTER = LOADERS && BM * BN > 64 * 128;
+        const int full = AFTER ? k_end - 1 : k_end;
+        for (int ks = k_begin; ks < full; ++ks) {
+            first_half();
+            if (LOADERS && !AFTER && ks + 1 == k_end) {
                 multiply(f1, std::integral_constant<int, 0>{}, [](int) {});
                 break;
             }
@@ -414,6 +413,10 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
                 else load_one(ks + NS, x - READS);            // into the stage that everybody has read
             });
             at = next;
+        }
+        if (AFTER) {
+            first_half();
+            multiply(f1, std::integral_constant<int, 0>{}, [](int) {});
         }
     }
     if (!LOADERS) WAIT_HERE(waitcnt_imm(0, 15));              // drain the clamped look-ahead loads
