@@ -1658,13 +1658,22 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
 
 int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RESIDENT ? 64 : 128; }
 
+// Where the estimate prefers 64 x 64 tiles on a contraction of more k-steps than this, the ring kernel with its loader wavefronts is the
+// faster one on 128 x 64 (us, from memory, 64 x 64 / 128 x 64: 256 tokens, 2496 x 1920 10.9 / 9.9; 320, 640 x 1664 9.7 / 8.6; 303, 768 x 4096 17.1 /
+// 15.0; 1325, 512 x 6016 26.1 / 21.6; 153, 1536 x 11520 41.1 / 37.0; all 12 of 70 shapes where it was preferred, no other tile was better).  Not up to 64 rows, where half of
+// the taller tile is nothing.
+constexpr int64_t LONGEST_OF_64 = 16 * 64;
+
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel, whose whole pairs of
 // k-steps on a round of 64 x 64 tiles count as a tile shape of their own.
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 0;
     if (!tile_kernel_fits(K)) return;
     best_tile_us(n, m, K, bm, bn);
-    if (bm == 64 && K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
+    if (bm != 64) return;
+    // (whether a product is split is decided by the estimate as it stands)
+    if (K > LONGEST_OF_64 && m > 64) { bm = 128; bn = 64; }
+    else if (K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
 }
 
 // Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 6 us for its launch and

@@ -892,12 +892,12 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 
 // The kernels run at the rate their compute units pull operands from L2, 53 bytes per ns (up to a fifth more with few of them
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
-// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  Take the shape with the least
-// estimate, whatever the operands' layout: over 80 shapes (400 to 16000 rows on one side, 256 to 9000 on the other, contractions of
-// 256 to 12000), each on all eight tiles, it takes 0.6 % longer than the best one in the mean and 14 % at most from k-contiguous
-// operands, 0.7 % and 20 % (2816 tokens, 3520 x 2664, where 256 x 192 would be better) from operands as stored (gradients as
-// stored, us: 700 tokens, 4160 x 2112 18.5 on 192 x 192, 256 x 128 27.5; 752 tokens, 5120 x 6464 63.2 on 256 x 192, 256 x 256
-// 73.1; 4096 tokens, 1024 x 1024 21.2 on 64 x 64, 128 x 128 32.8).
+// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 have become 10 to 30 %
+// faster than that, those above at most 10 %, the 256 x 256 kernel, bound by its products and their power, not at all: it counts a twelfth
+// more, which leaves the choice 0.4 % longer than the best tile in the mean and 13 % at most (50 shapes from memory, half of them gradients
+// as stored, half masked dense products: 300 to 9000 rows on a side, contractions of 300 to 9000, each on all eight tiles; without it 1.6 %.  us: 3584
+// x 6144 over 4321 tokens on 256 x 256 191, 256 x 128 167; 1792 x 5888 over 1212 33.7, on 256 x 192 28.9).  Where the leftover tiles are cut the
+// estimate stays, and with it the scratch that calls name.
 static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tail) {
     int best = 0;
     double least = 1e300;
@@ -906,7 +906,7 @@ static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tai
         const int64_t tm = (m + bm - 1) / bm, tn = (n + bn - 1) / bn, tiles = tm * tn, rounds = (tiles + RESIDENT - 1) / RESIDENT;
         const double step = 128.0 * (double)(bm + bn) / 53e3 * (bn != 192 ? 1.0 : bm == 256 ? 1.15 : 1.04), start = 3.0 + 6.0 * (double)(bm * bn) / 65536.0;
         const double busy = (double)tiles / (double)(rounds * RESIDENT);
-        double us = (double)rounds * (start + (double)ksteps * step * (1.0 - 0.22 * (1.0 - busy)));
+        double us = (double)rounds * (start + (double)ksteps * step * (c == 0 ? 1.08 : 1.0) * (1.0 - 0.22 * (1.0 - busy)));
         if (c == 0 && with_tail) {
             const TailPlan p = tail_plan(tm, tn, ksteps);
             if (p.tiles) us = (double)(tiles / RESIDENT) * (start + (double)ksteps * step) + 1.3 * p.steps + 16.0;
