@@ -1501,8 +1501,10 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // operand feed of a compute unit, 53 bytes per ns (a little more on the smaller tiles of the ring kernel; up to a fifth more
 // with few compute units at work), and takes longer for weight bytes that come from HBM: those that few token tiles share.
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
-// The constants were fitted on weights from HBM and on tiles that read a k-step before they multiplied it.  Against them the kernels
-// now take 1.02 (128 x 128) to 1.18 (256 x 192) of the estimate on such weights, 0.91 to 1.12 on those from the cache: over 110
+// The constants were fitted on weights from HBM and on tiles that read a k-step before they multiplied it, and before wavefronts that
+// only load, which take 5 to 20 % off the tiles up to 256 x 128 alike (over 70 shapes the whole tile chosen is now 0.9 % longer than the best,
+// 8 % at most).  Before those, against them the kernels
+// took 1.02 (128 x 128) to 1.18 (256 x 192) of the estimate on such weights, 0.91 to 1.12 on those from the cache: over 110
 // shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128 to 20000), each on five whole tiles and four splits of low
 // estimate, the form chosen takes 1.2 % longer than the best one in the mean, more than 10 % in one (65 tokens, 21888 x 7232),
 // 1.5 % on weights from the cache.
