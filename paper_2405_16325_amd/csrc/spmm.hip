@@ -1502,8 +1502,8 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // with few compute units at work), and takes longer for weight bytes that come from HBM: those that few token tiles share.
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
 // The constants were fitted on weights from HBM and on tiles that read a k-step before they multiplied it, and before wavefronts that
-// only load, which take 5 to 20 % off the tiles up to 256 x 128 alike (over 70 shapes the whole tile chosen is now 0.9 % longer than the best,
-// 8 % at most).  Before those, against them the kernels
+// only load, which take up to 15 % off the tiles up to 256 x 128 (over 70 shapes the whole tile chosen is now 0.6 % longer than the best in the
+// mean, 8 % at most; the line of LONGEST_OF_64 was drawn on the same shapes).  Before those, against them the kernels
 // took 1.02 (128 x 128) to 1.18 (256 x 192) of the estimate on such weights, 0.91 to 1.12 on those from the cache: over 110
 // shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128 to 20000), each on five whole tiles and four splits of low
 // estimate, the form chosen takes 1.2 % longer than the best one in the mean, more than 10 % in one (65 tokens, 21888 x 7232),
@@ -1662,8 +1662,8 @@ int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RE
 
 // Where the estimate prefers 64 x 64 tiles on a contraction of more k-steps than this, the ring kernel with its loader wavefronts is the
 // faster one on 128 x 64 (us, from memory, 64 x 64 / 128 x 64: 256 tokens, 2496 x 1920 10.9 / 9.9; 320, 640 x 1664 9.7 / 8.6; 303, 768 x 4096 17.1 /
-// 15.0; 1325, 512 x 6016 26.1 / 21.6; 153, 1536 x 11520 41.1 / 37.0; all 12 of 70 shapes where it was preferred, no other tile was better).  Not up to 64 rows, where half of
-// the taller tile is nothing.
+// 15.0; 1325, 512 x 6016 26.1 / 21.6; 153, 1536 x 11520 41.1 / 37.0; all 11 such of 70 shapes are 8 to 22 % faster so; three with at
+// most 12 k-steps are 16 and 12 % slower and 3 % faster).  Not up to 64 rows, where half of the taller tile is nothing.
 constexpr int64_t LONGEST_OF_64 = 16 * 64;
 
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel, whose whole pairs of

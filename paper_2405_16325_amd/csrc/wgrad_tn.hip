@@ -894,8 +894,9 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
 // of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 have become 10 to 30 %
 // faster than that, those above at most 10 %, the 256 x 256 kernel, bound by its products and their power, not at all: it counts a twelfth
-// more, which leaves the choice 0.4 % longer than the best tile in the mean and 13 % at most (50 shapes from memory, half of them gradients
-// as stored, half masked dense products: 300 to 9000 rows on a side, contractions of 300 to 9000, each on all eight tiles; without it 1.6 %.  us: 3584
+// more, which leaves the choice 0.4 % longer than the best tile in the mean and 13.5 % at most on the 50 shapes that the factor was fitted
+// on (from memory, 29 gradients as stored, 21 masked dense products: m 512 to 7936, n 512 to 6912, contractions of 305 to 8960, each on
+// 5 to 8 tiles; without it 1.6 % and 14.7 %.  us: 3584
 // x 6144 over 4321 tokens on 256 x 256 191, 256 x 128 167; 1792 x 5888 over 1212 33.7, on 256 x 192 28.9).  Where the leftover tiles are cut the
 // estimate stays, and with it the scratch that calls name.
 static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tail) {
