@@ -211,8 +211,10 @@ __device__ __forceinline__ bool dense_tn_sums(const DenseOperand& At, const Dens
     constexpr bool LOADERS = tn_loaders(BM, BN) != 0;
     // The first k-steps' loads are shared out to eight as they would be without loaders, of whom the multiplying wavefronts are the first: four
     // loaders alone took long to fill the ring (us, from memory, by themselves / so: masked dense 768 x 704 over 518 5.0 / 4.7, 576 x 1408 over
-    // 1625 7.8 / 7.5; dW of 1000 x 1000 over 1000 9.5 / 9.3, 1024 x 1024 over 4096 17.3 / 17.0; eight, no loaders: 5.0, 7.7, 9.3, 19.0)
-    constexpr int PRE = 3;                                    // (what `behind` is asked for knows)
+    // 1625 7.8 / 7.5; dW of 1000 x 1000 over 1000 9.5 / 9.3, 1024 x 1024 over 4096 17.3 / 17.0; eight, no loaders: 5.0, 7.7, 9.3, 19.0).  No more
+    // steps than the ring holds ahead: a third one on 256 x 128 was loaded twice, which took 0.3 to 1.8 % more on 8 to 20 k-steps.
+    constexpr int PRE = NS - 1 < 3 ? NS - 1 : 3;              // (what `behind` is asked for knows)
+    static_assert(PRE <= NS - 1, "the steps that are shared out are among those loaded before the loop, so that each is loaded once");
     constexpr int LAST = (NS - 1) * S::STAGE;
     if (LOADERS && wave >= MULT) {
         constexpr int EACH = 8 / TN_LOADERS;                  // a loader has the loads of so many of the eight
