@@ -97,20 +97,29 @@ constexpr int tn_mult(int bm, int bn) { return tn_loaders(bm, bn) ? 4 : 8; }
 constexpr int tn_threads(int bm, int bn) { return 64 * (tn_mult(bm, bn) + tn_loaders(bm, bn)); }
 enum { EPI_MASKED_PACKED = 0, EPI_PLAIN = 1 };
 
-// Metadata of the 32 Q columns of W^R from c (a multiple of 32) of row o, by dwords; columns outside the matrix: any.  The dwords of
-// rows that are not a multiple of 32 columns may lie at any byte, and the last of such a row, which ends inside it, is read by bytes.
-template <int Q>
-__device__ __forceinline__ void load_meta(const uint8_t* __restrict__ meta, int o, int c, int m, int n, uint32_t (&w)[Q]) {
+// Metadata of the 32 Q columns of W^R from c (a multiple of 32) of rows o, o + 16, .. of N, by dwords; columns outside the matrix: any.  The
+// dwords of rows that are not a multiple of 32 columns may lie at any byte, and the last of such a row, which ends inside it, is read by
+// bytes.  All rows' loads leave together: row after row each costs a trip to memory.
+template <int N, int Q>
+__device__ __forceinline__ void load_meta(const uint8_t* __restrict__ meta, int o, int c, int m, int n, uint32_t (&w)[N][Q]) {
     typedef uint32_t __attribute__((aligned(1))) u32_a1;
     const uint8_t* const p = meta + (size_t)o * (m / 8) + c / 8;
+    const size_t next = (size_t)16 * (m / 8);
 #pragma unroll
-    for (int q = 0; q < Q; ++q) w[q] = o < n && c + 32 * q + 32 <= m ? *(const u32_a1*)(p + 4 * q) : 0u;
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) w[j][q] = o + 16 * j < n && c + 32 * q + 32 <= m ? *(const u32_a1*)(p + j * next + 4 * q) : 0u;
     if (m % 32 != 0 && c < m && c + 32 * Q > m) {             // uniform
-        uint32_t v = 0;
-        if (o < n)
-            for (int e = 0; e < m / 8 % 4; ++e) v |= (uint32_t)p[(m - c) / 32 * 4 + e] << (8 * e);
+        const int bytes = m / 8 % 4;
+        uint32_t v[N][3];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) w[q] = q == (m - c) / 32 ? v : w[q];
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) v[j][e] = e < bytes && o + 16 * j < n ? p[j * next + (m - c) / 32 * 4 + e] : 0u;
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) w[j][q] = q == (m - c) / 32 ? v[j][0] | v[j][1] << 8 | v[j][2] << 16 : w[j][q];
     }
 }
 
@@ -130,24 +139,33 @@ __device__ __forceinline__ void store_masked_packed(const f32x4 (&acc)[MF][NF], 
                                                               // of one store fall on 64 different banks
     const size_t gpitch = (size_t)m / 2;
     __syncthreads();                                          // every wavefront is done with the rings
+    // Columns whose metadata is loaded together.  With four wavefronts a wavefront has twice the columns, and column after column each
+    // paid a trip to memory; with eight, all together are slower.  (163 gradients of up to 1e10 products, from memory, time one by one over all
+    // together, up to 8 k-steps and beyond 40: 64 x 128 1.08 and 1.03, 128 x 128 1.06 and 1.02, 192 x 128 1.04 and 1.02, 256 x 128 1.03 and
+    // 1.02, 64 x 64 1.03 and 1.02; the tiles of eight, 123 gradients, 256 x 256 0.98 and 0.99, 256 x 192 0.99 and 1.00, 192 x 192 1.00.  us: 281 tokens,
+    // 768 x 8960 11.6 / 11.3; 533, 1360 x 856 9.8 / 9.5.)
+    constexpr int TOGETHER = THREADS < 512 ? NF : 1;
 #pragma unroll
-    for (int j = 0; j < NF; ++j) {
-        int o = o0 + j * 16 + l16;
-        // metadata of the wavefront's WM d_in columns of row o: WM / 4 groups = WM / 8 bytes
-        uint32_t mw[WM / 32];
-        load_meta(meta, o, c0, m, n, mw);
+    for (int j0 = 0; j0 < NF; j0 += TOGETHER) {
+        // of the wavefront's WM d_in columns of each row: WM / 4 groups = WM / 8 bytes
+        uint32_t mw[TOGETHER][WM / 32];
+        load_meta(meta, o0 + j0 * 16 + l16, c0, m, n, mw);
 #pragma unroll
-        for (int i = 0; i < MF; ++i) {
-            int gl = i * 4 + lq;                              // group index inside the WM columns
-            uint32_t nib = (mw[i >> 1] >> (4 * (gl & 7))) & 0xFu;
-            uint32_t a = nib & 3u, c = nib >> 2;
-            f32x4 v = acc[i][j];
-            float v0 = a == 0 ? v[0] : (a == 1 ? v[1] : v[2]);
-            float v1 = c == 1 ? v[1] : (c == 2 ? v[2] : v[3]);
-            union { __bf16 h[2]; uint32_t u; } pr;
-            pr.h[0] = (__bf16)v0;
-            pr.h[1] = (__bf16)v1;
-            *(uint32_t*)(smem + (o - tile_o0) * CP + ((c0 - tile_c0) / 4 + gl) * 4) = pr.u;
+        for (int jj = 0; jj < TOGETHER; ++jj) {
+            const int j = j0 + jj, o = o0 + j * 16 + l16;
+#pragma unroll
+            for (int i = 0; i < MF; ++i) {
+                int gl = i * 4 + lq;                          // group index inside the WM columns
+                uint32_t nib = (mw[jj][i >> 1] >> (4 * (gl & 7))) & 0xFu;
+                uint32_t a = nib & 3u, c = nib >> 2;
+                f32x4 v = acc[i][j];
+                float v0 = a == 0 ? v[0] : (a == 1 ? v[1] : v[2]);
+                float v1 = c == 1 ? v[1] : (c == 2 ? v[2] : v[3]);
+                union { __bf16 h[2]; uint32_t u; } pr;
+                pr.h[0] = (__bf16)v0;
+                pr.h[1] = (__bf16)v1;
+                *(uint32_t*)(smem + (o - tile_o0) * CP + ((c0 - tile_c0) / 4 + gl) * 4) = pr.u;
+            }
         }
     }
     __syncthreads();

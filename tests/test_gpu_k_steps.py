@@ -49,6 +49,18 @@ def test_weight_gradient(b, d_out, d_in, tile):
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
 
 
+# rows of metadata that end one, two and three bytes into a dword, on the tiles whose wavefronts load several rows' ends together
+@pytest.mark.parametrize("b,d_out,d_in,tile", [(533, 1360, 856, (64, 128)), (700, 1360, 840, (64, 128)), (600, 1992, 1008, (64, 128)),
+                                               (600, 1920, 2008, (128, 128)), (520, 1400, 1072, (64, 128))])
+def test_weight_gradient_row_ends(b, d_out, d_in, tile):
+    print(f"wgrad b={b} d_out={d_out} d_in={d_in}", flush=True)
+    X, dY = gauss(b, d_in), gauss(b, d_out)
+    _, meta, mask = sl.slope_prune_rows(gauss(d_out, d_in), want_mask=True)
+    want = (dY.float().t() @ X.float())[unpack_bits(mask)].reshape(d_out, d_in // 2)
+    assert tiles(lambda: sl.slope_wgrad_masked(dY, X, meta)) == [("dense_tn_kernel", tile)]
+    assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
+
+
 # sparse products without an adapter or scratch for slabs, by tile (weight rows x tokens): the ring kernel's pairs, odd ends of them, blocks of
 # metadata; the other kernel's quads and what is left of them.  (64 x 64, the generic kernel's form for whole pairs of k-steps, is
 # the 128 x 64 tile's neighbour: 21 k-steps are on that one.)
