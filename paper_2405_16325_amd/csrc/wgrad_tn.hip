@@ -912,29 +912,41 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 
 // The kernels run at the rate their compute units pull operands from L2, 53 bytes per ns (up to a fifth more with few of them
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
-// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 have become 10 to 30 %
-// faster than that, those above at most 10 %, the 256 x 256 kernel, bound by its products and their power, not at all: it counts a twelfth
-// more, which leaves the choice 0.4 % longer than the best tile in the mean and 13.5 % at most on the 50 shapes that the factor was fitted
-// on (from memory, 29 gradients as stored, 21 masked dense products: m 512 to 7936, n 512 to 6912, contractions of 305 to 8960, each on
-// 5 to 8 tiles; without it 1.6 % and 14.7 %.  us: 3584
-// x 6144 over 4321 tokens on 256 x 256 191, 256 x 128 167; 1792 x 5888 over 1212 33.7, on 256 x 192 28.9).  Where the leftover tiles are cut the
-// estimate stays, and with it the scratch that calls name.
-static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool with_tail) {
+// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 are 10 to 30 % faster
+// than that by now; the order of the estimates, which is all that counts, has held.
+// `start`: what a round of the 256 x 256 kernel takes beside its k-steps.
+static double dense_tile_us(int c, int64_t m, int64_t n, int64_t ksteps, double start = 9.0) {
+    const int bm = DENSE_TILES[c].bm, bn = DENSE_TILES[c].bn;
+    const int64_t tiles = ((m + bm - 1) / bm) * ((n + bn - 1) / bn), rounds = (tiles + RESIDENT - 1) / RESIDENT;
+    const double step = 128.0 * (double)(bm + bn) / 53e3 * (bn != 192 ? 1.0 : bm == 256 ? 1.15 : 1.04), busy = (double)tiles / (double)(rounds * RESIDENT);
+    if (c != 0) start = 3.0 + 6.0 * (double)(bm * bn) / 65536.0;
+    return (double)rounds * (start + (double)ksteps * step * (1.0 - 0.22 * (1.0 - busy)));
+}
+
+// Tile of a product of whole tiles.  On operands as stored a round of the 256 x 256 kernel takes 2 us longer than from k-contiguous ones: over
+// 1332 gradients (256 to 16384 tokens, widths 200 to 36864; times from memory, each on 6 to 8 tiles) the tile chosen is 0.3 % longer than the best
+// in the mean, 21 % at most, without the 2 us 0.7 % and 25 % (1264 tokens, 2048 x 11520 58 us on 256 x 192, 73 on 256 x 256).  Over 752 products
+// from k-contiguous operands, on none of which the line was drawn, it is 0.4 % and 16 %.  (With a factor of a twelfth on its k-steps instead, for both
+// layouts, 0.8 % and 20 %: 1232, 8000 x 5184 92 us on 256 x 256, 111 on 256 x 192.)  Up to three k-steps, where
+// results take most of the time, it has no such handicap (130 tokens, 18432 x 16384 253 us, on 256 x 192 267).
+static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool as_stored) {
     int best = 0;
-    double least = 1e300;
-    for (int c = 0; c < (int)(sizeof(DENSE_TILES) / sizeof(DENSE_TILES[0])); ++c) {
-        const int bm = DENSE_TILES[c].bm, bn = DENSE_TILES[c].bn;
-        const int64_t tm = (m + bm - 1) / bm, tn = (n + bn - 1) / bn, tiles = tm * tn, rounds = (tiles + RESIDENT - 1) / RESIDENT;
-        const double step = 128.0 * (double)(bm + bn) / 53e3 * (bn != 192 ? 1.0 : bm == 256 ? 1.15 : 1.04), start = 3.0 + 6.0 * (double)(bm * bn) / 65536.0;
-        const double busy = (double)tiles / (double)(rounds * RESIDENT);
-        double us = (double)rounds * (start + (double)ksteps * step * (c == 0 ? 1.08 : 1.0) * (1.0 - 0.22 * (1.0 - busy)));
-        if (c == 0 && with_tail) {
-            const TailPlan p = tail_plan(tm, tn, ksteps);
-            if (p.tiles) us = (double)(tiles / RESIDENT) * (start + (double)ksteps * step) + 1.3 * p.steps + 16.0;
-        }
+    double least = dense_tile_us(0, m, n, ksteps, as_stored && ksteps > 3 ? 11.0 : 9.0);
+    for (int c = 1; c < (int)(sizeof(DENSE_TILES) / sizeof(DENSE_TILES[0])); ++c) {
+        const double us = dense_tile_us(c, m, n, ksteps);
         if (us < least) { least = us; best = c; }
     }
     return best;
+}
+
+// Cutting what is left over after the whole rounds is estimated to be no longer than whole tiles of another shape.  Scratch of the calls follows
+// from it, so that this estimate stays as it is, whatever becomes of the kernels.
+static bool cutting_pays(int64_t m, int64_t n, int64_t ksteps, const TailPlan& p) {
+    const int64_t rounds = ((m + 255) / 256) * ((n + 255) / 256) / RESIDENT;
+    const double cut = (double)rounds * (9.0 + (double)ksteps * (128.0 * 512.0 / 53e3)) + 1.3 * p.steps + 16.0;
+    for (int c = 1; c < (int)(sizeof(DENSE_TILES) / sizeof(DENSE_TILES[0])); ++c)
+        if (dense_tile_us(c, m, n, ksteps) < cut) return false;
+    return true;
 }
 
 template <int EPI, bool AKM, bool BKM>
@@ -963,7 +975,7 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
     const int64_t whole = ((d_in + 255) / 256) * ((d_out + 255) / 256) / RESIDENT * 512 * 100;
     const int64_t cut = whole + (int64_t)(512.0 * 100.0 * p.steps / (double)(ksteps + 6));
     if (cut > rows(256, 128) || cut > rows(128, 128) || cut > rows(128, 64)) return 0;
-    if (dense_tile_choice(d_in, d_out, ksteps, true) != 0) return 0;
+    if (!cutting_pays(d_in, d_out, ksteps, p)) return 0;
     return (size_t)p.parts * (size_t)p.bundle * (256 * 256 * 4);
 }
 
@@ -972,7 +984,7 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
 hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b, const uint8_t* meta, int64_t d_out,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s) {
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
-    const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
+    const int tile = tail_or_null ? 0 : dense_tile_choice(d_in, d_out, bp / 64, false);
     return launch_dense_tile<EPI_MASKED_PACKED, false, false>(tile, {Xt, (int)d_in, (int)ld, (int)bp}, {dYt, (int)d_out, (int)ld, (int)bp}, bp / 64, meta, gvals, s, tail_or_null);
 }
 
@@ -985,8 +997,8 @@ hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b,
 // neither copied, X, dY, both: 8192 x 8192 1486, 1513, 1537, 1605; 36864 x 9216 7700, 7287, 7691, 7522; 9216 x 36864 7802, 7713, 7539,
 // 7610; 16384 x 16384 6022, 5926, 6014, 6057: the rule loses 2 % there, elsewhere nothing).
 enum { COPY_X = 1, COPY_DY = 2 };
-static int wgrad_copies(int64_t b, int64_t d_in, int64_t d_out, bool with_tail) {
-    if (d_in % 32 != 0 || dense_tile_choice(d_in, d_out, (b + 63) / 64, with_tail) != 0) return 0;
+static int wgrad_copies(int64_t d_in, int64_t d_out, int tile) {
+    if (d_in % 32 != 0 || tile != 0) return 0;
     const double product = 2.0 * (double)d_out * (double)d_in / 1.5e9, x = 4.0 * (double)d_in / 5.9e6, dy = 4.0 * (double)d_out / 5.9e6;   // us per token
     const double cost[4] = {0.088 * product, x + 0.032 * product, dy + 0.042 * product, x + dy};
     int best = 0;
@@ -1005,8 +1017,8 @@ hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, con
     if (too_wide(d_in, d_out)) return launch_wgrad_wide(dY, X, b, meta, d_out, d_in, gvals, s);
     if (wgrad_in_groups(b, d_in, d_out)) return launch_wgrad_groups(dY, X, b, meta, d_out, d_in, gvals, s);
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
-    const int tile = dense_tile_choice(d_in, d_out, bp / 64, tail_or_null != nullptr);
-    const int copies = Xt && dYt ? wgrad_copies(b, d_in, d_out, tail_or_null != nullptr) : 0;
+    const int tile = tail_or_null ? 0 : dense_tile_choice(d_in, d_out, bp / 64, true);
+    const int copies = Xt && dYt ? wgrad_copies(d_in, d_out, tile) : 0;
     const DenseOperand x = copies & COPY_X ? DenseOperand{Xt, (int)d_in, (int)ld, (int)bp} : DenseOperand{X, (int)d_in, (int)d_in, (int)b};
     const DenseOperand dy = copies & COPY_DY ? DenseOperand{dYt, (int)d_out, (int)ld, (int)bp} : DenseOperand{dY, (int)d_out, (int)d_out, (int)b};
     if (copies) {

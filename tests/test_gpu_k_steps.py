@@ -61,6 +61,23 @@ def test_weight_gradient_row_ends(b, d_out, d_in, tile):
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
 
 
+# Long contractions on a partial round of 256 x 256 tiles stay on them, whatever the operands' layout, short ones on more than a round of them
+# do not: (call, rows of B or tokens, rows of A or d_out, contraction or d_in)
+@pytest.mark.parametrize("call,b,d_out,d_in,kernel", [("gemm", 2242, 4352, 6400, "dense_tn_split_kernel"), ("gemm", 1232, 8000, 5184, "dense_tn_split_kernel"),
+                                                      ("wgrad", 6655, 18688, 512, "dense_tn_split_kernel"), ("wgrad", 9532, 1536, 7680, "dense_tn_split_kernel"),
+                                                      ("wgrad", 1264, 2048, 11520, (256, 192)), ("wgrad", 1401, 11520, 2048, (256, 192))])
+def test_tile_of_a_dense_product(call, b, d_out, d_in, kernel):
+    print(f"{call} b={b} d_out={d_out} d_in={d_in}", flush=True)
+    X = gauss(b, d_in)
+    if call == "gemm":
+        A = gauss(d_out, d_in)
+        got = tiles(lambda: sl.slope_gemm_tn(X, A))
+    else:
+        dY, meta = gauss(b, d_out), sl.slope_prune_rows(gauss(d_out, d_in))[1]
+        got = tiles(lambda: sl.slope_wgrad_masked(dY, X, meta))
+    assert got[-1] == ("dense_tn_kernel", kernel) if isinstance(kernel, tuple) else got[-1][0] == kernel
+
+
 # sparse products without an adapter or scratch for slabs, by tile (weight rows x tokens): the ring kernel's pairs, odd ends of them, blocks of
 # metadata; the other kernel's quads and what is left of them.  (64 x 64, the generic kernel's form for whole pairs of k-steps, is
 # the 128 x 64 tile's neighbour: 21 k-steps are on that one.)
