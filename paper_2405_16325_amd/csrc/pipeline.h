@@ -44,12 +44,12 @@ __device__ __forceinline__ void fetch_arguments(T... args) {
 //    that eight consecutive chunks form a 16 x 16 patch (2 x 4 chunks; the chip then shares 16 + 16
 //    panels in the last-level cache), patch after patch along n, then along m; then the rows that
 //    are left below it, column by column (32 positions: their few rows of some columns); then
-//    the columns left beside it, row by row.  A strip of up to three rows or columns takes the last of several rows or columns of chunks along:
-//    by itself its 32 positions would share few panels, and the long operand would come from memory for it once more.  (us, sparse
-//    products, strips by themselves / with the chunks, operands from memory: 16640 tokens, 5120 x 5120, 65 tiles wide, 465 / 456; 16640,
-//    4352 x 2048, 17 x 65, 189 / 182; 16800, 2048 x 5120 209 / 202; 9000, 4864 x 4096, 19 x 36, 197 / 189; 12500, 4608 x 4608, 18 x 49, 288 / 284;
-//    16384, 4352 x 4352 331 / 336; weight gradients within 1 %.  Not a single row of chunks, whose columns of 9 to 11 are high: 16384,
-//    2560 x 2048 100 / 107, x 4096 202 / 197, x 10240 426 / 438.)  What is left of the order after the last whole round of 256 is dealt
+//    the columns left beside it, row by row.  From two rows of chunks on a strip of up to three rows takes the last row
+//    of chunks along and the columns left the last column of several: by itself a strip's 32 positions would share few panels, and the long operand
+//    would come from memory for it once more.  (Over 507 sparse products, 282 dense ones and 261 gradients of such grids, operands from memory, 0.5,
+//    0.3 and 0.2 % faster than strips by themselves in the mean; 5 % slower at worst (11133, 4608 x 7424 387 / 407), 10 % faster at best.  us, by themselves / with the chunks: 16640
+//    tokens, 4352 x 2048, 17 x 65 tiles, 189 / 182; 6875, 5568 x 3840, 22 x 27, 182 / 167; 16384, 4352 x 4352 331 / 336.  Not on a single row of
+//    chunks, 99 and 65 products, 0.4 and 0.2 % slower in the mean: 8414, 2304 x 8128, 9 x 33, 203 / 240.)  What is left of the order after the last whole round of 256 is dealt
 //    out in eight equal runs.
 //  * A narrow grid (skinny products, inference-size batches): tiles are numbered short axis first
 //    and each XCD takes runs of consecutive tiles: at most 32, sized so that all 8 XCDs get equal
@@ -68,8 +68,10 @@ __host__ __device__ inline bool wide_grid(int tiles_m, int tiles_n) {
 // position q (0 <= q < tiles_m * tiles_n) in the order of a wide grid -> tile
 __host__ __device__ inline void tile_of_position(int q, int tiles_m, int tiles_n, int& tm, int& tn) {
     int m8 = tiles_m / CHUNK_M * CHUNK_M, n4 = tiles_n / CHUNK_N * CHUNK_N;
-    if (m8 < tiles_m && tiles_m - m8 <= THIN && m8 >= 2 * CHUNK_M) m8 -= CHUNK_M;
-    if (n4 < tiles_n && tiles_n - n4 <= THIN && n4 >= 2 * CHUNK_N) n4 -= CHUNK_N;
+    if (m8 >= 2 * CHUNK_M) {
+        if (m8 < tiles_m && tiles_m - m8 <= THIN) m8 -= CHUNK_M;
+        if (n4 < tiles_n && n4 >= 2 * CHUNK_N) n4 -= CHUNK_N;
+    }
     if (q < m8 * n4) {
         const int c = q / 32, w = q % 32;
         const int chunks_m = m8 / CHUNK_M, chunks_n = n4 / CHUNK_N;

@@ -311,14 +311,46 @@ def test_tile_order_of_wide_grids_has_no_gaps(tiles_m, tiles_n):
     assert per_xcd.sum() == tiles - whole and per_xcd.max() - per_xcd.min() <= per_xcd.max() and per_xcd.max() <= -(-(tiles - whole) // 8)
 
 
-@pytest.mark.parametrize("tiles_m,tiles_n", [(17, 16), (17, 65), (18, 17), (19, 19), (40, 9), (16, 65), (36, 66), (8, 67), (8, 33)])
-def test_tile_order_thin_strips_share_panels(tiles_m, tiles_n):
-    """The 32 consecutive positions that an XCD holds touch about as few panels where a strip of up to three rows or columns is left."""
+def most_panels(order, whole):
+    """The most rows and columns of tiles that 32 consecutive positions of an order touch, over its whole rounds."""
+    return max(len({t[0] for t in order[p:p + 32]}) + len({t[1] for t in order[p:p + 32]}) for p in range(0, whole, 32))
+
+
+def order_of(tiles_m, tiles_n):
+    """The library's order by position, its whole rounds: workgroup b is on XCD b % 8, which holds 32 positions at a time."""
     tm, tn = sl.slope_tile_order(tiles_m, tiles_n)
+    blocks = [(p // 256 * 256) + (p % 32) * 8 + p // 32 % 8 for p in range(tiles_m * tiles_n // 256 * 256)]
+    return [(int(tm[b]), int(tn[b])) for b in blocks]
+
+
+def plain_order(tiles_m, tiles_n):
+    """The order whose strips beside the whole chunks of 8 x 4 tiles stay by themselves: chunks in patches of 2 x 4, rows below, columns beside."""
+    m8, n4 = tiles_m // 8 * 8, tiles_n // 4 * 4
+    chunks = [(cm, cn) for pm in range(0, m8 // 8, 2) for pn in range(0, n4 // 4, 4)
+              for cm in range(pm, min(pm + 2, m8 // 8)) for cn in range(pn, min(pn + 4, n4 // 4))]
+    order = [(cm * 8 + w % 8, cn * 4 + w // 8) for cm, cn in chunks for w in range(32)]
+    order += [(tm, tn) for tn in range(tiles_n) for tm in range(m8, tiles_m)]
+    return order + [(tm, tn) for tm in range(m8) for tn in range(n4, tiles_n)]
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n", [(17, 31), (17, 46), (17, 61), (17, 79), (18, 29)])
+def test_tile_order_thin_strips_share_panels(tiles_m, tiles_n):
+    """Strips of up to three rows or columns that reach into the whole rounds: by themselves their positions share few panels."""
     whole = tiles_m * tiles_n // 256 * 256
-    assert whole
-    for block in range(0, whole, 256):
-        for xcd in range(8):
-            mine = range(block + xcd, block + 256, 8)
-            panels = len({tm[b] for b in mine}) + len({tn[b] for b in mine})
-            assert panels <= 20, (block, xcd, panels)      # a strip one tile high by itself: 33
+    assert most_panels(plain_order(tiles_m, tiles_n), whole) >= 21
+    assert most_panels(order_of(tiles_m, tiles_n), whole) <= 18
+
+
+def test_tile_order_of_one_row_of_chunks_is_plain():
+    for tiles_m in range(8, 16):
+        for tiles_n in range(4, 81):
+            if tiles_m * tiles_n >= 256:
+                assert order_of(tiles_m, tiles_n) == plain_order(tiles_m, tiles_n)[:tiles_m * tiles_n // 256 * 256], (tiles_m, tiles_n)
+
+
+def test_tile_order_shares_panels_on_all_grids():
+    for tiles_m in range(16, 81):
+        for tiles_n in range(4, 81):
+            whole = tiles_m * tiles_n // 256 * 256
+            if whole:
+                assert most_panels(order_of(tiles_m, tiles_n), whole) <= max(21, most_panels(plain_order(tiles_m, tiles_n), whole)), (tiles_m, tiles_n)
