@@ -515,7 +515,8 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
 #pragma unroll
         for (int i = 0; i < 2 * T_LD; ++i) {
             const int g = wave * T_LD + i % T_LD, rl = g * 8 + (lane >> 3), step = i / T_LD;
-            dma16((const uint8_t*)B + (size_t)wrap_row_near(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)(k_first + step) * 128,
+            const int kc = TAIL && step >= ksteps ? 0 : step;    // one k-step: again rather than past the row's end
+            dma16((const uint8_t*)B + (size_t)wrap_row_near(n0 + rl, n) * K * 2 + (((lane & 7) ^ ((rl >> 1) & 7)) * 16) + (size_t)(k_first + kc) * 128,
                   smem + S::B_OFF + step * S::B_STAGE + g * 1024);
         }
         WAIT_HERE(waitcnt_imm(T_LD, 15));
