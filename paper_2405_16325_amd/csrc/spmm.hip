@@ -1503,8 +1503,8 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // with few compute units at work), and takes longer for weight bytes that come from HBM: those that few token tiles share.
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
 // The constants were fitted on weights from HBM and on tiles that read a k-step before they multiplied it, and before wavefronts that
-// only load, which take up to 15 % off the tiles up to 256 x 128 (over 70 shapes the whole tile chosen is now 0.6 % longer than the best in the
-// mean, 8 % at most; the line of LONGEST_OF_64 was drawn on the same shapes).  Before those, against them the kernels
+// only load, which take up to 15 % off the tiles up to 256 x 128 (over 70 shapes, most of them in the last-level cache, the whole tile chosen
+// is 2.5 % longer than the best in the mean, 21.8 % at most, mostly for 64 x 64: see spmm_tile_choice).  Before those, against them the kernels
 // took 1.02 (128 x 128) to 1.18 (256 x 192) of the estimate on such weights, 0.91 to 1.12 on those from the cache: over 110
 // shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128 to 20000), each on five whole tiles and four splits of low
 // estimate, the form chosen takes 1.2 % longer than the best one in the mean, more than 10 % in one (65 tokens, 21888 x 7232),
@@ -1661,22 +1661,17 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
 
 int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RESIDENT ? 64 : 128; }
 
-// Where the estimate prefers 64 x 64 tiles on a contraction of more k-steps than this, the ring kernel with its loader wavefronts is the
-// faster one on 128 x 64 (us, from memory, 64 x 64 / 128 x 64: 256 tokens, 2496 x 1920 10.9 / 9.9; 320, 640 x 1664 9.7 / 8.6; 303, 768 x 4096 17.1 /
-// 15.0; 1325, 512 x 6016 26.1 / 21.6; 153, 1536 x 11520 41.1 / 37.0; all 11 such of 70 shapes are 8 to 22 % faster so; three with at
-// most 12 k-steps are 16 and 12 % slower and 3 % faster).  Not up to 64 rows, where half of the taller tile is nothing.
-constexpr int64_t LONGEST_OF_64 = 16 * 64;
-
+// Where the estimate prefers 64 x 64 tiles, the ring kernel's 128 x 64, half as many workgroups, is the faster one only on operands from the
+// last-level cache without an adapter (5 % in the mean).  us, 64 x 64 / 128 x 64: 600 tokens, 512 x 2304 with weights from HBM and tokens
+// from the cache 12.6 / 14.2, all from HBM 13.4 / 14.6; 600, 512 x 1792 with rank 64, all from HBM, 20.5 / 23.4.  Over 322 shapes with 18 k-steps and more all
+// from HBM 6 % slower, 252 with the weights from HBM 6 %, 168 with rank 64 10 %.
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel, whose whole pairs of
 // k-steps on a round of 64 x 64 tiles count as a tile shape of their own.
 void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
     bm = bn = 0;
     if (!tile_kernel_fits(K)) return;
     best_tile_us(n, m, K, bm, bn);
-    if (bm != 64) return;
-    // (whether a product is split is decided by the estimate as it stands)
-    if (K > LONGEST_OF_64 && m > 64) { bm = 128; bn = 64; }
-    else if (K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
+    if (bm == 64 && K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
 }
 
 // Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 6 us for its launch and
