@@ -73,8 +73,9 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
         const uint8_t* tr = smem + (8 * lq + (l16 >> 2)) * PITCH + 2 * (f0 - tile_f0 + 4 * (l16 & 3));
         // pieces of the staged chunk per thread: a compile-time count, so that all of a thread's global loads are
         // in flight together (a loop of load, wait, LDS store per piece pays the L2 latency once per piece)
-        // (at most eight: the accumulators are most of the registers of a wavefront with a quarter of a large tile)
-        constexpr int PER = 128 * SEG / THREADS, ROUNDS = (PER + 7) / 8, EACH = PER / ROUNDS;
+        // (at most twelve: the accumulators are most of the registers of a wavefront with a quarter of a 256 x 128 tile, which would
+        // spill; us on 192 x 128, in two rounds of six / one: 2078 tokens, 2560 x 256, rank 256 19.5 / 19.1)
+        constexpr int PER = 128 * SEG / THREADS, ROUNDS = (PER + 11) / 12, EACH = PER / ROUNDS;
         constexpr int FIRST = THREADS < 512 && MF * NF > 24 ? 0 : 2;   // steps whose token-side fragments are requested before the pieces
         static_assert(128 * SEG % THREADS == 0 && PER % ROUNDS == 0, "whole pieces per thread and round");
         for (int kc = 0; kc < KR; kc += 128) {
@@ -139,27 +140,39 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
             int row = t0 + j * 16 + l16;
             b_row[j] = B2 + (size_t)wrap_row(row, n) * K2 + lq * 8;
         }
-        constexpr int AHEAD = THREADS >= 512 || MF * NF <= 16 ? 1 : 0;   // as above: no room for the operands of two steps beside larger tiles' sums
-        AFrag a2[2][MF], b2[2][NF];
-#pragma unroll
-        for (int i = 0; i < MF; ++i) a2[0][i].u = *(const u32x4*)(a_row[i]);
+        // Beside a large tile's sums there is no room for the features of two steps: a fragment of the next step is then loaded into
+        // the registers of the same one as soon as its products are queued.  (us, from memory, each step's loads after the products before it / so: 5658
+        // tokens, 768 x 256, rank 160 on 192 x 96 19.9 / 16.1; 11469, 512 x 256, rank 160 on 256 x 128 27.2 / 20.6; 664, 5888 x 3072, rank 160 47.3 / 40.9)
+        constexpr bool IN_PLACE = THREADS < 512 && MF * NF > 16;
+        constexpr int A_SETS = IN_PLACE ? 1 : 2;
+        AFrag a2[A_SETS][MF], b2[2][NF];
 #pragma unroll
         for (int j = 0; j < NF; ++j) b2[0][j].u = *(const u32x4*)(b_row[j]);
+#pragma unroll
+        for (int i = 0; i < MF; ++i) a2[0][i].u = *(const u32x4*)(a_row[i]);
         for (int k0 = 0; k0 < K2; k0 += 64) {                 // K2 % 32 == 0: two steps per trip, the second maybe absent
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int kk = k0 + 32 * h;                   // uniform
                 if (kk >= K2) break;
-                const int kn = AHEAD && kk + 32 < K2 ? kk + 32 : kk;   // the last step re-reads itself (unused)
+                const int kn = kk + 32 < K2 ? kk + 32 : kk;   // the last step re-reads itself (unused)
+                if (!IN_PLACE) {
 #pragma unroll
-                for (int i = 0; i < MF; ++i) a2[h ^ AHEAD][i].u = *(const u32x4*)(a_row[i] + kn);
+                    for (int i = 0; i < MF; ++i) a2[(h ^ 1) % A_SETS][i].u = *(const u32x4*)(a_row[i] + kn);
+                }
 #pragma unroll
-                for (int j = 0; j < NF; ++j) b2[h ^ AHEAD][j].u = *(const u32x4*)(b_row[j] + kn);
+                for (int j = 0; j < NF; ++j) b2[h ^ 1][j].u = *(const u32x4*)(b_row[j] + kn);
+                if (IN_PLACE) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < MF; ++i)
+                for (int i = 0; i < MF; ++i) {
 #pragma unroll
                     for (int j = 0; j < NF; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[h][i].v, b2[h][j].v, acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[h % A_SETS][i].v, b2[h][j].v, acc[i][j], 0, 0, 0);
+                    if (IN_PLACE) {
+                        a2[0][i].u = *(const u32x4*)(a_row[i] + kn);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
             }
         }
     }

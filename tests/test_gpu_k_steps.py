@@ -98,6 +98,26 @@ def test_sparse_product(b, d_out, tile, ksteps):
     assert_all_close(sl.slope_spmm_fwd(X, vals, meta), want, "Y")
 
 
+# the adapter's extension where four wavefronts multiply: the factor along the features (forward) and along the ranks (input gradient), one
+# step of 32 ranks, an even and an odd number of them, more than a chunk of 128; ragged at both edges
+@pytest.mark.parametrize("r", [32, 96, 128, 160])
+@pytest.mark.parametrize("b,rows,tile", [(700, 4168, (192, 64)), (1500, 3064, (192, 96)), (2040, 3000, (192, 128)), (2040, 3896, (256, 128)),
+                                         (1500, 2040, (128, 96)), (2000, 1928, (128, 128))])
+def test_adapter_of_a_sparse_product(b, rows, tile, r):
+    print(f"spmm with adapter b={b} rows={rows} r={r}", flush=True)
+    X, W = gauss(b, 256), gauss(rows, 256)
+    vals, meta, mask = sl.slope_prune_rows(W, want_mask=True)
+    base = X.float() @ torch.where(unpack_bits(mask), W, torch.zeros_like(W)).float().t()
+    L, R = gauss(256, r), gauss(r, rows) * 0.125
+    want = base + (X.float() @ L.float()).to(torch.bfloat16).float() @ R.float()
+    assert tiles(lambda: sl.slope_spmm_fwd(X, vals, meta, L, R))[-1][1] == tile
+    assert_all_close(sl.slope_spmm_fwd(X, vals, meta, L, R), want, "Y", two_stage=True)
+    L, R = gauss(rows, r) * 0.125, gauss(r, 256)
+    want = base + (X.float() @ R.float().t()).to(torch.bfloat16).float() @ L.float().t()
+    assert tiles(lambda: sl.slope_spmm_bwd_x_adapter(X, vals, meta, L, R))[-1][1] == tile
+    assert_all_close(sl.slope_spmm_bwd_x_adapter(X, vals, meta, L, R), want, "dX", two_stage=True)
+
+
 # blocks of metadata (8 k-steps) that end inside the contraction: 256 x 256 tiles, slabs of 20 k-steps
 @pytest.mark.parametrize("b,d_out,ksteps", [(4090, 4088, k) for k in (2, 3, 4, 5, 7, 8, 9, 11, 12, 13, 16, 17)] + [(128, 9216, 120)])
 def test_metadata_blocks_of_a_sparse_product(b, d_out, ksteps):
