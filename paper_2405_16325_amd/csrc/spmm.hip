@@ -866,11 +866,11 @@ struct RingSmem {
     static_assert(STAGES >= 3 && M_BLOCK % 1024 == 0, "a ring");
 };
 
-// Loads of the STAGES - 2 pairs after the pair with index u in its block of metadata: what may be in flight while that pair is read
+// Loads of the `pairs` pairs after the pair with index u in its block of metadata: what may be in flight while that pair is read
 template <class S>
-constexpr int ring_leave(int u, int each, int meta) {
+constexpr int ring_leave(int u, int pairs, int each, int meta) {
     int c = 0;
-    for (int q = 1; q <= S::STAGES - 2; ++q) c += each + ((u + q) % S::META_PAIRS == 0 ? meta : 0);
+    for (int q = 1; q <= pairs; ++q) c += each + ((u + q) % S::META_PAIRS == 0 ? meta : 0);
     return c;
 }
 
@@ -970,11 +970,16 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
         for (int p = 1; p < S::STAGES - 1; ++p)
             if (p < pairs) issue(p, p, p % META_PAIRS == 0);
         int stage = S::STAGES - 1;
-        // pair p, with index u in its block of metadata, has landed (in the last STAGES - 2 pairs there are fewer loads behind it: then
-        // all are waited for) and everybody has read the one before it, whose stage is filled again
+        // pair p, with index u in its block of metadata, has landed, with up to STAGES - 2 pairs still behind it, and everybody has read the
+        // one before it, whose stage is filled again.  (Where fewer than STAGES - 2 follow, waiting for all of them, with one wavefront per
+        // SIMD left to multiply, made contractions of 256 slower than with eight: us, eight / four, all / four, so: 1889 tokens, 768 x 256 on 128 x
+        // 64 4.7 / 5.1 / 4.7; over 61 products of contractions up to 1024 on that tile 2 % slower, now 2 % faster in the mean.)
         auto pair = [&](int p, auto index) {
-            constexpr int u = decltype(index)::value, leave = ring_leave<S>(u, A_LD + 2 * B_LD, M_LD);
-            if (p + S::STAGES - 2 < pairs) WAIT_HERE(waitcnt_imm(leave, 15));
+            constexpr int u = decltype(index)::value, EACH = A_LD + 2 * B_LD, BEHIND = S::STAGES - 2;
+            static_assert(BEHIND >= 1 && BEHIND <= 3, "each number of pairs has its wait");
+            if (p + BEHIND < pairs) WAIT_HERE(waitcnt_imm(ring_leave<S>(u, BEHIND, EACH, M_LD), 15));
+            else if (BEHIND > 2 && p + 2 < pairs) WAIT_HERE(waitcnt_imm(ring_leave<S>(u, 2, EACH, M_LD), 15));
+            else if (BEHIND > 1 && p + 1 < pairs) WAIT_HERE(waitcnt_imm(ring_leave<S>(u, 1, EACH, M_LD), 15));
             else WAIT_HERE(waitcnt_imm(0, 15));
             wg_barrier();
             if (p + S::STAGES - 1 < pairs) issue(p + S::STAGES - 1, stage, (u + S::STAGES - 1) % META_PAIRS == 0);
