@@ -914,29 +914,39 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
 // of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 are 10 to 30 % faster
 // than that by now; the order of the estimates, which is all that counts, has held.
-// `start`: what a round of the 256 x 256 kernel takes beside its k-steps.
-static double dense_tile_us(int c, int64_t m, int64_t n, int64_t ksteps, double start = 9.0) {
+// `start` and `slower`: what a round of the 256 x 256 kernel takes beside its k-steps, and the factor on these.
+static double dense_tile_us(int c, int64_t m, int64_t n, int64_t ksteps, double start = 9.0, double slower = 1.0) {
     const int bm = DENSE_TILES[c].bm, bn = DENSE_TILES[c].bn;
     const int64_t tiles = ((m + bm - 1) / bm) * ((n + bn - 1) / bn), rounds = (tiles + RESIDENT - 1) / RESIDENT;
     const double step = 128.0 * (double)(bm + bn) / 53e3 * (bn != 192 ? 1.0 : bm == 256 ? 1.15 : 1.04), busy = (double)tiles / (double)(rounds * RESIDENT);
-    if (c != 0) start = 3.0 + 6.0 * (double)(bm * bn) / 65536.0;
-    return (double)rounds * (start + (double)ksteps * step * (1.0 - 0.22 * (1.0 - busy)));
+    if (c != 0) { start = 3.0 + 6.0 * (double)(bm * bn) / 65536.0; slower = 1.0; }
+    return (double)rounds * (start + (double)ksteps * step * slower * (1.0 - 0.22 * (1.0 - busy)));
 }
 
-// Tile of a product of whole tiles.  On operands as stored a round of the 256 x 256 kernel takes 2 us longer than from k-contiguous ones: over
-// 1332 gradients (256 to 16384 tokens, widths 200 to 36864; times from memory, each on 6 to 8 tiles) the tile chosen is 0.3 % longer than the best
-// in the mean, 21 % at most, without the 2 us 0.7 % and 25 % (1264 tokens, 2048 x 11520 58 us on 256 x 192, 73 on 256 x 256).  Over 752 products
-// from k-contiguous operands, on none of which the line was drawn, it is 0.4 % and 16 %.  (With a factor of a twelfth on its k-steps instead, for both
-// layouts, 0.8 % and 20 %: 1232, 8000 x 5184 92 us on 256 x 256, 111 on 256 x 192.)  Up to three k-steps, where
-// results take most of the time, it has no such handicap (130 tokens, 18432 x 16384 253 us, on 256 x 192 267).
-static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, bool as_stored) {
+// Tile of a product of whole tiles.  Where 256 x 256 and 256 x 192 have as many rounds, the former is the faster one on operands from HBM and the latter
+// on operands from the last-level cache, by 5 to 18 % each (us, 256 x 192 / 256 x 256: gradient of 12606 tokens, 5120 x 2048 240 / 285 cached, 253 /
+// 231 from HBM; masked dense 4674 tokens, 5120 x 8192 292 / 323, 332 / 312).
+//  - k-contiguous operands, masked dense weights: as from HBM.  Also right behind the kernel that makes the weights other traffic has passed through the
+//    cache (16 steps of 1000 to 16000 tokens 0 to 15 % faster than with 256 x 192: 3613 tokens, 5632 x 5888 524 / 457; 1232, 8000 x 5184 295 / 276).
+//  - operands as stored, gradients: dY has just been read for the input gradient, and X is still there if it is not more than half of the cache.
+//    Then a twelfth more for the k-steps of 256 x 256 (`cached`; us, forward and both gradients of one layer: 11959 tokens, 3072 x 3328 502 / 543; 3867, 4608 x 2048 169 /
+//    182; of 400 steps of 512 to 16384 tokens the 22 that it concerns are up to 8 % faster, one 1 % slower; with X from HBM the gradient alone loses: 4068, 2560 x 3840 87 / 80).  Else a round takes 2 us
+//    longer than from k-contiguous ones from the fourth k-step on (over 1332 gradients from memory the tile chosen so is 0.3 % longer than the
+//    best in the mean, 21 % at most; us, forward and both gradients: 15599, 2048 x 5120 696 / 669).
+enum DenseFrom { K_CONTIGUOUS, AS_STORED, AS_STORED_CACHED };
+static int dense_tile_choice(int64_t m, int64_t n, int64_t ksteps, DenseFrom from) {
     int best = 0;
-    double least = dense_tile_us(0, m, n, ksteps, as_stored && ksteps > 3 ? 11.0 : 9.0);
+    if (ksteps <= 3) from = K_CONTIGUOUS;                     // results take most of the time
+    double least = dense_tile_us(0, m, n, ksteps, from == AS_STORED ? 11.0 : 9.0, from == AS_STORED_CACHED ? 1.08 : 1.0);
     for (int c = 1; c < (int)(sizeof(DENSE_TILES) / sizeof(DENSE_TILES[0])); ++c) {
         const double us = dense_tile_us(c, m, n, ksteps);
         if (us < least) { least = us; best = c; }
     }
     return best;
+}
+static DenseFrom gradient_operands(int64_t b, int64_t d_in, int64_t d_out) {
+    const bool cached = (size_t)(2 * b * d_in) <= LAST_LEVEL_CACHE_BYTES / 2 && (size_t)(2 * b * (d_in + d_out)) <= LAST_LEVEL_CACHE_BYTES;
+    return cached ? AS_STORED_CACHED : AS_STORED;
 }
 
 // Cutting what is left over after the whole rounds is estimated to be no longer than whole tiles of another shape.  Scratch of the calls follows
@@ -984,7 +994,7 @@ size_t wgrad_tail_bytes(int64_t b, int64_t d_in, int64_t d_out) {
 hipError_t launch_wgrad_masked_t(const bf16_t* dYt, const bf16_t* Xt, int64_t b, const uint8_t* meta, int64_t d_out,
                                  int64_t d_in, bf16_t* gvals, float* tail_or_null, hipStream_t s) {
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
-    const int tile = tail_or_null ? 0 : dense_tile_choice(d_in, d_out, bp / 64, false);
+    const int tile = tail_or_null ? 0 : dense_tile_choice(d_in, d_out, bp / 64, K_CONTIGUOUS);
     return launch_dense_tile<EPI_MASKED_PACKED, false, false>(tile, {Xt, (int)d_in, (int)ld, (int)bp}, {dYt, (int)d_out, (int)ld, (int)bp}, bp / 64, meta, gvals, s, tail_or_null);
 }
 
@@ -1017,7 +1027,7 @@ hipError_t launch_wgrad_masked(const bf16_t* dY, const bf16_t* X, int64_t b, con
     if (too_wide(d_in, d_out)) return launch_wgrad_wide(dY, X, b, meta, d_out, d_in, gvals, s);
     if (wgrad_in_groups(b, d_in, d_out)) return launch_wgrad_groups(dY, X, b, meta, d_out, d_in, gvals, s);
     const int64_t bp = (b + 63) / 64 * 64, ld = token_pitch(bp);
-    const int tile = tail_or_null ? 0 : dense_tile_choice(d_in, d_out, bp / 64, true);
+    const int tile = tail_or_null ? 0 : dense_tile_choice(d_in, d_out, bp / 64, gradient_operands(b, d_in, d_out));
     const int copies = Xt && dYt ? wgrad_copies(d_in, d_out, tile) : 0;
     const DenseOperand x = copies & COPY_X ? DenseOperand{Xt, (int)d_in, (int)ld, (int)bp} : DenseOperand{X, (int)d_in, (int)d_in, (int)b};
     const DenseOperand dy = copies & COPY_DY ? DenseOperand{dYt, (int)d_out, (int)ld, (int)bp} : DenseOperand{dY, (int)d_out, (int)d_out, (int)b};
@@ -1169,7 +1179,7 @@ hipError_t launch_skinny_factor(const bf16_t* B, int64_t n, int64_t K, const bf1
 // The same product for any shape (dense weights with a general N:M mask, where no sparse MFMA applies)
 hipError_t launch_dense_tn_any(const bf16_t* B, int64_t n, const bf16_t* A, int64_t m, int64_t K, bf16_t* C,
                                hipStream_t s) {
-    return launch_dense_tile<EPI_PLAIN, false, false>(dense_tile_choice(m, n, K / 64, false), {A, (int)m, (int)K, (int)K}, {B, (int)n, (int)K, (int)K}, K / 64, nullptr, C, s);
+    return launch_dense_tile<EPI_PLAIN, false, false>(dense_tile_choice(m, n, K / 64, K_CONTIGUOUS), {A, (int)m, (int)K, (int)K}, {B, (int)n, (int)K, (int)K}, K / 64, nullptr, C, s);
 }
 
 // ------------------------------------------------------------------------------------------

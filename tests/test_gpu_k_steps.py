@@ -61,11 +61,14 @@ def test_weight_gradient_row_ends(b, d_out, d_in, tile):
     assert_all_close(sl.slope_wgrad_masked(dY, X, meta), want, "dW")
 
 
-# Long contractions on a partial round of 256 x 256 tiles stay on them, whatever the operands' layout, short ones on more than a round of them
-# do not: (call, rows of B or tokens, rows of A or d_out, contraction or d_in)
+# Long contractions on a partial round of 256 x 256 tiles stay on them from k-contiguous operands and where X, more than 128 MiB of it, comes from
+# memory, but not where the operands of a gradient fit the last-level cache: (call, rows of B or tokens, rows of A or d_out, contraction or d_in)
 @pytest.mark.parametrize("call,b,d_out,d_in,kernel", [("gemm", 2242, 4352, 6400, "dense_tn_split_kernel"), ("gemm", 1232, 8000, 5184, "dense_tn_split_kernel"),
-                                                      ("wgrad", 6655, 18688, 512, "dense_tn_split_kernel"), ("wgrad", 9532, 1536, 7680, "dense_tn_split_kernel"),
-                                                      ("wgrad", 1264, 2048, 11520, (256, 192)), ("wgrad", 1401, 11520, 2048, (256, 192))])
+                                                      ("wgrad", 7100, 18688, 512, "dense_tn_split_kernel"), ("wgrad", 9532, 1536, 7680, "dense_tn_split_kernel"),
+                                                      ("wgrad", 1264, 2048, 11520, (256, 192)), ("wgrad", 1401, 11520, 2048, (256, 192)),
+                                                      ("wgrad", 3867, 4608, 2048, (256, 192)), ("wgrad", 12606, 5120, 2048, (256, 192)),
+                                                      ("wgrad", 15599, 2048, 5120, "dense_tn_split_kernel"), ("wgrad", 13106, 2048, 5120, (256, 192)),
+                                                      ("wgrad", 13108, 2048, 5120, "dense_tn_split_kernel")])
 def test_tile_of_a_dense_product(call, b, d_out, d_in, kernel):
     print(f"{call} b={b} d_out={d_out} d_in={d_in}", flush=True)
     X = gauss(b, d_in)
