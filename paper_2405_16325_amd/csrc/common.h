@@ -35,7 +35,7 @@ hipError_t launch_spmm(const bf16_t* B, int64_t n, const bf16_t* A_vals, const u
                        int64_t K, const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s);
 // the choices behind it (pure functions of the shape): tile of the tile kernels (0 x 0 = the generic kernel),
 // weight rows per workgroup of the small-batch kernel, chunks of 64 rows of L per slab that the scratch of X L is sized by
-void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn);
+void spmm_tile_choice(int64_t n, int64_t m, int64_t K, bool adapter, int& bm, int& bn);
 int spmm_generic_edge(int64_t n, int64_t m);                 // edge of the generic kernel's tile
 int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K);   // the last tokens, which the small-batch kernel takes (adapters: K2 <= 0)
 int spmm_stream_rows(int64_t n, int64_t m, int64_t K);

@@ -504,7 +504,7 @@ slope_status slope_spmm_fwd_plan(int64_t b, int64_t d_in, int64_t d_out, int64_t
         const SpmmSplit split = with_workspace ? fwd_split(b, d_in, d_out, r) : SpmmSplit{0, 0, 0};
         const int64_t rest = split.slabs > 0 ? 0 : spmm_rest_tokens(b, d_out, d_in);
         int bm, bn;
-        spmm_tile_choice(b - rest, d_out, d_in, bm, bn);
+        spmm_tile_choice(b - rest, d_out, d_in, r > 0, bm, bn);
         if (split.slabs > 0) { plan[0] = 1; plan[1] = split.bm; plan[2] = split.bn; plan[3] = split.slabs; }
         else if (bm == 0) { plan[0] = 3; plan[1] = plan[2] = spmm_generic_edge(b - rest, d_out); }
         else { plan[0] = 2; plan[1] = bm; plan[2] = bn; }

@@ -1522,7 +1522,7 @@ static bool ring_tile(int bm, int bn) { return bn <= 96 || (bm == 128 && bn == 1
 // With slabs: the k-steps of one, and the second launch, which reads what the first has written.
 // The constants were fitted on weights from HBM and on tiles that read a k-step before they multiplied it, and before wavefronts that
 // only load, which take up to 15 % off the tiles up to 256 x 128 (over 70 shapes, most of them in the last-level cache, the whole tile chosen
-// is 2.5 % longer than the best in the mean, 21.8 % at most, mostly for 64 x 64: see spmm_tile_choice).  Before those, against them the kernels
+// is 2.5 % longer than the best in the mean, 21.8 % at most, mostly where that is 64 x 64: see spmm_tile_choice).  Before those, against them the kernels
 // took 1.02 (128 x 128) to 1.18 (256 x 192) of the estimate on such weights, 0.91 to 1.12 on those from the cache: over 110
 // shapes of 33 to 6000 tokens (512 to 36864 rows, contractions of 128 to 20000), each on five whole tiles and four splits of low
 // estimate, the form chosen takes 1.2 % longer than the best one in the mean, more than 10 % in one (65 tokens, 21888 x 7232),
@@ -1679,17 +1679,29 @@ hipError_t launch_spmm_slabs(const bf16_t* B, int64_t n, const bf16_t* A_vals, c
 
 int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RESIDENT ? 64 : 128; }
 
-// Where the estimate prefers 64 x 64 tiles, the ring kernel's 128 x 64, half as many workgroups, is the faster one only on operands from the
-// last-level cache without an adapter (5 % in the mean).  us, 64 x 64 / 128 x 64: 600 tokens, 512 x 2304 with weights from HBM and tokens
-// from the cache 12.6 / 14.2, all from HBM 13.4 / 14.6; 600, 512 x 1792 with rank 64, all from HBM, 20.5 / 23.4.  Over 322 shapes with 18 k-steps and more all
-// from HBM 6 % slower, 252 with the weights from HBM 6 %, 168 with rank 64 10 %.
+// Where the estimate prefers 64 x 64 tiles on a contraction of more k-steps than this, the ring kernel on 128 x 64, with half as many workgroups, is the
+// faster one
+//  - where an odd last k-step leaves the generic kernel (us, generic / 128 x 64: 43 tokens, 4160 x 1728 15.2 / 12.3 on operands from the last-level
+//    cache, 15.3 / 13.2 from HBM; 37 products without an adapter are 17 and 13 % faster in the mean, 42 with one 6 and 3 %);
+//  - on operands from the last-level cache, more so the longer they are, while from HBM it is 5 % slower without an adapter, 7 to 10 % with one: so from the
+//    bytes of operands on where it gains more than it loses.  us, 64 x 64 / 128 x 64 cached and from HBM: 112 tokens, 512 x 1280 10.8 / 11.2 and
+//    9.2 / 10.3; 231, 1272 x 2432 15.0 / 14.1 and 14.0 / 15.5; 1214, 424 x 2432 16.1 / 14.1 and 14.7 / 15.4; 1019, 576 x 3328 20.4 / 16.8 and 18.9
+//    / 19.6.  Mean over 150 products without an adapter below / above the line: 0 / 11 % faster cached, 8 / 5 % slower from HBM; over 179 with one 0
+//    / 7 % faster cached, 9 / 7 % slower from HBM.
+constexpr int64_t LONGEST_OF_64 = 16 * 64;
+constexpr double FEWEST_BYTES = 2.5e6, FEWEST_BYTES_WITH_ADAPTER = 16e6;
+
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel, whose whole pairs of
 // k-steps on a round of 64 x 64 tiles count as a tile shape of their own.
-void spmm_tile_choice(int64_t n, int64_t m, int64_t K, int& bm, int& bn) {
+void spmm_tile_choice(int64_t n, int64_t m, int64_t K, bool adapter, int& bm, int& bn) {
     bm = bn = 0;
     if (!tile_kernel_fits(K)) return;
     best_tile_us(n, m, K, bm, bn);
-    if (bm == 64 && K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
+    if (bm != 64) return;
+    // (whether a product is split is decided by the estimate as it stands; not up to 64 rows, where half of the taller tile is nothing)
+    const double bytes = (double)K * (1.125 * (double)m + 2.0 * (double)n);
+    if (K > LONGEST_OF_64 && m > 64 && (K % 128 != 0 || bytes >= (adapter ? FEWEST_BYTES_WITH_ADAPTER : FEWEST_BYTES))) { bm = 128; bn = 64; }
+    else if (K % 128 != 0 && one_round_of_64(n, m)) bm = bn = 0;
 }
 
 // Tokens at the end of a batch that a pass of the small-batch kernel over the packed weight (5 TB/s, 6 us for its launch and
@@ -1712,7 +1724,7 @@ int64_t spmm_rest_tokens(int64_t n, int64_t m, int64_t K) {
 static hipError_t launch_tiles(const bf16_t* B, int64_t n, const bf16_t* A_vals, const uint8_t* A_meta, int64_t m, int64_t K,
                                const bf16_t* B2, const bf16_t* A2, int64_t K2, bf16_t* C, hipStream_t s) {
     int bm, bn;
-    spmm_tile_choice(n, m, K, bm, bn);
+    spmm_tile_choice(n, m, K, K2 != 0, bm, bn);
     if (bm == 0) {
         return launch_generic(B, n, A_vals, A_meta, m, K, B2, A2, K2, C, s);
     }

@@ -101,12 +101,15 @@ def test_contractions_by_their_multiple_of_64():
     assert sl.slope_spmm_fwd_plan(3000, 64, 4480)["product"] == GENERIC
 
 
-# half as many workgroups of 128 x 64 tiles lose 4 to 16 % there with an adapter, and without one where the weights come from HBM
-@pytest.mark.parametrize("b,d_out,d_in", [(300, 1024, 1792), (600, 512, 2304), (67, 5888, 2560), (200, 768, 1152), (1300, 512, 1792)])
-def test_long_contractions_on_a_round_of_64_x_64_tiles_stay_there(b, d_out, d_in):
-    for r in (0, 64, 160):
+# where the estimate takes a round of 64 x 64 tiles for more than 16 k-steps: 128 x 64 for an odd number of them, from 2.5 MB of operands on, with an
+# adapter from 16 MB on
+@pytest.mark.parametrize("b,d_out,d_in,plain,adapter", [
+    (200, 768, 1152, 64, 64), (112, 512, 1280, 64, 64), (300, 1024, 1792, 128, 64), (600, 512, 2304, 128, 64), (1300, 512, 1792, 128, 64),
+    (67, 5888, 2560, 128, 128), (43, 4160, 1728, 128, 128), (86, 256, 1344, 128, 128), (300, 64, 1344, 0, 0), (300, 1024, 1024, 64, 64)])
+def test_rows_of_a_tile_where_a_round_of_64_x_64_is_estimated(b, d_out, d_in, plain, adapter):
+    for r, rows in ((0, plain), (32, adapter), (160, adapter)):
         p = sl.slope_spmm_fwd_plan(b, d_in, d_out, r, False)
-        assert (p["product"], p["rows"], p["tokens"]) == (TILE, 64, 64)
+        assert (p["product"], p["rows"], p["tokens"]) == ((TILE, rows, 64) if rows else (GENERIC, 64, 64))
 
 
 @pytest.mark.parametrize("b,d_out,d_in", [(33, 16640, 1024), (64, 20480, 1024), (64, 20480, 1088), (64, 25344, 576)])
