@@ -314,7 +314,6 @@ inline int leftover_grid(const Leftover& left) { return (left.count + XCDS - 1) 
 // read of arguments before the first load (2 to 4 %: 447 tokens, 2168 x 128 4.46 us, 559, 3960 x 128 5.78 -> 6.04).
 struct WholeJob {};
 template <class Job> constexpr bool is_split = std::is_same<Job, SplitJob>::value;
-template <class Job> constexpr bool is_leftover = std::is_same<Job, Leftover>::value;
 
 // The workgroup's tile of a launch that is not split; false: none
 template <int BM, int BN>
@@ -680,8 +679,9 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
     // not fit into the last-level cache: lines that come from there rather than from HBM arrive soon enough anyway,
     // and the scalar loads then cost more than they gain (measured: 1-5 % faster with 16384 tokens of 9216 features
     // or more, 3-12 % slower with 8192 tokens or fewer).  It is a template parameter because a branch around the
-    // loads inside the k-loop cost what they gain.  Tiles outside whole chunks touch rows as if they were in one:
-    // harmless, and they are few.
+    // loads inside the k-loop cost what they gain.  Tiles outside whole chunks, up to 11 rows and 7 columns of them, touch rows as if they
+    // were in one, so that some rows of their panels are touched more than once and some not at all.  (us, without / with, grids with such strips: 16384 tokens,
+    // 4352 x 10240 748 / 695; 16640, 4608 x 9216 714 / 667; 12544, 4352 x 16384 893 / 884; 44 products of 4096 to 10496 rows 1 to 10 % faster.)
     uint32_t pf[2 * PF_ROWS];
 #pragma unroll
     for (int r = 0; r < 2 * PF_ROWS; ++r) pf[r] = 0;
@@ -840,8 +840,8 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_split_kernel(const bf16_t* 
 // 4352: of 940 cycles per k-step four of the wavefronts spent 390 at the barrier, waiting for the other four; 50 for loads).  us, operands
 // in the last-level cache and from HBM, eight that load and multiply / eight that multiply and four that load: 700 tokens, 4160 x 2112 on
 // 192 x 64 17.0 / 15.1 and 17.1 / 15.3; 1000, 4352 x 4352 on 192 x 96 32.4 / 29.1 and 37.5 / 35.4; 1500, 2040 x 4096 on 128 x 96 22.2 / 20.1 and
-// 22.3 / 20.3; 2048, 768 x 3072 on 128 x 64 13.2 / 12.5.  Two loaders: 2 to 7 % slower than four; four of higher priority: 0 to 4 %.  The
-// kernel above, whose loads are spread among its products, gains nothing by it.
+// 22.3 / 20.3; 2048, 768 x 3072 on 128 x 64 13.2 / 12.5.  Two loaders: 2 to 7 % slower than four; four of higher priority: 0 to 4 %.  In the
+// kernel above, whose loads are spread among its products, loaders beside eight that multiply gain nothing; see tile_mult for those beside four.
 // Four that multiply have a quarter of the tile each, a third fewer bytes from LDS in all than eight, and the workgroup starts faster (us, from
 // memory, eight / four and four loaders: 1000 tokens, 4352 x 4352 30.4 / 29.7; 1114, 704 x 1600 9.9 / 9.5; 875, 1536 x 768 6.8 / 6.6, without
 // loaders 6.7; 2000, 1920 x 2048 15.4 / 15.1; 424, 1792 x 3584 in slabs 14.4 / 14.2; 300, 9216 x 4096 20.9 / 21.5).

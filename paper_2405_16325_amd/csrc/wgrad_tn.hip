@@ -10,8 +10,8 @@
 //     far apart crowd the same L2 channels: the padded pitch is 2-3 % faster at b = 16384)
 // The product
 //     D[i, j] = sum_t X[t, i] * dY[t, j]
-// runs with the same machinery as the sparse kernels: 8 wavefronts, with one barrier per k-step or in two groups half a k-step
-// apart (dense_tn_sums), global -> LDS loads of full 128-byte lines, conflict-free LDS reads in MFMA order, v_mfma_f32_16x16x32_bf16.
+// runs with the same machinery as the sparse kernels: 8 wavefronts, all of which load and multiply or, up to 256 x 128, four multiply and
+// four load, with one barrier per k-step or in two groups half a k-step apart (dense_tn_sums), global -> LDS loads of full 128-byte lines, conflict-free LDS reads in MFMA order, v_mfma_f32_16x16x32_bf16.
 // D rows are d_in and D columns d_out, so a lane's four accumulators (column l%16, rows
 // 4*(l/16) .. +3) are exactly one group of four of W^R's row: the epilogue picks two of them with
 // the group's metadata nibble and stores one 4-byte pair of the packed gradient.
@@ -912,7 +912,7 @@ constexpr DenseTile DENSE_TILES[] = {{256, 256}, {256, 192}, {192, 192}, {256, 1
 
 // The kernels run at the rate their compute units pull operands from L2, 53 bytes per ns (up to a fifth more with few of them
 // at work, a little less on 192 x 192, a seventh less on 256 x 192, whose ring has two stages): a launch takes rounds
-// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 are 10 to 30 % faster
+// of 256 resident tiles, each its k-steps, 3 us, and up to 6 for the way of its results.  The tiles up to 256 x 128 are up to 15 % faster
 // than that by now; the order of the estimates, which is all that counts, has held.
 // `start` and `slower`: what a round of the 256 x 256 kernel takes beside its k-steps, and the factor on these.
 static double dense_tile_us(int c, int64_t m, int64_t n, int64_t ksteps, double start = 9.0, double slower = 1.0) {
