@@ -45,6 +45,40 @@
 
 namespace {
 
+template <int BMT> constexpr int FACTOR_PITCH = BMT * 2 + 32;  // pitch % 128 == 32: the four rows of a transposing read fall on distinct banks
+
+// Rows kc .. kc + kn - 1 of a k-major factor, BMT columns, to LDS between two barriers, by THREADS threads.  Pieces of 16 bytes per thread: a
+// compile-time count, so that all of a thread's global loads are in flight together (a loop of load, wait, LDS store per piece pays the L2 latency
+// once per piece).  (A macro: as a function, inlined or not, the kernels with eight pieces per thread spill.)
+#define STAGE_CHUNK                                                                                    \
+    {                                                                                                  \
+        constexpr int SEG = BMT / 8, PER = 128 * SEG / THREADS;                                        \
+        static_assert(128 * SEG % THREADS == 0, "whole pieces per thread");                            \
+        u32x4 piece[PER];                                                                              \
+        _Pragma("unroll") for (int u = 0; u < PER; ++u) {                                              \
+            const int idx = tid + u * THREADS, k = idx / SEG, col = tile_f0 + 8 * (idx % SEG);         \
+            piece[u] = (u32x4){0u, 0u, 0u, 0u};                                                        \
+            if (k < kn && col < m) piece[u] = *(const u32x4*)(A2 + (size_t)(kc + k) * m + col);        \
+        }                                                                                              \
+        __syncthreads();                                      /* the rings are drained / the last chunk is consumed */ \
+        _Pragma("unroll") for (int u = 0; u < PER; ++u) {                                              \
+            const int idx = tid + u * THREADS;                                                         \
+            *(u32x4*)(smem + (idx / SEG) * FACTOR_PITCH<BMT> + (idx % SEG) * 16) = piece[u];           \
+        }                                                                                              \
+    }
+
+// The factor's chunks by the wavefronts that only load, THREADS of them: the first is requested while the others multiply the last k-steps, the
+// next ones while they multiply a chunk.  tid counts from the first of these wavefronts.  (us, from memory, eight wavefronts that stage / four that
+// multiply / four that load: 2132 tokens, 3584 x 512, rank 160 on 256 x 128 23.0 / 23.5 / 22.6; 1239, 2816 x 256, rank 256 on 192 x 128 16.5 / 17.2 / 16.3.)
+template <int BMT, int THREADS>
+__device__ __forceinline__ void stage_factor(const bf16_t* __restrict__ A2, int K2, int m, uint8_t* smem, int tile_f0, int tid) {
+    for (int kc = 0; kc < -K2; kc += 128) {
+        const int kn = -K2 - kc < 128 ? -K2 - kc : 128;
+        STAGE_CHUNK
+        __syncthreads();
+    }
+}
+
 // Tail shared by the tile kernels, for one wavefront whose acc[i][j] is the 16 x 16 fragment at
 // features f0 + 16 i, tokens t0 + 16 j.
 //  - dense K-extension: C += B2 * A2^T with v_mfma_f32_16x16x32_bf16.  K2 > 0: A2 is [m][K2],
@@ -52,32 +86,25 @@ namespace {
 //    k = 8*(l/16) .. +7).  K2 < 0: A2 is k-major, [-K2][m] (the adapter factor R as stored): the
 //    workgroup stages the tile's BMT columns of 128 rows at a time in LDS (the rings are idle by
 //    then) and the wavefronts read their fragments back with the transposing LDS read; every
-//    thread of the workgroup must make the call (it contains barriers);
+//    thread of the workgroup must make the call (it contains barriers) or, STAGED, all others that of stage_factor;
 //  - epilogue: store_rows. BNT = tokens of the workgroup's tile, tile_t0 its first token; every thread must make the call.
 //  - with a slab buffer (a split over k, see launch_spmm_slabs): the fp32 accumulators go to
 //    partial[token][feature] instead, 16 bytes per lane, and a reduction kernel finishes.
-template <int MF, int NF, int BMT, int BNT, int THREADS>
+template <int MF, int NF, int BMT, int BNT, int THREADS, bool STAGED = false>
 __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, int t0, int m, int n, int l16, int lq,
                                                  const bf16_t* __restrict__ B2, const bf16_t* __restrict__ A2,
                                                  int K2, bf16_t* __restrict__ C, uint8_t* smem, int tile_f0,
                                                  int tile_t0, float* __restrict__ partial = nullptr) {
     if (K2 < 0) {
-        constexpr int PITCH = BMT * 2 + 32;                   // pitch % 128 == 32: the four rows of a transposing
-                                                              // read fall on distinct banks
-        constexpr int SEG = BMT / 8;                          // 16-byte pieces per staged row
+        constexpr int PITCH = FACTOR_PITCH<BMT>;
         const int KR = -K2, tid = (int)threadIdx.x;
         const bf16_t* b_row[NF];
 #pragma unroll
         for (int j = 0; j < NF; ++j) b_row[j] = B2 + (size_t)wrap_row(t0 + j * 16 + l16, n) * KR + lq * 8;
         // lane (s = l16, q = lq) points at staged row 8 q + 4 h + s / 4, column 4 (s % 4) of a fragment
         const uint8_t* tr = smem + (8 * lq + (l16 >> 2)) * PITCH + 2 * (f0 - tile_f0 + 4 * (l16 & 3));
-        // pieces of the staged chunk per thread: a compile-time count, so that all of a thread's global loads are
-        // in flight together (a loop of load, wait, LDS store per piece pays the L2 latency once per piece)
-        // (at most twelve: the accumulators are most of the registers of a wavefront with a quarter of a 256 x 128 tile, which would
-        // spill; us on 192 x 128, in two rounds of six / one: 2078 tokens, 2560 x 256, rank 256 19.5 / 19.1)
-        constexpr int PER = 128 * SEG / THREADS, ROUNDS = (PER + 11) / 12, EACH = PER / ROUNDS;
-        constexpr int FIRST = THREADS < 512 && MF * NF > 24 ? 0 : 2;   // steps whose token-side fragments are requested before the pieces
-        static_assert(128 * SEG % THREADS == 0 && PER % ROUNDS == 0, "whole pieces per thread and round");
+        // steps whose token-side fragments are requested before the pieces of the factor; where stage_factor brings those, all
+        constexpr int FIRST = STAGED ? 4 : 2;
         for (int kc = 0; kc < KR; kc += 128) {
             const int kn = KR - kc < 128 ? KR - kc : 128;     // a multiple of 32
             // the token-side fragments of the whole chunk come straight from global memory: requested first
@@ -87,22 +114,8 @@ __device__ __forceinline__ void extend_and_store(f32x4 (&acc)[MF][NF], int f0, i
             for (int st = 0; st < FIRST; ++st)
 #pragma unroll
                 for (int j = 0; j < NF; ++j) b2[st][j].u = *(const u32x4*)(b_row[j] + kc + (32 * st < kn ? 32 * st : 0));
-#pragma unroll
-            for (int round = 0; round < ROUNDS; ++round) {
-                u32x4 piece[EACH];
-#pragma unroll
-                for (int u = 0; u < EACH; ++u) {
-                    const int idx = tid + (round * EACH + u) * THREADS, k = idx / SEG, col = tile_f0 + 8 * (idx % SEG);
-                    piece[u] = (u32x4){0u, 0u, 0u, 0u};
-                    if (k < kn && col < m) piece[u] = *(const u32x4*)(A2 + (size_t)(kc + k) * m + col);
-                }
-                if (round == 0) __syncthreads();              // the rings are drained / the last chunk is consumed
-#pragma unroll
-                for (int u = 0; u < EACH; ++u) {
-                    const int idx = tid + (round * EACH + u) * THREADS;
-                    *(u32x4*)(smem + (idx / SEG) * PITCH + (idx % SEG) * 16) = piece[u];
-                }
-            }
+            if (STAGED) __syncthreads();                      // (the two of stage_factor)
+            else STAGE_CHUNK
 #pragma unroll
             for (int st = FIRST; st < 4; ++st)                // in the registers the staged pieces have left
 #pragma unroll
@@ -487,6 +500,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
                 LAST_STEP(2)
                 step(ks0 + 3, std::integral_constant<int, 3>{});
             }
+            if (K2 < 0 && slab == extension_slab) stage_factor<BM, 64 * LOADERS>(A2, K2, m, smem, m0, t - 64 * MULT);
             return;
         }
     }
@@ -588,7 +602,7 @@ __global__ void __launch_bounds__(SPMM_THREADS) spmm_kernel(const bf16_t* __rest
     int te = threadIdx.x;                                    // (the lane's coordinates again rather than kept across the loop)
     if (!OWN) asm volatile("" : "+v"(te));
     const int we = __builtin_amdgcn_readfirstlane(te >> 6);
-    extend_and_store<MF, NF, BM, BN, 64 * MULT>(acc, m0 + (we & 1) * MF * 16, n0 + (we >> 1) * NF * 16, m, n, te & 15, te >> 4 & 3, B2, A2,
+    extend_and_store<MF, NF, BM, BN, 64 * MULT, !OWN>(acc, m0 + (we & 1) * MF * 16, n0 + (we >> 1) * NF * 16, m, n, te & 15, te >> 4 & 3, B2, A2,
                                                 slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
 }
 
@@ -996,6 +1010,7 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
                 pair(p + 3, std::integral_constant<int, 3>{});
             }
         }
+        if (K2 < 0 && slab == extension_slab) stage_factor<BM, 64 * LOADERS>(A2, K2, m, smem, m0, t - 64 * RING_MULT);
         return;
     }
 
@@ -1081,7 +1096,7 @@ __global__ void __launch_bounds__(RING_THREADS) spmm_ring_kernel(const bf16_t* _
         }
     }
     static_assert(BN * (BM * 2 + 16) <= S::TOTAL && 128 * (BM * 2 + 32) <= S::TOTAL, "the staged output tile and factor fit in the ring");
-    extend_and_store<MF, NF, BM, BN, 64 * RING_MULT>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
+    extend_and_store<MF, NF, BM, BN, 64 * RING_MULT, true>(acc, m0 + wm * MF * 16, n0 + wn * NF * 16, m, n, l16, lq, B2, A2,
                                                    slab == extension_slab ? K2 : 0, C, smem, m0, n0, sums);
 }
 
