@@ -49,7 +49,7 @@ template <int BMT> constexpr int FACTOR_PITCH = BMT * 2 + 32;  // pitch % 128 ==
 
 // Rows kc .. kc + kn - 1 of a k-major factor, BMT columns, to LDS between two barriers, by THREADS threads.  Pieces of 16 bytes per thread: a
 // compile-time count, so that all of a thread's global loads are in flight together (a loop of load, wait, LDS store per piece pays the L2 latency
-// once per piece).  (A macro: as a function, inlined or not, the kernels with eight pieces per thread spill.)
+// once per piece).  (A macro: as an inlined function the kernels with eight pieces per thread spill.)
 #define STAGE_CHUNK                                                                                    \
     {                                                                                                  \
         constexpr int SEG = BMT / 8, PER = 128 * SEG / THREADS;                                        \
@@ -69,7 +69,7 @@ template <int BMT> constexpr int FACTOR_PITCH = BMT * 2 + 32;  // pitch % 128 ==
 
 // The factor's chunks by the wavefronts that only load, THREADS of them: the first is requested while the others multiply the last k-steps, the
 // next ones while they multiply a chunk.  tid counts from the first of these wavefronts.  (us, from memory, eight wavefronts that stage / four that
-// multiply / four that load: 2132 tokens, 3584 x 512, rank 160 on 256 x 128 23.0 / 23.5 / 22.6; 1239, 2816 x 256, rank 256 on 192 x 128 16.5 / 17.2 / 16.3.)
+// multiply / four that load: 2132 tokens, 3584 x 512, rank 160 on 256 x 128 23.0 / 23.5 / 22.6; 1239, 2816 x 256, rank 256 on 128 x 128 16.5 / 17.2 / 16.3.)
 template <int BMT, int THREADS>
 __device__ __forceinline__ void stage_factor(const bf16_t* __restrict__ A2, int K2, int m, uint8_t* smem, int tile_f0, int tid) {
     for (int kc = 0; kc < -K2; kc += 128) {
