@@ -1701,10 +1701,10 @@ int spmm_generic_edge(int64_t n, int64_t m) { return tiles_of_64(n, m) <= 2 * RE
 //  - on operands from the last-level cache, more so the longer they are, while from HBM it is 5 % slower without an adapter, 7 to 10 % with one: so from the
 //    bytes of operands on where it gains more than it loses.  us, 64 x 64 / 128 x 64 cached and from HBM: 112 tokens, 512 x 1280 10.8 / 11.2 and
 //    9.2 / 10.3; 231, 1272 x 2432 15.0 / 14.1 and 14.0 / 15.5; 1214, 424 x 2432 16.1 / 14.1 and 14.7 / 15.4; 1019, 576 x 3328 20.4 / 16.8 and 18.9
-//    / 19.6.  Mean over 150 products without an adapter below / above the line: 0 / 11 % faster cached, 8 / 5 % slower from HBM; over 179 with one 0
-//    / 7 % faster cached, 9 / 7 % slower from HBM.
+//    / 19.6; with an adapter 68, 4864 x 2560, rank 128, a call, cached 20.0 / 19.5.  Mean over 150 products without an adapter below / above the line: 0 / 11 %
+//    faster cached, 8 / 5 % slower from HBM; over 179 with one 1 % slower / 3 % faster cached, 9 / 8 % slower from HBM.
 constexpr int64_t LONGEST_OF_64 = 16 * 64;
-constexpr double FEWEST_BYTES = 2.5e6, FEWEST_BYTES_WITH_ADAPTER = 16e6;
+constexpr double FEWEST_BYTES = 2.5e6, FEWEST_BYTES_WITH_ADAPTER = 5e6;
 
 // Tile of the product for n tokens, m sparse rows, contraction K: bm = bn = 0 means the generic kernel, whose whole pairs of
 // k-steps on a round of 64 x 64 tiles count as a tile shape of their own.

@@ -102,9 +102,9 @@ def test_contractions_by_their_multiple_of_64():
 
 
 # where the estimate takes a round of 64 x 64 tiles for more than 16 k-steps: 128 x 64 for an odd number of them, from 2.5 MB of operands on, with an
-# adapter from 16 MB on
+# adapter from 5 MB on
 @pytest.mark.parametrize("b,d_out,d_in,plain,adapter", [
-    (200, 768, 1152, 64, 64), (112, 512, 1280, 64, 64), (300, 1024, 1792, 128, 64), (600, 512, 2304, 128, 64), (1300, 512, 1792, 128, 64),
+    (200, 768, 1152, 64, 64), (112, 512, 1280, 64, 64), (300, 1024, 1792, 128, 64), (600, 512, 2304, 128, 64), (1300, 512, 1792, 128, 128),
     (67, 5888, 2560, 128, 128), (43, 4160, 1728, 128, 128), (86, 256, 1344, 128, 128), (300, 64, 1344, 0, 0), (300, 1024, 1024, 64, 64)])
 def test_rows_of_a_tile_where_a_round_of_64_x_64_is_estimated(b, d_out, d_in, plain, adapter):
     for r, rows in ((0, plain), (32, adapter), (160, adapter)):
